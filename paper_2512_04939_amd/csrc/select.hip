@@ -1,8 +1,8 @@
 // Token partition (Sec. 3.4 "GA Token Partitioning"): one workgroup per frame keeps the
-// frame's scores in LDS, picks one dst token per grid cell (lowest score), the GA tokens
-// (highest scores among the rest) by rank counting, and writes the ascending index lists
-// with a block-wide prefix sum.  All per-frame counts are closed-form, so every frame
-// knows its output offsets without any cross-frame communication.
+// frame's scores in LDS, picks one dst token per grid cell (lowest score), finds the score of
+// the last GA token (the n_ga-th highest among the rest) by radix selection, and writes the
+// ascending index lists with ballot prefix sums.  All per-frame counts are closed-form, so every
+// frame knows its output offsets without any cross-frame communication.
 #include "common.h"
 #include "internal.h"
 
@@ -18,32 +18,42 @@ __device__ __forceinline__ uint32_t order_key(float s) {
 struct Tri {
   int k, d, s;
 };
-__device__ __forceinline__ Tri operator+(Tri a, Tri b) { return {a.k + b.k, a.d + b.d, a.s + b.s}; }
 
-__global__ __launch_bounds__(256) void k_select(
+// What bounds this kernel is the latency of one frame: a frame is a few KB, and short sequences
+// have fewer frames than the chip has CUs.  Hence 16 waves per frame; the GA threshold by four
+// 8-bit histogram passes over the keys (P reads each; counting every token's rank against all
+// others read P^2 keys from LDS: 221 us per call for 32 frames of 37 x 37 patches, now about 10);
+// and index lists written in token order, 64 tokens per wave and step, with ballots
+// giving the positions (coalesced stores, no barrier between steps).
+constexpr int kSelThreads = 1024;
+constexpr int kSelWaves = kSelThreads / 64;
+
+__global__ __launch_bounds__(kSelThreads) void k_select(
     const float *__restrict__ score, int H, int W, int S, int cell, int n_ga, int n_dst_pf,
     int n_src_pf, uint8_t *__restrict__ role_out, int32_t *__restrict__ kept_idx,
     int32_t *__restrict__ dst_idx, int32_t *__restrict__ src_idx,
     int32_t *__restrict__ anchor_of, int32_t *__restrict__ slot_of) {
-  extern __shared__ uint32_t smem[];
+  extern __shared__ uint32_t key[];           // [P] order keys; 0 marks a dst token
+  __shared__ uint32_t hist[256];
+  __shared__ uint32_t s_prefix, s_need;       // radix selection: digits fixed so far, rank left inside them
+  __shared__ int eq_cnt[kSelWaves];
+  __shared__ Tri wtot[kSelWaves];
   const int P = H * W, T = P + S, f = blockIdx.x;
-  uint32_t *key = smem;                       // [P] order keys
-  uint32_t *cand = smem + P;                  // [P] key of non-dst tokens, 0 for dst tokens
-  uint8_t *role = (uint8_t *)(smem + 2 * P);  // [P]
-  __shared__ Tri wtot[4];
-  const int tid = threadIdx.x;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const bool all_dst = (f == 0) || (n_src_pf == 0);
+  const uint64_t below = lane == 0 ? 0ull : (~0ull >> (64 - lane));   // the lanes before this one
 
-  for (int t = tid; t < P; t += blockDim.x) {
-    uint32_t k = order_key(score[(size_t)f * P + t]);
-    key[t] = k;
-    cand[t] = k;
-    role[t] = all_dst ? LV_ROLE_DST : LV_ROLE_SRC;
+  for (int t = tid; t < P; t += kSelThreads) key[t] = all_dst ? 0u : order_key(score[(size_t)f * P + t]);
+  if (tid == 0) {
+    s_prefix = 0u;
+    s_need = (uint32_t)n_ga;
   }
   __syncthreads();
   if (!all_dst) {
+    // cells are disjoint: the thread that owns one is the only reader and writer of its keys
     const int ncw = (W + cell - 1) / cell, nch = (H + cell - 1) / cell;
-    for (int c = tid; c < nch * ncw; c += blockDim.x) {
+    for (int c = tid; c < nch * ncw; c += kSelThreads) {
       const int ci = (c / ncw) * cell, cj = (c % ncw) * cell;
       uint32_t best = 0xffffffffu;
       int bt = -1;
@@ -55,73 +65,133 @@ __global__ __launch_bounds__(256) void k_select(
             bt = i * W + j;
           }
         }
-      role[bt] = LV_ROLE_DST;
-      cand[bt] = 0u;
+      key[bt] = 0u;
     }
     __syncthreads();
-    if (n_ga > 0) {
-      for (int t = tid; t < P; t += blockDim.x) {
-        const uint32_t k = cand[t];
-        if (k == 0u) continue;
-        int rank = 0;
-        for (int u = 0; u < P; ++u) {
-          uint32_t ku = cand[u];
-          rank += (ku > k) || (ku == k && u < t);
-        }
-        if (rank < n_ga) role[t] = LV_ROLE_PROTECTED;
+  }
+  // The n_ga-th largest key of the tokens that are left (there are at least n_ga; keys of
+  // tokens are never 0): digit by digit from the top, among the keys that share the digits so far.
+  const bool pick = !all_dst && n_ga > 0;
+  if (pick) {
+    for (int shift = 24; shift >= 0; shift -= 8) {
+      if (tid < 256) hist[tid] = 0u;
+      __syncthreads();
+      const uint32_t prefix = s_prefix, need = s_need;
+      const uint32_t mask = shift == 24 ? 0u : ~0u << (shift + 8);
+      for (int t = tid; t < P; t += kSelThreads) {
+        const uint32_t k = key[t];
+        if (k != 0u && (k & mask) == prefix) atomicAdd(&hist[(k >> shift) & 255u], 1u);
       }
-    }
-    __syncthreads();
-  }
-
-  // prefix sums of (kept, dst, src) flags over the frame's T tokens, chunk per thread
-  const int per = (T + blockDim.x - 1) / blockDim.x;
-  const int t0 = min(tid * per, T), t1 = min(t0 + per, T);
-  Tri mine = {0, 0, 0};
-  for (int t = t0; t < t1; ++t) {
-    int r = t < S ? LV_ROLE_PROTECTED : role[t - S];
-    mine.k += r != LV_ROLE_SRC;
-    mine.d += r == LV_ROLE_DST;
-    mine.s += r == LV_ROLE_SRC;
-  }
-  Tri inc = mine;
-  const int lane = tid & 63, wave = tid >> 6;
+      __syncthreads();
+      if (wave == 0) {   // lane l: bins 255 - 4l down to 252 - 4l
+        uint32_t h[4], sum = 0u;
 #pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    Tri n = {__shfl_up(inc.k, o, 64), __shfl_up(inc.d, o, 64), __shfl_up(inc.s, o, 64)};
-    if (lane >= o) inc = inc + n;
+        for (int i = 0; i < 4; ++i) {
+          h[i] = hist[255 - 4 * lane - i];
+          sum += h[i];
+        }
+        uint32_t inc = sum;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+          const uint32_t up = __shfl_up(inc, o, 64);
+          if (lane >= o) inc += up;
+        }
+        uint32_t above = inc - sum;   // keys in higher bins
+        if (above < need && need <= inc) {   // exactly one lane
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            if (above < need && need <= above + h[i]) {
+              s_prefix = prefix | ((uint32_t)(255 - 4 * lane - i) << shift);
+              s_need = need - above;
+            }
+            above += h[i];
+          }
+        }
+      }
+      __syncthreads();
+    }
   }
-  if (lane == 63) wtot[wave] = inc;
-  __syncthreads();
-  Tri base = {0, 0, 0};
-  for (int w = 0; w < wave; ++w) base = base + wtot[w];
-  Tri pos = {base.k + inc.k - mine.k, base.d + inc.d - mine.d, base.s + inc.s - mine.s};
+  const uint32_t last = pick ? s_prefix : 0xffffffffu;   // key of the last GA token; of those equal to it ...
+  const int n_eq = pick ? (int)s_need : 0;               // ... the n_eq lowest token numbers are GA tokens
 
+  // Each wave owns a run of whole 64-token steps of the frame's T tokens.
+  const int steps = (T + 63) / 64, per = (steps + kSelWaves - 1) / kSelWaves;
+  const int t0 = wave * per * 64, t1 = min(t0 + per * 64, T);
+  int eq = 0;
+  for (int tb = t0; tb < t1; tb += 64) {
+    const int t = tb + lane - S;
+    eq += __popcll(__builtin_amdgcn_ballot_w64(tb + lane < t1 && t >= 0 && key[t] == last));
+  }
+  if (lane == 0) eq_cnt[wave] = eq;
+  __syncthreads();
+  int eq_before = 0;
+  for (int w = 0; w < wave; ++w) eq_before += eq_cnt[w];
+  // role of this lane's token of the step that starts at tb (seen: equal keys before the step)
+  auto role_at = [&](int tb, int &seen) {
+    const int t = tb + lane - S;
+    const bool on = tb + lane < t1;
+    const uint32_t k = on && t >= 0 ? key[t] : 0u;
+    const uint64_t eqm = __builtin_amdgcn_ballot_w64(on && t >= 0 && k == last);
+    int r = LV_ROLE_PROTECTED;
+    if (t >= 0) {
+      const bool ga = k > last || (k == last && seen + (int)__popcll(eqm & below) < n_eq);
+      r = k == 0u ? LV_ROLE_DST : ga ? LV_ROLE_PROTECTED : LV_ROLE_SRC;
+    }
+    seen += __popcll(eqm);
+    return on ? r : -1;
+  };
+  Tri mine = {0, 0, 0};
+  int seen = eq_before;
+  for (int tb = t0; tb < t1; tb += 64) {
+    const int r = role_at(tb, seen);
+    const int d = __popcll(__builtin_amdgcn_ballot_w64(r == LV_ROLE_DST));
+    const int sn = __popcll(__builtin_amdgcn_ballot_w64(r == LV_ROLE_SRC));
+    mine.d += d;
+    mine.s += sn;
+    mine.k += min(64, t1 - tb) - sn;
+  }
+  if (lane == 0) wtot[wave] = mine;
+  __syncthreads();
+  Tri pos = {0, 0, 0};
+  for (int w = 0; w < wave; ++w) {
+    pos.k += wtot[w].k;
+    pos.d += wtot[w].d;
+    pos.s += wtot[w].s;
+  }
   const int K = n_dst_pf + n_ga;
   const int64_t kb = f == 0 ? 0 : (int64_t)T + (int64_t)(f - 1) * (S + K);
   const int64_t db = f == 0 ? 0 : (int64_t)P + (int64_t)(f - 1) * n_dst_pf;
   const int64_t sb = f == 0 ? 0 : (int64_t)(f - 1) * n_src_pf;
-  for (int t = t0; t < t1; ++t) {
-    const int r = t < S ? LV_ROLE_PROTECTED : role[t - S];
-    const int64_t g = (int64_t)f * T + t;
-    role_out[g] = (uint8_t)r;
-    if (r != LV_ROLE_SRC) {
-      kept_idx[kb + pos.k] = (int32_t)g;
-      slot_of[g] = (int32_t)(kb + pos.k);
-      anchor_of[g] = (int32_t)g;
-      ++pos.k;
+  seen = eq_before;
+  for (int tb = t0; tb < t1; tb += 64) {
+    const int r = role_at(tb, seen);
+    const uint64_t dm = __builtin_amdgcn_ballot_w64(r == LV_ROLE_DST), sm = __builtin_amdgcn_ballot_w64(r == LV_ROLE_SRC);
+    const uint64_t km = __builtin_amdgcn_ballot_w64(r >= 0) & ~sm;
+    const int64_t g = (int64_t)f * T + tb + lane;
+    if (r >= 0) {
+      role_out[g] = (uint8_t)r;
+      if (r == LV_ROLE_SRC) {
+        src_idx[sb + pos.s + __popcll(sm & below)] = (int32_t)g;
+      } else {
+        const int64_t slot = kb + pos.k + __popcll(km & below);
+        kept_idx[slot] = (int32_t)g;
+        slot_of[g] = (int32_t)slot;
+        anchor_of[g] = (int32_t)g;
+        if (r == LV_ROLE_DST) dst_idx[db + pos.d + __popcll(dm & below)] = (int32_t)g;
+      }
     }
-    if (r == LV_ROLE_DST) dst_idx[db + pos.d++] = (int32_t)g;
-    if (r == LV_ROLE_SRC) src_idx[sb + pos.s++] = (int32_t)g;
+    pos.k += __popcll(km);
+    pos.d += __popcll(dm);
+    pos.s += __popcll(sm);
   }
 }
 
 int launch_select(const float *score, const Dims &d, const litevggt_plan_t &pl,
                   const litevggt_index &ix, hipStream_t st) {
-  size_t lds = (size_t)d.P * 9;
-  lds = align_up(lds, 16);
-  if (lds > 60 * 1024) return LV_ERR_SHAPE;
-  hipLaunchKernelGGL(k_select, dim3((unsigned)d.F), dim3(256), lds, st, score, d.H, d.W, d.S,
+  // the limit on P of the earlier layout (9 bytes of LDS per patch within 60 KB) is kept
+  if (align_up((size_t)d.P * 9, 16) > 60 * 1024) return LV_ERR_SHAPE;
+  const size_t lds = align_up((size_t)d.P * sizeof(uint32_t), 16);
+  hipLaunchKernelGGL(k_select, dim3((unsigned)d.F), dim3(kSelThreads), lds, st, score, d.H, d.W, d.S,
                      pl.cell, pl.n_ga_per_frame, pl.n_dst_per_frame, pl.n_src_per_frame, ix.role,
                      ix.kept_idx, ix.dst_idx, ix.src_idx, ix.anchor_of, ix.slot_of);
   LV_HIP_CHECK_LAUNCH();
