@@ -103,42 +103,95 @@ int launch_pack_rows(const uint16_t *x, int64_t n, int64_t n_pad, int C, void *p
 // finished tile into its running (best, second best) pair without cross-lane traffic.
 //
 // The kernel is persistent: one workgroup per CU.  The workgroups the hardware deals to one
-// XCD (block index mod 8) form a team of 8 src tiles x 4 sweeps; the team takes every 8th
-// super-row of 8 src tiles, and in it workgroup (src tile, sweep dl) visits the dst tiles dl,
-// dl + 4, dl + 8, ...  The team moves from one dst tile to the next together (a bounded,
-// advisory wait on a counter in the XCD's L2), so its 32 workgroups ask for the same 8 src
-// and 4 dst tiles within a few microseconds of each other and 4 of 5 requests hit that L2.
-// The four partial results of a src row are merged by k_match_finish.
+// XCD (block index mod 8) form a team of (src tiles) x (sweeps), 8 x 4 where nothing speaks
+// against it; in every full round the team takes its own super-row of src tiles, and in it
+// workgroup (src tile, sweep dl) visits the dst tiles dl, dl + n, dl + 2n, ... of n sweeps.  The
+// team moves from one dst tile to the next together (a bounded, advisory wait on a counter in the
+// XCD's L2), so its workgroups ask for the same src and dst tiles within a few microseconds of
+// each other and 4 of 5 requests hit that L2.  The src tiles that do not fill a round of all the
+// teams are shared out in a last round over the whole chip, as many sweeps per src tile as there
+// are workgroups for it (MatchSched: which shape).  The partial results of a src row, one per
+// sweep, are merged by k_match_finish.
 // ---------------------------------------------------------------------------------
 constexpr int kGTile = 256;          // src and dst rows per workgroup tile
 constexpr int kGStages = 4;          // LDS ring depth
 constexpr int kGStageU4 = 2 * 2 * 8 * 64;   // u32x4 per stage: [src|dst][2 k-steps][8 fragments][64 lanes]
 constexpr int kTeamSpin = 512;       // polls of the team counter before a workgroup goes on alone
 constexpr int kInvBufs = 8;          // per-wave LDS buffers of 64 inverse dst norms
-constexpr int kGLanes = 4;           // dst tiles are dealt to this many workgroups per src tile (<= kMaxSweeps of k_match_finish)
+constexpr int kTeam = 32;            // workgroups per team: the CUs of an XCD
+constexpr int kMaxSweeps = 64;       // sweeps of one src tile, at most
+
+// How the src tiles are dealt out.  Rounds 0 .. n_full - 1: team x takes the sr src tiles from
+// (round * 8 + x) * sr on, each with n_sweeps sweeps.  Then the n_rest tiles from `full` on, each
+// with rest_sweeps sweeps.  The partial results of a row lie n_sweeps * full tiles of rows, sweep
+// by sweep, then rest_sweeps * n_rest tiles.
+struct MatchSched {
+  int n_sweeps, sr, n_full, rest_sweeps, n_rest, full;
+};
+inline int div_up(int a, int b) { return (a + b - 1) / b; }
+
+// A tile step (256 x 256 rows, all channels) takes the same time on every CU, so the time of a
+// shape is its number of steps: rounds * ceil(dst tiles / sweeps).  With 8 x 4 teams alone a last
+// round with one super-row in it costs as much as a full one, and a dst tile count that is no
+// multiple of 4 idles a part of the team: 32 frames of 37 x 37 patches (150 x 18 tiles) took 15
+// steps for 10.5 steps' worth of tiles and 542 us, now 11; 100 frames of 28 x 37 patches under
+// the fixed rule (258 x 107) 135 for 107.8 and 4090 us, now 109.  Among shapes of nearly equal
+// step counts the one that asks its L2 for the fewest distinct tiles wins: 8 x 4 and 4 x 8 ask
+// for 12, and at 1000 frames 8 x 4 was 1 % faster than 16 x 2 and 3 % faster than 4 x 8.
+static MatchSched match_sched(int src_tiles, int dst_tiles, int team) {
+  MatchSched best = {1, 1, 0, 1, 0, 0};
+  double best_cost = 1e300;
+  for (int l = 1; l <= team && l <= dst_tiles && l <= kMaxSweeps; ++l) {
+    const int sr = team / l, per_round = sr * kXcd;
+    const double share = 1.0 + 0.04 * ((sr + l) / 12.0 - 1.0) + (l == 4 ? 0.0 : 0.01);
+    const int most = src_tiles / per_round;
+    for (int f = most; f >= 0 && f >= most - 1; --f) {
+      const int rest = src_tiles - f * per_round;
+      if (rest > team * kXcd) break;
+      int rs = rest ? team * kXcd / rest : 1;
+      if (rs > dst_tiles) rs = dst_tiles;
+      if (rs > kMaxSweeps) rs = kMaxSweeps;
+      // + a few percent of a step per round for filling the pipeline and writing the result
+      const double cost = f * (div_up(dst_tiles, l) * share + 0.1) + (rest ? div_up(dst_tiles, rs) * 1.03 + 0.1 : 0.0);
+      if (cost < best_cost) {
+        best_cost = cost;
+        best = {l, sr, f, rs, rest, f * per_round};
+      }
+    }
+  }
+  return best;
+}
+static size_t sched_partials(const MatchSched &s) {   // tiles of 256 partial results
+  return (size_t)s.n_sweeps * s.full + (size_t)s.rest_sweeps * s.n_rest;
+}
 
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_match_sim(
     const u32x4 *__restrict__ srcp, const u32x4 *__restrict__ dstp, const float *__restrict__ invd,
-    int n_dst, int n_src_tiles, int n_dst_tiles, int n_lanes, int KS, int n_src_pad,
-    int team_size, int spin_budget, uint32_t *team_ctr, Top2 *__restrict__ top2p) {
+    int n_dst, int n_dst_tiles, MatchSched sched, int KS, int spin_budget, uint32_t *team_ctr,
+    Top2 *__restrict__ top2p) {
   extern __shared__ u32x4 ring[];    // kGStages stages
   const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wd = wave & 3, wsrc = wave >> 2;
   const int team = blockIdx.x & (kXcd - 1), rank = blockIdx.x >> 3;
-  if (rank >= team_size) return;     // not a member of its team: nothing to do
-  const int dl = rank % n_lanes, sti = rank / n_lanes, sr_tiles = team_size / n_lanes;
-  const int n_super = (n_src_tiles + sr_tiles - 1) / sr_tiles;
+  const int per_team = gridDim.x >> 3, team_size = sched.n_sweeps * sched.sr;
+  const int SPT = KS >> 1;           // stages per tile
+  uint32_t *ctr = team_ctr + team * 32;      // one counter per team, 128 bytes apart
+  uint32_t rounds = 0;                       // sweep steps of the rounds the team has finished
+  const int n_rounds = sched.n_full + (sched.n_rest ? 1 : 0);
+
+  for (int rd = 0; rd < n_rounds; ++rd) {
+  const bool in_team = rd < sched.n_full;    // else the last round, over the whole chip
+  // chip-wide the workgroups of an XCD are neighbours: few src tiles with many sweeps each
+  const int id = in_team ? rank : team * per_team + rank;
+  const int n_lanes = in_team ? sched.n_sweeps : sched.rest_sweeps;
+  const int dl = id % n_lanes, sti = id / n_lanes;
+  const int st = in_team ? (rd * kXcd + team) * sched.sr + sti : sched.full + sti;
   const int nt_max = (n_dst_tiles + n_lanes - 1) / n_lanes;
   const int nt = dl < n_dst_tiles ? (n_dst_tiles - dl + n_lanes - 1) / n_lanes : 0;   // my dst tiles
-  const int SPT = KS >> 1;           // stages per tile
   const int total = nt * SPT;
-  uint32_t *ctr = team_ctr + team * 32;      // one counter per team, 128 bytes apart
-  uint32_t rounds = 0;                       // sweep steps of the super-rows the team has finished
-
-  for (int sr = team; sr < n_super; sr += kXcd) {   // super-row: sr_tiles consecutive src tiles
-  const int st = sr * sr_tiles + sti;
-  const bool active = st < n_src_tiles && total > 0;
+  const bool member = sti < (in_team ? sched.sr : sched.n_rest);
+  const bool active = member && total > 0;
   Top2 best[4];
 #pragma unroll
   for (int b = 0; b < 4; ++b) best[b] = Top2{-INFINITY, -1, -INFINITY, -1};
@@ -249,7 +302,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     float *share = (float *)(ring + (size_t)kGStages * kGStageU4) + 8 * kInvBufs * 64;   // [parity][wsrc][b][wd][column]
     float thr[4] = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
 #pragma unroll
-    for (int b = 0; b < 4; ++b) {   // before the first barrier of the super-row
+    for (int b = 0; b < 4; ++b) {   // before the first barrier of the round
       share[((wsrc * 4 + b) * 4 + wd) * 32 + (lane & 31)] = -INFINITY;
       share[1024 + ((wsrc * 4 + b) * 4 + wd) * 32 + (lane & 31)] = -INFINITY;
     }
@@ -340,12 +393,12 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         // start the next one together, so that what one of them fetches is still in their
         // XCD's L2 when the others ask for it.  The wait is advisory: it is bounded, and no
         // result depends on it.
-        if (tid == 0) __hip_atomic_fetch_add(ctr, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (in_team && tid == 0) __hip_atomic_fetch_add(ctr, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         fold(tile, steps & (kInvBufs - 1), steps & 1);
         sidx = 0;
         tile += n_lanes;
         ++steps;
-        if (tid == 0) {
+        if (in_team && tid == 0) {
           const uint32_t target = (uint32_t)team_size * (rounds + (uint32_t)steps);
           for (int spin = 0; spin < spin_budget; ++spin) {
             if (__hip_atomic_load(ctr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= target) break;
@@ -359,13 +412,13 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   }
   __syncthreads();
   // sweep steps this workgroup did not take still count for its team
-  {
-    const uint32_t missing = (uint32_t)(nt_max - (active ? nt : 0));
+  if (in_team && member) {
+    const uint32_t missing = (uint32_t)(nt_max - nt);
     if (tid == 0 && missing)
       __hip_atomic_fetch_add(ctr, missing, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     rounds += (uint32_t)nt_max;
   }
-  if (st < n_src_tiles) {
+  if (member) {
     // merge the two half-wave copies of a column and the four dst quarters (waves wd = 0..3)
     Top2 *cand = (Top2 *)ring;
 #pragma unroll
@@ -380,98 +433,126 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
           top2_insert_any(t, cd.v1, cd.i1);
           top2_insert_any(t, cd.v2, cd.i2);
         }
-      top2p[(size_t)dl * n_src_pad + (size_t)st * kGTile + tid] = t;
+      const size_t at = in_team ? (size_t)dl * sched.full + st
+                                : (size_t)sched.n_sweeps * sched.full + (size_t)dl * sched.n_rest + sti;
+      top2p[at * kGTile + tid] = t;
     }
-    __syncthreads();   // the ring is reused by the next super-row
+    __syncthreads();   // the ring is reused by the next round
   }
-  }   // super-rows
+  }   // rounds
 }
 
-// Final decision per src row (one wave each).  Every sweep hands over its two best candidates
-// by fp32 similarity (up to kMaxSweeps * 2 per row).  If the runner-up is closer than
-// kRescoreGap to the best, every candidate inside that gap is recomputed in float64 and the
-// decision is taken on those values rounded to fp32, lowest token index on a tie: the rule the
-// fp32 accumulation order cannot disturb.  A row with more near-equal candidates than one
-// sweep's two best can still lose its true best inside a sweep; what it picks instead is within
-// twice the fp32 accumulation error of it (C / 16 additions of exact 16-product sums).
-constexpr int kMaxSweeps = 4;
-static_assert(kGLanes <= kMaxSweeps, "k_match_finish reads every sweep's candidates");
+// Final decision per src row.  Every sweep hands over its two best candidates by fp32 similarity.
+// If the runner-up is closer than kRescoreGap to the best, every candidate inside that gap is
+// recomputed in float64 and the decision is taken on those values rounded to fp32, lowest token
+// index on a tie: the rule the fp32 accumulation order cannot disturb.  A row with more
+// near-equal candidates than one sweep's two best can still lose its true best inside a sweep;
+// what it picks instead is within twice the fp32 accumulation error of it (C / 16 additions of
+// exact 16-product sums).
+//
+// Bound by the latency of its index chain: a wave takes kFinRows consecutive rows at once, 8 lanes
+// per row reading the row's sweeps, and only the rows with near-equal candidates one after the
+// other with all 64 lanes (a wave per row: 32 us for 38,192 rows none of which is near-equal).
+// 8 rows and no more, because in late refreshes most rows are near-equal and want many waves.
+constexpr int kFinRows = 8;
 
 __global__ __launch_bounds__(256) void k_match_finish(
     const uint16_t *__restrict__ x, const int32_t *__restrict__ src_idx,
     const int32_t *__restrict__ dst_idx, const float *__restrict__ inv,
-    const Top2 *__restrict__ top2p, int n_lanes, int n_src_pad, int n_src, int C,
+    const Top2 *__restrict__ top2p, MatchSched sched, int n_src, int C,
     int32_t *__restrict__ anchor_of, int32_t *slot_of, float *__restrict__ best_sim) {
-  const int lane = threadIdx.x & 63, wpb = blockDim.x >> 6, nch = C >> 3;
-  for (int p = blockIdx.x * wpb + (threadIdx.x >> 6); p < n_src; p += gridDim.x * wpb) {
-    float cv[2 * kMaxSweeps];
-    int ci[2 * kMaxSweeps];
-    Top2 t = Top2{-INFINITY, -1, -INFINITY, -1};
+  const int lane = threadIdx.x & 63, nch = C >> 3, sub = lane & 7;
+  const int64_t p0 = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * kFinRows;
+  if (p0 >= n_src) return;
+  const int p = (int)min(p0 + (lane >> 3), (int64_t)n_src - 1);
+  // the sweeps of the rows of this wave (a tile of 256 rows holds whole waves' rows)
+  const int tile = (int)(p0 / kGTile);
+  const bool in_full = tile < sched.full;
+  const int n_sweeps = in_full ? sched.n_sweeps : sched.rest_sweeps;
+  const size_t stride = (size_t)(in_full ? sched.full : sched.n_rest) * kGTile;
+  const Top2 *part = in_full ? top2p : top2p + (size_t)sched.n_sweeps * sched.full * kGTile - (size_t)sched.full * kGTile;
+  const int s = src_idx[p];
+  Top2 t = Top2{-INFINITY, -1, -INFINITY, -1};
+  for (int l = sub; l < n_sweeps; l += 8) {
+    const Top2 o = part[l * stride + p];
+    top2_insert_any(t, o.v1, o.i1);
+    top2_insert_any(t, o.v2, o.i2);
+  }
+  const float invs = inv[s];
 #pragma unroll
-    for (int l = 0; l < kMaxSweeps; ++l) {    // every sweep's candidates for this row
-      Top2 o = Top2{-INFINITY, -1, -INFINITY, -1};
-      if (l < n_lanes) o = top2p[(size_t)l * n_src_pad + p];
-      cv[2 * l] = o.v1;
-      ci[2 * l] = o.i1;
-      cv[2 * l + 1] = o.v2;
-      ci[2 * l + 1] = o.i2;
-      top2_insert_any(t, o.v1, o.i1);
-      top2_insert_any(t, o.v2, o.i2);
+  for (int o = 1; o < 8; o <<= 1) {
+    const Top2 u = Top2{__shfl_xor(t.v1, o, 64), __shfl_xor(t.i1, o, 64), __shfl_xor(t.v2, o, 64), __shfl_xor(t.i2, o, 64)};
+    top2_insert_any(t, u.v1, u.i1);
+    top2_insert_any(t, u.v2, u.i2);
+  }
+  int choose = t.i1 < 0 ? 0 : t.i1;
+  float sim = t.i1 < 0 ? 0.f : t.v1 * invs;
+  const bool near = t.i1 >= 0 && t.i2 >= 0 && (t.v1 - t.v2) * invs < kRescoreGap;
+  uint64_t rows = __builtin_amdgcn_ballot_w64(near && sub == 0 && p0 + (lane >> 3) < n_src);
+  while (rows) {
+    const int r = __builtin_ctzll(rows);       // first lane of the row's eight
+    rows &= rows - 1;
+    const int rp = __builtin_amdgcn_readlane(p, r), rs = __builtin_amdgcn_readlane(s, r);
+    const float v1 = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, t.v1), r));
+    const float is32 = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, invs), r));
+    // lane l holds the two candidates of sweep l
+    Top2 o = Top2{-INFINITY, -1, -INFINITY, -1};
+    if (lane < n_sweeps) o = part[lane * stride + rp];
+    uint64_t c1 = __builtin_amdgcn_ballot_w64(o.i1 >= 0 && (v1 - o.v1) * is32 < kRescoreGap);
+    uint64_t c2 = __builtin_amdgcn_ballot_w64(o.i2 >= 0 && (v1 - o.v2) * is32 < kRescoreGap);
+    double ss = 0;
+    for (int ch = lane; ch < nch; ch += 64) {
+      const u32x4 w = ((const u32x4 *)(x + (size_t)rs * C))[ch];
+      const uint32_t us[4] = {w.x, w.y, w.z, w.w};
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const double sl = bf16_lo(us[q]), sh = bf16_hi(us[q]);
+        ss += sl * sl + sh * sh;
+      }
     }
-    const int s = src_idx[p];
-    const float invs = inv[s];
-    int choose = t.i1 < 0 ? 0 : t.i1;
-    float sim = t.i1 < 0 ? 0.f : t.v1 * invs;
-    if (t.i1 >= 0 && t.i2 >= 0 && (t.v1 - t.v2) * invs < kRescoreGap) {
-      double ss = 0;
+    ss = wave_sum(ss);
+    const double is = 1.0 / fmax(sqrt(ss), 1e-12);
+    float bs = -INFINITY;
+    int bd = 0x7fffffff, bi = 0;
+    while (c1 | c2) {                          // the candidates inside the gap (never none: the best is one)
+      const bool first = c1 != 0;
+      const int l = __builtin_ctzll(first ? c1 : c2);
+      if (first) c1 &= c1 - 1;
+      else c2 &= c2 - 1;
+      const int ci = first ? __builtin_amdgcn_readlane(o.i1, l) : __builtin_amdgcn_readlane(o.i2, l);
+      const int d = dst_idx[ci];
+      double nn = 0, pp = 0;
       for (int ch = lane; ch < nch; ch += 64) {
-        const u32x4 w = ((const u32x4 *)(x + (size_t)s * C))[ch];
-        const uint32_t us[4] = {w.x, w.y, w.z, w.w};
+        const u32x4 wd = ((const u32x4 *)(x + (size_t)d * C))[ch];
+        const u32x4 w = ((const u32x4 *)(x + (size_t)rs * C))[ch];   // the src row again: a cache hit
+        const uint32_t us[4] = {w.x, w.y, w.z, w.w}, ud[4] = {wd.x, wd.y, wd.z, wd.w};
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
           const double sl = bf16_lo(us[q]), sh = bf16_hi(us[q]);
-          ss += sl * sl + sh * sh;
+          const double al = bf16_lo(ud[q]), ah = bf16_hi(ud[q]);
+          nn += al * al + ah * ah;
+          pp += sl * al + sh * ah;
         }
       }
-      ss = wave_sum(ss);
-      const double is = 1.0 / fmax(sqrt(ss), 1e-12);
-      float bs = -INFINITY;
-      int bd = 0x7fffffff, bi = choose;
-#pragma unroll
-      for (int c = 0; c < 2 * kMaxSweeps; ++c) {
-        if (ci[c] < 0 || !((t.v1 - cv[c]) * invs < kRescoreGap)) continue;   // wave-uniform
-        const int d = dst_idx[ci[c]];
-        double nn = 0, pp = 0;
-        for (int ch = lane; ch < nch; ch += 64) {
-          const u32x4 wd = ((const u32x4 *)(x + (size_t)d * C))[ch];
-          const u32x4 w = ((const u32x4 *)(x + (size_t)s * C))[ch];   // the src row again: a cache hit
-          const uint32_t us[4] = {w.x, w.y, w.z, w.w}, ud[4] = {wd.x, wd.y, wd.z, wd.w};
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            const double sl = bf16_lo(us[q]), sh = bf16_hi(us[q]);
-            const double al = bf16_lo(ud[q]), ah = bf16_hi(ud[q]);
-            nn += al * al + ah * ah;
-            pp += sl * al + sh * ah;
-          }
-        }
-        nn = wave_sum(nn);
-        pp = wave_sum(pp);
-        const float sc = (float)(pp * is * (1.0 / fmax(sqrt(nn), 1e-12)));
-        if (sc > bs || (sc == bs && d < bd)) {
-          bs = sc;
-          bd = d;
-          bi = ci[c];
-        }
+      nn = wave_sum(nn);
+      pp = wave_sum(pp);
+      const float sc = (float)(pp * is * (1.0 / fmax(sqrt(nn), 1e-12)));
+      if (sc > bs || (sc == bs && d < bd)) {
+        bs = sc;
+        bd = d;
+        bi = ci;
       }
+    }
+    if (lane == r && bd != 0x7fffffff) {       // (NaN similarities leave the fp32 choice)
       choose = bi;
       sim = bs;
     }
-    if (lane == 0) {
-      const int a = dst_idx[choose];
-      anchor_of[s] = a;
-      slot_of[s] = slot_of[a];
-      if (best_sim) best_sim[p] = sim;
-    }
+  }
+  if (sub == 0 && p0 + (lane >> 3) < n_src) {
+    const int a = dst_idx[choose];
+    anchor_of[s] = a;
+    slot_of[s] = slot_of[a];
+    if (best_sim) best_sim[p] = sim;
   }
 }
 
@@ -593,7 +674,8 @@ struct MatchWs {
   int32_t *vals[2];
   uint32_t *hist, *team_ctr;
   size_t bytes;
-  int n_dst_pad, n_src_pad, n_lanes, nchunks;
+  size_t partials;       // tiles of 256 partial results that top2p holds
+  int n_dst_pad, n_src_pad, nchunks;
 };
 
 static MatchWs carve(const Dims &d, const litevggt_plan_t &pl, char *base) {
@@ -606,14 +688,13 @@ static MatchWs carve(const Dims &d, const litevggt_plan_t &pl, char *base) {
   };
   w.n_dst_pad = (int)align_up((size_t)pl.n_dst, kGTile);
   w.n_src_pad = (int)align_up((size_t)pl.n_src, kGTile);
-  const int dst_tiles = w.n_dst_pad / kGTile;
-  w.n_lanes = dst_tiles < kGLanes ? (dst_tiles > 0 ? dst_tiles : 1) : kGLanes;
   w.nchunks = (int)((d.N + kSortChunk - 1) / kSortChunk);
   w.inv = (float *)take((size_t)d.N * 4);
   w.dstp = (u32x4 *)take((size_t)w.n_dst_pad * d.C * 2);
   w.srcp = (u32x4 *)take((size_t)w.n_src_pad * d.C * 2);
   w.invd = (float *)take((size_t)w.n_dst_pad * 4);
-  w.top2p = (Top2 *)take((size_t)w.n_lanes * w.n_src_pad * sizeof(Top2));
+  w.partials = sched_partials(match_sched(w.n_src_pad / kGTile, w.n_dst_pad / kGTile, kTeam));
+  w.top2p = (Top2 *)take(w.partials * kGTile * sizeof(Top2));
   for (int i = 0; i < 2; ++i) {
     w.keys[i] = (uint32_t *)take((size_t)d.N * 4);
     w.vals[i] = (int32_t *)take((size_t)d.N * 4);
@@ -652,16 +733,17 @@ int launch_match(const uint16_t *x, const Dims &d, const litevggt_plan_t &pl,
     if (hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
       return LV_ERR_HIP;
-    int per_team = n_cu / kXcd;
-    if (per_team < w.n_lanes) per_team = w.n_lanes;
-    const int team_size = per_team / w.n_lanes * w.n_lanes;
+    const int per_team = n_cu >= kXcd ? n_cu / kXcd : 1;
+    MatchSched sched = match_sched(src_tiles, dst_tiles, per_team);
+    if (sched_partials(sched) > w.partials) {   // other teams than the workspace was sized for: one sweep per src tile
+      const int round = per_team * kXcd;
+      sched = {1, per_team, src_tiles / round, 1, src_tiles % round, src_tiles / round * round};
+    }
     hipLaunchKernelGGL(k_match_sim, dim3((unsigned)(per_team * kXcd)), dim3(512), lds, st, w.srcp,
-                       w.dstp, w.invd, n_dst, src_tiles, dst_tiles, w.n_lanes, d.C / 16, w.n_src_pad,
-                       team_size, kTeamSpin, w.team_ctr, w.top2p);
-    const unsigned fin = (unsigned)(((n_src + 3) / 4) < 16384 ? ((n_src + 3) / 4) : 16384);
+                       w.dstp, w.invd, n_dst, dst_tiles, sched, d.C / 16, kTeamSpin, w.team_ctr, w.top2p);
+    const unsigned fin = (unsigned)((n_src + 4 * kFinRows - 1) / (4 * kFinRows));
     hipLaunchKernelGGL(k_match_finish, dim3(fin), dim3(256), 0, st, x, ix.src_idx, ix.dst_idx,
-                       w.inv, w.top2p, w.n_lanes, w.n_src_pad, n_src, d.C, ix.anchor_of, ix.slot_of,
-                       best_sim);
+                       w.inv, w.top2p, sched, n_src, d.C, ix.anchor_of, ix.slot_of, best_sim);
     LV_HIP_CHECK_LAUNCH();
   }
   // CSR groups by stable radix sort of slot_of

@@ -55,3 +55,76 @@ def test_select_edges(B, h, w, special, ratio, kind):
     kept = ref["kept_idx"].astype(np.int64)
     assert np.array_equal(_i32(ib.anchor_of)[kept], kept)
     assert np.array_equal(_i32(ib.slot_of)[kept], np.arange(len(kept)))
+
+
+# ------------------------------------------------------------------------------- matching
+def _check_index(B, ph, x, near=1e-6):
+    """Matching of bf16 rows x against every dst row in float64, and the groups it implies."""
+    import torch
+    pl = B.litevggt_plan(ph)
+    ib = B.alloc_index(pl)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(3)
+    score = torch.rand(ph.frames, ph.grid_h * ph.grid_w, generator=g, device="cuda")
+    best = torch.empty(max(pl.n_src, 1), device="cuda")
+    B.litevggt_select_anchors(ph, score, ib)
+    B.litevggt_match(ph, x, ib, best, B.alloc_ws(pl.ws_bytes))
+    torch.cuda.synchronize()
+    xn = x.double()
+    xn = xn / xn.norm(dim=1, keepdim=True).clamp_min(1e-12)
+    src, dst = ib.src_idx[:pl.n_src].long(), ib.dst_idx[:pl.n_dst].long()
+    dn = xn[dst].t().contiguous()
+    for i in range(0, pl.n_src, 8192):
+        sim = xn[src[i:i + 8192]] @ dn
+        top, at = sim.topk(2, dim=1)
+        got = ib.anchor_of[src[i:i + 8192]].long()
+        wrong = got != dst[at[:, 0]]
+        assert bool(((top[:, 0] - top[:, 1])[wrong] < near).all())
+        pos = torch.searchsorted(dst, got)
+        assert torch.equal(dst[pos], got)
+        assert float((top[:, 0] - sim.gather(1, pos[:, None])[:, 0]).max()) < near
+        assert float((best[i:i + 8192].double() - top[:, 0]).abs().max()) < 2e-5
+    # groups: members ascending inside every slot, slots in the order of the kept tokens
+    slot = ib.slot_of.long()
+    kept = ib.kept_idx.long()
+    assert torch.equal(kept[slot], ib.anchor_of.long())
+    order = torch.sort(slot, stable=True)[1]
+    assert torch.equal(ib.group_mem.long(), order)
+    off = torch.zeros(pl.M + 1, dtype=torch.int64, device="cuda")
+    off[1:] = torch.cumsum(torch.bincount(slot, minlength=pl.M), 0)
+    assert torch.equal(ib.group_off.long(), off)
+
+
+# src x dst tiles of 256 rows: 1 x 2 and 1 x 30 (one src tile, a sweep per dst tile), 12 x 3 (no full
+# round), 83 x 8 (the same with ragged sweeps), 252 x 20 (three full rounds of 8 x 4 teams, a rest of
+# 60), 143 x 57 (a full round of 16 x 2 teams, a rest of 15 tiles by 17 sweeps)
+@pytest.mark.parametrize("frames,h,w,ratio,dim", [(2, 16, 16, 0.5, 64), (2, 77, 77, 0.01, 64), (9, 20, 20, 0.9, 192),
+                                                  (60, 20, 20, 0.9, 64), (180, 20, 20, 0.9, 128), (141, 20, 20, -1.0, 64)])
+def test_match_schedules(B, frames, h, w, ratio, dim):
+    import torch
+    ph = B.make_params(frames, h, w, dim, dim // 64, merge_ratio=ratio)
+    pl = B.litevggt_plan(ph)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(frames)
+    x = torch.randn(pl.N, ph.dim, generator=g, device="cuda").to(torch.bfloat16)
+    _check_index(B, ph, x)
+
+
+def test_match_near_equal_rows_of_many_sweeps(B):
+    """Every dst row appears in several dst tiles (exact copies): float64 ties over sweeps go to
+    the lowest token number."""
+    import torch
+    ph = B.make_params(40, 16, 16, 128, 2, merge_ratio=0.5)
+    pl = B.litevggt_plan(ph)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(1)
+    frame = torch.randn(pl.N // 40, 128, generator=g, device="cuda").to(torch.bfloat16)
+    x = frame.repeat(40, 1).contiguous()
+    ib = B.alloc_index(pl)
+    score = torch.rand(1, 256, generator=g, device="cuda").repeat(40, 1).contiguous()
+    B.litevggt_select_anchors(ph, score, ib)
+    B.litevggt_match(ph, x, ib, None, B.alloc_ws(pl.ws_bytes))
+    torch.cuda.synchronize()
+    src = ib.src_idx[:pl.n_src].long()
+    # frame 0 is all dst, so every src token has its exact copy there, and no dst precedes it
+    assert torch.equal(ib.anchor_of[src].long(), src % (pl.N // 40))
