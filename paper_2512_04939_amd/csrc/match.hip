@@ -19,54 +19,85 @@ struct Top2 {
   int i2;
 };
 
-// inv[i] = 1 / max(|x_i|, 1e-12), norm accumulated in float64.  One wave per row.
-__global__ __launch_bounds__(256) void k_inv_norm(const uint16_t *__restrict__ x, int64_t N, int C,
-                                                  float *__restrict__ inv) {
-  const int lane = threadIdx.x & 63, wpb = blockDim.x >> 6, nch = C >> 3;
-  for (int64_t i = (int64_t)blockIdx.x * wpb + (threadIdx.x >> 6); i < N;
-       i += (int64_t)gridDim.x * wpb) {
-    double ss = 0.0;
-    for (int ch = lane; ch < nch; ch += 64) {
-      u32x4 w = ((const u32x4 *)(x + (size_t)i * C))[ch];
-      double a0 = bf16_lo(w.x), a1 = bf16_hi(w.x), a2 = bf16_lo(w.y), a3 = bf16_hi(w.y);
-      double a4 = bf16_lo(w.z), a5 = bf16_hi(w.z), a6 = bf16_lo(w.w), a7 = bf16_hi(w.w);
-      ss += a0 * a0 + a1 * a1 + a2 * a2 + a3 * a3 + a4 * a4 + a5 * a5 + a6 * a6 + a7 * a7;
-    }
-    ss = wave_sum(ss);
-    if (lane == 0) inv[i] = (float)(1.0 / fmax(sqrt(ss), 1e-12));
-  }
-}
-
-// Gather token rows into fragment-major order: fragment (tile t of 32 rows, k-step s of 16
-// channels) is 1 KB contiguous, lane (h*32 + r) holds row r, channels 16s+8h .. 16s+8h+7.
-// idx_of == NULL packs rows 0..n-1 in place order.  Rows beyond n are zero.  inv_out (optional)
-// receives the rows' inverse norms, 0 beyond n; zero256 (optional) is a 256-word array to clear.
+// Rows 0..n-1 of x into fragment-major order: fragment (tile t of 32 rows, k-step s of 16
+// channels) is 1 KB contiguous, lane (h*32 + r) holds row r, channels 16s+8h .. 16s+8h+7.  Rows
+// beyond n are zero.
 // A wave writes whole fragments (1 KB stores); it takes 4 consecutive k-steps of its 32 rows,
 // so the 128 bytes it needs of a row are one cache line read by 4 back-to-back loads.
 // Grid: (row tiles, ceil(KS / 16)); a workgroup's 4 waves take 4 k-steps each.
-__global__ __launch_bounds__(256) void k_pack_rows(const uint16_t *__restrict__ x,
-                                                   const int32_t *__restrict__ idx_of,
-                                                   const float *__restrict__ inv, int n, int n_pad,
-                                                   int C, u32x4 *__restrict__ packed,
-                                                   float *__restrict__ inv_out,
-                                                   uint32_t *__restrict__ zero256) {
+__global__ __launch_bounds__(256) void k_pack_rows(const uint16_t *__restrict__ x, int n, int C,
+                                                   u32x4 *__restrict__ packed) {
   const int KS = C >> 4;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, h = lane >> 5, r = lane & 31;
-  const int t = blockIdx.x, j = t * 32 + r;
-  if (zero256 && blockIdx.x == 0 && blockIdx.y == 0) zero256[threadIdx.x] = 0u;   // the similarity kernel's team counters
-  int row = -1;
-  if (j < n) row = idx_of ? idx_of[j] : j;
-  if (inv_out && blockIdx.y == 0 && wave == 0 && h == 0 && j < n_pad) inv_out[j] = row >= 0 ? inv[row] : 0.f;
+  const int t = blockIdx.x, row = t * 32 + r;
   const int s0 = (blockIdx.y * 4 + wave) * 4;
   u32x4 w[4];
 #pragma unroll
   for (int u = 0; u < 4; ++u) {
     w[u] = u32x4{0u, 0u, 0u, 0u};
-    if (row >= 0 && s0 + u < KS) w[u] = ((const u32x4 *)(x + (size_t)row * C))[(s0 + u) * 2 + h];
+    if (row < n && s0 + u < KS) w[u] = ((const u32x4 *)(x + (size_t)row * C))[(s0 + u) * 2 + h];
   }
 #pragma unroll
   for (int u = 0; u < 4; ++u)
     if (s0 + u < KS) packed[((size_t)t * KS + s0 + u) * 64 + lane] = w[u];
+}
+
+// The operands of the similarity kernel: dst rows and src rows gathered into the same order, and
+// each row's 1 / max(|x|, 1e-12), the norm accumulated in float64 from the registers that are
+// being moved.  Workgroups 0 .. dst_tiles - 1 take 32 dst rows each, the others 32 src rows;
+// a wave takes every fourth group of 4 k-steps, all its loads (at most 16, C <= 1024) in flight
+// at once.  Bound by HBM: every row is read once and written once.  (One launch instead of a
+// norm pass over all tokens and two packs, which read every row twice: 55 -> 29 us at 32 frames
+// of 37 x 37 patches, 124 -> 76 us at 100 frames of 28 x 37, C = 1024.)
+__global__ __launch_bounds__(256) void k_match_pack(const uint16_t *__restrict__ x,
+                                                    const int32_t *__restrict__ dst_idx, int n_dst, int dst_tiles,
+                                                    const int32_t *__restrict__ src_idx, int n_src, int C,
+                                                    u32x4 *__restrict__ dstp, u32x4 *__restrict__ srcp,
+                                                    float *__restrict__ invd, float *__restrict__ invs,
+                                                    uint32_t *__restrict__ team_ctr) {
+  __shared__ double part[4][32];
+  const int KS = C >> 4;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, h = lane >> 5, r = lane & 31;
+  const bool is_dst = (int)blockIdx.x < dst_tiles;
+  const int t = is_dst ? blockIdx.x : (int)blockIdx.x - dst_tiles, j = t * 32 + r;
+  if (blockIdx.x == 0) team_ctr[threadIdx.x] = 0u;   // the similarity kernel's team counters
+  int row = -1;
+  if (j < (is_dst ? n_dst : n_src)) row = is_dst ? dst_idx[j] : src_idx[j];
+  u32x4 w[4][4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int s0 = (i * 4 + wave) * 4;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      w[i][u] = u32x4{0u, 0u, 0u, 0u};
+      if (row >= 0 && s0 + u < KS) w[i][u] = ((const u32x4 *)(x + (size_t)row * C))[(s0 + u) * 2 + h];
+    }
+  }
+  u32x4 *packed = is_dst ? dstp : srcp;
+  double ss = 0.0;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int s0 = (i * 4 + wave) * 4;
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if (s0 + u < KS) {
+        const u32x4 v = w[i][u];
+        packed[((size_t)t * KS + s0 + u) * 64 + lane] = v;
+        const uint32_t b[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const double lo = bf16_lo(b[q]), hi = bf16_hi(b[q]);
+          ss += lo * lo + hi * hi;
+        }
+      }
+  }
+  ss += __shfl_xor(ss, 32, 64);
+  if (h == 0) part[wave][r] = ss;
+  __syncthreads();
+  if (threadIdx.x < 32) {   // row r of the tile; rows beyond the list get 0
+    const double n2 = (part[0][r] + part[1][r]) + (part[2][r] + part[3][r]);
+    (is_dst ? invd : invs)[j] = row >= 0 ? (float)(1.0 / fmax(sqrt(n2), 1e-12)) : 0.f;
+  }
 }
 
 __device__ __forceinline__ void top2_insert_any(Top2 &t, float v, int i) {
@@ -85,9 +116,7 @@ __device__ __forceinline__ void top2_insert_any(Top2 &t, float v, int i) {
 int launch_pack_rows(const uint16_t *x, int64_t n, int64_t n_pad, int C, void *packed, hipStream_t st) {
   if (n_pad >= ((int64_t)1 << 31) || n_pad % 32 != 0 || C % 16 != 0) return LV_ERR_SHAPE;
   hipLaunchKernelGGL(k_pack_rows, dim3((unsigned)(n_pad / 32), (unsigned)((C / 16 + 15) / 16)), dim3(256), 0, st, x,
-                     (const int32_t *)nullptr, (const float *)nullptr, (int)n, (int)n_pad, C,
-                     (u32x4 *)packed,
-                     (float *)nullptr, (uint32_t *)nullptr);
+                     (int)n, C, (u32x4 *)packed);
   LV_HIP_CHECK_LAUNCH();
   return LV_OK;
 }
@@ -458,7 +487,7 @@ constexpr int kFinRows = 8;
 
 __global__ __launch_bounds__(256) void k_match_finish(
     const uint16_t *__restrict__ x, const int32_t *__restrict__ src_idx,
-    const int32_t *__restrict__ dst_idx, const float *__restrict__ inv,
+    const int32_t *__restrict__ dst_idx, const float *__restrict__ inv_src,
     const Top2 *__restrict__ top2p, MatchSched sched, int n_src, int C,
     int32_t *__restrict__ anchor_of, int32_t *slot_of, float *__restrict__ best_sim) {
   const int lane = threadIdx.x & 63, nch = C >> 3, sub = lane & 7;
@@ -478,7 +507,7 @@ __global__ __launch_bounds__(256) void k_match_finish(
     top2_insert_any(t, o.v1, o.i1);
     top2_insert_any(t, o.v2, o.i2);
   }
-  const float invs = inv[s];
+  const float invs = inv_src[p];
 #pragma unroll
   for (int o = 1; o < 8; o <<= 1) {
     const Top2 u = Top2{__shfl_xor(t.v1, o, 64), __shfl_xor(t.i1, o, 64), __shfl_xor(t.v2, o, 64), __shfl_xor(t.i2, o, 64)};
@@ -666,9 +695,8 @@ __global__ __launch_bounds__(256) void k_csr_finish(const uint32_t *__restrict__
 
 // ---------------------------------------------------------------------------------
 struct MatchWs {
-  float *inv;
   u32x4 *dstp, *srcp;
-  float *invd;
+  float *invd, *invs;
   Top2 *top2p;
   uint32_t *keys[2];
   int32_t *vals[2];
@@ -689,10 +717,10 @@ static MatchWs carve(const Dims &d, const litevggt_plan_t &pl, char *base) {
   w.n_dst_pad = (int)align_up((size_t)pl.n_dst, kGTile);
   w.n_src_pad = (int)align_up((size_t)pl.n_src, kGTile);
   w.nchunks = (int)((d.N + kSortChunk - 1) / kSortChunk);
-  w.inv = (float *)take((size_t)d.N * 4);
   w.dstp = (u32x4 *)take((size_t)w.n_dst_pad * d.C * 2);
   w.srcp = (u32x4 *)take((size_t)w.n_src_pad * d.C * 2);
   w.invd = (float *)take((size_t)w.n_dst_pad * 4);
+  w.invs = (float *)take((size_t)w.n_src_pad * 4);
   w.partials = sched_partials(match_sched(w.n_src_pad / kGTile, w.n_dst_pad / kGTile, kTeam));
   w.top2p = (Top2 *)take(w.partials * kGTile * sizeof(Top2));
   for (int i = 0; i < 2; ++i) {
@@ -718,14 +746,9 @@ int launch_match(const uint16_t *x, const Dims &d, const litevggt_plan_t &pl,
     const size_t lds = (size_t)kGStages * kGStageU4 * 16 + 8 * kInvBufs * 64 * sizeof(float) + 2 * 1024 * sizeof(float);
     static std::atomic<uint64_t> lds_done{0};
     if (int rc = allow_dynamic_lds((const void *)k_match_sim, lds, lds_done)) return rc;
-    const unsigned rows_grid = (unsigned)(((d.N + 3) / 4) < 16384 ? ((d.N + 3) / 4) : 16384);
-    hipLaunchKernelGGL(k_inv_norm, dim3(rows_grid), dim3(256), 0, st, x, d.N, d.C, w.inv);
-    const unsigned ks_groups = (unsigned)((d.C / 16 + 15) / 16);
-    hipLaunchKernelGGL(k_pack_rows, dim3((unsigned)(w.n_dst_pad / 32), ks_groups), dim3(256), 0, st, x,
-                       ix.dst_idx, w.inv, n_dst, w.n_dst_pad, d.C, w.dstp, w.invd, w.team_ctr);
-    hipLaunchKernelGGL(k_pack_rows, dim3((unsigned)(w.n_src_pad / 32), ks_groups), dim3(256), 0, st, x,
-                       ix.src_idx, w.inv, n_src, w.n_src_pad, d.C, w.srcp, (float *)nullptr,
-                       (uint32_t *)nullptr);
+    const int pack_dst = w.n_dst_pad / 32, pack_src = w.n_src_pad / 32;
+    hipLaunchKernelGGL(k_match_pack, dim3((unsigned)(pack_dst + pack_src)), dim3(256), 0, st, x, ix.dst_idx, n_dst,
+                       pack_dst, ix.src_idx, n_src, d.C, w.dstp, w.srcp, w.invd, w.invs, w.team_ctr);
     // One workgroup per CU, all resident at once; the workgroups the hardware deals to one
     // XCD (block index mod 8) form a team of (src tiles per super-row) x (sweeps).
     const int src_tiles = w.n_src_pad / kGTile, dst_tiles = w.n_dst_pad / kGTile;
@@ -743,7 +766,7 @@ int launch_match(const uint16_t *x, const Dims &d, const litevggt_plan_t &pl,
                        w.dstp, w.invd, n_dst, dst_tiles, sched, d.C / 16, kTeamSpin, w.team_ctr, w.top2p);
     const unsigned fin = (unsigned)((n_src + 4 * kFinRows - 1) / (4 * kFinRows));
     hipLaunchKernelGGL(k_match_finish, dim3(fin), dim3(256), 0, st, x, ix.src_idx, ix.dst_idx,
-                       w.inv, w.top2p, sched, n_src, d.C, ix.anchor_of, ix.slot_of, best_sim);
+                       w.invs, w.top2p, sched, n_src, d.C, ix.anchor_of, ix.slot_of, best_sim);
     LV_HIP_CHECK_LAUNCH();
   }
   // CSR groups by stable radix sort of slot_of
