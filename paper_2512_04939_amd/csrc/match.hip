@@ -94,9 +94,9 @@ __global__ __launch_bounds__(256) void k_match_pack(const uint16_t *__restrict__
   ss += __shfl_xor(ss, 32, 64);
   if (h == 0) part[wave][r] = ss;
   __syncthreads();
-  if (threadIdx.x < 32) {   // row r of the tile; rows beyond the list get 0
+  if (threadIdx.x < 32) {   // row r of the tile; rows beyond the list get NaN: no comparison picks them
     const double n2 = (part[0][r] + part[1][r]) + (part[2][r] + part[3][r]);
-    (is_dst ? invd : invs)[j] = row >= 0 ? (float)(1.0 / fmax(sqrt(n2), 1e-12)) : 0.f;
+    (is_dst ? invd : invs)[j] = row >= 0 ? (float)(1.0 / fmax(sqrt(n2), 1e-12)) : __builtin_nanf("");
   }
 }
 
@@ -119,6 +119,16 @@ int launch_pack_rows(const uint16_t *x, int64_t n, int64_t n_pad, int C, void *p
                      (int)n, C, (u32x4 *)packed);
   LV_HIP_CHECK_LAUNCH();
   return LV_OK;
+}
+
+// The same for an element of a higher row than every one before it: equal values lose.  A NaN
+// (rows beyond the list) is never taken.
+__device__ __forceinline__ void top2_insert_later(Top2 &t, float v, int i) {
+  const bool c1 = v > t.v1, c2 = v > t.v2;
+  t.v2 = c1 ? t.v1 : c2 ? v : t.v2;
+  t.i2 = c1 ? t.i1 : c2 ? i : t.i2;
+  t.v1 = c1 ? v : t.v1;
+  t.i1 = c1 ? i : t.i1;
 }
 
 // ---------------------------------------------------------------------------------
@@ -196,7 +206,7 @@ static size_t sched_partials(const MatchSched &s) {   // tiles of 256 partial re
 
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_match_sim(
     const u32x4 *__restrict__ srcp, const u32x4 *__restrict__ dstp, const float *__restrict__ invd,
-    int n_dst, int n_dst_tiles, MatchSched sched, int KS, int spin_budget, uint32_t *team_ctr,
+    int n_dst_tiles, MatchSched sched, int KS, int spin_budget, uint32_t *team_ctr,
     Top2 *__restrict__ top2p) {
   extern __shared__ u32x4 ring[];    // kGStages stages
   const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5;
@@ -362,8 +372,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
               if (hit[r] != 0) {   // insertions only raise the thresholds: the masks stay a superset
-                const int j2 = row0 + (r >> 2) * 8 + (r & 3);
-                if (j2 < n_dst) top2_insert_any(best[b], v[r], j2);
+                top2_insert_later(best[b], v[r], row0 + (r >> 2) * 8 + (r & 3));
               }
             }
             thr[b] = fmaxf(thr[b], best[b].v2);
@@ -763,7 +772,7 @@ int launch_match(const uint16_t *x, const Dims &d, const litevggt_plan_t &pl,
       sched = {1, per_team, src_tiles / round, 1, src_tiles % round, src_tiles / round * round};
     }
     hipLaunchKernelGGL(k_match_sim, dim3((unsigned)(per_team * kXcd)), dim3(512), lds, st, w.srcp,
-                       w.dstp, w.invd, n_dst, dst_tiles, sched, d.C / 16, kTeamSpin, w.team_ctr, w.top2p);
+                       w.dstp, w.invd, dst_tiles, sched, d.C / 16, kTeamSpin, w.team_ctr, w.top2p);
     const unsigned fin = (unsigned)((n_src + 4 * kFinRows - 1) / (4 * kFinRows));
     hipLaunchKernelGGL(k_match_finish, dim3(fin), dim3(256), 0, st, x, ix.src_idx, ix.dst_idx,
                        w.invs, w.top2p, sched, n_src, d.C, ix.anchor_of, ix.slot_of, best_sim);
