@@ -595,43 +595,69 @@ __global__ __launch_bounds__(256) void k_match_finish(
 }
 
 // ---------------------------------------------------------------------------------
-// CSR groups: a stable LSD radix sort of (slot_of[i], i) gives the members of every slot
-// in ascending token order.  One wave per 1024-element chunk keeps the scatter stable.
+// CSR groups: a stable LSD radix sort of (slot_of[i], i) gives the members of every slot in
+// ascending token order.  All of it is latency: a few MB at the most per pass, three launches per
+// pass.  Digits are as narrow as the number of passes allows (fewer counters to scan); a
+// workgroup takes a chunk of 1024 elements, each of its 4 waves 256 consecutive ones, so the
+// scatter is a chain of 4 steps and not of 16; the last pass writes group_mem itself.
+// Together 56 -> 34 us at 32 frames of 37 x 37 patches, 73 -> 41 us at 100 frames of 28 x 37.
 // ---------------------------------------------------------------------------------
 constexpr int kSortChunk = 1024;
+constexpr int kScanPer = 16;     // counters per thread and tile of the scan
 
-__global__ __launch_bounds__(64) void k_radix_hist(const uint32_t *__restrict__ keys, int64_t N,
-                                                   int shift, int nchunks,
-                                                   uint32_t *__restrict__ hist) {
+__global__ __launch_bounds__(256) void k_radix_hist(const uint32_t *__restrict__ keys, int64_t N,
+                                                    int shift, int bins, int nchunks,
+                                                    uint32_t *__restrict__ hist) {
   __shared__ uint32_t h[256];
-  const int lane = threadIdx.x;
-  for (int d = lane; d < 256; d += 64) h[d] = 0;
+  const int tid = threadIdx.x;
+  h[tid] = 0u;
   __syncthreads();
   const int64_t b = (int64_t)blockIdx.x * kSortChunk;
-  for (int i = lane; i < kSortChunk; i += 64)
-    if (b + i < N) atomicAdd(&h[(keys[b + i] >> shift) & 255u], 1u);
+#pragma unroll
+  for (int i = 0; i < kSortChunk / 256; ++i) {
+    const int64_t g = b + i * 256 + tid;
+    if (g < N) atomicAdd(&h[(keys[g] >> shift) & (uint32_t)(bins - 1)], 1u);
+  }
   __syncthreads();
-  for (int d = lane; d < 256; d += 64) hist[(size_t)d * nchunks + blockIdx.x] = h[d];
+  if (tid < bins) hist[(size_t)tid * nchunks + blockIdx.x] = h[tid];
 }
 
-// exclusive prefix sum over hist[256*nchunks] in place (digit-major), single workgroup: tiles
-// of 4096 elements, 4 consecutive elements per thread, the running total carried from tile to tile
+// inclusive prefix sum over the 64 lanes
+__device__ __forceinline__ uint32_t wave_scan(uint32_t v, int lane) {
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const uint32_t up = __shfl_up(v, o, 64);
+    if (lane >= o) v += up;
+  }
+  return v;
+}
+
+// exclusive prefix sum over hist[bins*nchunks] in place (digit-major), single workgroup: tiles
+// of 16384 elements, 16 consecutive elements per thread, the running total carried from tile to tile
 __global__ __launch_bounds__(1024) void k_radix_scan(uint32_t *__restrict__ hist, int64_t n) {
   __shared__ uint32_t wtot[16];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   uint32_t carry = 0;
-  for (int64_t t0 = 0; t0 < n; t0 += 4096) {
-    const int64_t i = t0 + (int64_t)tid * 4;
-    uint32_t v[4];
+  for (int64_t t0 = 0; t0 < n; t0 += 1024 * kScanPer) {
+    const int64_t i = t0 + (int64_t)tid * kScanPer;
+    uint32_t v[kScanPer], sum = 0u;
 #pragma unroll
-    for (int u = 0; u < 4; ++u) v[u] = i + u < n ? hist[i + u] : 0u;
-    const uint32_t sum = v[0] + v[1] + v[2] + v[3];
-    uint32_t inc = sum;
+    for (int u = 0; u < kScanPer; u += 4) {
+      u32x4 q = u32x4{0u, 0u, 0u, 0u};
+      if (i + u + 3 < n) {   // the array starts on a 256-byte boundary
+        q = *(const u32x4 *)(hist + i + u);
+      } else {
 #pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const uint32_t up = __shfl_up(inc, o, 64);
-      if (lane >= o) inc += up;
+        for (int e = 0; e < 4; ++e)
+          if (i + u + e < n) q[e] = hist[i + u + e];
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        v[u + e] = q[e];
+        sum += q[e];
+      }
     }
+    const uint32_t inc = wave_scan(sum, lane);
     if (lane == 63) wtot[wave] = inc;
     __syncthreads();
     uint32_t base = 0, total = 0;
@@ -643,63 +669,179 @@ __global__ __launch_bounds__(1024) void k_radix_scan(uint32_t *__restrict__ hist
     }
     uint32_t run = carry + base + inc - sum;
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      if (i + u < n) hist[i + u] = run;
-      run += v[u];
+    for (int u = 0; u < kScanPer; u += 4) {
+      u32x4 q;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        q[e] = run;
+        run += v[u + e];
+      }
+      if (i + u + 3 < n) {
+        *(u32x4 *)(hist + i + u) = q;
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (i + u + e < n) hist[i + u + e] = q[e];
+      }
     }
     carry += total;
     __syncthreads();   // wtot is rewritten by the next tile
   }
 }
 
-__global__ __launch_bounds__(64) void k_radix_scatter(const uint32_t *__restrict__ keys,
-                                                      const int32_t *__restrict__ vals, int64_t N,
-                                                      int shift, int nchunks,
-                                                      const uint32_t *__restrict__ hist,
-                                                      uint32_t *__restrict__ keys_out,
-                                                      int32_t *__restrict__ vals_out) {
-  __shared__ uint32_t base[256];
-  const int lane = threadIdx.x;
-  for (int d = lane; d < 256; d += 64) base[d] = hist[(size_t)d * nchunks + blockIdx.x];
-  __syncthreads();
-  const int64_t b = (int64_t)blockIdx.x * kSortChunk;
-  const uint64_t lt = lane == 0 ? 0ull : (~0ull >> (64 - lane));
-  for (int i0 = 0; i0 < kSortChunk; i0 += 64) {
-    const int64_t g = b + i0 + lane;
-    const bool ok = g < N;
-    const uint32_t key = ok ? keys[g] : 0u;
-    const int32_t val = ok ? (vals ? vals[g] : (int32_t)g) : 0;
-    const uint32_t d = (key >> shift) & 255u;
-    uint64_t peers = __builtin_amdgcn_ballot_w64(ok);
+// the lanes that are on and hold the same digit as this one
+__device__ __forceinline__ uint64_t digit_peers(uint32_t d, int bits, bool on) {
+  uint64_t peers = __builtin_amdgcn_ballot_w64(on);
+  for (int bit = 0; bit < bits; ++bit) {
+    const uint64_t bal = __builtin_amdgcn_ballot_w64((d >> bit) & 1u);
+    peers &= ((d >> bit) & 1u) ? bal : ~bal;
+  }
+  return peers;
+}
+// A wave's own LDS accesses complete in program order; this keeps the compiler to that order.
+__device__ __forceinline__ void wave_lds_order() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_wave_barrier();
+}
+
+// vals_in NULL: element i carries i.  keys_out may be NULL (nobody reads them).
+__global__ __launch_bounds__(256) void k_radix_scatter(const uint32_t *__restrict__ keys,
+                                                       const int32_t *__restrict__ vals_in, int64_t N,
+                                                       int shift, int bits, int nchunks,
+                                                       const uint32_t *__restrict__ hist,
+                                                       uint32_t *__restrict__ keys_out,
+                                                       int32_t *__restrict__ vals_out) {
+  __shared__ uint32_t base[4][256];   // per wave: elements of a digit counted, then the next position
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const uint32_t mask = (1u << bits) - 1u;
+  const int64_t b = (int64_t)blockIdx.x * kSortChunk + wave * 256;
+  const uint64_t below = lane == 0 ? 0ull : (~0ull >> (64 - lane));
+  uint32_t key[4];
+  int32_t val[4];
 #pragma unroll
-    for (int bit = 0; bit < 8; ++bit) {
-      const uint64_t bal = __builtin_amdgcn_ballot_w64((d >> bit) & 1u);
-      peers &= ((d >> bit) & 1u) ? bal : ~bal;
+  for (int i = 0; i < 4; ++i) {
+    const int64_t g = b + i * 64 + lane;
+    key[i] = g < N ? keys[g] : 0u;
+    val[i] = g < N ? (vals_in ? vals_in[g] : (int32_t)g) : 0;
+  }
+#pragma unroll
+  for (int w = 0; w < 4; ++w) base[w][tid] = 0u;
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+    if (b + i * 64 + lane < N) atomicAdd(&base[wave][(key[i] >> shift) & mask], 1u);
+  __syncthreads();
+  if (tid <= (int)mask) {
+    uint32_t run = hist[(size_t)tid * nchunks + blockIdx.x];
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+      const uint32_t c = base[w][tid];
+      base[w][tid] = run;
+      run += c;
     }
-    const uint32_t rank = (uint32_t)__popcll(peers & lt);
-    const uint32_t cnt = (uint32_t)__popcll(peers);
-    uint32_t pos = 0;
-    if (ok) pos = base[d] + rank;
-    __syncthreads();
-    if (ok && rank == cnt - 1) base[d] += cnt;   // one lane per digit present
-    __syncthreads();
+  }
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const bool ok = b + i * 64 + lane < N;
+    const uint32_t d = (key[i] >> shift) & mask;
+    const uint64_t peers = digit_peers(d, bits, ok);
+    const uint32_t rank = (uint32_t)__popcll(peers & below), cnt = (uint32_t)__popcll(peers);
+    const uint32_t at = base[wave][d];
+    wave_lds_order();
+    if (ok && rank == cnt - 1) base[wave][d] = at + cnt;   // one lane per digit present
+    wave_lds_order();
     if (ok) {
-      keys_out[pos] = key;
-      vals_out[pos] = val;
+      if (keys_out) keys_out[at + rank] = key[i];
+      vals_out[at + rank] = val[i];
     }
   }
 }
 
-__global__ __launch_bounds__(256) void k_csr_finish(const uint32_t *__restrict__ keys,
-                                                    const int32_t *__restrict__ vals, int64_t N,
-                                                    int64_t M, int32_t *__restrict__ group_off,
-                                                    int32_t *__restrict__ group_mem) {
+// group_off from the sorted slots (every slot has a member: its own kept token)
+__global__ __launch_bounds__(256) void k_csr_finish(const uint32_t *__restrict__ keys, int64_t N,
+                                                    int64_t M, int32_t *__restrict__ group_off) {
   const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (j >= N) return;
-  group_mem[j] = vals[j];
   const uint32_t k = keys[j];
   if ((j == 0 || keys[j - 1] != k) && (int64_t)k < M) group_off[k] = (int32_t)j;
   if (j == N - 1) group_off[M] = (int32_t)N;
+}
+
+// Short sequences: the whole sort in one workgroup.  An element is slot << 14 | token; wave w
+// owns elements w * per .. in steps of 64, ranks them against the earlier ones of its own with
+// the same digit (two passes of 7 bits), and the positions follow from one scan over the
+// counters of all digits and waves.  The elements are in registers while they are moved, so one
+// LDS array serves both passes.  Up to kCsrSmall tokens, where its time on one CU (about 8 us at
+// 522 tokens, 20 at 16384) is below the seven launches of the general way (35-40 us).
+constexpr int kCsrSmall = 16384;
+constexpr int kCsrSteps = kCsrSmall / 1024;   // 64-element steps per wave, at most
+
+__global__ __launch_bounds__(1024) void k_csr_small(const int32_t *__restrict__ slot_of, int N, int M,
+                                                    int32_t *__restrict__ group_off,
+                                                    int32_t *__restrict__ group_mem) {
+  extern __shared__ uint32_t elem[];            // [N]
+  __shared__ uint32_t cnt[128 * 16];            // [digit][wave]
+  __shared__ uint32_t wtot[16];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const uint64_t below = lane == 0 ? 0ull : (~0ull >> (64 - lane));
+  const int steps = (N + 1023) / 1024, b = wave * steps * 64 + lane;
+  uint32_t e[kCsrSteps], rk[kCsrSteps];
+#pragma unroll
+  for (int i = 0; i < kCsrSteps; ++i) {
+    const int g = b + i * 64;
+    e[i] = i < steps && g < N ? (uint32_t)slot_of[g] << 14 | (uint32_t)g : 0u;
+  }
+  for (int pass = 0; pass < 2; ++pass) {
+    const int shift = 14 + 7 * pass;
+    cnt[tid] = 0u;
+    cnt[tid + 1024] = 0u;
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kCsrSteps; ++i) {
+      if (i < steps) {
+        const bool ok = b + i * 64 < N;
+        const uint32_t d = (e[i] >> shift) & 127u;
+        const uint64_t peers = digit_peers(d, 7, ok);
+        const uint32_t r = (uint32_t)__popcll(peers & below), n = (uint32_t)__popcll(peers);
+        const uint32_t at = cnt[d * 16 + wave];
+        wave_lds_order();
+        if (ok && r == n - 1) cnt[d * 16 + wave] = at + n;
+        wave_lds_order();
+        rk[i] = at + r;
+      }
+    }
+    __syncthreads();
+    const uint32_t c0 = cnt[2 * tid], c1 = cnt[2 * tid + 1];
+    const uint32_t inc = wave_scan(c0 + c1, lane);
+    if (lane == 63) wtot[wave] = inc;
+    __syncthreads();
+    uint32_t run = inc - c0 - c1;
+    for (int w = 0; w < wave; ++w) run += wtot[w];
+    cnt[2 * tid] = run;
+    cnt[2 * tid + 1] = run + c0;
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kCsrSteps; ++i)
+      if (i < steps && b + i * 64 < N) elem[cnt[((e[i] >> shift) & 127u) * 16 + wave] + rk[i]] = e[i];
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kCsrSteps; ++i)
+      if (i < steps && b + i * 64 < N) e[i] = elem[b + i * 64];
+    __syncthreads();
+  }
+#pragma unroll
+  for (int i = 0; i < kCsrSteps; ++i) {
+    const int j = b + i * 64;
+    if (i < steps && j < N) {
+      const int slot = (int)(e[i] >> 14);
+      group_mem[j] = (int32_t)(e[i] & 0x3fffu);
+      if (slot < M && (j == 0 || (int)(elem[j - 1] >> 14) != slot)) group_off[slot] = j;
+    }
+  }
+  if (tid == 0) group_off[M] = N;
 }
 
 // ---------------------------------------------------------------------------------
@@ -779,25 +921,33 @@ int launch_match(const uint16_t *x, const Dims &d, const litevggt_plan_t &pl,
     LV_HIP_CHECK_LAUNCH();
   }
   // CSR groups by stable radix sort of slot_of
+  if (d.N <= kCsrSmall) {   // M <= N: slots fit 14 bits
+    const size_t lds = align_up((size_t)d.N * sizeof(uint32_t), 16);
+    static std::atomic<uint64_t> lds_done{0};
+    if (int rc = allow_dynamic_lds((const void *)k_csr_small, kCsrSmall * sizeof(uint32_t), lds_done)) return rc;
+    hipLaunchKernelGGL(k_csr_small, dim3(1), dim3(1024), lds, st, (const int32_t *)ix.slot_of, (int)d.N, (int)pl.M,
+                       ix.group_off, ix.group_mem);
+    LV_HIP_CHECK_LAUNCH();
+    return LV_OK;
+  }
   int bits = 1;
   while (((int64_t)1 << bits) < pl.M) ++bits;
-  const int passes = (bits + 7) / 8;
+  const int passes = (bits + 7) / 8, per_pass = (bits + passes - 1) / passes;
   const uint32_t *kin = (const uint32_t *)ix.slot_of;
   const int32_t *vin = nullptr;
   for (int p = 0; p < passes; ++p) {
     uint32_t *kout = w.keys[p & 1];
-    int32_t *vout = w.vals[p & 1];
-    hipLaunchKernelGGL(k_radix_hist, dim3((unsigned)w.nchunks), dim3(64), 0, st, kin, d.N, 8 * p,
-                       w.nchunks, w.hist);
-    hipLaunchKernelGGL(k_radix_scan, dim3(1), dim3(1024), 0, st, w.hist,
-                       (int64_t)256 * w.nchunks);
-    hipLaunchKernelGGL(k_radix_scatter, dim3((unsigned)w.nchunks), dim3(64), 0, st, kin, vin, d.N,
-                       8 * p, w.nchunks, w.hist, kout, vout);
+    int32_t *vout = p == passes - 1 ? ix.group_mem : w.vals[p & 1];
+    hipLaunchKernelGGL(k_radix_hist, dim3((unsigned)w.nchunks), dim3(256), 0, st, kin, d.N, per_pass * p,
+                       1 << per_pass, w.nchunks, w.hist);
+    hipLaunchKernelGGL(k_radix_scan, dim3(1), dim3(1024), 0, st, w.hist, (int64_t)w.nchunks << per_pass);
+    hipLaunchKernelGGL(k_radix_scatter, dim3((unsigned)w.nchunks), dim3(256), 0, st, kin, vin, d.N,
+                       per_pass * p, per_pass, w.nchunks, w.hist, kout, vout);
     kin = kout;
     vin = vout;
   }
-  hipLaunchKernelGGL(k_csr_finish, dim3((unsigned)((d.N + 255) / 256)), dim3(256), 0, st, kin, vin,
-                     d.N, pl.M, ix.group_off, ix.group_mem);
+  hipLaunchKernelGGL(k_csr_finish, dim3((unsigned)((d.N + 255) / 256)), dim3(256), 0, st, kin, d.N, pl.M,
+                     ix.group_off);
   LV_HIP_CHECK_LAUNCH();
   return LV_OK;
 }

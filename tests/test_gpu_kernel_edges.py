@@ -128,3 +128,17 @@ def test_match_near_equal_rows_of_many_sweeps(B):
     src = ib.src_idx[:pl.n_src].long()
     # frame 0 is all dst, so every src token has its exact copy there, and no dst precedes it
     assert torch.equal(ib.anchor_of[src].long(), src % (pl.N // 40))
+
+
+# groups: the largest sequence one workgroup sorts, the smallest beyond it, a chunk of the general
+# sort that ends on a wave's last element, and one slot count above 16 bits (three digit passes)
+@pytest.mark.parametrize("frames,h,w,special,ratio", [(64, 15, 17, 1, 0.9), (5, 52, 63, 1, 0.5), (2, 1, 1, 0, 0.0),
+                                                      (17, 32, 32, 0, 0.75), (70, 32, 32, 2, 0.0)])
+def test_groups_edges(B, frames, h, w, special, ratio):
+    import torch
+    ph = B.make_params(frames, h, w, 64, 1, n_special=special, merge_ratio=ratio)
+    pl = B.litevggt_plan(ph)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(7)
+    x = torch.randn(pl.N, 64, generator=g, device="cuda").to(torch.bfloat16)
+    _check_index(B, ph, x)
