@@ -324,10 +324,13 @@ __global__ __launch_bounds__(256) void k_quant_pack_fp8(const uint16_t *__restri
 
 // ---------------------------------------------------------------------------------------
 // Y[M, Nout] = A[M, K] W[Nout, K]^T + bias (optionally GELU), bf16 in and out, fp32
-// accumulation.  Same machinery as the similarity kernel of the matching step: 256 x 256
-// output tiles, both operands pre-packed fragment-major, fetched straight into a 4-stage LDS
-// ring (2 k-steps per stage, 3 stages ahead), fragments read by hand one k-step ahead, 8 waves
-// of 64 rows x 128 columns.  The finished tile goes from the accumulators straight to global
+// accumulation.  Output tiles of BM rows x 256 columns, waves of 64 rows x 128 columns; both
+// operands come pre-packed fragment-major and are fetched straight into an LDS ring (2 k-steps
+// per stage).  BM = 256: 8 waves, 4 stages, one workgroup per CU, 128 flop per fetched byte.
+// BM = 128: 4 waves, 3 stages, two workgroups per CU, whose epilogues run beside each other's
+// main loops: for row counts that fill the chip badly with 256-row tiles (half_tiles).  Bound by
+// the matrix pipe and what keeps a wave from feeding it: issuing the fetches, the barrier, the
+// fragment reads; the MFMAs alone take 70 % of the loop's time.  The finished tile goes from the accumulators straight to global
 // memory (bias, optional GELU, one rounding to bf16); `addend` (optional, shaped like the
 // output) is added to the rounded result on the way out.  The ring is free meanwhile, so the
 // next tile's first stages are fetched during the epilogue.
@@ -339,17 +342,23 @@ __global__ __launch_bounds__(256) void k_quant_pack_fp8(const uint16_t *__restri
 // FP8: the same ring and the same byte traffic per stage, but a stage (two 1 KB units per
 // fragment) is one k-step of 64 for v_mfma_f32_32x32x64_f8f6f4, whose operands are the two
 // units of a fragment side by side in 8 registers: per stage a wave issues 8 MFMAs of twice
-// the work.  The activation fragments of the next stage go to a second register set at the
-// start of a stage, the weight fragments replace those of the current stage pair by pair as
-// its MFMAs have been issued.  `alpha` (FP8: the product of the two scales) multiplies the
+// the work.  `alpha` (FP8: the product of the two scales) multiplies the
 // accumulators before the bias.
 // ---------------------------------------------------------------------------------------
 __device__ __forceinline__ void lds_read1_async(u32x4 &dst, uint32_t addr) {
   asm volatile("ds_read_b128 %0, %1" : "=&v"(dst) : "v"(addr) : "memory");
 }
-constexpr int kTile = 256;
-constexpr int kStages = 4;
-constexpr int kStageU4 = 2 * 2 * 8 * 64;     // [weights|activations][2 k-steps][8 fragments][64 lanes]
+constexpr int kTile = 256;                   // output channels per workgroup tile, and what rows are padded to
+// Shape of a workgroup with BM rows per tile: BM / 32 waves of 64 rows x 128 columns.
+template <int BM>
+struct GemmShape {
+  static constexpr int kWaves = BM / 32, kThreads = kWaves * 64;
+  static constexpr int kFragA = BM / 32;                  // activation fragments per k-step (8 of weights)
+  static constexpr int kStageU4 = 2 * (8 + kFragA) * 64;  // [weights: 2 k-steps x 8 | activations: 2 x kFragA][64 lanes]
+  static constexpr int kStages = BM == 256 ? 4 : 3;       // LDS ring: 128 KB, one workgroup per CU; or 72 KB, two
+  static constexpr int kLoads = 2 * (8 + kFragA) / kWaves;   // fragments a wave fetches per stage
+  static constexpr size_t kLds = (size_t)kStages * kStageU4 * 16 + 2 * kTile * sizeof(float);   // + two tiles' bias values
+};
 
 // GELU in its erf form, x * Phi(x).  erfc(|x| / sqrt 2) by the rational-times-exponential form of
 // Abramowitz & Stegun 7.1.26 (absolute error <= 1.5e-7, four orders below a bf16 step); the
@@ -366,89 +375,101 @@ __device__ __forceinline__ float gelu_erf(float v) {
   return 0.5f * v * (v < 0.f ? erfc_abs : 2.0f - erfc_abs);
 }
 
-template <bool FP8, bool PACKED>
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_gemm_bt(
+template <bool FP8, bool PACKED, int BM>
+__global__ __launch_bounds__(GemmShape<BM>::kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_gemm_bt(
     const u32x4 *__restrict__ ap, const u32x4 *__restrict__ wp, int64_t M, int KS, int nt_n,
     const float *__restrict__ bias, int gelu, uint16_t *__restrict__ out, int split,
     const float *__restrict__ alpha_p, int n_tiles, const uint16_t *__restrict__ addend,
     const uint32_t *__restrict__ out_inv, uint32_t *__restrict__ out_amax) {
+  using S = GemmShape<BM>;
+  constexpr int kStages = S::kStages, kStageU4 = S::kStageU4;
   extern __shared__ u32x4 ring[];
   const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wd = wave & 3, wn = wave >> 2;
+  const int wd = wave % (BM / 64), wn = wave / (BM / 64);
   const int total = KS >> 1;
   // persistent: one workgroup per CU walks the tiles (a workgroup owns a whole CU's LDS, so a
   // launch per tile would pay a dispatch between any two tiles of a CU)
   // Workgroup w runs on XCD w % 8.  An XCD takes the row tiles tm = x, x + 8, ..., so an
-  // activation tile is fetched into one L2 only.  Its workgroups form a block of Rb row tiles x G
-  // column tiles (8 x 4 with 32 workgroups) that takes one group of G column tiles through all
-  // the XCD's row tiles before it moves to the next group: the G weight tiles of a group (2 MB
-  // at K = 1024) stay in that L2 meanwhile, and an activation tile is shared by G workgroups.
+  // activation tile is fetched into one L2 only, and walks its tiles one group of G = 4 column
+  // tiles after the other, row by row inside a group: the G weight tiles of a group (2 MB at
+  // K = 1024) stay in that L2 meanwhile, and an activation tile is shared by G workgroups.  Its
+  // workgroups take this list in turn, so they differ by one tile at most.  With no more tiles than
+  // workgroups each takes one and the order does not matter.
   const int nt_m = n_tiles / nt_n;
-  const int xcd = blockIdx.x & (kXcd - 1), per_xcd = (int)gridDim.x >> 3;
-  const int G = nt_n < 4 ? nt_n : 4, Rb = per_xcd / G;
-  const bool by_xcd = (gridDim.x & (kXcd - 1)) == 0 && Rb >= 1;
-  const int my_rows = by_xcd ? (nt_m - xcd + kXcd - 1) / kXcd : 0;   // row tiles of this XCD
-  const int n_rb = by_xcd ? (my_rows + Rb - 1) / Rb : 0, n_cg = (nt_n + G - 1) / G;
-  const int jr = (int)(blockIdx.x >> 3) / G, jc = (int)(blockIdx.x >> 3) % G;
-  const int n_steps = by_xcd ? n_rb * n_cg : (n_tiles + (int)gridDim.x - 1) / (int)gridDim.x;
-  // the first step >= k at which this workgroup has a tile (n_steps if none), and that tile
-  auto next_step = [&](int k, int &tm_, int &tn_) {
-    for (; k < n_steps; ++k) {
-      if (by_xcd) {
-        const int cg = k / n_rb, rb = k - cg * n_rb, lr = rb * Rb + jr, col = cg * G + jc;
-        if (jr < Rb && lr < my_rows && col < nt_n) {
-          tm_ = lr * kXcd + xcd;
-          tn_ = col;
-          break;
-        }
-      } else {
-        const int v = (int)blockIdx.x + k * (int)gridDim.x;
-        if (v < n_tiles) {
-          tm_ = v / nt_n;
-          tn_ = v % nt_n;
-          break;
-        }
-      }
+  const int xcd = blockIdx.x & (kXcd - 1);
+  const bool by_xcd = (gridDim.x & (kXcd - 1)) == 0 && n_tiles > (int)gridDim.x;
+  const int my_rows = by_xcd ? (nt_m - xcd + kXcd - 1) / kXcd : nt_m;   // row tiles of this XCD
+  const int my_tiles = my_rows * nt_n, stride = by_xcd ? (int)gridDim.x >> 3 : (int)gridDim.x;
+  const int n_group = my_rows * 4;                                     // tiles of a full column group
+  auto tile_at = [&](int v, int &tm_, int &tn_) {                      // tile v of the list (v < my_tiles)
+    if (by_xcd) {
+      const int cg = v / n_group, in = v - cg * n_group, width = min(4, nt_n - cg * 4);
+      tm_ = in / width * kXcd + xcd;
+      tn_ = cg * 4 + in % width;
+    } else {
+      tm_ = v / nt_n;
+      tn_ = v % nt_n;
     }
-    return k;
   };
   bool primed = false;   // the previous tile's epilogue has issued this tile's first stages
   int parity = 0;
-  int tm = 0, tn = 0, tm2 = 0, tn2 = 0, k2 = 0;
-  for (int k = next_step(0, tm, tn); k < n_steps; k = k2, tm = tm2, tn = tn2, parity ^= 1) {
-  k2 = next_step(k + 1, tm2, tn2);
+  int tm = 0, tn = 0, tm2 = 0, tn2 = 0;
+  for (int v = by_xcd ? (int)blockIdx.x >> 3 : (int)blockIdx.x; v < my_tiles; v += stride, parity ^= 1) {
+  tile_at(v, tm, tn);
+  const bool more = v + stride < my_tiles;
+  if (more) tile_at(v + stride, tm2, tn2);
   // this tile's 256 bias values wait in LDS behind the ring (read in the epilogue, many barriers
   // later); two buffers in turn, so a wave still in the previous tile's epilogue reads its own
   float *bias_lds = (float *)(ring + (size_t)kStages * kStageU4) + parity * kTile;
   if (tid < kTile) bias_lds[tid] = bias ? bias[tn * kTile + tid] : 0.f;
 
-  // fetch: this wave moves fragments f = 4*wave .. 4*wave+3 of a stage (f = op*16 + ks*8 + a)
-  const int f_op = wave >> 2, f_ks = (wave >> 1) & 1, f_a0 = (wave & 1) * 4;
+  // fetch: with 8 waves, waves 0-3 move 4 weight fragments of a stage each, waves 4-7 4 activation
+  // fragments; with 4 waves each moves 4 weight and 2 activation fragments
+  const int f_ks = (wave >> 1) & 1;
   int pf_g = 0, f_tm = tm, f_tn = tn;
-  auto fetch = [&]() {
+  auto slot_of = [](int g) { return kStages == 4 ? g & 3 : g % kStages; };
+  const u32x4 *f_src[2];   // this wave's next weight and activation fragments (8 waves: [0] is either)
+  u32x4 *f_dst[2];
+  auto fetch_begin = [&]() {
     const int s = pf_g < total ? pf_g : total - 1;   // past the end: the last stage again, into a free slot
-    const u32x4 *src = (f_op ? ap + (size_t)(f_tm * 8 + f_a0) * KS * 64 : wp + (size_t)(f_tn * 8 + f_a0) * KS * 64) +
-                       (size_t)(s * 2 + f_ks) * 64 + lane;
-    u32x4 *dst = ring + (size_t)(pf_g & (kStages - 1)) * kStageU4 + (size_t)(wave * 4) * 64;
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-      __builtin_amdgcn_global_load_lds(src + (size_t)i * KS * 64, dst + i * 64, 16, 0, 0);
+    const size_t at = (size_t)(s * 2 + f_ks) * 64;   // uniform: the lane is added in the load
+    u32x4 *stage = ring + (size_t)slot_of(pf_g) * kStageU4;
+    if constexpr (S::kWaves == 8) {
+      const int a0 = (wave & 1) * 4;
+      f_src[0] = (wave >> 2 ? ap + (size_t)(f_tm * 8 + a0) * KS * 64 : wp + (size_t)(f_tn * 8 + a0) * KS * 64) + at;
+      f_dst[0] = stage + (size_t)(wave * 4) * 64;
+    } else {
+      f_src[0] = wp + (size_t)(f_tn * 8 + (wave & 1) * 4) * KS * 64 + at;
+      f_src[1] = ap + (size_t)(f_tm * S::kFragA + (wave & 1) * (S::kFragA / 2)) * KS * 64 + at;
+      f_dst[0] = stage + (size_t)(wave * 4) * 64;
+      f_dst[1] = stage + (size_t)(16 + wave * (S::kFragA / 2)) * 64;
+    }
     ++pf_g;
   };
-  const uint32_t ring_lane = lds_addr(&ring[lane]);
-  const uint32_t b_off = (uint32_t)((wn * 4) * 1024), a_off = (uint32_t)((16 + wd * 2) * 1024);
-  u32x4 fb[2][4], fa[2][2];
-  auto read_frags = [&](int g, int ks, u32x4(&b)[4], u32x4(&a)[2]) {
-    const uint32_t base = ring_lane + (uint32_t)((g & (kStages - 1)) * kStageU4 * 16 + ks * 8 * 1024);
-    lds_read4_async(b, base + b_off);
-    lds_read2_async(a, base + a_off);
+  auto fetch_one = [&](auto idx) {
+    constexpr int i = decltype(idx)::value;
+    if constexpr (i < S::kLoads)
+      __builtin_amdgcn_global_load_lds(f_src[i >> 2] + (size_t)(i & 3) * KS * 64 + lane, f_dst[i >> 2] + (i & 3) * 64, 16, 0, 0);
   };
-  auto wait_frags = [&](u32x4(&b)[4], u32x4(&a)[2]) {
-    asm volatile("s_waitcnt lgkmcnt(0)"
-                 : "+v"(b[0]), "+v"(b[1]), "+v"(b[2]), "+v"(b[3]), "+v"(a[0]), "+v"(a[1])
-                 :
-                 : "memory");
+  auto fetch = [&]() {
+    fetch_begin();
+    fetch_one(std::integral_constant<int, 0>{});
+    fetch_one(std::integral_constant<int, 1>{});
+    fetch_one(std::integral_constant<int, 2>{});
+    fetch_one(std::integral_constant<int, 3>{});
+    fetch_one(std::integral_constant<int, 4>{});
+    fetch_one(std::integral_constant<int, 5>{});
+  };
+  const uint32_t ring_lane = lds_addr(&ring[lane]);
+  // byte offsets of this wave's fragments inside a stage, k-step 0, and from k-step 0 to k-step 1
+  const uint32_t b_off = (uint32_t)((wn * 4) * 1024), a_off = (uint32_t)((16 + wd * 2) * 1024);
+  constexpr uint32_t b_ks = 8 * 1024, a_ks = S::kFragA * 1024;
+  u32x4 fb[FP8 ? 1 : 2][2][4], fa[2][2][2];   // [set][k-step (FP8: unit of 32)][fragment]
+  auto read_frags = [&](int g, int ks, u32x4(&b)[4], u32x4(&a)[2]) {
+    const uint32_t base = ring_lane + (uint32_t)(slot_of(g) * kStageU4 * 16);
+    lds_read4_async(b, base + b_off + ks * b_ks);
+    lds_read2_async(a, base + a_off + ks * a_ks);
   };
   f32x16 acc[2][4];
 #pragma unroll
@@ -457,91 +478,116 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     for (int b = 0; b < 4; ++b)
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[a][b][r] = 0.f;
-  auto mma = [&](const u32x4(&b)[4], const u32x4(&a)[2]) {
-#pragma unroll
-    for (int bi = 0; bi < 4; ++bi)
-#pragma unroll
-      for (int ai = 0; ai < 2; ++ai)
-        acc[ai][bi] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, b[bi]),
-                                                             __builtin_bit_cast(bf16x8, a[ai]),
-                                                             acc[ai][bi], 0, 0, 0);
-  };
-
   if (primed) {
     pf_g = kStages;
     // the stages were issued ahead of the previous epilogue's stores: wait for everything
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   } else {
 #pragma unroll
-    for (int i = 0; i < kStages; ++i) fetch();               // stages 0..3
-    asm volatile("s_waitcnt vmcnt(12)" ::: "memory");        // stage 0 has landed (this wave's part)
+    for (int i = 0; i < kStages; ++i) fetch();               // the ring's stages
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"((kStages - 1) * S::kLoads) : "memory");   // stage 0 has landed (this wave's part)
   }
   __builtin_amdgcn_s_barrier();
-  if constexpr (!FP8) {
-    read_frags(0, 0, fb[0], fa[0]);
-    for (int g = 0; g < total; ++g) {
-      __builtin_amdgcn_sched_barrier(0);
-      wait_frags(fb[0], fa[0]);
-      read_frags(g, 1, fb[1], fa[1]);
-      __builtin_amdgcn_sched_barrier(0);
-      mma(fb[0], fa[0]);
-      __builtin_amdgcn_sched_barrier(0);
-      wait_frags(fb[1], fa[1]);
-      asm volatile("s_waitcnt vmcnt(8)" ::: "memory");         // stage g+1 has landed; g+2, g+3 may be in flight
-      __builtin_amdgcn_s_barrier();
-      fetch();                                                 // stage g+4 -> slot of stage g
-      read_frags(g + 1, 0, fb[0], fa[0]);                      // past the end: a stale slot, never used
-      __builtin_amdgcn_sched_barrier(0);
-      mma(fb[1], fa[1]);
-    }
-  } else {
-    // fb[u][bi], fa[set][u][ai]: unit u of a fragment; an operand is (unit 0, unit 1)
-    u32x4 fa2[2][2][2];
-    read_frags(0, 0, fb[0], fa2[0][0]);
-    read_frags(0, 1, fb[1], fa2[0][1]);
-    auto stage = [&](int g, u32x4(&ac)[2][2], u32x4(&an)[2][2]) {
-      __builtin_amdgcn_sched_barrier(0);
-      asm volatile("s_waitcnt lgkmcnt(0)"
-                   : "+v"(fb[0][0]), "+v"(fb[0][1]), "+v"(fb[0][2]), "+v"(fb[0][3]), "+v"(fb[1][0]),
-                     "+v"(fb[1][1]), "+v"(fb[1][2]), "+v"(fb[1][3]), "+v"(ac[0][0]), "+v"(ac[0][1]),
-                     "+v"(ac[1][0]), "+v"(ac[1][1])
-                   :
-                   : "memory");
-      asm volatile("s_waitcnt vmcnt(8)" ::: "memory");       // stage g+1 has landed; g+2, g+3 may be in flight
-      __builtin_amdgcn_s_barrier();                          // and nobody reads stage g from LDS any more
-      fetch();                                               // stage g+4 -> slot of stage g
-      // past the end these read a stale slot; the values are never used
-      const uint32_t base = ring_lane + (uint32_t)(((g + 1) & (kStages - 1)) * kStageU4 * 16);
-      lds_read2_async(an[0], base + a_off);
-      lds_read2_async(an[1], base + 8 * 1024 + a_off);
-#pragma unroll
-      for (int bi = 0; bi < 4; ++bi) {
-        __builtin_amdgcn_sched_barrier(0);
-        const i32x8 b8 = cat8(fb[0][bi], fb[1][bi]);
-#pragma unroll
-        for (int ai = 0; ai < 2; ++ai)
-          acc[ai][bi] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(b8, cat8(ac[0][ai], ac[1][ai]),
-                                                                        acc[ai][bi], 0, 0, 0, 0, 0, 0);
-        __builtin_amdgcn_sched_barrier(0);
-        lds_read1_async(fb[0][bi], base + b_off + bi * 1024);
-        lds_read1_async(fb[1][bi], base + 8 * 1024 + b_off + bi * 1024);
-      }
-    };
-    int g = 0;
-    for (; g + 1 < total; g += 2) {
-      stage(g, fa2[0], fa2[1]);
-      stage(g + 1, fa2[1], fa2[0]);
-    }
-    if (g < total) stage(g, fa2[0], fa2[1]);
-    // the reads issued by the last stage are waited for below, before their registers die
+  // Steady state: all fragments of a stage are in registers while its MFMAs run, and those of the
+  // next stage are read meanwhile: into a second set, a whole stage ahead of their use (bf16), or,
+  // where the registers do not hold two sets of weight fragments beside the 8-register operands
+  // (FP8), the activations into a second set and each weight fragment into its own registers once
+  // its MFMAs have been issued.  The barrier, the reads and the fetch instructions, one or two at a
+  // time (a wave that issues a stage's 4 or 6 back to back waits for the address unit, and its
+  // MFMAs with it), sit between pairs of MFMAs, so that the MFMA pipe has queued work of this wave
+  // while it does them.  (All of it behind the barrier at the head of a k-step: 1046 us for the qkv
+  // layer at M = 143,232, C = 1024 in bf16, 900 like this.)
+  auto wait_set = [&](u32x4(&b)[2][4], u32x4(&a)[2][2]) {
     asm volatile("s_waitcnt lgkmcnt(0)"
-                 : "+v"(fb[0][0]), "+v"(fb[0][1]), "+v"(fb[0][2]), "+v"(fb[0][3]), "+v"(fb[1][0]),
-                   "+v"(fb[1][1]), "+v"(fb[1][2]), "+v"(fb[1][3]), "+v"(fa2[0][0][0]), "+v"(fa2[0][0][1]),
-                   "+v"(fa2[0][1][0]), "+v"(fa2[0][1][1]), "+v"(fa2[1][0][0]), "+v"(fa2[1][0][1]),
-                   "+v"(fa2[1][1][0]), "+v"(fa2[1][1][1])
+                 : "+v"(b[0][0]), "+v"(b[0][1]), "+v"(b[0][2]), "+v"(b[0][3]), "+v"(b[1][0]), "+v"(b[1][1]),
+                   "+v"(b[1][2]), "+v"(b[1][3]), "+v"(a[0][0]), "+v"(a[0][1]), "+v"(a[1][0]), "+v"(a[1][1])
                  :
                  : "memory");
+  };
+  // the two MFMAs of column block bi: of k-step u, or (FP8) of both, whose units lie side by side
+  auto pair = [&](const u32x4(&b)[2][4], const u32x4(&a)[2][2], int u, int bi) {
+#pragma unroll
+    for (int ai = 0; ai < 2; ++ai) {
+      if constexpr (FP8)
+        acc[ai][bi] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(cat8(b[0][bi], b[1][bi]), cat8(a[0][ai], a[1][ai]),
+                                                                      acc[ai][bi], 0, 0, 0, 0, 0, 0);
+      else
+        acc[ai][bi] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, b[u][bi]),
+                                                             __builtin_bit_cast(bf16x8, a[u][ai]), acc[ai][bi], 0, 0, 0);
+    }
+  };
+  auto ld = [&](auto i) {
+    __builtin_amdgcn_sched_barrier(0);
+    fetch_one(i);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+#define LV_LD(i) ld(std::integral_constant<int, i>{})
+  auto stage = [&](int g, u32x4(&bc)[2][4], u32x4(&ac)[2][2], u32x4(&bn)[2][4], u32x4(&an)[2][2]) {
+    __builtin_amdgcn_sched_barrier(0);
+    wait_set(bc, ac);
+    if constexpr (!FP8) pair(bc, ac, 0, 0);
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"((kStages - 2) * S::kLoads) : "memory");   // stage g+1 has landed; later ones may be in flight
+    __builtin_amdgcn_s_barrier();                            // and nobody reads stage g from LDS any more
+    __builtin_amdgcn_sched_barrier(0);
+    // stage g + kStages goes to the slot of stage g; past the end the reads get a stale slot, never used
+    if constexpr (FP8) {
+      const uint32_t base = ring_lane + (uint32_t)(slot_of(g + 1) * kStageU4 * 16);
+      auto again = [&](int bi) {                             // the next stage's weight fragment bi
+        __builtin_amdgcn_sched_barrier(0);
+        lds_read1_async(bn[0][bi], base + b_off + bi * 1024);
+        lds_read1_async(bn[1][bi], base + b_ks + b_off + bi * 1024);
+      };
+      lds_read2_async(an[0], base + a_off);
+      lds_read2_async(an[1], base + a_ks + a_off);
+      fetch_begin();
+      LV_LD(0);
+      pair(bc, ac, 0, 0);
+      again(0);
+      LV_LD(1);
+      pair(bc, ac, 0, 1);
+      again(1);
+      LV_LD(2); LV_LD(4);
+      pair(bc, ac, 0, 2);
+      again(2);
+      LV_LD(3); LV_LD(5);
+      pair(bc, ac, 0, 3);
+      again(3);
+    } else {
+      pair(bc, ac, 0, 1);
+      __builtin_amdgcn_sched_barrier(0);
+      read_frags(g + 1, 0, bn[0], an[0]);
+      fetch_begin();
+      LV_LD(0);
+      pair(bc, ac, 0, 2);
+      __builtin_amdgcn_sched_barrier(0);
+      read_frags(g + 1, 1, bn[1], an[1]);
+      __builtin_amdgcn_sched_barrier(0);
+      pair(bc, ac, 0, 3);
+      LV_LD(1);
+      pair(bc, ac, 1, 0);
+      LV_LD(2);
+      pair(bc, ac, 1, 1);
+      LV_LD(3);
+      pair(bc, ac, 1, 2);
+      LV_LD(4);
+      pair(bc, ac, 1, 3);
+      LV_LD(5);
+    }
+  };
+#undef LV_LD
+  read_frags(0, 0, fb[0][0], fa[0][0]);
+  read_frags(0, 1, fb[0][1], fa[0][1]);
+  constexpr int kSetB = FP8 ? 0 : 1;   // the weight set of odd stages
+  int g = 0;
+  for (; g + 1 < total; g += 2) {
+    stage(g, fb[0], fa[0], fb[kSetB], fa[1]);
+    stage(g + 1, fb[kSetB], fa[1], fb[0], fa[0]);
   }
+  if (g < total) stage(g, fb[0], fa[0], fb[kSetB], fa[1]);
+  // the reads issued by the last stage are waited for before their registers die
+  wait_set(fb[0], fa[0]);
+  wait_set(fb[kSetB], fa[1]);
   asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");   // nothing may land in LDS any more
   __syncthreads();
 
@@ -555,7 +601,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   const float alpha = alpha_p ? *alpha_p : 1.0f;
   int anchor = 0;   // opaque zero: keeps the address arithmetic below inside this tile's epilogue
   asm volatile("" : "+v"(anchor));   // (hoisted out of the tile loop it would stay live through the main loop)
-  if (k2 < n_steps) {
+  if (more) {
     f_tn = tn2;
     f_tm = tm2;
     pf_g = 0;
@@ -578,13 +624,13 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       // largest |value| of the rows below M goes into *out_amax; rows beyond M are written as zeros.
       const float r = __uint_as_float(*out_inv);
       const int KSn = nt_n * (kTile / 32);
-      u32x4 *op = (u32x4 *)out + ((size_t)(tm * 8 + wd * 2) * KSn + tn * (kTile / 32) + wn * 4) * 64 + lane + anchor;
+      u32x4 *op = (u32x4 *)out + ((size_t)(tm * S::kFragA + wd * 2) * KSn + tn * (kTile / 32) + wn * 4) * 64 + lane + anchor;
       float m = 0.f;
 #pragma unroll
       for (int b = 0; b < 4; ++b)
 #pragma unroll
         for (int a = 0; a < 2; ++a) {
-          const bool live = (int64_t)tm * kTile + wd * 64 + 32 * a + (lane & 31) < M;
+          const bool live = (int64_t)tm * BM + wd * 64 + 32 * a + (lane & 31) < M;
           uint32_t d[4];
 #pragma unroll
           for (int g = 0; g < 4; ++g) {
@@ -611,7 +657,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       continue;
     }
     const int KSn = nt_n * (kTile / 16);
-    u32x4 *op = (u32x4 *)out + ((size_t)(tm * 8 + wd * 2) * KSn + tn * (kTile / 16) + wn * 8) * 64 + lane + anchor;
+    u32x4 *op = (u32x4 *)out + ((size_t)(tm * S::kFragA + wd * 2) * KSn + tn * (kTile / 16) + wn * 8) * 64 + lane + anchor;
 #pragma unroll
     for (int b = 0; b < 4; ++b)
 #pragma unroll
@@ -663,7 +709,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         const auto s0 = __builtin_amdgcn_permlane32_swap(pack_bf16(v0[0], v0[1]), pack_bf16(v1[0], v1[1]), false, false);
         const auto s1 = __builtin_amdgcn_permlane32_swap(pack_bf16(v0[2], v0[3]), pack_bf16(v1[2], v1[3]), false, false);
         u32x4 t = u32x4{s0[0], s1[0], s0[1], s1[1]};
-        const int64_t m = (int64_t)tm * kTile + wd * 64 + 32 * a + (lane & 31);
+        const int64_t m = (int64_t)tm * BM + wd * 64 + 32 * a + (lane & 31);
         if (addend) {   // out = addend + (this layer's output, already rounded to bf16): one more rounding
           const u32x4 y = m < M ? *(const u32x4 *)(addend + (ob - out) + (size_t)m * split + 32 * b + 16 * gp)
                                 : u32x4{0u, 0u, 0u, 0u};
@@ -734,6 +780,33 @@ struct LinearOpts {
   uint32_t *out_amax = nullptr;        // ... and where the largest |output| is reduced into
 };
 
+// Whether 128-row tiles (two workgroups per CU) beat 256-row tiles (one) on nt_n column tiles.  In
+// units of one 256-row tile's time on one CU (27-36 us at K = 1024 with all CUs busy): 256-row
+// tiles take whole rounds; a round of pairs of 128-row tiles takes 3 % more (half as much again is
+// fetched into LDS; 3-15 % measured), but what is left over, if every CU gets one at most, only
+// 0.6, and 0.72 where there is nothing else.  Measured at C = 1024 in bf16, 128 against 256 rows,
+// layers qkv / out / MLP 1 / MLP 2 in us: M = 394: 18 / 16 / 21 / 51 against 25 / 24 / 29 / 76;
+// 5776: 44 / 19 / 56 / 61 against 55 / 27 / 67 / 83; 15432: 99 / 41 / 140 / 125 against
+// 99 / 35 / 145 / 122; 143232: 952 / 311 / 1242 / 1172 against 890 / 282 / 1183 / 1015.
+static bool half_tiles(int64_t M, int nt_n, int n_cu) {
+  const auto rounds = [&](int rows, int slots, int64_t &rest) {   // of the XCD with the most tiles
+    const int64_t nt_m = (M + rows - 1) / rows, tiles = nt_m * nt_n;
+    if (tiles <= slots) {
+      rest = tiles;
+      return (int64_t)0;
+    }
+    const int64_t per = (nt_m + kXcd - 1) / kXcd * nt_n, s = slots / kXcd > 0 ? slots / kXcd : 1;
+    rest = per % s * kXcd;
+    return per / s;
+  };
+  int64_t rest;
+  const int64_t r256 = rounds(256, n_cu, rest);
+  const double t256 = (double)r256 + (rest ? 1.0 : 0.0);
+  const int64_t r128 = rounds(128, 2 * n_cu, rest);
+  const double t128 = 1.03 * (double)r128 + (rest == 0 ? 0.0 : rest > n_cu ? 1.03 : r128 ? 0.6 : 0.72);
+  return t128 < t256;
+}
+
 // Y = A W^T + bias: brings both operands into operand order where they are not yet (FP8: after
 // taking their amax and quantising them), then the tiled kernel.
 static int launch_linear(const uint16_t *A, int64_t M, int K, const uint16_t *W, int Nout,
@@ -744,21 +817,30 @@ static int launch_linear(const uint16_t *A, int64_t M, int K, const uint16_t *W,
   if (o.pack_out && (o.addend || split != Nout || (o.fp8 && (!o.out_inv || !o.out_amax)))) return LV_ERR_PARAM;
   if (K % 64 != 0 || Nout % kTile != 0 || split % kTile != 0 || Nout % split != 0) return LV_ERR_SHAPE;
   int rc;
-  const size_t lds = (size_t)kStages * kStageU4 * 16 + 2 * kTile * sizeof(float);   // + two tiles' bias values
-  static std::atomic<uint64_t> lds_done[4];
-  if ((rc = allow_dynamic_lds((const void *)k_gemm_bt<false, false>, lds, lds_done[0]))) return rc;
-  if ((rc = allow_dynamic_lds((const void *)k_gemm_bt<true, false>, lds, lds_done[1]))) return rc;
-  if ((rc = allow_dynamic_lds((const void *)k_gemm_bt<false, true>, lds, lds_done[2]))) return rc;
-  if ((rc = allow_dynamic_lds((const void *)k_gemm_bt<true, true>, lds, lds_done[3]))) return rc;
   const int nt_n = Nout / kTile;
-  const int64_t nt_m = w.Mp / kTile;
-  if (nt_m * nt_n >= ((int64_t)1 << 31) || w.Mp >= ((int64_t)1 << 31)) return LV_ERR_SHAPE;
-  const int n_tiles = (int)(nt_m * nt_n);
+  if (w.Mp / kTile * nt_n >= ((int64_t)1 << 30) || w.Mp >= ((int64_t)1 << 31)) return LV_ERR_SHAPE;
   int dev = 0, n_cu = 0;
   if (hipGetDevice(&dev) != hipSuccess ||
       hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n_cu < 1)
     return LV_ERR_HIP;
-  const unsigned grid = (unsigned)(n_tiles < n_cu ? n_tiles : n_cu);
+  const bool half = half_tiles(M, nt_n, n_cu);
+  auto gemm = [&](auto fp8, auto packed, auto bm, const u32x4 *act, int KS, const float *alpha) -> int {
+    constexpr bool F8 = decltype(fp8)::value, PK = decltype(packed)::value;
+    constexpr int BM = decltype(bm)::value;
+    static std::atomic<uint64_t> lds_done{0};
+    if (int rc2 = allow_dynamic_lds((const void *)k_gemm_bt<F8, PK, BM>, GemmShape<BM>::kLds, lds_done)) return rc2;
+    const int n_tiles = (int)((M + BM - 1) / BM) * nt_n, slots = n_cu * (kTile / BM);
+    const unsigned grid = (unsigned)(n_tiles < slots ? n_tiles : slots);
+    hipLaunchKernelGGL((k_gemm_bt<F8, PK, BM>), dim3(grid), dim3(GemmShape<BM>::kThreads), GemmShape<BM>::kLds, st, act,
+                       w_packed, M, KS, nt_n, bias, gelu, out, split, alpha, n_tiles, o.addend, o.out_inv, o.out_amax);
+    return LV_OK;
+  };
+  auto launch = [&](auto fp8, const u32x4 *act, int KS, const float *alpha) -> int {
+    using B128 = std::integral_constant<int, 128>;
+    using B256 = std::integral_constant<int, 256>;
+    if (o.pack_out) return half ? gemm(fp8, std::true_type{}, B128{}, act, KS, alpha) : gemm(fp8, std::true_type{}, B256{}, act, KS, alpha);
+    return half ? gemm(fp8, std::false_type{}, B128{}, act, KS, alpha) : gemm(fp8, std::false_type{}, B256{}, act, KS, alpha);
+  };
   const u32x4 *a_packed = o.a_packed;
   if (o.fp8) {
     auto amax = [&](const uint16_t *t, int64_t n16, uint32_t *dst) {
@@ -787,28 +869,14 @@ static int launch_linear(const uint16_t *A, int64_t M, int K, const uint16_t *W,
       }
       if (o.pack_w) quant(W, Nout, Nout, sc + 3, w_packed, (uint32_t *)nullptr);
     }
-    if (o.pack_out)
-      hipLaunchKernelGGL((k_gemm_bt<true, true>), dim3(grid), dim3(512), lds, st, a_packed, w_packed, M, K / 32,
-                         nt_n, bias, gelu, out, split, (const float *)(sc + 4), n_tiles, o.addend, o.out_inv,
-                         o.out_amax);
-    else
-      hipLaunchKernelGGL((k_gemm_bt<true, false>), dim3(grid), dim3(512), lds, st, a_packed, w_packed, M, K / 32,
-                         nt_n, bias, gelu, out, split, (const float *)(sc + 4), n_tiles, o.addend,
-                         (const uint32_t *)nullptr, (uint32_t *)nullptr);
+    if ((rc = launch(std::true_type{}, a_packed, K / 32, (const float *)(sc + 4)))) return rc;
   } else {
     if (!a_packed) {
       if ((rc = launch_pack_rows(A, M, w.Mp, K, w.apack, st))) return rc;
       a_packed = w.apack;
     }
     if (o.pack_w && (rc = launch_pack_rows(W, Nout, Nout, K, w_packed, st))) return rc;
-    if (o.pack_out)
-      hipLaunchKernelGGL((k_gemm_bt<false, true>), dim3(grid), dim3(512), lds, st, a_packed, w_packed, M, K / 16,
-                         nt_n, bias, gelu, out, split, (const float *)nullptr, n_tiles, o.addend,
-                         (const uint32_t *)nullptr, (uint32_t *)nullptr);
-    else
-      hipLaunchKernelGGL((k_gemm_bt<false, false>), dim3(grid), dim3(512), lds, st, a_packed, w_packed, M, K / 16,
-                         nt_n, bias, gelu, out, split, (const float *)nullptr, n_tiles, o.addend,
-                         (const uint32_t *)nullptr, (uint32_t *)nullptr);
+    if ((rc = launch(std::false_type{}, a_packed, K / 16, nullptr))) return rc;
   }
   LV_HIP_CHECK_LAUNCH();
   return LV_OK;

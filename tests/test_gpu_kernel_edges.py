@@ -142,3 +142,58 @@ def test_groups_edges(B, frames, h, w, special, ratio):
     g.manual_seed(7)
     x = torch.randn(pl.N, 64, generator=g, device="cuda").to(torch.bfloat16)
     _check_index(B, ph, x)
+
+
+# ------------------------------------------------------------------------------- linear layers
+def _block64(z, t, heads):
+    """The transformer block in float64, rounded to bf16 where the block stores its intermediates."""
+    import torch
+    r = lambda a: a.to(torch.bfloat16).double()  # noqa: E731
+
+    def lin(a, w, b):
+        return a @ t[w].double().t().contiguous() + t[b].double()
+
+    def ln(a, g, b):
+        d = a - a.mean(1, keepdim=True)
+        return r(d / torch.sqrt((d * d).mean(1, keepdim=True) + 1e-6) * t[g].double() + t[b].double())
+
+    z, c = z.double(), z.shape[1]
+    qkv = r(lin(ln(z, "ln1_g", "ln1_b"), "w_qkv", "b_qkv"))
+    a = torch.empty_like(z)
+    for h in range(heads):
+        q, k, v = (qkv[:, i * c + h * 64:i * c + h * 64 + 64] for i in range(3))
+        q, k = (r(x / torch.sqrt((x * x).mean(1, keepdim=True) + 1e-6)) for x in (q, k))
+        for i in range(0, len(z), 4096):
+            a[i:i + 4096, h * 64:h * 64 + 64] = torch.softmax(q[i:i + 4096] @ k.t().contiguous() * 0.125, 1) @ v
+    u1 = r(lin(r(a), "w_o", "b_o"))
+    hid = lin(ln(z + u1, "ln2_g", "ln2_b"), "w_1", "b_1")
+    hid = r(0.5 * hid * (1.0 + torch.erf(hid / 2.0 ** 0.5)))
+    return u1 + r(lin(hid, "w_2", "b_2"))
+
+
+# rows of one tile, around the two tile heights, one height for every layer or a mix of both (640 and
+# 5776 rows at 1024 channels, more tiles than workgroups), a column count that is no multiple of 4 tiles
+@pytest.mark.parametrize("m,dim", [(1, 256), (127, 256), (129, 256), (257, 768), (640, 1024), (5776, 1024), (17000, 256),
+                                   (33000, 256)])
+@pytest.mark.parametrize("linear", ["bf16", "fp8", "fp8-delayed"])
+def test_block_tile_heights(B, m, dim, linear):
+    import torch
+    w = synth.block_weights(dim, seed=m)
+    t = {k: torch.from_numpy(v).cuda() for k, v in w.items()}
+    t = {k: v.to(torch.bfloat16) if k.startswith("w_") else v for k, v in t.items()}
+    g = torch.Generator(device="cuda")
+    g.manual_seed(m)
+    z = torch.randn(m, dim, generator=g, device="cuda").to(torch.bfloat16)
+    state = torch.zeros(B.FP8_STATE_BYTES, dtype=torch.uint8, device="cuda")
+    bw = B.block_weights(t) if linear == "bf16" else B.block_weights(
+        t, B.LINEAR_FP8_E4M3, B.FP8_CURRENT if linear == "fp8" else B.FP8_DELAYED, state)
+    ph = B.make_params(1, 1, 1, dim, dim // 64, n_special=0, qk_norm=1)
+    delta = torch.full_like(z, float("nan"))
+    ws = B.alloc_ws(B.litevggt_global_block_ws_bytes(ph, m))
+    for _ in range(2 if linear == "fp8-delayed" else 1):     # the second call scales by the first one's amaxes
+        B.litevggt_global_block(ph, m, z, bw, delta, ws)
+    torch.cuda.synchronize()
+    ref = _block64(z, t, dim // 64)
+    err = float((delta.double() - ref).abs().max() / ref.abs().max())
+    # bf16: one rounding step of an intermediate apart; E4M3 layers: 2^-4 per code, four layers deep
+    assert err <= (2e-2 if linear == "bf16" else 1e-1)
