@@ -7,58 +7,125 @@
 namespace lv {
 
 // ---------------------------------------------------------------------------------
-// Psi_g.  One workgroup per (frame, patch row): the patch+2 luma rows it needs are
-// built once in LDS (border pixels replicated), then each wave reduces whole patches.
+// Psi_g.  One workgroup per (frame, patch row); neighbouring patch rows run on the same XCD, whose
+// L2 then has the two pixel rows they share.  The patch + 2 pixel rows (border rows replicated)
+// are one contiguous run of each colour plane: four pixels per load, all planes' loads of four
+// steps in flight, their luma kept in LDS.  Then a thread walks down its pixel column with the
+// three rows of its three columns in registers (3 LDS reads per pixel, not 8) and the columns of a
+// patch are added up.  Bound by HBM, as long as enough loads are in flight: 140 us for 100 frames
+// of 518 x 518 in fp32 (2.3 TB/s) with one pixel per load and a division per pixel, now 57.
+// VEC: the planes are whole numbers of 4-pixel pieces from an aligned base, so pieces never leave
+// a plane; else one pixel at a time.
 // ---------------------------------------------------------------------------------
-template <typename PixT>
-__global__ __launch_bounds__(256) void k_grad_map(const PixT *__restrict__ img, int H, int W,
+template <typename PixT> struct Quad;
+template <> struct Quad<float> { typedef f32x4 type; };
+template <> struct Quad<uint8_t> { typedef uint32_t type; };
+__device__ __forceinline__ f32x4 quad_f32(f32x4 v) { return v; }
+__device__ __forceinline__ f32x4 quad_f32(uint32_t v) {
+  return f32x4{(float)(v & 255u), (float)((v >> 8) & 255u), (float)((v >> 16) & 255u), (float)(v >> 24)};
+}
+
+template <typename PixT, bool VEC>
+__global__ __launch_bounds__(640) void k_grad_map(const PixT *__restrict__ img, int F, int H, int W,
                                                   int patch, float *__restrict__ psi_g) {
-  extern __shared__ float luma[];            // [(patch+2)][Wi+2]
-  const int Hi = H * patch, Wi = W * patch, LW = Wi + 2;
-  const int f = blockIdx.x / H, ph = blockIdx.x % H;
+  extern __shared__ f32x4 luma4[];           // luma of the pixel rows, from the last multiple of 4 pixels on
+  float *luma = (float *)luma4;
+  const int Hi = H * patch, Wi = W * patch;
+  const uint32_t nblk = (uint32_t)F * H, lb = xcd_contiguous(blockIdx.x, nblk);
+  if (lb >= nblk) return;
+  const int f = lb / H, ph = lb % H, tid = threadIdx.x, nt = blockDim.x;
   const size_t plane = (size_t)Hi * Wi;
   const PixT *base = img + (size_t)f * 3 * plane;
   const float unit = sizeof(PixT) == 1 ? (1.0f / 255.0f) : 1.0f;
-  for (int i = threadIdx.x; i < (patch + 2) * LW; i += blockDim.x) {
-    int rr = i / LW, cc = i - rr * LW;
-    int y = min(max(ph * patch + rr - 1, 0), Hi - 1);
-    int x = min(max(cc - 1, 0), Wi - 1);
-    size_t o = (size_t)y * Wi + x;
-    float r = (float)base[o] * unit, g = (float)base[plane + o] * unit,
-          b = (float)base[2 * plane + o] * unit;
-    luma[i] = 0.299f * r + 0.587f * g + 0.114f * b;
+  const int y0 = max(ph * patch - 1, 0), y1 = min(ph * patch + patch + 1, Hi);   // pixel rows [y0, y1)
+  const int p0 = y0 * Wi, p1 = y1 * Wi;      // (a plane has less than 2^31 pixels: its rows fit LDS)
+  const int q0 = VEC ? p0 >> 2 : p0;
+  if constexpr (VEC) {
+    typedef typename Quad<PixT>::type Q;
+    const Q *r4 = (const Q *)base, *g4 = (const Q *)(base + plane), *b4 = (const Q *)(base + 2 * plane);
+    const int q1 = (p1 + 3) >> 2;
+    for (int q = q0 + tid; q < q1; q += 4 * nt) {
+      Q v[4][3];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int at = min(q + u * nt, q1 - 1);
+        v[u][0] = r4[at];
+        v[u][1] = g4[at];
+        v[u][2] = b4[at];
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const f32x4 r = quad_f32(v[u][0]) * unit, g = quad_f32(v[u][1]) * unit, b = quad_f32(v[u][2]) * unit;
+        f32x4 l;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) l[e] = 0.299f * r[e] + 0.587f * g[e] + 0.114f * b[e];
+        if (q + u * nt < q1) luma4[q + u * nt - q0] = l;
+      }
+    }
+  } else {
+    for (int i = p0 + tid; i < p1; i += nt) {
+      const float r = (float)base[i] * unit, g = (float)base[plane + i] * unit, b = (float)base[2 * plane + i] * unit;
+      luma[i - q0] = 0.299f * r + 0.587f * g + 0.114f * b;
+    }
   }
   __syncthreads();
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, nw = blockDim.x >> 6;
-  const int pp = patch * patch;
-  for (int pw = wave; pw < W; pw += nw) {
+  const int rows = ((y1 - y0) * Wi + 3 + 3) & ~3;          // floats before the column sums
+  float *colsum = luma + rows;                             // [Wi]
+  const float *top = luma + (VEC ? p0 & 3 : 0);            // pixel row y0
+  for (int x = tid; x < Wi; x += nt) {
+    const int xl = max(x - 1, 0), xr = min(x + 1, Wi - 1);
+    auto row = [&](int y) { return top + (min(max(y, 0), Hi - 1) - y0) * Wi; };
+    const float *c = row(ph * patch - 1);
+    float al = c[xl], am = c[x], ar = c[xr];
+    c = row(ph * patch);
+    float bl = c[xl], bm = c[x], br = c[xr];
     float acc = 0.f;
-    for (int i = lane; i < pp; i += 64) {
-      int py = i / patch, px = i - py * patch;
-      const float *c = luma + (py + 1) * LW + pw * patch + px + 1;
-      float tl = c[-LW - 1], tc = c[-LW], tr = c[-LW + 1];
-      float ml = c[-1], mr = c[1];
-      float bl = c[LW - 1], bc = c[LW], br = c[LW + 1];
-      float gx = (tr + 2.f * mr + br) - (tl + 2.f * ml + bl);
-      float gy = (bl + 2.f * bc + br) - (tl + 2.f * tc + tr);
+    for (int py = 0; py < patch; ++py) {
+      c = row(ph * patch + py + 1);
+      const float cl = c[xl], cm = c[x], cr = c[xr];
+      const float gx = (ar + 2.f * br + cr) - (al + 2.f * bl + cl);
+      const float gy = (cl + 2.f * cm + cr) - (al + 2.f * am + ar);
       acc += sqrtf(gx * gx + gy * gy);
+      al = bl, am = bm, ar = br;
+      bl = cl, bm = cm, br = cr;
     }
-    acc = wave_sum(acc);
-    if (lane == 0) psi_g[((size_t)f * H + ph) * W + pw] = acc / (float)pp;
+    colsum[x] = acc;
+  }
+  __syncthreads();
+  const float pp = (float)(patch * patch);
+  for (int pw = tid; pw < W; pw += nt) {
+    float acc = 0.f;
+    for (int i = 0; i < patch; ++i) acc += colsum[pw * patch + i];
+    psi_g[((size_t)f * H + ph) * W + pw] = acc / pp;
   }
 }
 
 int launch_grad_map(const void *images, int img_dtype, const Dims &d, int patch, float *psi_g,
                     hipStream_t st) {
-  size_t lds = (size_t)(patch + 2) * (d.W * patch + 2) * sizeof(float);
-  if (lds > 64 * 1024) return LV_ERR_SHAPE;
-  dim3 grid((unsigned)(d.F * d.H));
-  if (img_dtype == LV_IMG_F32)
-    hipLaunchKernelGGL(k_grad_map<float>, grid, dim3(256), lds, st, (const float *)images, d.H,
-                       d.W, patch, psi_g);
-  else
-    hipLaunchKernelGGL(k_grad_map<uint8_t>, grid, dim3(256), lds, st, (const uint8_t *)images,
-                       d.H, d.W, patch, psi_g);
+  // the limit of the earlier layout ((patch + 2) rows of Wi + 2 luma values within 64 KB) is kept
+  const int Wi = d.W * patch;
+  if ((size_t)(patch + 2) * (Wi + 2) * sizeof(float) > 64 * 1024) return LV_ERR_SHAPE;
+  const size_t lds = ((size_t)(patch + 2) * Wi + Wi + 8) * sizeof(float);   // pixel rows, column sums
+  const int passes = (Wi + 639) / 640;       // a thread per pixel column, as few idle as may be
+  const unsigned threads = (unsigned)(((Wi + passes - 1) / passes + 63) / 64 * 64);
+  const dim3 grid((unsigned)align_up((size_t)d.F * d.H, kXcd));
+  const size_t pix = img_dtype == LV_IMG_F32 ? 4 : 1;
+  const bool vec = (size_t)d.H * patch * Wi % 4 == 0 && (uintptr_t)images % (4 * pix) == 0;
+  static std::atomic<uint64_t> lds_done[4];
+  int rc;
+#define LV_GRAD(T, V, I)                                                                          \
+  do {                                                                                            \
+    if ((rc = allow_dynamic_lds((const void *)k_grad_map<T, V>, 96 * 1024, lds_done[I]))) return rc; \
+    hipLaunchKernelGGL((k_grad_map<T, V>), grid, dim3(threads), lds, st, (const T *)images, d.F, d.H, d.W, patch, psi_g); \
+  } while (0)
+  if (img_dtype == LV_IMG_F32) {
+    if (vec) LV_GRAD(float, true, 0);
+    else LV_GRAD(float, false, 1);
+  } else {
+    if (vec) LV_GRAD(uint8_t, true, 2);
+    else LV_GRAD(uint8_t, false, 3);
+  }
+#undef LV_GRAD
   LV_HIP_CHECK_LAUNCH();
   return LV_OK;
 }
@@ -175,8 +242,12 @@ __global__ __launch_bounds__(128) void k_var_map(const uint16_t *__restrict__ x,
 // Per column the lane keeps d of row i-1 and the pair sum d(i-1) + d(i-2) in fp32, so every
 // token is widened once: vertical sum = d(i) + pair, then pair <- d(i) + d(i-1); the horizontal
 // 3-sum slides over the strip's columns.  Cells outside the grid are fed as the pivot token
-// (d = 0) and n counts the cells inside.  The bits of row i+1 are requested into a column's
+// (d = 0) and n counts the cells inside.  The bits of row i+2 are requested into a column's
 // registers as soon as that column of row i has been widened.
+// A strip is a chain of one memory round trip after the other, about 1.7 us per row, so short
+// sequences, whose strips do not fill the 1024 workgroup slots, cut the rows into segments, each
+// with one more row read on either side (var_row_segments; 63 -> 36 us for 32 frames of 37 x 37,
+// 25 -> 9 for 2 of 16 x 16).
 // ---------------------------------------------------------------------------------
 #ifndef LV_VAR_SEG
 #define LV_VAR_SEG 4
@@ -185,13 +256,17 @@ constexpr int kSeg = LV_VAR_SEG;
 constexpr int kVarWaves = 2;                   // waves per workgroup: 512 channels each, 8 per lane
 
 __global__ __launch_bounds__(64 * kVarWaves) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_var_map3(
-    const uint16_t *__restrict__ x, int F, int H, int W, int S, int C, int nseg, float *__restrict__ psi_v) {
+    const uint16_t *__restrict__ x, int F, int H, int W, int S, int C, int nseg, int row_segs,
+    float *__restrict__ psi_v) {
   constexpr int NC = kSeg + 2;               // columns a strip reads: its own and one on each side
   __shared__ float comb[2][kVarWaves][kSeg]; // the waves' partial sums of a grid row, by row parity
-  const uint32_t nblk = (uint32_t)F * nseg;
+  const uint32_t nblk = (uint32_t)F * row_segs * nseg;
   const uint32_t lb = xcd_contiguous(blockIdx.x, nblk);   // neighbouring strips share an L2
   if (lb >= nblk) return;
-  const int f = lb / nseg, j0 = (int)(lb % nseg) * kSeg;
+  const int fr = lb / nseg, j0 = (int)(lb % nseg) * kSeg;
+  const int f = fr / row_segs, rs = fr % row_segs;
+  const int r0 = (int)((int64_t)H * rs / row_segs), r1 = (int)((int64_t)H * (rs + 1) / row_segs);   // output rows [r0, r1)
+  const int ib = max(r0 - 1, 0);                          // the first grid row that is read
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int T = H * W + S;
   const uint16_t *frame = x + ((size_t)f * T + S) * C;
@@ -210,12 +285,12 @@ __global__ __launch_bounds__(64 * kVarWaves) __attribute__((amdgpu_waves_per_eu(
     auto fetch = [&](int i, int a, u32x4 &dst) {   // column a of the strip in grid row i, or the pivot
       const int jj = j0 - 1 + a;
       dst = pbits;
-      if (on && i < H && jj >= 0 && jj < W) dst = *(const u32x4 *)(frame + ((size_t)i * W + jj) * C + c0);
+      if (on && i < H && i <= r1 && jj >= 0 && jj < W) dst = *(const u32x4 *)(frame + ((size_t)i * W + jj) * C + c0);
     };
 #pragma unroll
     for (int a = 0; a < NC; ++a) {
-      fetch(0, a, raw[0][a]);
-      fetch(1, a, raw[1][a]);
+      fetch(ib, a, raw[0][a]);
+      fetch(ib + 1, a, raw[1][a]);
       e1[a] = epair[a] = 0.f;
 #pragma unroll
       for (int e = 0; e < 8; ++e) d1[a][e] = pair[a][e] = 0.f;
@@ -272,20 +347,20 @@ __global__ __launch_bounds__(64 * kVarWaves) __attribute__((amdgpu_waves_per_eu(
       float r = res[0];
 #pragma unroll
       for (int q = 1; q < kSeg; ++q) r = lane == q ? res[q] : r;
-      if (lane < kSeg) comb[i & 1][wave][lane] = r;
+      if (lane < kSeg) comb[decltype(parity)::value][wave][lane] = r;
       __syncthreads();
-      if (wave == 0 && lane < kSeg && io >= 0 && io < H && j0 + lane < W) {
+      if (wave == 0 && lane < kSeg && io >= r0 && io < r1 && j0 + lane < W) {
         r = 0.f;
 #pragma unroll
-        for (int w2 = 0; w2 < kVarWaves; ++w2) r += comb[i & 1][w2][lane];
+        for (int w2 = 0; w2 < kVarWaves; ++w2) r += comb[decltype(parity)::value][w2][lane];
         r *= inv_c;
         float *o = out + (size_t)io * W + j0 + lane;
         *o = cbase ? *o + r : r;
       }
     };
-    // rows 0 .. H; row H is a row of pivots that flushes output row H - 1 (a step beyond it sees
+    // rows ib .. r1; row H is a row of pivots that flushes output row H - 1 (a step beyond r1 sees
     // pivots only and writes nothing)
-    for (int i = 0; i <= H; i += 2) {
+    for (int i = ib; i <= r1; i += 2) {
       step(std::integral_constant<int, 0>{}, i);
       step(std::integral_constant<int, 1>{}, i + 1);
     }
@@ -293,11 +368,26 @@ __global__ __launch_bounds__(64 * kVarWaves) __attribute__((amdgpu_waves_per_eu(
   }
 }
 
+// Row segments per strip: rounds of 1024 workgroups (256 CUs, 2 waves per SIMD, 2 waves each), a
+// segment costing its rows, the two rows around them and about two rows' time to start.
+static int var_row_segments(int64_t strips, int H) {
+  int best = 1;
+  int64_t best_cost = 0;
+  for (int k = 1; k <= H && k <= 64; ++k) {
+    const int64_t cost = (strips * k + 1023) / 1024 * ((H + k - 1) / k + (k > 1 ? 2 : 0) + 2);
+    if (k == 1 || cost < best_cost) {
+      best = k;
+      best_cost = cost;
+    }
+  }
+  return best;
+}
+
 int launch_var_map(const uint16_t *x, const Dims &d, int pool, float *psi_v, hipStream_t st) {
   if (pool == 3) {
-    const int nseg = (d.W + kSeg - 1) / kSeg;
-    hipLaunchKernelGGL(k_var_map3, dim3((unsigned)align_up((size_t)d.F * nseg, kXcd)), dim3(64 * kVarWaves), 0, st, x, d.F,
-                       d.H, d.W, d.S, d.C, nseg, psi_v);
+    const int nseg = (d.W + kSeg - 1) / kSeg, row_segs = var_row_segments((int64_t)d.F * nseg, d.H);
+    hipLaunchKernelGGL(k_var_map3, dim3((unsigned)align_up((size_t)d.F * row_segs * nseg, kXcd)), dim3(64 * kVarWaves),
+                       0, st, x, d.F, d.H, d.W, d.S, d.C, nseg, row_segs, psi_v);
     LV_HIP_CHECK_LAUNCH();
     return LV_OK;
   }
@@ -321,11 +411,12 @@ int launch_var_map(const uint16_t *x, const Dims &d, int pool, float *psi_v, hip
 // Fusion: one workgroup per frame finds min/max of both maps, then writes
 // alpha*norm(Psi_g) + beta*norm(Psi_v).
 // ---------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void k_ga_fuse(const float *__restrict__ psi_g,
+constexpr int kFuseWaves = 16;   // a frame is a few KB: its latency counts, not the bandwidth
+__global__ __launch_bounds__(64 * kFuseWaves) void k_ga_fuse(const float *__restrict__ psi_g,
                                                  const float *__restrict__ psi_v, int P,
                                                  float alpha, float beta,
                                                  float *__restrict__ score) {
-  __shared__ float red[4][4];
+  __shared__ float red[kFuseWaves][4];
   const float *g = psi_g + (size_t)blockIdx.x * P, *v = psi_v + (size_t)blockIdx.x * P;
   float glo = INFINITY, ghi = -INFINITY, vlo = INFINITY, vhi = -INFINITY;
   for (int t = threadIdx.x; t < P; t += blockDim.x) {
@@ -347,10 +438,13 @@ __global__ __launch_bounds__(256) void k_ga_fuse(const float *__restrict__ psi_g
     red[wave][3] = vhi;
   }
   __syncthreads();
-  glo = fminf(fminf(red[0][0], red[1][0]), fminf(red[2][0], red[3][0]));
-  ghi = fmaxf(fmaxf(red[0][1], red[1][1]), fmaxf(red[2][1], red[3][1]));
-  vlo = fminf(fminf(red[0][2], red[1][2]), fminf(red[2][2], red[3][2]));
-  vhi = fmaxf(fmaxf(red[0][3], red[1][3]), fmaxf(red[2][3], red[3][3]));
+#pragma unroll
+  for (int w = 0; w < kFuseWaves; ++w) {
+    glo = fminf(glo, red[w][0]);
+    ghi = fmaxf(ghi, red[w][1]);
+    vlo = fminf(vlo, red[w][2]);
+    vhi = fmaxf(vhi, red[w][3]);
+  }
   const float gr = ghi - glo, vr = vhi - vlo;
   for (int t = threadIdx.x; t < P; t += blockDim.x) {
     float ng = gr > 0.f ? (g[t] - glo) / gr : 0.f;
@@ -361,7 +455,7 @@ __global__ __launch_bounds__(256) void k_ga_fuse(const float *__restrict__ psi_g
 
 int launch_ga_fuse(const float *psi_g, const float *psi_v, const Dims &d, float alpha, float beta,
                    float *score, hipStream_t st) {
-  hipLaunchKernelGGL(k_ga_fuse, dim3((unsigned)d.F), dim3(256), 0, st, psi_g, psi_v, d.P, alpha,
+  hipLaunchKernelGGL(k_ga_fuse, dim3((unsigned)d.F), dim3(64 * kFuseWaves), 0, st, psi_g, psi_v, d.P, alpha,
                      beta, score);
   LV_HIP_CHECK_LAUNCH();
   return LV_OK;

@@ -5,7 +5,7 @@ import pytest
 from oracle import litevggt_oracle as O
 from paper_2512_04939_amd import synth
 
-from helpers import hip_params, oracle_params
+from helpers import hip_params, oracle_params, stored_inputs, to_dev_bf16
 
 pytestmark = pytest.mark.gpu
 
@@ -197,3 +197,31 @@ def test_block_tile_heights(B, m, dim, linear):
     err = float((delta.double() - ref).abs().max() / ref.abs().max())
     # bf16: one rounding step of an intermediate apart; E4M3 layers: 2^-4 per code, four layers deep
     assert err <= (2e-2 if linear == "bf16" else 1e-1)
+
+
+# ------------------------------------------------------------------------------- importance
+# pixel rows that are no multiple of 4 pixels, planes that are none (one pixel at a time), images
+# behind an unaligned address, a single patch row and column, pixel rows wider than a workgroup,
+# grids of one row segment per row and of segments of unequal height
+@pytest.mark.parametrize("frames,h,w,patch,dim", [(2, 16, 16, 14, 64), (3, 5, 7, 3, 128), (2, 1, 1, 14, 64), (2, 3, 50, 14, 64),
+                                                  (1, 37, 5, 14, 192), (3, 9, 2, 7, 1024), (260, 6, 6, 2, 64)])
+@pytest.mark.parametrize("kind", ["f32", "f32 at 4", "u8", "u8 at 1"])
+def test_importance_edges(B, frames, h, w, patch, dim, kind):
+    import torch
+    wl = synth.Workload("t", frames=frames, grid_h=h, grid_w=w, dim=dim, heads=dim // 64, patch=patch, canvas=64, seed=h)
+    bits, xf, im = stored_inputs(wl)
+    u8 = kind.startswith("u8")
+    if u8:
+        im = np.floor(im * 255).astype(np.uint8)
+    flat = torch.zeros(im.size + 8, dtype=torch.uint8 if u8 else torch.float32, device="cuda")
+    at = 1 if "at" in kind else 0
+    img = flat[at:at + im.size]
+    img.copy_(torch.from_numpy(im.reshape(-1)))
+    ph = hip_params(wl, img_dtype=B.IMG_U8 if u8 else B.IMG_F32)
+    grad = torch.full((frames, h * w), float("nan"), device="cuda")
+    score = torch.full((frames, h * w), float("nan"), device="cuda")
+    B.litevggt_importance(ph, img, to_dev_bf16(bits), grad, True, score, B.alloc_ws(frames * h * w * 4))
+    torch.cuda.synchronize()
+    ref, psi_g = O.importance(im.astype(np.float64) / (255.0 if u8 else 1.0), xf, oracle_params(wl))
+    assert np.abs(grad.cpu().numpy() - psi_g.reshape(frames, -1)).max() <= 2e-5 * max(1.0, np.abs(psi_g).max())
+    assert np.abs(score.cpu().numpy() - ref.reshape(frames, -1)).max() <= 2e-5
