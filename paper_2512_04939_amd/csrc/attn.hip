@@ -834,13 +834,11 @@ __device__ __forceinline__ u32x4 norm8(const u32x4 w, float ss_head, int qk_norm
   return qk_norm ? scale8(w, 1.0f / sqrtf(ss_head * (1.0f / 64.0f) + kQkEps)) : w;
 }
 
-__global__ __launch_bounds__(256) void k_zero_words(uint32_t *p, size_t n) {
+// n words, and (optional) the four of an amax block
+__global__ __launch_bounds__(256) void k_zero_words(uint32_t *p, size_t n, uint32_t *amax) {
   const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
   if (i < n) p[i] = 0u;
-}
-
-__global__ void k_attn_amax_zero(uint32_t *amax) {
-  if (threadIdx.x < 4) amax[threadIdx.x] = 0u;
+  if (amax && i < 4) amax[i] = 0u;
 }
 
 // amax[0..2] = max |q^|, |k^|, |v| over the call's tensors (q^, k^ normalised when qk_norm).
@@ -879,7 +877,9 @@ __global__ __launch_bounds__(256) void k_attn_amax(const uint16_t *__restrict__ 
   if (threadIdx.x < 3) {
     const float m = fmaxf(fmaxf(red[threadIdx.x][0], red[threadIdx.x][1]),
                           fmaxf(red[threadIdx.x][2], red[threadIdx.x][3]));
-    atomicMax(&amax[threadIdx.x], __float_as_uint(m));   // non-negative floats order like uints
+    // non-negative floats order like uints; only a value that would raise the word sends an atomic
+    if (__float_as_uint(m) > __hip_atomic_load(&amax[threadIdx.x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+      atomicMax(&amax[threadIdx.x], __float_as_uint(m));
   }
 }
 
@@ -1501,19 +1501,18 @@ int launch_attn(const uint16_t *q, const uint16_t *k, const uint16_t *v, uint16_
     u32x2 *kp = (u32x2 *)frag, *vp = (u32x2 *)(frag + per);
     const int C = heads * 64;
     const int64_t nchunks = n * (C / 8);
-    const unsigned ag = (unsigned)(((nchunks + 255) / 256) < 4096 ? ((nchunks + 255) / 256) : 4096);
-    hipLaunchKernelGGL(k_attn_amax_zero, dim3(1), dim3(64), 0, st, amax);
-    hipLaunchKernelGGL(k_attn_amax, dim3(ag), dim3(256), 0, st, q, k, v, n, C, qk_norm, amax);
+    const unsigned ag = (unsigned)(((nchunks + 255) / 256) < 2048 ? ((nchunks + 255) / 256) : 2048);
     // bounded scores (unit-RMS heads, exponent range checked like for bf16): the branch-free
     // kernel against the fixed reference first, then the running-maximum kernel on the query
     // blocks the first one flagged (normally none: its workgroups return at once)
     const bool bounded = qk_norm && kF8Bound * c <= 64.0f;
-    uint32_t *redo = nullptr;
+    uint32_t *redo = (uint32_t *)(frag + 4 * per);
+    const size_t words = bounded ? fp8_flag_words(heads, n) : 0;
+    hipLaunchKernelGGL(k_zero_words, dim3((unsigned)((words + 255) / 256 + 1)), dim3(256), 0, st, redo, words, amax);
+    hipLaunchKernelGGL(k_attn_amax, dim3(ag), dim3(256), 0, st, q, k, v, n, C, qk_norm, amax);
+    if (!bounded) redo = nullptr;
     if (bounded) {
       u32x2 *kpb = (u32x2 *)(frag + 2 * per), *vpb = (u32x2 *)(frag + 3 * per);
-      redo = (uint32_t *)(frag + 4 * per);
-      const size_t words = fp8_flag_words(heads, n);
-      hipLaunchKernelGGL(k_zero_words, dim3((unsigned)((words + 255) / 256)), dim3(256), 0, st, redo, words);
       hipLaunchKernelGGL(k_attn_pack_fp8b, dim3((unsigned)n_kt, (unsigned)heads), dim3(256), 0, st, k, v, n,
                          heads, n_kt, amax, kpb, vpb);
       if (after_pack && hipEventRecord(after_pack, st) != hipSuccess) return LV_ERR_HIP;
@@ -1542,7 +1541,8 @@ int launch_attn(const uint16_t *q, const uint16_t *k, const uint16_t *v, uint16_
   uint32_t *redo = (uint32_t *)(frag + 2 * per);
   if (!bounded) {
     const size_t words = fp8_flag_words(heads * n_seq, n);
-    hipLaunchKernelGGL(k_zero_words, dim3((unsigned)((words + 255) / 256)), dim3(256), 0, st, redo, words);
+    hipLaunchKernelGGL(k_zero_words, dim3((unsigned)((words + 255) / 256)), dim3(256), 0, st, redo, words,
+                       (uint32_t *)nullptr);
   }
   hipLaunchKernelGGL(k_attn_pack, dim3((unsigned)n_kt, (unsigned)(heads * n_seq)), dim3(256), 0, st,
                      k, v, n, heads, n_kt, qk_norm, kp, vp);

@@ -38,14 +38,14 @@ __device__ __forceinline__ void ln_row(const u32x4 (&w)[CPL], const u32x4 (&a)[C
       sum += v[c][2 * i] + v[c][2 * i + 1];
     }
   }
-  const float mean = wave_sum(sum) / (float)C;
+  const float mean = wave_sum_uniform(sum) / (float)C;
   float ss = 0.f;
 #pragma unroll
   for (int c = 0; c < CPL; ++c)
     if (lane + 64 * c < nch)
 #pragma unroll
       for (int i = 0; i < 8; ++i) ss += (v[c][i] - mean) * (v[c][i] - mean);
-  const float rstd = 1.0f / sqrtf(wave_sum(ss) / (float)C + kLnEps);
+  const float rstd = 1.0f / sqrtf(wave_sum_uniform(ss) / (float)C + kLnEps);
 #pragma unroll
   for (int c = 0; c < CPL; ++c) {
     const int ch = lane + 64 * c;
@@ -93,10 +93,20 @@ __global__ __launch_bounds__(256) void k_layernorm(const uint16_t *__restrict__ 
     if (lane + 64 * c < nch) ((u32x4 *)(out + (size_t)row * C))[lane + 64 * c] = o[c];
 }
 
+// Only a value that would raise the word sends an atomic (a stale read only sends one too many), and
+// one thread per workgroup does: a few thousand waves that start together all find the word at 0,
+// and their atomics on one address take longer than reading the tensor (5-10 ns each).
+__device__ __forceinline__ void raise_max(uint32_t *word, float m) {
+  if (__float_as_uint(m) > __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+    atomicMax(word, __float_as_uint(m));
+}
+
 // The same LayerNorm with the result written as a linear layer's activation operand (the
 // fragment order k_pack_rows produces: [row / 32][k-step of 16 channels][lane = row % 32 + 32 *
 // (second 8 of the 16)], 16 bytes each).  A workgroup owns the 32 rows of one fragment row, a
-// wave 8 of them (their loads are all issued before the first row is reduced); the normalised
+// wave 4 of them (their loads are all issued before the first row is reduced, and more waves
+// per workgroup would leave a wave too few; 8 rows per wave and sums through LDS shuffles: 13.7 us
+// for 5776 rows of 1024 channels, 29 for 15432 in FP8); the normalised
 // rows meet in LDS (row stride C * 2 + 16 bytes: the 32 rows a wave reads back at one channel
 // piece then lie in different banks) and leave as one contiguous run of 32 * C * 2 bytes.
 // Rows beyond M are written as zeros.
@@ -106,8 +116,9 @@ __global__ __launch_bounds__(256) void k_layernorm(const uint16_t *__restrict__ 
 // rows x 32 channels, lane h * 32 + r holds the 16 codes of channels 32u + 16h .. + 15 of row
 // r); the largest |value| of the rows below M is reduced into *amax.  Row stride in LDS: C + 16
 // bytes.
+constexpr int kLnWaves = 8;
 template <int CPL, bool FP8>
-__global__ __launch_bounds__(256) void k_layernorm_packed(const uint16_t *__restrict__ x,
+__global__ __launch_bounds__(64 * kLnWaves) void k_layernorm_packed(const uint16_t *__restrict__ x,
                                                           const uint16_t *__restrict__ add,
                                                           const float *__restrict__ gamma,
                                                           const float *__restrict__ beta, int64_t M, int C,
@@ -115,7 +126,8 @@ __global__ __launch_bounds__(256) void k_layernorm_packed(const uint16_t *__rest
                                                           const uint32_t *__restrict__ inv,
                                                           uint32_t *__restrict__ amax) {
   extern __shared__ u32x4 ln_stage[];
-  constexpr int RB = CPL <= 2 ? 8 : 4;   // rows whose loads are in flight together
+  constexpr int kRows = 32 / kLnWaves;            // rows of a wave
+  constexpr int RB = CPL <= 2 ? kRows : kRows / 2;   // rows whose loads are in flight together
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nch = C >> 3, stride = nch + 1;
   if constexpr (FP8) {
     const float r = __uint_as_float(*inv);
@@ -123,16 +135,16 @@ __global__ __launch_bounds__(256) void k_layernorm_packed(const uint16_t *__rest
     u32x2 *stage8 = (u32x2 *)ln_stage;
     float m = 0.f;
 #pragma unroll 1
-    for (int j0 = 0; j0 < 8; j0 += RB) {
+    for (int j0 = 0; j0 < kRows; j0 += RB) {
       u32x4 w[RB][CPL], a[RB][CPL];
 #pragma unroll
       for (int j = 0; j < RB; ++j) {
-        const int64_t row = (int64_t)blockIdx.x * 32 + wave * 8 + j0 + j;
+        const int64_t row = (int64_t)blockIdx.x * 32 + wave * kRows + j0 + j;
         ln_load<CPL>(x, add, row < M ? row : 0, C, lane, row < M ? nch : 0, w[j], a[j]);
       }
 #pragma unroll
       for (int j = 0; j < RB; ++j) {
-        const int rr = wave * 8 + j0 + j;
+        const int rr = wave * kRows + j0 + j;
         u32x4 o[CPL];
         ln_row<CPL>(w[j], a[j], gamma, beta, lane, nch, C, o);
         const bool live = (int64_t)blockIdx.x * 32 + rr < M;
@@ -144,12 +156,17 @@ __global__ __launch_bounds__(256) void k_layernorm_packed(const uint16_t *__rest
           }
       }
     }
+    __shared__ float red[kLnWaves];
     m = wave_max(m);
-    if (lane == 0 && __float_as_uint(m) > __hip_atomic_load(amax, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
-      atomicMax(amax, __float_as_uint(m));
+    if (lane == 0) red[wave] = m;
     __syncthreads();
+    if (threadIdx.x == 0) {
+#pragma unroll
+      for (int i = 1; i < kLnWaves; ++i) m = fmaxf(m, red[i]);
+      raise_max(amax, m);
+    }
     const int pieces = 32 * (C >> 4);   // = (C / 32) units x 64 lanes
-    for (int p = threadIdx.x; p < pieces; p += 256) {
+    for (int p = threadIdx.x; p < pieces; p += 64 * kLnWaves) {
       const int u = p >> 6, lp = p & 63;
       const u32x2 *src = stage8 + (lp & 31) * stride8 + 4 * u + 2 * (lp >> 5);
       const u32x2 lo = src[0], hi = src[1];
@@ -158,16 +175,16 @@ __global__ __launch_bounds__(256) void k_layernorm_packed(const uint16_t *__rest
     return;
   }
 #pragma unroll 1
-  for (int j0 = 0; j0 < 8; j0 += RB) {
+  for (int j0 = 0; j0 < kRows; j0 += RB) {
     u32x4 w[RB][CPL], a[RB][CPL];
 #pragma unroll
     for (int j = 0; j < RB; ++j) {
-      const int64_t row = (int64_t)blockIdx.x * 32 + wave * 8 + j0 + j;
+      const int64_t row = (int64_t)blockIdx.x * 32 + wave * kRows + j0 + j;
       ln_load<CPL>(x, add, row < M ? row : 0, C, lane, row < M ? nch : 0, w[j], a[j]);
     }
 #pragma unroll
     for (int j = 0; j < RB; ++j) {
-      const int rr = wave * 8 + j0 + j;
+      const int rr = wave * kRows + j0 + j;
       u32x4 o[CPL];
       ln_row<CPL>(w[j], a[j], gamma, beta, lane, nch, C, o);
       const bool live = (int64_t)blockIdx.x * 32 + rr < M;
@@ -178,7 +195,7 @@ __global__ __launch_bounds__(256) void k_layernorm_packed(const uint16_t *__rest
   }
   __syncthreads();
   const int pieces = 32 * nch;   // = (C / 16) k-steps x 64 lanes
-  for (int p = threadIdx.x; p < pieces; p += 256) {
+  for (int p = threadIdx.x; p < pieces; p += 64 * kLnWaves) {
     const int ks = p >> 6, lp = p & 63;
     packed[(size_t)blockIdx.x * pieces + p] = ln_stage[(lp & 31) * stride + 2 * ks + (lp >> 5)];
   }
@@ -202,7 +219,7 @@ static int launch_layernorm(const uint16_t *x, const uint16_t *add, const float 
 #define LV_LNP(CPL, F8)                                                                                       \
   if ((rc = allow_dynamic_lds((const void *)k_layernorm_packed<CPL, F8>, lds, lds_done[(CPL - 1) * 2 + F8])))   \
     return rc;                                                                                                \
-  hipLaunchKernelGGL((k_layernorm_packed<CPL, F8>), dim3(grid), dim3(256), lds, st, x, add, gamma, beta, M, C,  \
+  hipLaunchKernelGGL((k_layernorm_packed<CPL, F8>), dim3(grid), dim3(64 * kLnWaves), lds, st, x, add, gamma, beta, M, C,  \
                      packed, fp8_inv, fp8_amax)
     if (fp8_inv) {
       switch (cpl) {
@@ -246,10 +263,13 @@ static int launch_layernorm(const uint16_t *x, const uint16_t *add, const float 
 // ---------------------------------------------------------------------------------------
 constexpr int kFp8Words = 8;
 
-__global__ void k_fp8_zero(uint32_t *sc) {
-  if (threadIdx.x < kFp8Words) sc[threadIdx.x] = 0u;
+// The workgroup's maximum of m, in thread 0
+__device__ __forceinline__ float block_max4(float m, float (&red)[4]) {
+  m = wave_max(m);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
+  __syncthreads();
+  return fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
 }
-
 // amax of a bf16 tensor of n16 16-byte pieces
 __global__ __launch_bounds__(256) void k_amax_bf16(const u32x4 *__restrict__ x, int64_t n16,
                                                    uint32_t *__restrict__ amax) {
@@ -258,19 +278,16 @@ __global__ __launch_bounds__(256) void k_amax_bf16(const u32x4 *__restrict__ x, 
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n16;
        i += (int64_t)gridDim.x * blockDim.x)
     m = fmaxf(m, absmax8(x[i]));
-  m = wave_max(m);
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
-  __syncthreads();
-  if (threadIdx.x == 0)
-    atomicMax(amax, __float_as_uint(fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]))));
+  m = block_max4(m, red);
+  if (threadIdx.x == 0) raise_max(amax, m);
 }
 
-// One wave: picks the scales of a layer from the tensors' own amax (current scaling).
+// One wave: picks the scales of a layer from the tensors' own amax (current scaling; the weight's
+// are in place already).
 __global__ __launch_bounds__(64) void k_fp8_scales(uint32_t *__restrict__ sc) {
   if (threadIdx.x == 0) {
-    const float ia = fp8_scale_inv(sc[0]), iw = fp8_scale_inv(sc[1]);
+    const float ia = fp8_scale_inv(sc[0]), iw = __uint_as_float(sc[3]);
     sc[2] = __float_as_uint(ia);
-    sc[3] = __float_as_uint(iw);
     sc[4] = __float_as_uint((1.0f / ia) * (1.0f / iw));
   }
 }
@@ -285,15 +302,12 @@ __global__ __launch_bounds__(64) void k_fp8_scales(uint32_t *__restrict__ sc) {
 // bytes of each bf16 row).  Grid: (row tiles, ceil(units / 16)).
 // amax != NULL: the largest |x| read is reduced into *amax on the way (delayed scaling needs
 // it only afterwards, for the history, so no pass of its own).
-__global__ __launch_bounds__(256) void k_quant_pack_fp8(const uint16_t *__restrict__ x, int n,
-                                                        int K, const uint32_t *__restrict__ inv,
-                                                        u32x4 *__restrict__ packed,
-                                                        uint32_t *__restrict__ amax) {
+__device__ __forceinline__ void quant_pack_units(const uint16_t *__restrict__ x, int n, int K, float r, int t, int group,
+                                                 u32x4 *__restrict__ packed, uint32_t *__restrict__ amax) {
   const int KS = K >> 5;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, h = lane >> 5, rr = lane & 31;
-  const int t = blockIdx.x, j = t * 32 + rr;
-  const int s0 = (blockIdx.y * 4 + wave) * 4;
-  const float r = __uint_as_float(*inv);
+  const int j = t * 32 + rr;
+  const int s0 = (group * 4 + wave) * 4;
   u32x4 src[4][2];
 #pragma unroll
   for (int u = 0; u < 4; ++u) {
@@ -314,11 +328,69 @@ __global__ __launch_bounds__(256) void k_quant_pack_fp8(const uint16_t *__restri
     float m = 0.f;
 #pragma unroll
     for (int u = 0; u < 4; ++u) m = fmaxf(m, fmaxf(absmax8(src[u][0]), absmax8(src[u][1])));
-    m = wave_max(m);
-    // one word for 10^5 waves: only a wave that would raise it sends an atomic (a stale read only
-    // sends one too many)
-    if (lane == 0 && __float_as_uint(m) > __hip_atomic_load(amax, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
-      atomicMax(amax, __float_as_uint(m));
+    __shared__ float red[4];
+    m = block_max4(m, red);
+    if (threadIdx.x == 0) raise_max(amax, m);
+  }
+}
+__global__ __launch_bounds__(256) void k_quant_pack_fp8(const uint16_t *__restrict__ x, int n,
+                                                        int K, const uint32_t *__restrict__ inv,
+                                                        u32x4 *__restrict__ packed,
+                                                        uint32_t *__restrict__ amax) {
+  quant_pack_units(x, n, K, __uint_as_float(*inv), blockIdx.x, blockIdx.y, packed, amax);
+}
+
+// ---- The block's four weight matrices (qkv, output, MLP 1, MLP 2: 3C x C, C x C, 4C x C, C x 4C) in
+// one launch each for their amaxes and for their way into operand order: 24 MB at C = 1024, which
+// four launches apiece did in 78 us (one atomic per workgroup on one word) and 20 us, now about 9
+// and 9.
+struct BlockWeights4 {
+  const uint16_t *w[4];
+  u32x4 *dst[4];
+};
+constexpr int kWAmaxUnit = 32;                     // workgroups per C x C elements of weights
+constexpr int kWAmaxParts = 12 * kWAmaxUnit;       // partial maxima, layer by layer
+__device__ __forceinline__ int weight_first_unit(int l) { return l == 0 ? 0 : l == 1 ? 3 : l == 2 ? 4 : l == 3 ? 8 : 12; }
+
+__global__ __launch_bounds__(256) void k_weights_amax(BlockWeights4 bw, int C, uint32_t *__restrict__ partial) {
+  __shared__ float red[4];
+  const int unit = blockIdx.x / kWAmaxUnit, l = unit < 3 ? 0 : unit < 4 ? 1 : unit < 8 ? 2 : 3;
+  const int u0 = weight_first_unit(l), n_wg = (weight_first_unit(l + 1) - u0) * kWAmaxUnit;
+  const u32x4 *x = (const u32x4 *)bw.w[l];
+  const int64_t n16 = (int64_t)(n_wg / kWAmaxUnit) * C * C / 8;
+  float m = 0.f;
+  for (int64_t i = (int64_t)((int)blockIdx.x - u0 * kWAmaxUnit) * 256 + threadIdx.x; i < n16; i += (int64_t)n_wg * 256 * 4) {
+    u32x4 v[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) v[u] = i + (int64_t)u * n_wg * 256 < n16 ? x[i + (int64_t)u * n_wg * 256] : u32x4{0u, 0u, 0u, 0u};
+#pragma unroll
+    for (int u = 0; u < 4; ++u) m = fmaxf(m, absmax8(v[u]));
+  }
+  m = block_max4(m, red);
+  if (threadIdx.x == 0) partial[blockIdx.x] = __float_as_uint(m);
+}
+
+// grid: per weight (rows / 32) row tiles x ceil(k-steps / 16) groups, one weight after the other
+template <bool FP8>
+__global__ __launch_bounds__(256) void k_weights_pack(BlockWeights4 bw, int C, const uint32_t *__restrict__ sc) {
+  const int g1 = (C / (FP8 ? 32 : 16) + 15) / 16, g4 = (4 * C / (FP8 ? 32 : 16) + 15) / 16;   // groups at K = C, 4C
+  const int rt = C / 32;
+  int l = 0, b = blockIdx.x;
+  if (b >= 3 * rt * g1) b -= 3 * rt * g1, l = 1;
+  if (l == 1 && b >= rt * g1) b -= rt * g1, l = 2;
+  if (l == 2 && b >= 4 * rt * g1) b -= 4 * rt * g1, l = 3;
+  const int groups = l == 3 ? g4 : g1, K = l == 3 ? 4 * C : C, t = b / groups, y = b % groups;
+  if constexpr (FP8) {
+    quant_pack_units(bw.w[l], t * 32 + 32, K, __uint_as_float(sc[l * kFp8Words + 3]), t, y, bw.dst[l], nullptr);
+  } else {
+    const int KS = K >> 4, lane = threadIdx.x & 63, wave = threadIdx.x >> 6, s0 = (y * 4 + wave) * 4;
+    const u32x4 *row = (const u32x4 *)(bw.w[l] + (size_t)(t * 32 + (lane & 31)) * K);
+    u32x4 w[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) w[u] = s0 + u < KS ? row[(s0 + u) * 2 + (lane >> 5)] : u32x4{0u, 0u, 0u, 0u};
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if (s0 + u < KS) bw.dst[l][((size_t)t * KS + s0 + u) * 64 + lane] = w[u];
   }
 }
 
@@ -412,6 +484,8 @@ __global__ __launch_bounds__(GemmShape<BM>::kThreads) __attribute__((amdgpu_wave
       tn_ = v % nt_n;
     }
   };
+  __shared__ uint32_t wg_amax;   // FP8 && PACKED: the largest |value| this workgroup has written
+  if (FP8 && PACKED && tid == 0) wg_amax = 0u;   // (many barriers before its first use)
   bool primed = false;   // the previous tile's epilogue has issued this tile's first stages
   int parity = 0;
   int tm = 0, tn = 0, tm2 = 0, tn2 = 0;
@@ -652,8 +726,7 @@ __global__ __launch_bounds__(GemmShape<BM>::kThreads) __attribute__((amdgpu_wave
           op[((size_t)a * KSn + b) * 64] = u32x4{s0[0], s0[1], s1[0], s1[1]};
         }
       m = wave_max(m);
-      if (lane == 0 && __float_as_uint(m) > __hip_atomic_load(out_amax, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
-        atomicMax(out_amax, __float_as_uint(m));
+      if (lane == 0) atomicMax(&wg_amax, __float_as_uint(m));   // in LDS; once per workgroup to memory
       continue;
     }
     const int KSn = nt_n * (kTile / 16);
@@ -722,13 +795,17 @@ __global__ __launch_bounds__(GemmShape<BM>::kThreads) __attribute__((amdgpu_wave
       }
     }
   }   // tiles
+  if constexpr (FP8 && PACKED) {
+    __syncthreads();
+    if (tid == 0) raise_max(out_amax, __uint_as_float(wg_amax));
+  }
 }
 
 // ---------------------------------------------------------------------------------------
 struct BlockWs {
   uint16_t *h, *qkv, *a, *u1, *h3;
   u32x4 *apack, *wpack;
-  uint32_t *fp8sc;
+  uint32_t *fp8sc, *wpart;
   void *attn;
   size_t bytes;
   int64_t Mp;
@@ -755,6 +832,7 @@ static BlockWs carve_block(int64_t M, int C, int heads, int attn_dtype, char *ba
   w.apack = (u32x4 *)take((size_t)w.Mp * 4 * C);       // a layer's activation operand: bf16 with K = C, FP8 with K <= 4C
   w.wpack = (u32x4 *)take(block_wpack_bytes(C));
   w.fp8sc = (uint32_t *)take(4 * kFp8Words * sizeof(uint32_t));   // one set per linear layer
+  w.wpart = (uint32_t *)take(kWAmaxParts * sizeof(uint32_t));     // the weights' partial maxima
   w.attn = take(attn_ws_bytes(heads, M, attn_dtype));
   w.bytes = off;
   return w;
@@ -770,12 +848,11 @@ struct LinearOpts {
   const u32x4 *a_packed = nullptr;     // the activation operand, already in operand order (then A is unused)
   bool pack_out = false;               // out receives the next layer's (K = Nout) operand, Mp rows, instead of row-major rows
   const uint16_t *addend = nullptr;    // row-major, same shape as out: out = addend + result
-  u32x4 *w_packed = nullptr;           // where the weight operand lives (default: the workspace)
-  bool pack_w = true;                  // false: w_packed already holds it
-  // FP8 with this layer's scalars prepared by k_fp8_prepare (nothing is zeroed, derived or
-  // recorded here): A, unless a_packed, is quantised with sc[2] and its amax reduced into sc[0];
-  // W, if pack_w, is quantised with sc[3]
+  const u32x4 *w_packed = nullptr;     // the weight operand
+  // FP8: this layer's scalars, prepared by k_fp8_prepare.  A, unless a_packed, is quantised with
+  // sc[2] and its amax reduced into sc[0]; `current`: sc[2] and sc[4] are taken from that amax first
   uint32_t *sc = nullptr;
+  bool current = false;
   const uint32_t *out_inv = nullptr;   // FP8 pack_out: the next layer's input scale ...
   uint32_t *out_amax = nullptr;        // ... and where the largest |output| is reduced into
 };
@@ -807,13 +884,12 @@ static bool half_tiles(int64_t M, int nt_n, int n_cu) {
   return t128 < t256;
 }
 
-// Y = A W^T + bias: brings both operands into operand order where they are not yet (FP8: after
-// taking their amax and quantising them), then the tiled kernel.
-static int launch_linear(const uint16_t *A, int64_t M, int K, const uint16_t *W, int Nout,
+// Y = A W^T + bias: brings the activation into operand order where it is not yet (FP8: quantised,
+// current scaling after taking its amax), then the tiled kernel.
+static int launch_linear(const uint16_t *A, int64_t M, int K, int Nout,
                          const float *bias, int gelu, uint16_t *out, int split, BlockWs &w,
                          hipStream_t st, const LinearOpts &o) {
-  u32x4 *const w_packed = o.w_packed ? o.w_packed : w.wpack;
-  if (o.fp8 && !o.sc && (!o.pack_w || o.a_packed || o.pack_out)) return LV_ERR_PARAM;
+  if (!o.w_packed || (o.fp8 && !o.sc) || (o.current && (o.a_packed || o.pack_out))) return LV_ERR_PARAM;
   if (o.pack_out && (o.addend || split != Nout || (o.fp8 && (!o.out_inv || !o.out_amax)))) return LV_ERR_PARAM;
   if (K % 64 != 0 || Nout % kTile != 0 || split % kTile != 0 || Nout % split != 0) return LV_ERR_SHAPE;
   int rc;
@@ -832,7 +908,7 @@ static int launch_linear(const uint16_t *A, int64_t M, int K, const uint16_t *W,
     const int n_tiles = (int)((M + BM - 1) / BM) * nt_n, slots = n_cu * (kTile / BM);
     const unsigned grid = (unsigned)(n_tiles < slots ? n_tiles : slots);
     hipLaunchKernelGGL((k_gemm_bt<F8, PK, BM>), dim3(grid), dim3(GemmShape<BM>::kThreads), GemmShape<BM>::kLds, st, act,
-                       w_packed, M, KS, nt_n, bias, gelu, out, split, alpha, n_tiles, o.addend, o.out_inv, o.out_amax);
+                       o.w_packed, M, KS, nt_n, bias, gelu, out, split, alpha, n_tiles, o.addend, o.out_inv, o.out_amax);
     return LV_OK;
   };
   auto launch = [&](auto fp8, const u32x4 *act, int KS, const float *alpha) -> int {
@@ -843,31 +919,17 @@ static int launch_linear(const uint16_t *A, int64_t M, int K, const uint16_t *W,
   };
   const u32x4 *a_packed = o.a_packed;
   if (o.fp8) {
-    auto amax = [&](const uint16_t *t, int64_t n16, uint32_t *dst) {
-      const unsigned g = (unsigned)(((n16 + 255) / 256) < 4096 ? ((n16 + 255) / 256) : 4096);
-      hipLaunchKernelGGL(k_amax_bf16, dim3(g), dim3(256), 0, st, (const u32x4 *)t, n16, dst);
-    };
-    auto quant = [&](const uint16_t *t, int64_t n, int64_t n_pad, const uint32_t *inv, u32x4 *dst, uint32_t *amax_out) {
-      hipLaunchKernelGGL(k_quant_pack_fp8, dim3((unsigned)(n_pad / 32), (unsigned)((K / 32 + 15) / 16)), dim3(256), 0, st, t, (int)n,
-                         K, inv, dst, amax_out);
-    };
-    uint32_t *sc = o.sc;
-    if (!sc) {
-      // current scaling: both amaxes first, then the scales, then the two quantisation passes
-      sc = w.fp8sc;
-      hipLaunchKernelGGL(k_fp8_zero, dim3(1), dim3(64), 0, st, sc);
-      amax(A, M * (K / 8), sc);
-      amax(W, (int64_t)Nout * (K / 8), sc + 1);
-      hipLaunchKernelGGL(k_fp8_scales, dim3(1), dim3(64), 0, st, sc);
-      quant(A, M, w.Mp, sc + 2, w.apack, (uint32_t *)nullptr);
-      quant(W, Nout, Nout, sc + 3, w_packed, (uint32_t *)nullptr);
-      a_packed = w.apack;
-    } else {
-      if (!a_packed) {
-        quant(A, M, w.Mp, sc + 2, w.apack, sc);
-        a_packed = w.apack;
+    uint32_t *const sc = o.sc;
+    if (!a_packed) {
+      if (o.current) {   // the tensor's own amax first
+        const int64_t n16 = M * (K / 8);
+        const unsigned g = (unsigned)(((n16 + 255) / 256) < 1024 ? ((n16 + 255) / 256) : 1024);
+        hipLaunchKernelGGL(k_amax_bf16, dim3(g), dim3(256), 0, st, (const u32x4 *)A, n16, sc);
+        hipLaunchKernelGGL(k_fp8_scales, dim3(1), dim3(64), 0, st, sc);
       }
-      if (o.pack_w) quant(W, Nout, Nout, sc + 3, w_packed, (uint32_t *)nullptr);
+      hipLaunchKernelGGL(k_quant_pack_fp8, dim3((unsigned)(w.Mp / 32), (unsigned)((K / 32 + 15) / 16)), dim3(256), 0, st, A, (int)M,
+                         K, (const uint32_t *)(sc + 2), w.apack, o.current ? (uint32_t *)nullptr : sc);
+      a_packed = w.apack;
     }
     if ((rc = launch(std::true_type{}, a_packed, K / 32, (const float *)(sc + 4)))) return rc;
   } else {
@@ -875,27 +937,39 @@ static int launch_linear(const uint16_t *A, int64_t M, int K, const uint16_t *W,
       if ((rc = launch_pack_rows(A, M, w.Mp, K, w.apack, st))) return rc;
       a_packed = w.apack;
     }
-    if (o.pack_w && (rc = launch_pack_rows(W, Nout, Nout, K, w_packed, st))) return rc;
     if ((rc = launch(std::false_type{}, a_packed, K / 16, nullptr))) return rc;
   }
   LV_HIP_CHECK_LAUNCH();
   return LV_OK;
 }
 
-// Delayed scaling with every layer's scalars prepared ahead of the kernels that produce the
-// layers' inputs: block L of the grid fills the 8 words of layer L (input amax cleared, the
-// weight's amax, 448 / the largest recorded input amax, 448 / the weight's amax, the product of
-// the two inverse scales).  Same arithmetic as k_fp8_scales; a history with nothing recorded yet gives scale 1.
+// Every layer's scalars, prepared ahead of the kernels that produce the layers' inputs: block L of
+// the grid fills the 8 words of layer L (input amax cleared, the weight's amax and 448 / it; delayed
+// scaling: also 448 / the largest recorded input amax, and the product of the two inverse scales;
+// a history with nothing recorded yet gives scale 1).  partial: the weights' partial maxima, which
+// are reduced into wamax first; NULL: wamax holds the amaxes.
 __global__ __launch_bounds__(64) void k_fp8_prepare(uint32_t *__restrict__ sc, const float *__restrict__ state,
-                                                    const uint32_t *__restrict__ wamax) {
+                                                    uint32_t *__restrict__ wamax, const uint32_t *__restrict__ partial) {
   const int lane = threadIdx.x, L = blockIdx.x;
-  const float *hist = state + (size_t)L * (LV_FP8_HISTORY + 2);
-  const float m = wave_max(fmaxf(hist[lane], lane + 64 < LV_FP8_HISTORY ? hist[lane + 64] : 0.f));
+  float wm = 0.f;
+  if (partial) {
+    const int e = weight_first_unit(L + 1) * kWAmaxUnit;
+    for (int i = weight_first_unit(L) * kWAmaxUnit + lane; i < e; i += 64) wm = fmaxf(wm, __uint_as_float(partial[i]));
+    wm = wave_max(wm);
+    if (lane == 0) wamax[L] = __float_as_uint(wm);
+  } else {
+    wm = __uint_as_float(wamax[L]);
+  }
+  float m = 0.f;
+  if (state) {
+    const float *hist = state + (size_t)L * (LV_FP8_HISTORY + 2);
+    m = wave_max(fmaxf(hist[lane], lane + 64 < LV_FP8_HISTORY ? hist[lane + 64] : 0.f));
+  }
   if (lane == 0) {
     uint32_t *s = sc + L * kFp8Words;
-    const float ia = fp8_scale_inv(__float_as_uint(m)), iw = fp8_scale_inv(wamax[L]);
+    const float ia = fp8_scale_inv(__float_as_uint(m)), iw = fp8_scale_inv(__float_as_uint(wm));
     s[0] = 0u;
-    s[1] = wamax[L];
+    s[1] = __float_as_uint(wm);
     s[2] = __float_as_uint(ia);
     s[3] = __float_as_uint(iw);
     s[4] = __float_as_uint((1.0f / ia) * (1.0f / iw));
@@ -930,42 +1004,45 @@ int launch_global_block(const uint16_t *z, int64_t M, int C, int heads, float sc
   const size_t cc16 = (size_t)C * C * 2 / 16;
   u32x4 *const wp_l[4] = {wp, wp + 3 * cc16, wp + 4 * cc16, wp + 8 * cc16};
   uint32_t *const wamax = (uint32_t *)(wp + 12 * cc16);
-  const uint16_t *const W[4] = {(const uint16_t *)bw.w_qkv, (const uint16_t *)bw.w_o, (const uint16_t *)bw.w_1,
-                                (const uint16_t *)bw.w_2};
-  const int w_rows[4] = {3 * C, C, 4 * C, C}, w_k[4] = {C, C, C, 4 * C};
+  const BlockWeights4 bw4 = {{(const uint16_t *)bw.w_qkv, (const uint16_t *)bw.w_o, (const uint16_t *)bw.w_1,
+                              (const uint16_t *)bw.w_2},
+                             {wp_l[0], wp_l[1], wp_l[2], wp_l[3]}};
   const float *const bias[4] = {bw.b_qkv, bw.b_o, bw.b_1, bw.b_2};
   const uint16_t *q = w.qkv, *k = w.qkv + (size_t)M * C, *v = w.qkv + (size_t)2 * M * C;
+
+  // the weights' amaxes and every layer's scalars, then the weights into operand order
+  const int unit = f8 ? 32 : 16, g1 = (C / unit + 15) / 16, g4 = (4 * C / unit + 15) / 16;
+  const unsigned wgrid = (unsigned)(C / 32 * (8 * g1 + g4));
+  if (f8) {
+    if (pack_w) hipLaunchKernelGGL(k_weights_amax, dim3(kWAmaxParts), dim3(256), 0, st, bw4, C, w.wpart);
+    hipLaunchKernelGGL(k_fp8_prepare, dim3(4), dim3(64), 0, st, w.fp8sc, delayed ? (const float *)bw.fp8_state : nullptr,
+                       wamax, pack_w ? (const uint32_t *)w.wpart : (const uint32_t *)nullptr);
+    if (pack_w) hipLaunchKernelGGL(k_weights_pack<true>, dim3(wgrid), dim3(256), 0, st, bw4, C, (const uint32_t *)w.fp8sc);
+  } else if (pack_w) {
+    hipLaunchKernelGGL(k_weights_pack<false>, dim3(wgrid), dim3(256), 0, st, bw4, C, (const uint32_t *)nullptr);
+  }
+  LV_HIP_CHECK_LAUNCH();
 
   if (delayed) {
     // FP8 layers, delayed scaling: every input scale is known before its tensor exists, so the
     // LayerNorms and the first MLP layer quantise their results themselves (taking the amax for
     // the history on the way); only the attention output goes through k_quant_pack_fp8.
     uint32_t *const sc = w.fp8sc;
-    if (pack_w) {
-      hipLaunchKernelGGL(k_fp8_zero, dim3(1), dim3(64), 0, st, wamax);
-      for (int l = 0; l < 4; ++l) {
-        const int64_t n16 = (int64_t)w_rows[l] * (w_k[l] / 8);
-        const unsigned g = (unsigned)(((n16 + 255) / 256) < 4096 ? ((n16 + 255) / 256) : 4096);
-        hipLaunchKernelGGL(k_amax_bf16, dim3(g), dim3(256), 0, st, (const u32x4 *)W[l], n16, wamax + l);
-      }
-    }
-    hipLaunchKernelGGL(k_fp8_prepare, dim3(4), dim3(64), 0, st, sc, (const float *)bw.fp8_state, (const uint32_t *)wamax);
     auto layer = [&](int l) {
       LinearOpts o;
       o.fp8 = true;
       o.sc = sc + l * kFp8Words;
       o.w_packed = wp_l[l];
-      o.pack_w = pack_w;
       return o;
     };
     if ((rc = launch_layernorm(z, nullptr, bw.ln1_g, bw.ln1_b, M, C, nullptr, st, w.apack, w.Mp, sc + 2, sc))) return rc;
     LinearOpts o = layer(0);
     o.a_packed = w.apack;
-    if ((rc = launch_linear(nullptr, M, C, W[0], 3 * C, bias[0], 0, w.qkv, C, w, st, o))) return rc;
+    if ((rc = launch_linear(nullptr, M, C, 3 * C, bias[0], 0, w.qkv, C, w, st, o))) return rc;
     if ((rc = launch_attn(q, k, v, w.a, M, heads, scale, attn_dtype, qk_norm, w.attn, st, after_pack))) return rc;
     if (after_attn && hipEventRecord(after_attn, st) != hipSuccess) return LV_ERR_HIP;
     o = layer(1);
-    if ((rc = launch_linear(w.a, M, C, W[1], C, bias[1], 0, w.u1, C, w, st, o))) return rc;
+    if ((rc = launch_linear(w.a, M, C, C, bias[1], 0, w.u1, C, w, st, o))) return rc;
     if ((rc = launch_layernorm(z, w.u1, bw.ln2_g, bw.ln2_b, M, C, nullptr, st, w.apack, w.Mp,
                                sc + 2 * kFp8Words + 2, sc + 2 * kFp8Words)))
       return rc;
@@ -974,11 +1051,11 @@ int launch_global_block(const uint16_t *z, int64_t M, int C, int heads, float sc
     o.pack_out = true;
     o.out_inv = sc + 3 * kFp8Words + 2;
     o.out_amax = sc + 3 * kFp8Words;
-    if ((rc = launch_linear(nullptr, M, C, W[2], 4 * C, bias[2], 1, w.h3, 4 * C, w, st, o))) return rc;
+    if ((rc = launch_linear(nullptr, M, C, 4 * C, bias[2], 1, w.h3, 4 * C, w, st, o))) return rc;
     o = layer(3);
     o.a_packed = (const u32x4 *)w.h3;
     o.addend = w.u1;
-    if ((rc = launch_linear(nullptr, M, 4 * C, W[3], C, bias[3], 0, delta, C, w, st, o))) return rc;
+    if ((rc = launch_linear(nullptr, M, 4 * C, C, bias[3], 0, delta, C, w, st, o))) return rc;
     hipLaunchKernelGGL(k_fp8_record_all, dim3(1), dim3(64), 0, st, (const uint32_t *)sc, (float *)bw.fp8_state);
     LV_HIP_CHECK_LAUNCH();
     return LV_OK;
@@ -986,9 +1063,9 @@ int launch_global_block(const uint16_t *z, int64_t M, int C, int heads, float sc
 
   auto layer = [&](int l) {
     LinearOpts o;
-    o.fp8 = f8;
+    o.fp8 = o.current = f8;
+    o.sc = f8 ? w.fp8sc + l * kFp8Words : nullptr;
     o.w_packed = wp_l[l];
-    o.pack_w = f8 || pack_w;
     return o;
   };
   // bf16 layers: the LayerNorms write their result in the following layer's operand order
@@ -996,7 +1073,7 @@ int launch_global_block(const uint16_t *z, int64_t M, int C, int heads, float sc
   if ((rc = launch_layernorm(z, nullptr, bw.ln1_g, bw.ln1_b, M, C, w.h, st, ln_packed, w.Mp))) return rc;
   LinearOpts o = layer(0);
   o.a_packed = ln_packed;
-  if ((rc = launch_linear(w.h, M, C, W[0], 3 * C, bias[0], 0, w.qkv, C, w, st, o))) return rc;
+  if ((rc = launch_linear(w.h, M, C, 3 * C, bias[0], 0, w.qkv, C, w, st, o))) return rc;
   // bf16 layers: where the attention kernel can, it writes the output projection's operand itself
   bool a_is_packed = false;
   if ((rc = launch_attn(q, k, v, w.a, M, heads, scale, attn_dtype, qk_norm, w.attn, st, after_pack, 1, nullptr,
@@ -1005,7 +1082,7 @@ int launch_global_block(const uint16_t *z, int64_t M, int C, int heads, float sc
   if (after_attn && hipEventRecord(after_attn, st) != hipSuccess) return LV_ERR_HIP;
   o = layer(1);
   o.a_packed = a_is_packed ? w.apack : nullptr;
-  if ((rc = launch_linear(w.a, M, C, W[1], C, bias[1], 0, w.u1, C, w, st, o))) return rc;
+  if ((rc = launch_linear(w.a, M, C, C, bias[1], 0, w.u1, C, w, st, o))) return rc;
   if ((rc = launch_layernorm(z, w.u1, bw.ln2_g, bw.ln2_b, M, C, w.h, st, ln_packed, w.Mp))) return rc;
   // bf16 layers: the first MLP layer writes its output in the second one's operand order.  All
   // layers: the second one's epilogue adds u1 (delta = u1 + u2, u2 rounded to bf16 first as if
@@ -1013,11 +1090,11 @@ int launch_global_block(const uint16_t *z, int64_t M, int C, int heads, float sc
   o = layer(2);
   o.a_packed = ln_packed;
   o.pack_out = !f8;
-  if ((rc = launch_linear(w.h, M, C, W[2], 4 * C, bias[2], 1, w.h3, 4 * C, w, st, o))) return rc;
+  if ((rc = launch_linear(w.h, M, C, 4 * C, bias[2], 1, w.h3, 4 * C, w, st, o))) return rc;
   o = layer(3);
   o.a_packed = f8 ? nullptr : (const u32x4 *)w.h3;
   o.addend = w.u1;
-  return launch_linear(w.h3, M, 4 * C, W[3], C, bias[3], 0, delta, C, w, st, o);
+  return launch_linear(w.h3, M, 4 * C, C, bias[3], 0, delta, C, w, st, o);
 }
 
 }  // namespace lv
