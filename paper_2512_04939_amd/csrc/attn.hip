@@ -58,9 +58,11 @@ __global__ __launch_bounds__(256) void k_attn_pack(const uint16_t *__restrict__ 
                                                    const uint16_t *__restrict__ v, int64_t n,
                                                    int heads, int n_kt, int qk_norm,
                                                    u32x4 *__restrict__ kp,
-                                                   u32x4 *__restrict__ vp) {
+                                                   u32x4 *__restrict__ vp, uint32_t *sync, int n_sync) {
   __shared__ __attribute__((aligned(16))) uint16_t vt[kKT][72];
   const int kt = blockIdx.x, t = threadIdx.x;
+  if (blockIdx.x == 0 && blockIdx.y == 0)   // what the pieces of cut blocks meet at
+    for (int i = t; i < n_sync; i += 256) sync[i] = 0u;
   const int seq = blockIdx.y / heads, head = blockIdx.y - seq * heads;
   const int C = heads * 64;
   k += (size_t)seq * n * C;
@@ -406,6 +408,89 @@ constexpr float kSumRaise = 1.0995116e12f;   // 2^40: a row sum beyond it raises
 constexpr int kBStages = 4;          // LDS ring of 64-key K/V stages
 
 
+// ---- Cutting the blocks of a short sequence.  A workgroup (256 queries of one head, all keys) takes
+// as long as any other and two fit on a CU, so fewer than 512 leave CUs idle: 368 blocks (5776 tokens,
+// 16 heads) put two on 112 CUs and one, which runs 1.5 times as fast alone, on 144: 149 us.  The
+// blocks are therefore cut in two along the keys, the first piece as long as k second pieces, so that
+// the slots the first pieces leave idle take k second pieces each (137 us).  The piece that comes to
+// its end first leaves its fp32 sums (O, row sums, ONLINE: the waves' references) in the workspace,
+// the other one waits until they are there (it is a workgroup that is running, and writing them is
+// the last thing it does), adds them to its own and finishes the block.  The sum of two is the same
+// in either order.  XCD x's blocks are those of its heads (heads a multiple of 8), so the same cut
+// serves every XCD.
+constexpr int kSlots = 64;                   // workgroups resident on an XCD: 32 CUs, 2 each
+struct AttnCut {
+  int n_cut;                                 // blocks per XCD, all of them cut (0: none is)
+  int small;                                 // stages of a second piece
+};
+constexpr size_t kPieceFloats = (size_t)256 * 64 + 2 * 256 * 2;   // O, row sums, references of one piece
+constexpr int kSyncWords = 2 * kXcd * kSlots;                 // per cut block: pieces that have arrived, sums are there
+
+// The end of a piece (every wave of its workgroup comes here, except those beyond the sequence end):
+// false: the other piece finishes the block; true: the sums now cover all keys.
+template <bool ONLINE>
+__device__ __forceinline__ bool join_pieces(f32x16 (&oacc)[2][2], float (&lsub)[2], float ref, uint32_t *sync,
+                                            float *partial, int wave, int lane) {
+#pragma clang fp contract(off)
+  __shared__ uint32_t arrived;
+  const bool lead = lane == 0 && __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) == 0;   // wave 0 is never beyond the end
+  if (lead) arrived = __hip_atomic_fetch_add(sync, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __syncthreads();
+  // The sums travel in relaxed agent-scope atomics of 8 bytes, which go to where every XCD sees them
+  // and are there when the wave's store counter says so.  (Plain stores between fences of that scope
+  // write back and invalidate the whole L2 each time: 150 us became 228.)
+  auto put = [&](size_t at, float x, float y) {
+    const uint64_t v = (uint64_t)__float_as_uint(x) | (uint64_t)__float_as_uint(y) << 32;
+    __hip_atomic_store((uint64_t *)partial + at, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  };
+  auto get = [&](size_t at) {
+    const uint64_t v = __hip_atomic_load((uint64_t *)partial + at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return f32x2{__uint_as_float((uint32_t)v), __uint_as_float((uint32_t)(v >> 32))};
+  };
+  const size_t row = (size_t)256 * 32 + wave * 64 + lane;   // after O: per wave and lane (row sum, reference)
+  if (arrived == 0u) {
+#pragma unroll
+    for (int sub = 0; sub < 2; ++sub)
+#pragma unroll
+      for (int dt = 0; dt < 2; ++dt)
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+          put((((wave * 2 + sub) * 2 + dt) * 8 + e) * 64 + lane, oacc[sub][dt][2 * e], oacc[sub][dt][2 * e + 1]);
+    put(row, lsub[0], lsub[1]);
+    if (ONLINE) put(row + 256, ref, 0.f);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (lead) __hip_atomic_store(sync + 1, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return false;
+  }
+  if (lead)
+    while (__hip_atomic_load(sync + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0u) __builtin_amdgcn_s_sleep(1);
+  __syncthreads();
+  float mine = 1.0f, theirs = 1.0f;
+  if (ONLINE) {                              // both to the larger of the two references
+    const float r = get(row + 256)[0], top = fmaxf(ref, r);
+    mine = __builtin_amdgcn_exp2f(ref - top);
+    theirs = __builtin_amdgcn_exp2f(r - top);
+  }
+  const f32x2 l = get(row);
+#pragma unroll
+  for (int sub = 0; sub < 2; ++sub) {
+#pragma unroll
+    for (int dt = 0; dt < 2; ++dt) {
+      f32x2 v[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) v[e] = get((((wave * 2 + sub) * 2 + dt) * 8 + e) * 64 + lane);
+#pragma unroll
+      for (int e = 0; e < 8; ++e)
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+          oacc[sub][dt][2 * e + i] = ONLINE ? oacc[sub][dt][2 * e + i] * mine + v[e][i] * theirs : oacc[sub][dt][2 * e + i] + v[e][i];
+    }
+    lsub[sub] = ONLINE ? lsub[sub] * mine + l[sub] * theirs : lsub[sub] + l[sub];
+  }
+  return true;
+}
+
 // PACKED (one sequence, no residual, not ONLINE): `o` is a linear layer's activation operand
 // buffer and receives the output rows in that layer's fragment order, [row / 32][k-step of 16
 // channels][lane = row % 32 + 32 * (second 8 of the 16)], 16 bytes each.
@@ -413,15 +498,28 @@ template <bool ONLINE, bool PACKED = false>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_attn_bf16_main(
     const uint16_t *q, const u32x4 *__restrict__ kp, const u32x4 *__restrict__ vp, uint16_t *o,
     const uint16_t *res, int64_t n, int heads, int n_seq, int n_kt, int nqb, float c, int qk_norm,
-    uint32_t *__restrict__ redo, int redo_stride) {
+    uint32_t *__restrict__ redo, int redo_stride, AttnCut cut, uint32_t *sync, float *partial) {
   __shared__ u32x4 ks[kBStages][8 * kFragU4];
   __shared__ u32x4 vs[kBStages][8 * kFragU4];
   const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5, ql = lane & 31;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int C = heads * 64;
   int sh, qb;   // (sequence, head) pair and query block; each XCD gets whole pairs
+  int first = 0, nkv = n_kt >> 1;   // the stages this workgroup takes (a piece: not all of them)
+  int piece = -1;                   // number of the cut block
   if (((heads * n_seq) & 7) == 0) {
-    const int hp = (heads * n_seq) >> 3, xcd = blockIdx.x & 7, local = blockIdx.x >> 3;
+    const int hp = (heads * n_seq) >> 3, xcd = blockIdx.x & 7;
+    int local = blockIdx.x >> 3;
+    if (cut.n_cut) {                // first all first pieces, then all second ones
+      if (local < cut.n_cut) {
+        nkv -= cut.small;
+      } else {
+        local -= cut.n_cut;
+        first = nkv - cut.small;
+        nkv = cut.small;
+      }
+      piece = xcd * cut.n_cut + local;
+    }
     sh = xcd * hp + local / nqb;
     qb = local % nqb;
   } else {
@@ -434,9 +532,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   if (res) res += (size_t)seq * n * C;
   const int64_t q0 = (int64_t)qb * kBQB + wave * kQW;
 
-  const int nkv = n_kt >> 1, nkt = n_kt;
-  const u32x4 *kh = kp + (size_t)sh * n_kt * 4 * kFragU4;
-  const u32x4 *vh = vp + (size_t)sh * n_kt * 4 * kFragU4;
+  const int nkt = 2 * nkv;
+  const int64_t n_keys = n - (int64_t)first * kKV;   // keys from the first one of these stages to the sequence end
+  const u32x4 *kh = kp + ((size_t)sh * n_kt + 2 * first) * 4 * kFragU4;
+  const u32x4 *vh = vp + ((size_t)sh * n_kt + 2 * first) * 4 * kFragU4;
   // Stage `stage` of this head's packed K and V (64 keys, 8 KB each) goes from global memory
   // straight into its ring slot, 1 KB per wave and instruction (global_load_lds_dwordx4: lane l
   // of a wave lands at the wave's LDS base + 16 l).  No registers are staged, so a stage can be
@@ -522,11 +621,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
             oacc[sub][dt], 0, 0, 0);
   };
   auto mask_tail = [&](int t, int sub) {   // keys beyond the sequence end
-    if ((int64_t)(t + 1) * kKT > n) {
+    if ((int64_t)(t + 1) * kKT > n_keys) {
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
         const int64_t key = (int64_t)t * kKT + (r >> 2) * 8 + h * 4 + (r & 3);
-        if (key >= n) sacc[sub][r] = -INFINITY;
+        if (key >= n_keys) sacc[sub][r] = -INFINITY;
       }
     }
   };
@@ -756,6 +855,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     const float lsum = lrow[sub][0] + lrow[sub][1];
     lsub[sub] = lsum + __shfl_xor(lsum, 32, 64);
   }
+  __shared__ int any_low;     // pieces only
+  if (piece >= 0) {
+    if (ONLINE && __syncthreads_or(over)) {   // the block is the second pass's; the other piece waits for nobody
+      if (tid == 0) redo[(size_t)sh * redo_stride + qb] = 1u;
+      return;
+    }
+    if (ONLINE && tid == 0) any_low = 0;
+    if (!join_pieces<ONLINE>(oacc, lsub, ref_run, sync + 2 * piece, partial + (size_t)piece * kPieceFloats, wave, lane)) return;
+  }
   if (ONLINE) {
     // A row whose scores all lie ~60 binades or more below its wave's reference has lost its
     // weights to underflow, and a reference beyond kRefUseful is not resolved: the whole
@@ -764,7 +872,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     bool low = over;
 #pragma unroll
     for (int sub = 0; sub < 2; ++sub) low |= q0 + sub * 32 + ql < n && !(lsub[sub] >= 8.67e-19f);   // 2^-60
-    if (__syncthreads_or(low)) {
+    bool redo_block;
+    if (piece >= 0) {         // the waves beyond the sequence end are gone by now: a plain barrier
+      if (__builtin_amdgcn_ballot_w64(low) != 0 && lane == 0) any_low = 1;
+      __syncthreads();
+      redo_block = any_low != 0;
+    } else {
+      redo_block = __syncthreads_or(low);
+    }
+    if (redo_block) {
       if (tid == 0) redo[(size_t)sh * redo_stride + qb] = 1u;
       return;
     }
@@ -1468,6 +1584,30 @@ static int n_key_tiles(int64_t n) { return (int)(2 * ((n + kKV - 1) / kKV)); }
 // 512-query block of the second pass
 static size_t fp8_flag_words(int heads, int64_t n) { return (size_t)heads * 2 * ((n + kQB - 1) / kQB); }
 
+// Whether and how (see AttnCut): b blocks for kSlots slots per XCD; a slot without a first piece takes
+// k = ceil(b / idle slots) second pieces, each with a start of its own (about 6 stages of 64 keys).
+// A stage takes about 1 us with one workgroup per CU and 1.55 with two, and a cut about 9 us in all.
+// Measured with 16 heads, whole against cut: 1500 tokens 26 -> 22 us, 4500 111 -> 100, 5776 149 -> 137,
+// 3500 57.4 -> 56.  With a full round before them, blocks do not end together and the last round's
+// idle slots are not there to be had (15432 tokens 866 -> 876 us, 20000 1356 -> 1364): not cut.  Nor
+// are the blocks of many sequences.
+static AttnCut attn_cut(int heads, int64_t n) {
+  const int64_t nqb = (n + kBQB - 1) / kBQB, nkv = (n + kKV - 1) / kKV, b = heads / kXcd * nqb;
+  if (heads % kXcd != 0 || b >= kSlots) return {0, 0};
+  const int64_t idle = kSlots - b, k = (b + idle - 1) / idle;
+  const int64_t small = (nkv - 6 * (k - 1)) / (k + 1);
+  if (small < 6) return {0, 0};
+  const auto stage_us = [](int64_t per_xcd) { return per_xcd <= kSlots / 2 ? 1.0 : 1.55; };
+  const int64_t chain = k * (small + 6) - 6, longest = nkv - small > chain ? nkv - small : chain;
+  const double whole = (double)nkv * stage_us(b), cut = (double)longest * stage_us(2 * b) + 9.0;
+  if (cut > 0.97 * whole) return {0, 0};
+  return {(int)b, (int)small};
+}
+static size_t cut_bytes(int heads, int64_t n, int n_seq) {
+  const AttnCut c = n_seq == 1 ? attn_cut(heads, n) : AttnCut{0, 0};
+  return c.n_cut ? kSyncWords * sizeof(uint32_t) + align_up((size_t)kXcd * c.n_cut * kPieceFloats * sizeof(float), 256) : 0;
+}
+
 size_t attn_ws_bytes(int heads, int64_t n_tokens, int attn_dtype, int n_seq) {
   const size_t elem = attn_dtype == LV_ATTN_FP8_E4M3 ? sizeof(u32x2) : sizeof(u32x4);
   const size_t per = (size_t)heads * n_seq * n_key_tiles(n_tokens) * 4 * kFragU4 * elem;
@@ -1476,7 +1616,7 @@ size_t attn_ws_bytes(int heads, int64_t n_tokens, int attn_dtype, int n_seq) {
   size_t total = 256 + 2 * align_up(per, 256);
   if (attn_dtype == LV_ATTN_FP8_E4M3) total += 2 * align_up(per, 256) + align_up(fp8_flag_words(heads, n_tokens) * 4, 256);
   // bf16: the flags of the online-softmax pass (one word per 256-query block)
-  else total += align_up(fp8_flag_words(heads * n_seq, n_tokens) * 4, 256);
+  else total += align_up(fp8_flag_words(heads * n_seq, n_tokens) * 4, 256) + cut_bytes(heads, n_tokens, n_seq);
   return total;
 }
 
@@ -1539,26 +1679,35 @@ int launch_attn(const uint16_t *q, const uint16_t *k, const uint16_t *v, uint16_
   // blocks the first pass flagged (normally none: its workgroups return at once)
   const bool bounded = qk_norm && 64.25f * c <= 64.0f;
   uint32_t *redo = (uint32_t *)(frag + 2 * per);
-  if (!bounded) {
-    const size_t words = fp8_flag_words(heads * n_seq, n);
+  const size_t words = fp8_flag_words(heads * n_seq, n);
+  if (!bounded)
     hipLaunchKernelGGL(k_zero_words, dim3((unsigned)((words + 255) / 256)), dim3(256), 0, st, redo, words,
                        (uint32_t *)nullptr);
-  }
-  hipLaunchKernelGGL(k_attn_pack, dim3((unsigned)n_kt, (unsigned)(heads * n_seq)), dim3(256), 0, st,
-                     k, v, n, heads, n_kt, qk_norm, kp, vp);
-  if (after_pack && hipEventRecord(after_pack, st) != hipSuccess) return LV_ERR_HIP;
   const int nqb2 = (int)((n + kBQB - 1) / kBQB);
+  int dev = 0, n_cu = 0;
+  if (hipGetDevice(&dev) != hipSuccess ||
+      hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+    return LV_ERR_HIP;
+  AttnCut cut = {0, 0};
+  if (n_seq == 1 && !res && 2 * n_cu == kXcd * kSlots) cut = attn_cut(heads, n);
+  uint32_t *sync = redo + align_up(words * 4, 256) / 4;
+  float *partial = (float *)(sync + kSyncWords);
+  hipLaunchKernelGGL(k_attn_pack, dim3((unsigned)n_kt, (unsigned)(heads * n_seq)), dim3(256), 0, st,
+                     k, v, n, heads, n_kt, qk_norm, kp, vp, sync, cut.n_cut ? kSyncWords : 0);
+  if (after_pack && hipEventRecord(after_pack, st) != hipSuccess) return LV_ERR_HIP;
+  const unsigned grid = cut.n_cut ? (unsigned)(kXcd * 2 * cut.n_cut) : (unsigned)(nqb2 * heads * n_seq);
   if (bounded && o_packed && wrote_packed && n_seq == 1 && !res) {
-    hipLaunchKernelGGL((k_attn_bf16_main<false, true>), dim3((unsigned)(nqb2 * heads)), dim3(256), 0,
+    hipLaunchKernelGGL((k_attn_bf16_main<false, true>), dim3(grid), dim3(256), 0,
                        st, q, kp, vp, (uint16_t *)o_packed, res, n, heads, n_seq, n_kt, nqb2, c, qk_norm,
-                       (uint32_t *)nullptr, 0);
+                       (uint32_t *)nullptr, 0, cut, sync, partial);
     *wrote_packed = true;
   } else if (bounded) {
-    hipLaunchKernelGGL(k_attn_bf16_main<false>, dim3((unsigned)(nqb2 * heads * n_seq)), dim3(256), 0,
-                       st, q, kp, vp, o, res, n, heads, n_seq, n_kt, nqb2, c, qk_norm, (uint32_t *)nullptr, 0);
+    hipLaunchKernelGGL(k_attn_bf16_main<false>, dim3(grid), dim3(256), 0,
+                       st, q, kp, vp, o, res, n, heads, n_seq, n_kt, nqb2, c, qk_norm, (uint32_t *)nullptr, 0, cut, sync,
+                       partial);
   } else {
-    hipLaunchKernelGGL(k_attn_bf16_main<true>, dim3((unsigned)(nqb2 * heads * n_seq)), dim3(256), 0,
-                       st, q, kp, vp, o, res, n, heads, n_seq, n_kt, nqb2, c, qk_norm, redo, 2 * nqb);
+    hipLaunchKernelGGL(k_attn_bf16_main<true>, dim3(grid), dim3(256), 0,
+                       st, q, kp, vp, o, res, n, heads, n_seq, n_kt, nqb2, c, qk_norm, redo, 2 * nqb, cut, sync, partial);
     hipLaunchKernelGGL(k_attn_bf16, dim3((unsigned)(nqb * heads * n_seq)), dim3(512), 0, st, q, kp,
                        vp, o, res, n, heads, n_seq, n_kt, nqb, c, qk_norm, (const uint32_t *)redo);
   }

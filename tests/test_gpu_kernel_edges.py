@@ -225,3 +225,40 @@ def test_importance_edges(B, frames, h, w, patch, dim, kind):
     ref, psi_g = O.importance(im.astype(np.float64) / (255.0 if u8 else 1.0), xf, oracle_params(wl))
     assert np.abs(grad.cpu().numpy() - psi_g.reshape(frames, -1)).max() <= 2e-5 * max(1.0, np.abs(psi_g).max())
     assert np.abs(score.cpu().numpy() - ref.reshape(frames, -1)).max() <= 2e-5
+
+
+# ------------------------------------------------------------------------------- attention
+def _attn64(q, k, v, norm, heads):
+    import torch
+    out = torch.empty(q.shape, dtype=torch.float64, device=q.device)
+    for h in range(heads):
+        qh, kh, vh = (t[:, h * 64:h * 64 + 64].double() for t in (q, k, v))
+        if norm:
+            qh, kh = (t / torch.sqrt((t * t).mean(1, keepdim=True) + 1e-6) for t in (qh, kh))
+        for i in range(0, len(q), 4096):
+            out[i:i + 4096, h * 64:h * 64 + 64] = torch.softmax(qh[i:i + 4096] @ kh.t().contiguous() * 0.125, 1) @ vh
+    return out
+
+
+# short sequences whose blocks are cut along the keys (8 XCDs with 64 slots): 12 blocks per XCD in
+# halves, 17 and 46 (three second pieces per idle slot, a ragged last block and key stage), 63 (nothing
+# to gain, not cut), 65 (more than a round, not cut), 33 with a last block of one query
+@pytest.mark.parametrize("n,heads", [(1500, 16), (4352, 8), (11709, 8), (5776, 16), (16640, 8), (16128, 8), (8193, 8)])
+@pytest.mark.parametrize("kind", ["norm", "plain", "climbing"])
+def test_attention_cut_rounds(B, n, heads, kind):
+    import torch
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n)
+    q, k, v = (torch.randn(n, heads * 64, generator=g, device="cuda") for _ in range(3))
+    if kind == "climbing":   # scores grow along the keys: every segment has a reference of its own
+        k *= torch.linspace(0.1, 6.0, n, device="cuda")[:, None]
+    q, k, v = (t.to(torch.bfloat16) for t in (q, k, v))
+    ph = B.make_params(1, 1, 1, heads * 64, heads, n_special=0, qk_norm=int(kind == "norm"))
+    o = torch.full_like(q, float("nan"))
+    B.litevggt_global_attn(ph, n, q, k, v, o, B.alloc_ws(B.litevggt_attn_ws_bytes(ph, n)))
+    again = torch.full_like(q, float("nan"))
+    B.litevggt_global_attn(ph, n, q, k, v, again, B.alloc_ws(B.litevggt_attn_ws_bytes(ph, n)))
+    torch.cuda.synchronize()
+    ref = _attn64(q, k, v, kind == "norm", heads)
+    assert float((o.double() - ref).abs().max() / ref.abs().max()) <= 2e-2
+    assert torch.equal(o, again)     # sums are added in key order
