@@ -396,11 +396,12 @@ __global__ __launch_bounds__(256) void k_weights_pack(BlockWeights4 bw, int C, c
 
 // ---------------------------------------------------------------------------------------
 // Y[M, Nout] = A[M, K] W[Nout, K]^T + bias (optionally GELU), bf16 in and out, fp32
-// accumulation.  Output tiles of BM rows x 256 columns, waves of 64 rows x 128 columns; both
+// accumulation.  Output tiles of BM rows x BN columns, waves of 64 rows x BN / 2 columns; both
 // operands come pre-packed fragment-major and are fetched straight into an LDS ring (2 k-steps
-// per stage).  BM = 256: 8 waves, 4 stages, one workgroup per CU, 128 flop per fetched byte.
-// BM = 128: 4 waves, 3 stages, two workgroups per CU, whose epilogues run beside each other's
-// main loops: for row counts that fill the chip badly with 256-row tiles (half_tiles).  Bound by
+// per stage).  256 x 256: 8 waves, 4 stages, one workgroup per CU, 128 flop per fetched byte.
+// 128 x 256 and 128 x 128: 4 waves, 3 and 4 stages, two workgroups per CU, whose epilogues run
+// beside each other's main loops: for row counts that fill the chip badly with larger tiles
+// (tile_shape).  Bound by
 // the matrix pipe and what keeps a wave from feeding it: issuing the fetches, the barrier, the
 // fragment reads; the MFMAs alone take 70 % of the loop's time.  The finished tile goes from the accumulators straight to global
 // memory (bias, optional GELU, one rounding to bf16); `addend` (optional, shaped like the
@@ -420,16 +421,17 @@ __global__ __launch_bounds__(256) void k_weights_pack(BlockWeights4 bw, int C, c
 __device__ __forceinline__ void lds_read1_async(u32x4 &dst, uint32_t addr) {
   asm volatile("ds_read_b128 %0, %1" : "=&v"(dst) : "v"(addr) : "memory");
 }
-constexpr int kTile = 256;                   // output channels per workgroup tile, and what rows are padded to
-// Shape of a workgroup with BM rows per tile: BM / 32 waves of 64 rows x 128 columns.
-template <int BM>
+constexpr int kTile = 256;                   // what rows are padded to and output channels are a multiple of
+// Shape of a workgroup with tiles of BM rows x BN columns: (BM / 64) x 2 waves of 64 rows x BN / 2 columns.
+template <int BM, int BN>
 struct GemmShape {
   static constexpr int kWaves = BM / 32, kThreads = kWaves * 64;
-  static constexpr int kFragA = BM / 32;                  // activation fragments per k-step (8 of weights)
-  static constexpr int kStageU4 = 2 * (8 + kFragA) * 64;  // [weights: 2 k-steps x 8 | activations: 2 x kFragA][64 lanes]
-  static constexpr int kStages = BM == 256 ? 4 : 3;       // LDS ring: 128 KB, one workgroup per CU; or 72 KB, two
-  static constexpr int kLoads = 2 * (8 + kFragA) / kWaves;   // fragments a wave fetches per stage
-  static constexpr size_t kLds = (size_t)kStages * kStageU4 * 16 + 2 * kTile * sizeof(float);   // + two tiles' bias values
+  static constexpr int kB = BN / 64;                      // weight fragments of a wave per k-step (2 of activations)
+  static constexpr int kFragW = BN / 32, kFragA = BM / 32;   // fragments of the tile per k-step
+  static constexpr int kStageU4 = 2 * (kFragW + kFragA) * 64;   // [weights: 2 k-steps x kFragW | activations: 2 x kFragA][64 lanes]
+  static constexpr int kStages = BM == 128 && BN == 256 ? 3 : 4;   // LDS ring: 128 KB, one workgroup per CU; 72 or 64 KB, two
+  static constexpr int kLoads = 2 * (kFragW + kFragA) / kWaves;   // fragments a wave fetches per stage
+  static constexpr size_t kLds = (size_t)kStages * kStageU4 * 16 + 2 * BN * sizeof(float);   // + two tiles' bias values
 };
 
 // GELU in its erf form, x * Phi(x).  erfc(|x| / sqrt 2) by the rational-times-exponential form of
@@ -447,14 +449,15 @@ __device__ __forceinline__ float gelu_erf(float v) {
   return 0.5f * v * (v < 0.f ? erfc_abs : 2.0f - erfc_abs);
 }
 
-template <bool FP8, bool PACKED, int BM>
-__global__ __launch_bounds__(GemmShape<BM>::kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_gemm_bt(
+template <bool FP8, bool PACKED, int BM, int BN>
+__global__ __launch_bounds__((GemmShape<BM, BN>::kThreads)) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_gemm_bt(
     const u32x4 *__restrict__ ap, const u32x4 *__restrict__ wp, int64_t M, int KS, int nt_n,
     const float *__restrict__ bias, int gelu, uint16_t *__restrict__ out, int split,
-    const float *__restrict__ alpha_p, int n_tiles, const uint16_t *__restrict__ addend,
+    const float *__restrict__ alpha_p, int n_tiles, int rows_by_xcd, const uint16_t *__restrict__ addend,
     const uint32_t *__restrict__ out_inv, uint32_t *__restrict__ out_amax) {
-  using S = GemmShape<BM>;
-  constexpr int kStages = S::kStages, kStageU4 = S::kStageU4;
+  using S = GemmShape<BM, BN>;
+  constexpr int kStages = S::kStages, kStageU4 = S::kStageU4, kB = S::kB;
+  constexpr bool kTwoSets = !FP8 || kB == 2;   // registers for two sets of weight fragments
   extern __shared__ u32x4 ring[];
   const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -466,11 +469,10 @@ __global__ __launch_bounds__(GemmShape<BM>::kThreads) __attribute__((amdgpu_wave
   // activation tile is fetched into one L2 only, and walks its tiles one group of G = 4 column
   // tiles after the other, row by row inside a group: the G weight tiles of a group (2 MB at
   // K = 1024) stay in that L2 meanwhile, and an activation tile is shared by G workgroups.  Its
-  // workgroups take this list in turn, so they differ by one tile at most.  With no more tiles than
-  // workgroups each takes one and the order does not matter.
+  // workgroups take this list in turn, so they differ by one tile at most.  (Few rows: plain order.)
   const int nt_m = n_tiles / nt_n;
   const int xcd = blockIdx.x & (kXcd - 1);
-  const bool by_xcd = (gridDim.x & (kXcd - 1)) == 0 && n_tiles > (int)gridDim.x;
+  const bool by_xcd = rows_by_xcd != 0 && (gridDim.x & (kXcd - 1)) == 0;
   const int my_rows = by_xcd ? (nt_m - xcd + kXcd - 1) / kXcd : nt_m;   // row tiles of this XCD
   const int my_tiles = my_rows * nt_n, stride = by_xcd ? (int)gridDim.x >> 3 : (int)gridDim.x;
   const int n_group = my_rows * 4;                                     // tiles of a full column group
@@ -493,13 +495,13 @@ __global__ __launch_bounds__(GemmShape<BM>::kThreads) __attribute__((amdgpu_wave
   tile_at(v, tm, tn);
   const bool more = v + stride < my_tiles;
   if (more) tile_at(v + stride, tm2, tn2);
-  // this tile's 256 bias values wait in LDS behind the ring (read in the epilogue, many barriers
+  // this tile's bias values wait in LDS behind the ring (read in the epilogue, many barriers
   // later); two buffers in turn, so a wave still in the previous tile's epilogue reads its own
-  float *bias_lds = (float *)(ring + (size_t)kStages * kStageU4) + parity * kTile;
-  if (tid < kTile) bias_lds[tid] = bias ? bias[tn * kTile + tid] : 0.f;
+  float *bias_lds = (float *)(ring + (size_t)kStages * kStageU4) + parity * BN;
+  if (tid < BN) bias_lds[tid] = bias ? bias[tn * BN + tid] : 0.f;
 
   // fetch: with 8 waves, waves 0-3 move 4 weight fragments of a stage each, waves 4-7 4 activation
-  // fragments; with 4 waves each moves 4 weight and 2 activation fragments
+  // fragments; with 4 waves each moves kB weight and 2 activation fragments
   const int f_ks = (wave >> 1) & 1;
   int pf_g = 0, f_tm = tm, f_tn = tn;
   auto slot_of = [](int g) { return kStages == 4 ? g & 3 : g % kStages; };
@@ -514,17 +516,18 @@ __global__ __launch_bounds__(GemmShape<BM>::kThreads) __attribute__((amdgpu_wave
       f_src[0] = (wave >> 2 ? ap + (size_t)(f_tm * 8 + a0) * KS * 64 : wp + (size_t)(f_tn * 8 + a0) * KS * 64) + at;
       f_dst[0] = stage + (size_t)(wave * 4) * 64;
     } else {
-      f_src[0] = wp + (size_t)(f_tn * 8 + (wave & 1) * 4) * KS * 64 + at;
-      f_src[1] = ap + (size_t)(f_tm * S::kFragA + (wave & 1) * (S::kFragA / 2)) * KS * 64 + at;
-      f_dst[0] = stage + (size_t)(wave * 4) * 64;
-      f_dst[1] = stage + (size_t)(16 + wave * (S::kFragA / 2)) * 64;
+      f_src[0] = wp + (size_t)(f_tn * S::kFragW + (wave & 1) * kB) * KS * 64 + at;
+      f_src[1] = ap + (size_t)(f_tm * S::kFragA + (wave & 1) * 2) * KS * 64 + at;
+      f_dst[0] = stage + (size_t)(wave * kB) * 64;
+      f_dst[1] = stage + (size_t)(2 * S::kFragW + wave * 2) * 64;
     }
     ++pf_g;
   };
   auto fetch_one = [&](auto idx) {
     constexpr int i = decltype(idx)::value;
+    constexpr int part = i >= kB ? 1 : 0, j = i - part * kB;
     if constexpr (i < S::kLoads)
-      __builtin_amdgcn_global_load_lds(f_src[i >> 2] + (size_t)(i & 3) * KS * 64 + lane, f_dst[i >> 2] + (i & 3) * 64, 16, 0, 0);
+      __builtin_amdgcn_global_load_lds(f_src[part] + (size_t)j * KS * 64 + lane, f_dst[part] + j * 64, 16, 0, 0);
   };
   auto fetch = [&]() {
     fetch_begin();
@@ -537,19 +540,20 @@ __global__ __launch_bounds__(GemmShape<BM>::kThreads) __attribute__((amdgpu_wave
   };
   const uint32_t ring_lane = lds_addr(&ring[lane]);
   // byte offsets of this wave's fragments inside a stage, k-step 0, and from k-step 0 to k-step 1
-  const uint32_t b_off = (uint32_t)((wn * 4) * 1024), a_off = (uint32_t)((16 + wd * 2) * 1024);
-  constexpr uint32_t b_ks = 8 * 1024, a_ks = S::kFragA * 1024;
-  u32x4 fb[FP8 ? 1 : 2][2][4], fa[2][2][2];   // [set][k-step (FP8: unit of 32)][fragment]
-  auto read_frags = [&](int g, int ks, u32x4(&b)[4], u32x4(&a)[2]) {
+  const uint32_t b_off = (uint32_t)((wn * kB) * 1024), a_off = (uint32_t)((2 * S::kFragW + wd * 2) * 1024);
+  constexpr uint32_t b_ks = S::kFragW * 1024, a_ks = S::kFragA * 1024;
+  u32x4 fb[kTwoSets ? 2 : 1][2][kB], fa[2][2][2];   // [set][k-step (FP8: unit of 32)][fragment]
+  auto read_frags = [&](int g, int ks, u32x4(&b)[kB], u32x4(&a)[2]) {
     const uint32_t base = ring_lane + (uint32_t)(slot_of(g) * kStageU4 * 16);
-    lds_read4_async(b, base + b_off + ks * b_ks);
+    if constexpr (kB == 4) lds_read4_async(b, base + b_off + ks * b_ks);
+    else lds_read2_async(b, base + b_off + ks * b_ks);
     lds_read2_async(a, base + a_off + ks * a_ks);
   };
-  f32x16 acc[2][4];
+  f32x16 acc[2][kB];
 #pragma unroll
   for (int a = 0; a < 2; ++a)
 #pragma unroll
-    for (int b = 0; b < 4; ++b)
+    for (int b = 0; b < kB; ++b)
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[a][b][r] = 0.f;
   if (primed) {
@@ -571,15 +575,17 @@ __global__ __launch_bounds__(GemmShape<BM>::kThreads) __attribute__((amdgpu_wave
   // MFMAs with it), sit between pairs of MFMAs, so that the MFMA pipe has queued work of this wave
   // while it does them.  (All of it behind the barrier at the head of a k-step: 1046 us for the qkv
   // layer at M = 143,232, C = 1024 in bf16, 900 like this.)
-  auto wait_set = [&](u32x4(&b)[2][4], u32x4(&a)[2][2]) {
+  auto wait_set = [&](u32x4(&b)[2][kB], u32x4(&a)[2][2]) {
     asm volatile("s_waitcnt lgkmcnt(0)"
-                 : "+v"(b[0][0]), "+v"(b[0][1]), "+v"(b[0][2]), "+v"(b[0][3]), "+v"(b[1][0]), "+v"(b[1][1]),
-                   "+v"(b[1][2]), "+v"(b[1][3]), "+v"(a[0][0]), "+v"(a[0][1]), "+v"(a[1][0]), "+v"(a[1][1])
+                 : "+v"(b[0][0]), "+v"(b[0][1]), "+v"(b[1][0]), "+v"(b[1][1]), "+v"(a[0][0]), "+v"(a[0][1]),
+                   "+v"(a[1][0]), "+v"(a[1][1])
                  :
                  : "memory");
+    if constexpr (kB == 4)
+      asm volatile("" : "+v"(b[0][2]), "+v"(b[0][3]), "+v"(b[1][2]), "+v"(b[1][3]) : : "memory");
   };
   // the two MFMAs of column block bi: of k-step u, or (FP8) of both, whose units lie side by side
-  auto pair = [&](const u32x4(&b)[2][4], const u32x4(&a)[2][2], int u, int bi) {
+  auto pair = [&](const u32x4(&b)[2][kB], const u32x4(&a)[2][2], int u, int bi) {
 #pragma unroll
     for (int ai = 0; ai < 2; ++ai) {
       if constexpr (FP8)
@@ -596,16 +602,16 @@ __global__ __launch_bounds__(GemmShape<BM>::kThreads) __attribute__((amdgpu_wave
     __builtin_amdgcn_sched_barrier(0);
   };
 #define LV_LD(i) ld(std::integral_constant<int, i>{})
-  auto stage = [&](int g, u32x4(&bc)[2][4], u32x4(&ac)[2][2], u32x4(&bn)[2][4], u32x4(&an)[2][2]) {
+  auto stage = [&](int g, u32x4(&bc)[2][kB], u32x4(&ac)[2][2], u32x4(&bn)[2][kB], u32x4(&an)[2][2]) {
     __builtin_amdgcn_sched_barrier(0);
     wait_set(bc, ac);
-    if constexpr (!FP8) pair(bc, ac, 0, 0);
+    if constexpr (kTwoSets) pair(bc, ac, 0, 0);
     __builtin_amdgcn_sched_barrier(0);
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"((kStages - 2) * S::kLoads) : "memory");   // stage g+1 has landed; later ones may be in flight
     __builtin_amdgcn_s_barrier();                            // and nobody reads stage g from LDS any more
     __builtin_amdgcn_sched_barrier(0);
     // stage g + kStages goes to the slot of stage g; past the end the reads get a stale slot, never used
-    if constexpr (FP8) {
+    if constexpr (!kTwoSets) {
       const uint32_t base = ring_lane + (uint32_t)(slot_of(g + 1) * kStageU4 * 16);
       auto again = [&](int bi) {                             // the next stage's weight fragment bi
         __builtin_amdgcn_sched_barrier(0);
@@ -627,32 +633,48 @@ __global__ __launch_bounds__(GemmShape<BM>::kThreads) __attribute__((amdgpu_wave
       LV_LD(3); LV_LD(5);
       pair(bc, ac, 0, 3);
       again(3);
+    } else if constexpr (FP8) {                              // kB == 2
+      read_frags(g + 1, 0, bn[0], an[0]);
+      read_frags(g + 1, 1, bn[1], an[1]);
+      fetch_begin();
+      LV_LD(0); LV_LD(1);
+      pair(bc, ac, 0, 1);
+      LV_LD(2); LV_LD(3);
     } else {
       pair(bc, ac, 0, 1);
       __builtin_amdgcn_sched_barrier(0);
       read_frags(g + 1, 0, bn[0], an[0]);
       fetch_begin();
       LV_LD(0);
-      pair(bc, ac, 0, 2);
-      __builtin_amdgcn_sched_barrier(0);
-      read_frags(g + 1, 1, bn[1], an[1]);
-      __builtin_amdgcn_sched_barrier(0);
-      pair(bc, ac, 0, 3);
-      LV_LD(1);
-      pair(bc, ac, 1, 0);
-      LV_LD(2);
-      pair(bc, ac, 1, 1);
-      LV_LD(3);
-      pair(bc, ac, 1, 2);
-      LV_LD(4);
-      pair(bc, ac, 1, 3);
-      LV_LD(5);
+      if constexpr (kB == 4) {
+        pair(bc, ac, 0, 2);
+        __builtin_amdgcn_sched_barrier(0);
+        read_frags(g + 1, 1, bn[1], an[1]);
+        __builtin_amdgcn_sched_barrier(0);
+        pair(bc, ac, 0, 3);
+        LV_LD(1);
+        pair(bc, ac, 1, 0);
+        LV_LD(2);
+        pair(bc, ac, 1, 1);
+        LV_LD(3);
+        pair(bc, ac, 1, 2);
+        LV_LD(4);
+        pair(bc, ac, 1, 3);
+        LV_LD(5);
+      } else {
+        pair(bc, ac, 1, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        read_frags(g + 1, 1, bn[1], an[1]);
+        LV_LD(1);
+        pair(bc, ac, 1, 1);
+        LV_LD(2); LV_LD(3);
+      }
     }
   };
 #undef LV_LD
   read_frags(0, 0, fb[0][0], fa[0][0]);
   read_frags(0, 1, fb[0][1], fa[0][1]);
-  constexpr int kSetB = FP8 ? 0 : 1;   // the weight set of odd stages
+  constexpr int kSetB = kTwoSets ? 1 : 0;   // the weight set of odd stages
   int g = 0;
   for (; g + 1 < total; g += 2) {
     stage(g, fb[0], fa[0], fb[kSetB], fa[1]);
@@ -697,18 +719,18 @@ __global__ __launch_bounds__(GemmShape<BM>::kThreads) __attribute__((amdgpu_wave
       // per register group g, lanes l and l + 32 trade groups 2, 3 against groups 0, 1.  The
       // largest |value| of the rows below M goes into *out_amax; rows beyond M are written as zeros.
       const float r = __uint_as_float(*out_inv);
-      const int KSn = nt_n * (kTile / 32);
-      u32x4 *op = (u32x4 *)out + ((size_t)(tm * S::kFragA + wd * 2) * KSn + tn * (kTile / 32) + wn * 4) * 64 + lane + anchor;
+      const int KSn = nt_n * (BN / 32);
+      u32x4 *op = (u32x4 *)out + ((size_t)(tm * S::kFragA + wd * 2) * KSn + tn * (BN / 32) + wn * kB) * 64 + lane + anchor;
       float m = 0.f;
 #pragma unroll
-      for (int b = 0; b < 4; ++b)
+      for (int b = 0; b < kB; ++b)
 #pragma unroll
         for (int a = 0; a < 2; ++a) {
           const bool live = (int64_t)tm * BM + wd * 64 + 32 * a + (lane & 31) < M;
           uint32_t d[4];
 #pragma unroll
           for (int g = 0; g < 4; ++g) {
-            const f32x4 bv = *(const f32x4 *)(bias_lds + wn * 128 + 32 * b + 8 * g + 4 * h);
+            const f32x4 bv = *(const f32x4 *)(bias_lds + wn * 32 * kB + 32 * b + 8 * g + 4 * h);
             float v[4];
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
@@ -729,13 +751,13 @@ __global__ __launch_bounds__(GemmShape<BM>::kThreads) __attribute__((amdgpu_wave
       if (lane == 0) atomicMax(&wg_amax, __float_as_uint(m));   // in LDS; once per workgroup to memory
       continue;
     }
-    const int KSn = nt_n * (kTile / 16);
-    u32x4 *op = (u32x4 *)out + ((size_t)(tm * S::kFragA + wd * 2) * KSn + tn * (kTile / 16) + wn * 8) * 64 + lane + anchor;
+    const int KSn = nt_n * (BN / 16);
+    u32x4 *op = (u32x4 *)out + ((size_t)(tm * S::kFragA + wd * 2) * KSn + tn * (BN / 16) + wn * 2 * kB) * 64 + lane + anchor;
 #pragma unroll
-    for (int b = 0; b < 4; ++b)
+    for (int b = 0; b < kB; ++b)
 #pragma unroll
       for (int gp = 0; gp < 2; ++gp) {
-        const int ch0 = wn * 128 + 32 * b + 16 * gp + 4 * h;
+        const int ch0 = wn * 32 * kB + 32 * b + 16 * gp + 4 * h;
         const f32x4 bv0 = *(const f32x4 *)(bias_lds + ch0), bv1 = *(const f32x4 *)(bias_lds + ch0 + 8);
 #pragma unroll
         for (int a = 0; a < 2; ++a) {
@@ -759,13 +781,13 @@ __global__ __launch_bounds__(GemmShape<BM>::kThreads) __attribute__((amdgpu_wave
   }
   // row-major rows of `split` channels: per store instruction a wave writes 32 bytes of each of
   // 32 rows; the four stores that complete a 128-byte line follow each other
-  const int blk = (tn * kTile) / split, col0 = (tn * kTile) % split;   // a tile never straddles two blocks
-  uint16_t *ob = out + (size_t)blk * M * split + col0 + wn * 128 + 8 * h + anchor;
+  const int blk = (tn * BN) / split, col0 = (tn * BN) % split;   // a tile never straddles two blocks
+  uint16_t *ob = out + (size_t)blk * M * split + col0 + wn * 32 * kB + 8 * h + anchor;
 #pragma unroll
-  for (int b = 0; b < 4; ++b)
+  for (int b = 0; b < kB; ++b)
 #pragma unroll
     for (int gp = 0; gp < 2; ++gp) {
-      const int ch0 = wn * 128 + 32 * b + 16 * gp + 4 * h;
+      const int ch0 = wn * 32 * kB + 32 * b + 16 * gp + 4 * h;
       const f32x4 bv0 = *(const f32x4 *)(bias_lds + ch0), bv1 = *(const f32x4 *)(bias_lds + ch0 + 8);
 #pragma unroll
       for (int a = 0; a < 2; ++a) {
@@ -857,17 +879,20 @@ struct LinearOpts {
   uint32_t *out_amax = nullptr;        // ... and where the largest |output| is reduced into
 };
 
-// Whether 128-row tiles (two workgroups per CU) beat 256-row tiles (one) on nt_n column tiles.  In
-// units of one 256-row tile's time on one CU (27-36 us at K = 1024 with all CUs busy): 256-row
-// tiles take whole rounds; a round of pairs of 128-row tiles takes 3 % more (half as much again is
-// fetched into LDS; 3-15 % measured), but what is left over, if every CU gets one at most, only
-// 0.6, and 0.72 where there is nothing else.  Measured at C = 1024 in bf16, 128 against 256 rows,
-// layers qkv / out / MLP 1 / MLP 2 in us: M = 394: 18 / 16 / 21 / 51 against 25 / 24 / 29 / 76;
-// 5776: 44 / 19 / 56 / 61 against 55 / 27 / 67 / 83; 15432: 99 / 41 / 140 / 125 against
-// 99 / 35 / 145 / 122; 143232: 952 / 311 / 1242 / 1172 against 890 / 282 / 1183 / 1015.
-static bool half_tiles(int64_t M, int nt_n, int n_cu) {
-  const auto rounds = [&](int rows, int slots, int64_t &rest) {   // of the XCD with the most tiles
-    const int64_t nt_m = (M + rows - 1) / rows, tiles = nt_m * nt_n;
+// Which output tile suits M rows and Nout columns: 256 x 256 (one workgroup per CU), 128 x 256 or
+// 128 x 128 (two), by estimated time in units of a 256 x 256 tile's on one CU (24-36 us at K = 1024).
+// Whole rounds of workgroups cost 1, 1.03 and 0.6 (smaller tiles fetch 1.5 and 2 times as much into
+// LDS per product); what is left over costs less where every CU gets one at most, and less still
+// where it is the only round.  Fitted to (C = 1024, bf16, us for the layers qkv / out / MLP 1 / MLP 2)
+//   M =    394: 25 24 29 75   19 16 21 50   13 12 15 32        M =  9000: 62 29 100  92   65 30  81  97   62 27  85  92
+//   M =   2200: 28 24 33 77   22 18 32 52   20 12 34 36        M = 15432: 99 36 143 116  100 35 139 119  112 38 159 133
+//   M =   5776: 54 27 66 83   43 19 54 59   42 19 58 56        M = 143232: 890 282 1183 1015  952 311 1242 1172
+// with the three tiles in that order.
+enum TileShape { kTile256x256, kTile128x256, kTile128x128 };
+static TileShape tile_shape(int64_t M, int Nout, int n_cu) {
+  int64_t rest = 0;
+  const auto rounds = [&](int bm, int bn, int slots) {   // full rounds (of the XCD with the most tiles), and what is left
+    const int64_t nt_m = (M + bm - 1) / bm, nt_n = Nout / bn, tiles = nt_m * nt_n;
     if (tiles <= slots) {
       rest = tiles;
       return (int64_t)0;
@@ -876,12 +901,14 @@ static bool half_tiles(int64_t M, int nt_n, int n_cu) {
     rest = per % s * kXcd;
     return per / s;
   };
-  int64_t rest;
-  const int64_t r256 = rounds(256, n_cu, rest);
+  const int64_t r256 = rounds(256, 256, n_cu);
   const double t256 = (double)r256 + (rest ? 1.0 : 0.0);
-  const int64_t r128 = rounds(128, 2 * n_cu, rest);
-  const double t128 = 1.03 * (double)r128 + (rest == 0 ? 0.0 : rest > n_cu ? 1.03 : r128 ? 0.6 : 0.72);
-  return t128 < t256;
+  const int64_t r128 = rounds(128, 256, 2 * n_cu);
+  const double t128 = 1.03 * (double)r128 + (rest == 0 ? 0.0 : rest > n_cu ? 1.03 : r128 ? 0.55 : 0.72);
+  const int64_t r64 = rounds(128, 128, 2 * n_cu);
+  const double more = rest > n_cu ? (double)(rest - n_cu) / n_cu : 0.0;
+  const double t64 = 0.6 * (double)r64 + (rest == 0 ? 0.0 : r64 ? (rest > n_cu ? 0.6 : 0.3) : rest > n_cu ? 0.64 + 0.1 * more : 0.48);
+  return t64 < t128 && t64 < t256 ? kTile128x128 : t128 < t256 ? kTile128x256 : kTile256x256;
 }
 
 // Y = A W^T + bias: brings the activation into operand order where it is not yet (FP8: quantised,
@@ -893,29 +920,38 @@ static int launch_linear(const uint16_t *A, int64_t M, int K, int Nout,
   if (o.pack_out && (o.addend || split != Nout || (o.fp8 && (!o.out_inv || !o.out_amax)))) return LV_ERR_PARAM;
   if (K % 64 != 0 || Nout % kTile != 0 || split % kTile != 0 || Nout % split != 0) return LV_ERR_SHAPE;
   int rc;
-  const int nt_n = Nout / kTile;
-  if (w.Mp / kTile * nt_n >= ((int64_t)1 << 30) || w.Mp >= ((int64_t)1 << 31)) return LV_ERR_SHAPE;
+  if (w.Mp / 128 * (Nout / 128) >= ((int64_t)1 << 30) || w.Mp >= ((int64_t)1 << 31)) return LV_ERR_SHAPE;
   int dev = 0, n_cu = 0;
   if (hipGetDevice(&dev) != hipSuccess ||
       hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n_cu < 1)
     return LV_ERR_HIP;
-  const bool half = half_tiles(M, nt_n, n_cu);
-  auto gemm = [&](auto fp8, auto packed, auto bm, const u32x4 *act, int KS, const float *alpha) -> int {
+  const TileShape shape = tile_shape(M, Nout, n_cu);
+  auto gemm = [&](auto fp8, auto packed, auto bm, auto bn, const u32x4 *act, int KS, const float *alpha) -> int {
     constexpr bool F8 = decltype(fp8)::value, PK = decltype(packed)::value;
-    constexpr int BM = decltype(bm)::value;
+    constexpr int BM = decltype(bm)::value, BN = decltype(bn)::value;
+    using S = GemmShape<BM, BN>;
     static std::atomic<uint64_t> lds_done{0};
-    if (int rc2 = allow_dynamic_lds((const void *)k_gemm_bt<F8, PK, BM>, GemmShape<BM>::kLds, lds_done)) return rc2;
-    const int n_tiles = (int)((M + BM - 1) / BM) * nt_n, slots = n_cu * (kTile / BM);
-    const unsigned grid = (unsigned)(n_tiles < slots ? n_tiles : slots);
-    hipLaunchKernelGGL((k_gemm_bt<F8, PK, BM>), dim3(grid), dim3(GemmShape<BM>::kThreads), GemmShape<BM>::kLds, st, act,
-                       o.w_packed, M, KS, nt_n, bias, gelu, out, split, alpha, n_tiles, o.addend, o.out_inv, o.out_amax);
+    if (int rc2 = allow_dynamic_lds((const void *)k_gemm_bt<F8, PK, BM, BN>, S::kLds, lds_done)) return rc2;
+    const int nt_m = (int)((M + BM - 1) / BM), nt_n = Nout / BN, n_tiles = nt_m * nt_n, slots = n_cu * (256 / BM);
+    // One round only: row tiles still go to one XCD each (M = 5776, K = 4096: 69 us dealt out in
+    // plain order, 56 like this) unless the fullest XCD would then have more than its share of CUs or slots.
+    const int fullest = (nt_m + kXcd - 1) / kXcd * nt_n, share = (n_tiles <= n_cu ? n_cu : slots) / kXcd;
+    const bool by_xcd = n_tiles > slots || (nt_m >= 2 * kXcd && fullest <= share);
+    const unsigned grid = (unsigned)(n_tiles > slots ? slots : by_xcd ? fullest * kXcd : n_tiles);
+    hipLaunchKernelGGL((k_gemm_bt<F8, PK, BM, BN>), dim3(grid), dim3(S::kThreads), S::kLds, st, act,
+                       o.w_packed, M, KS, nt_n, bias, gelu, out, split, alpha, n_tiles, by_xcd ? 1 : 0, o.addend, o.out_inv,
+                       o.out_amax);
     return LV_OK;
   };
   auto launch = [&](auto fp8, const u32x4 *act, int KS, const float *alpha) -> int {
-    using B128 = std::integral_constant<int, 128>;
-    using B256 = std::integral_constant<int, 256>;
-    if (o.pack_out) return half ? gemm(fp8, std::true_type{}, B128{}, act, KS, alpha) : gemm(fp8, std::true_type{}, B256{}, act, KS, alpha);
-    return half ? gemm(fp8, std::false_type{}, B128{}, act, KS, alpha) : gemm(fp8, std::false_type{}, B256{}, act, KS, alpha);
+    using N128 = std::integral_constant<int, 128>;
+    using N256 = std::integral_constant<int, 256>;
+    auto tiles = [&](auto packed) -> int {
+      if (shape == kTile128x128) return gemm(fp8, packed, N128{}, N128{}, act, KS, alpha);
+      if (shape == kTile128x256) return gemm(fp8, packed, N128{}, N256{}, act, KS, alpha);
+      return gemm(fp8, packed, N256{}, N256{}, act, KS, alpha);
+    };
+    return o.pack_out ? tiles(std::true_type{}) : tiles(std::false_type{});
   };
   const u32x4 *a_packed = o.a_packed;
   if (o.fp8) {

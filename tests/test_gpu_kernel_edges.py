@@ -171,12 +171,13 @@ def _block64(z, t, heads):
     return u1 + r(lin(hid, "w_2", "b_2"))
 
 
-# rows of one tile, around the two tile heights, one height for every layer or a mix of both (640 and
-# 5776 rows at 1024 channels, more tiles than workgroups), a column count that is no multiple of 4 tiles
-@pytest.mark.parametrize("m,dim", [(1, 256), (127, 256), (129, 256), (257, 768), (640, 1024), (5776, 1024), (17000, 256),
-                                   (33000, 256)])
+# rows of one tile, around the two tile heights, row tiles by XCD or in plain order (2200 rows at 1024
+# channels: both), every tile shape and mixes of them (5776, 9000), more tiles than workgroups (33000 at
+# 256: the largest tile), a column count that is no multiple of 4 tiles
+@pytest.mark.parametrize("m,dim", [(1, 256), (127, 256), (129, 256), (257, 768), (640, 1024), (2200, 1024), (5776, 1024),
+                                   (9000, 1024), (17000, 256), (33000, 256)])
 @pytest.mark.parametrize("linear", ["bf16", "fp8", "fp8-delayed"])
-def test_block_tile_heights(B, m, dim, linear):
+def test_block_tile_shapes(B, m, dim, linear):
     import torch
     w = synth.block_weights(dim, seed=m)
     t = {k: torch.from_numpy(v).cuda() for k, v in w.items()}
