@@ -266,7 +266,7 @@ __global__ __launch_bounds__(64 * kVarWaves) __attribute__((amdgpu_waves_per_eu(
   const int fr = lb / nseg, j0 = (int)(lb % nseg) * kSeg;
   const int f = fr / row_segs, rs = fr % row_segs;
   const int r0 = (int)((int64_t)H * rs / row_segs), r1 = (int)((int64_t)H * (rs + 1) / row_segs);   // output rows [r0, r1)
-  const int ib = max(r0 - 1, 0);                          // the first grid row that is read
+  const int ib = max(r0 - 1, 0), last_row = min(r1, H - 1);   // the grid rows that are read
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int T = H * W + S;
   const uint16_t *frame = x + ((size_t)f * T + S) * C;
@@ -285,7 +285,7 @@ __global__ __launch_bounds__(64 * kVarWaves) __attribute__((amdgpu_waves_per_eu(
     auto fetch = [&](int i, int a, u32x4 &dst) {   // column a of the strip in grid row i, or the pivot
       const int jj = j0 - 1 + a;
       dst = pbits;
-      if (on && i < H && i <= r1 && jj >= 0 && jj < W) dst = *(const u32x4 *)(frame + ((size_t)i * W + jj) * C + c0);
+      if (on && i <= last_row && jj >= 0 && jj < W) dst = *(const u32x4 *)(frame + ((size_t)i * W + jj) * C + c0);
     };
 #pragma unroll
     for (int a = 0; a < NC; ++a) {
