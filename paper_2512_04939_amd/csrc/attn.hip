@@ -494,8 +494,9 @@ __device__ __forceinline__ bool join_pieces(f32x16 (&oacc)[2][2], float (&lsub)[
 // PACKED (one sequence, no residual, not ONLINE): `o` is a linear layer's activation operand
 // buffer and receives the output rows in that layer's fragment order, [row / 32][k-step of 16
 // channels][lane = row % 32 + 32 * (second 8 of the 16)], 16 bytes each.
-template <bool ONLINE, bool PACKED = false>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_attn_bf16_main(
+// CUT: the blocks are pieces (AttnCut).
+template <bool ONLINE, bool PACKED, bool CUT>
+__device__ __forceinline__ void attn_bf16_main(
     const uint16_t *q, const u32x4 *__restrict__ kp, const u32x4 *__restrict__ vp, uint16_t *o,
     const uint16_t *res, int64_t n, int heads, int n_seq, int n_kt, int nqb, float c, int qk_norm,
     uint32_t *__restrict__ redo, int redo_stride, AttnCut cut, uint32_t *sync, float *partial) {
@@ -510,7 +511,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   if (((heads * n_seq) & 7) == 0) {
     const int hp = (heads * n_seq) >> 3, xcd = blockIdx.x & 7;
     int local = blockIdx.x >> 3;
-    if (cut.n_cut) {                // first all first pieces, then all second ones
+    if constexpr (CUT) {            // first all first pieces, then all second ones
       if (local < cut.n_cut) {
         nkv -= cut.small;
       } else {
@@ -855,8 +856,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     const float lsum = lrow[sub][0] + lrow[sub][1];
     lsub[sub] = lsum + __shfl_xor(lsum, 32, 64);
   }
-  __shared__ int any_low;     // pieces only
-  if (piece >= 0) {
+  __shared__ int any_low;     // CUT only
+  if constexpr (CUT) {
     if (ONLINE && __syncthreads_or(over)) {   // the block is the second pass's; the other piece waits for nobody
       if (tid == 0) redo[(size_t)sh * redo_stride + qb] = 1u;
       return;
@@ -873,7 +874,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 #pragma unroll
     for (int sub = 0; sub < 2; ++sub) low |= q0 + sub * 32 + ql < n && !(lsub[sub] >= 8.67e-19f);   // 2^-60
     bool redo_block;
-    if (piece >= 0) {         // the waves beyond the sequence end are gone by now: a plain barrier
+    if constexpr (CUT) {      // the waves beyond the sequence end are gone by now: a plain barrier
       if (__builtin_amdgcn_ballot_w64(low) != 0 && lane == 0) any_low = 1;
       __syncthreads();
       redo_block = any_low != 0;
@@ -935,6 +936,23 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         }
     }
   }
+}
+
+template <bool ONLINE, bool PACKED = false>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_attn_bf16_main(
+    const uint16_t *q, const u32x4 *__restrict__ kp, const u32x4 *__restrict__ vp, uint16_t *o,
+    const uint16_t *res, int64_t n, int heads, int n_seq, int n_kt, int nqb, float c, int qk_norm,
+    uint32_t *__restrict__ redo, int redo_stride) {
+  attn_bf16_main<ONLINE, PACKED, false>(q, kp, vp, o, res, n, heads, n_seq, n_kt, nqb, c, qk_norm, redo, redo_stride,
+                                        AttnCut{0, 0}, nullptr, nullptr);
+}
+template <bool ONLINE, bool PACKED = false>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_attn_bf16_cut(
+    const uint16_t *q, const u32x4 *__restrict__ kp, const u32x4 *__restrict__ vp, uint16_t *o,
+    int64_t n, int heads, int n_kt, int nqb, float c, int qk_norm,
+    uint32_t *__restrict__ redo, int redo_stride, AttnCut cut, uint32_t *sync, float *partial) {
+  attn_bf16_main<ONLINE, PACKED, true>(q, kp, vp, o, nullptr, n, heads, 1, n_kt, nqb, c, qk_norm, redo, redo_stride, cut,
+                                       sync, partial);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -1695,19 +1713,24 @@ int launch_attn(const uint16_t *q, const uint16_t *k, const uint16_t *v, uint16_
   hipLaunchKernelGGL(k_attn_pack, dim3((unsigned)n_kt, (unsigned)(heads * n_seq)), dim3(256), 0, st,
                      k, v, n, heads, n_kt, qk_norm, kp, vp, sync, cut.n_cut ? kSyncWords : 0);
   if (after_pack && hipEventRecord(after_pack, st) != hipSuccess) return LV_ERR_HIP;
-  const unsigned grid = cut.n_cut ? (unsigned)(kXcd * 2 * cut.n_cut) : (unsigned)(nqb2 * heads * n_seq);
+  auto main_kernel = [&](auto online, auto packed, uint16_t *out) {
+    constexpr bool ON = decltype(online)::value, PK = decltype(packed)::value;
+    uint32_t *const flags = ON ? redo : nullptr;
+    const int stride = ON ? 2 * nqb : 0;
+    if (cut.n_cut)
+      hipLaunchKernelGGL((k_attn_bf16_cut<ON, PK>), dim3((unsigned)(kXcd * 2 * cut.n_cut)), dim3(256), 0, st, q, kp, vp, out,
+                         n, heads, n_kt, nqb2, c, qk_norm, flags, stride, cut, sync, partial);
+    else
+      hipLaunchKernelGGL((k_attn_bf16_main<ON, PK>), dim3((unsigned)(nqb2 * heads * n_seq)), dim3(256), 0, st, q, kp, vp, out,
+                         res, n, heads, n_seq, n_kt, nqb2, c, qk_norm, flags, stride);
+  };
   if (bounded && o_packed && wrote_packed && n_seq == 1 && !res) {
-    hipLaunchKernelGGL((k_attn_bf16_main<false, true>), dim3(grid), dim3(256), 0,
-                       st, q, kp, vp, (uint16_t *)o_packed, res, n, heads, n_seq, n_kt, nqb2, c, qk_norm,
-                       (uint32_t *)nullptr, 0, cut, sync, partial);
+    main_kernel(std::false_type{}, std::true_type{}, (uint16_t *)o_packed);
     *wrote_packed = true;
   } else if (bounded) {
-    hipLaunchKernelGGL(k_attn_bf16_main<false>, dim3(grid), dim3(256), 0,
-                       st, q, kp, vp, o, res, n, heads, n_seq, n_kt, nqb2, c, qk_norm, (uint32_t *)nullptr, 0, cut, sync,
-                       partial);
+    main_kernel(std::false_type{}, std::false_type{}, o);
   } else {
-    hipLaunchKernelGGL(k_attn_bf16_main<true>, dim3(grid), dim3(256), 0,
-                       st, q, kp, vp, o, res, n, heads, n_seq, n_kt, nqb2, c, qk_norm, redo, 2 * nqb, cut, sync, partial);
+    main_kernel(std::true_type{}, std::false_type{}, o);
     hipLaunchKernelGGL(k_attn_bf16, dim3((unsigned)(nqb * heads * n_seq)), dim3(512), 0, st, q, kp,
                        vp, o, res, n, heads, n_seq, n_kt, nqb, c, qk_norm, (const uint32_t *)redo);
   }
