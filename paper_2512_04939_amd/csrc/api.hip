@@ -80,20 +80,20 @@ int make_plan(const litevggt_params *p, const Dims &d, litevggt_plan_t *pl) {
 size_t importance_ws_bytes(const Dims &d) { return align_up((size_t)d.F * d.P * sizeof(float), 256); }
 
 // driver scratch: z and y [M,C] bf16, then the larger of the per-op scratches
-size_t driver_ws_bytes(const litevggt_params *p, const Dims &d, const litevggt_plan_t &pl) {
+size_t driver_ws_bytes(const litevggt_params *p, const Dims &d, const litevggt_plan_t &pl, bool least = false) {
   size_t zy = 2 * align_up((size_t)pl.M * d.C * 2, 256);
   if (p->block) zy += block_wpack_bytes(d.C);   // the block's weights in operand order, kept across the layers
   size_t op = importance_ws_bytes(d);
-  size_t m = match_ws_bytes(d, pl);
+  size_t m = match_ws_bytes(d, pl, least);
   if (m > op) op = m;
-  size_t a = attn_ws_bytes(d.heads, pl.M, p->attn_dtype);
+  size_t a = attn_ws_bytes(d.heads, pl.M, p->attn_dtype, 1, least);
   if (a > op) op = a;
   if (p->frame_attn) {
-    a = attn_ws_bytes(d.heads, d.T, LV_ATTN_BF16, d.F);
+    a = attn_ws_bytes(d.heads, d.T, LV_ATTN_BF16, d.F, least);
     if (a > op) op = a;
   }
   if (p->block) {
-    a = block_ws_bytes(pl.M, d.C, d.heads, p->attn_dtype);
+    a = block_ws_bytes(pl.M, d.C, d.heads, p->attn_dtype, least);
     if (a > op) op = a;
   }
   return zy + op;
@@ -207,8 +207,8 @@ int litevggt_match(const litevggt_params *p, const void *x, litevggt_index *inde
   if (rc) return rc;
   if (!x || !index_ok(index)) return LV_ERR_NULL;
   if (d.C > 1024) return LV_ERR_SHAPE;
-  if (!ws_ok(ws, ws_bytes, match_ws_bytes(d, pl))) return LV_ERR_WORKSPACE;
-  return launch_match((const uint16_t *)x, d, pl, *index, best_sim, ws, (hipStream_t)stream);
+  if (!ws_ok(ws, ws_bytes, match_ws_bytes(d, pl, true))) return LV_ERR_WORKSPACE;
+  return launch_match((const uint16_t *)x, d, pl, *index, best_sim, ws, ws_bytes, (hipStream_t)stream);
 }
 
 int litevggt_merge(const litevggt_params *p, const void *x, const litevggt_index *index, void *z,
@@ -230,9 +230,10 @@ int litevggt_global_attn(const litevggt_params *p, int64_t n_tokens, const void 
   if (rc) return rc;
   if (!q || !k || !v || !o) return LV_ERR_NULL;
   if (n_tokens < 1 || n_tokens >= ((int64_t)1 << 31)) return LV_ERR_SHAPE;
-  if (!ws_ok(ws, ws_bytes, attn_ws_bytes(d.heads, n_tokens, p->attn_dtype))) return LV_ERR_WORKSPACE;
+  if (!ws_ok(ws, ws_bytes, attn_ws_bytes(d.heads, n_tokens, p->attn_dtype, 1, true))) return LV_ERR_WORKSPACE;
   return launch_attn((const uint16_t *)q, (const uint16_t *)k, (const uint16_t *)v, (uint16_t *)o,
-                     n_tokens, d.heads, scale_of(p), p->attn_dtype, p->qk_norm, ws, (hipStream_t)stream);
+                     n_tokens, d.heads, scale_of(p), p->attn_dtype, p->qk_norm, ws, ws_bytes,
+                     (hipStream_t)stream);
 }
 
 static int check_block_weights(const litevggt_block_weights *w) {
@@ -262,9 +263,9 @@ int litevggt_global_block(const litevggt_params *p, int64_t n_tokens, const void
   if (!z || !delta) return LV_ERR_NULL;
   if ((rc = check_block_weights(weights))) return rc;
   if (n_tokens < 1 || n_tokens >= ((int64_t)1 << 31) || d.C % 256 != 0) return LV_ERR_SHAPE;
-  if (!ws_ok(ws, ws_bytes, block_ws_bytes(n_tokens, d.C, d.heads, p->attn_dtype))) return LV_ERR_WORKSPACE;
+  if (!ws_ok(ws, ws_bytes, block_ws_bytes(n_tokens, d.C, d.heads, p->attn_dtype, true))) return LV_ERR_WORKSPACE;
   return launch_global_block((const uint16_t *)z, n_tokens, d.C, d.heads, scale_of(p), p->attn_dtype,
-                             p->qk_norm, *weights, (uint16_t *)delta, ws, (hipStream_t)stream);
+                             p->qk_norm, *weights, (uint16_t *)delta, ws, ws_bytes, (hipStream_t)stream);
 }
 
 size_t litevggt_frame_attn_ws_bytes(const litevggt_params *p) {
@@ -279,10 +280,10 @@ int litevggt_frame_attn(const litevggt_params *p, const void *q, const void *k, 
   int rc = check_params(p, &d);
   if (rc) return rc;
   if (!q || !k || !v || !o) return LV_ERR_NULL;
-  if (!ws_ok(ws, ws_bytes, attn_ws_bytes(d.heads, d.T, LV_ATTN_BF16, d.F))) return LV_ERR_WORKSPACE;
+  if (!ws_ok(ws, ws_bytes, attn_ws_bytes(d.heads, d.T, LV_ATTN_BF16, d.F, true))) return LV_ERR_WORKSPACE;
   return launch_attn((const uint16_t *)q, (const uint16_t *)k, (const uint16_t *)v, (uint16_t *)o,
-                     d.T, d.heads, scale_of(p), LV_ATTN_BF16, p->qk_norm, ws, (hipStream_t)stream,
-                     nullptr, d.F, (const uint16_t *)residual);
+                     d.T, d.heads, scale_of(p), LV_ATTN_BF16, p->qk_norm, ws, ws_bytes,
+                     (hipStream_t)stream, nullptr, d.F, (const uint16_t *)residual);
 }
 
 int litevggt_unmerge(const litevggt_params *p, const void *y, const litevggt_index *index,
@@ -313,13 +314,14 @@ int litevggt_layers_run(const litevggt_params *p, int n_layers, const void *imag
     if (d.C % 256 != 0) return LV_ERR_SHAPE;
     if ((rc = check_block_weights(p->block))) return rc;
   }
-  if (!ws_ok(ws, ws_bytes, driver_ws_bytes(p, d, pl))) return LV_ERR_WORKSPACE;
+  if (!ws_ok(ws, ws_bytes, driver_ws_bytes(p, d, pl, true))) return LV_ERR_WORKSPACE;
   hipStream_t st = (hipStream_t)stream;
   const size_t zy = align_up((size_t)pl.M * d.C * 2, 256);
   uint16_t *z = (uint16_t *)ws;
   uint16_t *y = (uint16_t *)((char *)ws + zy);
   void *wpack = (char *)ws + 2 * zy;   // block only: the weights in operand order, written by the first layer
   void *op_ws = (char *)wpack + (p->block ? block_wpack_bytes(d.C) : 0);
+  const size_t op_bytes = ws_bytes - (size_t)((char *)op_ws - (char *)ws);
   uint16_t *xx = (uint16_t *)x;
   for (int l = 0; l < n_layers; ++l) {
     const bool refresh = (l % p->refresh_interval) == 0;
@@ -350,7 +352,7 @@ int litevggt_layers_run(const litevggt_params *p, int n_layers, const void *imag
     }
     if ((rc = mark(LV_EV_SELECT_END))) return rc;
     if (refresh) {
-      rc = launch_match(xx, d, pl, *index, nullptr, op_ws, st);
+      rc = launch_match(xx, d, pl, *index, nullptr, op_ws, op_bytes, st);
       if (rc) return rc;
     }
     if ((rc = mark(LV_EV_MATCH_END))) return rc;
@@ -359,12 +361,12 @@ int litevggt_layers_run(const litevggt_params *p, int n_layers, const void *imag
     if ((rc = mark(LV_EV_MERGE_END))) return rc;
     if (p->block) {
       rc = launch_global_block(z, pl.M, d.C, d.heads, scale_of(p), p->attn_dtype, p->qk_norm,
-                               *p->block, y, op_ws, st, ev ? ev[LV_EV_ATTN_PACK_END] : nullptr,
+                               *p->block, y, op_ws, op_bytes, st, ev ? ev[LV_EV_ATTN_PACK_END] : nullptr,
                                ev ? ev[LV_EV_ATTN_END] : nullptr, wpack, l > 0);
       if (rc) return rc;
     } else {
-      rc = launch_attn(z, z, z, y, pl.M, d.heads, scale_of(p), p->attn_dtype, p->qk_norm, op_ws, st,
-                       ev ? ev[LV_EV_ATTN_PACK_END] : nullptr);
+      rc = launch_attn(z, z, z, y, pl.M, d.heads, scale_of(p), p->attn_dtype, p->qk_norm, op_ws, op_bytes,
+                       st, ev ? ev[LV_EV_ATTN_PACK_END] : nullptr);
       if (rc) return rc;
       if ((rc = mark(LV_EV_ATTN_END))) return rc;
     }
@@ -373,7 +375,7 @@ int litevggt_layers_run(const litevggt_params *p, int n_layers, const void *imag
     if (rc) return rc;
     if ((rc = mark(LV_EV_UNMERGE_END))) return rc;
     if (p->frame_attn) {
-      rc = launch_attn(xx, xx, xx, xx, d.T, d.heads, scale_of(p), LV_ATTN_BF16, p->qk_norm, op_ws,
+      rc = launch_attn(xx, xx, xx, xx, d.T, d.heads, scale_of(p), LV_ATTN_BF16, p->qk_norm, op_ws, op_bytes,
                        st, nullptr, d.F, xx);
       if (rc) return rc;
     }

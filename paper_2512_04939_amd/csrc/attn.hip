@@ -1626,7 +1626,7 @@ static size_t cut_bytes(int heads, int64_t n, int n_seq) {
   return c.n_cut ? kSyncWords * sizeof(uint32_t) + align_up((size_t)kXcd * c.n_cut * kPieceFloats * sizeof(float), 256) : 0;
 }
 
-size_t attn_ws_bytes(int heads, int64_t n_tokens, int attn_dtype, int n_seq) {
+size_t attn_ws_bytes(int heads, int64_t n_tokens, int attn_dtype, int n_seq, bool least) {
   const size_t elem = attn_dtype == LV_ATTN_FP8_E4M3 ? sizeof(u32x2) : sizeof(u32x4);
   const size_t per = (size_t)heads * n_seq * n_key_tiles(n_tokens) * 4 * kFragU4 * elem;
   // [amax block][K fragments][V fragments]; FP8: a second pair of K/V arrays in the layout of
@@ -1634,7 +1634,7 @@ size_t attn_ws_bytes(int heads, int64_t n_tokens, int attn_dtype, int n_seq) {
   size_t total = 256 + 2 * align_up(per, 256);
   if (attn_dtype == LV_ATTN_FP8_E4M3) total += 2 * align_up(per, 256) + align_up(fp8_flag_words(heads, n_tokens) * 4, 256);
   // bf16: the flags of the online-softmax pass (one word per 256-query block)
-  else total += align_up(fp8_flag_words(heads * n_seq, n_tokens) * 4, 256) + cut_bytes(heads, n_tokens, n_seq);
+  else total += align_up(fp8_flag_words(heads * n_seq, n_tokens) * 4, 256) + (least ? 0 : cut_bytes(heads, n_tokens, n_seq));
   return total;
 }
 
@@ -1643,7 +1643,7 @@ size_t attn_ws_bytes(int heads, int64_t n_tokens, int attn_dtype, int n_seq) {
 // sequences and the fused residual (o = res + attention, res may be o: a workgroup reads the
 // rows it writes and nothing else of them) are supported by the bf16 kernels only.
 int launch_attn(const uint16_t *q, const uint16_t *k, const uint16_t *v, uint16_t *o,
-                int64_t n, int heads, float scale, int attn_dtype, int qk_norm, void *ws,
+                int64_t n, int heads, float scale, int attn_dtype, int qk_norm, void *ws, size_t ws_bytes,
                 hipStream_t st, hipEvent_t after_pack, int n_seq, const uint16_t *res,
                 void *o_packed, bool *wrote_packed) {
   if (wrote_packed) *wrote_packed = false;
@@ -1707,7 +1707,8 @@ int launch_attn(const uint16_t *q, const uint16_t *k, const uint16_t *v, uint16_
       hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
     return LV_ERR_HIP;
   AttnCut cut = {0, 0};
-  if (n_seq == 1 && !res && 2 * n_cu == kXcd * kSlots) cut = attn_cut(heads, n);
+  if (n_seq == 1 && !res && 2 * n_cu == kXcd * kSlots && ws_bytes >= attn_ws_bytes(heads, n, attn_dtype))
+    cut = attn_cut(heads, n);
   uint32_t *sync = redo + align_up(words * 4, 256) / 4;
   float *partial = (float *)(sync + kSyncWords);
   hipLaunchKernelGGL(k_attn_pack, dim3((unsigned)n_kt, (unsigned)(heads * n_seq)), dim3(256), 0, st,

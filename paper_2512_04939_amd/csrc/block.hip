@@ -829,7 +829,7 @@ struct BlockWs {
   u32x4 *apack, *wpack;
   uint32_t *fp8sc, *wpart;
   void *attn;
-  size_t bytes;
+  size_t attn_bytes, bytes;
   int64_t Mp;
 };
 
@@ -837,7 +837,7 @@ struct BlockWs {
 // then a 256-byte tail for their four amaxes (FP8 layers)
 size_t block_wpack_bytes(int C) { return align_up((size_t)12 * C * C * 2, 256) + 256; }
 
-static BlockWs carve_block(int64_t M, int C, int heads, int attn_dtype, char *base) {
+static BlockWs carve_block(int64_t M, int C, int heads, int attn_dtype, bool least, char *base) {
   BlockWs w;
   size_t off = 0;
   auto take = [&](size_t bytes) {
@@ -854,14 +854,15 @@ static BlockWs carve_block(int64_t M, int C, int heads, int attn_dtype, char *ba
   w.apack = (u32x4 *)take((size_t)w.Mp * 4 * C);       // a layer's activation operand: bf16 with K = C, FP8 with K <= 4C
   w.wpack = (u32x4 *)take(block_wpack_bytes(C));
   w.fp8sc = (uint32_t *)take(4 * kFp8Words * sizeof(uint32_t));   // one set per linear layer
-  w.wpart = (uint32_t *)take(kWAmaxParts * sizeof(uint32_t));     // the weights' partial maxima
-  w.attn = take(attn_ws_bytes(heads, M, attn_dtype));
+  w.wpart = (uint32_t *)w.apack;   // the weights' partial maxima, gone before the first activation
+  w.attn_bytes = attn_ws_bytes(heads, M, attn_dtype, 1, least);
+  w.attn = take(w.attn_bytes);
   w.bytes = off;
   return w;
 }
 
-size_t block_ws_bytes(int64_t M, int C, int heads, int attn_dtype) {
-  return carve_block(M, C, heads, attn_dtype, nullptr).bytes;
+size_t block_ws_bytes(int64_t M, int C, int heads, int attn_dtype, bool least) {
+  return carve_block(M, C, heads, attn_dtype, least, nullptr).bytes;
 }
 
 // What a linear layer finds ready and what it leaves behind.
@@ -1024,10 +1025,10 @@ __global__ void k_fp8_record_all(const uint32_t *__restrict__ sc, float *__restr
 
 int launch_global_block(const uint16_t *z, int64_t M, int C, int heads, float scale, int attn_dtype,
                         int qk_norm, const litevggt_block_weights &bw, uint16_t *delta, void *ws,
-                        hipStream_t st, hipEvent_t after_pack, hipEvent_t after_attn, void *wpack_keep,
+                        size_t ws_bytes, hipStream_t st, hipEvent_t after_pack, hipEvent_t after_attn, void *wpack_keep,
                         bool wpack_ready) {
   if (C % kTile != 0) return LV_ERR_SHAPE;
-  BlockWs w = carve_block(M, C, heads, attn_dtype, (char *)ws);
+  BlockWs w = carve_block(M, C, heads, attn_dtype, ws_bytes < block_ws_bytes(M, C, heads, attn_dtype), (char *)ws);
   int rc;
   const bool f8 = bw.linear_dtype == LV_LINEAR_FP8_E4M3;
   const bool delayed = f8 && bw.fp8_recipe == LV_FP8_DELAYED;
@@ -1075,7 +1076,7 @@ int launch_global_block(const uint16_t *z, int64_t M, int C, int heads, float sc
     LinearOpts o = layer(0);
     o.a_packed = w.apack;
     if ((rc = launch_linear(nullptr, M, C, 3 * C, bias[0], 0, w.qkv, C, w, st, o))) return rc;
-    if ((rc = launch_attn(q, k, v, w.a, M, heads, scale, attn_dtype, qk_norm, w.attn, st, after_pack))) return rc;
+    if ((rc = launch_attn(q, k, v, w.a, M, heads, scale, attn_dtype, qk_norm, w.attn, w.attn_bytes, st, after_pack))) return rc;
     if (after_attn && hipEventRecord(after_attn, st) != hipSuccess) return LV_ERR_HIP;
     o = layer(1);
     if ((rc = launch_linear(w.a, M, C, C, bias[1], 0, w.u1, C, w, st, o))) return rc;
@@ -1112,7 +1113,7 @@ int launch_global_block(const uint16_t *z, int64_t M, int C, int heads, float sc
   if ((rc = launch_linear(w.h, M, C, 3 * C, bias[0], 0, w.qkv, C, w, st, o))) return rc;
   // bf16 layers: where the attention kernel can, it writes the output projection's operand itself
   bool a_is_packed = false;
-  if ((rc = launch_attn(q, k, v, w.a, M, heads, scale, attn_dtype, qk_norm, w.attn, st, after_pack, 1, nullptr,
+  if ((rc = launch_attn(q, k, v, w.a, M, heads, scale, attn_dtype, qk_norm, w.attn, w.attn_bytes, st, after_pack, 1, nullptr,
                         f8 ? nullptr : (void *)w.apack, &a_is_packed)))
     return rc;
   if (after_attn && hipEventRecord(after_attn, st) != hipSuccess) return LV_ERR_HIP;

@@ -50,9 +50,11 @@ int launch_select(const float *score, const Dims &d, const litevggt_plan_t &pl,
                   const litevggt_index &ix, hipStream_t st);
 
 // match.hip
-size_t match_ws_bytes(const Dims &d, const litevggt_plan_t &pl);
+// Scratch that the call asks for or, with `least`, that it does with: calls choose between ways by the
+// room there is, so that scratch of a longer sequence always serves a shorter one.
+size_t match_ws_bytes(const Dims &d, const litevggt_plan_t &pl, bool least = false);
 int launch_match(const uint16_t *x, const Dims &d, const litevggt_plan_t &pl,
-                 const litevggt_index &ix, float *best_sim, void *ws, hipStream_t st);
+                 const litevggt_index &ix, float *best_sim, void *ws, size_t ws_bytes, hipStream_t st);
 
 // rows 0..n-1 of a row-major [n, C] bf16 matrix -> fragment-major (1 KB per 32 rows x 16
 // channels), padded with zero rows to n_pad
@@ -60,7 +62,7 @@ int launch_pack_rows(const uint16_t *x, int64_t n, int64_t n_pad, int C, void *p
                      hipStream_t st);
 
 // block.hip
-size_t block_ws_bytes(int64_t M, int C, int heads, int attn_dtype);
+size_t block_ws_bytes(int64_t M, int C, int heads, int attn_dtype, bool least = false);
 size_t block_wpack_bytes(int C);
 // delta = Block(z) - z for M tokens; the two events (optional) are recorded around the
 // attention kernel inside the block.  wpack_keep (optional, block_wpack_bytes(C), bf16 layers
@@ -68,7 +70,7 @@ size_t block_wpack_bytes(int C);
 // already holds them from an earlier call with the same weights.
 int launch_global_block(const uint16_t *z, int64_t M, int C, int heads, float scale, int attn_dtype,
                         int qk_norm, const litevggt_block_weights &bw, uint16_t *delta, void *ws,
-                        hipStream_t st, hipEvent_t after_pack = nullptr,
+                        size_t ws_bytes, hipStream_t st, hipEvent_t after_pack = nullptr,
                         hipEvent_t after_attn = nullptr, void *wpack_keep = nullptr,
                         bool wpack_ready = false);
 
@@ -79,7 +81,7 @@ int launch_unmerge(const uint16_t *y, const Dims &d, const litevggt_index &ix,
                    const uint16_t *residual, uint16_t *out, hipStream_t st);
 
 // attn.hip
-size_t attn_ws_bytes(int heads, int64_t n_tokens, int attn_dtype, int n_seq = 1);
+size_t attn_ws_bytes(int heads, int64_t n_tokens, int attn_dtype, int n_seq = 1, bool least = false);
 // `after_pack`, when not NULL, is recorded between the K/V re-layout and the main kernel;
 // n_seq sequences of n_tokens each; res: optional residual added to the output.  o_packed
 // (optional, with wrote_packed): a linear layer's activation operand buffer for align_up(n_tokens,
@@ -87,7 +89,7 @@ size_t attn_ws_bytes(int heads, int64_t n_tokens, int attn_dtype, int n_seq = 1)
 // layer's fragment order instead of to o, and *wrote_packed tells whether it did.
 int launch_attn(const uint16_t *q, const uint16_t *k, const uint16_t *v, uint16_t *o,
                 int64_t n_tokens, int heads, float scale, int attn_dtype, int qk_norm, void *ws,
-                hipStream_t st, hipEvent_t after_pack = nullptr, int n_seq = 1,
+                size_t ws_bytes, hipStream_t st, hipEvent_t after_pack = nullptr, int n_seq = 1,
                 const uint16_t *res = nullptr, void *o_packed = nullptr, bool *wrote_packed = nullptr);
 
 }  // namespace lv

@@ -159,6 +159,8 @@ constexpr int kTeamSpin = 512;       // polls of the team counter before a workg
 constexpr int kInvBufs = 8;          // per-wave LDS buffers of 64 inverse dst norms
 constexpr int kTeam = 32;            // workgroups per team: the CUs of an XCD
 constexpr int kMaxSweeps = 64;       // sweeps of one src tile, at most
+constexpr int kFewSweeps = 4;        // ... where the scratch was sized for another sequence: schedules that need many
+                                     // partial results come and go with the tile counts, these grow with them
 
 // How the src tiles are dealt out.  Rounds 0 .. n_full - 1: team x takes the sr src tiles from
 // (round * 8 + x) * sr on, each with n_sweeps sweeps.  Then the n_rest tiles from `full` on, each
@@ -177,10 +179,10 @@ inline int div_up(int a, int b) { return (a + b - 1) / b; }
 // the fixed rule (258 x 107) 135 for 107.8 and 4090 us, now 109.  Among shapes of nearly equal
 // step counts the one that asks its L2 for the fewest distinct tiles wins: 8 x 4 and 4 x 8 ask
 // for 12, and at 1000 frames 8 x 4 was 1 % faster than 16 x 2 and 3 % faster than 4 x 8.
-static MatchSched match_sched(int src_tiles, int dst_tiles, int team) {
+static MatchSched match_sched(int src_tiles, int dst_tiles, int team, int max_sweeps = kMaxSweeps) {
   MatchSched best = {1, 1, 0, 1, 0, 0};
   double best_cost = 1e300;
-  for (int l = 1; l <= team && l <= dst_tiles && l <= kMaxSweeps; ++l) {
+  for (int l = 1; l <= team && l <= dst_tiles && l <= max_sweeps; ++l) {
     const int sr = team / l, per_round = sr * kXcd;
     const double share = 1.0 + 0.04 * ((sr + l) / 12.0 - 1.0) + (l == 4 ? 0.0 : 0.01);
     const int most = src_tiles / per_round;
@@ -189,7 +191,7 @@ static MatchSched match_sched(int src_tiles, int dst_tiles, int team) {
       if (rest > team * kXcd) break;
       int rs = rest ? team * kXcd / rest : 1;
       if (rs > dst_tiles) rs = dst_tiles;
-      if (rs > kMaxSweeps) rs = kMaxSweeps;
+      if (rs > max_sweeps) rs = max_sweeps;
       // + a few percent of a step per round for filling the pipeline and writing the result
       const double cost = f * (div_up(dst_tiles, l) * share + 0.1) + (rest ? div_up(dst_tiles, rs) * 1.03 + 0.1 : 0.0);
       if (cost < best_cost) {
@@ -857,7 +859,7 @@ struct MatchWs {
   int n_dst_pad, n_src_pad, nchunks;
 };
 
-static MatchWs carve(const Dims &d, const litevggt_plan_t &pl, char *base) {
+static MatchWs carve(const Dims &d, const litevggt_plan_t &pl, bool least, char *base) {
   MatchWs w;
   size_t off = 0;
   auto take = [&](size_t bytes) {
@@ -872,7 +874,10 @@ static MatchWs carve(const Dims &d, const litevggt_plan_t &pl, char *base) {
   w.srcp = (u32x4 *)take((size_t)w.n_src_pad * d.C * 2);
   w.invd = (float *)take((size_t)w.n_dst_pad * 4);
   w.invs = (float *)take((size_t)w.n_src_pad * 4);
-  w.partials = sched_partials(match_sched(w.n_src_pad / kGTile, w.n_dst_pad / kGTile, kTeam));
+  const int src_tiles = w.n_src_pad / kGTile, dst_tiles = w.n_dst_pad / kGTile;
+  w.partials = (size_t)(dst_tiles < kFewSweeps ? dst_tiles : kFewSweeps) * src_tiles;
+  const size_t ideal = sched_partials(match_sched(src_tiles, dst_tiles, kTeam));
+  if (!least && ideal > w.partials) w.partials = ideal;
   w.top2p = (Top2 *)take(w.partials * kGTile * sizeof(Top2));
   for (int i = 0; i < 2; ++i) {
     w.keys[i] = (uint32_t *)take((size_t)d.N * 4);
@@ -884,11 +889,11 @@ static MatchWs carve(const Dims &d, const litevggt_plan_t &pl, char *base) {
   return w;
 }
 
-size_t match_ws_bytes(const Dims &d, const litevggt_plan_t &pl) { return carve(d, pl, nullptr).bytes; }
+size_t match_ws_bytes(const Dims &d, const litevggt_plan_t &pl, bool least) { return carve(d, pl, least, nullptr).bytes; }
 
 int launch_match(const uint16_t *x, const Dims &d, const litevggt_plan_t &pl,
-                 const litevggt_index &ix, float *best_sim, void *ws, hipStream_t st) {
-  MatchWs w = carve(d, pl, (char *)ws);
+                 const litevggt_index &ix, float *best_sim, void *ws, size_t ws_bytes, hipStream_t st) {
+  MatchWs w = carve(d, pl, ws_bytes < match_ws_bytes(d, pl), (char *)ws);
   const int n_src = (int)pl.n_src, n_dst = (int)pl.n_dst;
   if (n_src > 0) {
     if (d.C % 32 != 0 || n_dst <= 0) return LV_ERR_SHAPE;
@@ -909,10 +914,7 @@ int launch_match(const uint16_t *x, const Dims &d, const litevggt_plan_t &pl,
       return LV_ERR_HIP;
     const int per_team = n_cu >= kXcd ? n_cu / kXcd : 1;
     MatchSched sched = match_sched(src_tiles, dst_tiles, per_team);
-    if (sched_partials(sched) > w.partials) {   // other teams than the workspace was sized for: one sweep per src tile
-      const int round = per_team * kXcd;
-      sched = {1, per_team, src_tiles / round, 1, src_tiles % round, src_tiles / round * round};
-    }
+    if (sched_partials(sched) > w.partials) sched = match_sched(src_tiles, dst_tiles, per_team, kFewSweeps);
     hipLaunchKernelGGL(k_match_sim, dim3((unsigned)(per_team * kXcd)), dim3(512), lds, st, w.srcp,
                        w.dstp, w.invd, dst_tiles, sched, d.C / 16, kTeamSpin, w.team_ctr, w.top2p);
     const unsigned fin = (unsigned)((n_src + 4 * kFinRows - 1) / (4 * kFinRows));

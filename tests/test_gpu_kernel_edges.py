@@ -263,3 +263,66 @@ def test_attention_cut_rounds(B, n, heads, kind):
     ref = _attn64(q, k, v, kind == "norm", heads)
     assert float((o.double() - ref).abs().max() / ref.abs().max()) <= 2e-2
     assert torch.equal(o, again)     # sums are added in key order
+
+
+# ------------------------------------------------------------------------------- scratch
+# scratch sized for a longer sequence serves a shorter one that would ask for more: cut attention blocks
+# (2000 of 2050 tokens, 14800 of 14850) and matching schedules with many partial results
+@pytest.mark.parametrize("short,long,heads", [(2000, 2050, 16), (14800, 14850, 8)])
+@pytest.mark.parametrize("norm", [1, 0])
+def test_attention_in_scratch_of_a_longer_sequence(B, short, long, heads, norm):
+    import torch
+    g = torch.Generator(device="cuda")
+    g.manual_seed(short)
+    q, k, v = (torch.randn(short, heads * 64, generator=g, device="cuda").to(torch.bfloat16) for _ in range(3))
+    ph = B.make_params(1, 1, 1, heads * 64, heads, n_special=0, qk_norm=norm)
+    need = B.litevggt_attn_ws_bytes(ph, long)
+    assert need + 512 < B.litevggt_attn_ws_bytes(ph, short)
+    ws = B.alloc_ws(need)
+    used = (ws.data_ptr() + 255) // 256 * 256 - ws.data_ptr() + need
+    ws[used:] = 0x5a
+    o = torch.full_like(q, float("nan"))
+    B.litevggt_global_attn(ph, short, q, k, v, o, ws[:used])
+    torch.cuda.synchronize()
+    ref = _attn64(q, k, v, norm, heads)
+    assert float((o.double() - ref).abs().max() / ref.abs().max()) <= 2e-2
+    assert bool((ws[used:] == 0x5a).all())
+
+
+def test_block_in_scratch_of_a_longer_sequence(B):
+    import torch
+    w = synth.block_weights(1024, seed=1)
+    t = {k: torch.from_numpy(v).cuda() for k, v in w.items()}
+    t = {k: v.to(torch.bfloat16) if k.startswith("w_") else v for k, v in t.items()}
+    g = torch.Generator(device="cuda")
+    g.manual_seed(1)
+    z = torch.randn(2000, 1024, generator=g, device="cuda").to(torch.bfloat16)
+    ph = B.make_params(1, 1, 1, 1024, 16, n_special=0, qk_norm=1)
+    need = B.litevggt_global_block_ws_bytes(ph, 2050)
+    assert need + 512 < B.litevggt_global_block_ws_bytes(ph, 2000)
+    delta = torch.full_like(z, float("nan"))
+    B.litevggt_global_block(ph, 2000, z, B.block_weights(t), delta, B.alloc_ws(need))
+    torch.cuda.synchronize()
+    ref = _block64(z, t, 16)
+    assert float((delta.double() - ref).abs().max() / ref.abs().max()) <= 2e-2
+
+
+@pytest.mark.parametrize("frames,h,w,ratio", [(87, 16, 16, 0.5), (55, 20, 20, 0.5), (57, 16, 16, 0.9)])
+def test_matching_in_scratch_of_a_longer_sequence(B, frames, h, w, ratio):
+    import torch
+    ph = B.make_params(frames, h, w, 64, 1, merge_ratio=ratio)
+    pl = B.litevggt_plan(ph)
+    need = B.litevggt_plan(B.make_params(frames + 1, h, w, 64, 1, merge_ratio=ratio)).ws_bytes
+    assert need + 512 < pl.ws_bytes
+    g = torch.Generator(device="cuda")
+    g.manual_seed(frames)
+    x = torch.randn(pl.N, 64, generator=g, device="cuda").to(torch.bfloat16)
+    images = torch.rand(frames, 3, h * ph.patch, w * ph.patch, generator=g, device="cuda")
+    out = []
+    for nbytes in (pl.ws_bytes, need):
+        ib, xx = B.alloc_index(pl), x.clone()
+        grad, score = (torch.zeros(frames, h * w, device="cuda") for _ in range(2))
+        B.litevggt_layers_run(ph, 1, images, xx, ib, grad, score, B.alloc_ws(nbytes))
+        torch.cuda.synchronize()
+        out.append((ib.anchor_of, ib.group_off, ib.group_mem, xx))
+    assert all(torch.equal(a, b) for a, b in zip(*out))
