@@ -158,18 +158,20 @@ constexpr int kGStageU4 = 2 * 2 * 8 * 64;   // u32x4 per stage: [src|dst][2 k-st
 constexpr int kTeamSpin = 512;       // polls of the team counter before a workgroup goes on alone
 constexpr int kInvBufs = 8;          // per-wave LDS buffers of 64 inverse dst norms
 constexpr int kTeam = 32;            // workgroups per team: the CUs of an XCD
-constexpr int kMaxSweeps = 64;       // sweeps of one src tile, at most
-constexpr int kFewSweeps = 4;        // ... where the scratch was sized for another sequence: schedules that need many
-                                     // partial results come and go with the tile counts, these grow with them
+constexpr int kMaxLists = 64;        // candidate lists of one src row, at most
+constexpr int kFewLists = 4;         // ... at least, and at most where the scratch was sized for another sequence:
+                                     // many lists come and go with the tile counts, these grow with them
 
 // How the src tiles are dealt out.  Rounds 0 .. n_full - 1: team x takes the sr src tiles from
 // (round * 8 + x) * sr on, each with n_sweeps sweeps.  Then the n_rest tiles from `full` on, each
-// with rest_sweeps sweeps.  The partial results of a row lie n_sweeps * full tiles of rows, sweep
-// by sweep, then rest_sweeps * n_rest tiles.
+// with rest_sweeps sweeps.  A sweep hands over one list of two candidates per row, or, so that near-equal
+// rows are told apart among at least kFewLists lists whatever the shape, one per half or quarter of the
+// workgroup's dst rows.  They lie full_lists * full tiles of rows, list by list, then rest_lists * n_rest.
 struct MatchSched {
-  int n_sweeps, sr, n_full, rest_sweeps, n_rest, full;
+  int n_sweeps, sr, n_full, rest_sweeps, n_rest, full, full_lists, rest_lists;
 };
 inline int div_up(int a, int b) { return (a + b - 1) / b; }
+static int lists_of(int sweeps) { return sweeps == 1 ? 4 : sweeps < kFewLists ? 2 * sweeps : sweeps; }
 
 // A tile step (256 x 256 rows, all channels) takes the same time on every CU, so the time of a
 // shape is its number of steps: rounds * ceil(dst tiles / sweeps).  With 8 x 4 teams alone a last
@@ -179,10 +181,11 @@ inline int div_up(int a, int b) { return (a + b - 1) / b; }
 // the fixed rule (258 x 107) 135 for 107.8 and 4090 us, now 109.  Among shapes of nearly equal
 // step counts the one that asks its L2 for the fewest distinct tiles wins: 8 x 4 and 4 x 8 ask
 // for 12, and at 1000 frames 8 x 4 was 1 % faster than 16 x 2 and 3 % faster than 4 x 8.
-static MatchSched match_sched(int src_tiles, int dst_tiles, int team, int max_sweeps = kMaxSweeps) {
-  MatchSched best = {1, 1, 0, 1, 0, 0};
+static MatchSched match_sched(int src_tiles, int dst_tiles, int team, int max_lists = kMaxLists) {
+  MatchSched best = {1, 1, 0, 1, 0, 0, 4, 4};
   double best_cost = 1e300;
-  for (int l = 1; l <= team && l <= dst_tiles && l <= max_sweeps; ++l) {
+  for (int l = 1; l <= team && l <= dst_tiles; ++l) {
+    if (lists_of(l) > max_lists) continue;
     const int sr = team / l, per_round = sr * kXcd;
     const double share = 1.0 + 0.04 * ((sr + l) / 12.0 - 1.0) + (l == 4 ? 0.0 : 0.01);
     const int most = src_tiles / per_round;
@@ -191,19 +194,20 @@ static MatchSched match_sched(int src_tiles, int dst_tiles, int team, int max_sw
       if (rest > team * kXcd) break;
       int rs = rest ? team * kXcd / rest : 1;
       if (rs > dst_tiles) rs = dst_tiles;
-      if (rs > max_sweeps) rs = max_sweeps;
+      if (rs > max_lists) rs = max_lists;
+      while (lists_of(rs) > max_lists) --rs;
       // + a few percent of a step per round for filling the pipeline and writing the result
       const double cost = f * (div_up(dst_tiles, l) * share + 0.1) + (rest ? div_up(dst_tiles, rs) * 1.03 + 0.1 : 0.0);
       if (cost < best_cost) {
         best_cost = cost;
-        best = {l, sr, f, rs, rest, f * per_round};
+        best = {l, sr, f, rs, rest, f * per_round, lists_of(l), lists_of(rs)};
       }
     }
   }
   return best;
 }
 static size_t sched_partials(const MatchSched &s) {   // tiles of 256 partial results
-  return (size_t)s.n_sweeps * s.full + (size_t)s.rest_sweeps * s.n_rest;
+  return (size_t)s.full_lists * s.full + (size_t)s.rest_lists * s.n_rest;
 }
 
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_match_sim(
@@ -466,16 +470,19 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     __syncthreads();
     if (tid < kGTile) {
       const int ws2 = tid >> 7, b = (tid >> 5) & 3, c = tid & 31;
-      Top2 t = Top2{-INFINITY, -1, -INFINITY, -1};
-      for (int w = 0; w < 4; ++w)
-        for (int hh = 0; hh < 2; ++hh) {
-          const Top2 cd = cand[((ws2 * 4 + w) * 4 + b) * 64 + hh * 32 + c];
-          top2_insert_any(t, cd.v1, cd.i1);
-          top2_insert_any(t, cd.v2, cd.i2);
-        }
-      const size_t at = in_team ? (size_t)dl * sched.full + st
-                                : (size_t)sched.n_sweeps * sched.full + (size_t)dl * sched.n_rest + sti;
-      top2p[at * kGTile + tid] = t;
+      const int lists = (in_team ? sched.full_lists : sched.rest_lists) / n_lanes;   // of this sweep
+      for (int g = 0, w = 0; g < lists; ++g) {
+        Top2 t = Top2{-INFINITY, -1, -INFINITY, -1};
+        for (; w < 4 * (g + 1) / lists; ++w)
+          for (int hh = 0; hh < 2; ++hh) {
+            const Top2 cd = cand[((ws2 * 4 + w) * 4 + b) * 64 + hh * 32 + c];
+            top2_insert_any(t, cd.v1, cd.i1);
+            top2_insert_any(t, cd.v2, cd.i2);
+          }
+        const size_t at = in_team ? (size_t)(dl * lists + g) * sched.full + st
+                                  : (size_t)sched.full_lists * sched.full + (size_t)(dl * lists + g) * sched.n_rest + sti;
+        top2p[at * kGTile + tid] = t;
+      }
     }
     __syncthreads();   // the ring is reused by the next round
   }
@@ -491,7 +498,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 // exact 16-product sums).
 //
 // Bound by the latency of its index chain: a wave takes kFinRows consecutive rows at once, 8 lanes
-// per row reading the row's sweeps, and only the rows with near-equal candidates one after the
+// per row reading the row's lists, and only the rows with near-equal candidates one after the
 // other with all 64 lanes (a wave per row: 32 us for 38,192 rows none of which is near-equal).
 // 8 rows and no more, because in late refreshes most rows are near-equal and want many waves.
 constexpr int kFinRows = 8;
@@ -508,12 +515,12 @@ __global__ __launch_bounds__(256) void k_match_finish(
   // the sweeps of the rows of this wave (a tile of 256 rows holds whole waves' rows)
   const int tile = (int)(p0 / kGTile);
   const bool in_full = tile < sched.full;
-  const int n_sweeps = in_full ? sched.n_sweeps : sched.rest_sweeps;
+  const int n_lists = in_full ? sched.full_lists : sched.rest_lists;
   const size_t stride = (size_t)(in_full ? sched.full : sched.n_rest) * kGTile;
-  const Top2 *part = in_full ? top2p : top2p + (size_t)sched.n_sweeps * sched.full * kGTile - (size_t)sched.full * kGTile;
+  const Top2 *part = in_full ? top2p : top2p + (size_t)sched.full_lists * sched.full * kGTile - (size_t)sched.full * kGTile;
   const int s = src_idx[p];
   Top2 t = Top2{-INFINITY, -1, -INFINITY, -1};
-  for (int l = sub; l < n_sweeps; l += 8) {
+  for (int l = sub; l < n_lists; l += 8) {
     const Top2 o = part[l * stride + p];
     top2_insert_any(t, o.v1, o.i1);
     top2_insert_any(t, o.v2, o.i2);
@@ -535,9 +542,9 @@ __global__ __launch_bounds__(256) void k_match_finish(
     const int rp = __builtin_amdgcn_readlane(p, r), rs = __builtin_amdgcn_readlane(s, r);
     const float v1 = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, t.v1), r));
     const float is32 = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, invs), r));
-    // lane l holds the two candidates of sweep l
+    // lane l holds the two candidates of list l
     Top2 o = Top2{-INFINITY, -1, -INFINITY, -1};
-    if (lane < n_sweeps) o = part[lane * stride + rp];
+    if (lane < n_lists) o = part[lane * stride + rp];
     uint64_t c1 = __builtin_amdgcn_ballot_w64(o.i1 >= 0 && (v1 - o.v1) * is32 < kRescoreGap);
     uint64_t c2 = __builtin_amdgcn_ballot_w64(o.i2 >= 0 && (v1 - o.v2) * is32 < kRescoreGap);
     double ss = 0;
@@ -875,7 +882,7 @@ static MatchWs carve(const Dims &d, const litevggt_plan_t &pl, bool least, char 
   w.invd = (float *)take((size_t)w.n_dst_pad * 4);
   w.invs = (float *)take((size_t)w.n_src_pad * 4);
   const int src_tiles = w.n_src_pad / kGTile, dst_tiles = w.n_dst_pad / kGTile;
-  w.partials = (size_t)(dst_tiles < kFewSweeps ? dst_tiles : kFewSweeps) * src_tiles;
+  w.partials = (size_t)kFewLists * src_tiles;
   const size_t ideal = sched_partials(match_sched(src_tiles, dst_tiles, kTeam));
   if (!least && ideal > w.partials) w.partials = ideal;
   w.top2p = (Top2 *)take(w.partials * kGTile * sizeof(Top2));
@@ -914,7 +921,7 @@ int launch_match(const uint16_t *x, const Dims &d, const litevggt_plan_t &pl,
       return LV_ERR_HIP;
     const int per_team = n_cu >= kXcd ? n_cu / kXcd : 1;
     MatchSched sched = match_sched(src_tiles, dst_tiles, per_team);
-    if (sched_partials(sched) > w.partials) sched = match_sched(src_tiles, dst_tiles, per_team, kFewSweeps);
+    if (sched_partials(sched) > w.partials) sched = match_sched(src_tiles, dst_tiles, per_team, kFewLists);
     hipLaunchKernelGGL(k_match_sim, dim3((unsigned)(per_team * kXcd)), dim3(512), lds, st, w.srcp,
                        w.dstp, w.invd, dst_tiles, sched, d.C / 16, kTeamSpin, w.team_ctr, w.top2p);
     const unsigned fin = (unsigned)((n_src + 4 * kFinRows - 1) / (4 * kFinRows));
