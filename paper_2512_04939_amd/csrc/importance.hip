@@ -247,7 +247,8 @@ __global__ __launch_bounds__(128) void k_var_map(const uint16_t *__restrict__ x,
 // A strip is a chain of one memory round trip after the other, about 1.7 us per row, so short
 // sequences, whose strips do not fill the 1024 workgroup slots, cut the rows into segments, each
 // with one more row read on either side (var_row_segments; 63 -> 36 us for 32 frames of 37 x 37,
-// 25 -> 9 for 2 of 16 x 16).
+// 25 -> 9 for 2 of 16 x 16).  Whole strips are a kernel of their own (SEG false): with the bounds of a
+// segment in registers 1000 frames took 800 us, without them 760.
 // ---------------------------------------------------------------------------------
 #ifndef LV_VAR_SEG
 #define LV_VAR_SEG 4
@@ -255,18 +256,21 @@ __global__ __launch_bounds__(128) void k_var_map(const uint16_t *__restrict__ x,
 constexpr int kSeg = LV_VAR_SEG;
 constexpr int kVarWaves = 2;                   // waves per workgroup: 512 channels each, 8 per lane
 
+template <bool SEG>
 __global__ __launch_bounds__(64 * kVarWaves) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_var_map3(
     const uint16_t *__restrict__ x, int F, int H, int W, int S, int C, int nseg, int row_segs,
     float *__restrict__ psi_v) {
   constexpr int NC = kSeg + 2;               // columns a strip reads: its own and one on each side
   __shared__ float comb[2][kVarWaves][kSeg]; // the waves' partial sums of a grid row, by row parity
+  if constexpr (!SEG) row_segs = 1;
   const uint32_t nblk = (uint32_t)F * row_segs * nseg;
   const uint32_t lb = xcd_contiguous(blockIdx.x, nblk);   // neighbouring strips share an L2
   if (lb >= nblk) return;
   const int fr = lb / nseg, j0 = (int)(lb % nseg) * kSeg;
   const int f = fr / row_segs, rs = fr % row_segs;
-  const int r0 = (int)((int64_t)H * rs / row_segs), r1 = (int)((int64_t)H * (rs + 1) / row_segs);   // output rows [r0, r1)
-  const int ib = max(r0 - 1, 0), last_row = min(r1, H - 1);   // the grid rows that are read
+  // output rows [r0, r1), and the grid rows that are read
+  const int r0 = SEG ? (int)((int64_t)H * rs / row_segs) : 0, r1 = SEG ? (int)((int64_t)H * (rs + 1) / row_segs) : H;
+  const int ib = SEG ? max(r0 - 1, 0) : 0, row_end = SEG ? min(r1 + 1, H) : H;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int T = H * W + S;
   const uint16_t *frame = x + ((size_t)f * T + S) * C;
@@ -285,7 +289,7 @@ __global__ __launch_bounds__(64 * kVarWaves) __attribute__((amdgpu_waves_per_eu(
     auto fetch = [&](int i, int a, u32x4 &dst) {   // column a of the strip in grid row i, or the pivot
       const int jj = j0 - 1 + a;
       dst = pbits;
-      if (on && i <= last_row && jj >= 0 && jj < W) dst = *(const u32x4 *)(frame + ((size_t)i * W + jj) * C + c0);
+      if (on && i < row_end && jj >= 0 && jj < W) dst = *(const u32x4 *)(frame + ((size_t)i * W + jj) * C + c0);
     };
 #pragma unroll
     for (int a = 0; a < NC; ++a) {
@@ -347,12 +351,13 @@ __global__ __launch_bounds__(64 * kVarWaves) __attribute__((amdgpu_waves_per_eu(
       float r = res[0];
 #pragma unroll
       for (int q = 1; q < kSeg; ++q) r = lane == q ? res[q] : r;
-      if (lane < kSeg) comb[decltype(parity)::value][wave][lane] = r;
+      const int par = SEG ? decltype(parity)::value : i & 1;
+      if (lane < kSeg) comb[par][wave][lane] = r;
       __syncthreads();
       if (wave == 0 && lane < kSeg && io >= r0 && io < r1 && j0 + lane < W) {
         r = 0.f;
 #pragma unroll
-        for (int w2 = 0; w2 < kVarWaves; ++w2) r += comb[decltype(parity)::value][w2][lane];
+        for (int w2 = 0; w2 < kVarWaves; ++w2) r += comb[par][w2][lane];
         r *= inv_c;
         float *o = out + (size_t)io * W + j0 + lane;
         *o = cbase ? *o + r : r;
@@ -386,8 +391,12 @@ static int var_row_segments(int64_t strips, int H) {
 int launch_var_map(const uint16_t *x, const Dims &d, int pool, float *psi_v, hipStream_t st) {
   if (pool == 3) {
     const int nseg = (d.W + kSeg - 1) / kSeg, row_segs = var_row_segments((int64_t)d.F * nseg, d.H);
-    hipLaunchKernelGGL(k_var_map3, dim3((unsigned)align_up((size_t)d.F * row_segs * nseg, kXcd)), dim3(64 * kVarWaves),
-                       0, st, x, d.F, d.H, d.W, d.S, d.C, nseg, row_segs, psi_v);
+    const dim3 grid((unsigned)align_up((size_t)d.F * row_segs * nseg, kXcd));
+    if (row_segs > 1)
+      hipLaunchKernelGGL(k_var_map3<true>, grid, dim3(64 * kVarWaves), 0, st, x, d.F, d.H, d.W, d.S, d.C, nseg, row_segs,
+                         psi_v);
+    else
+      hipLaunchKernelGGL(k_var_map3<false>, grid, dim3(64 * kVarWaves), 0, st, x, d.F, d.H, d.W, d.S, d.C, nseg, 1, psi_v);
     LV_HIP_CHECK_LAUNCH();
     return LV_OK;
   }
@@ -411,7 +420,9 @@ int launch_var_map(const uint16_t *x, const Dims &d, int pool, float *psi_v, hip
 // Fusion: one workgroup per frame finds min/max of both maps, then writes
 // alpha*norm(Psi_g) + beta*norm(Psi_v).
 // ---------------------------------------------------------------------------------
-constexpr int kFuseWaves = 16;   // a frame is a few KB: its latency counts, not the bandwidth
+// A frame is a few KB: while there are CUs to spare its latency counts (100 frames 6.9 -> 4.9 us with 16
+// waves in place of 4), with more frames than CUs the launch of its waves (1000 frames 12.2 us against 9.5)
+constexpr int kFuseWaves = 16;
 __global__ __launch_bounds__(64 * kFuseWaves) void k_ga_fuse(const float *__restrict__ psi_g,
                                                  const float *__restrict__ psi_v, int P,
                                                  float alpha, float beta,
@@ -438,8 +449,7 @@ __global__ __launch_bounds__(64 * kFuseWaves) void k_ga_fuse(const float *__rest
     red[wave][3] = vhi;
   }
   __syncthreads();
-#pragma unroll
-  for (int w = 0; w < kFuseWaves; ++w) {
+  for (int w = 0; w < (int)blockDim.x / 64; ++w) {
     glo = fminf(glo, red[w][0]);
     ghi = fmaxf(ghi, red[w][1]);
     vlo = fminf(vlo, red[w][2]);
@@ -455,7 +465,7 @@ __global__ __launch_bounds__(64 * kFuseWaves) void k_ga_fuse(const float *__rest
 
 int launch_ga_fuse(const float *psi_g, const float *psi_v, const Dims &d, float alpha, float beta,
                    float *score, hipStream_t st) {
-  hipLaunchKernelGGL(k_ga_fuse, dim3((unsigned)d.F), dim3(64 * kFuseWaves), 0, st, psi_g, psi_v, d.P, alpha,
+  hipLaunchKernelGGL(k_ga_fuse, dim3((unsigned)d.F), dim3(d.F > 256 ? 256 : 64 * kFuseWaves), 0, st, psi_g, psi_v, d.P, alpha,
                      beta, score);
   LV_HIP_CHECK_LAUNCH();
   return LV_OK;
