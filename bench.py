@@ -409,7 +409,7 @@ def main():
         "merge": dict(ms=avg["merge"], gbs=merge_bytes / (avg["merge"] * 1e-3) / 1e9),
         "unmerge": dict(ms=avg["unmerge"], gbs=unmerge_bytes / (avg["unmerge"] * 1e-3) / 1e9),
         "importance": dict(ms=avg["importance"]),
-        "select": dict(ms=avg["select"], note="per refresh: per-frame cell arg-mins and rank counting, latency-bound (5.5 MB in)"),
+        "select": dict(ms=avg["select"], note="per refresh: per-frame cell arg-mins and a radix selection, latency-bound (5.5 MB in)"),
     }
     if args.anchor_policy == "ga":
         # refreshes after the first read the cached gradient map: x patch rows once + three maps
