@@ -38,14 +38,14 @@ __device__ __forceinline__ void ln_row(const u32x4 (&w)[CPL], const u32x4 (&a)[C
       sum += v[c][2 * i] + v[c][2 * i + 1];
     }
   }
-  const float mean = wave_sum_uniform(sum) / (float)C;
+  const float mean = wave_sum_ordered(sum) / (float)C;
   float ss = 0.f;
 #pragma unroll
   for (int c = 0; c < CPL; ++c)
     if (lane + 64 * c < nch)
 #pragma unroll
       for (int i = 0; i < 8; ++i) ss += (v[c][i] - mean) * (v[c][i] - mean);
-  const float rstd = 1.0f / sqrtf(wave_sum_uniform(ss) / (float)C + kLnEps);
+  const float rstd = 1.0f / sqrtf(wave_sum_ordered(ss) / (float)C + kLnEps);
 #pragma unroll
   for (int c = 0; c < CPL; ++c) {
     const int ch = lane + 64 * c;
@@ -105,8 +105,8 @@ __device__ __forceinline__ void raise_max(uint32_t *word, float m) {
 // fragment order k_pack_rows produces: [row / 32][k-step of 16 channels][lane = row % 32 + 32 *
 // (second 8 of the 16)], 16 bytes each).  A workgroup owns the 32 rows of one fragment row, a
 // wave 4 of them (their loads are all issued before the first row is reduced, and more waves
-// per workgroup would leave a wave too few; 8 rows per wave and sums through LDS shuffles: 13.7 us
-// for 5776 rows of 1024 channels, 29 for 15432 in FP8); the normalised
+// per workgroup would leave a wave too few; 8 rows per wave and sums through LDS shuffles: 15.2 us
+// for 5776 rows of 1024 channels in bf16, now 10.1; 38 for 15432 in FP8, now 20); the normalised
 // rows meet in LDS (row stride C * 2 + 16 bytes: the 32 rows a wave reads back at one channel
 // piece then lie in different banks) and leave as one contiguous run of 32 * C * 2 bytes.
 // Rows beyond M are written as zeros.

@@ -56,6 +56,20 @@ __device__ __forceinline__ float wave_sum_uniform(float v) {
   v += dpp_take<0x143, 0xC>(v);   // row_bcast31 into rows 2 and 3
   return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), 63));
 }
+// wave_sum without LDS round trips: the same additions in the same order (lanes 32, 16, 8, 4, 2
+// and 1 apart), so the result has the same bits.  Once lanes 32 and 16 apart are equal, so are the
+// values a rotation by 8, and then by 4, inside a row of 16 brings.
+__device__ __forceinline__ float wave_sum_ordered(float v) {
+  const auto s32 = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = __uint_as_float(s32[0]) + __uint_as_float(s32[1]);
+  const auto s16 = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = __uint_as_float(s16[0]) + __uint_as_float(s16[1]);
+  v += dpp_take<0x128, 0xF>(v);   // row_ror:8
+  v += dpp_take<0x124, 0xF>(v);   // row_ror:4
+  v += dpp_take<0x4E, 0xF>(v);    // quad_perm [2,3,0,1]
+  v += dpp_take<0xB1, 0xF>(v);    // quad_perm [1,0,3,2]
+  return v;
+}
 __device__ __forceinline__ float wave_max(float v) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));

@@ -200,6 +200,33 @@ def test_block_tile_shapes(B, m, dim, linear):
     assert err <= (2e-2 if linear == "bf16" else 1e-1)
 
 
+@pytest.mark.parametrize("dim", [512, 768, 1024])
+def test_block_layernorm_cancels_opposite_lanes_first(B, dim):
+    """Two channels 32 lanes apart hold +-2^30: added to each other first they vanish and the mean of the
+    rest is kept; in any order that adds something else in between, it is lost to rounding."""
+    import torch
+    big = 2.0 ** 30
+    g = torch.Generator(device="cuda")
+    g.manual_seed(dim)
+    z = (1.0 + 0.1 * torch.randn(1, dim, generator=g, device="cuda")).to(torch.bfloat16)
+    z.view(dim // 8, 8)[torch.arange(0, dim // 8, 32, device="cuda")] = 0.0     # what lanes 0 and 32 hold
+    z[0, 0], z[0, 256] = big, -big
+    t = {k: torch.zeros(v.shape, device="cuda") for k, v in synth.block_weights(dim, seed=0).items()}
+    t["ln1_g"] += big
+    t["ln1_g"][[0, 256]] = 0.0
+    t["w_qkv"][2 * dim:] = torch.eye(dim, device="cuda")    # q = k = 0 and v = LN(z): one token attends to itself
+    t["w_o"][:] = torch.eye(dim, device="cuda")
+    t = {k: v.to(torch.bfloat16) if k.startswith("w_") else v for k, v in t.items()}
+    ph = B.make_params(1, 1, 1, dim, dim // 64, n_special=0, qk_norm=1)
+    delta = torch.full_like(z, float("nan"))
+    B.litevggt_global_block(ph, 1, z, B.block_weights(t), delta, B.alloc_ws(B.litevggt_global_block_ws_bytes(ph, 1)))
+    torch.cuda.synchronize()
+    d = z.double() - z.double().mean()
+    ref = d / torch.sqrt((d * d).mean() + 1e-6) * t["ln1_g"].double()
+    # one bf16 rounding of a value that went through identity layers
+    assert bool(((delta.double() - ref).abs() <= 2.0 ** -8 * ref.abs() + 1e-4).all())
+
+
 # ------------------------------------------------------------------------------- importance
 # pixel rows that are no multiple of 4 pixels, planes that are none (one pixel at a time), images
 # behind an unaligned address, a single patch row and column, pixel rows wider than a workgroup,
