@@ -166,7 +166,9 @@ constexpr int kFewLists = 4;         // ... at least, and at most where the scra
 // (round * 8 + x) * sr on, each with n_sweeps sweeps.  Then the n_rest tiles from `full` on, each
 // with rest_sweeps sweeps.  A sweep hands over one list of two candidates per row, or, so that near-equal
 // rows are told apart among at least kFewLists lists whatever the shape, one per half or quarter of the
-// workgroup's dst rows.  They lie full_lists * full tiles of rows, list by list, then rest_lists * n_rest.
+// workgroup's dst rows.  Each list is the two best of its own rows: the fold's bound is shared inside a
+// list only (32 frames, two sweeps for most src tiles: 423 -> 427 us against one bound per sweep).
+// They lie full_lists * full tiles of rows, list by list, then rest_lists * n_rest.
 struct MatchSched {
   int n_sweeps, sr, n_full, rest_sweeps, n_rest, full, full_lists, rest_lists;
 };
@@ -237,6 +239,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   const int total = nt * SPT;
   const bool member = sti < (in_team ? sched.sr : sched.n_rest);
   const bool active = member && total > 0;
+  const int lists = (in_team ? sched.full_lists : sched.rest_lists) / n_lanes;   // of this sweep: 1, 2 or 4
   Top2 best[4];
 #pragma unroll
   for (int b = 0; b < 4; ++b) best[b] = Top2{-INFINITY, -1, -INFINITY, -1};
@@ -338,13 +341,14 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     //
     // A column's rows are spread over eight running pairs (four waves, two lane halves), each
     // of which alone would let through about 2 ln(rows / 8) elements.  The test is therefore
-    // made against thr >= the largest second best any of the eight had at the end of the
-    // previous tile (exchanged through LDS once per tile): an element at or below it cannot be
-    // one of the column's two best, and with equal values it has the higher row index, because
-    // earlier tiles hold lower rows.  Two buffers by tile parity: a wave that is already done
+    // made against thr >= the largest second best that any pair of the same list had at the end
+    // of the previous tile (exchanged through LDS once per tile; a list is all four waves, two or
+    // one): an element at or below it cannot be one of the list's two best, and with equal
+    // values it has the higher row index, because earlier tiles hold lower rows.  Two buffers by tile parity: a wave that is already done
     // with this tile writes the other one (bounds from this tile's rows could tie with a lower
     // row that a slower wave has yet to see), and nobody is more than one tile-end barrier apart.
     float *share = (float *)(ring + (size_t)kGStages * kGStageU4) + 8 * kInvBufs * 64;   // [parity][wsrc][b][wd][column]
+    const int peers = 4 / lists - 1, w0 = wd & ~peers;   // the waves of this one's list: w0 .. w0 + peers
     float thr[4] = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
 #pragma unroll
     for (int b = 0; b < 4; ++b) {   // before the first barrier of the round
@@ -356,7 +360,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       for (int b = 0; b < 4; ++b)
 #pragma unroll
         for (int w = 0; w < 4; ++w)
-          thr[b] = fmaxf(thr[b], share[parity * 1024 + ((wsrc * 4 + b) * 4 + w) * 32 + (lane & 31)]);
+          thr[b] = fmaxf(thr[b], share[parity * 1024 + ((wsrc * 4 + b) * 4 + w0 + (w & peers)) * 32 + (lane & 31)]);
 #pragma unroll
       for (int a = 0; a < 2; ++a) {
         const int row0 = tile * kGTile + wd * 64 + a * 32 + h * 4;
@@ -470,7 +474,6 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     __syncthreads();
     if (tid < kGTile) {
       const int ws2 = tid >> 7, b = (tid >> 5) & 3, c = tid & 31;
-      const int lists = (in_team ? sched.full_lists : sched.rest_lists) / n_lanes;   // of this sweep
       for (int g = 0, w = 0; g < lists; ++g) {
         Top2 t = Top2{-INFINITY, -1, -INFINITY, -1};
         for (; w < 4 * (g + 1) / lists; ++w)

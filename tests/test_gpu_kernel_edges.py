@@ -130,6 +130,59 @@ def test_match_near_equal_rows_of_many_sweeps(B):
     assert torch.equal(ib.anchor_of[src].long(), src % (pl.N // 40))
 
 
+def _near_equal_families(rng, count, dim):
+    """(row, [best, second, third]): bf16 rows whose cosines with `row` are exactly 1 and, for the other
+    two, one or two fp32 steps below it in float64, while fp32 products with fp32 inverse norms rank the
+    best one last or level with the others.  (Small integers times an odd factor: every product sum is exact in fp32, so the fp32
+    values follow from the rounding of the inverse norm alone.)"""
+    f32, out = np.float32, []
+    while len(out) < count:
+        row = rng.integers(-31, 32, dim).astype(np.float64)
+        n2 = float((row * row).sum())
+        va, k = min((f32(f * n2) * f32(1 / np.sqrt(f * f * n2)), f) for f in (1, 3, 5, 7))
+        others = []
+        for i in np.flatnonzero(np.abs(row) >= 16):
+            d = row.copy()
+            d[i] += np.sign(d[i]) / 8
+            dot, d2 = float((row * d).sum()), float((d * d).sum())
+            if f32(dot) * f32(1 / np.sqrt(d2)) >= va and f32(dot / np.sqrt(d2) / np.sqrt(n2)) < f32(1):
+                others.append(d)
+        if len(others) >= 2:
+            out.append((row, [k * row, others[0], others[1]]))
+    return out
+
+
+# one, two and three sweeps per src tile: lists of a quarter, of a half, of a half of the dst rows
+@pytest.mark.parametrize("frames,h,w,ratio", [(230, 16, 16, 0.98), (80, 20, 20, 0.9), (60, 20, 20, 0.9)])
+def test_match_lists_keep_their_own_candidates(B, frames, h, w, ratio):
+    """Two near-equal rows in the first quarter of the first dst tile, the best one in the last quarter of
+    a later tile of the same sweep: float64 decides among all three, whatever fp32 made of them."""
+    import torch
+    ph = B.make_params(frames, h, w, 256, 4, merge_ratio=ratio)
+    pl = B.litevggt_plan(ph)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(frames)
+    x = torch.randn(pl.N, 256, generator=g, device="cuda").to(torch.bfloat16)
+    ib = B.alloc_index(pl)
+    score = torch.rand(frames, h * w, generator=g, device="cuda")
+    B.litevggt_select_anchors(ph, score, ib)
+    torch.cuda.synchronize()
+    src, dst = _i32(ib.src_idx)[:pl.n_src], _i32(ib.dst_idx)[:pl.n_dst]
+    rng = np.random.default_rng(frames)
+    rows = rng.choice(pl.n_src, 30, replace=False)
+    want = []
+    for n, (p, (row, cand)) in enumerate(zip(rows, _near_equal_families(rng, 30, 256))):
+        at = [dst[256 * (1 + n % 3) + 192 + n], dst[2 * n], dst[2 * n + 1]]
+        for t, v in zip([src[p]] + at, [row] + cand):
+            b = torch.from_numpy(v).cuda()
+            x[t] = b.to(torch.bfloat16)
+            assert torch.equal(x[t].double(), b)
+        want.append(at[0])
+    B.litevggt_match(ph, x, ib, None, B.alloc_ws(pl.ws_bytes))
+    torch.cuda.synchronize()
+    assert np.array_equal(_i32(ib.anchor_of)[src[rows]], np.array(want))
+
+
 # groups: the largest sequence one workgroup sorts, the smallest beyond it, a chunk of the general
 # sort that ends on a wave's last element, and one slot count above 16 bits (three digit passes)
 @pytest.mark.parametrize("frames,h,w,special,ratio", [(64, 15, 17, 1, 0.9), (5, 52, 63, 1, 0.5), (2, 1, 1, 0, 0.0),
