@@ -308,6 +308,30 @@ def test_importance_edges(B, frames, h, w, patch, dim, kind):
     assert np.abs(score.cpu().numpy() - ref.reshape(frames, -1)).max() <= 2e-5
 
 
+# White noise has gradients of one size everywhere, so the rounding of single pixels averages out and the
+# sums decide: 2^-24, half a step of the result, is more than they may lose together (2-norm)
+@pytest.mark.parametrize("h,w,patch", [(37, 37, 14), (5, 50, 7), (9, 11, 31)])
+def test_gradient_map_sums_lose_less_than_the_results_rounding(B, h, w, patch):
+    import torch
+    g = torch.Generator(device="cuda")
+    g.manual_seed(patch)
+    img = torch.rand(12, 3, h * patch, w * patch, generator=g, device="cuda")
+    ph = B.make_params(12, h, w, 64, 1, patch=patch)
+    pl = B.litevggt_plan(ph)
+    grad, score = (torch.empty(12, h * w, device="cuda") for _ in range(2))
+    x = torch.zeros(pl.N, 64, dtype=torch.bfloat16, device="cuda")
+    B.litevggt_importance(ph, img, x, grad, True, score, B.alloc_ws(pl.ws_bytes))
+    torch.cuda.synchronize()
+    v = img.double()
+    lum = torch.nn.functional.pad((0.299 * v[:, 0] + 0.587 * v[:, 1] + 0.114 * v[:, 2])[:, None], (1, 1, 1, 1),
+                                  mode="replicate")[:, 0]
+    t, m, b = lum[:, :-2], lum[:, 1:-1], lum[:, 2:]
+    gx = (t + 2 * m + b)[:, :, 2:] - (t + 2 * m + b)[:, :, :-2]
+    gy = (b - t)[:, :, :-2] + 2 * (b - t)[:, :, 1:-1] + (b - t)[:, :, 2:]
+    ref = torch.sqrt(gx * gx + gy * gy).reshape(12, h, patch, w, patch).mean((2, 4)).reshape(12, h * w)
+    assert float((grad.double() - ref).norm() / ref.norm()) <= 2.0 ** -24
+
+
 # ------------------------------------------------------------------------------- attention
 def _attn64(q, k, v, norm, heads):
     import torch
