@@ -1613,7 +1613,11 @@ static size_t fp8_flag_words(int heads, int64_t n) { return (size_t)heads * 2 * 
 // 3500 57.4 -> 56.  With a full round before them, blocks do not end together and the last round's
 // idle slots are not there to be had (15432 tokens 866 -> 876 us, 20000 1356 -> 1364): not cut.  Nor
 // are the blocks of many sequences.
-static AttnCut attn_cut(int heads, int64_t n) {
+// The bounded kernel (no running reference) takes 0.87 us per stage where a quarter of the CUs or more idle,
+// and sharing CUs then costs more than the cut gives: 8 heads, whole against cut, 4500 tokens 65.0 and
+// 67.1 us, 5000 72.3 and 74.7, 6000 86.6 and 87.0, from 6500 on 96.2 and 94.8 (the online kernel gains 8 %
+// there).  Scratch is asked for as if by the online kernel, which is cut wherever the bounded one is.
+static AttnCut attn_cut(int heads, int64_t n, bool bounded = false) {
   const int64_t nqb = (n + kBQB - 1) / kBQB, nkv = (n + kKV - 1) / kKV, b = heads / kXcd * nqb;
   if (heads % kXcd != 0 || b >= kSlots) return {0, 0};
   const int64_t idle = kSlots - b, k = (b + idle - 1) / idle;
@@ -1621,7 +1625,8 @@ static AttnCut attn_cut(int heads, int64_t n) {
   if (small < 6) return {0, 0};
   const auto stage_us = [](int64_t per_xcd) { return per_xcd <= kSlots / 2 ? 1.0 : 1.55; };
   const int64_t chain = k * (small + 6) - 6, longest = nkv - small > chain ? nkv - small : chain;
-  const double whole = (double)nkv * stage_us(b), cut = (double)longest * stage_us(2 * b) + 9.0;
+  const double alone = bounded && b <= kSlots * 3 / 8 && 2 * b > kSlots / 2 ? 0.87 : 1.0;
+  const double whole = (double)nkv * stage_us(b) * alone, cut = (double)longest * stage_us(2 * b) + 9.0;
   if (cut > 0.97 * whole) return {0, 0};
   return {(int)b, (int)small};
 }
@@ -1712,7 +1717,7 @@ int launch_attn(const uint16_t *q, const uint16_t *k, const uint16_t *v, uint16_
     return LV_ERR_HIP;
   AttnCut cut = {0, 0};
   if (n_seq == 1 && !res && 2 * n_cu == kXcd * kSlots && ws_bytes >= attn_ws_bytes(heads, n, attn_dtype))
-    cut = attn_cut(heads, n);
+    cut = attn_cut(heads, n, bounded);
   uint32_t *sync = redo + align_up(words * 4, 256) / 4;
   float *partial = (float *)(sync + kSyncWords);
   auto pack_kernel = [&](auto is_cut) {
