@@ -198,8 +198,9 @@ def test_groups_edges(B, frames, h, w, special, ratio):
 
 
 # ------------------------------------------------------------------------------- linear layers
-def _block64(z, t, heads):
-    """The transformer block in float64, rounded to bf16 where the block stores its intermediates."""
+def _block64(z, t, heads, seen=None):
+    """The transformer block in float64, rounded to bf16 where the block stores its intermediates; `seen`
+    receives the largest |input| of each linear layer."""
     import torch
     r = lambda a: a.to(torch.bfloat16).double()  # noqa: E731
 
@@ -211,7 +212,8 @@ def _block64(z, t, heads):
         return r(d / torch.sqrt((d * d).mean(1, keepdim=True) + 1e-6) * t[g].double() + t[b].double())
 
     z, c = z.double(), z.shape[1]
-    qkv = r(lin(ln(z, "ln1_g", "ln1_b"), "w_qkv", "b_qkv"))
+    h1 = ln(z, "ln1_g", "ln1_b")
+    qkv = r(lin(h1, "w_qkv", "b_qkv"))
     a = torch.empty_like(z)
     for h in range(heads):
         q, k, v = (qkv[:, i * c + h * 64:i * c + h * 64 + 64] for i in range(3))
@@ -219,14 +221,18 @@ def _block64(z, t, heads):
         for i in range(0, len(z), 4096):
             a[i:i + 4096, h * 64:h * 64 + 64] = torch.softmax(q[i:i + 4096] @ k.t().contiguous() * 0.125, 1) @ v
     u1 = r(lin(r(a), "w_o", "b_o"))
-    hid = lin(ln(z + u1, "ln2_g", "ln2_b"), "w_1", "b_1")
+    h2 = ln(z + u1, "ln2_g", "ln2_b")
+    hid = lin(h2, "w_1", "b_1")
     hid = r(0.5 * hid * (1.0 + torch.erf(hid / 2.0 ** 0.5)))
+    if seen is not None:
+        seen += [float(x.abs().max()) for x in (h1, r(a), h2, hid)]
     return u1 + r(lin(hid, "w_2", "b_2"))
 
 
 # rows of one tile, around the two tile heights, row tiles by XCD or in plain order (2200 rows at 1024
-# channels: both), every tile shape and mixes of them (5776, 9000), more tiles than workgroups (33000 at
-# 256: the largest tile), a column count that is no multiple of 4 tiles
+# channels: both), every tile shape and mixes of them (5776, 9000; the largest tile with its output in
+# operand order: test_block_largest_tiles), more tiles than workgroups (33000 at 256), a column count that
+# is no multiple of 4 tiles
 @pytest.mark.parametrize("m,dim", [(1, 256), (127, 256), (129, 256), (257, 768), (640, 1024), (2200, 1024), (5776, 1024),
                                    (9000, 1024), (17000, 256), (33000, 256)])
 @pytest.mark.parametrize("linear", ["bf16", "fp8", "fp8-delayed"])
@@ -280,6 +286,35 @@ def test_block_layernorm_cancels_opposite_lanes_first(B, dim):
     assert bool(((delta.double() - ref).abs() <= 2.0 ** -8 * ref.abs() + 1e-4).all())
 
 
+# the first MLP layer on 256 x 256 tiles with its output in operand order, more tiles than CUs (8 x 61, 12 x 35)
+# and a ragged last row tile
+@pytest.mark.parametrize("m,dim", [(15400, 512), (8900, 768)])
+@pytest.mark.parametrize("linear", ["bf16", "fp8-delayed"])
+def test_block_largest_tiles(B, m, dim, linear):
+    import torch
+    t = {k: torch.from_numpy(v).cuda() for k, v in synth.block_weights(dim, seed=m).items()}
+    t = {k: v.to(torch.bfloat16) if k.startswith("w_") else v for k, v in t.items()}
+    g = torch.Generator(device="cuda")
+    g.manual_seed(m)
+    z = torch.randn(m, dim, generator=g, device="cuda").to(torch.bfloat16)
+    state = torch.zeros(B.FP8_STATE_BYTES, dtype=torch.uint8, device="cuda")
+    bw = B.block_weights(t) if linear == "bf16" else B.block_weights(t, B.LINEAR_FP8_E4M3, B.FP8_DELAYED, state)
+    ph = B.make_params(1, 1, 1, dim, dim // 64, n_special=0, qk_norm=1)
+    delta = torch.full_like(z, float("nan"))
+    ws = B.alloc_ws(B.litevggt_global_block_ws_bytes(ph, m))
+    for _ in range(1 if linear == "bf16" else 2):            # the second call scales by the first one's amaxes
+        B.litevggt_global_block(ph, m, z, bw, delta, ws)
+    torch.cuda.synchronize()
+    seen = []
+    ref = _block64(z, t, dim // 64, seen)
+    err = float((delta.double() - ref).abs().max() / ref.abs().max())
+    assert err <= (2e-2 if linear == "bf16" else 1e-1)       # as in test_block_tile_shapes
+    if linear != "bf16":    # recorded amaxes of the four layers' inputs: LayerNorm of z to a bf16 step, the others behind E4M3 layers
+        amax = state.view(torch.float32).reshape(4, -1)[:, 1].tolist()
+        assert abs(amax[0] / seen[0] - 1) <= 2.0 ** -8
+        assert all(abs(a / s - 1) <= 0.1 for a, s in zip(amax[1:], seen[1:])), (amax, seen)
+
+
 # ------------------------------------------------------------------------------- importance
 # pixel rows that are no multiple of 4 pixels, planes that are none (one pixel at a time), images
 # behind an unaligned address, a single patch row and column, pixel rows wider than a workgroup,
@@ -306,6 +341,13 @@ def test_importance_edges(B, frames, h, w, patch, dim, kind):
     ref, psi_g = O.importance(im.astype(np.float64) / (255.0 if u8 else 1.0), xf, oracle_params(wl))
     assert np.abs(grad.cpu().numpy() - psi_g.reshape(frames, -1)).max() <= 2e-5 * max(1.0, np.abs(psi_g).max())
     assert np.abs(score.cpu().numpy() - ref.reshape(frames, -1)).max() <= 2e-5
+
+
+# more than 1024 channels: a second pass over the channels adds to the map, with the rows of a strip in
+# segments (few frames) and whole
+@pytest.mark.parametrize("frames,h,w,dim", [(2, 9, 5, 1536), (1, 37, 6, 1088), (260, 4, 5, 1536)])
+def test_importance_two_channel_passes(B, frames, h, w, dim):
+    test_importance_edges(B, frames, h, w, 2, dim, "f32")
 
 
 # White noise has gradients of one size everywhere, so the rounding of single pixels averages out and the
@@ -366,7 +408,56 @@ def test_attention_cut_rounds(B, n, heads, kind):
     torch.cuda.synchronize()
     ref = _attn64(q, k, v, kind == "norm", heads)
     assert float((o.double() - ref).abs().max() / ref.abs().max()) <= 2e-2
-    assert torch.equal(o, again)     # sums are added in key order
+    assert torch.equal(o, again)     # two partial sums: the same in either order
+
+
+# Blocks cut in two along the keys whose pieces leave blocks to the per-row kernel (heads by fate: the block
+# that holds the one query with a component along a long key's own direction).  n is 5 blocks and two waves, or
+# one, of a sixth; its key stages are 11 and 11, or 11 and 10
+@pytest.mark.parametrize("n", [1400, 1300])
+def test_attention_cut_blocks_left_to_the_second_pass(B, n):
+    import torch
+    heads, nqb, nkv = 16, (n + 255) // 256, (n + 63) // 64
+    split = 64 * (nkv - nkv // 2)                   # the first key of the second piece
+    # per head: long keys, score of the query along them in binades (256 is what a reference may reach,
+    # a row 60 under its wave's reference is lost), and how many pieces of the block arrive at their sums
+    fates = {"reference too large in the first piece": ([100], 360, 1), "... in its first tile": ([5], 360, 1),
+             "... in the second piece": ([split + 200], 360, 1), "... in its first tile too": ([split + 5], 360, 1),
+             "... in both": ([100, split + 200], 360, 0), "low rows by the second piece": ([split + 200], 120, 2),
+             "low rows by the first piece": ([5], 120, 2), "nothing": ([5], 30, 2)}
+    plan = [(list(fates.values())[h % len(fates)], (5 * h + h // 8) % nqb) for h in range(heads)]
+    assert {b for _, b in plan} == set(range(nqb))
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n)
+    q, k, v = (torch.randn(n, heads, 64, generator=g, device="cuda") for _ in range(3))
+    q[:, :, 0] = k[:, :, 0] = 0.0
+    for h, ((keys, binades, _), blk) in enumerate(plan):
+        q[blk * 256 + 7 * h % 16 + (64 * (h % 4) if blk < nqb - 1 else 0), h, 0] = 32.0
+        k[keys, h, 0] = binades * np.log(2.0) / (32.0 * 0.125)
+    q, k, v = (t.reshape(n, heads * 64).to(torch.bfloat16) for t in (q, k, v))
+    ph = B.make_params(1, 1, 1, heads * 64, heads, n_special=0)
+    need = B.litevggt_attn_ws_bytes(ph, n)
+    per = (heads * 2 * nkv * 4 * 64 * 16 + 255) // 256 * 256
+    stride = 2 * ((n + 511) // 512)
+    flags_at = 256 + 2 * per                        # behind the packed K and V; then the pieces' words
+    sync_at = flags_at + (heads * stride * 4 + 255) // 256 * 256
+    assert need > sync_at + heads * nqb * (256 * 64 + 1024) * 4        # room for every block's sums: cut
+    ws = B.alloc_ws(need)
+    o = torch.full_like(q, float("nan"))
+    B.litevggt_global_attn(ph, n, q, k, v, o, ws)
+    torch.cuda.synchronize()
+    ref = _attn64(q, k, v, False, heads)
+    assert float((o.double() - ref).abs().max() / ref.abs().max()) <= 2e-2
+    base = (ws.data_ptr() + 255) // 256 * 256 - ws.data_ptr()
+    words = ws[base:base + need].cpu().numpy()[:need // 4 * 4].view(np.uint32)
+    flags = words[flags_at // 4:][:heads * stride].reshape(heads, stride)[:, :nqb]
+    arrived = words[sync_at // 4:][:2 * heads * nqb:2].reshape(heads, nqb)
+    want_flags, want_arrived = np.zeros((heads, nqb), np.uint32), np.full((heads, nqb), 2, np.uint32)
+    for h, ((_, binades, pieces), blk) in enumerate(plan):
+        want_flags[h, blk] = binades > 60
+        want_arrived[h, blk] = pieces
+    assert np.array_equal(flags != 0, want_flags != 0)
+    assert np.array_equal(arrived, want_arrived)
 
 
 # ------------------------------------------------------------------------------- scratch
