@@ -429,17 +429,20 @@ int launch_var_map(const uint16_t *x, const Dims &d, int pool, float *psi_v, hip
 // Fusion: one workgroup per frame finds min/max of both maps, then writes
 // alpha*norm(Psi_g) + beta*norm(Psi_v).
 // ---------------------------------------------------------------------------------
-// A frame is a few KB: while there are CUs to spare its latency counts (100 frames 6.9 -> 4.9 us with 16
-// waves in place of 4), with more frames than CUs the launch of its waves (1000 frames 12.2 us against 9.5)
-constexpr int kFuseWaves = 16;
-__global__ __launch_bounds__(64 * kFuseWaves) void k_ga_fuse(const float *__restrict__ psi_g,
-                                                 const float *__restrict__ psi_v, int P,
-                                                 float alpha, float beta,
-                                                 float *__restrict__ score) {
-  __shared__ float red[kFuseWaves][4];
+// A frame is a few KB: while there are CUs to spare its latency counts (100 frames 5.5 -> 4.1 us with 16
+// waves in place of 4), with more frames than CUs the launch of its waves (1000 frames 12.2 us against
+// 9.5).  The number of waves is a template argument: as a launch parameter it cost the four waves 3 %
+// (1000 frames 8.8 us, 8.5 like this).
+constexpr int kFuseWavesFew = 16, kFuseWavesMany = 4;
+template <int WAVES>
+__global__ __launch_bounds__(64 * WAVES) void k_ga_fuse(const float *__restrict__ psi_g,
+                                                        const float *__restrict__ psi_v, int P,
+                                                        float alpha, float beta,
+                                                        float *__restrict__ score) {
+  __shared__ float red[WAVES][4];
   const float *g = psi_g + (size_t)blockIdx.x * P, *v = psi_v + (size_t)blockIdx.x * P;
   float glo = INFINITY, ghi = -INFINITY, vlo = INFINITY, vhi = -INFINITY;
-  for (int t = threadIdx.x; t < P; t += blockDim.x) {
+  for (int t = threadIdx.x; t < P; t += 64 * WAVES) {
     float a = g[t], b = v[t];
     glo = fminf(glo, a);
     ghi = fmaxf(ghi, a);
@@ -458,14 +461,15 @@ __global__ __launch_bounds__(64 * kFuseWaves) void k_ga_fuse(const float *__rest
     red[wave][3] = vhi;
   }
   __syncthreads();
-  for (int w = 0; w < (int)blockDim.x / 64; ++w) {
+#pragma unroll
+  for (int w = 0; w < WAVES; ++w) {
     glo = fminf(glo, red[w][0]);
     ghi = fmaxf(ghi, red[w][1]);
     vlo = fminf(vlo, red[w][2]);
     vhi = fmaxf(vhi, red[w][3]);
   }
   const float gr = ghi - glo, vr = vhi - vlo;
-  for (int t = threadIdx.x; t < P; t += blockDim.x) {
+  for (int t = threadIdx.x; t < P; t += 64 * WAVES) {
     float ng = gr > 0.f ? (g[t] - glo) / gr : 0.f;
     float nv = vr > 0.f ? (v[t] - vlo) / vr : 0.f;
     score[(size_t)blockIdx.x * P + t] = alpha * ng + beta * nv;
@@ -474,8 +478,12 @@ __global__ __launch_bounds__(64 * kFuseWaves) void k_ga_fuse(const float *__rest
 
 int launch_ga_fuse(const float *psi_g, const float *psi_v, const Dims &d, float alpha, float beta,
                    float *score, hipStream_t st) {
-  hipLaunchKernelGGL(k_ga_fuse, dim3((unsigned)d.F), dim3(d.F > 256 ? 256 : 64 * kFuseWaves), 0, st, psi_g, psi_v, d.P, alpha,
-                     beta, score);
+  if (d.F > 256)
+    hipLaunchKernelGGL(k_ga_fuse<kFuseWavesMany>, dim3((unsigned)d.F), dim3(64 * kFuseWavesMany), 0, st, psi_g, psi_v, d.P,
+                       alpha, beta, score);
+  else
+    hipLaunchKernelGGL(k_ga_fuse<kFuseWavesFew>, dim3((unsigned)d.F), dim3(64 * kFuseWavesFew), 0, st, psi_g, psi_v, d.P, alpha,
+                       beta, score);
   LV_HIP_CHECK_LAUNCH();
   return LV_OK;
 }
