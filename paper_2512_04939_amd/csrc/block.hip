@@ -675,12 +675,10 @@ __global__ __launch_bounds__((GemmShape<BM, BN>::kThreads)) __attribute__((amdgp
   read_frags(0, 0, fb[0][0], fa[0][0]);
   read_frags(0, 1, fb[0][1], fa[0][1]);
   constexpr int kSetB = kTwoSets ? 1 : 0;   // the weight set of odd stages
-  int g = 0;
-  for (; g + 1 < total; g += 2) {
+  for (int g = 0; g < total; g += 2) {       // (an even number of stages: K is a multiple of 128)
     stage(g, fb[0], fa[0], fb[kSetB], fa[1]);
     stage(g + 1, fb[kSetB], fa[1], fb[0], fa[0]);
   }
-  if (g < total) stage(g, fb[0], fa[0], fb[kSetB], fa[1]);
   // the reads issued by the last stage are waited for before their registers die
   wait_set(fb[0], fa[0]);
   wait_set(fb[kSetB], fa[1]);
@@ -717,7 +715,7 @@ __global__ __launch_bounds__((GemmShape<BM, BN>::kThreads)) __attribute__((amdgp
       // holds the 16 codes of channels 32u + 16h .. + 15 of row r): every value is rounded to
       // bf16 as if it had been stored, then scaled by *out_inv; a lane has one dword of four codes
       // per register group g, lanes l and l + 32 trade groups 2, 3 against groups 0, 1.  The
-      // largest |value| of the rows below M goes into *out_amax; rows beyond M are written as zeros.
+      // largest |value| of the rows below M goes into *out_amax; the tile's rows beyond M are written as zeros.
       const float r = __uint_as_float(*out_inv);
       const int KSn = nt_n * (BN / 32);
       u32x4 *op = (u32x4 *)out + ((size_t)(tm * S::kFragA + wd * 2) * KSn + tn * (BN / 32) + wn * kB) * 64 + lane + anchor;
@@ -869,7 +867,9 @@ size_t block_ws_bytes(int64_t M, int C, int heads, int attn_dtype, bool least) {
 struct LinearOpts {
   bool fp8 = false;
   const u32x4 *a_packed = nullptr;     // the activation operand, already in operand order (then A is unused)
-  bool pack_out = false;               // out receives the next layer's (K = Nout) operand, Mp rows, instead of row-major rows
+  // out receives the next layer's (K = Nout) operand instead of row-major rows: the rows of whole tiles (128
+  // or 256 each), rows M and up undefined; the next layer may read up to Mp rows, into outputs it drops
+  bool pack_out = false;
   const uint16_t *addend = nullptr;    // row-major, same shape as out: out = addend + result
   const u32x4 *w_packed = nullptr;     // the weight operand
   // FP8: this layer's scalars, prepared by k_fp8_prepare.  A, unless a_packed, is quantised with
@@ -919,7 +919,7 @@ static int launch_linear(const uint16_t *A, int64_t M, int K, int Nout,
                          hipStream_t st, const LinearOpts &o) {
   if (!o.w_packed || (o.fp8 && !o.sc) || (o.current && (o.a_packed || o.pack_out))) return LV_ERR_PARAM;
   if (o.pack_out && (o.addend || split != Nout || (o.fp8 && (!o.out_inv || !o.out_amax)))) return LV_ERR_PARAM;
-  if (K % 64 != 0 || Nout % kTile != 0 || split % kTile != 0 || Nout % split != 0) return LV_ERR_SHAPE;
+  if (K % 128 != 0 || Nout % kTile != 0 || split % kTile != 0 || Nout % split != 0) return LV_ERR_SHAPE;
   int rc;
   if (w.Mp / 128 * (Nout / 128) >= ((int64_t)1 << 30) || w.Mp >= ((int64_t)1 << 31)) return LV_ERR_SHAPE;
   int dev = 0, n_cu = 0;

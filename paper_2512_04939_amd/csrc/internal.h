@@ -65,9 +65,9 @@ int launch_pack_rows(const uint16_t *x, int64_t n, int64_t n_pad, int C, void *p
 size_t block_ws_bytes(int64_t M, int C, int heads, int attn_dtype, bool least = false);
 size_t block_wpack_bytes(int C);
 // delta = Block(z) - z for M tokens; the two events (optional) are recorded around the
-// attention kernel inside the block.  wpack_keep (optional, block_wpack_bytes(C), bf16 layers
-// only): receives the weights in the linear kernel's operand order, or, with wpack_ready,
-// already holds them from an earlier call with the same weights.
+// attention kernel inside the block.  wpack_keep (optional, block_wpack_bytes(C)): receives the
+// weights in the linear kernel's operand order (FP8 layers: quantised, with their amaxes), or, with
+// wpack_ready, already holds them from an earlier call with the same weights.
 int launch_global_block(const uint16_t *z, int64_t M, int C, int heads, float scale, int attn_dtype,
                         int qk_norm, const litevggt_block_weights &bw, uint16_t *delta, void *ws,
                         size_t ws_bytes, hipStream_t st, hipEvent_t after_pack = nullptr,

@@ -716,7 +716,7 @@ __device__ __forceinline__ void wave_lds_order() {
   __builtin_amdgcn_wave_barrier();
 }
 
-// vals_in NULL: element i carries i.  keys_out may be NULL (nobody reads them).
+// vals_in NULL: element i carries i.
 __global__ __launch_bounds__(256) void k_radix_scatter(const uint32_t *__restrict__ keys,
                                                        const int32_t *__restrict__ vals_in, int64_t N,
                                                        int shift, int bits, int nchunks,
@@ -765,7 +765,7 @@ __global__ __launch_bounds__(256) void k_radix_scatter(const uint32_t *__restric
     if (ok && rank == cnt - 1) base[wave][d] = at + cnt;   // one lane per digit present
     wave_lds_order();
     if (ok) {
-      if (keys_out) keys_out[at + rank] = key[i];
+      keys_out[at + rank] = key[i];
       vals_out[at + rank] = val[i];
     }
   }
