@@ -20,6 +20,11 @@
  *   - inputs are never written; outputs must not overlap inputs unless stated.
  *   - `ws` is scratch device memory of at least the size the matching *_ws_bytes /
  *     litevggt_plan reports, 256-byte aligned; its contents are undefined afterwards.
+ *     The reported size is not monotone: some sequence lengths have use for more (the
+ *     partial sums of attention blocks that are cut in two, the candidate lists of a
+ *     matching schedule).  Scratch of the size reported for a longer sequence, all else
+ *     equal, is accepted too: the call then does without these, which may take longer and
+ *     rounds differently.  Less than what is needed without them is LV_ERR_WORKSPACE.
  */
 #ifndef LITEVGGT_H
 #define LITEVGGT_H
