@@ -492,11 +492,11 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   }   // rounds
 }
 
-// Final decision per src row.  Every sweep hands over its two best candidates by fp32 similarity.
+// Final decision per src row.  Every list (MatchSched) holds its two best candidates by fp32 similarity.
 // If the runner-up is closer than kRescoreGap to the best, every candidate inside that gap is
 // recomputed in float64 and the decision is taken on those values rounded to fp32, lowest token
 // index on a tie: the rule the fp32 accumulation order cannot disturb.  A row with more
-// near-equal candidates than one sweep's two best can still lose its true best inside a sweep;
+// near-equal candidates than one list's two best can still lose its true best inside a list;
 // what it picks instead is within twice the fp32 accumulation error of it (C / 16 additions of
 // exact 16-product sums).
 //
