@@ -323,6 +323,7 @@ int litevggt_layers_run(const litevggt_params *p, int n_layers, const void *imag
   void *op_ws = (char *)wpack + (p->block ? block_wpack_bytes(d.C) : 0);
   const size_t op_bytes = ws_bytes - (size_t)((char *)op_ws - (char *)ws);
   uint16_t *xx = (uint16_t *)x;
+  bool merged = false;   // z already holds this layer's merged tokens
   for (int l = 0; l < n_layers; ++l) {
     const bool refresh = (l % p->refresh_interval) == 0;
     if (refresh_log) refresh_log[l] = refresh ? 1 : 0;
@@ -356,8 +357,10 @@ int litevggt_layers_run(const litevggt_params *p, int n_layers, const void *imag
       if (rc) return rc;
     }
     if ((rc = mark(LV_EV_MATCH_END))) return rc;
-    rc = launch_merge(xx, d, pl.M, *index, z, st);
-    if (rc) return rc;
+    if (!merged) {
+      rc = launch_merge(xx, d, pl.M, *index, z, st);
+      if (rc) return rc;
+    }
     if ((rc = mark(LV_EV_MERGE_END))) return rc;
     if (p->block) {
       rc = launch_global_block(z, pl.M, d.C, d.heads, scale_of(p), p->attn_dtype, p->qk_norm,
@@ -371,7 +374,10 @@ int litevggt_layers_run(const litevggt_params *p, int n_layers, const void *imag
       if ((rc = mark(LV_EV_ATTN_END))) return rc;
     }
     if ((rc = mark(LV_EV_BLOCK_END))) return rc;
-    rc = launch_unmerge(y, d, *index, xx, xx, st);
+    // Where the next layer merges by the same index and nothing comes between, its merge is done in the
+    // same pass over the tokens.  A caller who times the steps gets them one by one.
+    merged = !events && !p->frame_attn && l + 1 < n_layers && (l + 1) % p->refresh_interval != 0;
+    rc = merged ? launch_unmerge_merge(y, d, pl.M, *index, xx, z, st) : launch_unmerge(y, d, *index, xx, xx, st);
     if (rc) return rc;
     if ((rc = mark(LV_EV_UNMERGE_END))) return rc;
     if (p->frame_attn) {

@@ -79,6 +79,9 @@ int launch_merge(const uint16_t *x, const Dims &d, int64_t M, const litevggt_ind
                  uint16_t *z, hipStream_t st);
 int launch_unmerge(const uint16_t *y, const Dims &d, const litevggt_index &ix,
                    const uint16_t *residual, uint16_t *out, hipStream_t st);
+// launch_unmerge(y, x -> x) and launch_merge(x -> z) in one; y and z are different buffers
+int launch_unmerge_merge(const uint16_t *y, const Dims &d, int64_t M, const litevggt_index &ix, uint16_t *x, uint16_t *z,
+                         hipStream_t st);
 
 // attn.hip
 size_t attn_ws_bytes(int heads, int64_t n_tokens, int attn_dtype, int n_seq = 1, bool least = false);

@@ -17,10 +17,22 @@ __device__ __forceinline__ void acc8(float (&a)[8], const u32x4 w) {
   a[7] += bf16_hi(w.w);
 }
 
+// ADD (k_merge): the token rows are written as well
+template <bool ADD> struct MergeX { typedef const uint16_t *__restrict__ type; };
+template <> struct MergeX<true> { typedef uint16_t *__restrict__ type; };
+
 #ifndef LV_MERGE_COOP
 #define LV_MERGE_COOP 64
 #endif
 constexpr int kCoopSize = LV_MERGE_COOP;   // groups larger than this are summed by all 4 waves of a workgroup
+
+// two rows of eight bf16 values added, one rounding
+__device__ __forceinline__ u32x4 add8(const u32x4 v, const u32x4 w) {
+  return u32x4{pack_bf16(bf16_lo(v.x) + bf16_lo(w.x), bf16_hi(v.x) + bf16_hi(w.x)),
+               pack_bf16(bf16_lo(v.y) + bf16_lo(w.y), bf16_hi(v.y) + bf16_hi(w.y)),
+               pack_bf16(bf16_lo(v.z) + bf16_lo(w.z), bf16_hi(v.z) + bf16_hi(w.z)),
+               pack_bf16(bf16_lo(v.w) + bf16_lo(w.w), bf16_hi(v.w) + bf16_hi(w.w))};
+}
 
 // acc += rows group_mem[lo..hi) of x, this lane's chunks; R member rows in flight per lane.
 // Rows are taken in batches of R; the last batch is masked (lo, hi are wave-uniform), so its
@@ -51,6 +63,55 @@ __device__ __forceinline__ void sum_rows(const uint16_t *__restrict__ x,
   }
 }
 
+// The same with row i becoming x[i] + y first (rounded to bf16 and stored; y: the slot's row).  The
+// loads of a batch are issued ahead of the stores of the batch before it: loads and stores of a wave are
+// waited for in the order of their issue, so behind them they would wait for the stores as well.
+// Few rows per batch: the two batches' registers decide how many waves a SIMD holds (32 frames of 37 x 37
+// patches, C = 1024, R = 8: 57 us, 4: 46, 2: 47; 200 frames 290, 254, 270; without the loads ahead 61 us).
+constexpr int kAddRows = 4;
+template <int CPL, int R>
+__device__ __forceinline__ void add_sum_rows(uint16_t *x, const u32x4 (&y)[CPL], const int32_t *__restrict__ group_mem,
+                                             int lo, int hi, int C, int nch, int lane, float (&a)[CPL][8]) {
+  int r[2][R];
+  u32x4 w[2][R][CPL];
+  auto index = [&](int j, int (&q)[R]) {
+#pragma unroll
+    for (int u = 0; u < R; ++u) q[u] = j + u < hi ? group_mem[j + u] : -1;
+  };
+  auto load = [&](const int (&q)[R], u32x4(&v)[R][CPL]) {
+#pragma unroll
+    for (int u = 0; u < R; ++u)
+#pragma unroll
+      for (int c = 0; c < CPL; ++c) {
+        const int ch = lane + 64 * c;
+        v[u][c] = (q[u] >= 0 && ch < nch) ? ((const u32x4 *)(x + (size_t)q[u] * C))[ch] : u32x4{0u, 0u, 0u, 0u};
+      }
+  };
+  auto step = [&](int j, int (&q)[R], u32x4(&v)[R][CPL], int (&qn)[R], u32x4(&vn)[R][CPL]) {
+    load(qn, vn);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int u = 0; u < R; ++u)
+#pragma unroll
+      for (int c = 0; c < CPL; ++c) {
+        const int ch = lane + 64 * c;
+        if (q[u] >= 0 && ch < nch) {
+          v[u][c] = add8(y[c], v[u][c]);
+          ((u32x4 *)(x + (size_t)q[u] * C))[ch] = v[u][c];
+        }
+        acc8(a[c], v[u][c]);
+      }
+    index(j + 2 * R, q);
+  };
+  index(lo, r[0]);
+  load(r[0], w[0]);
+  index(lo + R, r[1]);
+  for (int j = lo; j < hi; j += 2 * R) {
+    step(j, r[0], w[0], r[1], w[1]);
+    if (j + R < hi) step(j + R, r[1], w[1], r[0], w[0]);
+  }
+}
+
 template <int CPL>
 __device__ __forceinline__ void store_mean(uint16_t *__restrict__ z, int m, int C, int nch, int lane,
                                            const float (&a)[CPL][8], float inv) {
@@ -76,10 +137,17 @@ __device__ __forceinline__ void store_mean(uint16_t *__restrict__ z, int m, int 
 // group size, so results are reproducible.  The large groups are the long jobs, so they are
 // started first: workgroups 0 .. nb0-1 scan kScan slots each (nb0 apart) and sum the large
 // groups among them, workgroups nb0 .. take the small ones behind them.
+//
+// ADD: the unmerge of one layer and the merge of the next in one pass over the tokens, where both use
+// the same groups: row i of slot m becomes x[i] + y[m] (the sum that k_unmerge stores, bit for bit) and
+// enters the mean of its slot as it is stored.  Bound by HBM like its two halves, which read x twice and
+// gather y per token; C = 1024, 37 x 37 patches, both halves -> together: 32 frames at ratio 0.9
+// 56 -> 46 us (4.4 TB/s), 200 frames 358 -> 254 (5.0 TB/s), 48 frames at ratio 0.5 100 -> 74; two frames
+// of 16 x 16, C = 256 7.2 -> 3.9.
 constexpr int kScan = 64;
 
-template <int CPL>
-__global__ __launch_bounds__(256) void k_merge(const uint16_t *__restrict__ x,
+template <int CPL, bool ADD>
+__global__ __launch_bounds__(256) void k_merge(typename MergeX<ADD>::type x, const uint16_t *__restrict__ y,
                                                const int32_t *__restrict__ group_off,
                                                const int32_t *__restrict__ group_mem, int M,
                                                int C, int nb0, uint16_t *__restrict__ z) {
@@ -87,6 +155,13 @@ __global__ __launch_bounds__(256) void k_merge(const uint16_t *__restrict__ x,
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int nch = C >> 3;
+  auto slot_row = [&](int m, u32x4(&row)[CPL]) {   // ADD: this lane's pieces of y[m]
+#pragma unroll
+    for (int c = 0; c < CPL; ++c) {
+      row[c] = u32x4{0u, 0u, 0u, 0u};
+      if (ADD && lane + 64 * c < nch) row[c] = ((const u32x4 *)(y + (size_t)m * C))[lane + 64 * c];
+    }
+  };
   if ((int)blockIdx.x < nb0) {           // cooperative pass over the large groups of kScan slots
     // strided: neighbouring slots (the all-dst first frame) hold the largest groups
     const int64_t ms = (int64_t)blockIdx.x + (int64_t)lane * nb0;
@@ -104,7 +179,10 @@ __global__ __launch_bounds__(256) void k_merge(const uint16_t *__restrict__ x,
       for (int c = 0; c < CPL; ++c)
 #pragma unroll
         for (int i = 0; i < 8; ++i) a[c][i] = 0.f;
-      sum_rows<CPL, 16>(x, group_mem, lo, hi, C, nch, lane, a);
+      u32x4 ym[CPL];
+      slot_row(m, ym);
+      if constexpr (ADD) add_sum_rows<CPL, kAddRows>(x, ym, group_mem, lo, hi, C, nch, lane, a);
+      else sum_rows<CPL, 16>(x, group_mem, lo, hi, C, nch, lane, a);
       if (wave > 0) {
 #pragma unroll
         for (int c = 0; c < CPL; ++c)
@@ -134,19 +212,23 @@ __global__ __launch_bounds__(256) void k_merge(const uint16_t *__restrict__ x,
       for (int c = 0; c < CPL; ++c)
 #pragma unroll
         for (int i = 0; i < 8; ++i) a[c][i] = 0.f;
-      sum_rows<CPL, 8>(x, group_mem, b, e, C, nch, lane, a);
+      u32x4 ym[CPL];
+      slot_row(m, ym);
+      if constexpr (ADD) add_sum_rows<CPL, kAddRows>(x, ym, group_mem, b, e, C, nch, lane, a);
+      else sum_rows<CPL, 8>(x, group_mem, b, e, C, nch, lane, a);
       store_mean<CPL>(z, m, C, nch, lane, a, 1.0f / (float)(e - b));
     }
   }
 }
 
-int launch_merge(const uint16_t *x, const Dims &d, int64_t M, const litevggt_index &ix,
-                 uint16_t *z, hipStream_t st) {
+template <bool ADD>
+static int merge_rows(typename MergeX<ADD>::type x, const uint16_t *y, const Dims &d, int64_t M, const litevggt_index &ix,
+                      uint16_t *z, hipStream_t st) {
   const int cpl = (d.C / 8 + 63) / 64;
   const int nb0 = (int)((M + kScan - 1) / kScan);
   const unsigned grid = (unsigned)(nb0 + (M + 3) / 4);
-#define LV_MERGE(CPL)                                                                       \
-  hipLaunchKernelGGL(k_merge<CPL>, dim3(grid), dim3(256), 0, st, x, ix.group_off, ix.group_mem, \
+#define LV_MERGE(CPL)                                                                                     \
+  hipLaunchKernelGGL((k_merge<CPL, ADD>), dim3(grid), dim3(256), 0, st, x, y, ix.group_off, ix.group_mem, \
                      (int)M, d.C, nb0, z)
   switch (cpl) {
     case 1: LV_MERGE(1); break;
@@ -158,6 +240,15 @@ int launch_merge(const uint16_t *x, const Dims &d, int64_t M, const litevggt_ind
 #undef LV_MERGE
   LV_HIP_CHECK_LAUNCH();
   return LV_OK;
+}
+
+int launch_merge(const uint16_t *x, const Dims &d, int64_t M, const litevggt_index &ix, uint16_t *z, hipStream_t st) {
+  return merge_rows<false>(x, nullptr, d, M, ix, z, st);
+}
+
+int launch_unmerge_merge(const uint16_t *y, const Dims &d, int64_t M, const litevggt_index &ix, uint16_t *x, uint16_t *z,
+                         hipStream_t st) {
+  return merge_rows<true>(x, y, d, M, ix, z, st);
 }
 
 #ifndef LV_UNMERGE_ROWS
@@ -190,12 +281,7 @@ __global__ __launch_bounds__(256) void k_unmerge(const uint16_t *__restrict__ y,
       for (int r = 0; r < R; ++r) {
         if (i0 + r >= N) break;
         u32x4 v = w[r];
-        if (RES) {
-          v.x = pack_bf16(bf16_lo(v.x) + bf16_lo(res[r].x), bf16_hi(v.x) + bf16_hi(res[r].x));
-          v.y = pack_bf16(bf16_lo(v.y) + bf16_lo(res[r].y), bf16_hi(v.y) + bf16_hi(res[r].y));
-          v.z = pack_bf16(bf16_lo(v.z) + bf16_lo(res[r].z), bf16_hi(v.z) + bf16_hi(res[r].z));
-          v.w = pack_bf16(bf16_lo(v.w) + bf16_lo(res[r].w), bf16_hi(v.w) + bf16_hi(res[r].w));
-        }
+        if (RES) v = add8(v, res[r]);
         __builtin_nontemporal_store(v, (u32x4 *)(out + (size_t)(i0 + r) * C) + ch);
       }
     }

@@ -521,3 +521,45 @@ def test_matching_in_scratch_of_a_longer_sequence(B, frames, h, w, ratio):
         torch.cuda.synchronize()
         out.append((ib.anchor_of, ib.group_off, ib.group_mem, xx))
     assert all(torch.equal(a, b) for a, b in zip(*out))
+
+
+# ------------------------------------------------------------------------------- layers that share an index
+# The driver does the unmerge of a layer and the merge of the next in one pass where both use the same
+# groups; step by step they give the same bits.  Widths of one piece per lane, a part of one, two; groups
+# from one member to more than 64 and 256 (a still scene), a refresh in between, special tokens only.
+@pytest.mark.parametrize("frames,h,w,special,ratio,dim,still", [(2, 16, 16, 5, 0.5, 256, False), (40, 9, 11, 3, 0.9, 64, True),
+                                                                (300, 3, 4, 1, 0.9, 576, True), (5, 12, 13, 5, -1.0, 1024, False),
+                                                                (3, 2, 2, 0, 0.0, 128, False)])
+def test_layers_in_one_pass_equal_the_single_steps(B, frames, h, w, special, ratio, dim, still):
+    import torch
+    g = torch.Generator(device="cuda")
+    g.manual_seed(frames + dim)
+    wl = synth.Workload("t", frames=frames, grid_h=h, grid_w=w, dim=dim, heads=dim // 64, n_special=special, merge_ratio=ratio,
+                        refresh_interval=3)
+    ph = hip_params(wl)
+    pl = B.litevggt_plan(ph)
+    x = torch.randn(frames, h * w + special, dim, generator=g, device="cuda")
+    if still:   # every frame shows a handful of things: large groups
+        x[:, special:] = x[0, special:special + 4].repeat(frames, (h * w + 3) // 4, 1)[:, :h * w] + 0.1 * x[:, special:]
+    x = x.reshape(pl.N, dim).to(torch.bfloat16)
+    images = torch.rand(frames, 3, h * ph.patch, w * ph.patch, generator=g, device="cuda")
+    maps = [torch.empty(frames, h * w, device="cuda") for _ in range(4)]
+    ib, ws = B.alloc_index(pl), B.alloc_ws(pl.ws_bytes)
+    got = x.clone()
+    B.litevggt_layers_run(ph, 5, images, got, ib, maps[0], maps[1], ws)
+    want, ix = x.clone(), B.alloc_index(pl)
+    z = torch.empty(pl.M, dim, dtype=torch.bfloat16, device="cuda")
+    y = torch.empty_like(z)
+    largest = 0
+    for l in range(5):
+        if l % 3 == 0:
+            B.litevggt_importance(ph, images, want, maps[2], l == 0, maps[3], ws)
+            B.litevggt_select_anchors(ph, maps[3], ix)
+            B.litevggt_match(ph, want, ix, None, ws)
+            largest = max(largest, int(ix.group_off[1:].sub(ix.group_off[:-1]).max()))
+        B.litevggt_merge(ph, want, ix, z)
+        B.litevggt_global_attn(ph, pl.M, z, z, z, y, ws)
+        B.litevggt_unmerge(ph, y, ix, want, want)
+    torch.cuda.synchronize()
+    assert torch.equal(got.view(torch.int16), want.view(torch.int16))
+    assert not still or largest > 64
