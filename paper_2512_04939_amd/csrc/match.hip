@@ -612,7 +612,8 @@ __global__ __launch_bounds__(256) void k_match_finish(
 // pass.  Digits are as narrow as the number of passes allows (fewer counters to scan); a
 // workgroup takes a chunk of 1024 elements, each of its 4 waves 256 consecutive ones, so the
 // scatter is a chain of 4 steps and not of 16; the last pass writes group_mem itself.
-// Together 56 -> 34 us at 32 frames of 37 x 37 patches, 73 -> 41 us at 100 frames of 28 x 37.
+// Together 56 -> 34 us at 32 frames of 37 x 37 patches, 73 -> 41 us at 100 frames of 28 x 37 (before the
+// three-launch way, which takes both of these sizes now: 15 and 26 us under the trace).
 // ---------------------------------------------------------------------------------
 constexpr int kSortChunk = 1024;
 constexpr int kScanPer = 16;     // counters per thread and tile of the scan
@@ -767,6 +768,120 @@ __global__ __launch_bounds__(256) void k_radix_scatter(const uint32_t *__restric
     if (ok) {
       keys_out[at + rank] = key[i];
       vals_out[at + rank] = val[i];
+    }
+  }
+}
+
+// ---- Two passes in three launches (k_radix_first, two k_radix_move), where the counters are few enough
+// for every workgroup to sum them itself: at these sizes a launch costs more than what it does. Counters lie [chunk][digit].  The first move counts the second one's digits on the way, at
+// the places where its elements come to lie, and the second one finds the groups' starts as the lowest
+// place of each slot; both by integer atomics, whose order leaves no trace.
+// One refresh call, seven launches -> three: 12 frames of 37 x 37 patches 94.7 -> 90.5 us, 64 of 16 x 16
+// 79.5 -> 73.7, 100 of 28 x 37 (13,056 counters) 1226.0 -> 1221.3; with 32,768 counters 1419 -> 1424.
+constexpr int kMoveCounters = 16384;   // chunks x digits, at most
+
+// Counts the first pass' digits, clears the second pass' counters, and sets group_off to no place yet.
+__global__ __launch_bounds__(256) void k_radix_first(const uint32_t *__restrict__ keys, int N, int M, int bits,
+                                                     uint32_t *__restrict__ hist, uint32_t *__restrict__ hist2,
+                                                     int32_t *__restrict__ group_off) {
+  __shared__ uint32_t h[256];
+  const int tid = threadIdx.x, bins = 1 << bits;
+  h[tid] = 0u;
+  __syncthreads();
+  const int b = blockIdx.x * kSortChunk;
+#pragma unroll
+  for (int i = 0; i < kSortChunk / 256; ++i) {
+    const int g = b + i * 256 + tid;
+    if (g < N) atomicAdd(&h[keys[g] & (uint32_t)(bins - 1)], 1u);
+    if (g <= M) group_off[g] = g == M ? N : 0x7fffffff;   // M <= N
+  }
+  if (N == M && blockIdx.x == gridDim.x - 1 && tid == 0) group_off[M] = N;
+  __syncthreads();
+  if (tid < bins) {
+    hist[blockIdx.x * bins + tid] = h[tid];
+    hist2[blockIdx.x * bins + tid] = 0u;
+  }
+}
+
+// FIRST: element i carries i, and the elements' second digits are counted.  Else: the low digits are sorted
+// and vals_out is group_mem.  16 waves of 64 elements: the counters of all chunks are read in two or three
+// batches, and no wave has a chain of steps.
+constexpr int kMoveWaves = kSortChunk / 64;
+
+template <bool FIRST>
+__global__ __launch_bounds__(kSortChunk) void k_radix_move(const uint32_t *__restrict__ keys,
+                                                           const int32_t *__restrict__ vals_in, int N, int M, int bits,
+                                                           int nchunks, const uint32_t *__restrict__ hist,
+                                                           uint32_t *__restrict__ hist2, uint32_t *__restrict__ keys_out,
+                                                           int32_t *__restrict__ vals_out, int32_t *__restrict__ group_off) {
+  __shared__ uint32_t base[kMoveWaves][256];   // per wave: elements of a digit, then the place of its first one
+  __shared__ uint32_t total[256], before[256], wtot[4];
+  const int tid = threadIdx.x, lane = tid & 63, bins = 1 << bits, chunk = blockIdx.x;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const uint32_t mask = (uint32_t)bins - 1u;
+  const int g = chunk * kSortChunk + tid;
+  const uint64_t below = lane == 0 ? 0ull : (~0ull >> (64 - lane));
+  const bool ok = g < N;
+  const uint32_t key = ok ? keys[g] : 0u;
+  const int32_t val = ok ? (FIRST ? g : vals_in[g]) : 0;
+  // of digit tid & mask, in every (1024 / bins)-th chunk: all elements, and those of earlier chunks
+  uint32_t all = 0u, early = 0u;
+  const int groups = kSortChunk >> bits;
+  for (int c = tid >> bits; c < nchunks; c += 8 * groups) {
+    uint32_t v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v[u] = c + u * groups < nchunks ? hist[(c + u * groups) * bins + (tid & (int)mask)] : 0u;
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      all += v[u];
+      early += c + u * groups < chunk ? v[u] : 0u;
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < kMoveWaves * 256 / kSortChunk; ++i) (&base[0][0])[i * kSortChunk + tid] = 0u;
+  if (tid < 256) total[tid] = before[tid] = 0u;
+  __syncthreads();
+  const uint32_t d = (FIRST ? key : key >> bits) & mask;
+  const uint64_t peers = digit_peers(d, bits, ok);
+  const uint32_t rank = (uint32_t)__popcll(peers & below);
+  if (ok && rank == 0u) base[wave][d] = (uint32_t)__popcll(peers);
+  atomicAdd(&total[tid & (int)mask], all);
+  atomicAdd(&before[tid & (int)mask], early);
+  __syncthreads();
+  // first place of a digit = all elements of lower digits + its elements in earlier chunks
+  const uint32_t mine = tid < bins ? total[tid] : 0u;
+  uint32_t inc = 0u;
+  if (wave < 4) {
+    inc = wave_scan(mine, lane);
+    if (lane == 63) wtot[wave] = inc;
+  }
+  __syncthreads();
+  if (tid < bins) {
+    uint32_t run = inc - mine + before[tid];
+    for (int w = 0; w < wave; ++w) run += wtot[w];
+#pragma unroll
+    for (int w = 0; w < kMoveWaves; ++w) {
+      const uint32_t c = base[w][tid];
+      base[w][tid] = run;
+      run += c;
+    }
+  }
+  __syncthreads();
+  const uint32_t to = base[wave][d] + rank;
+  if constexpr (FIRST) {
+    if (ok) {
+      keys_out[to] = key;
+      vals_out[to] = val;
+      atomicAdd(&hist2[(to / kSortChunk) * bins + ((key >> bits) & mask)], 1u);
+    }
+  } else {
+    // lower lanes of the same high digit have no larger low digits: the nearest one tells whether the
+    // slot has been here already
+    const uint64_t lower = peers & below;
+    const uint32_t prev = __shfl(key, lower ? 63 - __builtin_clzll(lower) : lane, 64);
+    if (ok) {
+      vals_out[to] = val;
+      if ((!lower || prev != key) && key < (uint32_t)M) atomicMin(&group_off[key], (int32_t)to);
     }
   }
 }
@@ -947,6 +1062,19 @@ int launch_match(const uint16_t *x, const Dims &d, const litevggt_plan_t &pl,
   const int passes = (bits + 7) / 8, per_pass = (bits + passes - 1) / passes;
   const uint32_t *kin = (const uint32_t *)ix.slot_of;
   const int32_t *vin = nullptr;
+  if (passes == 2 && (w.nchunks << per_pass) <= kMoveCounters) {
+    uint32_t *hist2 = w.keys[1];   // (at least as many words as counters: N > 16384)
+    const int N = (int)d.N, M = (int)pl.M;
+    hipLaunchKernelGGL(k_radix_first, dim3((unsigned)w.nchunks), dim3(256), 0, st, kin, N, M, per_pass, w.hist, hist2,
+                       ix.group_off);
+    hipLaunchKernelGGL(k_radix_move<true>, dim3((unsigned)w.nchunks), dim3(kSortChunk), 0, st, kin, vin, N, M, per_pass, w.nchunks,
+                       (const uint32_t *)w.hist, hist2, w.keys[0], w.vals[0], ix.group_off);
+    hipLaunchKernelGGL(k_radix_move<false>, dim3((unsigned)w.nchunks), dim3(kSortChunk), 0, st, (const uint32_t *)w.keys[0],
+                       (const int32_t *)w.vals[0], N, M, per_pass, w.nchunks, (const uint32_t *)hist2, (uint32_t *)nullptr,
+                       (uint32_t *)nullptr, ix.group_mem, ix.group_off);
+    LV_HIP_CHECK_LAUNCH();
+    return LV_OK;
+  }
   for (int p = 0; p < passes; ++p) {
     uint32_t *kout = w.keys[p & 1];
     int32_t *vout = p == passes - 1 ? ix.group_mem : w.vals[p & 1];
