@@ -900,9 +900,10 @@ __global__ __launch_bounds__(256) void k_csr_finish(const uint32_t *__restrict__
 // owns elements w * per .. in steps of 64, ranks them against the earlier ones of its own with
 // the same digit (two passes of 7 bits), and the positions follow from one scan over the
 // counters of all digits and waves.  The elements are in registers while they are moved, so one
-// LDS array serves both passes.  Up to kCsrSmall tokens, where its time on one CU (about 8 us at
-// 522 tokens, 20 at 16384) is below the seven launches of the general way (35-40 us).
-constexpr int kCsrSmall = 16384;
+// LDS array serves both passes.  Up to kCsrSmall tokens, where its time on one CU is below the three
+// launches of the general way.  One refresh call, this way against that: 2,748 tokens 53.5 and 61.3 us, 4,122 58.3 and
+// 61.3, 6,870 63.7 and 61.5, 10,992 84.3 and 75.1, 15,114 95.6 and 78.5.
+constexpr int kCsrSmall = 5120;
 constexpr int kCsrSteps = kCsrSmall / 1024;   // 64-element steps per wave, at most
 
 __global__ __launch_bounds__(1024) void k_csr_small(const int32_t *__restrict__ slot_of, int N, int M,
@@ -1063,7 +1064,7 @@ int launch_match(const uint16_t *x, const Dims &d, const litevggt_plan_t &pl,
   const uint32_t *kin = (const uint32_t *)ix.slot_of;
   const int32_t *vin = nullptr;
   if (passes == 2 && (w.nchunks << per_pass) <= kMoveCounters) {
-    uint32_t *hist2 = w.keys[1];   // (at least as many words as counters: N > 16384)
+    uint32_t *hist2 = w.keys[1];   // (at least as many words as counters: N > kCsrSmall)
     const int N = (int)d.N, M = (int)pl.M;
     hipLaunchKernelGGL(k_radix_first, dim3((unsigned)w.nchunks), dim3(256), 0, st, kin, N, M, per_pass, w.hist, hist2,
                        ix.group_off);

@@ -183,11 +183,12 @@ def test_match_lists_keep_their_own_candidates(B, frames, h, w, ratio):
     assert np.array_equal(_i32(ib.anchor_of)[src[rows]], np.array(want))
 
 
-# groups: the largest sequence one workgroup sorts, the smallest beyond it, a chunk of the general
+# groups: the largest sequence one workgroup sorts, the smallest beyond it, one digit pass, a chunk of the general
 # sort that ends on a wave's last element, and one slot count above 16 bits (three digit passes); two
 # passes in three launches: whole chunks of kept tokens only, large groups of few slots, the most counters
 # that are summed in the move and one chunk more
-@pytest.mark.parametrize("frames,h,w,special,ratio", [(64, 15, 17, 1, 0.9), (5, 52, 63, 1, 0.5), (2, 1, 1, 0, 0.0),
+@pytest.mark.parametrize("frames,h,w,special,ratio", [(20, 15, 17, 1, 0.9), (3, 42, 40, 27, 0.5), (50, 8, 16, 0, 0.99),
+                                                      (64, 15, 17, 1, 0.9), (5, 52, 63, 1, 0.5), (2, 1, 1, 0, 0.0),
                                                       (17, 32, 32, 0, 0.75), (70, 32, 32, 2, 0.0),
                                                       (17, 32, 32, 0, 0.0), (40, 20, 21, 0, 0.98), (64, 32, 32, 0, 0.5),
                                                       (65, 32, 32, 0, 0.5), (32, 37, 37, 5, 0.9)])
