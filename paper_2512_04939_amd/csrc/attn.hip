@@ -56,19 +56,23 @@ __device__ __forceinline__ u32x4 rms_scale8(const u32x4 w, int log2_lanes) {
 //      the S^T accumulator holds its rows, so P needs no shuffle before the second MFMA)
 // With several sequences of n tokens each in one call (frame attention: one per frame) the
 // second grid dimension runs over (sequence, head) pairs and so do the packed arrays.
-// CUT: also clears the words that the pieces of cut blocks meet at (a kernel of its own: behind a
-// run-time test it cost every call 2 %, 42.8 -> 43.7 us for 32 frames of 1374 tokens).
-template <bool CUT>
+// CUT: also clears the words that the pieces of cut blocks meet at; FLAGS: and the flags of the online
+// kernel, n_flags (<= n_kt) per (sequence, head) pair, which took a launch of 2 us (kernels of their own:
+// behind a run-time test it cost every call 2 %, 42.8 -> 43.7 us for 32 frames of 1374 tokens).
+template <bool CUT, bool FLAGS>
 __global__ __launch_bounds__(256) void k_attn_pack(const uint16_t *__restrict__ k,
                                                    const uint16_t *__restrict__ v, int64_t n,
                                                    int heads, int n_kt, int qk_norm,
                                                    u32x4 *__restrict__ kp,
-                                                   u32x4 *__restrict__ vp, uint32_t *sync) {
+                                                   u32x4 *__restrict__ vp, uint32_t *sync,
+                                                   uint32_t *flags, int n_flags) {
   __shared__ __attribute__((aligned(16))) uint16_t vt[kKT][72];
   const int kt = blockIdx.x, t = threadIdx.x;
   if constexpr (CUT)
     if (blockIdx.x == 0 && blockIdx.y == 0)
       for (int i = t; i < kSyncWords; i += 256) sync[i] = 0u;
+  if constexpr (FLAGS)
+    if (t == 0 && kt < n_flags) flags[(size_t)blockIdx.y * n_flags + kt] = 0u;
   const int seq = blockIdx.y / heads, head = blockIdx.y - seq * heads;
   const int C = heads * 64;
   k += (size_t)seq * n * C;
@@ -960,6 +964,319 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 }
 
 // ---------------------------------------------------------------------------------------
+// Short sequences.  Blocks of 256 queries are few (394 tokens of 4 heads: 8) and each walks all keys
+// alone.  Here a workgroup has 64 queries and its four waves take a quarter of the keys each, every
+// wave as in the main kernel (two 32-query blocks half a step apart, the same weights and references);
+// a wave's K and V fragments come straight from L2 into its registers, a whole tile ahead of their
+// use: no wave reads what another one does, so there is no ring, and no barrier before the end.  There
+// the partial sums meet in LDS: wave w adds up quarter w of the output (query block w / 2, channels
+// 32 (w % 2) .. + 31) in pairs and stores it.  Bound by latency: kernel start, one round trip for
+// q, K and V each, a few tiles per wave (394 tokens of 4 heads, the call with its K/V re-layout, 14.1 ->
+// 9.8 us).  Eight waves with an eighth of the keys each gave nothing (9.8 -> 10.7; 4000 tokens 28.1 -> 28.5).
+// attn_is_short says where it is used.
+// ---------------------------------------------------------------------------------------
+constexpr int kShortWaves = 4;   // (sum4 below)
+template <bool ONLINE, bool PACKED>
+__global__ __launch_bounds__(64 * kShortWaves) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_attn_bf16_short(
+    const uint16_t *q, const u32x4 *__restrict__ kp, const u32x4 *__restrict__ vp, uint16_t *o,
+    const uint16_t *res, int64_t n, int heads, int n_seq, int n_kt, int nqs, float c, int qk_norm,
+    uint32_t *__restrict__ redo, int redo_stride) {
+  constexpr int WAVES = kShortWaves, R = 64 / WAVES;   // of a lane's 64 output registers (query block, channels 32 dt .., row) a
+                                             // wave adds up and stores R
+  __shared__ f32x4 part[WAVES][WAVES - 1][R / 4 * 64];   // [wave][whose registers, its own left out][group of 4][lane]
+  __shared__ f32x2 psum[WAVES][64];          // row sums of the two query blocks
+  __shared__ float pref[WAVES];              // ONLINE: the waves' references
+  __shared__ int any_low;
+  const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5, ql = lane & 31;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int C = heads * 64;
+  int sh, qs;   // (sequence, head) pair and 64-query block; each XCD gets whole pairs
+  if (((heads * n_seq) & 7) == 0) {
+    const int hp = (heads * n_seq) >> 3, xcd = blockIdx.x & 7, local = blockIdx.x >> 3;
+    sh = xcd * hp + local / nqs;
+    qs = local % nqs;
+  } else {
+    sh = blockIdx.x / nqs;
+    qs = blockIdx.x % nqs;
+  }
+  const int seq = sh / heads, head = sh - seq * heads;
+  q += (size_t)seq * n * C;
+  o += (size_t)seq * n * C;
+  if (res) res += (size_t)seq * n * C;
+  const int64_t q0 = (int64_t)qs * kQW;
+  const int nt = (int)((n + kKT - 1) / kKT);                       // tiles with keys in them
+  const int64_t pairs = (nt + 1) / 2;                              // a wave takes whole steps of its loop: two tiles
+  const int t0 = min(nt, 2 * (int)(pairs * wave / WAVES)), t1 = min(nt, 2 * (int)(pairs * (wave + 1) / WAVES));
+  const u32x4 *kh = kp + (size_t)sh * n_kt * 4 * kFragU4 + lane;
+  const u32x4 *vh = vp + (size_t)sh * n_kt * 4 * kFragU4 + lane;
+  auto load = [&](const u32x4 *from, int t, u32x4(&dst)[4]) {      // past the wave's last tile: that one again
+    const u32x4 *p = from + (size_t)min(t, t1 - 1) * 4 * kFragU4;
+#pragma unroll
+    for (int f = 0; f < 4; ++f) dst[f] = p[f * kFragU4];
+  };
+  u32x4 fv[2][4], fk[2][4];            // [tile & 1]
+  bf16x8 qf[2][4];
+  f32x16 oacc[2][2], sacc[2], s_start;
+  float lrow[2][2] = {{0.f, 0.f}, {0.f, 0.f}}, lnew[2] = {0.f, 0.f}, ref_run = ONLINE ? -INFINITY : 0.f;
+  bool over = false;
+  u32x4 pb[2][2];
+#pragma unroll
+  for (int sub = 0; sub < 2; ++sub)
+#pragma unroll
+    for (int dt = 0; dt < 2; ++dt)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) oacc[sub][dt][r] = 0.f;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) s_start[r] = 0.f;
+  if (ONLINE && tid == 0) any_low = 0;
+
+  auto mma_s = [&](int sub, const u32x4(&kf)[4]) {
+    f32x16 acc = s_start;
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, kf[s]), qf[sub][s], acc, 0, 0, 0);
+    sacc[sub] = acc;
+  };
+  auto mma_pv = [&](int sub, const u32x4(&vf)[4]) {
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+      for (int dt = 0; dt < 2; ++dt)
+        oacc[sub][dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, vf[u * 2 + dt]),
+                                                                __builtin_bit_cast(bf16x8, pb[sub][u]), oacc[sub][dt], 0, 0, 0);
+  };
+  auto mask_tail = [&](int t, int sub) {   // keys beyond the sequence end
+    const int left = (int)(n - (int64_t)t * kKT) - 4 * h;
+    if (left + 4 * h < kKT) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r)
+        if ((r >> 2) * 8 + (r & 3) >= left) sacc[sub][r] = -INFINITY;
+    }
+  };
+  auto weights = [&](int sub) {
+    float l0 = lrow[sub][0], l1 = lrow[sub][1];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      uint32_t w[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float p0 = __builtin_amdgcn_exp2f(sacc[sub][8 * u + 2 * e]);
+        const float p1 = __builtin_amdgcn_exp2f(sacc[sub][8 * u + 2 * e + 1]);
+        w[e] = pack_bf16(p0, p1);
+        l0 += p0;
+        l1 += p1;
+      }
+      pb[sub][u] = u32x4{w[0], w[1], w[2], w[3]};
+    }
+    lnew[0] = l0;
+    lnew[1] = l1;
+  };
+  // ONLINE: accept the new row sums, or raise the reference first (settle() of the main kernel)
+  auto settle = [&](int sub) {
+    if (ONLINE && __builtin_amdgcn_ballot_w64(!(lnew[0] + lnew[1] <= kSumRaise)) != 0) {
+      float mx = sacc[sub][0];
+#pragma unroll
+      for (int r = 1; r < 16; ++r) mx = fmaxf(mx, sacc[sub][r]);
+      const float delta = fmaxf(wave_max(mx), 0.f);
+      const float alpha = __builtin_amdgcn_exp2f(-delta);
+      ref_run += delta;
+      over |= !(ref_run <= kRefUseful);
+#pragma unroll
+      for (int b = 0; b < 2; ++b) {
+        lrow[b][0] *= alpha;
+        lrow[b][1] *= alpha;
+#pragma unroll
+        for (int dt = 0; dt < 2; ++dt)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) oacc[b][dt][r] *= alpha;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) sacc[b][r] -= delta;
+      }
+#pragma unroll
+      for (int r = 0; r < 16; ++r) s_start[r] = -ref_run;
+      weights(sub);
+    }
+    lrow[sub][0] = lnew[0];
+    lrow[sub][1] = lnew[1];
+  };
+
+  if (t0 < t1) {
+    load(kh, t0, fk[0]);
+    load(vh, t0, fv[0]);
+    load(kh, t0 + 1, fk[1]);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int sub = 0; sub < 2; ++sub) {      // q as in the main kernel
+      const int64_t row = min(q0 + sub * 32 + ql, n - 1);
+      const uint16_t *qp = q + (size_t)row * C + head * 64 + 8 * h;
+      u32x4 w[4];
+#pragma unroll
+      for (int s = 0; s < 4; ++s) w[s] = *(const u32x4 *)(qp + 16 * s);
+      float ss = (sumsq8(w[0]) + sumsq8(w[1])) + (sumsq8(w[2]) + sumsq8(w[3]));
+      ss += __shfl_xor(ss, 32, 64);
+      const float r = qk_norm ? c / sqrtf(ss * (1.0f / 64.0f) + kQkEps) : c;
+#pragma unroll
+      for (int s = 0; s < 4; ++s) qf[sub][s] = __builtin_bit_cast(bf16x8, scale8(w[s], r));
+    }
+    mma_s(0, fk[0]);
+    mma_s(1, fk[0]);
+    mask_tail(t0, 0);
+    mask_tail(t0, 1);
+    if (ONLINE) {
+      float mx = fmaxf(sacc[0][0], sacc[1][0]);
+#pragma unroll
+      for (int r = 1; r < 16; ++r) mx = fmaxf(mx, fmaxf(sacc[0][r], sacc[1][r]));
+      ref_run = wave_max(mx);
+      over = !(ref_run <= kRefUseful);
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        s_start[r] = -ref_run;
+        sacc[0][r] -= ref_run;
+        sacc[1][r] -= ref_run;
+      }
+    }
+    weights(0);
+    lrow[0][0] = lnew[0];
+    lrow[0][1] = lnew[1];
+    // B(t): weights of block 1, tile t || PV(t) and scores(t + 1) of block 0;  A(t + 1): weights of block 0,
+    // tile t + 1 || PV(t) and scores(t + 1) of block 1.  V(t + 1) and K(t + 2) are requested ahead of both.
+    auto tile = [&](int t, u32x4(&v)[4], u32x4(&v2)[4], u32x4(&k1)[4], u32x4(&k2)[4]) {
+      __builtin_amdgcn_sched_barrier(0);
+      load(vh, t + 1, v2);
+      load(kh, t + 2, k2);
+      __builtin_amdgcn_sched_barrier(0);
+      weights(1);
+      mma_pv(0, v);
+      mma_s(0, k1);
+      mask_tail(t + 1, 0);
+      settle(1);
+      weights(0);
+      mma_pv(1, v);
+      mma_s(1, k1);
+      mask_tail(t + 1, 1);
+      settle(0);
+    };
+    int t = t0;
+    for (; t + 2 < t1; t += 2) {
+      tile(t, fv[0], fv[1], fk[1], fk[0]);
+      tile(t + 1, fv[1], fv[0], fk[0], fk[1]);
+    }
+    if (t + 1 < t1) {
+      tile(t, fv[0], fv[1], fk[1], fk[0]);
+#pragma unroll
+      for (int f = 0; f < 4; ++f) fv[0][f] = fv[1][f];
+    }
+    weights(1);                              // the last tile
+    mma_pv(0, fv[0]);
+    settle(1);
+    mma_pv(1, fv[0]);
+  }
+
+  // ---- the four waves' sums meet
+  float lsub[2];
+#pragma unroll
+  for (int sub = 0; sub < 2; ++sub) {
+    const float l = lrow[sub][0] + lrow[sub][1];
+    lsub[sub] = l + __shfl_xor(l, 32, 64);
+  }
+#pragma unroll
+  for (int w = 0; w < WAVES; ++w)
+    if (w != wave) {
+      f32x4 *dst = part[wave][w < wave ? w : w - 1] + lane;
+#pragma unroll
+      for (int g = 0; g < R / 4; ++g) {
+        const int at = w * R + 4 * g;
+        const f32x16 &a = oacc[at >> 5][(at >> 4) & 1];
+        dst[g * 64] = f32x4{a[at & 15], a[(at & 15) + 1], a[(at & 15) + 2], a[(at & 15) + 3]};
+      }
+    }
+  psum[wave][lane] = f32x2{lsub[0], lsub[1]};
+  if (ONLINE && lane == 0) pref[wave] = over ? __builtin_nanf("") : ref_run;
+  __syncthreads();
+  float scale[WAVES];
+  bool low = false;
+  if (ONLINE) {
+    float top = -INFINITY;
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w) {
+      low |= pref[w] != pref[w];             // a reference that does not serve
+      top = fmaxf(top, pref[w]);
+    }
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w) scale[w] = __builtin_amdgcn_exp2f(pref[w] - top);
+  }
+  const int sub = wave * R >> 5, dt = (wave * R >> 4) & 1, r0 = wave * R & 15;
+  const int64_t row = q0 + sub * 32 + ql;
+  const bool live = row < n;
+  float own[R], l = 0.f;
+#pragma unroll
+  for (int w = 0; w < WAVES; ++w)            // (wave is uniform: one copy runs)
+    if (w == wave)
+#pragma unroll
+      for (int r = 0; r < R; ++r) own[r] = oacc[(w * R + r) >> 5][((w * R + r) >> 4) & 1][(w * R + r) & 15];
+  float acc[R], lw[WAVES];
+  auto sum4 = [&](const float (&x)[WAVES]) {   // neighbours first, whoever adds
+    return ONLINE ? (x[0] * scale[0] + x[1] * scale[1]) + (x[2] * scale[2] + x[3] * scale[3]) : (x[0] + x[1]) + (x[2] + x[3]);
+  };
+#pragma unroll
+  for (int w = 0; w < WAVES; ++w) lw[w] = psum[w][lane][sub];
+  l = sum4(lw);
+#pragma unroll
+  for (int g = 0; g < R / 4; ++g) {
+    f32x4 v[WAVES];
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w) v[w] = part[w][w == wave ? 0 : wave < w ? wave : wave - 1][g * 64 + lane];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      float x[WAVES];
+#pragma unroll
+      for (int w = 0; w < WAVES; ++w) x[w] = w == wave ? own[4 * g + i] : v[w][i];
+      acc[4 * g + i] = sum4(x);
+    }
+  }
+  if (ONLINE) {                              // as in the main kernel: rows lost to underflow go to the second pass
+    low |= live && !(l >= 8.67e-19f);        // 2^-60
+    if (__builtin_amdgcn_ballot_w64(low) != 0 && lane == 0) any_low = 1;
+    __syncthreads();
+    if (any_low != 0) {
+      if (tid == 0) redo[(size_t)sh * redo_stride + (q0 / kBQB)] = 1u;
+      return;
+    }
+  }
+  const float inv = live ? 1.0f / l : 0.f;
+  if constexpr (PACKED) {
+    u32x4 *op = (u32x4 *)o + ((size_t)((q0 + sub * 32) >> 5) * (C >> 4) + head * 4 + dt * 2 + (r0 >> 3)) * 64 + lane;
+#pragma unroll
+    for (int gp = 0; gp < R / 8; ++gp) {
+      float r[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) r[i] = live ? acc[8 * gp + i] * inv : 0.f;
+      const auto s0 = __builtin_amdgcn_permlane32_swap(pack_bf16(r[0], r[1]), pack_bf16(r[4], r[5]), false, false);
+      const auto s1 = __builtin_amdgcn_permlane32_swap(pack_bf16(r[2], r[3]), pack_bf16(r[6], r[7]), false, false);
+      op[gp * 64] = u32x4{s0[0], s1[0], s0[1], s1[1]};
+    }
+    return;
+  }
+  if (live) {
+    const size_t at = (size_t)row * C + head * 64 + 32 * dt + 2 * r0 + 4 * h;
+#pragma unroll
+    for (int g = 0; g < R / 4; ++g) {
+      float r[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) r[i] = acc[4 * g + i] * inv;
+      if (res) {   // out = res + attention, one rounding
+        const u32x2 x = *(const u32x2 *)(res + at + 8 * g);
+        r[0] += bf16_lo(x.x);
+        r[1] += bf16_hi(x.x);
+        r[2] += bf16_lo(x.y);
+        r[3] += bf16_hi(x.y);
+      }
+      *(u32x2 *)(o + at + 8 * g) = u32x2{pack_bf16(r[0], r[1]), pack_bf16(r[2], r[3])};
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------------------
 // FP8 (E4M3, OCP "fn": bias 7, max 448) variant: q, k, v are quantised per tensor with
 // scale = amax/448 taken in the same call, the softmax weights with a fixed scale 2^8; the
 // MFMAs are v_mfma_f32_32x32x64_f8f6f4, everything else (scores, max, sums, O) stays fp32.
@@ -1635,6 +1952,19 @@ static size_t cut_bytes(int heads, int64_t n, int n_seq) {
   return c.n_cut ? kSyncWords * sizeof(uint32_t) + align_up((size_t)kXcd * c.n_cut * kPieceFloats * sizeof(float), 256) : 0;
 }
 
+// Whether the blocks of 64 queries (k_attn_bf16_short) are used: as long as all of them are on the chip at once,
+// two per CU.  One call, otherwise against this way, us: 16 heads with q, k normalised 394 tokens 14.6 and
+// 10.9, 700 18.3 and 11.8, 1024 (256 blocks) 22.1 and 13.5, 2000 (512) 32.8 and 28.3, 2500 (640) 45.3 and
+// 43.5, 4000 (1008) 73.2 and 83.6; 4 heads, which are never cut, 4000 tokens 59.6 and 28.2, 8190 (512) 107.5 and 76.9, 9000 119 and
+// 112; 2 frames of 37 x 37 of 8 heads (352) 30.0 and 20.8.  The online kernel's steady loop is the slower one here
+// (its references are registers the loop would need): where its blocks can be cut, only up to one
+// per CU (8 heads: 2000 tokens 31.5 and 26.1, 3000 39.4 and 39.6, 4000 48.9 and 51.0).  A block that it leaves to
+// the second pass has sisters that are stored by then: not with a residual, which may be added in place.
+static bool attn_is_short(int64_t blocks, bool bounded, bool can_be_cut, bool has_res, int n_cu) {
+  if (!bounded && has_res) return false;
+  return blocks <= (bounded || !can_be_cut ? 2 * n_cu : n_cu);
+}
+
 size_t attn_ws_bytes(int heads, int64_t n_tokens, int attn_dtype, int n_seq, bool least) {
   const size_t elem = attn_dtype == LV_ATTN_FP8_E4M3 ? sizeof(u32x2) : sizeof(u32x4);
   const size_t per = (size_t)heads * n_seq * n_key_tiles(n_tokens) * 4 * kFragU4 * elem;
@@ -1707,22 +2037,26 @@ int launch_attn(const uint16_t *q, const uint16_t *k, const uint16_t *v, uint16_
   const bool bounded = qk_norm && 64.25f * c <= 64.0f;
   uint32_t *redo = (uint32_t *)(frag + 2 * per);
   const size_t words = fp8_flag_words(heads * n_seq, n);
-  if (!bounded)
-    hipLaunchKernelGGL(k_zero_words, dim3((unsigned)((words + 255) / 256)), dim3(256), 0, st, redo, words,
-                       (uint32_t *)nullptr);
   const int nqb2 = (int)((n + kBQB - 1) / kBQB);
   int dev = 0, n_cu = 0;
   if (hipGetDevice(&dev) != hipSuccess ||
       hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
     return LV_ERR_HIP;
+  const int nqs = (int)((n + kQW - 1) / kQW);
+  const bool is_short = attn_is_short((int64_t)nqs * heads * n_seq, bounded, n_seq == 1 && heads % kXcd == 0, res != nullptr, n_cu);
   AttnCut cut = {0, 0};
-  if (n_seq == 1 && !res && 2 * n_cu == kXcd * kSlots && ws_bytes >= attn_ws_bytes(heads, n, attn_dtype))
+  if (!is_short && n_seq == 1 && !res && 2 * n_cu == kXcd * kSlots && ws_bytes >= attn_ws_bytes(heads, n, attn_dtype))
     cut = attn_cut(heads, n, bounded);
   uint32_t *sync = redo + align_up(words * 4, 256) / 4;
   float *partial = (float *)(sync + kSyncWords);
   auto pack_kernel = [&](auto is_cut) {
-    hipLaunchKernelGGL(k_attn_pack<decltype(is_cut)::value>, dim3((unsigned)n_kt, (unsigned)(heads * n_seq)), dim3(256), 0, st,
-                       k, v, n, heads, n_kt, qk_norm, kp, vp, sync);
+    constexpr bool CUT = decltype(is_cut)::value;
+    const dim3 grid((unsigned)n_kt, (unsigned)(heads * n_seq));
+    if (bounded)
+      hipLaunchKernelGGL((k_attn_pack<CUT, false>), grid, dim3(256), 0, st, k, v, n, heads, n_kt, qk_norm, kp, vp, sync, redo, 0);
+    else
+      hipLaunchKernelGGL((k_attn_pack<CUT, true>), grid, dim3(256), 0, st, k, v, n, heads, n_kt, qk_norm, kp, vp, sync, redo,
+                         2 * nqb);
   };
   if (cut.n_cut) pack_kernel(std::true_type{});
   else pack_kernel(std::false_type{});
@@ -1731,7 +2065,10 @@ int launch_attn(const uint16_t *q, const uint16_t *k, const uint16_t *v, uint16_
     constexpr bool ON = decltype(online)::value, PK = decltype(packed)::value;
     uint32_t *const flags = ON ? redo : nullptr;
     const int stride = ON ? 2 * nqb : 0;
-    if (cut.n_cut)
+    if (is_short)
+      hipLaunchKernelGGL((k_attn_bf16_short<ON, PK>), dim3((unsigned)(nqs * heads * n_seq)), dim3(256), 0, st, q, kp, vp, out,
+                         res, n, heads, n_seq, n_kt, nqs, c, qk_norm, flags, stride);
+    else if (cut.n_cut)
       hipLaunchKernelGGL((k_attn_bf16_cut<ON, PK>), dim3((unsigned)(kXcd * 2 * cut.n_cut)), dim3(256), 0, st, q, kp, vp, out,
                          n, heads, n_kt, nqb2, c, qk_norm, flags, stride, cut, sync, partial);
     else

@@ -568,3 +568,82 @@ def test_layers_in_one_pass_equal_the_single_steps(B, frames, h, w, special, rat
     torch.cuda.synchronize()
     assert torch.equal(got.view(torch.int16), want.view(torch.int16))
     assert not still or largest > 64
+
+
+# ------------------------------------------------------------------------------- short sequences, attention
+# 64-query blocks whose waves share the keys out: waves without a key tile (1 to 96 tokens), the last tile
+# with one key, whole tiles, one tile more for one wave, the most blocks that are taken this way and one
+# token more (16 heads: 2048 normalised, 1024 as given; 4 and 12 heads, never cut: 8192 and 2688)
+@pytest.mark.parametrize("n,heads", [(1, 4), (31, 1), (32, 8), (33, 4), (64, 16), (65, 3), (96, 8), (97, 4), (129, 4), (394, 4),
+                                     (522, 4), (1024, 16), (1025, 16), (2048, 16), (2049, 16), (2688, 12), (2689, 12),
+                                     (8192, 4), (8193, 4)])
+@pytest.mark.parametrize("kind", ["norm", "plain", "climbing", "falling"])
+def test_attention_short_sequences(B, n, heads, kind):
+    import torch
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n)
+    q, k, v = (torch.randn(n, heads * 64, generator=g, device="cuda") for _ in range(3))
+    if kind in ("climbing", "falling"):   # every wave's keys have a reference of their own
+        ramp = torch.linspace(0.1, 6.0, n, device="cuda")[:, None]
+        k *= ramp if kind == "climbing" else ramp.flip(0)
+    q, k, v = (t.to(torch.bfloat16) for t in (q, k, v))
+    ph = B.make_params(1, 1, 1, heads * 64, heads, n_special=0, qk_norm=int(kind == "norm"))
+    ws = B.alloc_ws(B.litevggt_attn_ws_bytes(ph, n))
+    ws.fill_(0x7f)                        # flags are cleared by the call
+    o, again = torch.full_like(q, float("nan")), torch.full_like(q, float("nan"))
+    B.litevggt_global_attn(ph, n, q, k, v, o, ws)
+    B.litevggt_global_attn(ph, n, q, k, v, again, ws)
+    torch.cuda.synchronize()
+    ref = _attn64(q, k, v, kind == "norm", heads)
+    assert float((o.double() - ref).abs().max() / ref.abs().max()) <= 2e-2
+    assert torch.equal(o, again)
+
+
+# queries along long keys: references beyond what serves in one wave's keys or another's, rows far below their
+# wave's reference, in the first, a middle and the last 64-query block of a 256-query flag and across two flags
+@pytest.mark.parametrize("n,heads", [(700, 8), (394, 4)])
+def test_attention_short_blocks_left_to_the_second_pass(B, n, heads):
+    import torch
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n)
+    q, k, v = (torch.randn(n, heads, 64, generator=g, device="cuda") for _ in range(3))
+    q[:, :, 0] = k[:, :, 0] = 0.0
+    spots = [(5, 3, 360), (n - 1, 70, 120), (n // 2, 255, 360), (7, n - 1, 30), (n // 3, 256, 20)]   # key, query, binades
+    for h in range(heads):
+        for key, query, binades in spots[h % 4:h % 4 + 2]:
+            q[query, h, 0] = 32.0
+            k[key, h, 0] = binades * np.log(2.0) / (32.0 * 0.125)
+    q, k, v = (t.reshape(n, heads * 64).to(torch.bfloat16) for t in (q, k, v))
+    ph = B.make_params(1, 1, 1, heads * 64, heads, n_special=0)
+    need = B.litevggt_attn_ws_bytes(ph, n)
+    ws = B.alloc_ws(need)
+    o = torch.full_like(q, float("nan"))
+    B.litevggt_global_attn(ph, n, q, k, v, o, ws)
+    torch.cuda.synchronize()
+    ref = _attn64(q, k, v, False, heads)
+    assert float((o.double() - ref).abs().max() / ref.abs().max()) <= 2e-2
+    nqb, stride, nkv = (n + 255) // 256, 2 * ((n + 511) // 512), (n + 63) // 64
+    base = (ws.data_ptr() + 255) // 256 * 256 - ws.data_ptr() + 256 + 2 * ((heads * 2 * nkv * 4 * 64 * 16 + 255) // 256 * 256)
+    flags = ws[base:base + heads * stride * 4].cpu().numpy().view(np.uint32).reshape(heads, stride)[:, :nqb]
+    want = np.zeros((heads, nqb), bool)
+    for h in range(heads):
+        for _, query, _ in spots[h % 4:h % 4 + 2]:      # a query meets both keys of its head
+            want[h, query // 256] |= max(b for _, _, b in spots[h % 4:h % 4 + 2]) > 60
+    assert np.array_equal(flags != 0, want)
+
+
+# frames of a few hundred tokens with the residual added in place, in 64-query blocks and one frame beyond
+@pytest.mark.parametrize("frames,h,w,heads,norm", [(2, 16, 16, 4, 1), (25, 15, 17, 4, 1), (26, 15, 17, 4, 1), (2, 37, 37, 8, 1),
+                                                   (2, 5, 5, 1, 0)])
+def test_frame_attention_short_frames_in_place(B, frames, h, w, heads, norm):
+    import torch
+    n = h * w + 5
+    g = torch.Generator(device="cuda")
+    g.manual_seed(frames)
+    x = torch.randn(frames * n, heads * 64, generator=g, device="cuda").to(torch.bfloat16)
+    ph = B.make_params(frames, h, w, heads * 64, heads, qk_norm=norm)
+    got = x.clone()
+    B.litevggt_frame_attn(ph, got, got, got, got, got, B.alloc_ws(B.litevggt_frame_attn_ws_bytes(ph)))
+    torch.cuda.synchronize()
+    ref = torch.cat([f.double() + _attn64(f, f, f, norm, heads) for f in x.reshape(frames, n, -1)])
+    assert float((got.double() - ref).abs().max() / ref.abs().max()) <= 2e-2
