@@ -56,21 +56,21 @@ __device__ __forceinline__ u32x4 rms_scale8(const u32x4 w, int log2_lanes) {
 //      the S^T accumulator holds its rows, so P needs no shuffle before the second MFMA)
 // With several sequences of n tokens each in one call (frame attention: one per frame) the
 // second grid dimension runs over (sequence, head) pairs and so do the packed arrays.
-// CUT: also clears the words that the pieces of cut blocks meet at; FLAGS: and the flags of the online
+// SYNC: also clears the words that workgroups meet at (pieces of cut blocks, the next blocks' counters); FLAGS: and the flags of the online
 // kernel, n_flags (<= n_kt) per (sequence, head) pair, which took a launch of 2 us (kernels of their own:
 // behind a run-time test it cost every call 2 %, 42.8 -> 43.7 us for 32 frames of 1374 tokens).
-template <bool CUT, bool FLAGS>
+template <bool SYNC, bool FLAGS>
 __global__ __launch_bounds__(256) void k_attn_pack(const uint16_t *__restrict__ k,
                                                    const uint16_t *__restrict__ v, int64_t n,
                                                    int heads, int n_kt, int qk_norm,
                                                    u32x4 *__restrict__ kp,
-                                                   u32x4 *__restrict__ vp, uint32_t *sync,
+                                                   u32x4 *__restrict__ vp, uint32_t *sync, int n_sync,
                                                    uint32_t *flags, int n_flags) {
   __shared__ __attribute__((aligned(16))) uint16_t vt[kKT][72];
   const int kt = blockIdx.x, t = threadIdx.x;
-  if constexpr (CUT)
+  if constexpr (SYNC)
     if (blockIdx.x == 0 && blockIdx.y == 0)
-      for (int i = t; i < kSyncWords; i += 256) sync[i] = 0u;
+      for (int i = t; i < n_sync; i += 256) sync[i] = 0u;
   if constexpr (FLAGS)
     if (t == 0 && kt < n_flags) flags[(size_t)blockIdx.y * n_flags + kt] = 0u;
   const int seq = blockIdx.y / heads, head = blockIdx.y - seq * heads;
@@ -961,6 +961,347 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     uint32_t *__restrict__ redo, int redo_stride, AttnCut cut, uint32_t *sync, float *partial) {
   attn_bf16_main<ONLINE, PACKED, true>(q, kp, vp, o, nullptr, n, heads, 1, n_kt, nqb, c, qk_norm, redo, redo_stride, cut,
                                        sync, partial);
+}
+
+// ---------------------------------------------------------------------------------------
+// More blocks than the chip holds at once.  The main kernel's loop without a running reference, in
+// workgroups that stay: one per slot of the chip takes block after block, and the seam between two blocks is part of
+// the stream.  The next block's number comes from a counter per XCD; its first two K/V stages are fetched during
+// the last two of this one, into the ring as if they followed them; its q rows and this block's
+// residual rows are requested while the last weights are taken: neither a workgroup start nor a round trip
+// to memory stands between them, and the other workgroup of the CU has less time to run alone in.  K/V
+// stages, slots and phases as in attn_bf16_main (the scores' MFMAs stand first in a phase's source, or the
+// scheduler leaves them to the phase's end: 3 % in long sequences).  Bound like the main kernel by the MFMA and VALU issue of the loop.
+// One launch per block -> this: frame attention, 16 heads, 100 frames of 37 x 37 943 -> 911 us, 50 of 28 x 37 321 ->
+// 307, 200 of 16 x 16 261 -> 209; one sequence of 9000 tokens 348 -> 333, 15432 821 -> 802, 60000 11685 -> 11632.
+// ---------------------------------------------------------------------------------------
+constexpr int kStreamStages = 4;     // key stages of a sequence, at least
+constexpr int kStreamMost = 1024;    // ... and at most (65,536 keys): the seam is nothing beside a longer block (100,000
+                                     // tokens level, 143,232 level on one box and 3 % slower on another)
+constexpr int kStreamWords = 8 * 8;  // counters: one per XCD, 32 bytes apart
+
+template <bool PACKED, bool RES>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_attn_bf16_stream(
+    const uint16_t *q, const u32x4 *__restrict__ kp, const u32x4 *__restrict__ vp, uint16_t *o,
+    const uint16_t *res, int64_t n, int heads, int n_seq, int n_kt, int nqb, float c, int qk_norm, uint32_t *ctr) {
+  __shared__ u32x4 ks[kBStages][8 * kFragU4];
+  __shared__ u32x4 vs[kBStages][8 * kFragU4];
+  __shared__ int next_block;
+  const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5, ql = lane & 31;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int C = heads * 64, nkv = n_kt >> 1, nkt = n_kt;
+  // each XCD's list: the blocks of its (sequence, head) pairs; else one list for all
+  const int pairs = heads * n_seq, lists = (pairs & 7) == 0 ? 8 : 1, list = lists == 8 ? blockIdx.x & 7 : 0;
+  const int in_list = pairs / lists * nqb, slots = gridDim.x / lists;
+  int blk = lists == 8 ? blockIdx.x >> 3 : blockIdx.x;
+
+  int sh = 0, qb = 0;
+  const u32x4 *kh, *vh;
+  auto place = [&](int b) {          // block b of the list: its pair, query block and packed K and V
+    sh = list * (pairs / lists) + b / nqb;
+    qb = b % nqb;
+    kh = kp + (size_t)sh * n_kt * 4 * kFragU4 + tid;
+    vh = vp + (size_t)sh * n_kt * 4 * kFragU4 + tid;
+  };
+  int base = 0;                      // ring slot of the block's stage 0
+  int fslot = 0;
+  size_t foff = 0;
+  auto fetch1 = [&](int part) {      // one of the four fetch instructions of a stage
+    const u32x4 *src = (part < 2 ? kh : vh) + foff + (part & 1) * 256;
+    u32x4 *dst = (part < 2 ? &ks[fslot][0] : &vs[fslot][0]) + (part & 1) * 256 + wave * 64;
+    __builtin_amdgcn_global_load_lds(src, dst, 16, 0, 0);
+  };
+  auto at_stage = [&](int src, int ring) {
+    fslot = (base + ring) & (kBStages - 1);
+    foff = (size_t)src * 8 * kFragU4;
+  };
+  auto fetch = [&](int stage) {
+    at_stage(stage, stage);
+    fetch1(0);
+    fetch1(1);
+    fetch1(2);
+    fetch1(3);
+  };
+  u32x4 qraw[2][4];
+  auto load_q = [&]() {
+    const int seq = sh / heads, head = sh - seq * heads;
+#pragma unroll
+    for (int sub = 0; sub < 2; ++sub) {
+      const int64_t row = (int64_t)seq * n + min((int64_t)qb * kBQB + wave * kQW + sub * 32 + ql, n - 1);
+      const uint16_t *qp = q + (size_t)row * C + head * 64 + 8 * h;
+#pragma unroll
+      for (int s = 0; s < 4; ++s) qraw[sub][s] = *(const u32x4 *)(qp + 16 * s);
+    }
+  };
+
+  bf16x8 qf[2][4];
+  f32x16 oacc[2][2], sacc[2];
+  float lrow[2][2];
+  u32x4 pb[2][2], fv[2][4], fk[2][4];
+  const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  auto mma_s = [&](int sub, const u32x4(&kf)[4]) {
+    f32x16 acc = zero;
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, kf[s]), qf[sub][s], acc, 0, 0, 0);
+    sacc[sub] = acc;
+  };
+  auto mma_pv = [&](int sub, const u32x4(&vf)[4]) {
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+      for (int dt = 0; dt < 2; ++dt)
+        oacc[sub][dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, vf[u * 2 + dt]),
+                                                                __builtin_bit_cast(bf16x8, pb[sub][u]), oacc[sub][dt], 0, 0, 0);
+  };
+  const int n_last = (int)(n - (int64_t)(nkv - 1) * kKV) - 4 * h;   // keys of the last stage, from this lane half's first row
+  auto mask_tail = [&](int tile, int sub) {                         // tile 0, 1 of the last stage
+#pragma unroll
+    for (int r = 0; r < 16; ++r)
+      if (tile * kKT + (r >> 2) * 8 + (r & 3) >= n_last) sacc[sub][r] = -INFINITY;
+  };
+  auto weights = [&](int sub) {
+    float l0 = lrow[sub][0], l1 = lrow[sub][1];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      uint32_t w[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float p0 = __builtin_amdgcn_exp2f(sacc[sub][8 * u + 2 * e]);
+        const float p1 = __builtin_amdgcn_exp2f(sacc[sub][8 * u + 2 * e + 1]);
+        w[e] = pack_bf16(p0, p1);
+        l0 += p0;
+        l1 += p1;
+      }
+      pb[sub][u] = u32x4{w[0], w[1], w[2], w[3]};
+    }
+    lrow[sub][0] = l0;
+    lrow[sub][1] = l1;
+  };
+  auto recipe = [&]() {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      __builtin_amdgcn_sched_group_barrier(0x400, 2, 0);   // 2 exp2
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);   // 1 MFMA
+      __builtin_amdgcn_sched_group_barrier(0x002, 3, 0);   // pack + 2 adds
+    }
+  };
+  const uint32_t ks_lane = lds_addr(&ks[0][lane]), vs_lane = lds_addr(&vs[0][lane]);
+  auto frag_off = [&](int t) {   // byte offset of tile t's four fragments in a ring array
+    return (uint32_t)(((((t >> 1) + base) & (kBStages - 1)) * 8 + (t & 1) * 4) * kFragU4 * 16);
+  };
+  auto phase_a = [&](int t, const u32x4(&v_prev)[4], u32x4(&v_cur)[4], const u32x4(&k_cur)[4], u32x4(&k_next)[4],
+                     int fq = -1) {
+    lds_read4_async(v_cur, vs_lane + frag_off(t));
+    lds_read4_async(k_next, ks_lane + frag_off(t + 1));   // past the last tile: a slot that may be arriving, never used
+    if (fq >= 0) fetch1(fq);
+    __builtin_amdgcn_sched_barrier(0);
+    mma_s(1, k_cur);
+    weights(0);
+    mma_pv(1, v_prev);
+    recipe();
+  };
+  auto phase_b = [&](u32x4(&v_cur)[4], u32x4(&k_next)[4], int fq = -1) {
+    __builtin_amdgcn_sched_barrier(0);
+    lds_wait(v_cur, k_next);
+    if (fq >= 0) {
+      fetch1(fq);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    mma_s(0, k_next);
+    weights(1);
+    mma_pv(0, v_cur);
+    recipe();
+  };
+  // outside the loop: the row sums are taken where they stand (else the additions are moved to the
+  // end of the block and the weights that wait for them to scratch)
+  auto pin = [&]() { asm volatile("" : "+v"(lrow[0][0]), "+v"(lrow[0][1]), "+v"(lrow[1][0]), "+v"(lrow[1][1])); };
+  // this wave's part of the stage after the next has landed (all but the newest fetches); after the barrier all of it
+  auto publish = [&](auto newest) {
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(decltype(newest)::value) : "memory");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  // When the next block's number is asked for: where the last round fills no more than half of the slots, at a
+  // block's first stage, in the order in which the slots were filled, one per CU before two, so that its blocks
+  // have a CU to themselves (it is worth 1.5 times the rate); else as late as the answer can be waited for, so
+  // that who is ahead takes it.  16 heads, in one launch per block, early, late: 17000 tokens (2.09 rounds)
+  // 1098 1088 1126 us, 13500 (1.66) 691 705 664, 30000 (3.69) 3076 3105 3021.
+  const int claim_at = in_list % slots * 2 <= slots ? 0 : nkv - kStreamStages;
+  bool more = true;
+  auto turn = [&]() {      // the workgroup's next block (or none: this one's stages again, into slots nobody reads)
+    int nb;
+    asm volatile("ds_read_b32 %0, %1\n\ts_waitcnt lgkmcnt(0)" : "=&v"(nb) : "v"(lds_addr(&next_block)) : "memory");
+    nb = __builtin_amdgcn_readfirstlane(nb);
+    more = nb < in_list;
+    if (more) blk = nb;
+    place(blk);
+  };
+
+  place(blk);
+  fetch(0);
+  fetch(1);
+  load_q();
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  while (true) {
+    const int64_t q0 = (int64_t)qb * kBQB + wave * kQW;
+    const int seq = sh / heads, head = sh - seq * heads;
+    uint16_t *const ob = o + (size_t)seq * n * C;
+    const uint16_t *const rb = RES ? res + (size_t)seq * n * C : nullptr;
+#pragma unroll
+    for (int sub = 0; sub < 2; ++sub) {
+      float ss = (sumsq8(qraw[sub][0]) + sumsq8(qraw[sub][1])) + (sumsq8(qraw[sub][2]) + sumsq8(qraw[sub][3]));
+      ss += __shfl_xor(ss, 32, 64);
+      const float r = qk_norm ? c / sqrtf(ss * (1.0f / 64.0f) + kQkEps) : c;
+#pragma unroll
+      for (int s = 0; s < 4; ++s) qf[sub][s] = __builtin_bit_cast(bf16x8, scale8(qraw[sub][s], r));
+#pragma unroll
+      for (int dt = 0; dt < 2; ++dt) oacc[sub][dt] = zero;
+      lrow[sub][0] = lrow[sub][1] = 0.f;
+    }
+    // stages 0 and 1 were requested ahead of q (and the last block's stores, eight at most, after it):
+    // this wave's parts have landed; after the barrier all of them, and nobody reads the last block's any more
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+    fetch(2);
+    if (q0 >= n) {
+      // no queries: the wave only moves its share of the stages
+      for (int i = 0; i < nkv - 3; ++i) {
+        at_stage(i + 3, i + 3);
+        fetch1(0);
+        fetch1(1);
+        fetch1(2);
+        publish(std::integral_constant<int, 3>{});
+        fetch1(3);
+      }
+      publish(std::integral_constant<int, 0>{});
+      turn();
+      for (int i = 0; i < 2; ++i) {
+        at_stage(i, nkv + i);
+        fetch1(0);
+        fetch1(1);
+        fetch1(2);
+        fetch1(3);
+      }
+      load_q();
+    } else {
+      lds_read4_async(fk[0], ks_lane + frag_off(0));
+      lds_read4_async(fv[0], vs_lane + frag_off(0));
+      lds_wait(fk[0], fv[0]);
+      lds_read4_async(fk[1], ks_lane + frag_off(1));
+      mma_s(0, fk[0]);
+      weights(0);
+      mma_s(1, fk[0]);
+      pin();
+      uint32_t taken = 0u;
+#pragma unroll 1
+      for (int i = 0; i < nkv - 3; ++i) {
+        if (i == claim_at && tid == 0)
+          taken = __hip_atomic_fetch_add(ctr + list * 8, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        int st = i + 3;
+        asm volatile("" : "+s"(st));   // (addresses from the stage number, not carried along: the recipe counts their arithmetic)
+        at_stage(st, st);
+        phase_b(fv[0], fk[1], 0);                           // B(2i)
+        phase_a(2 * i + 1, fv[0], fv[1], fk[1], fk[0], 1);  // A(2i+1)
+        phase_b(fv[1], fk[0], 2);                           // B(2i+1)
+        publish(std::integral_constant<int, 3>{});
+        phase_a(2 * i + 2, fv[1], fv[0], fk[0], fk[1], 3);  // A(2i+2)
+      }
+      if (tid == 0) next_block = slots + (int)taken;        // (wave 0 always has queries)
+      phase_b(fv[0], fk[1]);                                // stage nkv - 3: nothing of this block is left to fetch
+      pin();
+      phase_a(nkt - 5, fv[0], fv[1], fk[1], fk[0]);
+      pin();
+      phase_b(fv[1], fk[0]);
+      pin();
+      publish(std::integral_constant<int, 0>{});
+      phase_a(nkt - 4, fv[1], fv[0], fk[0], fk[1]);
+      pin();
+      lds_wait(fv[0], fk[1]);
+      turn();                                               // from here on the next block's stages 0 and 1 are fetched
+      at_stage(0, nkv);
+      phase_b(fv[0], fk[1], 0);
+      pin();
+      phase_a(nkt - 3, fv[0], fv[1], fk[1], fk[0], 1);
+      pin();
+      phase_b(fv[1], fk[0], 2);
+      pin();
+      if (n_last + 4 * h < kKV) mask_tail(0, 0);
+      phase_a(nkt - 2, fv[1], fv[0], fk[0], fk[1], 3);
+      pin();
+      if (n_last + 4 * h < kKV) mask_tail(0, 1);
+      at_stage(1, nkv + 1);
+      phase_b(fv[0], fk[1], 0);
+      fetch1(1);
+      pin();
+      if (n_last + 4 * h < kKV) mask_tail(1, 0);
+      phase_a(nkt - 1, fv[0], fv[1], fk[1], fk[0], 2);
+      fetch1(3);
+      pin();
+      if (n_last + 4 * h < kKV) mask_tail(1, 1);
+      lds_wait(fv[1], fk[0]);
+      weights(1);
+      pin();
+      // this block's residual rows and the next block's q rows, in the registers of the fragments and scores
+      __builtin_amdgcn_sched_barrier(0);
+      u32x4 rw[2][4];
+      if constexpr (RES) {
+#pragma unroll
+        for (int sub = 0; sub < 2; ++sub) {
+          const int64_t row = min(q0 + sub * 32 + ql, n - 1);
+#pragma unroll
+          for (int i = 0; i < 4; ++i) rw[sub][i] = *(const u32x4 *)(rb + (size_t)row * C + head * 64 + 16 * i + 8 * h);
+        }
+      }
+      load_q();
+      __builtin_amdgcn_sched_barrier(0);
+      mma_pv(0, fv[1]);
+      mma_pv(1, fv[1]);
+      // lanes l and l + 32 trade halves: lane l then has channels 0-7, lane l + 32 channels 8-15 of 16
+#pragma unroll
+      for (int sub = 0; sub < 2; ++sub) {
+        float l = lrow[sub][0] + lrow[sub][1];
+        l += __shfl_xor(l, 32, 64);
+        const int64_t row = q0 + sub * 32 + ql;
+        const bool live = row < n;
+        const float inv = PACKED && !live ? 0.f : 1.0f / l;
+#pragma unroll
+        for (int dt = 0; dt < 2; ++dt)
+#pragma unroll
+          for (int gp = 0; gp < 2; ++gp) {
+            float r[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) r[i] = PACKED && !live ? 0.f : oacc[sub][dt][8 * gp + i] * inv;
+            if constexpr (RES) {   // out = res + attention, one rounding: halves traded the other way first
+              const u32x4 x = rw[sub][dt * 2 + gp];
+              const auto a = __builtin_amdgcn_permlane32_swap(x.x, x.z, false, false);
+              const auto b = __builtin_amdgcn_permlane32_swap(x.y, x.w, false, false);
+              r[0] += bf16_lo(a[0]);
+              r[1] += bf16_hi(a[0]);
+              r[2] += bf16_lo(b[0]);
+              r[3] += bf16_hi(b[0]);
+              r[4] += bf16_lo(a[1]);
+              r[5] += bf16_hi(a[1]);
+              r[6] += bf16_lo(b[1]);
+              r[7] += bf16_hi(b[1]);
+            }
+            const auto s0 = __builtin_amdgcn_permlane32_swap(pack_bf16(r[0], r[1]), pack_bf16(r[4], r[5]), false, false);
+            const auto s1 = __builtin_amdgcn_permlane32_swap(pack_bf16(r[2], r[3]), pack_bf16(r[6], r[7]), false, false);
+            const u32x4 w = u32x4{s0[0], s1[0], s0[1], s1[1]};
+            if constexpr (PACKED)
+              ((u32x4 *)o)[((size_t)((q0 + sub * 32) >> 5) * (C >> 4) + head * 4 + dt * 2 + gp) * 64 + lane] = w;
+            else if (live)
+              *(u32x4 *)(ob + (size_t)row * C + head * 64 + 32 * dt + 16 * gp + 8 * h) = w;
+          }
+      }
+    }
+    base = (base + nkv) & (kBStages - 1);
+    if (!more) break;
+  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // nothing may land after the workgroup ends
 }
 
 // ---------------------------------------------------------------------------------------
@@ -2049,16 +2390,25 @@ int launch_attn(const uint16_t *q, const uint16_t *k, const uint16_t *v, uint16_
     cut = attn_cut(heads, n, bounded);
   uint32_t *sync = redo + align_up(words * 4, 256) / 4;
   float *partial = (float *)(sync + kSyncWords);
-  auto pack_kernel = [&](auto is_cut) {
-    constexpr bool CUT = decltype(is_cut)::value;
+  // more blocks than slots: workgroups that stay (their rows are written and the residual's read 16 bytes
+  // at a time, the main kernel's 8)
+  uint32_t *const ctr = (uint32_t *)ws;
+  const int64_t n_blocks = (int64_t)nqb2 * heads * n_seq;
+  const bool stream = bounded && n_kt / 2 >= kStreamStages && n_kt / 2 <= kStreamMost && n_blocks > 2 * n_cu && n_blocks < ((int64_t)1 << 30) &&
+                      n_cu % 4 == 0 && (((uintptr_t)o | (uintptr_t)res) & 15u) == 0;
+  auto pack_kernel = [&](auto has_sync) {
+    constexpr bool SYNC = decltype(has_sync)::value;
+    uint32_t *const words = stream ? ctr : sync;
+    const int n_words = stream ? kStreamWords : kSyncWords;
     const dim3 grid((unsigned)n_kt, (unsigned)(heads * n_seq));
     if (bounded)
-      hipLaunchKernelGGL((k_attn_pack<CUT, false>), grid, dim3(256), 0, st, k, v, n, heads, n_kt, qk_norm, kp, vp, sync, redo, 0);
+      hipLaunchKernelGGL((k_attn_pack<SYNC, false>), grid, dim3(256), 0, st, k, v, n, heads, n_kt, qk_norm, kp, vp, words,
+                         n_words, redo, 0);
     else
-      hipLaunchKernelGGL((k_attn_pack<CUT, true>), grid, dim3(256), 0, st, k, v, n, heads, n_kt, qk_norm, kp, vp, sync, redo,
-                         2 * nqb);
+      hipLaunchKernelGGL((k_attn_pack<SYNC, true>), grid, dim3(256), 0, st, k, v, n, heads, n_kt, qk_norm, kp, vp, words,
+                         n_words, redo, 2 * nqb);
   };
-  if (cut.n_cut) pack_kernel(std::true_type{});
+  if (cut.n_cut || stream) pack_kernel(std::true_type{});
   else pack_kernel(std::false_type{});
   if (after_pack && hipEventRecord(after_pack, st) != hipSuccess) return LV_ERR_HIP;
   auto main_kernel = [&](auto online, auto packed, uint16_t *out) {
@@ -2068,6 +2418,9 @@ int launch_attn(const uint16_t *q, const uint16_t *k, const uint16_t *v, uint16_
     if (is_short)
       hipLaunchKernelGGL((k_attn_bf16_short<ON, PK>), dim3((unsigned)(nqs * heads * n_seq)), dim3(256), 0, st, q, kp, vp, out,
                          res, n, heads, n_seq, n_kt, nqs, c, qk_norm, flags, stride);
+    else if (!ON && stream)
+      hipLaunchKernelGGL((res ? k_attn_bf16_stream<PK, !PK> : k_attn_bf16_stream<PK, false>), dim3((unsigned)(2 * n_cu)),
+                         dim3(256), 0, st, q, kp, vp, out, res, n, heads, n_seq, n_kt, nqb2, c, qk_norm, ctr);
     else if (cut.n_cut)
       hipLaunchKernelGGL((k_attn_bf16_cut<ON, PK>), dim3((unsigned)(kXcd * 2 * cut.n_cut)), dim3(256), 0, st, q, kp, vp, out,
                          n, heads, n_kt, nqb2, c, qk_norm, flags, stride, cut, sync, partial);

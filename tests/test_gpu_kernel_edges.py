@@ -647,3 +647,52 @@ def test_frame_attention_short_frames_in_place(B, frames, h, w, heads, norm):
     torch.cuda.synchronize()
     ref = torch.cat([f.double() + _attn64(f, f, f, norm, heads) for f in x.reshape(frames, n, -1)])
     assert float((got.double() - ref).abs().max() / ref.abs().max()) <= 2e-2
+
+
+# ------------------------------------------------------------------------------- blocks that follow each other
+# more 256-query blocks than slots, in workgroups that stay: the fewest key stages (4) and one fewer, a
+# last stage of one key and a whole one, last blocks with one, two and all waves at work, one list for all
+# XCDs (pairs no multiple of 8), tails of the last round up to half of the slots and beyond, residual in
+# place and none, an output that is 8-byte aligned only
+@pytest.mark.parametrize("frames,h,w,heads,res", [(65, 14, 18, 8, 1), (65, 12, 16, 8, 1), (65, 11, 17, 8, 1), (90, 14, 18, 3, 1),
+                                                  (33, 16, 16, 16, 1), (43, 17, 18, 7, 0), (40, 24, 25, 6, 1), (20, 37, 37, 8, 1),
+                                                  (20, 37, 37, 8, 8), (13, 28, 37, 12, 1)])
+def test_attention_blocks_in_a_stream(B, frames, h, w, heads, res):
+    import torch
+    n = h * w + 5
+    g = torch.Generator(device="cuda")
+    g.manual_seed(frames * heads)
+    x = torch.randn(frames * n, heads * 64, generator=g, device="cuda").to(torch.bfloat16)
+    ph = B.make_params(frames, h, w, heads * 64, heads, qk_norm=1)
+    ws = B.alloc_ws(B.litevggt_frame_attn_ws_bytes(ph))
+    ws.fill_(0x7f)                              # counters are cleared by the call
+    outs = []
+    for _ in range(2):
+        if res == 1:
+            got = x.clone()
+            B.litevggt_frame_attn(ph, got, got, got, got, got, ws)
+        else:
+            got = torch.full((x.numel() + 8,), float("nan"), dtype=torch.bfloat16, device="cuda")[res // 2:][:x.numel()].view_as(x)
+            B.litevggt_frame_attn(ph, x, x, x, x if res else None, got, ws)
+        torch.cuda.synchronize()
+        outs.append(got.clone())
+    ref = torch.cat([_attn64(f, f, f, True, heads) + (f.double() if res else 0.0) for f in x.reshape(frames, n, -1)])
+    assert float((outs[0].double() - ref).abs().max() / ref.abs().max()) <= 2e-2
+    assert torch.equal(outs[0], outs[1])
+
+
+# the same rows alone (one launch per block) and as one of many blocks have the same bits
+@pytest.mark.parametrize("n,heads", [(8200, 16), (13500, 16), (11200, 12)])
+def test_attention_stream_equals_single_blocks(B, n, heads):
+    import torch
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n)
+    q, k, v = (torch.randn(n, heads * 64, generator=g, device="cuda").to(torch.bfloat16) for _ in range(3))
+    ph = B.make_params(1, 1, 1, heads * 64, heads, n_special=0, qk_norm=1)
+    ws = B.alloc_ws(B.litevggt_attn_ws_bytes(ph, n))
+    o = torch.full_like(q, float("nan"))
+    B.litevggt_global_attn(ph, n, q, k, v, o, ws)
+    odd = torch.full((q.numel() + 8,), float("nan"), dtype=torch.bfloat16, device="cuda")[4:][:q.numel()].view_as(q)
+    B.litevggt_global_attn(ph, n, q, k, v, odd, ws)
+    torch.cuda.synchronize()
+    assert torch.equal(o, odd)
