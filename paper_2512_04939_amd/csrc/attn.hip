@@ -1630,19 +1630,15 @@ __device__ __forceinline__ u32x4 norm8(const u32x4 w, float ss_head, int qk_norm
   return qk_norm ? scale8(w, 1.0f / sqrtf(ss_head * (1.0f / 64.0f) + kQkEps)) : w;
 }
 
-// n words, and (optional) the four of an amax block
-__global__ __launch_bounds__(256) void k_zero_words(uint32_t *p, size_t n, uint32_t *amax) {
-  const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
-  if (i < n) p[i] = 0u;
-  if (amax && i < 4) amax[i] = 0u;
-}
-
-// amax[0..2] = max |q^|, |k^|, |v| over the call's tensors (q^, k^ normalised when qk_norm).
-// One thread per 8-value chunk; the 8 lanes of a (row, head) combine their sums of squares.
+// part[workgroup] = max |q^|, |k^|, |v| over its share of the call's tensors (q^, k^ normalised when
+// qk_norm); k_attn_amax_final reduces them.  One thread per 8-value chunk; the 8 lanes of a (row, head) combine
+// their sums of squares.  No atomics: a few thousand workgroups end together and all find the words at 0, and
+// how many of them send one varies (15,432 tokens of 16 heads 19-26 us with conditional atomics on three words,
+// now 17.5; a call of 600 tokens 28.1 -> 24.1 with the launch that only cleared words gone as well).
 __global__ __launch_bounds__(256) void k_attn_amax(const uint16_t *__restrict__ q,
                                                    const uint16_t *__restrict__ k,
                                                    const uint16_t *__restrict__ v, int64_t n, int C,
-                                                   int qk_norm, uint32_t *__restrict__ amax) {
+                                                   int qk_norm, f32x4 *__restrict__ part) {
   __shared__ float red[3][4];
   const int64_t nchunks = n * (C >> 3);
   float mq = 0.f, mk = 0.f, mv = 0.f;
@@ -1670,13 +1666,38 @@ __global__ __launch_bounds__(256) void k_attn_amax(const uint16_t *__restrict__ 
     red[2][wave] = mv;
   }
   __syncthreads();
-  if (threadIdx.x < 3) {
-    const float m = fmaxf(fmaxf(red[threadIdx.x][0], red[threadIdx.x][1]),
-                          fmaxf(red[threadIdx.x][2], red[threadIdx.x][3]));
-    // non-negative floats order like uints; only a value that would raise the word sends an atomic
-    if (__float_as_uint(m) > __hip_atomic_load(&amax[threadIdx.x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
-      atomicMax(&amax[threadIdx.x], __float_as_uint(m));
+  if (threadIdx.x == 0) {
+    f32x4 m = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int t = 0; t < 3; ++t) m[t] = fmaxf(fmaxf(red[t][0], red[t][1]), fmaxf(red[t][2], red[t][3]));
+    part[blockIdx.x] = m;
   }
+}
+
+// amax[0..2] from the n_part parts, and the flags cleared
+__global__ __launch_bounds__(256) void k_attn_amax_final(const f32x4 *__restrict__ part, int n_part, uint32_t *__restrict__ amax,
+                                                         uint32_t *__restrict__ flags, size_t n_flags) {
+  const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
+  if (i < n_flags) flags[i] = 0u;
+  if (blockIdx.x != 0) return;
+  __shared__ float red[3][4];
+  f32x4 m = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 8
+  for (int p = threadIdx.x; p < n_part; p += 256) {
+    const f32x4 v = part[p];
+#pragma unroll
+    for (int t = 0; t < 3; ++t) m[t] = fmaxf(m[t], v[t]);
+  }
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+#pragma unroll
+  for (int t = 0; t < 3; ++t) {
+    m[t] = wave_max(m[t]);
+    if (lane == 0) red[t][wave] = m[t];
+  }
+  __syncthreads();
+  if (threadIdx.x < 3)
+    amax[threadIdx.x] = __float_as_uint(fmaxf(fmaxf(red[threadIdx.x][0], red[threadIdx.x][1]),
+                                              fmaxf(red[threadIdx.x][2], red[threadIdx.x][3])));
 }
 
 // fp8 counterpart of k_attn_pack: same fragment-major orders with 8 bytes per lane.
@@ -1684,10 +1705,8 @@ __global__ __launch_bounds__(256) void k_attn_pack_fp8(const uint16_t *__restric
                                                        const uint16_t *__restrict__ v, int64_t n,
                                                        int heads, int n_kt, int qk_norm,
                                                        const uint32_t *__restrict__ amax,
-                                                       const uint32_t *__restrict__ gate,
                                                        u32x2 *__restrict__ kp, u32x2 *__restrict__ vp) {
   __shared__ __attribute__((aligned(8))) uint8_t vt[kKT][72];
-  if (gate && *gate == 0u) return;   // second pass with nothing flagged: no one will read the result
   const int kt = blockIdx.x, head = blockIdx.y, t = threadIdx.x;
   const int C = heads * 64;
   const int key = t >> 3, chunk = t & 7;
@@ -1724,6 +1743,8 @@ __device__ __forceinline__ i32x8 cat_fp8(u32x2 a, u32x2 b, u32x2 c, u32x2 d) {
 // head for the scores, all keys of a stage for the output), which runs at twice the rate of the
 // 32x32x16 fp8 form; the order of the 64 contraction indices inside an operand is the same for
 // both operands (piece p of the packed fragments = indices 16p .. 16p+15 in fragment order).
+// SECOND: the pass behind the bounded kernel, over that kernel's packed K and V (k_attn_pack_fp8b).
+template <bool SECOND>
 __global__ __launch_bounds__(512) void k_attn_fp8(
     const uint16_t *__restrict__ q, const u32x2 *__restrict__ kp, const u32x2 *__restrict__ vp,
     uint16_t *__restrict__ o, int64_t n, int heads, int n_kt, int nqb, float c_in, int qk_norm,
@@ -1745,7 +1766,7 @@ __global__ __launch_bounds__(512) void k_attn_fp8(
   }
   // second pass behind the bounded kernel: only the query blocks it has flagged (one flag per
   // 256 queries; the whole workgroup takes the same branch, before any barrier)
-  if (redo && redo[(size_t)head * (2 * nqb) + 2 * qb] == 0u && redo[(size_t)head * (2 * nqb) + 2 * qb + 1] == 0u)
+  if (SECOND && redo[(size_t)head * (2 * nqb) + 2 * qb] == 0u && redo[(size_t)head * (2 * nqb) + 2 * qb + 1] == 0u)
     return;
   const int64_t q0 = (int64_t)qb * kQB + wave * kQW;
   const float inv_sq = fp8_scale_inv(amax[0]);
@@ -1782,10 +1803,13 @@ __global__ __launch_bounds__(512) void k_attn_fp8(
   const u32x2 *kh = kp + (size_t)head * n_kt * 4 * kFragU4;
   const u32x2 *vh = vp + (size_t)head * n_kt * 4 * kFragU4;
   u32x2 rk, rv;
+  // SECOND: where the piece that lies at tid in LDS, fragment (kt2, s) of K, (kt2, u, dt) of V, is in 16-byte pieces
+  const int kt2_ = wave >> 2, k_at = SECOND ? ((kt2_ * 2 + ((wave >> 1) & 1)) * 64 + lane) * 2 + (wave & 1) : tid;
+  const int v_at = SECOND ? (((wave & 1) * 2 + kt2_) * 64 + lane) * 2 + ((wave >> 1) & 1) : tid;
   auto g2r = [&](int j) {
     const size_t off = (size_t)j * 8 * kFragU4;
-    rk = kh[off + tid];
-    rv = vh[off + tid];
+    rk = kh[off + k_at];
+    rv = vh[off + v_at];
   };
   auto r2s = [&](int j) {
     ks[j % kKSlots][tid] = rk;
@@ -2028,8 +2052,7 @@ __global__ __launch_bounds__(256) void k_attn_pack_fp8b(const uint16_t *__restri
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_attn_fp8_bounded(
     const uint16_t *__restrict__ q, const u32x4 *__restrict__ kp, const u32x4 *__restrict__ vp,
     uint16_t *__restrict__ o, int64_t n, int heads, int nkv, int nqb, float c_in,
-    const uint32_t *__restrict__ amax, uint32_t *__restrict__ redo, int redo_stride,
-    uint32_t *__restrict__ redo_any) {
+    const uint32_t *__restrict__ amax, uint32_t *__restrict__ redo, int redo_stride) {
   __shared__ u32x4 ks[kF8Stages][4 * 64];
   __shared__ u32x4 vs[kF8Stages][4 * 64];
   const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5, ql = lane & 31;
@@ -2252,10 +2275,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         }
     }
   }
-  if (redo && __builtin_amdgcn_ballot_w64(low) != 0 && lane == 0) {
-    atomicOr(&redo[(size_t)head * redo_stride + qb], 1u);
-    atomicOr(redo_any, 1u);
-  }
+  if (__builtin_amdgcn_ballot_w64(low) != 0 && lane == 0) atomicOr(&redo[(size_t)head * redo_stride + qb], 1u);
 }
 
 static int n_key_tiles(int64_t n) { return (int)(2 * ((n + kKV - 1) / kKV)); }
@@ -2346,9 +2366,10 @@ int launch_attn(const uint16_t *q, const uint16_t *k, const uint16_t *v, uint16_
     const bool bounded = qk_norm && kF8Bound * c <= 64.0f;
     uint32_t *redo = (uint32_t *)(frag + 4 * per);
     const size_t words = bounded ? fp8_flag_words(heads, n) : 0;
-    hipLaunchKernelGGL(k_zero_words, dim3((unsigned)((words + 255) / 256 + 1)), dim3(256), 0, st, redo, words, amax);
-    hipLaunchKernelGGL(k_attn_amax, dim3(ag), dim3(256), 0, st, q, k, v, n, C, qk_norm, amax);
-    if (!bounded) redo = nullptr;
+    f32x4 *const part = (f32x4 *)kp;   // (16 bytes per 2048 of K, gone before K is written)
+    hipLaunchKernelGGL(k_attn_amax, dim3(ag), dim3(256), 0, st, q, k, v, n, C, qk_norm, part);
+    hipLaunchKernelGGL(k_attn_amax_final, dim3((unsigned)((words + 255) / 256 + 1)), dim3(256), 0, st, (const f32x4 *)part,
+                       (int)ag, amax, redo, words);
     if (bounded) {
       u32x2 *kpb = (u32x2 *)(frag + 2 * per), *vpb = (u32x2 *)(frag + 3 * per);
       hipLaunchKernelGGL(k_attn_pack_fp8b, dim3((unsigned)n_kt, (unsigned)heads), dim3(256), 0, st, k, v, n,
@@ -2357,13 +2378,16 @@ int launch_attn(const uint16_t *q, const uint16_t *k, const uint16_t *v, uint16_
       const int nqb2 = (int)((n + kBQB - 1) / kBQB);
       hipLaunchKernelGGL(k_attn_fp8_bounded, dim3((unsigned)(nqb2 * heads)), dim3(256), 0, st, q,
                          (const u32x4 *)kpb, (const u32x4 *)vpb, o, n, heads, n_kt / 2, nqb2, c, amax, redo,
-                         2 * nqb, amax + 3);
+                         2 * nqb);
+      hipLaunchKernelGGL(k_attn_fp8<true>, dim3((unsigned)(nqb * heads)), dim3(512), 0, st, q, kpb, vpb, o, n,
+                         heads, n_kt, nqb, c, qk_norm, amax, (const uint32_t *)redo);
+    } else {
+      hipLaunchKernelGGL(k_attn_pack_fp8, dim3((unsigned)n_kt, (unsigned)heads), dim3(256), 0, st, k,
+                         v, n, heads, n_kt, qk_norm, amax, kp, vp);
+      if (after_pack && hipEventRecord(after_pack, st) != hipSuccess) return LV_ERR_HIP;
+      hipLaunchKernelGGL(k_attn_fp8<false>, dim3((unsigned)(nqb * heads)), dim3(512), 0, st, q, kp, vp, o, n,
+                         heads, n_kt, nqb, c, qk_norm, amax, (const uint32_t *)nullptr);
     }
-    hipLaunchKernelGGL(k_attn_pack_fp8, dim3((unsigned)n_kt, (unsigned)heads), dim3(256), 0, st, k,
-                       v, n, heads, n_kt, qk_norm, amax, bounded ? amax + 3 : (const uint32_t *)nullptr, kp, vp);
-    if (!bounded && after_pack && hipEventRecord(after_pack, st) != hipSuccess) return LV_ERR_HIP;
-    hipLaunchKernelGGL(k_attn_fp8, dim3((unsigned)(nqb * heads)), dim3(512), 0, st, q, kp, vp, o, n,
-                       heads, n_kt, nqb, c, qk_norm, amax, redo);
     LV_HIP_CHECK_LAUNCH();
     return LV_OK;
   }
