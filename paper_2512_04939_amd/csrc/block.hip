@@ -401,7 +401,8 @@ __global__ __launch_bounds__(256) void k_weights_pack(BlockWeights4 bw, int C, c
 // per stage).  256 x 256: 8 waves, 4 stages, one workgroup per CU, 128 flop per fetched byte.
 // 128 x 256 and 128 x 128: 4 waves, 3 and 4 stages, two workgroups per CU, whose epilogues run
 // beside each other's main loops: for row counts that fill the chip badly with larger tiles
-// (tile_shape).  Bound by
+// (tile_shape).  KG = 2 (64 x 64, 128 x 128): two groups of waves with a ring each take half of K each and
+// meet in LDS: for row counts that do not fill it at all (one tile per workgroup).  Bound by
 // the matrix pipe and what keeps a wave from feeding it: issuing the fetches, the barrier, the
 // fragment reads; the MFMAs alone take 70 % of the loop's time.  The finished tile goes from the accumulators straight to global
 // memory (bias, optional GELU, one rounding to bf16); `addend` (optional, shaped like the
@@ -422,7 +423,8 @@ __device__ __forceinline__ void lds_read1_async(u32x4 &dst, uint32_t addr) {
   asm volatile("ds_read_b128 %0, %1" : "=&v"(dst) : "v"(addr) : "memory");
 }
 constexpr int kTile = 256;                   // what rows are padded to and output channels are a multiple of
-// Shape of a workgroup with tiles of BM rows x BN columns: (BM / 64) x 2 waves of 64 rows x BN / 2 columns.
+// Shape of a workgroup (KG = 2: of a K group) with tiles of BM rows x BN columns: (BM / 64) x 2 waves of 64 rows x
+// BN / 2 columns.
 template <int BM, int BN>
 struct GemmShape {
   static constexpr int kWaves = BM / 32, kThreads = kWaves * 64;
@@ -431,6 +433,7 @@ struct GemmShape {
   static constexpr int kStageU4 = 2 * (kFragW + kFragA) * 64;   // [weights: 2 k-steps x kFragW | activations: 2 x kFragA][64 lanes]
   static constexpr int kStages = BM == 128 && BN == 256 ? 3 : 4;   // LDS ring: 128 KB, one workgroup per CU; 72 or 64 KB, two
   static constexpr int kLoads = 2 * (kFragW + kFragA) / kWaves;   // fragments a wave fetches per stage
+  static constexpr int kLoadsW = kWaves == 8 ? kLoads : 2 * kFragW / kWaves;   // ... of these of the weights (8 waves: all or none)
   static constexpr size_t kLds = (size_t)kStages * kStageU4 * 16 + 2 * BN * sizeof(float);   // + two tiles' bias values
 };
 
@@ -449,20 +452,22 @@ __device__ __forceinline__ float gelu_erf(float v) {
   return 0.5f * v * (v < 0.f ? erfc_abs : 2.0f - erfc_abs);
 }
 
-template <bool FP8, bool PACKED, int BM, int BN>
-__global__ __launch_bounds__((GemmShape<BM, BN>::kThreads)) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_gemm_bt(
+template <bool FP8, bool PACKED, int BM, int BN, int KG = 1>
+__global__ __launch_bounds__((GemmShape<BM, BN>::kThreads * KG)) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_gemm_bt(
     const u32x4 *__restrict__ ap, const u32x4 *__restrict__ wp, int64_t M, int KS, int nt_n,
     const float *__restrict__ bias, int gelu, uint16_t *__restrict__ out, int split,
     const float *__restrict__ alpha_p, int n_tiles, int rows_by_xcd, const uint16_t *__restrict__ addend,
     const uint32_t *__restrict__ out_inv, uint32_t *__restrict__ out_amax) {
   using S = GemmShape<BM, BN>;
   constexpr int kStages = S::kStages, kStageU4 = S::kStageU4, kB = S::kB;
-  constexpr bool kTwoSets = !FP8 || kB == 2;   // registers for two sets of weight fragments
-  extern __shared__ u32x4 ring[];
+  constexpr bool kTwoSets = !FP8 || kB <= 2;   // registers for two sets of weight fragments
+  extern __shared__ u32x4 rings[];             // one ring per K group
   const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int kg = KG == 1 ? 0 : __builtin_amdgcn_readfirstlane(tid >> 6) / S::kWaves;   // this wave's part of K
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6) - kg * S::kWaves;
+  u32x4 *const ring = rings + (size_t)kg * kStages * kStageU4;
   const int wd = wave % (BM / 64), wn = wave / (BM / 64);
-  const int total = KS >> 1;
+  const int total = (KS >> 1) / KG;
   // persistent: one workgroup per CU walks the tiles (a workgroup owns a whole CU's LDS, so a
   // launch per tile would pay a dispatch between any two tiles of a CU)
   // Workgroup w runs on XCD w % 8.  An XCD takes the row tiles tm = x, x + 8, ..., so an
@@ -497,35 +502,35 @@ __global__ __launch_bounds__((GemmShape<BM, BN>::kThreads)) __attribute__((amdgp
   if (more) tile_at(v + stride, tm2, tn2);
   // this tile's bias values wait in LDS behind the ring (read in the epilogue, many barriers
   // later); two buffers in turn, so a wave still in the previous tile's epilogue reads its own
-  float *bias_lds = (float *)(ring + (size_t)kStages * kStageU4) + parity * BN;
+  float *bias_lds = (float *)(rings + (size_t)KG * kStages * kStageU4) + parity * BN;
   if (tid < BN) bias_lds[tid] = bias ? bias[tn * BN + tid] : 0.f;
 
   // fetch: with 8 waves, waves 0-3 move 4 weight fragments of a stage each, waves 4-7 4 activation
   // fragments; with 4 waves each moves kB weight and 2 activation fragments
-  const int f_ks = (wave >> 1) & 1;
+  const int f_ks = S::kWaves == 2 ? wave : (wave >> 1) & 1, f_half = S::kWaves == 2 ? 0 : wave & 1;
   int pf_g = 0, f_tm = tm, f_tn = tn;
   auto slot_of = [](int g) { return kStages == 4 ? g & 3 : g % kStages; };
   const u32x4 *f_src[2];   // this wave's next weight and activation fragments (8 waves: [0] is either)
   u32x4 *f_dst[2];
   auto fetch_begin = [&]() {
     const int s = pf_g < total ? pf_g : total - 1;   // past the end: the last stage again, into a free slot
-    const size_t at = (size_t)(s * 2 + f_ks) * 64;   // uniform: the lane is added in the load
+    const size_t at = (size_t)((kg * total + s) * 2 + f_ks) * 64;   // uniform: the lane is added in the load
     u32x4 *stage = ring + (size_t)slot_of(pf_g) * kStageU4;
     if constexpr (S::kWaves == 8) {
       const int a0 = (wave & 1) * 4;
       f_src[0] = (wave >> 2 ? ap + (size_t)(f_tm * 8 + a0) * KS * 64 : wp + (size_t)(f_tn * 8 + a0) * KS * 64) + at;
       f_dst[0] = stage + (size_t)(wave * 4) * 64;
     } else {
-      f_src[0] = wp + (size_t)(f_tn * S::kFragW + (wave & 1) * kB) * KS * 64 + at;
-      f_src[1] = ap + (size_t)(f_tm * S::kFragA + (wave & 1) * 2) * KS * 64 + at;
-      f_dst[0] = stage + (size_t)(wave * kB) * 64;
+      f_src[0] = wp + (size_t)(f_tn * S::kFragW + f_half * kB) * KS * 64 + at;
+      f_src[1] = ap + (size_t)(f_tm * S::kFragA + f_half * 2) * KS * 64 + at;
+      f_dst[0] = stage + (size_t)(wave * S::kLoadsW) * 64;
       f_dst[1] = stage + (size_t)(2 * S::kFragW + wave * 2) * 64;
     }
     ++pf_g;
   };
   auto fetch_one = [&](auto idx) {
     constexpr int i = decltype(idx)::value;
-    constexpr int part = i >= kB ? 1 : 0, j = i - part * kB;
+    constexpr int part = i >= S::kLoadsW ? 1 : 0, j = i - part * S::kLoadsW;
     if constexpr (i < S::kLoads)
       __builtin_amdgcn_global_load_lds(f_src[part] + (size_t)j * KS * 64 + lane, f_dst[part] + j * 64, 16, 0, 0);
   };
@@ -546,7 +551,8 @@ __global__ __launch_bounds__((GemmShape<BM, BN>::kThreads)) __attribute__((amdgp
   auto read_frags = [&](int g, int ks, u32x4(&b)[kB], u32x4(&a)[2]) {
     const uint32_t base = ring_lane + (uint32_t)(slot_of(g) * kStageU4 * 16);
     if constexpr (kB == 4) lds_read4_async(b, base + b_off + ks * b_ks);
-    else lds_read2_async(b, base + b_off + ks * b_ks);
+    else if constexpr (kB == 2) lds_read2_async(b, base + b_off + ks * b_ks);
+    else lds_read1_async(b[0], base + b_off + ks * b_ks);
     lds_read2_async(a, base + a_off + ks * a_ks);
   };
   f32x16 acc[2][kB];
@@ -577,10 +583,10 @@ __global__ __launch_bounds__((GemmShape<BM, BN>::kThreads)) __attribute__((amdgp
   // layer at M = 143,232, C = 1024 in bf16, 900 like this.)
   auto wait_set = [&](u32x4(&b)[2][kB], u32x4(&a)[2][2]) {
     asm volatile("s_waitcnt lgkmcnt(0)"
-                 : "+v"(b[0][0]), "+v"(b[0][1]), "+v"(b[1][0]), "+v"(b[1][1]), "+v"(a[0][0]), "+v"(a[0][1]),
-                   "+v"(a[1][0]), "+v"(a[1][1])
+                 : "+v"(b[0][0]), "+v"(b[1][0]), "+v"(a[0][0]), "+v"(a[0][1]), "+v"(a[1][0]), "+v"(a[1][1])
                  :
                  : "memory");
+    if constexpr (kB >= 2) asm volatile("" : "+v"(b[0][1]), "+v"(b[1][1]) : : "memory");
     if constexpr (kB == 4)
       asm volatile("" : "+v"(b[0][2]), "+v"(b[0][3]), "+v"(b[1][2]), "+v"(b[1][3]) : : "memory");
   };
@@ -633,12 +639,19 @@ __global__ __launch_bounds__((GemmShape<BM, BN>::kThreads)) __attribute__((amdgp
       LV_LD(3); LV_LD(5);
       pair(bc, ac, 0, 3);
       again(3);
-    } else if constexpr (FP8) {                              // kB == 2
+    } else if constexpr (FP8) {                              // kB <= 2
       read_frags(g + 1, 0, bn[0], an[0]);
       read_frags(g + 1, 1, bn[1], an[1]);
       fetch_begin();
       LV_LD(0); LV_LD(1);
-      pair(bc, ac, 0, 1);
+      if constexpr (kB == 2) pair(bc, ac, 0, 1);
+      LV_LD(2); LV_LD(3);
+    } else if constexpr (kB == 1) {
+      read_frags(g + 1, 0, bn[0], an[0]);
+      read_frags(g + 1, 1, bn[1], an[1]);
+      fetch_begin();
+      LV_LD(0); LV_LD(1);
+      pair(bc, ac, 1, 0);
       LV_LD(2); LV_LD(3);
     } else {
       pair(bc, ac, 0, 1);
@@ -684,6 +697,33 @@ __global__ __launch_bounds__((GemmShape<BM, BN>::kThreads)) __attribute__((amdgp
   wait_set(fb[kSetB], fa[1]);
   asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");   // nothing may land in LDS any more
   __syncthreads();
+  // Two K groups trade sums through their rings: group kg finishes row block a = kg, group 0's sum first.
+  auto mine = [&](int a) { return KG == 1 || a == kg; };
+  if constexpr (KG == 2) {
+    auto at = [&](int from, int b, int g) {
+      return (f32x4 *)(rings + (size_t)from * kStages * kStageU4) + (size_t)((wave * kB + b) * 4 + g) * 64 + lane;
+    };
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+      if (a != kg)                           // (uniform: one copy runs)
+#pragma unroll
+        for (int b = 0; b < kB; ++b)
+#pragma unroll
+          for (int g = 0; g < 4; ++g)
+            *at(kg, b, g) = f32x4{acc[a][b][4 * g], acc[a][b][4 * g + 1], acc[a][b][4 * g + 2], acc[a][b][4 * g + 3]};
+    __syncthreads();
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+      if (a == kg)
+#pragma unroll
+        for (int b = 0; b < kB; ++b)
+#pragma unroll
+          for (int g = 0; g < 4; ++g) {
+            const f32x4 x = *at(1 - a, b, g);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) acc[a][b][4 * g + i] += x[i];
+          }
+  }
 
   // Epilogue: bias, activation, bf16, straight from the accumulators to global memory; nothing
   // goes through LDS, so the next tile's first stages are issued first and land while the
@@ -695,7 +735,7 @@ __global__ __launch_bounds__((GemmShape<BM, BN>::kThreads)) __attribute__((amdgp
   const float alpha = alpha_p ? *alpha_p : 1.0f;
   int anchor = 0;   // opaque zero: keeps the address arithmetic below inside this tile's epilogue
   asm volatile("" : "+v"(anchor));   // (hoisted out of the tile loop it would stay live through the main loop)
-  if (more) {
+  if (KG == 1 && more) {
     f_tn = tn2;
     f_tm = tm2;
     pf_g = 0;
@@ -724,6 +764,7 @@ __global__ __launch_bounds__((GemmShape<BM, BN>::kThreads)) __attribute__((amdgp
       for (int b = 0; b < kB; ++b)
 #pragma unroll
         for (int a = 0; a < 2; ++a) {
+          if (!mine(a)) continue;
           const bool live = (int64_t)tm * BM + wd * 64 + 32 * a + (lane & 31) < M;
           uint32_t d[4];
 #pragma unroll
@@ -759,6 +800,7 @@ __global__ __launch_bounds__((GemmShape<BM, BN>::kThreads)) __attribute__((amdgp
         const f32x4 bv0 = *(const f32x4 *)(bias_lds + ch0), bv1 = *(const f32x4 *)(bias_lds + ch0 + 8);
 #pragma unroll
         for (int a = 0; a < 2; ++a) {
+          if (!mine(a)) continue;
           float v0[4], v1[4];
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
@@ -789,6 +831,7 @@ __global__ __launch_bounds__((GemmShape<BM, BN>::kThreads)) __attribute__((amdgp
       const f32x4 bv0 = *(const f32x4 *)(bias_lds + ch0), bv1 = *(const f32x4 *)(bias_lds + ch0 + 8);
 #pragma unroll
       for (int a = 0; a < 2; ++a) {
+        if (!mine(a)) continue;
         float v0[4], v1[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
@@ -867,8 +910,8 @@ size_t block_ws_bytes(int64_t M, int C, int heads, int attn_dtype, bool least) {
 struct LinearOpts {
   bool fp8 = false;
   const u32x4 *a_packed = nullptr;     // the activation operand, already in operand order (then A is unused)
-  // out receives the next layer's (K = Nout) operand instead of row-major rows: the rows of whole tiles (128
-  // or 256 each), rows M and up undefined; the next layer may read up to Mp rows, into outputs it drops
+  // out receives the next layer's (K = Nout) operand instead of row-major rows: the rows of whole tiles (64,
+  // 128 or 256 each), rows M and up undefined; the next layer may read up to Mp rows, into outputs it drops
   bool pack_out = false;
   const uint16_t *addend = nullptr;    // row-major, same shape as out: out = addend + result
   const u32x4 *w_packed = nullptr;     // the weight operand
@@ -889,8 +932,17 @@ struct LinearOpts {
 //   M =   2200: 28 24 33 77   22 18 32 52   20 12 34 36        M = 15432: 99 36 143 116  100 35 139 119  112 38 159 133
 //   M =   5776: 54 27 66 83   43 19 54 59   42 19 58 56        M = 143232: 890 282 1183 1015  952 311 1242 1172
 // with the three tiles in that order.
-enum TileShape { kTile256x256, kTile128x256, kTile128x128 };
-static TileShape tile_shape(int64_t M, int Nout, int n_cu) {
+// Where even the 128 x 128 tiles leave CUs idle, what counts is how long one workgroup is at a tile: it
+// gets 16 KB per stage at 150 GB/s and pays the barrier of every stage.  64 x 64 tiles in two K groups halve both, as
+// long as all of them are on the chip at once (two per CU); longer rows (K >= 2048 in bf16) gain from two K groups of 128 x 128
+// tiles, one per CU.  us for qkv / out / MLP 1 / MLP 2, 128 x 128 and as chosen:
+//   M =  394: 11.2 10.7 13.8 30.9    9.8 6.4 11.0 14.9      M = 2200: 19.8 12.2 33.7 36.5   (the same) (the same) (the same) 31.6
+//   M = 1000: 12.2 11.2 14.5 30.9   (the same) 7.7 (the same) 16.7     E4M3, M = 394: 8.5 8.4 13.4 19.6    7.4 5.4 8.9 9.8
+// (64 x 64 without groups 22.6 for MLP 2 at M = 394, 128 x 128 with them 25.7, 64 x 64 in four groups 14.7.)
+enum TileShape { kTile256x256, kTile128x256, kTile128x128, kTile128x128K2, kTile64x64K2 };
+static TileShape tile_shape(int64_t M, int Nout, int K, bool fp8, int n_cu) {
+  if ((M + 63) / 64 * (Nout / 64) <= 2 * n_cu) return kTile64x64K2;
+  if (!fp8 && K >= 2048 && (M + 127) / 128 * (Nout / 128) <= n_cu) return kTile128x128K2;
   int64_t rest = 0;
   const auto rounds = [&](int bm, int bn, int slots) {   // full rounds (of the XCD with the most tiles), and what is left
     const int64_t nt_m = (M + bm - 1) / bm, nt_n = Nout / bn, tiles = nt_m * nt_n;
@@ -926,20 +978,22 @@ static int launch_linear(const uint16_t *A, int64_t M, int K, int Nout,
   if (hipGetDevice(&dev) != hipSuccess ||
       hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n_cu < 1)
     return LV_ERR_HIP;
-  const TileShape shape = tile_shape(M, Nout, n_cu);
-  auto gemm = [&](auto fp8, auto packed, auto bm, auto bn, const u32x4 *act, int KS, const float *alpha) -> int {
+  const TileShape shape = tile_shape(M, Nout, K, o.fp8, n_cu);
+  auto gemm = [&](auto fp8, auto packed, auto bm, auto bn, auto kg, const u32x4 *act, int KS, const float *alpha) -> int {
     constexpr bool F8 = decltype(fp8)::value, PK = decltype(packed)::value;
-    constexpr int BM = decltype(bm)::value, BN = decltype(bn)::value;
+    constexpr int BM = decltype(bm)::value, BN = decltype(bn)::value, KG = decltype(kg)::value;
     using S = GemmShape<BM, BN>;
+    constexpr size_t kLds = S::kLds + (KG - 1) * (size_t)S::kStages * S::kStageU4 * 16;
     static std::atomic<uint64_t> lds_done{0};
-    if (int rc2 = allow_dynamic_lds((const void *)k_gemm_bt<F8, PK, BM, BN>, S::kLds, lds_done)) return rc2;
-    const int nt_m = (int)((M + BM - 1) / BM), nt_n = Nout / BN, n_tiles = nt_m * nt_n, slots = n_cu * (256 / BM);
+    if (int rc2 = allow_dynamic_lds((const void *)k_gemm_bt<F8, PK, BM, BN, KG>, kLds, lds_done)) return rc2;
+    const int nt_m = (int)((M + BM - 1) / BM), nt_n = Nout / BN, n_tiles = nt_m * nt_n;
+    const int slots = n_cu * (KG == 1 ? 256 / BM : BM == 64 ? 2 : 1);   // KG = 2: tile_shape() leaves one tile per workgroup
     // One round only: row tiles still go to one XCD each (M = 5776, K = 4096: 69 us dealt out in
     // plain order, 56 like this) unless the fullest XCD would then have more than its share of CUs or slots.
     const int fullest = (nt_m + kXcd - 1) / kXcd * nt_n, share = (n_tiles <= n_cu ? n_cu : slots) / kXcd;
     const bool by_xcd = n_tiles > slots || (nt_m >= 2 * kXcd && fullest <= share);
     const unsigned grid = (unsigned)(n_tiles > slots ? slots : by_xcd ? fullest * kXcd : n_tiles);
-    hipLaunchKernelGGL((k_gemm_bt<F8, PK, BM, BN>), dim3(grid), dim3(S::kThreads), S::kLds, st, act,
+    hipLaunchKernelGGL((k_gemm_bt<F8, PK, BM, BN, KG>), dim3(grid), dim3(S::kThreads * KG), kLds, st, act,
                        o.w_packed, M, KS, nt_n, bias, gelu, out, split, alpha, n_tiles, by_xcd ? 1 : 0, o.addend, o.out_inv,
                        o.out_amax);
     return LV_OK;
@@ -947,10 +1001,15 @@ static int launch_linear(const uint16_t *A, int64_t M, int K, int Nout,
   auto launch = [&](auto fp8, const u32x4 *act, int KS, const float *alpha) -> int {
     using N128 = std::integral_constant<int, 128>;
     using N256 = std::integral_constant<int, 256>;
+    using N64 = std::integral_constant<int, 64>;
+    using One = std::integral_constant<int, 1>;
+    using Two = std::integral_constant<int, 2>;
     auto tiles = [&](auto packed) -> int {
-      if (shape == kTile128x128) return gemm(fp8, packed, N128{}, N128{}, act, KS, alpha);
-      if (shape == kTile128x256) return gemm(fp8, packed, N128{}, N256{}, act, KS, alpha);
-      return gemm(fp8, packed, N256{}, N256{}, act, KS, alpha);
+      if (shape == kTile64x64K2) return gemm(fp8, packed, N64{}, N64{}, Two{}, act, KS, alpha);
+      if (shape == kTile128x128K2) return gemm(fp8, packed, N128{}, N128{}, Two{}, act, KS, alpha);
+      if (shape == kTile128x128) return gemm(fp8, packed, N128{}, N128{}, One{}, act, KS, alpha);
+      if (shape == kTile128x256) return gemm(fp8, packed, N128{}, N256{}, One{}, act, KS, alpha);
+      return gemm(fp8, packed, N256{}, N256{}, One{}, act, KS, alpha);
     };
     return o.pack_out ? tiles(std::true_type{}) : tiles(std::false_type{});
   };

@@ -237,9 +237,12 @@ def _block64(z, t, heads, seen=None):
 # rows of one tile, around the two tile heights, row tiles by XCD or in plain order (2200 rows at 1024
 # channels: both), every tile shape and mixes of them (5776, 9000; the largest tile with its output in
 # operand order: test_block_largest_tiles), more tiles than workgroups (33000 at 256), a column count that
-# is no multiple of 4 tiles
+# is no multiple of 4 tiles; two K groups: 64 x 64 tiles of one row, whole ones and one row more, the most of
+# them in one launch (2048 rows at 256: the first MLP layer) and one row more, 128 x 128 tiles from the fewest rows on
+# (4097 at 512: the second MLP layer) to the most (8192) and one row more
 @pytest.mark.parametrize("m,dim", [(1, 256), (127, 256), (129, 256), (257, 768), (640, 1024), (2200, 1024), (5776, 1024),
-                                   (9000, 1024), (17000, 256), (33000, 256)])
+                                   (9000, 1024), (17000, 256), (33000, 256), (63, 256), (64, 512), (65, 256), (2048, 256),
+                                   (2049, 256), (4097, 512), (8192, 512), (8193, 512)])
 @pytest.mark.parametrize("linear", ["bf16", "fp8", "fp8-delayed"])
 def test_block_tile_shapes(B, m, dim, linear):
     import torch
