@@ -492,6 +492,100 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   }   // rounds
 }
 
+// ---------------------------------------------------------------------------------
+// Few tokens.  A handful of 256 x 256 tiles leaves most CUs idle while each takes a whole tile step (1024 channels:
+// 28 us, and the fold's code for eight blocks comes in cold).  Here a workgroup has 64 src x 64 dst
+// rows and four waves: wave (kg, wn) multiplies half of the channels for 32 src rows with both halves
+// of the dst rows, fragments straight from L2 into registers, three batches of two k-steps ahead of
+// their use; the two channel halves meet in LDS, wave (kg, .) folds dst rows 32 kg .. + 31, and the
+// 64 dst rows of a tile are one candidate list.  Bound by the latency of its chain: the operands'
+// round trips, the fold, two barriers.
+// ---------------------------------------------------------------------------------
+constexpr int kSmallTile = 64;       // src and dst rows of a workgroup
+// Workgroups at most, four rounds of two per CU.  One refresh, otherwise -> this way: 2 frames of 16 x 16, C = 256 (10 of
+// them) 39.4 -> 24.2 us; C = 1024: 2 frames of 37 x 37 (460) 68.1 -> 44.0, 3 (975) 79.0 -> 60.2, 4 (1566) 86.0 -> 75.9, 5
+// (2156) 85.8 and 85.7, 6 (2910) 85.4 and 100.4.
+constexpr int kSmallTiles = 2048;
+
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_match_small(
+    const u32x4 *__restrict__ srcp, const u32x4 *__restrict__ dstp, const float *__restrict__ invd, int n_st,
+    int n_dt, int KS, int stride, Top2 *__restrict__ top2p) {
+  __shared__ f32x4 part[2][2][4 * 64];       // [kg][wn][register group][lane]: the sums the other group finishes
+  __shared__ Top2 cand[2][kSmallTile];
+  const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wn = wave & 1, kg = wave >> 1;
+  const uint32_t lb = xcd_contiguous(blockIdx.x, (uint32_t)(n_st * n_dt));   // an XCD's workgroups share src tiles
+  if (lb >= (uint32_t)(n_st * n_dt)) return;
+  const int st = lb / n_dt, dt = lb % n_dt;
+  const int nb = KS >> 2;                    // batches of two k-steps in this wave's half of the channels
+  const u32x4 *ap = dstp + ((size_t)(dt * 2) * KS + kg * (KS >> 1)) * 64 + lane;
+  const u32x4 *bp = srcp + ((size_t)(st * 2 + wn) * KS + kg * (KS >> 1)) * 64 + lane;
+  u32x4 fa[4][2][2], fb[4][2];               // [batch & 3][k-step][dst half]
+  auto load = [&](int i, u32x4(&a)[2][2], u32x4(&b)[2]) {   // past the end the last batch again
+    const size_t at = (size_t)min(i, nb - 1) * 2 * 64;
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      b[k] = bp[at + k * 64];
+#pragma unroll
+      for (int d = 0; d < 2; ++d) a[k][d] = ap[at + k * 64 + (size_t)d * KS * 64];
+    }
+  };
+  f32x16 acc[2];
+#pragma unroll
+  for (int d = 0; d < 2; ++d)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[d][r] = 0.f;
+#pragma unroll
+  for (int j = 0; j < 3; ++j) load(j, fa[j], fb[j]);
+  for (int i = 0; i < nb; i += 4) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      if (i + j < nb) {
+        load(i + j + 3, fa[(j + 3) & 3], fb[(j + 3) & 3]);
+#pragma unroll
+        for (int k = 0; k < 2; ++k)
+#pragma unroll
+          for (int d = 0; d < 2; ++d)
+            acc[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, fa[j][k][d]),
+                                                             __builtin_bit_cast(bf16x8, fb[j][k]), acc[d], 0, 0, 0);
+      }
+    }
+  }
+  // the inverse norms of the rows this wave folds, 8g + 4h .. + 3 of its half
+  f32x4 iv[4];
+#pragma unroll
+  for (int g = 0; g < 4; ++g) iv[g] = *(const f32x4 *)(invd + dt * kSmallTile + kg * 32 + 8 * g + 4 * h);
+#pragma unroll
+  for (int d = 0; d < 2; ++d)
+    if (d != kg)                             // (uniform: one copy runs)
+#pragma unroll
+      for (int g = 0; g < 4; ++g)
+        part[kg][wn][g * 64 + lane] = f32x4{acc[d][4 * g], acc[d][4 * g + 1], acc[d][4 * g + 2], acc[d][4 * g + 3]};
+  __syncthreads();
+  Top2 t = Top2{-INFINITY, -1, -INFINITY, -1};
+#pragma unroll
+  for (int g = 0; g < 4; ++g) {
+    const f32x4 o = part[1 - kg][wn][g * 64 + lane];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const float own = kg == 0 ? acc[0][4 * g + i] : acc[1][4 * g + i];
+      top2_insert_later(t, (own + o[i]) * iv[g][i], dt * kSmallTile + kg * 32 + 8 * g + 4 * h + i);
+    }
+  }
+  const Top2 u = Top2{__shfl_xor(t.v1, 32, 64), __shfl_xor(t.i1, 32, 64), __shfl_xor(t.v2, 32, 64), __shfl_xor(t.i2, 32, 64)};
+  top2_insert_any(t, u.v1, u.i1);
+  top2_insert_any(t, u.v2, u.i2);
+  if (h == 0) cand[kg][wn * 32 + lane] = t;
+  __syncthreads();
+  if (tid < kSmallTile) {
+    Top2 b = cand[0][tid];
+    const Top2 o = cand[1][tid];
+    top2_insert_any(b, o.v1, o.i1);
+    top2_insert_any(b, o.v2, o.i2);
+    top2p[(size_t)dt * stride + st * kSmallTile + tid] = b;
+  }
+}
+
 // Final decision per src row.  Every list (MatchSched) holds its two best candidates by fp32 similarity.
 // If the runner-up is closer than kRescoreGap to the best, every candidate inside that gap is
 // recomputed in float64 and the decision is taken on those values rounded to fp32, lowest token
@@ -973,6 +1067,12 @@ __global__ __launch_bounds__(1024) void k_csr_small(const int32_t *__restrict__ 
 }
 
 // ---------------------------------------------------------------------------------
+static int small_tiles(int rows) { return (rows + kSmallTile - 1) / kSmallTile; }
+// few tokens: k_match_small, with a list per dst tile
+static bool match_is_small(int n_src, int n_dst) {
+  return small_tiles(n_dst) <= kMaxLists && (int64_t)small_tiles(n_src) * small_tiles(n_dst) <= kSmallTiles;
+}
+
 struct MatchWs {
   u32x4 *dstp, *srcp;
   float *invd, *invs;
@@ -1002,7 +1102,8 @@ static MatchWs carve(const Dims &d, const litevggt_plan_t &pl, bool least, char 
   w.invs = (float *)take((size_t)w.n_src_pad * 4);
   const int src_tiles = w.n_src_pad / kGTile, dst_tiles = w.n_dst_pad / kGTile;
   w.partials = (size_t)kFewLists * src_tiles;
-  const size_t ideal = sched_partials(match_sched(src_tiles, dst_tiles, kTeam));
+  const size_t ideal = match_is_small((int)pl.n_src, (int)pl.n_dst) ? (size_t)small_tiles((int)pl.n_dst) * src_tiles
+                                                                    : sched_partials(match_sched(src_tiles, dst_tiles, kTeam));
   if (!least && ideal > w.partials) w.partials = ideal;
   w.top2p = (Top2 *)take(w.partials * kGTile * sizeof(Top2));
   for (int i = 0; i < 2; ++i) {
@@ -1039,10 +1140,18 @@ int launch_match(const uint16_t *x, const Dims &d, const litevggt_plan_t &pl,
         hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
       return LV_ERR_HIP;
     const int per_team = n_cu >= kXcd ? n_cu / kXcd : 1;
-    MatchSched sched = match_sched(src_tiles, dst_tiles, per_team);
-    if (sched_partials(sched) > w.partials) sched = match_sched(src_tiles, dst_tiles, per_team, kFewLists);
-    hipLaunchKernelGGL(k_match_sim, dim3((unsigned)(per_team * kXcd)), dim3(512), lds, st, w.srcp,
-                       w.dstp, w.invd, dst_tiles, sched, d.C / 16, kTeamSpin, w.team_ctr, w.top2p);
+    const int n_st = small_tiles(n_src), n_dt = small_tiles(n_dst);
+    MatchSched sched;
+    if (match_is_small(n_src, n_dst) && (size_t)n_dt * src_tiles <= w.partials) {
+      sched = {1, 1, 0, 1, src_tiles, 0, 1, n_dt};   // one list per dst tile of every src row
+      hipLaunchKernelGGL(k_match_small, dim3((unsigned)align_up((size_t)n_st * n_dt, kXcd)), dim3(256), 0, st, w.srcp, w.dstp,
+                         w.invd, n_st, n_dt, d.C / 16, src_tiles * kGTile, w.top2p);
+    } else {
+      sched = match_sched(src_tiles, dst_tiles, per_team);
+      if (sched_partials(sched) > w.partials) sched = match_sched(src_tiles, dst_tiles, per_team, kFewLists);
+      hipLaunchKernelGGL(k_match_sim, dim3((unsigned)(per_team * kXcd)), dim3(512), lds, st, w.srcp, w.dstp, w.invd, dst_tiles,
+                         sched, d.C / 16, kTeamSpin, w.team_ctr, w.top2p);
+    }
     const unsigned fin = (unsigned)((n_src + 4 * kFinRows - 1) / (4 * kFinRows));
     hipLaunchKernelGGL(k_match_finish, dim3(fin), dim3(256), 0, st, x, ix.src_idx, ix.dst_idx,
                        w.invs, w.top2p, sched, n_src, d.C, ix.anchor_of, ix.slot_of, best_sim);

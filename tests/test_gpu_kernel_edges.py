@@ -699,3 +699,19 @@ def test_attention_stream_equals_single_blocks(B, n, heads):
     B.litevggt_global_attn(ph, n, q, k, v, odd, ws)
     torch.cuda.synchronize()
     assert torch.equal(o, odd)
+
+
+# ------------------------------------------------------------------------------- matching of few tokens
+# 64 x 64 row tiles: one src row, whole tiles of both, one row more; one, three and five channel batches per
+# half, sixteen; the most dst tiles that are lists (4096 dst rows) and one more, and near the most workgroups
+@pytest.mark.parametrize("frames,h,w,special,ratio,dim", [(2, 1, 2, 0, 0.5, 64), (2, 8, 16, 0, 0.5, 192), (3, 8, 8, 0, 0.5, 320),
+                                                          (2, 64, 63, 0, 0.016, 64), (2, 64, 64, 0, 0.016, 64), (4, 37, 37, 5, 0.9, 128),
+                                                          (2, 37, 37, 5, 0.9, 1024), (30, 16, 16, 5, 0.9, 64)])
+def test_match_of_few_tokens(B, frames, h, w, special, ratio, dim):
+    import torch
+    ph = B.make_params(frames, h, w, dim, dim // 64, n_special=special, merge_ratio=ratio)
+    pl = B.litevggt_plan(ph)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(frames * dim)
+    x = torch.randn(pl.N, dim, generator=g, device="cuda").to(torch.bfloat16)
+    _check_index(B, ph, x)
