@@ -2287,6 +2287,7 @@ static size_t fp8_flag_words(int heads, int64_t n) { return (size_t)heads * 2 * 
 // Whether and how (see AttnCut): b blocks for kSlots slots per XCD; a slot without a first piece takes
 // k = ceil(b / idle slots) second pieces, each with a start of its own (about 6 stages of 64 keys).
 // A stage takes about 1 us with one workgroup per CU and 1.55 with two, and a cut about 9 us in all.
+// (Sequences whose 64-query blocks all fit, attn_is_short, do not come here.)
 // Measured with 16 heads, whole against cut: 1500 tokens 26 -> 22 us, 4500 111 -> 100, 5776 149 -> 137,
 // 3500 57.4 -> 56.  With a full round before them, blocks do not end together and the last round's
 // idle slots are not there to be had (15432 tokens 866 -> 876 us, 20000 1356 -> 1364): not cut.  Nor
