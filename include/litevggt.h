@@ -303,9 +303,9 @@ int litevggt_frame_attn(const litevggt_params *p, const void *q, const void *k, 
  *               void*) created by the caller; the driver records them on `stream` at the
  *               step boundaries of every layer (LV_EV_* below) so the caller can time each
  *               step inside a run.  On layers without a refresh the first four boundaries
- *               are recorded back to back.  With events == NULL the unmerge of a layer and the
- *               merge of the next one by the same index are one pass over the tokens (without
- *               frame_attn); the results are the same bits.
+ *               are recorded back to back.  With events == NULL the fusion of the score map and
+ *               the partition are one launch, and so are the unmerge of a layer and the merge of
+ *               the next one by the same index (without frame_attn); the results are the same bits.
  */
 enum {
   LV_EV_LAYER_BEGIN = 0,   /* before importance                                    */

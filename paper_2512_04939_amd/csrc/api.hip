@@ -340,15 +340,19 @@ int litevggt_layers_run(const litevggt_params *p, int n_layers, const void *imag
       }
       rc = launch_var_map(xx, d, p->var_pool, (float *)op_ws, st);
       if (rc) return rc;
-      rc = launch_ga_fuse(grad_cache, (const float *)op_ws, d, p->alpha, p->beta, score, st);
-      if (rc) return rc;
+      // fusion and partition are one launch, unless the caller times them
+      if (events) {
+        rc = launch_ga_fuse(grad_cache, (const float *)op_ws, d, p->alpha, p->beta, score, st);
+        if (rc) return rc;
+      }
     } else if (refresh) {
       rc = launch_naive_score(d, p->anchor_policy, p->policy_seed, score, st);
       if (rc) return rc;
     }
     if ((rc = mark(LV_EV_IMPORTANCE_END))) return rc;
     if (refresh) {
-      rc = launch_select(score, d, pl, *index, st);
+      rc = ga && !events ? launch_fuse_select(grad_cache, (const float *)op_ws, p->alpha, p->beta, score, d, pl, *index, st)
+                         : launch_select(score, d, pl, *index, st);
       if (rc) return rc;
     }
     if ((rc = mark(LV_EV_SELECT_END))) return rc;

@@ -88,6 +88,13 @@ __device__ __forceinline__ uint32_t xcd_contiguous(uint32_t b, uint32_t n) {
   return (b % kXcd) * per + b / kXcd;   // may be >= n: caller skips
 }
 
+// The fused score of one token: both maps min-max normalised over the frame (a flat map gives 0)
+__device__ __forceinline__ float ga_score(float g, float v, float glo, float gr, float vlo, float vr, float alpha, float beta) {
+  const float ng = gr > 0.f ? (g - glo) / gr : 0.f;
+  const float nv = vr > 0.f ? (v - vlo) / vr : 0.f;
+  return alpha * ng + beta * nv;
+}
+
 // LDS address (byte offset in the workgroup's LDS) of a __shared__ object
 __device__ __forceinline__ uint32_t lds_addr(const void *p) {
   return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const void *)p;

@@ -470,9 +470,7 @@ __global__ __launch_bounds__(64 * WAVES) void k_ga_fuse(const float *__restrict_
   }
   const float gr = ghi - glo, vr = vhi - vlo;
   for (int t = threadIdx.x; t < P; t += 64 * WAVES) {
-    float ng = gr > 0.f ? (g[t] - glo) / gr : 0.f;
-    float nv = vr > 0.f ? (v[t] - vlo) / vr : 0.f;
-    score[(size_t)blockIdx.x * P + t] = alpha * ng + beta * nv;
+    score[(size_t)blockIdx.x * P + t] = ga_score(g[t], v[t], glo, gr, vlo, vr, alpha, beta);
   }
 }
 

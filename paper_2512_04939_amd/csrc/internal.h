@@ -49,6 +49,10 @@ int static_importance_scratch(float **out);
 int launch_select(const float *score, const Dims &d, const litevggt_plan_t &pl,
                   const litevggt_index &ix, hipStream_t st);
 
+// launch_ga_fuse and launch_select in one
+int launch_fuse_select(const float *psi_g, const float *psi_v, float alpha, float beta, float *score, const Dims &d,
+                       const litevggt_plan_t &pl, const litevggt_index &ix, hipStream_t st);
+
 // match.hip
 // Scratch that the call asks for or, with `least`, that it does with: calls choose between ways by the
 // room there is, so that scratch of a longer sequence always serves a shorter one.

@@ -570,6 +570,7 @@ def test_layers_in_one_pass_equal_the_single_steps(B, frames, h, w, special, rat
         B.litevggt_unmerge(ph, y, ix, want, want)
     torch.cuda.synchronize()
     assert torch.equal(got.view(torch.int16), want.view(torch.int16))
+    assert torch.equal(maps[1], maps[3])         # the score map, fused on its own and with the partition
     assert not still or largest > 64
 
 
