@@ -2321,9 +2321,10 @@ static size_t cut_bytes(int heads, int64_t n, int n_seq) {
 // 112; 2 frames of 37 x 37 of 8 heads (352) 30.0 and 20.8.  The online kernel's steady loop is the slower one here
 // (its references are registers the loop would need): where its blocks can be cut, only up to one
 // per CU (8 heads: 2000 tokens 31.5 and 26.1, 3000 39.4 and 39.6, 4000 48.9 and 51.0).  A block that it leaves to
-// the second pass has sisters that are stored by then: not with a residual, which may be added in place.
-static bool attn_is_short(int64_t blocks, bool bounded, bool can_be_cut, bool has_res, int n_cu) {
-  if (!bounded && has_res) return false;
+// the second pass has sisters that are stored by then: not where o may be q, from which that pass starts again (a
+// residual may be added in place).
+static bool attn_is_short(int64_t blocks, bool bounded, bool can_be_cut, bool in_place, int n_cu) {
+  if (!bounded && in_place) return false;
   return blocks <= (bounded || !can_be_cut ? 2 * n_cu : n_cu);
 }
 
@@ -2409,7 +2410,7 @@ int launch_attn(const uint16_t *q, const uint16_t *k, const uint16_t *v, uint16_
       hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
     return LV_ERR_HIP;
   const int nqs = (int)((n + kQW - 1) / kQW);
-  const bool is_short = attn_is_short((int64_t)nqs * heads * n_seq, bounded, n_seq == 1 && heads % kXcd == 0, res != nullptr, n_cu);
+  const bool is_short = attn_is_short((int64_t)nqs * heads * n_seq, bounded, n_seq == 1 && heads % kXcd == 0, res || o == q, n_cu);
   AttnCut cut = {0, 0};
   if (!is_short && n_seq == 1 && !res && 2 * n_cu == kXcd * kSlots && ws_bytes >= attn_ws_bytes(heads, n, attn_dtype))
     cut = attn_cut(heads, n, bounded);

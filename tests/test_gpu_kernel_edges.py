@@ -634,6 +634,10 @@ def test_attention_short_blocks_left_to_the_second_pass(B, n, heads):
         for _, query, _ in spots[h % 4:h % 4 + 2]:      # a query meets both keys of its head
             want[h, query // 256] |= max(b for _, _, b in spots[h % 4:h % 4 + 2]) > 60
     assert np.array_equal(flags != 0, want)
+    # o in q's place: the second pass starts again from q, so no block of a flag may have been stored
+    B.litevggt_global_attn(ph, n, q, k, v, q, ws)
+    torch.cuda.synchronize()
+    assert float((q.double() - ref).abs().max() / ref.abs().max()) <= 2e-2
 
 
 # frames of a few hundred tokens with the residual added in place, in 64-query blocks and one frame beyond
