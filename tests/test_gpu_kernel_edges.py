@@ -57,6 +57,24 @@ def test_select_edges(B, h, w, special, ratio, kind):
     assert np.array_equal(_i32(ib.slot_of)[kept], np.arange(len(kept)))
 
 
+# 8 waves per frame: up to 512 patches, and one more; more than 512 frames, up to 2048 patches and one row
+# more; the last GA token's ties decided in the last digit
+@pytest.mark.parametrize("frames,h,w", [(3, 16, 32), (3, 19, 27), (512, 8, 65), (513, 8, 65), (513, 32, 64), (513, 33, 64)])
+def test_select_waves_per_frame(B, frames, h, w):
+    import torch
+    wl = synth.Workload("t", frames=frames, grid_h=h, grid_w=w, dim=64, heads=1, n_special=5, merge_ratio=0.75)
+    rng = np.random.default_rng(frames + h)
+    score = (np.float32(1.0) + np.float32(2.0 ** -23) * rng.integers(0, h * w, (frames, h * w))).astype(np.float32)
+    ref = O.select_anchors(score, oracle_params(wl))
+    ph = hip_params(wl)
+    ib = B.alloc_index(B.litevggt_plan(ph))
+    B.litevggt_select_anchors(ph, torch.from_numpy(score).cuda(), ib)
+    torch.cuda.synchronize()
+    assert np.array_equal(ib.role.cpu().numpy(), ref["role"])
+    for got, want in ((ib.kept_idx, "kept_idx"), (ib.dst_idx, "dst_idx"), (ib.src_idx, "src_idx")):
+        assert np.array_equal(_i32(got)[:len(ref[want])], ref[want])
+
+
 # ------------------------------------------------------------------------------- matching
 def _check_index(B, ph, x, near=1e-6):
     """Matching of bf16 rows x against every dst row in float64, and the groups it implies."""
