@@ -1,12 +1,27 @@
 // Merge (Sec. 3.4 merge equation) and unmerge (Sec. 3.4 "Token Unmerging").
 // Both are pure HBM streaming: every token row (dim bf16 values, 2 KB at dim 1024) is
 // read or written exactly once with 16-byte accesses per lane, whole rows per wave.
+#include <algorithm>
+#include <type_traits>
+
 #include "common.h"
 #include "internal.h"
 
 namespace lv {
 
-__device__ __forceinline__ void acc8(float (&a)[8], const u32x4 w) {
+__device__ __forceinline__ void acc_row(float (&a)[2], const uint32_t w) {
+  a[0] += bf16_lo(w);
+  a[1] += bf16_hi(w);
+}
+
+__device__ __forceinline__ void acc_row(float (&a)[4], const u32x2 w) {
+  a[0] += bf16_lo(w.x);
+  a[1] += bf16_hi(w.x);
+  a[2] += bf16_lo(w.y);
+  a[3] += bf16_hi(w.y);
+}
+
+__device__ __forceinline__ void acc_row(float (&a)[8], const u32x4 w) {
   a[0] += bf16_lo(w.x);
   a[1] += bf16_hi(w.x);
   a[2] += bf16_lo(w.y);
@@ -26,8 +41,15 @@ template <> struct MergeX<true> { typedef uint16_t *__restrict__ type; };
 #endif
 constexpr int kCoopSize = LV_MERGE_COOP;   // groups larger than this are summed by all 4 waves of a workgroup
 
-// two rows of eight bf16 values added, one rounding
-__device__ __forceinline__ u32x4 add8(const u32x4 v, const u32x4 w) {
+// two pieces of rows added, one rounding
+__device__ __forceinline__ uint32_t add_row(const uint32_t v, const uint32_t w) {
+  return pack_bf16(bf16_lo(v) + bf16_lo(w), bf16_hi(v) + bf16_hi(w));
+}
+__device__ __forceinline__ u32x2 add_row(const u32x2 v, const u32x2 w) {
+  return u32x2{pack_bf16(bf16_lo(v.x) + bf16_lo(w.x), bf16_hi(v.x) + bf16_hi(w.x)),
+               pack_bf16(bf16_lo(v.y) + bf16_lo(w.y), bf16_hi(v.y) + bf16_hi(w.y))};
+}
+__device__ __forceinline__ u32x4 add_row(const u32x4 v, const u32x4 w) {
   return u32x4{pack_bf16(bf16_lo(v.x) + bf16_lo(w.x), bf16_hi(v.x) + bf16_hi(w.x)),
                pack_bf16(bf16_lo(v.y) + bf16_lo(w.y), bf16_hi(v.y) + bf16_hi(w.y)),
                pack_bf16(bf16_lo(v.z) + bf16_lo(w.z), bf16_hi(v.z) + bf16_hi(w.z)),
@@ -59,35 +81,37 @@ __device__ __forceinline__ void sum_rows(const uint16_t *__restrict__ x,
 #pragma unroll
     for (int u = 0; u < R; ++u)
 #pragma unroll
-      for (int c = 0; c < CPL; ++c) acc8(a[c], w[u][c]);
+      for (int c = 0; c < CPL; ++c) acc_row(a[c], w[u][c]);
   }
 }
 
-// The same with row i becoming x[i] + y first (rounded to bf16 and stored; y: the slot's row).  The
+// The same with row i becoming x[i] + y first (rounded to bf16 and stored; y: the slot's row).  V: the piece of a
+// row that a lane holds, 64 CPL pieces in all from x on.  The
 // loads of a batch are issued ahead of the stores of the batch before it: loads and stores of a wave are
 // waited for in the order of their issue, so behind them they would wait for the stores as well.
-// Few rows per batch: the two batches' registers decide how many waves a SIMD holds (32 frames of 37 x 37
+// Few rows per batch: the two batches' registers decide how many waves a SIMD holds (with four rows of C = 1024
+// four; 32 frames of 37 x 37
 // patches, C = 1024, R = 8: 57 us, 4: 46, 2: 47; 200 frames 290, 254, 270; without the loads ahead 61 us).
-constexpr int kAddRows = 4;
-template <int CPL, int R>
-__device__ __forceinline__ void add_sum_rows(uint16_t *x, const u32x4 (&y)[CPL], const int32_t *__restrict__ group_mem,
-                                             int lo, int hi, int C, int nch, int lane, float (&a)[CPL][8]) {
+constexpr int kAddRows = 4, kAddRowsCoop = 16;
+template <typename V, int CPL, int R>
+__device__ __forceinline__ void add_sum_rows(uint16_t *x, const V (&y)[CPL], const int32_t *__restrict__ group_mem,
+                                             int lo, int hi, int C, int nch, int lane, float (&a)[CPL][sizeof(V) / 2]) {
   int r[2][R];
-  u32x4 w[2][R][CPL];
+  V w[2][R][CPL];
   auto index = [&](int j, int (&q)[R]) {
 #pragma unroll
     for (int u = 0; u < R; ++u) q[u] = j + u < hi ? group_mem[j + u] : -1;
   };
-  auto load = [&](const int (&q)[R], u32x4(&v)[R][CPL]) {
+  auto load = [&](const int (&q)[R], V(&v)[R][CPL]) {
 #pragma unroll
     for (int u = 0; u < R; ++u)
 #pragma unroll
       for (int c = 0; c < CPL; ++c) {
         const int ch = lane + 64 * c;
-        v[u][c] = (q[u] >= 0 && ch < nch) ? ((const u32x4 *)(x + (size_t)q[u] * C))[ch] : u32x4{0u, 0u, 0u, 0u};
+        v[u][c] = (q[u] >= 0 && ch < nch) ? ((const V *)(x + (size_t)q[u] * C))[ch] : V{};
       }
   };
-  auto step = [&](int j, int (&q)[R], u32x4(&v)[R][CPL], int (&qn)[R], u32x4(&vn)[R][CPL]) {
+  auto step = [&](int j, int (&q)[R], V(&v)[R][CPL], int (&qn)[R], V(&vn)[R][CPL]) {
     load(qn, vn);
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -96,10 +120,10 @@ __device__ __forceinline__ void add_sum_rows(uint16_t *x, const u32x4 (&y)[CPL],
       for (int c = 0; c < CPL; ++c) {
         const int ch = lane + 64 * c;
         if (q[u] >= 0 && ch < nch) {
-          v[u][c] = add8(y[c], v[u][c]);
-          ((u32x4 *)(x + (size_t)q[u] * C))[ch] = v[u][c];
+          v[u][c] = add_row(y[c], v[u][c]);
+          ((V *)(x + (size_t)q[u] * C))[ch] = v[u][c];
         }
-        acc8(a[c], v[u][c]);
+        acc_row(a[c], v[u][c]);
       }
     index(j + 2 * R, q);
   };
@@ -112,19 +136,20 @@ __device__ __forceinline__ void add_sum_rows(uint16_t *x, const u32x4 (&y)[CPL],
   }
 }
 
-template <int CPL>
+template <int CPL, int VALS>
 __device__ __forceinline__ void store_mean(uint16_t *__restrict__ z, int m, int C, int nch, int lane,
-                                           const float (&a)[CPL][8], float inv) {
+                                           const float (&a)[CPL][VALS], float inv) {
 #pragma unroll
   for (int c = 0; c < CPL; ++c) {
     const int ch = lane + 64 * c;
     if (ch < nch) {
-      u32x4 o;
-      o.x = pack_bf16(a[c][0] * inv, a[c][1] * inv);
-      o.y = pack_bf16(a[c][2] * inv, a[c][3] * inv);
-      o.z = pack_bf16(a[c][4] * inv, a[c][5] * inv);
-      o.w = pack_bf16(a[c][6] * inv, a[c][7] * inv);
-      ((u32x4 *)(z + (size_t)m * C))[ch] = o;
+      uint32_t o[VALS / 2];
+#pragma unroll
+      for (int i = 0; i < VALS / 2; ++i) o[i] = pack_bf16(a[c][2 * i] * inv, a[c][2 * i + 1] * inv);
+      uint32_t *row = (uint32_t *)(z + (size_t)m * C);
+      if constexpr (VALS == 8) ((u32x4 *)row)[ch] = u32x4{o[0], o[1], o[2], o[3]};
+      else if constexpr (VALS == 4) ((u32x2 *)row)[ch] = u32x2{o[0], o[1]};
+      else row[ch] = o[0];
     }
   }
 }
@@ -144,6 +169,14 @@ __device__ __forceinline__ void store_mean(uint16_t *__restrict__ z, int m, int 
 // gather y per token; C = 1024, 37 x 37 patches, both halves -> together: 32 frames at ratio 0.9
 // 56 -> 46 us (4.4 TB/s), 200 frames 358 -> 254 (5.0 TB/s), 48 frames at ratio 0.5 100 -> 74; two frames
 // of 16 x 16, C = 256 7.2 -> 3.9.
+// Its large groups are bound by the rows that a workgroup has in flight, a quarter of merge's where a wave holds two
+// batches of four whole rows.  So a workgroup takes a slice of the channels (128 up to 512 channels, else 256) of
+// 16 rows per batch and wave, in the same registers, and there are at least 512 of them, or as many as make sets of 8 slots
+// each.  Still scenes, both halves, together with whole rows by M / 64 workgroups, like this: 100 frames of 28 x 37 at ratio
+// 0.98 (groups of 100), C = 256 83, 135 and 34 us, C = 1024 190, 250 and 82; 500 of 16 x 16 (up to 645), C = 256, ratio 0.98
+// 63, 103 and 35; moving ones, 300 frames of 37 x 37 at a fourth refresh (1,718 groups hold 60 % of the tokens, up to 749)
+// 565, 430 and 373.  One group with nearly all tokens is one workgroup's in every way and stays slower than
+// the two halves: 38,193 of C = 1024 1,330, 3,700 and 1,550 us, 8,625 of C = 256 180, 515 and 310.
 constexpr int kScan = 64;
 
 template <int CPL, bool ADD>
@@ -151,59 +184,60 @@ __global__ __launch_bounds__(256) void k_merge(typename MergeX<ADD>::type x, con
                                                const int32_t *__restrict__ group_off,
                                                const int32_t *__restrict__ group_mem, int M,
                                                int C, int nb0, uint16_t *__restrict__ z) {
-  __shared__ float part[3][CPL * 64 * 8];
+  // cooperative pass: a lane's piece of a row, how many of them, values in one, and channels of a workgroup
+  using V = std::conditional_t<ADD, std::conditional_t<CPL == 1, uint32_t, u32x2>, u32x4>;
+  constexpr int kPieces = ADD ? 1 : CPL, kVals = sizeof(V) / 2, kSlice = 64 * kVals * kPieces;
+  __shared__ float part[3][kPieces * 64 * kVals];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int nch = C >> 3;
-  auto slot_row = [&](int m, u32x4(&row)[CPL]) {   // ADD: this lane's pieces of y[m]
-#pragma unroll
-    for (int c = 0; c < CPL; ++c) {
-      row[c] = u32x4{0u, 0u, 0u, 0u};
-      if (ADD && lane + 64 * c < nch) row[c] = ((const u32x4 *)(y + (size_t)m * C))[lane + 64 * c];
-    }
-  };
-  if ((int)blockIdx.x < nb0) {           // cooperative pass over the large groups of kScan slots
+  const int slices = (C + kSlice - 1) / kSlice;
+  if ((int)blockIdx.x < nb0 * slices) {  // cooperative pass over the large groups of kScan slots
+    const int set = (int)blockIdx.x / slices, ch0 = ((int)blockIdx.x - set * slices) * kSlice;   // first channel
+    const int pieces = (C - ch0) / kVals;
     // strided: neighbouring slots (the all-dst first frame) hold the largest groups
-    const int64_t ms = (int64_t)blockIdx.x + (int64_t)lane * nb0;
+    const int64_t ms = (int64_t)set + (int64_t)lane * nb0;
     const int bl = ms < M ? group_off[ms] : 0, el = ms < M ? group_off[ms + 1] : 0;
     uint64_t big = __builtin_amdgcn_ballot_w64(el - bl > kCoopSize);   // same in every wave
     while (big) {
       const int s = __builtin_ctzll(big);
       big &= big - 1;
-      const int m = (int)(blockIdx.x + (int64_t)s * nb0);   // < M: its lane passed the range check
+      const int m = (int)(set + (int64_t)s * nb0);   // < M: its lane passed the range check
       const int b = __builtin_amdgcn_readlane(bl, s), e = __builtin_amdgcn_readlane(el, s), n = e - b;
       const int per = (n + 3) >> 2;
       const int lo = min(b + wave * per, e), hi = min(lo + per, e);
-      float a[CPL][8];
+      float a[kPieces][kVals];
 #pragma unroll
-      for (int c = 0; c < CPL; ++c)
+      for (int c = 0; c < kPieces; ++c)
 #pragma unroll
-        for (int i = 0; i < 8; ++i) a[c][i] = 0.f;
-      u32x4 ym[CPL];
-      slot_row(m, ym);
-      if constexpr (ADD) add_sum_rows<CPL, kAddRows>(x, ym, group_mem, lo, hi, C, nch, lane, a);
-      else sum_rows<CPL, 16>(x, group_mem, lo, hi, C, nch, lane, a);
+        for (int i = 0; i < kVals; ++i) a[c][i] = 0.f;
+      if constexpr (ADD) {
+        const V ym[1] = {lane < pieces ? ((const V *)(y + (size_t)m * C + ch0))[lane] : V{}};
+        add_sum_rows<V, 1, kAddRowsCoop>(x + ch0, ym, group_mem, lo, hi, C, pieces, lane, a);
+      } else {
+        sum_rows<CPL, 16>(x, group_mem, lo, hi, C, pieces, lane, a);
+      }
       if (wave > 0) {
 #pragma unroll
-        for (int c = 0; c < CPL; ++c)
+        for (int c = 0; c < kPieces; ++c)
 #pragma unroll
-          for (int i = 0; i < 8; ++i) part[wave - 1][(c * 8 + i) * 64 + lane] = a[c][i];
+          for (int i = 0; i < kVals; ++i) part[wave - 1][(c * kVals + i) * 64 + lane] = a[c][i];
       }
       __syncthreads();
       if (wave == 0) {
 #pragma unroll
         for (int w = 0; w < 3; ++w)
 #pragma unroll
-          for (int c = 0; c < CPL; ++c)
+          for (int c = 0; c < kPieces; ++c)
 #pragma unroll
-            for (int i = 0; i < 8; ++i) a[c][i] += part[w][(c * 8 + i) * 64 + lane];
-        store_mean<CPL>(z, m, C, nch, lane, a, 1.0f / (float)n);
+            for (int i = 0; i < kVals; ++i) a[c][i] += part[w][(c * kVals + i) * 64 + lane];
+        store_mean(z + ch0, m, C, pieces, lane, a, 1.0f / (float)n);
       }
       __syncthreads();
     }
     return;
   }
-  const int m = ((int)blockIdx.x - nb0) * 4 + wave;   // own slot, if small
+  const int m = ((int)blockIdx.x - nb0 * slices) * 4 + wave;   // own slot, if small
   if (m < M) {
     const int b = group_off[m], e = group_off[m + 1];
     if (e - b <= kCoopSize) {
@@ -212,11 +246,16 @@ __global__ __launch_bounds__(256) void k_merge(typename MergeX<ADD>::type x, con
       for (int c = 0; c < CPL; ++c)
 #pragma unroll
         for (int i = 0; i < 8; ++i) a[c][i] = 0.f;
-      u32x4 ym[CPL];
-      slot_row(m, ym);
-      if constexpr (ADD) add_sum_rows<CPL, kAddRows>(x, ym, group_mem, b, e, C, nch, lane, a);
-      else sum_rows<CPL, 8>(x, group_mem, b, e, C, nch, lane, a);
-      store_mean<CPL>(z, m, C, nch, lane, a, 1.0f / (float)(e - b));
+      if constexpr (ADD) {
+        u32x4 ym[CPL];
+#pragma unroll
+        for (int c = 0; c < CPL; ++c)
+          ym[c] = lane + 64 * c < nch ? ((const u32x4 *)(y + (size_t)m * C))[lane + 64 * c] : u32x4{0u, 0u, 0u, 0u};
+        add_sum_rows<u32x4, CPL, kAddRows>(x, ym, group_mem, b, e, C, nch, lane, a);
+      } else {
+        sum_rows<CPL, 8>(x, group_mem, b, e, C, nch, lane, a);
+      }
+      store_mean(z, m, C, nch, lane, a, 1.0f / (float)(e - b));
     }
   }
 }
@@ -225,11 +264,13 @@ template <bool ADD>
 static int merge_rows(typename MergeX<ADD>::type x, const uint16_t *y, const Dims &d, int64_t M, const litevggt_index &ix,
                       uint16_t *z, hipStream_t st) {
   const int cpl = (d.C / 8 + 63) / 64;
-  const int nb0 = (int)((M + kScan - 1) / kScan);
-  const unsigned grid = (unsigned)(nb0 + (M + 3) / 4);
+  int64_t nb0 = (M + kScan - 1) / kScan;
+  const int slice = cpl == 1 ? 128 : 256, slices = ADD ? (d.C + slice - 1) / slice : 1;   // kSlice
+  if (ADD) nb0 = std::max(nb0, std::min<int64_t>(512 / slices, (M + 7) / 8));
+  const unsigned grid = (unsigned)(nb0 * slices + (M + 3) / 4);
 #define LV_MERGE(CPL)                                                                                     \
   hipLaunchKernelGGL((k_merge<CPL, ADD>), dim3(grid), dim3(256), 0, st, x, y, ix.group_off, ix.group_mem, \
-                     (int)M, d.C, nb0, z)
+                     (int)M, d.C, (int)nb0, z)
   switch (cpl) {
     case 1: LV_MERGE(1); break;
     case 2: LV_MERGE(2); break;
@@ -281,7 +322,7 @@ __global__ __launch_bounds__(256) void k_unmerge(const uint16_t *__restrict__ y,
       for (int r = 0; r < R; ++r) {
         if (i0 + r >= N) break;
         u32x4 v = w[r];
-        if (RES) v = add8(v, res[r]);
+        if (RES) v = add_row(v, res[r]);
         __builtin_nontemporal_store(v, (u32x4 *)(out + (size_t)(i0 + r) * C) + ch);
       }
     }

@@ -592,6 +592,77 @@ def test_layers_in_one_pass_equal_the_single_steps(B, frames, h, w, special, rat
     assert not still or largest > 64
 
 
+# The same with large groups whose rows go to several workgroups by channels: 128 at a time up to 512
+# channels (two and three slices, the last one of half a slice), 256 at a time beyond; one group with nearly every token
+@pytest.mark.parametrize("frames,h,w,special,ratio,dim,blank", [(80, 5, 6, 2, 0.9, 256, False), (70, 4, 4, 0, 0.9, 320, False),
+                                                                (80, 4, 4, 1, 0.9, 1024, False), (90, 6, 6, 5, 0.98, 960, False),
+                                                                (9, 20, 20, 5, 0.9, 768, True), (9, 20, 20, 0, 0.9, 64, True)])
+def test_large_groups_in_one_pass_equal_the_single_steps(B, frames, h, w, special, ratio, dim, blank):
+    import torch
+    g = torch.Generator(device="cuda")
+    g.manual_seed(frames + dim)
+    wl = synth.Workload("t", frames=frames, grid_h=h, grid_w=w, dim=dim, heads=dim // 64, n_special=special, merge_ratio=ratio)
+    ph = hip_params(wl)
+    pl = B.litevggt_plan(ph)
+    x = torch.randn(frames, h * w + special, dim, generator=g, device="cuda")
+    x[:, special:] = x[0, special:] + (0.0 if blank else 0.1) * x[:, special:]      # a still scene
+    if blank:
+        x[:, special:] = x[0, special]
+    x = x.reshape(pl.N, dim).to(torch.bfloat16)
+    images = torch.rand(frames, 3, h * ph.patch, w * ph.patch, generator=g, device="cuda")
+    grad, score = (torch.empty(frames, h * w, device="cuda") for _ in range(2))
+    ib, ws = B.alloc_index(pl), B.alloc_ws(pl.ws_bytes)
+    got, want = x.clone(), x.clone()
+    B.litevggt_layers_run(ph, 3, images, got, ib, grad, score, ws)
+    z = torch.empty(pl.M, dim, dtype=torch.bfloat16, device="cuda")
+    y = torch.empty_like(z)
+    for _ in range(3):
+        B.litevggt_merge(ph, want, ib, z)
+        B.litevggt_global_attn(ph, pl.M, z, z, z, y, ws)
+        B.litevggt_unmerge(ph, y, ib, want, want)
+    torch.cuda.synchronize()
+    assert torch.equal(got.view(torch.int16), want.view(torch.int16))
+    largest = int(ib.group_off[1:].sub(ib.group_off[:-1]).max())
+    assert largest > (pl.n_src if blank else 64)
+
+
+# With a block y is the block's delta, z feeds its LayerNorms and the packed weights are kept across the layers
+@pytest.mark.parametrize("frames,h,w,dim,still", [(2, 16, 16, 256, False), (80, 5, 6, 256, True), (3, 12, 13, 768, False)])
+def test_layers_with_a_block_in_one_pass_equal_the_single_steps(B, frames, h, w, dim, still):
+    import torch
+    g = torch.Generator(device="cuda")
+    g.manual_seed(frames + dim)
+    t = {k: torch.from_numpy(v).cuda() for k, v in synth.block_weights(dim, seed=frames).items()}
+    t = {k: v.to(torch.bfloat16) if k.startswith("w_") else v for k, v in t.items()}
+    bw = B.block_weights(t)
+    wl = synth.Workload("t", frames=frames, grid_h=h, grid_w=w, dim=dim, heads=dim // 64, n_special=5, merge_ratio=0.9,
+                        refresh_interval=3)
+    ph = hip_params(wl, block=bw)
+    pl = B.litevggt_plan(ph)
+    x = torch.randn(frames, h * w + 5, dim, generator=g, device="cuda")
+    if still:
+        x[:, 5:] = x[0, 5:] + 0.1 * x[:, 5:]
+    x = x.reshape(pl.N, dim).to(torch.bfloat16)
+    images = torch.rand(frames, 3, h * ph.patch, w * ph.patch, generator=g, device="cuda")
+    maps = [torch.empty(frames, h * w, device="cuda") for _ in range(4)]
+    ib, ix, ws = B.alloc_index(pl), B.alloc_index(pl), B.alloc_ws(pl.ws_bytes)
+    got, want = x.clone(), x.clone()
+    B.litevggt_layers_run(ph, 5, images, got, ib, maps[0], maps[1], ws)
+    z = torch.empty(pl.M, dim, dtype=torch.bfloat16, device="cuda")
+    y = torch.empty_like(z)
+    for l in range(5):
+        if l % 3 == 0:
+            B.litevggt_importance(ph, images, want, maps[2], l == 0, maps[3], ws)
+            B.litevggt_select_anchors(ph, maps[3], ix)
+            B.litevggt_match(ph, want, ix, None, ws)
+        B.litevggt_merge(ph, want, ix, z)
+        B.litevggt_global_block(ph, pl.M, z, bw, y, B.alloc_ws(B.litevggt_global_block_ws_bytes(ph, pl.M)))
+        B.litevggt_unmerge(ph, y, ix, want, want)
+    torch.cuda.synchronize()
+    assert torch.equal(got.view(torch.int16), want.view(torch.int16))
+    assert not still or int(ix.group_off[1:].sub(ix.group_off[:-1]).max()) > 64
+
+
 # ------------------------------------------------------------------------------- short sequences, attention
 # 64-query blocks whose waves share the keys out: waves without a key tile (1 to 96 tokens), the last tile
 # with one key, whole tiles, one tile more for one wave, the most blocks that are taken this way and one
