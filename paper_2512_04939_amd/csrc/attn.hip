@@ -979,6 +979,8 @@ constexpr int kStreamStages = 4;     // key stages of a sequence, at least
 constexpr int kStreamMost = 1024;    // ... and at most (65,536 keys): the seam is nothing beside a longer block (100,000
                                      // tokens level, 143,232 level on one box and 3 % slower on another)
 constexpr int kStreamWords = 8 * 8;  // counters: one per XCD, 32 bytes apart
+constexpr int kGiveWayStages = 32;   // (2,525 tokens, up to two rounds: 0.98 of one launch per block with, 0.96 without; 1,805
+                                     // 0.98 and 1.00, 765 0.99 and 1.06)
 
 template <bool PACKED, bool RES>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_attn_bf16_stream(
@@ -1139,12 +1141,31 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     place(blk);
   };
 
+  // Of a CU's two workgroups the hardware lets the older one issue first.  One that takes block after block would stay the
+  // older one, be ahead for good and leave its partner alone with most of a block at the end.  So a workgroup gives way
+  // with each block it takes, as a new workgroup would to the one beside it.  Not up to two rounds where the last one fills no
+  // more than half of the slots, which the workgroups that are ahead take one per CU, nor with long blocks there (2 to 4 %
+  // the other way).  One launch per block, without, with, us: 16 heads, 20 frames of 760 tokens (1.9 rounds) 74.6 82.7 74.1,
+  // 17 of 1600 (3.7) 220 230 215, 12 heads, 15 of 28 x 37 83.2 90.9 81.2.
+  const int rounds = (in_list - 1) / slots, last_round = in_list - rounds * slots;   // full rounds, blocks of the last one
+  const bool give_way = rounds >= 2 || (last_round * 2 > slots && nkv <= kGiveWayStages);
+  int taken_blocks = 0;
+  auto take_turn = [&]() {
+    switch (taken_blocks++ & 3) {
+      case 0: __builtin_amdgcn_s_setprio(3); break;
+      case 1: __builtin_amdgcn_s_setprio(2); break;
+      case 2: __builtin_amdgcn_s_setprio(1); break;
+      default: __builtin_amdgcn_s_setprio(0);
+    }
+  };
+
   place(blk);
   fetch(0);
   fetch(1);
   load_q();
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   while (true) {
+    if (give_way) take_turn();
     const int64_t q0 = (int64_t)qb * kBQB + wave * kQW;
     const int seq = sh / heads, head = sh - seq * heads;
     uint16_t *const ob = o + (size_t)seq * n * C;
