@@ -1125,12 +1125,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_sched_barrier(0);
   };
-  // When the next block's number is asked for: where the last round fills no more than half of the slots, at a
-  // block's first stage, in the order in which the slots were filled, one per CU before two, so that its blocks
-  // have a CU to themselves (it is worth 1.5 times the rate); else as late as the answer can be waited for, so
-  // that who is ahead takes it.  16 heads, in one launch per block, early, late: 17000 tokens (2.09 rounds)
-  // 1098 1088 1126 us, 13500 (1.66) 691 705 664, 30000 (3.69) 3076 3105 3021.
-  const int claim_at = in_list % slots * 2 <= slots ? 0 : nkv - kStreamStages;
+  // The next block's number is asked for as late as the answer can be waited for, so that who is ahead takes it.
+  // (At a block's first stage where the last round fills no more than half of the slots, in the hope that its blocks then
+  // go to one workgroup per CU: level with this where every XCD has its own counter, and where all share one they went
+  // to the XCDs that it answered first: 12 heads, one launch per block, early, late, us: 16,384 tokens (1.5 rounds)
+  // 710 883 701, 35,384 (3.3) 3312 3530 3192; 16 heads, 16,384 (2) 936 972 920.)
   bool more = true;
   auto turn = [&]() {      // the workgroup's next block (or none: this one's stages again, into slots nobody reads)
     int nb;
@@ -1220,7 +1219,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       uint32_t taken = 0u;
 #pragma unroll 1
       for (int i = 0; i < nkv - 3; ++i) {
-        if (i == claim_at && tid == 0)
+        if (i == nkv - kStreamStages && tid == 0)
           taken = __hip_atomic_fetch_add(ctr + list * 8, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         int st = i + 3;
         asm volatile("" : "+s"(st));   // (addresses from the stage number, not carried along: the recipe counts their arithmetic)
