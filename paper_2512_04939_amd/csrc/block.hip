@@ -688,7 +688,7 @@ __global__ __launch_bounds__((GemmShape<BM, BN>::kThreads * KG)) __attribute__((
   read_frags(0, 0, fb[0][0], fa[0][0]);
   read_frags(0, 1, fb[0][1], fa[0][1]);
   constexpr int kSetB = kTwoSets ? 1 : 0;   // the weight set of odd stages
-  for (int g = 0; g < total; g += 2) {       // (an even number of stages: K is a multiple of 128)
+  for (int g = 0; g < total; g += 2) {       // (an even number of stages in each K group: K is a multiple of 256)
     stage(g, fb[0], fa[0], fb[kSetB], fa[1]);
     stage(g + 1, fb[kSetB], fa[1], fb[0], fa[0]);
   }
@@ -971,7 +971,7 @@ static int launch_linear(const uint16_t *A, int64_t M, int K, int Nout,
                          hipStream_t st, const LinearOpts &o) {
   if (!o.w_packed || (o.fp8 && !o.sc) || (o.current && (o.a_packed || o.pack_out))) return LV_ERR_PARAM;
   if (o.pack_out && (o.addend || split != Nout || (o.fp8 && (!o.out_inv || !o.out_amax)))) return LV_ERR_PARAM;
-  if (K % 128 != 0 || Nout % kTile != 0 || split % kTile != 0 || Nout % split != 0) return LV_ERR_SHAPE;
+  if (K % 256 != 0 || Nout % kTile != 0 || split % kTile != 0 || Nout % split != 0) return LV_ERR_SHAPE;
   int rc;
   if (w.Mp / 128 * (Nout / 128) >= ((int64_t)1 << 30) || w.Mp >= ((int64_t)1 << 31)) return LV_ERR_SHAPE;
   int dev = 0, n_cu = 0;
