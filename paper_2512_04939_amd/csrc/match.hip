@@ -517,7 +517,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
   const uint32_t lb = xcd_contiguous(blockIdx.x, (uint32_t)(n_st * n_dt));   // an XCD's workgroups share src tiles
   if (lb >= (uint32_t)(n_st * n_dt)) return;
   const int st = lb / n_dt, dt = lb % n_dt;
-  const int nb = KS >> 2;                    // batches of two k-steps in this wave's half of the channels
+  const int nb = KS >> 2;                    // batches of two k-steps in this wave's half of the channels (C % 64 == 0)
   const u32x4 *ap = dstp + ((size_t)(dt * 2) * KS + kg * (KS >> 1)) * 64 + lane;
   const u32x4 *bp = srcp + ((size_t)(st * 2 + wn) * KS + kg * (KS >> 1)) * 64 + lane;
   u32x4 fa[4][2][2], fb[4][2];               // [batch & 3][k-step][dst half]
@@ -1123,7 +1123,7 @@ int launch_match(const uint16_t *x, const Dims &d, const litevggt_plan_t &pl,
   MatchWs w = carve(d, pl, ws_bytes < match_ws_bytes(d, pl), (char *)ws);
   const int n_src = (int)pl.n_src, n_dst = (int)pl.n_dst;
   if (n_src > 0) {
-    if (d.C % 32 != 0 || n_dst <= 0) return LV_ERR_SHAPE;
+    if (d.C % 64 != 0 || n_dst <= 0) return LV_ERR_SHAPE;   // (64: k_match_small)
     // 128 KB ring (reused for the final merge) + per wave kInvBufs buffers of 64 inverse norms
     // and two buffers of 8 x 4 x 32 second-best bounds the waves of a column exchange
     const size_t lds = (size_t)kGStages * kGStageU4 * 16 + 8 * kInvBufs * 64 * sizeof(float) + 2 * 1024 * sizeof(float);
