@@ -2354,8 +2354,9 @@ static bool attn_is_short(int64_t blocks, bool bounded, bool can_be_cut, bool in
 size_t attn_ws_bytes(int heads, int64_t n_tokens, int attn_dtype, int n_seq, bool least) {
   const size_t elem = attn_dtype == LV_ATTN_FP8_E4M3 ? sizeof(u32x2) : sizeof(u32x4);
   const size_t per = (size_t)heads * n_seq * n_key_tiles(n_tokens) * 4 * kFragU4 * elem;
-  // [amax block][K fragments][V fragments]; FP8: a second pair of K/V arrays in the layout of
-  // the second-pass kernel, and the flags
+  // [amax block][K fragments][V fragments]; FP8: the first pair is the running-maximum kernel's (with qk_norm the
+  // workgroups' maxima lie there until K is written), the second the bounded kernel's and its second pass', then
+  // the flags.  No call uses both pairs; they stay apart because callers have sized their scratch by this.
   size_t total = 256 + 2 * align_up(per, 256);
   if (attn_dtype == LV_ATTN_FP8_E4M3) total += 2 * align_up(per, 256) + align_up(fp8_flag_words(heads, n_tokens) * 4, 256);
   // bf16: the flags of the online-softmax pass (one word per 256-query block)
@@ -2447,15 +2448,15 @@ int launch_attn(const uint16_t *q, const uint16_t *k, const uint16_t *v, uint16_
                       n_cu % 4 == 0 && (((uintptr_t)o | (uintptr_t)res) & 15u) == 0;
   auto pack_kernel = [&](auto has_sync) {
     constexpr bool SYNC = decltype(has_sync)::value;
-    uint32_t *const words = stream ? ctr : sync;
-    const int n_words = stream ? kStreamWords : kSyncWords;
+    uint32_t *const cleared = stream ? ctr : sync;
+    const int n_cleared = stream ? kStreamWords : kSyncWords;
     const dim3 grid((unsigned)n_kt, (unsigned)(heads * n_seq));
     if (bounded)
-      hipLaunchKernelGGL((k_attn_pack<SYNC, false>), grid, dim3(256), 0, st, k, v, n, heads, n_kt, qk_norm, kp, vp, words,
-                         n_words, redo, 0);
+      hipLaunchKernelGGL((k_attn_pack<SYNC, false>), grid, dim3(256), 0, st, k, v, n, heads, n_kt, qk_norm, kp, vp, cleared,
+                         n_cleared, redo, 0);
     else
-      hipLaunchKernelGGL((k_attn_pack<SYNC, true>), grid, dim3(256), 0, st, k, v, n, heads, n_kt, qk_norm, kp, vp, words,
-                         n_words, redo, 2 * nqb);
+      hipLaunchKernelGGL((k_attn_pack<SYNC, true>), grid, dim3(256), 0, st, k, v, n, heads, n_kt, qk_norm, kp, vp, cleared,
+                         n_cleared, redo, 2 * nqb);
   };
   if (cut.n_cut || stream) pack_kernel(std::true_type{});
   else pack_kernel(std::false_type{});

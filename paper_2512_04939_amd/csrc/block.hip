@@ -939,6 +939,10 @@ struct LinearOpts {
 //   M =  394: 11.2 10.7 13.8 30.9    9.8 6.4 11.0 14.9      M = 2200: 19.8 12.2 33.7 36.5   (the same) (the same) (the same) 31.6
 //   M = 1000: 12.2 11.2 14.5 30.9   (the same) 7.7 (the same) 16.7     E4M3, M = 394: 8.5 8.4 13.4 19.6    7.4 5.4 8.9 9.8
 // (64 x 64 without groups 22.6 for MLP 2 at M = 394, 128 x 128 with them 25.7, 64 x 64 in four groups 14.7.)
+// Whole blocks with and without the 64 x 64 tiles, bf16 and E4M3 layers (delayed scaling), us: C = 256, where the output layers take them
+// up to 8,192 rows: M = 394 42.6 and 53.4, 55.9 and 65.3; 2048 55.6 and 64.8, 73.7 and 79.7; 4096 69.7 and 74.9, 87.2 and 92.5;
+// 8192 131.2 and 133.6, E4M3 level.  C = 512: 1000 61.9 and 73.1, 72.8 and 80.8; 4096 112.4 and 114.3, 124.7 and 126.7.
+// The costs below are bf16's; E4M3 layers take the same shapes.
 enum TileShape { kTile256x256, kTile128x256, kTile128x128, kTile128x128K2, kTile64x64K2 };
 static TileShape tile_shape(int64_t M, int Nout, int K, bool fp8, int n_cu) {
   if ((M + 63) / 64 * (Nout / 64) <= 2 * n_cu) return kTile64x64K2;

@@ -504,7 +504,9 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 constexpr int kSmallTile = 64;       // src and dst rows of a workgroup
 // Workgroups at most, four rounds of two per CU.  One refresh, otherwise -> this way: 2 frames of 16 x 16, C = 256 (10 of
 // them) 39.4 -> 24.2 us; C = 1024: 2 frames of 37 x 37 (460) 68.1 -> 44.0, 3 (975) 79.0 -> 60.2, 4 (1566) 86.0 -> 75.9, 5
-// (2156) 85.8 and 85.7, 6 (2910) 85.4 and 100.4.
+// (2156) 85.8 and 85.7, 6 (2910) 85.4 and 100.4.  The line lies here at every width: C = 256, 24 frames of 16 x 16 at the fixed
+// rule (1647) 57.6 -> 52.1, 32 at ratio 0.5 (2170) 58.3 and 57.8, 6 of 37 x 37 (2910) 63.1 and 68.7; C = 64 (1647) 50.8 -> 47.4,
+// (2170) 49.6 and 49.2, (2910) 55.3 and 59.3.
 constexpr int kSmallTiles = 2048;
 
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_match_small(
@@ -996,7 +998,8 @@ __global__ __launch_bounds__(256) void k_csr_finish(const uint32_t *__restrict__
 // counters of all digits and waves.  The elements are in registers while they are moved, so one
 // LDS array serves both passes.  Up to kCsrSmall tokens, where its time on one CU is below the three
 // launches of the general way.  One refresh call, this way against that: 2,748 tokens 53.5 and 61.3 us, 4,122 58.3 and
-// 61.3, 6,870 63.7 and 61.5, 10,992 84.3 and 75.1, 15,114 95.6 and 78.5.
+// 61.3, 6,870 63.7 and 61.5, 10,992 84.3 and 75.1, 15,114 95.6 and 78.5.  With at most 256 slots the general way is one digit
+// pass in four launches: 2,448 tokens 35.0 and 37.8, 4,320 38.3 and 38.0, 6,400 39.8 and 33.1.
 constexpr int kCsrSmall = 5120;
 constexpr int kCsrSteps = kCsrSmall / 1024;   // 64-element steps per wave, at most
 
