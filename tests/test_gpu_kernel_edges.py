@@ -414,9 +414,12 @@ def _attn64(q, k, v, norm, heads):
 
 
 # short sequences whose blocks are cut along the keys (8 XCDs with 64 slots): 12 blocks per XCD in
-# halves, 17 and 46 (three second pieces per idle slot, a ragged last block and key stage), 63 (nothing
-# to gain, not cut), 65 (more than a round, not cut), 33 with a last block of one query
-@pytest.mark.parametrize("n,heads", [(1500, 16), (4352, 8), (11709, 8), (5776, 16), (16640, 8), (16128, 8), (8193, 8)])
+# halves (as given: normalised they are 64-query blocks), 17 and 46 (as given; normalised 17 stay whole; 46: three second
+# pieces per idle slot, a ragged last block and key stage), 63 (nothing
+# to gain, not cut), 65 (more than a round, not cut), 33 with a last block of one query; 28 and 32, cut in halves
+# normalised as well
+@pytest.mark.parametrize("n,heads", [(1500, 16), (4352, 8), (11709, 8), (5776, 16), (16640, 8), (16128, 8), (8193, 8), (3500, 16),
+                                     (4096, 16)])
 @pytest.mark.parametrize("kind", ["norm", "plain", "climbing"])
 def test_attention_cut_rounds(B, n, heads, kind):
     import torch
@@ -488,8 +491,9 @@ def test_attention_cut_blocks_left_to_the_second_pass(B, n):
 
 # ------------------------------------------------------------------------------- scratch
 # scratch sized for a longer sequence serves a shorter one that would ask for more: cut attention blocks
-# (2000 of 2050 tokens, 14800 of 14850) and matching schedules with many partial results
-@pytest.mark.parametrize("short,long,heads", [(2000, 2050, 16), (14800, 14850, 8)])
+# (2000 of 2050 tokens as given; normalised they are 64-query blocks; 14800 of 14850, 5776 of 7000) and matching
+# schedules with many partial results
+@pytest.mark.parametrize("short,long,heads", [(2000, 2050, 16), (14800, 14850, 8), (5776, 7000, 16)])
 @pytest.mark.parametrize("norm", [1, 0])
 def test_attention_in_scratch_of_a_longer_sequence(B, short, long, heads, norm):
     import torch
@@ -510,19 +514,21 @@ def test_attention_in_scratch_of_a_longer_sequence(B, short, long, heads, norm):
     assert bool((ws[used:] == 0x5a).all())
 
 
-def test_block_in_scratch_of_a_longer_sequence(B):
+# (the attention of 2000 tokens in 64-query blocks, of 6900 in cut blocks where there is room)
+@pytest.mark.parametrize("short,long", [(2000, 2050), (6900, 6950)])
+def test_block_in_scratch_of_a_longer_sequence(B, short, long):
     import torch
     w = synth.block_weights(1024, seed=1)
     t = {k: torch.from_numpy(v).cuda() for k, v in w.items()}
     t = {k: v.to(torch.bfloat16) if k.startswith("w_") else v for k, v in t.items()}
     g = torch.Generator(device="cuda")
     g.manual_seed(1)
-    z = torch.randn(2000, 1024, generator=g, device="cuda").to(torch.bfloat16)
+    z = torch.randn(short, 1024, generator=g, device="cuda").to(torch.bfloat16)
     ph = B.make_params(1, 1, 1, 1024, 16, n_special=0, qk_norm=1)
-    need = B.litevggt_global_block_ws_bytes(ph, 2050)
-    assert need + 512 < B.litevggt_global_block_ws_bytes(ph, 2000)
+    need = B.litevggt_global_block_ws_bytes(ph, long)
+    assert need + 512 < B.litevggt_global_block_ws_bytes(ph, short)
     delta = torch.full_like(z, float("nan"))
-    B.litevggt_global_block(ph, 2000, z, B.block_weights(t), delta, B.alloc_ws(need))
+    B.litevggt_global_block(ph, short, z, B.block_weights(t), delta, B.alloc_ws(need))
     torch.cuda.synchronize()
     ref = _block64(z, t, 16)
     assert float((delta.double() - ref).abs().max() / ref.abs().max()) <= 2e-2
@@ -750,10 +756,12 @@ def test_frame_attention_short_frames_in_place(B, frames, h, w, heads, norm):
 # more 256-query blocks than slots, in workgroups that stay: the fewest key stages (4) and one fewer, a
 # last stage of one key and a whole one, last blocks with one, two and all waves at work, one list for all
 # XCDs (pairs no multiple of 8), tails of the last round up to half of the slots and beyond, residual in
-# place and none, an output that is 8-byte aligned only
+# place and none, an output that is 8-byte aligned only; six blocks per slot (priorities that come round again) with
+# one list and with eight
 @pytest.mark.parametrize("frames,h,w,heads,res", [(65, 14, 18, 8, 1), (65, 12, 16, 8, 1), (65, 11, 17, 8, 1), (90, 14, 18, 3, 1),
                                                   (33, 16, 16, 16, 1), (43, 17, 18, 7, 0), (40, 24, 25, 6, 1), (20, 37, 37, 8, 1),
-                                                  (20, 37, 37, 8, 8), (13, 28, 37, 12, 1)])
+                                                  (20, 37, 37, 8, 8), (13, 28, 37, 12, 1), (300, 11, 23, 5, 1),
+                                                  (200, 15, 17, 8, 0)])
 def test_attention_blocks_in_a_stream(B, frames, h, w, heads, res):
     import torch
     n = h * w + 5
