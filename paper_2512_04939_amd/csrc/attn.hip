@@ -1125,14 +1125,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_sched_barrier(0);
   };
-  const int rounds = (in_list - 1) / slots, last_round = in_list - rounds * slots;   // full rounds, blocks of the last one
-  // The next block's number is asked for as late as the answer can be waited for, so that who is ahead takes it; where
-  // every XCD has its own counter and one round and a last one of half of the slots at most are to be done, at the first
-  // stage, in the order in which the slots were filled, one per CU before two (frames of 260 and 400 tokens up to 1 % faster, else level).
-  // Where all XCDs share a counter such numbers go to those that it answers first, and behind two rounds the slots' order
-  // is lost: 12 heads, one launch per block, early, late, us: 16,384 tokens (1.5 rounds) 710 883 701, 35,384 (3.3) 3312 3530 3192;
-  // 16 heads, 16,384 (2) 936 972 920.
-  const int claim_at = lists == 8 && rounds < 2 && last_round * 2 <= slots ? 0 : nkv - kStreamStages;
+  // The next block's number is asked for as late as the answer can be waited for, so that who is ahead takes it.
+  // (At a block's first stage where the last round fills no more than half of the slots, in the hope that its blocks then
+  // go to one workgroup per CU: level with this where every XCD has its own counter, and where all share one they went
+  // to the XCDs that it answered first: 12 heads, one launch per block, early, late, us: 16,384 tokens (1.5 rounds)
+  // 710 883 701, 35,384 (3.3) 3312 3530 3192; 16 heads, 16,384 (2) 936 972 920.)
   bool more = true;
   auto turn = [&]() {      // the workgroup's next block (or none: this one's stages again, into slots nobody reads)
     int nb;
@@ -1149,6 +1146,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   // more than half of the slots, which the workgroups that are ahead take one per CU, nor with long blocks there (2 to 4 %
   // the other way).  One launch per block, without, with, us: 16 heads, 20 frames of 760 tokens (1.9 rounds) 74.6 82.7 74.1,
   // 17 of 1600 (3.7) 220 230 215, 12 heads, 15 of 28 x 37 83.2 90.9 81.2.
+  const int rounds = (in_list - 1) / slots, last_round = in_list - rounds * slots;   // full rounds, blocks of the last one
   const bool give_way = rounds >= 2 || (last_round * 2 > slots && nkv <= kGiveWayStages);
   int taken_blocks = 0;
   auto take_turn = [&]() {
@@ -1221,7 +1219,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       uint32_t taken = 0u;
 #pragma unroll 1
       for (int i = 0; i < nkv - 3; ++i) {
-        if (i == claim_at && tid == 0)
+        if (i == nkv - kStreamStages && tid == 0)
           taken = __hip_atomic_fetch_add(ctr + list * 8, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         int st = i + 3;
         asm volatile("" : "+s"(st));   // (addresses from the stage number, not carried along: the recipe counts their arithmetic)
