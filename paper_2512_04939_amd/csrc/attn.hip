@@ -1127,9 +1127,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   };
   // The next block's number is asked for as late as the answer can be waited for, so that who is ahead takes it.
   // (At a block's first stage where the last round fills no more than half of the slots, in the hope that its blocks then
-  // go to one workgroup per CU: level with this where every XCD has its own counter, and where all share one they went
-  // to the XCDs that it answered first: 12 heads, one launch per block, early, late, us: 16,384 tokens (1.5 rounds)
-  // 710 883 701, 35,384 (3.3) 3312 3530 3192; 16 heads, 16,384 (2) 936 972 920.)
+  // go to one workgroup per CU: level with this at best where every XCD has its own counter, and now and then, behind a
+  // kernel that leaves the slots in another order, two to a CU after all: blocks of E4M3 layers, 12,000 tokens, 900 or 960 us, late
+  // 900.  Where all XCDs share a counter they went to those that it answered first: 12 heads, one launch per block, early,
+  // late, us: 16,384 tokens (1.5 rounds) 710 883 701, 35,384 (3.3) 3312 3530 3192; 16 heads, 16,384 (2) 936 972 920.)
   bool more = true;
   auto turn = [&]() {      // the workgroup's next block (or none: this one's stages again, into slots nobody reads)
     int nb;
