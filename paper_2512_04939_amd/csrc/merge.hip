@@ -1,6 +1,7 @@
 // Merge (Sec. 3.4 merge equation) and unmerge (Sec. 3.4 "Token Unmerging").
 // Both are pure HBM streaming: every token row (dim bf16 values, 2 KB at dim 1024) is
-// read or written exactly once with 16-byte accesses per lane, whole rows per wave.
+// read or written exactly once with 16-byte accesses per lane, whole rows per wave (large groups
+// in the pass that does both: slices of rows, 4 or 8 bytes per lane).
 #include <algorithm>
 #include <type_traits>
 
@@ -172,11 +173,11 @@ __device__ __forceinline__ void store_mean(uint16_t *__restrict__ z, int m, int 
 // Its large groups are bound by the rows that a workgroup has in flight, a quarter of merge's where a wave holds two
 // batches of four whole rows.  So a workgroup takes a slice of the channels (128 up to 512 channels, else 256) of
 // 16 rows per batch and wave, in the same registers, and there are at least 512 of them, or as many as make sets of 8 slots
-// each.  Still scenes, both halves, together with whole rows by M / 64 workgroups, like this: 100 frames of 28 x 37 at ratio
-// 0.98 (groups of 100), C = 256 83, 135 and 34 us, C = 1024 190, 250 and 82; 500 of 16 x 16 (up to 645), C = 256, ratio 0.98
-// 63, 103 and 35; moving ones, 300 frames of 37 x 37 at a fourth refresh (1,718 groups hold 60 % of the tokens, up to 749)
-// 565, 430 and 373.  One group with nearly all tokens is one workgroup's in every way and stays slower than
-// the two halves: 38,193 of C = 1024 1,330, 3,700 and 1,550 us, 8,625 of C = 256 180, 515 and 310.
+// each.  Both halves, together with whole rows by M / 64 workgroups, like this (us): still scenes, 100 frames of 28 x 37 at ratio
+// 0.98 (groups of 100), C = 256 82, 135, 33, C = 1024 190, 244, 81; 500 of 16 x 16 (up to 645), C = 256, ratio 0.98
+// 63, 104, 35; moving, 300 frames of 37 x 37 over 20 layers (at last 1,718 groups with 60 % of the tokens, up to 749)
+// 546, 415, 370.  One group with nearly all tokens is one workgroup's in every way and stays slower than
+// the two halves: 38,193 of C = 1024 1,338, 3,755, 1,535, 8,625 of C = 256 181, 530, 315.
 constexpr int kScan = 64;
 
 template <int CPL, bool ADD>

@@ -803,6 +803,29 @@ def test_attention_stream_equals_single_blocks(B, n, heads):
     assert torch.equal(o, odd)
 
 
+# a captured call: its counters are cleared in every replay, also after eager calls in the same scratch
+def test_attention_stream_replays_from_a_graph(B):
+    import torch
+    g = torch.Generator(device="cuda")
+    g.manual_seed(2)
+    x = torch.randn(40 * 261, 512, generator=g, device="cuda").to(torch.bfloat16)
+    ph = B.make_params(40, 16, 16, 512, 8, qk_norm=1)
+    ws, want, got = B.alloc_ws(B.litevggt_frame_attn_ws_bytes(ph)), torch.empty_like(x), torch.empty_like(x)
+    B.litevggt_frame_attn(ph, x, x, x, x, want, ws)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        B.litevggt_frame_attn(ph, x, x, x, x, got, ws)
+    for _ in range(3):
+        got.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(got, want)
+        B.litevggt_frame_attn(ph, x, x, x, None, got, ws)
+        ws.fill_(0x7f)
+        torch.cuda.synchronize()
+
+
 # ------------------------------------------------------------------------------- matching of few tokens
 # 64 x 64 row tiles: one src row, whole tiles of both, one row more; one, three and five channel batches per
 # half, sixteen; the most dst tiles that are lists (4096 dst rows) and one more, and near the most workgroups
