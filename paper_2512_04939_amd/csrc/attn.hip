@@ -2028,13 +2028,19 @@ __global__ __launch_bounds__(512) void k_attn_fp8(
 // contracts 64 keys at once): a wave owns two 32-query blocks half a stage apart,
 //   A(t): weights of block 0, stage t   ||  PV of block 1, stage t-1;  scores of block 1, stage t
 //   B(t): weights of block 1, stage t   ||  PV of block 0, stage t;    scores of block 0, stage t+1
+// Bound by the issue of the loop: per stage and SIMD 128 exp2 and 64 packs of 9 cycles each, and every FP8 MFMA takes
+// about 30 cycles from a VALU that runs beside it (a loop of 16 exp2 and 8 packs alone 172 ns, 2 MFMAs alone 113, both
+// 227).  Scores of both blocks alive, MFMAs spread among the VALU part, row sums in half an MFMA, packs into stale
+// registers, against MFMAs at the ends of a phase, one block's scores alive, a whole MFMA per row sum, 16 heads:
+// 1,500 tokens 35.0 -> 31.0 us, 5,776 129 -> 115, 15,432 588 -> 521, 143,232 42.9 -> 38.3 ms; the same bits.
 // K and V are packed so that an MFMA operand is two 16-byte pieces per lane:
 //   K piece (stage, kt2, j): lane (h*32+key) holds channels 32j+8h .. +8 and 32j+16+8h .. +8 of
 //                            key 64 stage + 32 kt2 + key
 //   V piece (stage, dt, kt2): lane (h*32+dr) holds column 32dt+dr of the 16 keys of tile
 //                            2 stage + kt2 that the lane's accumulator rows map to (u = 0, 1)
 // ---------------------------------------------------------------------------------------
-constexpr int kF8Stages = 4;          // LDS ring of 64-key stages (4 KB of K, 4 KB of V each)
+constexpr int kF8Stages = 8;          // LDS ring of 64-key stages (4 KB of K, 4 KB of V each)
+constexpr int kF8Ahead = 5;           // stages fetched ahead
 constexpr float kF8Bound = 73.0f;     // |q.k| <= 64 (1 + 2^-8)^2 (1 + 2^-4)^2 < 73: unit-RMS rows rounded to bf16,
                                       // then to E4M3 (every element at most 2^-4 off, all in the same direction)
 constexpr float kF8Top = 8.75f;       // a weight at the bound is stored as 2^8.75
@@ -2126,18 +2132,18 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     for (int dt = 0; dt < 2; ++dt)
 #pragma unroll
       for (int r = 0; r < 16; ++r) oacc[sub][dt][r] = 0.f;
-  // Row sums come from the matrix pipe as well: a V fragment of ones (E4M3 1.0 = 0x38) makes
-  // every accumulator row the sum of the E4M3 weights of the lane's query.  The normaliser is
-  // then the sum of exactly the weights that multiply V: with a fixed reference the largest
-  // weight of a row is not a power of two (as it is relative to a running maximum) and carries
-  // up to 3 % rounding error, which cancels in this ratio and would not against the fp32 sum.
-  f32x16 lacc[2];
+  // Row sums come from the matrix pipe as well: a fragment of ones (E4M3 1.0 = 0x38) against the weights sums
+  // the E4M3 weights of the lane's query.  The normaliser is then the sum of exactly the weights that
+  // multiply V: with a fixed reference the largest weight of a row is not a power of two (as it is relative to a
+  // running maximum) and carries up to 3 % rounding error, which cancels in this ratio and would not against
+  // the fp32 sum.  The 16x16x128 form does it in half the cycles of another 32x32x64 and in 4 registers: fed with the
+  // operand of that form, its column c and k chunk of 32 are lane 16 * chunk + c, so even chunks hold query c and odd ones
+  // query c + 16.  Ones in the even chunks of even rows and in the odd chunks of odd rows keep them apart.
+  f32x4 lacc[2];
 #pragma unroll
-  for (int sub = 0; sub < 2; ++sub)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) lacc[sub][r] = 0.f;
-  const int kOne = 0x38383838;
-  const i32x8 ones8 = {kOne, kOne, kOne, kOne, kOne, kOne, kOne, kOne};
+  for (int sub = 0; sub < 2; ++sub) lacc[sub] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const int one = ((lane ^ (lane >> 4)) & 1) ? 0 : 0x38383838;
+  const i32x8 ones8 = {one, one, one, one, one, one, one, one};
   const float nr = -ref;
   const f32x16 kStart = {nr, nr, nr, nr, nr, nr, nr, nr, nr, nr, nr, nr, nr, nr, nr, nr};
 
@@ -2146,144 +2152,174 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   // one stage = 256 pieces of K and 256 of V: one direct-to-LDS load of each per thread
   // (stage `src` goes to the ring slot of stage `as`: past the end the last stage is fetched
   // again, into a slot nobody reads, so that the loop body has no branches)
-  auto fetch_k = [&](int src, int as) {
+  auto fetch = [&](int as) {
+    const int src = min(as, nkv - 1);
     __builtin_amdgcn_global_load_lds(kh + (size_t)src * 256 + tid, &ks[as & (kF8Stages - 1)][wave * 64], 16, 0, 0);
-  };
-  auto fetch_v = [&](int src, int as) {
     __builtin_amdgcn_global_load_lds(vh + (size_t)src * 256 + tid, &vs[as & (kF8Stages - 1)][wave * 64], 16, 0, 0);
   };
 
-  f32x16 sacc[2];      // [32-key half]: the scores in flight (of one query block at a time)
-  i32x8 pb[2];         // [query block]: E4M3 weights of its current stage
+  f32x16 sacc[2][2];   // [query block][32-key half]: scores
+  i32x8 pb[2] = {};    // [query block]: E4M3 weights of its current stage
   u32x4 fv[4], fk[4];  // the pieces of one stage of V and of K
 
-  auto load4 = [&](const u32x4 *base, u32x4(&dst)[4]) {
-#pragma unroll
-    for (int f = 0; f < 4; ++f) dst[f] = base[f * 64];
+  auto mma_s = [&](int sub, int kt2) {
+    sacc[sub][kt2] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(cat8(fk[2 * kt2], fk[2 * kt2 + 1]), qf8[sub],
+                                                                     kStart, 0, 0, 0, scale_k, 0, 127);
   };
-  auto mma_s = [&](int sub) {
-#pragma unroll
-    for (int kt2 = 0; kt2 < 2; ++kt2)
-      sacc[kt2] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(cat8(fk[2 * kt2], fk[2 * kt2 + 1]), qf8[sub],
-                                                                  kStart, 0, 0, 0, scale_k, 0, 127);
+  auto mma_pv = [&](int sub, int dt) {
+    oacc[sub][dt] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(cat8(fv[2 * dt], fv[2 * dt + 1]), pb[sub],
+                                                                    oacc[sub][dt], 0, 0, 0, 0, 0, 0);
   };
-  auto mma_pv = [&](int sub) {
-#pragma unroll
-    for (int dt = 0; dt < 2; ++dt)
-      oacc[sub][dt] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(cat8(fv[2 * dt], fv[2 * dt + 1]), pb[sub],
-                                                                      oacc[sub][dt], 0, 0, 0, 0, 0, 0);
-    lacc[sub] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(ones8, pb[sub], lacc[sub], 0, 0, 0, 0, 0, 0);
+  auto mma_l = [&](int sub) {
+    lacc[sub] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(ones8, pb[sub], lacc[sub], 0, 0, 0, 0, 0, 0);
   };
-  auto mask_tail = [&](int t) {   // keys beyond the sequence end
+  auto mask_tail = [&](int t, int sub) {   // keys beyond the sequence end
     if ((int64_t)(t + 1) * kKV > n) {
 #pragma unroll
       for (int kt2 = 0; kt2 < 2; ++kt2)
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
           const int64_t key = (int64_t)t * kKV + kt2 * 32 + (r >> 2) * 8 + h * 4 + (r & 3);
-          if (key >= n) sacc[kt2][r] = -INFINITY;
+          if (key >= n) sacc[sub][kt2][r] = -INFINITY;
         }
     }
   };
-  // exp2 against the fixed reference, E4M3 pack
-  auto weights = [&](int sub) {
+  // a quarter of a stage's weights of one block: exp2 against the fixed reference, E4M3 pack
+  auto weights = [&](int sub, int i) {
+    float pv[8];
 #pragma unroll
-    for (int kt2 = 0; kt2 < 2; ++kt2)
+    for (int e = 0; e < 8; ++e) pv[e] = __builtin_amdgcn_exp2f(sacc[sub][i >> 1][8 * (i & 1) + e]);
+    // (into the stale codes, not into a cleared register: all four bytes are written, and clearing took 16 moves per stage)
 #pragma unroll
-      for (int u = 0; u < 2; ++u) {
-        float pv[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) pv[e] = __builtin_amdgcn_exp2f(sacc[kt2][8 * u + e]);
-        pb[sub][(kt2 * 2 + u) * 2] = (int)cvt4_fp8(pv[0], pv[1], pv[2], pv[3]);
-        pb[sub][(kt2 * 2 + u) * 2 + 1] = (int)cvt4_fp8(pv[4], pv[5], pv[6], pv[7]);
-      }
+    for (int j = 0; j < 2; ++j) {
+      const int w = __builtin_amdgcn_cvt_pk_fp8_f32(pv[4 * j], pv[4 * j + 1], pb[sub][i * 2 + j], false);
+      pb[sub][i * 2 + j] = __builtin_amdgcn_cvt_pk_fp8_f32(pv[4 * j + 2], pv[4 * j + 3], w, true);
+    }
   };
-  auto wait4 = [&](u32x4(&f)[4]) {
-    asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(f[0]), "+v"(f[1]), "+v"(f[2]), "+v"(f[3]) : : "memory");
+  // Fragment reads but the newest `newer` are there.  `with`: the other operands of the MFMAs that need them, which keep
+  // those behind this wait (the fragments themselves in their place would cost a copy of each: two form one operand).
+  auto wait_frags = [&](i32x8(&with)[2], auto newer) {
+    asm volatile("s_waitcnt lgkmcnt(%2)" : "+v"(with[0]), "+v"(with[1]) : "n"(decltype(newer)::value) : "memory");
+    __builtin_amdgcn_sched_barrier(0);
   };
-  // A phase is: the MFMAs that consume what the phase before produced, the fragment read for
-  // the next consumer (by hand, waited for a whole VALU part later), the VALU part (the longer
-  // one: 32 exp2, 16 packs per lane against 3 + 2 MFMAs of 64 cycles), then the score
-  // MFMAs whose results the next phase's VALU part turns into weights.  Scores of only one
-  // query block are alive at a time, and one stage of K and of V.
+  using None = std::integral_constant<int, 0>;
+  using Four = std::integral_constant<int, 4>;
+  // A phase turns one block's scores into weights (32 exp2 and 16 packs, 8 cycles each: the longer pipe) while the
+  // matrix pipe works on the other block: the weights' product with V and their sum, and that block's next
+  // scores (4 x 64 + 32 cycles).  A MFMA stands between any two quarters of the VALU part, so that a wave waits for none of its
+  // own; the scores of both blocks are alive.  Fragments are read by hand, V(t+1) and K(t+2) in A(t+1) once the
+  // MFMAs that had their registers are issued, and waited for in B(t+1).
   const uint32_t ks_lane = lds_addr(&ks[0][lane]), vs_lane = lds_addr(&vs[0][lane]);
   auto slot_off = [&](int t) { return (uint32_t)((t & (kF8Stages - 1)) * 4 * 64 * 16); };
-  // B(t): PV(t) of block 0; read K(t+1); weights of block 1 (stage t); scores(t+1) of block 0
+#define LV_PIN() __builtin_amdgcn_sched_barrier(0)
+  // B(t): PV(t) and scores(t+1) of block 0; weights of block 1 (stage t)
   auto phase_b = [&](int t, bool last) {
-    __builtin_amdgcn_sched_barrier(0);
-    wait4(fv);                                            // V(t), read in A(t)
-    mma_pv(0);
-    __builtin_amdgcn_sched_barrier(0);
-    lds_read4_async(fk, ks_lane + slot_off(t + 1));
-    __builtin_amdgcn_sched_barrier(0);
-    weights(1);
-    __builtin_amdgcn_sched_barrier(0);
-    wait4(fk);
-    mma_s(0);
-    if (last) mask_tail(t + 1);
+    LV_PIN();
+    wait_frags(pb, Four{});
+    mma_pv(0, 0);
+    LV_PIN();
+    weights(1, 0);
+    LV_PIN();
+    mma_pv(0, 1);
+    LV_PIN();
+    weights(1, 1);
+    LV_PIN();
+    wait_frags(qf8, None{});
+    mma_s(0, 0);
+    LV_PIN();
+    weights(1, 2);
+    LV_PIN();
+    mma_s(0, 1);
+    LV_PIN();
+    weights(1, 3);
+    LV_PIN();
+    mma_l(0);
+    if (last) mask_tail(t + 1, 0);
   };
-  // A(t): PV(t-1) of block 1; read V(t); weights of block 0 (stage t); scores(t) of block 1
+  // A(t): PV(t-1) and scores(t) of block 1; weights of block 0 (stage t); reads V(t) and K(t+1)
   auto phase_a = [&](int t, bool last) {
-    __builtin_amdgcn_sched_barrier(0);
-    mma_pv(1);                                            // V(t-1): waited for in B(t-1)
-    __builtin_amdgcn_sched_barrier(0);
+    LV_PIN();
+    mma_pv(1, 0);
+    LV_PIN();
+    weights(0, 0);
+    LV_PIN();
+    mma_pv(1, 1);
+    LV_PIN();
     lds_read4_async(fv, vs_lane + slot_off(t));
-    __builtin_amdgcn_sched_barrier(0);
-    weights(0);
-    __builtin_amdgcn_sched_barrier(0);
-    mma_s(1);                                             // K(t): waited for in B(t-1)
-    if (last) mask_tail(t);
+    LV_PIN();
+    weights(0, 1);
+    LV_PIN();
+    mma_s(1, 0);
+    LV_PIN();
+    weights(0, 2);
+    LV_PIN();
+    mma_s(1, 1);
+    LV_PIN();
+    lds_read4_async(fk, ks_lane + slot_off(t + 1));   // past the end: a slot that may be arriving, never used
+    LV_PIN();
+    weights(0, 3);
+    LV_PIN();
+    mma_l(1);
+    if (last) mask_tail(t, 1);
   };
 
-  // stages 0, 1 complete and stage 2 in flight before the loop; iteration t fetches stage t+3
-  // into the slot of stage t-1, which nobody reads any more
-  fetch_k(0, 0);
-  fetch_v(0, 0);
-  fetch_k(min(1, nkv - 1), 1);
-  fetch_v(min(1, nkv - 1), 1);
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  __syncthreads();
-  fetch_k(min(2, nkv - 1), 2);
-  fetch_v(min(2, nkv - 1), 2);
+  // stages 0 and 1 complete and the next ones in flight before the loop; iteration t fetches stage t + kF8Ahead
+  // into a slot that nobody has read since stage t + kF8Ahead - kF8Stages
+#pragma unroll
+  for (int i = 0; i < kF8Ahead; ++i) fetch(i);
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * (kF8Ahead - 2)) : "memory");
+  __builtin_amdgcn_s_barrier();
   // A(0) without a PV
-  load4(&ks[0][lane], fk);
-  mma_s(0);
-  if (nkv == 1) mask_tail(0);
-  weights(0);
-  mma_s(1);
-  if (nkv == 1) mask_tail(0);
-  load4(&vs[0][lane], fv);
-  // steady state: B(t), A(t+1) for t <= nkv-3: the stages they touch (t+1) are complete ones
+  LV_PIN();
+  lds_read4_async(fk, ks_lane);
+  lds_read4_async(fv, vs_lane);
+  wait_frags(qf8, Four{});
+#pragma unroll
+  for (int sub = 0; sub < 2; ++sub) {
+    mma_s(sub, 0);
+    mma_s(sub, 1);
+    if (nkv == 1) mask_tail(0, sub);
+  }
+  LV_PIN();
+  lds_read4_async(fk, ks_lane + slot_off(1));
+  LV_PIN();
+#pragma unroll
+  for (int i = 0; i < 4; ++i) weights(0, i);
+  // steady state: B(t), A(t+1) for t <= nkv-3: the stages they read (t+1, t+2) are complete ones
   for (int t = 0; t < nkv - 2; ++t) {
-    // this wave's parts of stage t+1 have landed (the two newest loads, of stage t+2, may be in
-    // flight); after the barrier all of stage t+1 is readable
-    __builtin_amdgcn_sched_barrier(0);
-    asm volatile("s_waitcnt vmcnt(2)" ::: "memory");
+    // this wave's parts of stage t+2 have landed (the newest loads may be in flight); after the barrier all of
+    // stage t+2 is readable
+    LV_PIN();
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * (kF8Ahead - 3)) : "memory");
     __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_sched_barrier(0);
-    const int fs = min(t + 3, nkv - 1);
-    fetch_k(fs, t + 3);
-    fetch_v(fs, t + 3);
+    LV_PIN();
+    fetch(t + kF8Ahead);
     phase_b(t, false);
     phase_a(t + 1, false);
   }
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");        // nothing may land after the workgroup ends
-  __syncthreads();
   if (nkv >= 2) {                                         // enters the last stage, which may be ragged
     phase_b(nkv - 2, true);
     phase_a(nkv - 1, true);
   }
   // B(nkv-1) without scores of a next stage, and the last PV of block 1
-  __builtin_amdgcn_sched_barrier(0);
-  wait4(fv);
-  mma_pv(0);
-  weights(1);
-  mma_pv(1);
+  LV_PIN();
+  wait_frags(pb, None{});
+  asm volatile("" ::"v"(fk[0]), "v"(fk[1]), "v"(fk[2]), "v"(fk[3]));   // (the last K read ends before its registers do)
+#pragma unroll
+  for (int i = 0; i < 4; ++i) weights(1, i);
+#pragma unroll
+  for (int sub = 0; sub < 2; ++sub) {
+    mma_pv(sub, 0);
+    mma_pv(sub, 1);
+    mma_l(sub);
+  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");        // nothing may land after the workgroup ends
+#undef LV_PIN
 
   bool low = false;
 #pragma unroll
   for (int sub = 0; sub < 2; ++sub) {
-    const float l = lacc[sub][0];   // every row of the accumulator holds the lane's query's sum
+    const float l = (lane & 16) ? lacc[sub][1] : lacc[sub][0];
     const float inv = out_scale / l;
     const int64_t row = q0 + sub * 32 + ql;
     if (row < n) {
