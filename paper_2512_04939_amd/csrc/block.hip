@@ -410,7 +410,7 @@ __global__ __launch_bounds__(256) void k_weights_pack(BlockWeights4 bw, int C, c
 // next tile's first stages are fetched during the epilogue.
 // `split`: the output is Nout / split row-major blocks of [M, split] one after the other
 // (split = Nout: one plain matrix; split = C for the fused q|k|v projection).
-// PACKED: the output is the activation operand of a following layer with K = Nout and is
+// PACKED: the output, through GELU, is the activation operand of a following layer with K = Nout and is
 // written in that layer's operand order straight from the accumulators (bf16 fragments, or,
 // with FP8, E4M3 codes quantised with *out_inv while the largest |value| goes to *out_amax).
 // FP8: the same ring and the same byte traffic per stage, but a stage (two 1 KB units per
@@ -437,19 +437,28 @@ struct GemmShape {
   static constexpr size_t kLds = (size_t)kStages * kStageU4 * 16 + 2 * BN * sizeof(float);   // + two tiles' bias values
 };
 
-// GELU in its erf form, x * Phi(x).  erfc(|x| / sqrt 2) by the rational-times-exponential form of
-// Abramowitz & Stegun 7.1.26 (absolute error <= 1.5e-7, four orders below a bf16 step); the
-// negative side uses erfc itself, so nothing cancels there.  A third of erff's instructions: the
-// epilogue of the first MLP layer evaluates it 65536 times per tile.
+// GELU in its erf form, v * Phi(v) = max(v, 0) - |v| erfc(|v| / sqrt 2) / 2.  erfc by the rational-times-exponential form
+// of Abramowitz & Stegun 7.1.26 (absolute error <= 1.5e-7, four orders below a bf16 step) with sqrt 2 and the
+// half in its constants; the negative side uses erfc itself, so nothing cancels there.  The epilogue of the
+// first MLP layer evaluates it 65536 times per tile, where it is as long as an E4M3 main loop: 12 VALU instructions and
+// two transcendental ones (as v / 2 * (2 - erfc) with a select 17 and two: TIMES).  Against 64 bits on
+// [-12, 12] never further off than that form.  (|v| beyond 64, where the product is 0, is held there: infinity stays.)
 __device__ __forceinline__ float gelu_erf(float v) {
-  const float x = fabsf(v) * 0.70710678118654752f;
-  const float t = __builtin_amdgcn_rcpf(__builtin_fmaf(0.3275911f, x, 1.0f));
-  float p = __builtin_fmaf(1.061405429f, t, -1.453152027f);
-  p = __builtin_fmaf(p, t, 1.421413741f);
-  p = __builtin_fmaf(p, t, -0.284496736f);
-  p = __builtin_fmaf(p, t, 0.254829592f);
-  const float erfc_abs = p * t * __builtin_amdgcn_exp2f(-1.4426950408889634f * x * x);
-  return 0.5f * v * (v < 0.f ? erfc_abs : 2.0f - erfc_abs);
+  const float a = fminf(fabsf(v), 64.0f);
+  const float t = __builtin_amdgcn_rcpf(__builtin_fmaf(0.23164189f, a, 1.0f));
+  float p = __builtin_fmaf(0.5307027145f, t, -0.7265760135f);
+  p = __builtin_fmaf(p, t, 0.7107068705f);
+  p = __builtin_fmaf(p, t, -0.142248368f);
+  p = __builtin_fmaf(p, t, 0.127414796f);
+  const float half_erfc = p * t * __builtin_amdgcn_exp2f(-0.72134752f * v * v);
+  return __builtin_fmaf(-a, half_erfc, fmaxf(v, 0.f));
+}
+
+// max(m, |a|, |b|) in one instruction (written as fmaxf of fabsf, values taken from their bits are made canonical first)
+__device__ __forceinline__ float max3_abs(float m, float a, float b) {
+  float r;
+  asm("v_max3_f32 %0, %1, |%2|, |%3|" : "=v"(r) : "v"(m), "v"(a), "v"(b));
+  return r;
 }
 
 template <bool FP8, bool PACKED, int BM, int BN, int KG = 1>
@@ -765,22 +774,19 @@ __global__ __launch_bounds__((GemmShape<BM, BN>::kThreads * KG)) __attribute__((
 #pragma unroll
         for (int a = 0; a < 2; ++a) {
           if (!mine(a)) continue;
-          const bool live = (int64_t)tm * BM + wd * 64 + 32 * a + (lane & 31) < M;
+          uint32_t keep = (int64_t)tm * BM + wd * 64 + 32 * a + (lane & 31) < M ? ~0u : 0u;
+          asm volatile("" : "+v"(keep));     // (a mask: as a condition it becomes a branch around every four values)
           uint32_t d[4];
 #pragma unroll
           for (int g = 0; g < 4; ++g) {
             const f32x4 bv = *(const f32x4 *)(bias_lds + wn * 32 * kB + 32 * b + 8 * g + 4 * h);
             float v[4];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-              v[i] = acc[a][b][4 * g + i] * alpha + bv[i];
-              if (gelu) v[i] = gelu_erf(v[i]);
-            }
-            const uint32_t p0 = pack_bf16(v[0], v[1]), p1 = pack_bf16(v[2], v[3]);
-            if (live) m = fmaxf(m, fmaxf(fmaxf(fabsf(bf16_lo(p0)), fabsf(bf16_hi(p0))), fmaxf(fabsf(bf16_lo(p1)), fabsf(bf16_hi(p1)))));
-            d[g] = live ? cvt4_fp8(clamp448(bf16_lo(p0) * r), clamp448(bf16_hi(p0) * r), clamp448(bf16_lo(p1) * r),
-                                   clamp448(bf16_hi(p1) * r))
-                        : 0u;
+            for (int i = 0; i < 4; ++i) v[i] = gelu_erf(acc[a][b][4 * g + i] * alpha + bv[i]);
+            const uint32_t p0 = pack_bf16(v[0], v[1]) & keep, p1 = pack_bf16(v[2], v[3]) & keep;
+            m = max3_abs(m, bf16_lo(p0), bf16_hi(p0));
+            m = max3_abs(m, bf16_lo(p1), bf16_hi(p1));
+            d[g] = cvt4_fp8(clamp448(bf16_lo(p0) * r), clamp448(bf16_hi(p0) * r), clamp448(bf16_lo(p1) * r), clamp448(bf16_hi(p1) * r));
           }
           const auto s0 = __builtin_amdgcn_permlane32_swap(d[0], d[2], false, false);
           const auto s1 = __builtin_amdgcn_permlane32_swap(d[1], d[3], false, false);
@@ -804,12 +810,8 @@ __global__ __launch_bounds__((GemmShape<BM, BN>::kThreads * KG)) __attribute__((
           float v0[4], v1[4];
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
-            v0[i] = acc[a][b][8 * gp + i] + bv0[i];
-            v1[i] = acc[a][b][8 * gp + 4 + i] + bv1[i];
-            if (gelu) {
-              v0[i] = gelu_erf(v0[i]);
-              v1[i] = gelu_erf(v1[i]);
-            }
+            v0[i] = gelu_erf(acc[a][b][8 * gp + i] + bv0[i]);
+            v1[i] = gelu_erf(acc[a][b][8 * gp + 4 + i] + bv1[i]);
           }
           // first operand's lanes 32-63 <-> second operand's lanes 0-31
           const auto s0 = __builtin_amdgcn_permlane32_swap(pack_bf16(v0[0], v0[1]), pack_bf16(v1[0], v1[1]), false, false);
@@ -837,7 +839,10 @@ __global__ __launch_bounds__((GemmShape<BM, BN>::kThreads * KG)) __attribute__((
         for (int i = 0; i < 4; ++i) {
           v0[i] = FP8 ? acc[a][b][8 * gp + i] * alpha + bv0[i] : acc[a][b][8 * gp + i] + bv0[i];
           v1[i] = FP8 ? acc[a][b][8 * gp + 4 + i] * alpha + bv1[i] : acc[a][b][8 * gp + 4 + i] + bv1[i];
-          if (gelu) {
+        }
+        if (gelu) {                          // (one branch for eight values)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
             v0[i] = gelu_erf(v0[i]);
             v1[i] = gelu_erf(v1[i]);
           }
@@ -974,7 +979,7 @@ static int launch_linear(const uint16_t *A, int64_t M, int K, int Nout,
                          const float *bias, int gelu, uint16_t *out, int split, BlockWs &w,
                          hipStream_t st, const LinearOpts &o) {
   if (!o.w_packed || (o.fp8 && !o.sc) || (o.current && (o.a_packed || o.pack_out))) return LV_ERR_PARAM;
-  if (o.pack_out && (o.addend || split != Nout || (o.fp8 && (!o.out_inv || !o.out_amax)))) return LV_ERR_PARAM;
+  if (o.pack_out && (!gelu || o.addend || split != Nout || (o.fp8 && (!o.out_inv || !o.out_amax)))) return LV_ERR_PARAM;
   if (K % 256 != 0 || Nout % kTile != 0 || split % kTile != 0 || Nout % split != 0) return LV_ERR_SHAPE;
   int rc;
   if (w.Mp / 128 * (Nout / 128) >= ((int64_t)1 << 30) || w.Mp >= ((int64_t)1 << 31)) return LV_ERR_SHAPE;
