@@ -114,23 +114,17 @@ __device__ __forceinline__ void raise_max(uint32_t *word, float m) {
 // FP8: the normalised row (rounded to bf16, as if it had been stored) is quantised with the
 // scale *inv to E4M3 codes and leaves in the FP8 operand order of k_quant_pack_fp8 (units of 32
 // rows x 32 channels, lane h * 32 + r holds the 16 codes of channels 32u + 16h .. + 15 of row
-// r); the largest |value| of the rows below M is reduced into *amax.  Row stride in LDS: C + 16
-// bytes.
+// r); the largest |value| of the rows below M is kept for the history.  Row stride in LDS: C + 16 bytes.
 constexpr int kLnWaves = 8;
+// Row tile `tile`; FP8: quantised with r, the rows' largest |value| is returned in thread 0 (0 in bf16).
 template <int CPL, bool FP8>
-__global__ __launch_bounds__(64 * kLnWaves) void k_layernorm_packed(const uint16_t *__restrict__ x,
-                                                          const uint16_t *__restrict__ add,
-                                                          const float *__restrict__ gamma,
-                                                          const float *__restrict__ beta, int64_t M, int C,
-                                                          u32x4 *__restrict__ packed,
-                                                          const uint32_t *__restrict__ inv,
-                                                          uint32_t *__restrict__ amax) {
-  extern __shared__ u32x4 ln_stage[];
+__device__ __forceinline__ float ln_packed_tile(const uint16_t *__restrict__ x, const uint16_t *__restrict__ add,
+                                                const float *__restrict__ gamma, const float *__restrict__ beta, int64_t M, int C,
+                                                int tile, u32x4 *__restrict__ packed, float r, u32x4 *ln_stage) {
   constexpr int kRows = 32 / kLnWaves;            // rows of a wave
   constexpr int RB = CPL <= 2 ? kRows : kRows / 2;   // rows whose loads are in flight together
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nch = C >> 3, stride = nch + 1;
   if constexpr (FP8) {
-    const float r = __uint_as_float(*inv);
     const int stride8 = (C >> 3) + 2;   // u32x2 per row
     u32x2 *stage8 = (u32x2 *)ln_stage;
     float m = 0.f;
@@ -139,7 +133,7 @@ __global__ __launch_bounds__(64 * kLnWaves) void k_layernorm_packed(const uint16
       u32x4 w[RB][CPL], a[RB][CPL];
 #pragma unroll
       for (int j = 0; j < RB; ++j) {
-        const int64_t row = (int64_t)blockIdx.x * 32 + wave * kRows + j0 + j;
+        const int64_t row = (int64_t)tile * 32 + wave * kRows + j0 + j;
         ln_load<CPL>(x, add, row < M ? row : 0, C, lane, row < M ? nch : 0, w[j], a[j]);
       }
 #pragma unroll
@@ -147,7 +141,7 @@ __global__ __launch_bounds__(64 * kLnWaves) void k_layernorm_packed(const uint16
         const int rr = wave * kRows + j0 + j;
         u32x4 o[CPL];
         ln_row<CPL>(w[j], a[j], gamma, beta, lane, nch, C, o);
-        const bool live = (int64_t)blockIdx.x * 32 + rr < M;
+        const bool live = (int64_t)tile * 32 + rr < M;
 #pragma unroll
         for (int c = 0; c < CPL; ++c)
           if (lane + 64 * c < nch) {
@@ -160,26 +154,23 @@ __global__ __launch_bounds__(64 * kLnWaves) void k_layernorm_packed(const uint16
     m = wave_max(m);
     if (lane == 0) red[wave] = m;
     __syncthreads();
-    if (threadIdx.x == 0) {
-#pragma unroll
-      for (int i = 1; i < kLnWaves; ++i) m = fmaxf(m, red[i]);
-      raise_max(amax, m);
-    }
     const int pieces = 32 * (C >> 4);   // = (C / 32) units x 64 lanes
     for (int p = threadIdx.x; p < pieces; p += 64 * kLnWaves) {
       const int u = p >> 6, lp = p & 63;
       const u32x2 *src = stage8 + (lp & 31) * stride8 + 4 * u + 2 * (lp >> 5);
       const u32x2 lo = src[0], hi = src[1];
-      packed[(size_t)blockIdx.x * pieces + p] = u32x4{lo.x, lo.y, hi.x, hi.y};
+      packed[(size_t)tile * pieces + p] = u32x4{lo.x, lo.y, hi.x, hi.y};
     }
-    return;
+#pragma unroll
+    for (int i = 0; i < kLnWaves; ++i) m = fmaxf(m, red[i]);
+    return m;
   }
 #pragma unroll 1
   for (int j0 = 0; j0 < kRows; j0 += RB) {
     u32x4 w[RB][CPL], a[RB][CPL];
 #pragma unroll
     for (int j = 0; j < RB; ++j) {
-      const int64_t row = (int64_t)blockIdx.x * 32 + wave * kRows + j0 + j;
+      const int64_t row = (int64_t)tile * 32 + wave * kRows + j0 + j;
       ln_load<CPL>(x, add, row < M ? row : 0, C, lane, row < M ? nch : 0, w[j], a[j]);
     }
 #pragma unroll
@@ -187,7 +178,7 @@ __global__ __launch_bounds__(64 * kLnWaves) void k_layernorm_packed(const uint16
       const int rr = wave * kRows + j0 + j;
       u32x4 o[CPL];
       ln_row<CPL>(w[j], a[j], gamma, beta, lane, nch, C, o);
-      const bool live = (int64_t)blockIdx.x * 32 + rr < M;
+      const bool live = (int64_t)tile * 32 + rr < M;
 #pragma unroll
       for (int c = 0; c < CPL; ++c)
         if (lane + 64 * c < nch) ln_stage[rr * stride + lane + 64 * c] = live ? o[c] : u32x4{0u, 0u, 0u, 0u};
@@ -197,8 +188,22 @@ __global__ __launch_bounds__(64 * kLnWaves) void k_layernorm_packed(const uint16
   const int pieces = 32 * nch;   // = (C / 16) k-steps x 64 lanes
   for (int p = threadIdx.x; p < pieces; p += 64 * kLnWaves) {
     const int ks = p >> 6, lp = p & 63;
-    packed[(size_t)blockIdx.x * pieces + p] = ln_stage[(lp & 31) * stride + 2 * ks + (lp >> 5)];
+    packed[(size_t)tile * pieces + p] = ln_stage[(lp & 31) * stride + 2 * ks + (lp >> 5)];
   }
+  return 0.f;
+}
+
+template <int CPL, bool FP8>
+__global__ __launch_bounds__(64 * kLnWaves) void k_layernorm_packed(const uint16_t *__restrict__ x,
+                                                          const uint16_t *__restrict__ add,
+                                                          const float *__restrict__ gamma,
+                                                          const float *__restrict__ beta, int64_t M, int C,
+                                                          u32x4 *__restrict__ packed,
+                                                          const uint32_t *__restrict__ inv,
+                                                          uint32_t *__restrict__ amax) {
+  extern __shared__ u32x4 ln_stage[];
+  const float m = ln_packed_tile<CPL, FP8>(x, add, gamma, beta, M, C, blockIdx.x, packed, FP8 ? __uint_as_float(*inv) : 1.0f, ln_stage);
+  if (FP8 && threadIdx.x == 0) raise_max(amax, m);
 }
 
 // packed: the result goes there in a linear layer's operand order (Mp rows, the ones beyond M
@@ -298,16 +303,15 @@ __global__ __launch_bounds__(64) void k_fp8_scales(uint32_t *__restrict__ sc) {
 // units.  (Both operands use the same k order inside an operand, which is all a dot product
 // needs.)  The byte layout equals that of the bf16 packing of a matrix with K/2 columns, so
 // the tiled kernel fetches and reads both types the same way.  Rows n..n_pad-1 are zero.
-// A wave writes whole units (1 KB stores) and takes 4 consecutive units of its 32 rows (256
-// bytes of each bf16 row).  Grid: (row tiles, ceil(units / 16)).
+// A wave writes whole units (1 KB stores) and takes the 4 units from s0 on of its 32 rows (256
+// bytes of each bf16 row).  k_quant_pack_fp8's grid: (row tiles, ceil(units / 16)).
 // amax != NULL: the largest |x| read is reduced into *amax on the way (delayed scaling needs
 // it only afterwards, for the history, so no pass of its own).
-__device__ __forceinline__ void quant_pack_units(const uint16_t *__restrict__ x, int n, int K, float r, int t, int group,
+__device__ __forceinline__ void quant_pack_units(const uint16_t *__restrict__ x, int n, int K, float r, int t, int s0,
                                                  u32x4 *__restrict__ packed, uint32_t *__restrict__ amax) {
   const int KS = K >> 5;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, h = lane >> 5, rr = lane & 31;
+  const int lane = threadIdx.x & 63, h = lane >> 5, rr = lane & 31;
   const int j = t * 32 + rr;
-  const int s0 = (group * 4 + wave) * 4;
   u32x4 src[4][2];
 #pragma unroll
   for (int u = 0; u < 4; ++u) {
@@ -337,13 +341,12 @@ __global__ __launch_bounds__(256) void k_quant_pack_fp8(const uint16_t *__restri
                                                         int K, const uint32_t *__restrict__ inv,
                                                         u32x4 *__restrict__ packed,
                                                         uint32_t *__restrict__ amax) {
-  quant_pack_units(x, n, K, __uint_as_float(*inv), blockIdx.x, blockIdx.y, packed, amax);
+  quant_pack_units(x, n, K, __uint_as_float(*inv), blockIdx.x, (blockIdx.y * 4 + (threadIdx.x >> 6)) * 4, packed, amax);
 }
 
-// ---- The block's four weight matrices (qkv, output, MLP 1, MLP 2: 3C x C, C x C, 4C x C, C x 4C) in
-// one launch each for their amaxes and for their way into operand order: 24 MB at C = 1024, which
-// four launches apiece did in 78 us (one atomic per workgroup on one word) and 20 us, now about 9
-// and 9.
+// ---- The block's four weight matrices (qkv, output, MLP 1, MLP 2: 3C x C, C x C, 4C x C, C x 4C): their
+// amaxes in one launch, 24 MB at C = 1024 (four launches took 78 us with one atomic per workgroup on one
+// word, now about 8).
 struct BlockWeights4 {
   const uint16_t *w[4];
   u32x4 *dst[4];
@@ -370,28 +373,118 @@ __global__ __launch_bounds__(256) void k_weights_amax(BlockWeights4 bw, int C, u
   if (threadIdx.x == 0) partial[blockIdx.x] = __float_as_uint(m);
 }
 
-// grid: per weight (rows / 32) row tiles x ceil(k-steps / 16) groups, one weight after the other
-template <bool FP8>
-__global__ __launch_bounds__(256) void k_weights_pack(BlockWeights4 bw, int C, const uint32_t *__restrict__ sc) {
-  const int g1 = (C / (FP8 ? 32 : 16) + 15) / 16, g4 = (4 * C / (FP8 ? 32 : 16) + 15) / 16;   // groups at K = C, 4C
-  const int rt = C / 32;
-  int l = 0, b = blockIdx.x;
-  if (b >= 3 * rt * g1) b -= 3 * rt * g1, l = 1;
-  if (l == 1 && b >= rt * g1) b -= rt * g1, l = 2;
-  if (l == 2 && b >= 4 * rt * g1) b -= 4 * rt * g1, l = 3;
-  const int groups = l == 3 ? g4 : g1, K = l == 3 ? 4 * C : C, t = b / groups, y = b % groups;
-  if constexpr (FP8) {
-    quant_pack_units(bw.w[l], t * 32 + 32, K, __uint_as_float(sc[l * kFp8Words + 3]), t, y, bw.dst[l], nullptr);
-  } else {
-    const int KS = K >> 4, lane = threadIdx.x & 63, wave = threadIdx.x >> 6, s0 = (y * 4 + wave) * 4;
-    const u32x4 *row = (const u32x4 *)(bw.w[l] + (size_t)(t * 32 + (lane & 31)) * K);
-    u32x4 w[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) w[u] = s0 + u < KS ? row[(s0 + u) * 2 + (lane >> 5)] : u32x4{0u, 0u, 0u, 0u};
-#pragma unroll
-    for (int u = 0; u < 4; ++u)
-      if (s0 + u < KS) bw.dst[l][((size_t)t * KS + s0 + u) * 64 + lane] = w[u];
+// ---- The head of a block: what its first linear layer waits for, in one launch.  Workgroups by number: the
+// first LayerNorm's row tiles (n_ln; the longest chain, so they start first), the weights on their way into operand
+// order (n_pack; per weight (rows / 32) row tiles x ceil(k-steps / 32) groups, one weight after the other), and
+// with FP8 one for the layers' scalars.  All three depend on inputs only: with FP8 a workgroup takes the scale it needs from
+// the weights' partial maxima or the amax history itself.  Apart they were three launches one after the other that
+// each left most of the chip waiting: C = 1024, us, 5,776 rows in bf16 10.9 + 10.3, now 16.4; 15,432 rows in E4M3
+// 4.5 + 8.5 + 19.1, now 26.9; whole blocks of 394 rows in bf16 74.7 -> 70.0, in E4M3 (delayed scaling) 81.2 -> 73.6.
+struct Fp8Head {
+  uint32_t *sc;              // the four layers' scalars (8 words each)
+  const float *state;        // amax histories (delayed scaling), or NULL: every input's scale is 1 for now
+  uint32_t *wamax;           // the weights' amaxes: written (partial != NULL), or read
+  const uint32_t *partial;   // the weights' partial maxima, or NULL
+  uint32_t *ln_part;         // receives every row tile's largest |value| (the history's; no word to clear before)
+};
+__device__ __forceinline__ float weight_amax(const Fp8Head &hd, int l) {
+  if (!hd.partial) return __uint_as_float(hd.wamax[l]);
+  float m = 0.f;
+  const int e = weight_first_unit(l + 1) * kWAmaxUnit;
+  for (int i = weight_first_unit(l) * kWAmaxUnit + (threadIdx.x & 63); i < e; i += 64) m = fmaxf(m, __uint_as_float(hd.partial[i]));
+  return wave_max(m);
+}
+// 448 / the largest recorded input amax of layer l (a history with nothing recorded yet gives 1)
+__device__ __forceinline__ float history_inv(const Fp8Head &hd, int l) {
+  if (!hd.state) return 1.0f;
+  const float *hist = hd.state + (size_t)l * (LV_FP8_HISTORY + 2);
+  const int lane = threadIdx.x & 63;
+  return fp8_scale_inv(__float_as_uint(wave_max(fmaxf(hist[lane], lane + 64 < LV_FP8_HISTORY ? hist[lane + 64] : 0.f))));
+}
+
+template <int CPL, bool FP8>
+__global__ __launch_bounds__(64 * kLnWaves) void k_block_head(const uint16_t *__restrict__ z, const float *__restrict__ gamma,
+                                                              const float *__restrict__ beta, int64_t M, int C, int n_ln,
+                                                              u32x4 *__restrict__ packed, BlockWeights4 bw, int n_pack, Fp8Head hd) {
+  extern __shared__ u32x4 ln_stage[];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  int b = blockIdx.x;
+  if (b < n_ln) {
+    const float m = ln_packed_tile<CPL, FP8>(z, nullptr, gamma, beta, M, C, b, packed, FP8 ? history_inv(hd, 0) : 1.0f, ln_stage);
+    if (FP8 && threadIdx.x == 0) hd.ln_part[b] = __float_as_uint(m);
+    return;
   }
+  b -= n_ln;
+  if (b < n_pack) {
+    constexpr int kPer = 4 * kLnWaves;                                 // k-steps (units) of a workgroup
+    const int g1 = (C / (FP8 ? 32 : 16) + kPer - 1) / kPer, g4 = (4 * C / (FP8 ? 32 : 16) + kPer - 1) / kPer;   // groups at K = C, 4C
+    const int rt = C / 32;
+    int l = 0;
+    if (b >= 3 * rt * g1) b -= 3 * rt * g1, l = 1;
+    if (l == 1 && b >= rt * g1) b -= rt * g1, l = 2;
+    if (l == 2 && b >= 4 * rt * g1) b -= 4 * rt * g1, l = 3;
+    const int groups = l == 3 ? g4 : g1, K = l == 3 ? 4 * C : C, t = b / groups, s0 = (b % groups * kLnWaves + wave) * 4;
+    if constexpr (FP8) {
+      quant_pack_units(bw.w[l], t * 32 + 32, K, fp8_scale_inv(__float_as_uint(weight_amax(hd, l))), t, s0, bw.dst[l], nullptr);
+    } else {
+      const int KS = K >> 4;
+      const u32x4 *row = (const u32x4 *)(bw.w[l] + (size_t)(t * 32 + (lane & 31)) * K);
+      u32x4 w[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) w[u] = s0 + u < KS ? row[(s0 + u) * 2 + (lane >> 5)] : u32x4{0u, 0u, 0u, 0u};
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if (s0 + u < KS) bw.dst[l][((size_t)t * KS + s0 + u) * 64 + lane] = w[u];
+    }
+    return;
+  }
+  if constexpr (FP8) {
+    if (wave < 4) {
+      const float wm = weight_amax(hd, wave), ia = history_inv(hd, wave), iw = fp8_scale_inv(__float_as_uint(wm));
+      if (lane == 0) {
+        uint32_t *s = hd.sc + wave * kFp8Words;
+        s[0] = 0u;
+        s[1] = __float_as_uint(wm);
+        s[2] = __float_as_uint(ia);
+        s[3] = __float_as_uint(iw);
+        s[4] = __float_as_uint((1.0f / ia) * (1.0f / iw));
+        if (hd.partial) hd.wamax[wave] = __float_as_uint(wm);
+      }
+    }
+  }
+}
+
+static int launch_block_head(const uint16_t *z, const float *gamma, const float *beta, int64_t M, int64_t Mp, int C, u32x4 *packed,
+                             const BlockWeights4 *bw, bool fp8, const Fp8Head &hd, hipStream_t st) {
+  const int cpl = (C / 8 + 63) / 64;
+  if (C % 32 != 0 || cpl > 4 || Mp % 32 != 0 || Mp < M) return LV_ERR_SHAPE;
+  const int per = (fp8 ? 32 : 16) * 4 * kLnWaves, n_ln = packed ? (int)(Mp / 32) : 0;
+  const int n_pack = bw ? C / 32 * (8 * ((C + per - 1) / per) + (4 * C + per - 1) / per) : 0;
+  const unsigned grid = (unsigned)(n_ln + n_pack + (fp8 ? 1 : 0));
+  const size_t lds = packed ? (size_t)32 * (C / 8 + 1) * 16 : 0;
+  static std::atomic<uint64_t> lds_done[8];
+  const BlockWeights4 w4 = bw ? *bw : BlockWeights4{};
+  int rc;
+#define LV_HEAD(CPL, F8)                                                                                       \
+  if ((rc = allow_dynamic_lds((const void *)k_block_head<CPL, F8>, (size_t)32 * (C / 8 + 1) * 16, lds_done[(CPL - 1) * 2 + F8]))) \
+    return rc;                                                                                                 \
+  hipLaunchKernelGGL((k_block_head<CPL, F8>), dim3(grid), dim3(64 * kLnWaves), lds, st, z, gamma, beta, M, C, n_ln, packed, w4, n_pack, hd)
+#define LV_HEADS(F8)                   \
+  switch (cpl) {                       \
+    case 1: LV_HEAD(1, F8); break;     \
+    case 2: LV_HEAD(2, F8); break;     \
+    case 3: LV_HEAD(3, F8); break;     \
+    default: LV_HEAD(4, F8); break;    \
+  }
+  if (fp8) {
+    LV_HEADS(true)
+  } else {
+    LV_HEADS(false)
+  }
+#undef LV_HEADS
+#undef LV_HEAD
+  LV_HIP_CHECK_LAUNCH();
+  return LV_OK;
 }
 
 // ---------------------------------------------------------------------------------------
@@ -441,7 +534,7 @@ struct GemmShape {
 // of Abramowitz & Stegun 7.1.26 (absolute error <= 1.5e-7, four orders below a bf16 step) with sqrt 2 and the
 // half in its constants; the negative side uses erfc itself, so nothing cancels there.  The epilogue of the
 // first MLP layer evaluates it 65536 times per tile, where it is as long as an E4M3 main loop: 12 VALU instructions and
-// two transcendental ones (as v / 2 * (2 - erfc) with a select 17 and two: TIMES).  Against 64 bits on
+// two transcendental ones (as v / 2 * (2 - erfc) with a select 17 and two; C = 1024, E4M3, the layer at M = 5,776 46.6 -> 39.7 us, 15,432 107 -> 99).  Against 64 bits on
 // [-12, 12] never further off than that form.  (|v| beyond 64, where the product is 0, is held there: infinity stays.)
 __device__ __forceinline__ float gelu_erf(float v) {
   const float a = fminf(fabsf(v), 64.0f);
@@ -452,6 +545,26 @@ __device__ __forceinline__ float gelu_erf(float v) {
   p = __builtin_fmaf(p, t, 0.127414796f);
   const float half_erfc = p * t * __builtin_amdgcn_exp2f(-0.72134752f * v * v);
   return __builtin_fmaf(-a, half_erfc, fmaxf(v, 0.f));
+}
+
+// What the block's last layer leaves behind under delayed scaling: the four layers' input amaxes go into their
+// histories (a launch of their own took 4.5 us; every amax is known once the third layer has run).
+struct Fp8Record {
+  float *state = nullptr;             // NULL: nothing to record
+  const uint32_t *sc = nullptr;       // layers 1 to 3: word 0
+  const uint32_t *ln_part = nullptr;  // layer 0: n_part row tiles' maxima
+  int n_part = 0;
+};
+__device__ __forceinline__ void record_amaxes(const Fp8Record &rec, int lane) {
+  float m = 0.f;
+  for (int i = lane; i < rec.n_part; i += 64) m = fmaxf(m, __uint_as_float(rec.ln_part[i]));
+  m = wave_max(m);
+  if (lane < 4) {
+    float *hist = rec.state + (size_t)lane * (LV_FP8_HISTORY + 2);
+    uint32_t *step = (uint32_t *)(hist + LV_FP8_HISTORY);
+    hist[*step % LV_FP8_HISTORY] = lane == 0 ? m : __uint_as_float(rec.sc[lane * kFp8Words]);
+    *step += 1;
+  }
 }
 
 // max(m, |a|, |b|) in one instruction (written as fmaxf of fabsf, values taken from their bits are made canonical first)
@@ -466,7 +579,7 @@ __global__ __launch_bounds__((GemmShape<BM, BN>::kThreads * KG)) __attribute__((
     const u32x4 *__restrict__ ap, const u32x4 *__restrict__ wp, int64_t M, int KS, int nt_n,
     const float *__restrict__ bias, int gelu, uint16_t *__restrict__ out, int split,
     const float *__restrict__ alpha_p, int n_tiles, int rows_by_xcd, const uint16_t *__restrict__ addend,
-    const uint32_t *__restrict__ out_inv, uint32_t *__restrict__ out_amax) {
+    const uint32_t *__restrict__ out_inv, uint32_t *__restrict__ out_amax, Fp8Record rec) {
   using S = GemmShape<BM, BN>;
   constexpr int kStages = S::kStages, kStageU4 = S::kStageU4, kB = S::kB;
   constexpr bool kTwoSets = !FP8 || kB <= 2;   // registers for two sets of weight fragments
@@ -867,6 +980,8 @@ __global__ __launch_bounds__((GemmShape<BM, BN>::kThreads * KG)) __attribute__((
     __syncthreads();
     if (tid == 0) raise_max(out_amax, __uint_as_float(wg_amax));
   }
+  if constexpr (FP8 && !PACKED)
+    if (rec.state && blockIdx.x == gridDim.x - 1 && tid < 64) record_amaxes(rec, lane);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -900,7 +1015,7 @@ static BlockWs carve_block(int64_t M, int C, int heads, int attn_dtype, bool lea
   w.apack = (u32x4 *)take((size_t)w.Mp * 4 * C);       // a layer's activation operand: bf16 with K = C, FP8 with K <= 4C
   w.wpack = (u32x4 *)take(block_wpack_bytes(C));
   w.fp8sc = (uint32_t *)take(4 * kFp8Words * sizeof(uint32_t));   // one set per linear layer
-  w.wpart = (uint32_t *)w.apack;   // the weights' partial maxima, gone before the first activation
+  w.wpart = (uint32_t *)w.h3;   // the weights' partial maxima, gone before the first MLP layer writes there
   w.attn_bytes = attn_ws_bytes(heads, M, attn_dtype, 1, least);
   w.attn = take(w.attn_bytes);
   w.bytes = off;
@@ -920,12 +1035,13 @@ struct LinearOpts {
   bool pack_out = false;
   const uint16_t *addend = nullptr;    // row-major, same shape as out: out = addend + result
   const u32x4 *w_packed = nullptr;     // the weight operand
-  // FP8: this layer's scalars, prepared by k_fp8_prepare.  A, unless a_packed, is quantised with
+  // FP8: this layer's scalars, prepared by k_block_head.  A, unless a_packed, is quantised with
   // sc[2] and its amax reduced into sc[0]; `current`: sc[2] and sc[4] are taken from that amax first
   uint32_t *sc = nullptr;
   bool current = false;
   const uint32_t *out_inv = nullptr;   // FP8 pack_out: the next layer's input scale ...
   uint32_t *out_amax = nullptr;        // ... and where the largest |output| is reduced into
+  Fp8Record rec;                       // FP8, not pack_out: what to record once it has run
 };
 
 // Which output tile suits M rows and Nout columns: 256 x 256 (one workgroup per CU), 128 x 256 or
@@ -1004,7 +1120,7 @@ static int launch_linear(const uint16_t *A, int64_t M, int K, int Nout,
     const unsigned grid = (unsigned)(n_tiles > slots ? slots : by_xcd ? fullest * kXcd : n_tiles);
     hipLaunchKernelGGL((k_gemm_bt<F8, PK, BM, BN, KG>), dim3(grid), dim3(S::kThreads * KG), kLds, st, act,
                        o.w_packed, M, KS, nt_n, bias, gelu, out, split, alpha, n_tiles, by_xcd ? 1 : 0, o.addend, o.out_inv,
-                       o.out_amax);
+                       o.out_amax, o.rec);
     return LV_OK;
   };
   auto launch = [&](auto fp8, const u32x4 *act, int KS, const float *alpha) -> int {
@@ -1048,49 +1164,6 @@ static int launch_linear(const uint16_t *A, int64_t M, int K, int Nout,
   return LV_OK;
 }
 
-// Every layer's scalars, prepared ahead of the kernels that produce the layers' inputs: block L of
-// the grid fills the 8 words of layer L (input amax cleared, the weight's amax and 448 / it; delayed
-// scaling: also 448 / the largest recorded input amax, and the product of the two inverse scales;
-// a history with nothing recorded yet gives scale 1).  partial: the weights' partial maxima, which
-// are reduced into wamax first; NULL: wamax holds the amaxes.
-__global__ __launch_bounds__(64) void k_fp8_prepare(uint32_t *__restrict__ sc, const float *__restrict__ state,
-                                                    uint32_t *__restrict__ wamax, const uint32_t *__restrict__ partial) {
-  const int lane = threadIdx.x, L = blockIdx.x;
-  float wm = 0.f;
-  if (partial) {
-    const int e = weight_first_unit(L + 1) * kWAmaxUnit;
-    for (int i = weight_first_unit(L) * kWAmaxUnit + lane; i < e; i += 64) wm = fmaxf(wm, __uint_as_float(partial[i]));
-    wm = wave_max(wm);
-    if (lane == 0) wamax[L] = __float_as_uint(wm);
-  } else {
-    wm = __uint_as_float(wamax[L]);
-  }
-  float m = 0.f;
-  if (state) {
-    const float *hist = state + (size_t)L * (LV_FP8_HISTORY + 2);
-    m = wave_max(fmaxf(hist[lane], lane + 64 < LV_FP8_HISTORY ? hist[lane + 64] : 0.f));
-  }
-  if (lane == 0) {
-    uint32_t *s = sc + L * kFp8Words;
-    const float ia = fp8_scale_inv(__float_as_uint(m)), iw = fp8_scale_inv(__float_as_uint(wm));
-    s[0] = 0u;
-    s[1] = __float_as_uint(wm);
-    s[2] = __float_as_uint(ia);
-    s[3] = __float_as_uint(iw);
-    s[4] = __float_as_uint((1.0f / ia) * (1.0f / iw));
-  }
-}
-
-// ... and, once the four layers have run, each layer's input amax goes into its history
-__global__ void k_fp8_record_all(const uint32_t *__restrict__ sc, float *__restrict__ state) {
-  if (threadIdx.x < 4) {
-    float *hist = state + (size_t)threadIdx.x * (LV_FP8_HISTORY + 2);
-    uint32_t *step = (uint32_t *)(hist + LV_FP8_HISTORY);
-    hist[*step % LV_FP8_HISTORY] = __uint_as_float(sc[threadIdx.x * kFp8Words]);
-    *step += 1;
-  }
-}
-
 int launch_global_block(const uint16_t *z, int64_t M, int C, int heads, float scale, int attn_dtype,
                         int qk_norm, const litevggt_block_weights &bw, uint16_t *delta, void *ws,
                         size_t ws_bytes, hipStream_t st, hipEvent_t after_pack, hipEvent_t after_attn, void *wpack_keep,
@@ -1115,18 +1188,16 @@ int launch_global_block(const uint16_t *z, int64_t M, int C, int heads, float sc
   const float *const bias[4] = {bw.b_qkv, bw.b_o, bw.b_1, bw.b_2};
   const uint16_t *q = w.qkv, *k = w.qkv + (size_t)M * C, *v = w.qkv + (size_t)2 * M * C;
 
-  // the weights' amaxes and every layer's scalars, then the weights into operand order
-  const int unit = f8 ? 32 : 16, g1 = (C / unit + 15) / 16, g4 = (4 * C / unit + 15) / 16;
-  const unsigned wgrid = (unsigned)(C / 32 * (8 * g1 + g4));
+  // the weights' amaxes, then every layer's scalars, the weights into operand order and (bf16 layers and delayed
+  // scaling, where its scale is known) the first LayerNorm into the first layer's operand
+  Fp8Head hd{};
   if (f8) {
     if (pack_w) hipLaunchKernelGGL(k_weights_amax, dim3(kWAmaxParts), dim3(256), 0, st, bw4, C, w.wpart);
-    hipLaunchKernelGGL(k_fp8_prepare, dim3(4), dim3(64), 0, st, w.fp8sc, delayed ? (const float *)bw.fp8_state : nullptr,
-                       wamax, pack_w ? (const uint32_t *)w.wpart : (const uint32_t *)nullptr);
-    if (pack_w) hipLaunchKernelGGL(k_weights_pack<true>, dim3(wgrid), dim3(256), 0, st, bw4, C, (const uint32_t *)w.fp8sc);
-  } else if (pack_w) {
-    hipLaunchKernelGGL(k_weights_pack<false>, dim3(wgrid), dim3(256), 0, st, bw4, C, (const uint32_t *)nullptr);
+    hd = Fp8Head{w.fp8sc, delayed ? (const float *)bw.fp8_state : nullptr, wamax, pack_w ? (const uint32_t *)w.wpart : nullptr,
+                 (uint32_t *)w.h};
   }
-  LV_HIP_CHECK_LAUNCH();
+  u32x4 *const ln_packed = f8 && !delayed ? nullptr : w.apack;
+  if ((rc = launch_block_head(z, bw.ln1_g, bw.ln1_b, M, w.Mp, C, ln_packed, pack_w ? &bw4 : nullptr, f8, hd, st))) return rc;
 
   if (delayed) {
     // FP8 layers, delayed scaling: every input scale is known before its tensor exists, so the
@@ -1140,7 +1211,6 @@ int launch_global_block(const uint16_t *z, int64_t M, int C, int heads, float sc
       o.w_packed = wp_l[l];
       return o;
     };
-    if ((rc = launch_layernorm(z, nullptr, bw.ln1_g, bw.ln1_b, M, C, nullptr, st, w.apack, w.Mp, sc + 2, sc))) return rc;
     LinearOpts o = layer(0);
     o.a_packed = w.apack;
     if ((rc = launch_linear(nullptr, M, C, 3 * C, bias[0], 0, w.qkv, C, w, st, o))) return rc;
@@ -1160,10 +1230,11 @@ int launch_global_block(const uint16_t *z, int64_t M, int C, int heads, float sc
     o = layer(3);
     o.a_packed = (const u32x4 *)w.h3;
     o.addend = w.u1;
-    if ((rc = launch_linear(nullptr, M, 4 * C, C, bias[3], 0, delta, C, w, st, o))) return rc;
-    hipLaunchKernelGGL(k_fp8_record_all, dim3(1), dim3(64), 0, st, (const uint32_t *)sc, (float *)bw.fp8_state);
-    LV_HIP_CHECK_LAUNCH();
-    return LV_OK;
+    o.rec.state = (float *)bw.fp8_state;
+    o.rec.sc = sc;
+    o.rec.ln_part = hd.ln_part;
+    o.rec.n_part = (int)(w.Mp / 32);
+    return launch_linear(nullptr, M, 4 * C, C, bias[3], 0, delta, C, w, st, o);
   }
 
   auto layer = [&](int l) {
@@ -1174,8 +1245,7 @@ int launch_global_block(const uint16_t *z, int64_t M, int C, int heads, float sc
     return o;
   };
   // bf16 layers: the LayerNorms write their result in the following layer's operand order
-  u32x4 *const ln_packed = f8 ? nullptr : w.apack;
-  if ((rc = launch_layernorm(z, nullptr, bw.ln1_g, bw.ln1_b, M, C, w.h, st, ln_packed, w.Mp))) return rc;
+  if (f8 && (rc = launch_layernorm(z, nullptr, bw.ln1_g, bw.ln1_b, M, C, w.h, st))) return rc;
   LinearOpts o = layer(0);
   o.a_packed = ln_packed;
   if ((rc = launch_linear(w.h, M, C, 3 * C, bias[0], 0, w.qkv, C, w, st, o))) return rc;
