@@ -29,21 +29,11 @@ constexpr int kQW = 64;              // queries per wave
 constexpr int kQB = 512;             // queries per workgroup (8 waves)
 constexpr int kFragU4 = 64;          // one fragment = 64 lanes x 16 B
 
-constexpr float kQkEps = 1e-6f;
 constexpr float kRaise = 8.0f;       // log2 headroom before the softmax reference is raised
 
 // RMS-normalise a 64-value head row that is spread over 2^log2_lanes neighbouring lanes (8
 // bf16 values each, or several such chunks per lane): returns this lane's chunk scaled by
 // 1/sqrt(mean(x^2) + eps), rounded to bf16.
-__device__ __forceinline__ float sumsq8(const u32x4 w) {
-  const float a0 = bf16_lo(w.x), a1 = bf16_hi(w.x), a2 = bf16_lo(w.y), a3 = bf16_hi(w.y);
-  const float a4 = bf16_lo(w.z), a5 = bf16_hi(w.z), a6 = bf16_lo(w.w), a7 = bf16_hi(w.w);
-  return ((a0 * a0 + a1 * a1) + (a2 * a2 + a3 * a3)) + ((a4 * a4 + a5 * a5) + (a6 * a6 + a7 * a7));
-}
-__device__ __forceinline__ u32x4 scale8(const u32x4 w, float r) {
-  return u32x4{pack_bf16(bf16_lo(w.x) * r, bf16_hi(w.x) * r), pack_bf16(bf16_lo(w.y) * r, bf16_hi(w.y) * r),
-               pack_bf16(bf16_lo(w.z) * r, bf16_hi(w.z) * r), pack_bf16(bf16_lo(w.w) * r, bf16_hi(w.w) * r)};
-}
 __device__ __forceinline__ u32x4 rms_scale8(const u32x4 w, int log2_lanes) {
   float ss = sumsq8(w);
   for (int o = 1; o < (1 << log2_lanes); o <<= 1) ss += __shfl_xor(ss, o, 64);
@@ -1698,12 +1688,8 @@ __global__ __launch_bounds__(256) void k_attn_amax(const uint16_t *__restrict__ 
   }
 }
 
-// amax[0..2] from the n_part parts, and the flags cleared
-__global__ __launch_bounds__(256) void k_attn_amax_final(const f32x4 *__restrict__ part, int n_part, uint32_t *__restrict__ amax,
-                                                         uint32_t *__restrict__ flags, size_t n_flags) {
-  const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
-  if (i < n_flags) flags[i] = 0u;
-  if (blockIdx.x != 0) return;
+// amax[0..2] from the n_part parts
+__global__ __launch_bounds__(256) void k_attn_amax_final(const f32x4 *__restrict__ part, int n_part, uint32_t *__restrict__ amax) {
   __shared__ float red[3][4];
   f32x4 m = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll 8
@@ -2049,12 +2035,14 @@ __global__ __launch_bounds__(256) void k_attn_pack_fp8b(const uint16_t *__restri
                                                         const uint16_t *__restrict__ v, int64_t n,
                                                         int heads, int n_kt,
                                                         const uint32_t *__restrict__ amax,
-                                                        u32x2 *__restrict__ kp, u32x2 *__restrict__ vp) {
+                                                        u32x2 *__restrict__ kp, u32x2 *__restrict__ vp,
+                                                        uint32_t *__restrict__ flags, int n_flags) {
   __shared__ __attribute__((aligned(8))) uint8_t vt[kKT][72];
   const int kt = blockIdx.x, head = blockIdx.y, t = threadIdx.x;
   const int C = heads * 64;
   const int key = t >> 3, chunk = t & 7;
   const int64_t row = (int64_t)kt * kKT + key;
+  if (t == 0 && kt < n_flags) flags[(size_t)head * n_flags + kt] = 0u;   // (n_flags <= n_kt per head)
   u32x4 wk = {0u, 0u, 0u, 0u}, wv = {0u, 0u, 0u, 0u};
   if (row < n) {
     wk = *(const u32x4 *)(k + (size_t)row * C + head * 64 + chunk * 8);
@@ -2401,6 +2389,79 @@ size_t attn_ws_bytes(int heads, int64_t n_tokens, int attn_dtype, int n_seq, boo
   return total;
 }
 
+namespace {
+// Where a call's parts lie in its scratch.
+struct AttnPlan {
+  bool bounded, is_short = false, stream = false;
+  AttnCut cut = {0, 0};
+  size_t per, words;
+  int n_kt, nqb, nqb2, nqs, n_cu = 0;
+  uint32_t *head;           // 64 words: E4M3 the amaxes, else the counters of a stream's blocks
+  char *frag;
+  uint32_t *redo, *sync;
+  float *partial;
+};
+}  // namespace
+
+static int attn_plan(AttnPlan &a, int64_t n, int heads, float scale, int attn_dtype, int qk_norm, const void *q, const void *o,
+                     void *ws, size_t ws_bytes, int n_seq, const void *res) {
+  if (n_seq < 1 || (int64_t)heads * n_seq > 65535) return LV_ERR_SHAPE;
+  if ((n_seq > 1 || res) && attn_dtype != LV_ATTN_BF16) return LV_ERR_DTYPE;
+  if (attn_dtype != LV_ATTN_BF16 && attn_dtype != LV_ATTN_FP8_E4M3) return LV_ERR_DTYPE;
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess ||
+      hipDeviceGetAttribute(&a.n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+    return LV_ERR_HIP;
+  const float c = scale * 1.4426950408889634f;
+  const bool f8 = attn_dtype == LV_ATTN_FP8_E4M3;
+  a.n_kt = n_key_tiles(n);
+  a.nqb = (int)((n + kQB - 1) / kQB);
+  a.nqb2 = (int)((n + kBQB - 1) / kBQB);
+  a.nqs = (int)((n + kQW - 1) / kQW);
+  a.head = (uint32_t *)ws;
+  a.frag = (char *)ws + 256;
+  a.per = align_up((size_t)heads * n_seq * a.n_kt * 4 * kFragU4 * (f8 ? sizeof(u32x2) : sizeof(u32x4)), 256);
+  a.words = fp8_flag_words(heads * n_seq, n);
+  a.redo = (uint32_t *)(a.frag + (f8 ? 4 : 2) * a.per);
+  a.sync = a.redo + align_up(a.words * 4, 256) / 4;
+  a.partial = (float *)(a.sync + kSyncWords);
+  // two ways: q, k normalised with exponents that stay in range: the branch-free kernel with
+  // no (E4M3: a fixed) reference; otherwise (q, k as given, or a softmax scale beyond that range) the same kernel
+  // as online softmax with a per-wave running reference, then the per-row kernel on the query
+  // blocks the first pass flagged (normally none: its workgroups return at once)
+  a.bounded = qk_norm && (f8 ? kF8Bound : 64.25f) * c <= 64.0f;
+  if (f8) return LV_OK;
+  a.is_short = attn_is_short((int64_t)a.nqs * heads * n_seq, a.bounded, n_seq == 1 && heads % kXcd == 0, res || o == q, a.n_cu);
+  if (!a.is_short && n_seq == 1 && !res && 2 * a.n_cu == kXcd * kSlots && ws_bytes >= attn_ws_bytes(heads, n, attn_dtype))
+    a.cut = attn_cut(heads, n, a.bounded);
+  // more blocks than slots: workgroups that stay (their rows are written and the residual's read 16 bytes
+  // at a time, the main kernel's 8)
+  const int64_t n_blocks = (int64_t)a.nqb2 * heads * n_seq;
+  a.stream = a.bounded && a.n_kt / 2 >= kStreamStages && a.n_kt / 2 <= kStreamMost && n_blocks > 2 * a.n_cu &&
+             n_blocks < ((int64_t)1 << 30) && a.n_cu % 4 == 0 && (((uintptr_t)o | (uintptr_t)res) & 15u) == 0;
+  return LV_OK;
+}
+
+int attn_kv_target(AttnKV &kv, int64_t n, int heads, float scale, int attn_dtype, int qk_norm, const void *q, const void *o, void *ws,
+                   size_t ws_bytes) {
+  AttnPlan a;
+  if (int rc = attn_plan(a, n, heads, scale, attn_dtype, qk_norm, q, o, ws, ws_bytes, 1, nullptr)) return rc;
+  kv = AttnKV{};
+  kv.qk_norm = qk_norm;
+  kv.clear[0] = a.head;
+  kv.n_clear[0] = kStreamWords;
+  if (attn_dtype == LV_ATTN_FP8_E4M3) {
+    kv.amax = a.head;
+    return LV_OK;
+  }
+  kv.kp = a.frag;
+  kv.vp = a.frag + a.per;
+  kv.n_kt = a.n_kt;
+  kv.clear[1] = a.bounded ? a.sync : a.redo;   // the flags and, behind them, the words that pieces of cut blocks meet at
+  kv.n_clear[1] = (a.bounded ? 0 : (int)(a.sync - a.redo)) + (a.cut.n_cut ? kSyncWords : 0);
+  return LV_OK;
+}
+
 // n_seq independent sequences of n tokens each, stored one after the other (n_seq = 1: the
 // global attention over the merged sequence; n_seq = frames: frame attention).  Several
 // sequences and the fused residual (o = res + attention, res may be o: a workgroup reads the
@@ -2408,37 +2469,33 @@ size_t attn_ws_bytes(int heads, int64_t n_tokens, int attn_dtype, int n_seq, boo
 int launch_attn(const uint16_t *q, const uint16_t *k, const uint16_t *v, uint16_t *o,
                 int64_t n, int heads, float scale, int attn_dtype, int qk_norm, void *ws, size_t ws_bytes,
                 hipStream_t st, hipEvent_t after_pack, int n_seq, const uint16_t *res,
-                void *o_packed, bool *wrote_packed) {
+                void *o_packed, bool *wrote_packed, const AttnKV *ready) {
   if (wrote_packed) *wrote_packed = false;
-  if (n_seq < 1 || (int64_t)heads * n_seq > 65535) return LV_ERR_SHAPE;
-  if ((n_seq > 1 || res) && attn_dtype != LV_ATTN_BF16) return LV_ERR_DTYPE;
-  const int n_kt = n_key_tiles(n);
+  AttnPlan a;
+  if (int rc = attn_plan(a, n, heads, scale, attn_dtype, qk_norm, q, o, ws, ws_bytes, n_seq, res)) return rc;
+  const bool bounded = a.bounded, is_short = a.is_short, stream = a.stream;
+  const int n_kt = a.n_kt, nqb = a.nqb, nqb2 = a.nqb2, nqs = a.nqs, n_cu = a.n_cu;
   const float c = scale * 1.4426950408889634f;
-  const int nqb = (int)((n + kQB - 1) / kQB);
-  uint32_t *amax = (uint32_t *)ws;
-  char *frag = (char *)ws + 256;
+  const AttnCut cut = a.cut;
+  uint32_t *const redo = a.redo;
   if (attn_dtype == LV_ATTN_FP8_E4M3) {
-    const size_t per = align_up((size_t)heads * n_kt * 4 * kFragU4 * sizeof(u32x2), 256);
-    u32x2 *kp = (u32x2 *)frag, *vp = (u32x2 *)(frag + per);
+    uint32_t *const amax = a.head;
+    u32x2 *kp = (u32x2 *)a.frag, *vp = (u32x2 *)(a.frag + a.per);
     const int C = heads * 64;
-    const int64_t nchunks = n * (C / 8);
-    const unsigned ag = (unsigned)(((nchunks + 255) / 256) < 2048 ? ((nchunks + 255) / 256) : 2048);
-    // bounded scores (unit-RMS heads, exponent range checked like for bf16): the branch-free
-    // kernel against the fixed reference first, then the running-maximum kernel on the query
-    // blocks the first one flagged (normally none: its workgroups return at once)
-    const bool bounded = qk_norm && kF8Bound * c <= 64.0f;
-    uint32_t *redo = (uint32_t *)(frag + 4 * per);
-    const size_t words = bounded ? fp8_flag_words(heads, n) : 0;
-    f32x4 *const part = (f32x4 *)kp;   // (16 bytes per 2048 of K, gone before K is written)
-    hipLaunchKernelGGL(k_attn_amax, dim3(ag), dim3(256), 0, st, q, k, v, n, C, qk_norm, part);
-    hipLaunchKernelGGL(k_attn_amax_final, dim3((unsigned)((words + 255) / 256 + 1)), dim3(256), 0, st, (const f32x4 *)part,
-                       (int)ag, amax, redo, words);
+    if (!(ready && ready->amax)) {   // (else the layer that produced q, k and v has taken them)
+      const int64_t nchunks = n * (C / 8);
+      const unsigned ag = (unsigned)(((nchunks + 255) / 256) < 2048 ? ((nchunks + 255) / 256) : 2048);
+      f32x4 *const part = (f32x4 *)kp;   // (16 bytes per 2048 of K, gone before K is written)
+      hipLaunchKernelGGL(k_attn_amax, dim3(ag), dim3(256), 0, st, q, k, v, n, C, qk_norm, part);
+      hipLaunchKernelGGL(k_attn_amax_final, dim3(1), dim3(256), 0, st, (const f32x4 *)part, (int)ag, amax);
+    }
     if (bounded) {
-      u32x2 *kpb = (u32x2 *)(frag + 2 * per), *vpb = (u32x2 *)(frag + 3 * per);
+      // the branch-free kernel against the fixed reference first, then the running-maximum kernel on the query
+      // blocks the first one flagged (normally none: its workgroups return at once)
+      u32x2 *kpb = (u32x2 *)(a.frag + 2 * a.per), *vpb = (u32x2 *)(a.frag + 3 * a.per);
       hipLaunchKernelGGL(k_attn_pack_fp8b, dim3((unsigned)n_kt, (unsigned)heads), dim3(256), 0, st, k, v, n,
-                         heads, n_kt, amax, kpb, vpb);
+                         heads, n_kt, amax, kpb, vpb, redo, 2 * nqb);
       if (after_pack && hipEventRecord(after_pack, st) != hipSuccess) return LV_ERR_HIP;
-      const int nqb2 = (int)((n + kBQB - 1) / kBQB);
       hipLaunchKernelGGL(k_attn_fp8_bounded, dim3((unsigned)(nqb2 * heads)), dim3(256), 0, st, q,
                          (const u32x4 *)kpb, (const u32x4 *)vpb, o, n, heads, n_kt / 2, nqb2, c, amax, redo,
                          2 * nqb);
@@ -2454,35 +2511,9 @@ int launch_attn(const uint16_t *q, const uint16_t *k, const uint16_t *v, uint16_
     LV_HIP_CHECK_LAUNCH();
     return LV_OK;
   }
-  if (attn_dtype != LV_ATTN_BF16) return LV_ERR_DTYPE;
-  const size_t per = align_up((size_t)heads * n_seq * n_kt * 4 * kFragU4 * sizeof(u32x4), 256);
-  u32x4 *kp = (u32x4 *)frag;
-  u32x4 *vp = (u32x4 *)(frag + per);
-  // two ways: q, k normalised with exponents that stay in range: the branch-free kernel with
-  // no reference; otherwise (q, k as given, or a softmax scale beyond that range) the same kernel
-  // as online softmax with a per-wave running reference, then the per-row kernel on the query
-  // blocks the first pass flagged (normally none: its workgroups return at once)
-  const bool bounded = qk_norm && 64.25f * c <= 64.0f;
-  uint32_t *redo = (uint32_t *)(frag + 2 * per);
-  const size_t words = fp8_flag_words(heads * n_seq, n);
-  const int nqb2 = (int)((n + kBQB - 1) / kBQB);
-  int dev = 0, n_cu = 0;
-  if (hipGetDevice(&dev) != hipSuccess ||
-      hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
-    return LV_ERR_HIP;
-  const int nqs = (int)((n + kQW - 1) / kQW);
-  const bool is_short = attn_is_short((int64_t)nqs * heads * n_seq, bounded, n_seq == 1 && heads % kXcd == 0, res || o == q, n_cu);
-  AttnCut cut = {0, 0};
-  if (!is_short && n_seq == 1 && !res && 2 * n_cu == kXcd * kSlots && ws_bytes >= attn_ws_bytes(heads, n, attn_dtype))
-    cut = attn_cut(heads, n, bounded);
-  uint32_t *sync = redo + align_up(words * 4, 256) / 4;
-  float *partial = (float *)(sync + kSyncWords);
-  // more blocks than slots: workgroups that stay (their rows are written and the residual's read 16 bytes
-  // at a time, the main kernel's 8)
-  uint32_t *const ctr = (uint32_t *)ws;
-  const int64_t n_blocks = (int64_t)nqb2 * heads * n_seq;
-  const bool stream = bounded && n_kt / 2 >= kStreamStages && n_kt / 2 <= kStreamMost && n_blocks > 2 * n_cu && n_blocks < ((int64_t)1 << 30) &&
-                      n_cu % 4 == 0 && (((uintptr_t)o | (uintptr_t)res) & 15u) == 0;
+  u32x4 *kp = (u32x4 *)a.frag, *vp = (u32x4 *)(a.frag + a.per);
+  uint32_t *const sync = a.sync, *const ctr = a.head;
+  float *const partial = a.partial;
   auto pack_kernel = [&](auto has_sync) {
     constexpr bool SYNC = decltype(has_sync)::value;
     uint32_t *const cleared = stream ? ctr : sync;
@@ -2495,7 +2526,8 @@ int launch_attn(const uint16_t *q, const uint16_t *k, const uint16_t *v, uint16_
       hipLaunchKernelGGL((k_attn_pack<SYNC, true>), grid, dim3(256), 0, st, k, v, n, heads, n_kt, qk_norm, kp, vp, cleared,
                          n_cleared, redo, 2 * nqb);
   };
-  if (cut.n_cut || stream) pack_kernel(std::true_type{});
+  if (ready && ready->kp) {}          // the layer that produced k and v has packed them, and what they clear is cleared
+  else if (cut.n_cut || stream) pack_kernel(std::true_type{});
   else pack_kernel(std::false_type{});
   if (after_pack && hipEventRecord(after_pack, st) != hipSuccess) return LV_ERR_HIP;
   auto main_kernel = [&](auto online, auto packed, uint16_t *out) {

@@ -376,7 +376,7 @@ __global__ __launch_bounds__(256) void k_weights_amax(BlockWeights4 bw, int C, u
 // ---- The head of a block: what its first linear layer waits for, in one launch.  Workgroups by number: the
 // first LayerNorm's row tiles (n_ln; the longest chain, so they start first), the weights on their way into operand
 // order (n_pack; per weight (rows / 32) row tiles x ceil(k-steps / 32) groups, one weight after the other), and
-// with FP8 one for the layers' scalars.  All three depend on inputs only: with FP8 a workgroup takes the scale it needs from
+// one for the layers' scalars (FP8) and for words that the attention needs cleared.  All three depend on inputs only: with FP8 a workgroup takes the scale it needs from
 // the weights' partial maxima or the amax history itself.  Apart they were three launches one after the other that
 // each left most of the chip waiting: C = 1024, us, 5,776 rows in bf16 10.9 + 10.3, now 16.4; 15,432 rows in E4M3
 // 4.5 + 8.5 + 19.1, now 26.9; whole blocks of 394 rows in bf16 74.7 -> 70.0, in E4M3 (delayed scaling) 81.2 -> 73.6.
@@ -386,6 +386,10 @@ struct Fp8Head {
   uint32_t *wamax;           // the weights' amaxes: written (partial != NULL), or read
   const uint32_t *partial;   // the weights' partial maxima, or NULL
   uint32_t *ln_part;         // receives every row tile's largest |value| (the history's; no word to clear before)
+};
+struct ClearWords {          // what the attention (AttnKV) finds cleared
+  uint32_t *at[2];
+  int n[2];
 };
 __device__ __forceinline__ float weight_amax(const Fp8Head &hd, int l) {
   if (!hd.partial) return __uint_as_float(hd.wamax[l]);
@@ -405,7 +409,8 @@ __device__ __forceinline__ float history_inv(const Fp8Head &hd, int l) {
 template <int CPL, bool FP8>
 __global__ __launch_bounds__(64 * kLnWaves) void k_block_head(const uint16_t *__restrict__ z, const float *__restrict__ gamma,
                                                               const float *__restrict__ beta, int64_t M, int C, int n_ln,
-                                                              u32x4 *__restrict__ packed, BlockWeights4 bw, int n_pack, Fp8Head hd) {
+                                                              u32x4 *__restrict__ packed, BlockWeights4 bw, int n_pack, Fp8Head hd,
+                                                              ClearWords cw) {
   extern __shared__ u32x4 ln_stage[];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   int b = blockIdx.x;
@@ -438,6 +443,9 @@ __global__ __launch_bounds__(64 * kLnWaves) void k_block_head(const uint16_t *__
     }
     return;
   }
+#pragma unroll
+  for (int r = 0; r < 2; ++r)
+    for (int i = threadIdx.x; i < cw.n[r]; i += 64 * kLnWaves) cw.at[r][i] = 0u;
   if constexpr (FP8) {
     if (wave < 4) {
       const float wm = weight_amax(hd, wave), ia = history_inv(hd, wave), iw = fp8_scale_inv(__float_as_uint(wm));
@@ -455,12 +463,13 @@ __global__ __launch_bounds__(64 * kLnWaves) void k_block_head(const uint16_t *__
 }
 
 static int launch_block_head(const uint16_t *z, const float *gamma, const float *beta, int64_t M, int64_t Mp, int C, u32x4 *packed,
-                             const BlockWeights4 *bw, bool fp8, const Fp8Head &hd, hipStream_t st) {
+                             const BlockWeights4 *bw, bool fp8, const Fp8Head &hd, const AttnKV &kv, hipStream_t st) {
   const int cpl = (C / 8 + 63) / 64;
   if (C % 32 != 0 || cpl > 4 || Mp % 32 != 0 || Mp < M) return LV_ERR_SHAPE;
   const int per = (fp8 ? 32 : 16) * 4 * kLnWaves, n_ln = packed ? (int)(Mp / 32) : 0;
   const int n_pack = bw ? C / 32 * (8 * ((C + per - 1) / per) + (4 * C + per - 1) / per) : 0;
-  const unsigned grid = (unsigned)(n_ln + n_pack + (fp8 ? 1 : 0));
+  const unsigned grid = (unsigned)(n_ln + n_pack + 1);
+  const ClearWords cw = {{kv.clear[0], kv.clear[1]}, {kv.n_clear[0], kv.n_clear[1]}};
   const size_t lds = packed ? (size_t)32 * (C / 8 + 1) * 16 : 0;
   static std::atomic<uint64_t> lds_done[8];
   const BlockWeights4 w4 = bw ? *bw : BlockWeights4{};
@@ -468,7 +477,7 @@ static int launch_block_head(const uint16_t *z, const float *gamma, const float 
 #define LV_HEAD(CPL, F8)                                                                                       \
   if ((rc = allow_dynamic_lds((const void *)k_block_head<CPL, F8>, (size_t)32 * (C / 8 + 1) * 16, lds_done[(CPL - 1) * 2 + F8]))) \
     return rc;                                                                                                 \
-  hipLaunchKernelGGL((k_block_head<CPL, F8>), dim3(grid), dim3(64 * kLnWaves), lds, st, z, gamma, beta, M, C, n_ln, packed, w4, n_pack, hd)
+  hipLaunchKernelGGL((k_block_head<CPL, F8>), dim3(grid), dim3(64 * kLnWaves), lds, st, z, gamma, beta, M, C, n_ln, packed, w4, n_pack, hd, cw)
 #define LV_HEADS(F8)                   \
   switch (cpl) {                       \
     case 1: LV_HEAD(1, F8); break;     \
@@ -506,6 +515,10 @@ static int launch_block_head(const uint16_t *z, const float *gamma, const float 
 // PACKED: the output, through GELU, is the activation operand of a following layer with K = Nout and is
 // written in that layer's operand order straight from the accumulators (bf16 fragments, or,
 // with FP8, E4M3 codes quantised with *out_inv while the largest |value| goes to *out_amax).
+// kQkvAmax, kQkvPacked (the fused q|k|v projection, whole heads of 64 channels): the epilogue holds the bf16 values that
+// the attention's passes over q, k and v would read again, so it does their work: the amaxes that E4M3 attention scales
+// by (a pass of 17.6 us at 15,432 x 1024 and a launch of 4.7 for its sums), or K and V in fragment order (9 us at 5,776 x 1024).  Same
+// bits: values are rounded first, sums taken in the same order.  (k_attn_pack stays for q, k, v that come without the layer.)
 // FP8: the same ring and the same byte traffic per stage, but a stage (two 1 KB units per
 // fragment) is one k-step of 64 for v_mfma_f32_32x32x64_f8f6f4, whose operands are the two
 // units of a fragment side by side in 8 registers: per stage a wave issues 8 MFMAs of twice
@@ -574,13 +587,24 @@ __device__ __forceinline__ float max3_abs(float m, float a, float b) {
   return r;
 }
 
-template <bool FP8, bool PACKED, int BM, int BN, int KG = 1>
+// What becomes of the output (see above): rows; the next layer's operand; q|k|v as rows with their amaxes taken; q as
+// rows, K and V in the order the attention reads.
+enum GemmOut { kRows, kOperand, kQkvAmax, kQkvPacked };
+struct QkvOut {
+  u32x4 *kp = nullptr, *vp = nullptr;
+  uint32_t *amax = nullptr;
+  int n_kt = 0, qk_norm = 0;
+};
+
+template <bool FP8, GemmOut OUT, int BM, int BN, int KG = 1>
 __global__ __launch_bounds__((GemmShape<BM, BN>::kThreads * KG)) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_gemm_bt(
     const u32x4 *__restrict__ ap, const u32x4 *__restrict__ wp, int64_t M, int KS, int nt_n,
     const float *__restrict__ bias, int gelu, uint16_t *__restrict__ out, int split,
     const float *__restrict__ alpha_p, int n_tiles, int rows_by_xcd, const uint16_t *__restrict__ addend,
-    const uint32_t *__restrict__ out_inv, uint32_t *__restrict__ out_amax, Fp8Record rec) {
+    const uint32_t *__restrict__ out_inv, uint32_t *__restrict__ out_amax, Fp8Record rec, QkvOut qkv) {
   using S = GemmShape<BM, BN>;
+  constexpr bool PACKED = OUT == kOperand, QKV = OUT == kQkvAmax || OUT == kQkvPacked;
+  static_assert(OUT != kQkvPacked || BM == BN, "V's tiles swap rows and columns");
   constexpr int kStages = S::kStages, kStageU4 = S::kStageU4, kB = S::kB;
   constexpr bool kTwoSets = !FP8 || kB <= 2;   // registers for two sets of weight fragments
   extern __shared__ u32x4 rings[];             // one ring per K group
@@ -615,6 +639,9 @@ __global__ __launch_bounds__((GemmShape<BM, BN>::kThreads * KG)) __attribute__((
   };
   __shared__ uint32_t wg_amax;   // FP8 && PACKED: the largest |value| this workgroup has written
   if (FP8 && PACKED && tid == 0) wg_amax = 0u;   // (many barriers before its first use)
+  __shared__ uint32_t qkv_amax[OUT == kQkvAmax ? 3 : 1];   // kQkvAmax: of q, k and v
+  if (OUT == kQkvAmax && tid < 3) qkv_amax[tid] = 0u;
+  __shared__ float half_head[QKV && kB == 1 ? 2 * 2 * 32 : 1];   // two waves share a head: their sums of squares
   bool primed = false;   // the previous tile's epilogue has issued this tile's first stages
   int parity = 0;
   int tm = 0, tn = 0, tm2 = 0, tn2 = 0;
@@ -632,6 +659,10 @@ __global__ __launch_bounds__((GemmShape<BM, BN>::kThreads * KG)) __attribute__((
   const int f_ks = S::kWaves == 2 ? wave : (wave >> 1) & 1, f_half = S::kWaves == 2 ? 0 : wave & 1;
   int pf_g = 0, f_tm = tm, f_tn = tn;
   auto slot_of = [](int g) { return kStages == 4 ? g & 3 : g % kStages; };
+  // kQkvPacked: the tiles of V take activations and weights the other way round, so that a lane has one channel of four
+  // consecutive tokens per register group
+  const int third = split / BN;
+  auto swapped = [&](int t) { return OUT == kQkvPacked && t >= 2 * third; };
   const u32x4 *f_src[2];   // this wave's next weight and activation fragments (8 waves: [0] is either)
   u32x4 *f_dst[2];
   auto fetch_begin = [&]() {
@@ -640,11 +671,13 @@ __global__ __launch_bounds__((GemmShape<BM, BN>::kThreads * KG)) __attribute__((
     u32x4 *stage = ring + (size_t)slot_of(pf_g) * kStageU4;
     if constexpr (S::kWaves == 8) {
       const int a0 = (wave & 1) * 4;
-      f_src[0] = (wave >> 2 ? ap + (size_t)(f_tm * 8 + a0) * KS * 64 : wp + (size_t)(f_tn * 8 + a0) * KS * 64) + at;
+      const bool second = swapped(f_tn) != (wave >> 2 != 0);   // the activations' fragments
+      f_src[0] = (second ? ap + (size_t)(f_tm * 8 + a0) * KS * 64 : wp + (size_t)(f_tn * 8 + a0) * KS * 64) + at;
       f_dst[0] = stage + (size_t)(wave * 4) * 64;
     } else {
-      f_src[0] = wp + (size_t)(f_tn * S::kFragW + f_half * kB) * KS * 64 + at;
-      f_src[1] = ap + (size_t)(f_tm * S::kFragA + f_half * 2) * KS * 64 + at;
+      const bool sw = swapped(f_tn);
+      f_src[0] = (sw ? ap : wp) + (size_t)((sw ? f_tm : f_tn) * S::kFragW + f_half * kB) * KS * 64 + at;
+      f_src[1] = (sw ? wp : ap) + (size_t)((sw ? f_tn : f_tm) * S::kFragA + f_half * 2) * KS * 64 + at;
       f_dst[0] = stage + (size_t)(wave * S::kLoadsW) * 64;
       f_dst[1] = stage + (size_t)(2 * S::kFragW + wave * 2) * 64;
     }
@@ -937,6 +970,109 @@ __global__ __launch_bounds__((GemmShape<BM, BN>::kThreads * KG)) __attribute__((
   // row-major rows of `split` channels: per store instruction a wave writes 32 bytes of each of
   // 32 rows; the four stores that complete a 128-byte line follow each other
   const int blk = (tn * BN) / split, col0 = (tn * BN) % split;   // a tile never straddles two blocks
+  if constexpr (QKV) {
+    const int n_tok = tm * BM, ch_tile = col0 + anchor;
+    if (OUT == kQkvPacked && blk == 2) {
+      // V, rows and columns swapped: lane h * 32 + dr holds channel 32 dt + dr and, per 16 keys u, the 8 keys 16u + 8 (e / 4) +
+      // 4h + e % 4 of a tile: a fragment of the attention's V operand as it stands
+#pragma unroll
+      for (int a = 0; a < 2; ++a) {
+        if (!mine(a)) continue;
+        const int ch = wd * 64 + 32 * a;
+        const float bv = bias_lds[ch + (lane & 31)];
+        const size_t head = (size_t)(ch_tile + ch) >> 6;
+#pragma unroll
+        for (int b = 0; b < kB; ++b) {
+          const int kt = (n_tok + wn * 32 * kB + 32 * b) >> 5;
+          if (kt >= qkv.n_kt) continue;
+#pragma unroll
+          for (int u = 0; u < 2; ++u) {
+            uint32_t w[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+              w[i] = FP8 ? pack_bf16(acc[a][b][8 * u + 2 * i] * alpha + bv, acc[a][b][8 * u + 2 * i + 1] * alpha + bv)
+                         : pack_bf16(acc[a][b][8 * u + 2 * i] + bv, acc[a][b][8 * u + 2 * i + 1] + bv);
+            qkv.vp[((head * qkv.n_kt + kt) * 4 + u * 2 + (ch >> 5 & 1)) * 64 + lane] = u32x4{w[0], w[1], w[2], w[3]};
+          }
+        }
+      }
+      continue;
+    }
+    // q and k (and v as rows): a lane has 8 channels of its token per chunk of 16, lane l + 32 the other 8; kB column blocks
+    // are whole heads, or (kB = 1) half of one
+    constexpr int kHeads = kB == 1 ? 1 : kB / 2, kChunks = kB == 1 ? 2 : 4;   // of a wave, and of a (part of a) head
+    float top = 0.f;
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+      for (int j = 0; j < kHeads; ++j) {
+        u32x4 t[kChunks];
+        float ss = 0.f;
+        const int64_t m = (int64_t)n_tok + wd * 64 + 32 * a + (lane & 31);
+        if (mine(a)) {
+#pragma unroll
+          for (int s = 0; s < kChunks; ++s) {
+            const int b = j * 2 + (s >> 1), gp = s & 1;
+            const int ch0 = wn * 32 * kB + 32 * b + 16 * gp + 4 * h;
+            const f32x4 bv0 = *(const f32x4 *)(bias_lds + ch0), bv1 = *(const f32x4 *)(bias_lds + ch0 + 8);
+            float v0[4], v1[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+              v0[i] = FP8 ? acc[a][b][8 * gp + i] * alpha + bv0[i] : acc[a][b][8 * gp + i] + bv0[i];
+              v1[i] = FP8 ? acc[a][b][8 * gp + 4 + i] * alpha + bv1[i] : acc[a][b][8 * gp + 4 + i] + bv1[i];
+            }
+            const auto s0 = __builtin_amdgcn_permlane32_swap(pack_bf16(v0[0], v0[1]), pack_bf16(v1[0], v1[1]), false, false);
+            const auto s1 = __builtin_amdgcn_permlane32_swap(pack_bf16(v0[2], v0[3]), pack_bf16(v1[2], v1[3]), false, false);
+            t[s] = u32x4{s0[0], s1[0], s0[1], s1[1]};
+          }
+          // the sum of a head row's squares, as k_attn_pack takes it: chunks of 8, added in pairs
+          float pair_sum[kChunks];
+#pragma unroll
+          for (int s = 0; s < kChunks; ++s) {
+            const float cs = sumsq8(t[s]);
+            const auto x = __builtin_amdgcn_permlane32_swap(__float_as_uint(cs), __float_as_uint(cs), false, false);
+            pair_sum[s] = __uint_as_float(x[0]) + __uint_as_float(x[1]);
+          }
+          ss = pair_sum[0] + pair_sum[1];
+          if constexpr (kB > 1) ss += pair_sum[2] + pair_sum[3];
+        }
+        if constexpr (kB == 1) {             // (KG = 2: row block a is K group a's; the two waves of a group share its rows)
+          if (j == 0 && mine(a)) half_head[(kg * 2 + wn) * 32 + (lane & 31)] = ss;
+          __syncthreads();
+          if (mine(a)) ss = half_head[kg * 64 + (lane & 31)] + half_head[kg * 64 + 32 + (lane & 31)];
+        }
+        if (!mine(a)) continue;
+        const float r = qkv.qk_norm && blk < 2 ? 1.0f / sqrtf(ss * (1.0f / 64.0f) + kQkEps) : 1.0f;
+        if (OUT == kQkvPacked && blk == 1) {
+          const int64_t kt = m >> 5;         // (the same for all lanes)
+          const size_t head = (size_t)(ch_tile + wn * 32 * kB + 64 * j) >> 6;
+          if (kt < qkv.n_kt) {
+#pragma unroll
+            for (int s = 0; s < kChunks; ++s) {
+              const int step = s + (kB == 1 ? 2 * wn : 0);
+              const u32x4 w = qkv.qk_norm ? scale8(t[s], r) : t[s];
+              qkv.kp[((head * qkv.n_kt + kt) * 4 + step) * 64 + lane] = m < M ? w : u32x4{0u, 0u, 0u, 0u};
+            }
+          }
+          continue;
+        }
+        if (OUT == kQkvAmax && m < M) {      // rounding keeps the order, so the largest is rounded alone
+          float big = 0.f;
+#pragma unroll
+          for (int s = 0; s < kChunks; ++s) big = fmaxf(big, absmax8(t[s]));
+          top = fmaxf(top, bf16_lo(pack_bf16(big * r, 0.f)));
+        }
+        if (m < M)
+#pragma unroll
+          for (int s = 0; s < kChunks; ++s)
+            *(u32x4 *)(out + (size_t)blk * M * split + ch_tile + wn * 32 * kB + 64 * j + 16 * s + 8 * h + (size_t)m * split) = t[s];
+      }
+    if constexpr (OUT == kQkvAmax) {
+      top = wave_max(top);
+      if (lane == 0) atomicMax(&qkv_amax[blk], __float_as_uint(top));
+    }
+    continue;
+  }
   uint16_t *ob = out + (size_t)blk * M * split + col0 + wn * 32 * kB + 8 * h + anchor;
 #pragma unroll
   for (int b = 0; b < kB; ++b)
@@ -980,7 +1116,11 @@ __global__ __launch_bounds__((GemmShape<BM, BN>::kThreads * KG)) __attribute__((
     __syncthreads();
     if (tid == 0) raise_max(out_amax, __uint_as_float(wg_amax));
   }
-  if constexpr (FP8 && !PACKED)
+  if constexpr (OUT == kQkvAmax) {
+    __syncthreads();
+    if (tid < 3 && qkv_amax[tid] != 0u) raise_max(qkv.amax + tid, __uint_as_float(qkv_amax[tid]));
+  }
+  if constexpr (FP8 && OUT == kRows)
     if (rec.state && blockIdx.x == gridDim.x - 1 && tid < 64) record_amaxes(rec, lane);
 }
 
@@ -1042,6 +1182,8 @@ struct LinearOpts {
   const uint32_t *out_inv = nullptr;   // FP8 pack_out: the next layer's input scale ...
   uint32_t *out_amax = nullptr;        // ... and where the largest |output| is reduced into
   Fp8Record rec;                       // FP8, not pack_out: what to record once it has run
+  const AttnKV *kv = nullptr;          // the q|k|v layer: do this for the attention, if the tiles' shape allows it ...
+  bool *kv_done = nullptr;             // ... and tell whether it was
 };
 
 // Which output tile suits M rows and Nout columns: 256 x 256 (one workgroup per CU), 128 x 256 or
@@ -1096,6 +1238,7 @@ static int launch_linear(const uint16_t *A, int64_t M, int K, int Nout,
                          hipStream_t st, const LinearOpts &o) {
   if (!o.w_packed || (o.fp8 && !o.sc) || (o.current && (o.a_packed || o.pack_out))) return LV_ERR_PARAM;
   if (o.pack_out && (!gelu || o.addend || split != Nout || (o.fp8 && (!o.out_inv || !o.out_amax)))) return LV_ERR_PARAM;
+  if (o.kv && (o.pack_out || o.addend || gelu || Nout != 3 * split)) return LV_ERR_PARAM;
   if (K % 256 != 0 || Nout % kTile != 0 || split % kTile != 0 || Nout % split != 0) return LV_ERR_SHAPE;
   int rc;
   if (w.Mp / 128 * (Nout / 128) >= ((int64_t)1 << 30) || w.Mp >= ((int64_t)1 << 31)) return LV_ERR_SHAPE;
@@ -1104,8 +1247,11 @@ static int launch_linear(const uint16_t *A, int64_t M, int K, int Nout,
       hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n_cu < 1)
     return LV_ERR_HIP;
   const TileShape shape = tile_shape(M, Nout, K, o.fp8, n_cu);
-  auto gemm = [&](auto fp8, auto packed, auto bm, auto bn, auto kg, const u32x4 *act, int KS, const float *alpha) -> int {
-    constexpr bool F8 = decltype(fp8)::value, PK = decltype(packed)::value;
+  QkvOut qkv;
+  if (o.kv) qkv = QkvOut{(u32x4 *)o.kv->kp, (u32x4 *)o.kv->vp, o.kv->amax, o.kv->n_kt, o.kv->qk_norm};
+  auto gemm = [&](auto fp8, auto kind, auto bm, auto bn, auto kg, const u32x4 *act, int KS, const float *alpha) -> int {
+    constexpr bool F8 = decltype(fp8)::value;
+    constexpr GemmOut PK = decltype(kind)::value;
     constexpr int BM = decltype(bm)::value, BN = decltype(bn)::value, KG = decltype(kg)::value;
     using S = GemmShape<BM, BN>;
     constexpr size_t kLds = S::kLds + (KG - 1) * (size_t)S::kStages * S::kStageU4 * 16;
@@ -1120,7 +1266,7 @@ static int launch_linear(const uint16_t *A, int64_t M, int K, int Nout,
     const unsigned grid = (unsigned)(n_tiles > slots ? slots : by_xcd ? fullest * kXcd : n_tiles);
     hipLaunchKernelGGL((k_gemm_bt<F8, PK, BM, BN, KG>), dim3(grid), dim3(S::kThreads * KG), kLds, st, act,
                        o.w_packed, M, KS, nt_n, bias, gelu, out, split, alpha, n_tiles, by_xcd ? 1 : 0, o.addend, o.out_inv,
-                       o.out_amax, o.rec);
+                       o.out_amax, o.rec, qkv);
     return LV_OK;
   };
   auto launch = [&](auto fp8, const u32x4 *act, int KS, const float *alpha) -> int {
@@ -1129,14 +1275,20 @@ static int launch_linear(const uint16_t *A, int64_t M, int K, int Nout,
     using N64 = std::integral_constant<int, 64>;
     using One = std::integral_constant<int, 1>;
     using Two = std::integral_constant<int, 2>;
-    auto tiles = [&](auto packed) -> int {
-      if (shape == kTile64x64K2) return gemm(fp8, packed, N64{}, N64{}, Two{}, act, KS, alpha);
-      if (shape == kTile128x128K2) return gemm(fp8, packed, N128{}, N128{}, Two{}, act, KS, alpha);
-      if (shape == kTile128x128) return gemm(fp8, packed, N128{}, N128{}, One{}, act, KS, alpha);
-      if (shape == kTile128x256) return gemm(fp8, packed, N128{}, N256{}, One{}, act, KS, alpha);
-      return gemm(fp8, packed, N256{}, N256{}, One{}, act, KS, alpha);
+    auto tiles = [&](auto kind) -> int {
+      if (shape == kTile64x64K2) return gemm(fp8, kind, N64{}, N64{}, Two{}, act, KS, alpha);
+      if (shape == kTile128x128K2) return gemm(fp8, kind, N128{}, N128{}, Two{}, act, KS, alpha);
+      if (shape == kTile128x128) return gemm(fp8, kind, N128{}, N128{}, One{}, act, KS, alpha);
+      if constexpr (decltype(kind)::value != kQkvPacked)
+        if (shape == kTile128x256) return gemm(fp8, kind, N128{}, N256{}, One{}, act, KS, alpha);
+      return gemm(fp8, kind, N256{}, N256{}, One{}, act, KS, alpha);
     };
-    return o.pack_out ? tiles(std::true_type{}) : tiles(std::false_type{});
+    const bool kv = o.kv && (o.kv->amax || shape != kTile128x256);
+    if (o.kv_done) *o.kv_done = kv;
+    if (kv && o.kv->amax) return tiles(std::integral_constant<GemmOut, kQkvAmax>{});
+    if (kv) return tiles(std::integral_constant<GemmOut, kQkvPacked>{});
+    if (o.pack_out) return tiles(std::integral_constant<GemmOut, kOperand>{});
+    return tiles(std::integral_constant<GemmOut, kRows>{});
   };
   const u32x4 *a_packed = o.a_packed;
   if (o.fp8) {
@@ -1190,6 +1342,9 @@ int launch_global_block(const uint16_t *z, int64_t M, int C, int heads, float sc
 
   // the weights' amaxes, then every layer's scalars, the weights into operand order and (bf16 layers and delayed
   // scaling, where its scale is known) the first LayerNorm into the first layer's operand
+  AttnKV kv;                 // what the first layer does for the attention (kv_ready: has done)
+  bool kv_ready = false;
+  if ((rc = attn_kv_target(kv, M, heads, scale, attn_dtype, qk_norm, q, w.a, w.attn, w.attn_bytes))) return rc;
   Fp8Head hd{};
   if (f8) {
     if (pack_w) hipLaunchKernelGGL(k_weights_amax, dim3(kWAmaxParts), dim3(256), 0, st, bw4, C, w.wpart);
@@ -1197,7 +1352,7 @@ int launch_global_block(const uint16_t *z, int64_t M, int C, int heads, float sc
                  (uint32_t *)w.h};
   }
   u32x4 *const ln_packed = f8 && !delayed ? nullptr : w.apack;
-  if ((rc = launch_block_head(z, bw.ln1_g, bw.ln1_b, M, w.Mp, C, ln_packed, pack_w ? &bw4 : nullptr, f8, hd, st))) return rc;
+  if ((rc = launch_block_head(z, bw.ln1_g, bw.ln1_b, M, w.Mp, C, ln_packed, pack_w ? &bw4 : nullptr, f8, hd, kv, st))) return rc;
 
   if (delayed) {
     // FP8 layers, delayed scaling: every input scale is known before its tensor exists, so the
@@ -1213,8 +1368,12 @@ int launch_global_block(const uint16_t *z, int64_t M, int C, int heads, float sc
     };
     LinearOpts o = layer(0);
     o.a_packed = w.apack;
+    o.kv = &kv;
+    o.kv_done = &kv_ready;
     if ((rc = launch_linear(nullptr, M, C, 3 * C, bias[0], 0, w.qkv, C, w, st, o))) return rc;
-    if ((rc = launch_attn(q, k, v, w.a, M, heads, scale, attn_dtype, qk_norm, w.attn, w.attn_bytes, st, after_pack))) return rc;
+    if ((rc = launch_attn(q, k, v, w.a, M, heads, scale, attn_dtype, qk_norm, w.attn, w.attn_bytes, st, after_pack, 1, nullptr,
+                          nullptr, nullptr, kv_ready ? &kv : nullptr)))
+      return rc;
     if (after_attn && hipEventRecord(after_attn, st) != hipSuccess) return LV_ERR_HIP;
     o = layer(1);
     if ((rc = launch_linear(w.a, M, C, C, bias[1], 0, w.u1, C, w, st, o))) return rc;
@@ -1248,11 +1407,13 @@ int launch_global_block(const uint16_t *z, int64_t M, int C, int heads, float sc
   if (f8 && (rc = launch_layernorm(z, nullptr, bw.ln1_g, bw.ln1_b, M, C, w.h, st))) return rc;
   LinearOpts o = layer(0);
   o.a_packed = ln_packed;
+  o.kv = &kv;
+  o.kv_done = &kv_ready;
   if ((rc = launch_linear(w.h, M, C, 3 * C, bias[0], 0, w.qkv, C, w, st, o))) return rc;
   // bf16 layers: where the attention kernel can, it writes the output projection's operand itself
   bool a_is_packed = false;
   if ((rc = launch_attn(q, k, v, w.a, M, heads, scale, attn_dtype, qk_norm, w.attn, w.attn_bytes, st, after_pack, 1, nullptr,
-                        f8 ? nullptr : (void *)w.apack, &a_is_packed)))
+                        f8 ? nullptr : (void *)w.apack, &a_is_packed, kv_ready ? &kv : nullptr)))
     return rc;
   if (after_attn && hipEventRecord(after_attn, st) != hipSuccess) return LV_ERR_HIP;
   o = layer(1);

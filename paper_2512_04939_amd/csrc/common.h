@@ -95,6 +95,19 @@ __device__ __forceinline__ float ga_score(float g, float v, float glo, float gr,
   return alpha * ng + beta * nv;
 }
 
+// Eight channels of a 64-channel head row: their sum of squares, and scaled and rounded to bf16 again.  A row's
+// sum is taken in pairs of such chunks, wherever it is taken: the same bits.
+constexpr float kQkEps = 1e-6f;      // of the RMS normalisation of q and k
+__device__ __forceinline__ float sumsq8(const u32x4 w) {
+  const float a0 = bf16_lo(w.x), a1 = bf16_hi(w.x), a2 = bf16_lo(w.y), a3 = bf16_hi(w.y);
+  const float a4 = bf16_lo(w.z), a5 = bf16_hi(w.z), a6 = bf16_lo(w.w), a7 = bf16_hi(w.w);
+  return ((a0 * a0 + a1 * a1) + (a2 * a2 + a3 * a3)) + ((a4 * a4 + a5 * a5) + (a6 * a6 + a7 * a7));
+}
+__device__ __forceinline__ u32x4 scale8(const u32x4 w, float r) {
+  return u32x4{pack_bf16(bf16_lo(w.x) * r, bf16_hi(w.x) * r), pack_bf16(bf16_lo(w.y) * r, bf16_hi(w.y) * r),
+               pack_bf16(bf16_lo(w.z) * r, bf16_hi(w.z) * r), pack_bf16(bf16_lo(w.w) * r, bf16_hi(w.w) * r)};
+}
+
 // LDS address (byte offset in the workgroup's LDS) of a __shared__ object
 __device__ __forceinline__ uint32_t lds_addr(const void *p) {
   return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const void *)p;

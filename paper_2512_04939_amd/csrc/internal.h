@@ -89,14 +89,28 @@ int launch_unmerge_merge(const uint16_t *y, const Dims &d, int64_t M, const lite
 
 // attn.hip
 size_t attn_ws_bytes(int heads, int64_t n_tokens, int attn_dtype, int n_seq = 1, bool least = false);
+// What a layer that produces q, k and v can do for the attention over them (one sequence): bf16: write K, normalised
+// when qk_norm, and V straight into the order the attention reads (kp, vp; n_kt tiles of 32 keys per head); E4M3:
+// raise the amaxes of (normalised) q, k and v (words 0 to 2).  It needs the two ranges of words cleared before.
+struct AttnKV {
+  void *kp = nullptr, *vp = nullptr;
+  int n_kt = 0, qk_norm = 0;
+  uint32_t *amax = nullptr;
+  uint32_t *clear[2] = {nullptr, nullptr};
+  int n_clear[2] = {0, 0};
+};
+int attn_kv_target(AttnKV &kv, int64_t n_tokens, int heads, float scale, int attn_dtype, int qk_norm, const void *q, const void *o,
+                   void *ws, size_t ws_bytes);
 // `after_pack`, when not NULL, is recorded between the K/V re-layout and the main kernel;
 // n_seq sequences of n_tokens each; res: optional residual added to the output.  o_packed
 // (optional, with wrote_packed): a linear layer's activation operand buffer for align_up(n_tokens,
 // 256) rows; when the bf16 fixed-reference kernel runs it writes the output there in that
-// layer's fragment order instead of to o, and *wrote_packed tells whether it did.
+// layer's fragment order instead of to o, and *wrote_packed tells whether it did.  ready: an attn_kv_target() of
+// the same arguments whose work has been done.
 int launch_attn(const uint16_t *q, const uint16_t *k, const uint16_t *v, uint16_t *o,
                 int64_t n_tokens, int heads, float scale, int attn_dtype, int qk_norm, void *ws,
                 size_t ws_bytes, hipStream_t st, hipEvent_t after_pack = nullptr, int n_seq = 1,
-                const uint16_t *res = nullptr, void *o_packed = nullptr, bool *wrote_packed = nullptr);
+                const uint16_t *res = nullptr, void *o_packed = nullptr, bool *wrote_packed = nullptr,
+                const AttnKV *ready = nullptr);
 
 }  // namespace lv
