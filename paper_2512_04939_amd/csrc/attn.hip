@@ -1748,17 +1748,80 @@ __device__ __forceinline__ i32x8 cat_fp8(u32x2 a, u32x2 b, u32x2 c, u32x2 d) {
   return i32x8{(int)a.x, (int)a.y, (int)b.x, (int)b.y, (int)c.x, (int)c.y, (int)d.x, (int)d.y};
 }
 
+// Where the output of the E4M3 kernels goes: rows, or a linear layer's activation operand (rows beyond the sequence end
+// up to whole blocks of 256 zero): in bf16, or as E4M3 codes of the values rounded to bf16 (scale *inv), whose largest
+// magnitude is raised in *amax.  The layer's own pass over the rows took 10.6 us at 15,432 tokens of 16 heads.
+enum AttnOut { kOutRows, kOutBf16, kOutE4M3 };
+struct AttnOutArgs {
+  const uint32_t *inv;
+  uint32_t *amax;
+};
+// 32 queries from row0 on (query lane % 32) x the head's 64 channels, as a lane's accumulators hold them, times the lane's inv;
+// returns the largest |value| of a live row
+template <AttnOut OUT>
+__device__ __forceinline__ float store_head(const f32x16 (&acc)[2], float inv, int64_t row0, int64_t n, int C, int head,
+                                            uint16_t *o, float code_inv, int lane) {
+  const int h = lane >> 5;
+  const int64_t row = row0 + (lane & 31);
+  const bool live = row < n;
+  float m = 0.f;
+  if constexpr (OUT == kOutRows) {
+    if (live) {
+      uint16_t *op = o + (size_t)row * C + head * 64 + 4 * h;
+#pragma unroll
+      for (int dt = 0; dt < 2; ++dt)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          const u32x2 w = {pack_bf16(acc[dt][4 * g] * inv, acc[dt][4 * g + 1] * inv),
+                           pack_bf16(acc[dt][4 * g + 2] * inv, acc[dt][4 * g + 3] * inv)};
+          *(u32x2 *)(op + 32 * dt + 8 * g) = w;
+        }
+    }
+  } else {
+    if (row0 >= (n + kBQB - 1) / kBQB * kBQB) return 0.f;   // beyond the operand (uniform)
+#pragma unroll
+    for (int dt = 0; dt < 2; ++dt) {
+      uint32_t p[4][2];                // channels 8g + 4h .. + 3 of 32 dt
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        p[g][0] = live ? pack_bf16(acc[dt][4 * g] * inv, acc[dt][4 * g + 1] * inv) : 0u;
+        p[g][1] = live ? pack_bf16(acc[dt][4 * g + 2] * inv, acc[dt][4 * g + 3] * inv) : 0u;
+      }
+      if constexpr (OUT == kOutBf16) {
+#pragma unroll
+        for (int gp = 0; gp < 2; ++gp) {
+          const auto s0 = __builtin_amdgcn_permlane32_swap(p[2 * gp][0], p[2 * gp + 1][0], false, false);
+          const auto s1 = __builtin_amdgcn_permlane32_swap(p[2 * gp][1], p[2 * gp + 1][1], false, false);
+          ((u32x4 *)o)[((size_t)(row0 >> 5) * (C >> 4) + head * 4 + dt * 2 + gp) * 64 + lane] = u32x4{s0[0], s1[0], s0[1], s1[1]};
+        }
+      } else {
+        uint32_t d[4];
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          const float a = bf16_lo(p[g][0]), b = bf16_hi(p[g][0]), c = bf16_lo(p[g][1]), e = bf16_hi(p[g][1]);
+          m = fmaxf(m, fmaxf(fmaxf(fabsf(a), fabsf(b)), fmaxf(fabsf(c), fabsf(e))));
+          d[g] = cvt4_fp8(clamp448(a * code_inv), clamp448(b * code_inv), clamp448(c * code_inv), clamp448(e * code_inv));
+        }
+        const auto s0 = __builtin_amdgcn_permlane32_swap(d[0], d[2], false, false);
+        const auto s1 = __builtin_amdgcn_permlane32_swap(d[1], d[3], false, false);
+        ((u32x4 *)o)[((size_t)(row0 >> 5) * (C >> 5) + head * 2 + dt) * 64 + lane] = u32x4{s0[0], s0[1], s1[0], s1[1]};
+      }
+    }
+  }
+  return m;
+}
+
 // Same structure as k_attn_bf16 (two phase groups, lazily raised reference) on fp8 operands.
 // Each contraction is one v_mfma_f32_32x32x64_f8f6f4 (contraction length 64: all channels of a
 // head for the scores, all keys of a stage for the output), which runs at twice the rate of the
 // 32x32x16 fp8 form; the order of the 64 contraction indices inside an operand is the same for
 // both operands (piece p of the packed fragments = indices 16p .. 16p+15 in fragment order).
 // SECOND: the pass behind the bounded kernel, over that kernel's packed K and V (k_attn_pack_fp8b).
-template <bool SECOND>
+template <bool SECOND, AttnOut OUT>
 __global__ __launch_bounds__(512) void k_attn_fp8(
     const uint16_t *__restrict__ q, const u32x2 *__restrict__ kp, const u32x2 *__restrict__ vp,
     uint16_t *__restrict__ o, int64_t n, int heads, int n_kt, int nqb, float c_in, int qk_norm,
-    const uint32_t *__restrict__ amax, const uint32_t *__restrict__ redo) {
+    const uint32_t *__restrict__ amax, const uint32_t *__restrict__ redo, AttnOutArgs oa) {
   __shared__ u32x2 ks[kKSlots][8 * kFragU4];
   __shared__ u32x2 vs[kVSlots][8 * kFragU4];
   const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5, ql = lane & 31;
@@ -1978,25 +2041,18 @@ __global__ __launch_bounds__(512) void k_attn_fp8(
     __syncthreads();
   }
 
+  const float code_inv = OUT == kOutE4M3 ? __uint_as_float(*oa.inv) : 1.0f;
+  float m = 0.f;
 #pragma unroll
   for (int sub = 0; sub < 2; ++sub) {
     const float l = lrow[sub] + __shfl_xor(lrow[sub], 32, 64);
-    const float inv = out_scale / l;
-    const int64_t row = q0 + sub * 32 + ql;
-    if (row < n) {
-      uint16_t *op = o + (size_t)row * C + head * 64 + 4 * h;
-#pragma unroll
-      for (int dt = 0; dt < 2; ++dt)
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          u32x2 w = {pack_bf16(oacc[sub][dt][4 * g] * inv, oacc[sub][dt][4 * g + 1] * inv),
-                     pack_bf16(oacc[sub][dt][4 * g + 2] * inv, oacc[sub][dt][4 * g + 3] * inv)};
-          *(u32x2 *)(op + 32 * dt + 8 * g) = w;
-        }
-    }
+    m = fmaxf(m, store_head<OUT>(oacc[sub], out_scale / l, q0 + sub * 32, n, C, head, o, code_inv, lane));
+  }
+  if constexpr (OUT == kOutE4M3) {
+    m = wave_max(m);
+    if (lane == 0) raise_max(oa.amax, m);
   }
 }
-
 
 // ---------------------------------------------------------------------------------------
 // Bounded-score FP8 kernel (qk_norm).  With unit-RMS heads a score cannot exceed
@@ -2067,10 +2123,11 @@ __global__ __launch_bounds__(256) void k_attn_pack_fp8b(const uint16_t *__restri
   vp[2 * (base + (size_t)(dt * 2 + kt2) * 64 + lane) + u] = u32x2{w[0], w[1]};
 }
 
+template <AttnOut OUT>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_attn_fp8_bounded(
     const uint16_t *__restrict__ q, const u32x4 *__restrict__ kp, const u32x4 *__restrict__ vp,
     uint16_t *__restrict__ o, int64_t n, int heads, int nkv, int nqb, float c_in,
-    const uint32_t *__restrict__ amax, uint32_t *__restrict__ redo, int redo_stride) {
+    const uint32_t *__restrict__ amax, uint32_t *__restrict__ redo, int redo_stride, AttnOutArgs oa) {
   __shared__ u32x4 ks[kF8Stages][4 * 64];
   __shared__ u32x4 vs[kF8Stages][4 * 64];
   const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5, ql = lane & 31;
@@ -2304,26 +2361,21 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");        // nothing may land after the workgroup ends
 #undef LV_PIN
 
+  const float code_inv = OUT == kOutE4M3 ? __uint_as_float(*oa.inv) : 1.0f;
   bool low = false;
+  float m = 0.f;
 #pragma unroll
   for (int sub = 0; sub < 2; ++sub) {
     const float l = (lane & 16) ? lacc[sub][1] : lacc[sub][0];
-    const float inv = out_scale / l;
-    const int64_t row = q0 + sub * 32 + ql;
-    if (row < n) {
-      low |= !(l >= 1.0f);
-      uint16_t *op = o + (size_t)row * C + head * 64 + 4 * h;
-#pragma unroll
-      for (int dt = 0; dt < 2; ++dt)
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          const u32x2 w = {pack_bf16(oacc[sub][dt][4 * g] * inv, oacc[sub][dt][4 * g + 1] * inv),
-                           pack_bf16(oacc[sub][dt][4 * g + 2] * inv, oacc[sub][dt][4 * g + 3] * inv)};
-          *(u32x2 *)(op + 32 * dt + 8 * g) = w;
-        }
-    }
+    low |= q0 + sub * 32 + ql < n && !(l >= 1.0f);
+    m = fmaxf(m, store_head<OUT>(oacc[sub], out_scale / l, q0 + sub * 32, n, C, head, o, code_inv, lane));
   }
-  if (__builtin_amdgcn_ballot_w64(low) != 0 && lane == 0) atomicOr(&redo[(size_t)head * redo_stride + qb], 1u);
+  const bool flag = __builtin_amdgcn_ballot_w64(low) != 0;
+  if (flag && lane == 0) atomicOr(&redo[(size_t)head * redo_stride + qb], 1u);
+  if constexpr (OUT == kOutE4M3) {     // (a flagged wave's rows are not what the block ends up with)
+    m = wave_max(m);
+    if (!flag && lane == 0) raise_max(oa.amax, m);
+  }
 }
 
 static int n_key_tiles(int64_t n) { return (int)(2 * ((n + kKV - 1) / kKV)); }
@@ -2469,8 +2521,8 @@ int attn_kv_target(AttnKV &kv, int64_t n, int heads, float scale, int attn_dtype
 int launch_attn(const uint16_t *q, const uint16_t *k, const uint16_t *v, uint16_t *o,
                 int64_t n, int heads, float scale, int attn_dtype, int qk_norm, void *ws, size_t ws_bytes,
                 hipStream_t st, hipEvent_t after_pack, int n_seq, const uint16_t *res,
-                void *o_packed, bool *wrote_packed, const AttnKV *ready) {
-  if (wrote_packed) *wrote_packed = false;
+                AttnOperand *operand, const AttnKV *ready) {
+  if (operand && (n_seq != 1 || res)) return LV_ERR_PARAM;
   AttnPlan a;
   if (int rc = attn_plan(a, n, heads, scale, attn_dtype, qk_norm, q, o, ws, ws_bytes, n_seq, res)) return rc;
   const bool bounded = a.bounded, is_short = a.is_short, stream = a.stream;
@@ -2489,25 +2541,33 @@ int launch_attn(const uint16_t *q, const uint16_t *k, const uint16_t *v, uint16_
       hipLaunchKernelGGL(k_attn_amax, dim3(ag), dim3(256), 0, st, q, k, v, n, C, qk_norm, part);
       hipLaunchKernelGGL(k_attn_amax_final, dim3(1), dim3(256), 0, st, (const f32x4 *)part, (int)ag, amax);
     }
-    if (bounded) {
-      // the branch-free kernel against the fixed reference first, then the running-maximum kernel on the query
-      // blocks the first one flagged (normally none: its workgroups return at once)
-      u32x2 *kpb = (u32x2 *)(a.frag + 2 * a.per), *vpb = (u32x2 *)(a.frag + 3 * a.per);
+    u32x2 *kpb = (u32x2 *)(a.frag + 2 * a.per), *vpb = (u32x2 *)(a.frag + 3 * a.per);
+    if (bounded)
       hipLaunchKernelGGL(k_attn_pack_fp8b, dim3((unsigned)n_kt, (unsigned)heads), dim3(256), 0, st, k, v, n,
                          heads, n_kt, amax, kpb, vpb, redo, 2 * nqb);
-      if (after_pack && hipEventRecord(after_pack, st) != hipSuccess) return LV_ERR_HIP;
-      hipLaunchKernelGGL(k_attn_fp8_bounded, dim3((unsigned)(nqb2 * heads)), dim3(256), 0, st, q,
-                         (const u32x4 *)kpb, (const u32x4 *)vpb, o, n, heads, n_kt / 2, nqb2, c, amax, redo,
-                         2 * nqb);
-      hipLaunchKernelGGL(k_attn_fp8<true>, dim3((unsigned)(nqb * heads)), dim3(512), 0, st, q, kpb, vpb, o, n,
-                         heads, n_kt, nqb, c, qk_norm, amax, (const uint32_t *)redo);
-    } else {
+    else
       hipLaunchKernelGGL(k_attn_pack_fp8, dim3((unsigned)n_kt, (unsigned)heads), dim3(256), 0, st, k,
                          v, n, heads, n_kt, qk_norm, amax, kp, vp);
-      if (after_pack && hipEventRecord(after_pack, st) != hipSuccess) return LV_ERR_HIP;
-      hipLaunchKernelGGL(k_attn_fp8<false>, dim3((unsigned)(nqb * heads)), dim3(512), 0, st, q, kp, vp, o, n,
-                         heads, n_kt, nqb, c, qk_norm, amax, (const uint32_t *)nullptr);
-    }
+    if (after_pack && hipEventRecord(after_pack, st) != hipSuccess) return LV_ERR_HIP;
+    auto kernels = [&](auto kind, uint16_t *out) {
+      constexpr AttnOut OUT = decltype(kind)::value;
+      const AttnOutArgs oa = {operand ? operand->inv : nullptr, operand ? operand->amax : nullptr};
+      if (bounded) {
+        // the branch-free kernel against the fixed reference first, then the running-maximum kernel on the query
+        // blocks the first one flagged (normally none: its workgroups return at once)
+        hipLaunchKernelGGL(k_attn_fp8_bounded<OUT>, dim3((unsigned)(nqb2 * heads)), dim3(256), 0, st, q, (const u32x4 *)kpb,
+                           (const u32x4 *)vpb, out, n, heads, n_kt / 2, nqb2, c, amax, redo, 2 * nqb, oa);
+        hipLaunchKernelGGL((k_attn_fp8<true, OUT>), dim3((unsigned)(nqb * heads)), dim3(512), 0, st, q, kpb, vpb, out, n,
+                           heads, n_kt, nqb, c, qk_norm, amax, (const uint32_t *)redo, oa);
+      } else {
+        hipLaunchKernelGGL((k_attn_fp8<false, OUT>), dim3((unsigned)(nqb * heads)), dim3(512), 0, st, q, kp, vp, out, n,
+                           heads, n_kt, nqb, c, qk_norm, amax, (const uint32_t *)nullptr, oa);
+      }
+    };
+    if (operand) operand->written = true;
+    if (!operand) kernels(std::integral_constant<AttnOut, kOutRows>{}, o);
+    else if (operand->inv) kernels(std::integral_constant<AttnOut, kOutE4M3>{}, (uint16_t *)operand->at);
+    else kernels(std::integral_constant<AttnOut, kOutBf16>{}, (uint16_t *)operand->at);
     LV_HIP_CHECK_LAUNCH();
     return LV_OK;
   }
@@ -2547,9 +2607,9 @@ int launch_attn(const uint16_t *q, const uint16_t *k, const uint16_t *v, uint16_
       hipLaunchKernelGGL((k_attn_bf16_main<ON, PK>), dim3((unsigned)(nqb2 * heads * n_seq)), dim3(256), 0, st, q, kp, vp, out,
                          res, n, heads, n_seq, n_kt, nqb2, c, qk_norm, flags, stride);
   };
-  if (bounded && o_packed && wrote_packed && n_seq == 1 && !res) {
-    main_kernel(std::false_type{}, std::true_type{}, (uint16_t *)o_packed);
-    *wrote_packed = true;
+  if (bounded && operand && !operand->inv) {
+    main_kernel(std::false_type{}, std::true_type{}, (uint16_t *)operand->at);
+    operand->written = true;
   } else if (bounded) {
     main_kernel(std::false_type{}, std::false_type{}, o);
   } else {

@@ -93,14 +93,6 @@ __global__ __launch_bounds__(256) void k_layernorm(const uint16_t *__restrict__ 
     if (lane + 64 * c < nch) ((u32x4 *)(out + (size_t)row * C))[lane + 64 * c] = o[c];
 }
 
-// Only a value that would raise the word sends an atomic (a stale read only sends one too many), and
-// one thread per workgroup does: a few thousand waves that start together all find the word at 0,
-// and their atomics on one address take longer than reading the tensor (5-10 ns each).
-__device__ __forceinline__ void raise_max(uint32_t *word, float m) {
-  if (__float_as_uint(m) > __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
-    atomicMax(word, __float_as_uint(m));
-}
-
 // The same LayerNorm with the result written as a linear layer's activation operand (the
 // fragment order k_pack_rows produces: [row / 32][k-step of 16 channels][lane = row % 32 + 32 *
 // (second 8 of the 16)], 16 bytes each).  A workgroup owns the 32 rows of one fragment row, a
@@ -1357,7 +1349,7 @@ int launch_global_block(const uint16_t *z, int64_t M, int C, int heads, float sc
   if (delayed) {
     // FP8 layers, delayed scaling: every input scale is known before its tensor exists, so the
     // LayerNorms and the first MLP layer quantise their results themselves (taking the amax for
-    // the history on the way); only the attention output goes through k_quant_pack_fp8.
+    // the history on the way), and so does E4M3 attention; bf16 attention's output goes through k_quant_pack_fp8.
     uint32_t *const sc = w.fp8sc;
     auto layer = [&](int l) {
       LinearOpts o;
@@ -1371,11 +1363,13 @@ int launch_global_block(const uint16_t *z, int64_t M, int C, int heads, float sc
     o.kv = &kv;
     o.kv_done = &kv_ready;
     if ((rc = launch_linear(nullptr, M, C, 3 * C, bias[0], 0, w.qkv, C, w, st, o))) return rc;
+    AttnOperand a_op{w.apack, sc + kFp8Words + 2, sc + kFp8Words};
     if ((rc = launch_attn(q, k, v, w.a, M, heads, scale, attn_dtype, qk_norm, w.attn, w.attn_bytes, st, after_pack, 1, nullptr,
-                          nullptr, nullptr, kv_ready ? &kv : nullptr)))
+                          &a_op, kv_ready ? &kv : nullptr)))
       return rc;
     if (after_attn && hipEventRecord(after_attn, st) != hipSuccess) return LV_ERR_HIP;
     o = layer(1);
+    o.a_packed = a_op.written ? w.apack : nullptr;
     if ((rc = launch_linear(w.a, M, C, C, bias[1], 0, w.u1, C, w, st, o))) return rc;
     if ((rc = launch_layernorm(z, w.u1, bw.ln2_g, bw.ln2_b, M, C, nullptr, st, w.apack, w.Mp,
                                sc + 2 * kFp8Words + 2, sc + 2 * kFp8Words)))
@@ -1411,13 +1405,13 @@ int launch_global_block(const uint16_t *z, int64_t M, int C, int heads, float sc
   o.kv_done = &kv_ready;
   if ((rc = launch_linear(w.h, M, C, 3 * C, bias[0], 0, w.qkv, C, w, st, o))) return rc;
   // bf16 layers: where the attention kernel can, it writes the output projection's operand itself
-  bool a_is_packed = false;
+  AttnOperand a_op{w.apack};
   if ((rc = launch_attn(q, k, v, w.a, M, heads, scale, attn_dtype, qk_norm, w.attn, w.attn_bytes, st, after_pack, 1, nullptr,
-                        f8 ? nullptr : (void *)w.apack, &a_is_packed, kv_ready ? &kv : nullptr)))
+                        f8 ? nullptr : &a_op, kv_ready ? &kv : nullptr)))
     return rc;
   if (after_attn && hipEventRecord(after_attn, st) != hipSuccess) return LV_ERR_HIP;
   o = layer(1);
-  o.a_packed = a_is_packed ? w.apack : nullptr;
+  o.a_packed = a_op.written ? w.apack : nullptr;
   if ((rc = launch_linear(w.a, M, C, C, bias[1], 0, w.u1, C, w, st, o))) return rc;
   if ((rc = launch_layernorm(z, w.u1, bw.ln2_g, bw.ln2_b, M, C, w.h, st, ln_packed, w.Mp))) return rc;
   // bf16 layers: the first MLP layer writes its output in the second one's operand order.  All

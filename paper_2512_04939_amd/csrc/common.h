@@ -95,6 +95,14 @@ __device__ __forceinline__ float ga_score(float g, float v, float glo, float gr,
   return alpha * ng + beta * nv;
 }
 
+// Only a value that would raise the word sends an atomic (a stale read only sends one too many), and
+// one thread per workgroup does: a few thousand waves that start together all find the word at 0,
+// and their atomics on one address take longer than reading the tensor (5-10 ns each).
+__device__ __forceinline__ void raise_max(uint32_t *word, float m) {
+  if (__float_as_uint(m) > __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+    atomicMax(word, __float_as_uint(m));
+}
+
 // Eight channels of a 64-channel head row: their sum of squares, and scaled and rounded to bf16 again.  A row's
 // sum is taken in pairs of such chunks, wherever it is taken: the same bits.
 constexpr float kQkEps = 1e-6f;      // of the RMS normalisation of q and k

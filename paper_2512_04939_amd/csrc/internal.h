@@ -101,16 +101,22 @@ struct AttnKV {
 };
 int attn_kv_target(AttnKV &kv, int64_t n_tokens, int heads, float scale, int attn_dtype, int qk_norm, const void *q, const void *o,
                    void *ws, size_t ws_bytes);
+// A linear layer's activation operand buffer for align_up(n_tokens, 256) rows of K = 64 heads channels, in that layer's
+// fragment order.  inv: as E4M3 codes with the scale *inv, the largest |value| raised in *amax; NULL: as bf16.
+struct AttnOperand {
+  void *at;
+  const uint32_t *inv = nullptr;
+  uint32_t *amax = nullptr;
+  bool written = false;
+};
 // `after_pack`, when not NULL, is recorded between the K/V re-layout and the main kernel;
-// n_seq sequences of n_tokens each; res: optional residual added to the output.  o_packed
-// (optional, with wrote_packed): a linear layer's activation operand buffer for align_up(n_tokens,
-// 256) rows; when the bf16 fixed-reference kernel runs it writes the output there in that
-// layer's fragment order instead of to o, and *wrote_packed tells whether it did.  ready: an attn_kv_target() of
-// the same arguments whose work has been done.
+// n_seq sequences of n_tokens each; res: optional residual added to the output.  operand (optional; one sequence, no
+// residual): where the kernels can they write the output there instead of to o, and set `written`.  ready: an
+// attn_kv_target() of the same arguments whose work has been done.
 int launch_attn(const uint16_t *q, const uint16_t *k, const uint16_t *v, uint16_t *o,
                 int64_t n_tokens, int heads, float scale, int attn_dtype, int qk_norm, void *ws,
                 size_t ws_bytes, hipStream_t st, hipEvent_t after_pack = nullptr, int n_seq = 1,
-                const uint16_t *res = nullptr, void *o_packed = nullptr, bool *wrote_packed = nullptr,
+                const uint16_t *res = nullptr, AttnOperand *operand = nullptr,
                 const AttnKV *ready = nullptr);
 
 }  // namespace lv
