@@ -161,11 +161,8 @@ int litevggt_importance(const litevggt_params *p, const void *images, const void
   if (!x || !grad_cache || !score || (recompute_grad && !images)) return LV_ERR_NULL;
   if (!ws_ok(ws, ws_bytes, importance_ws_bytes(d))) return LV_ERR_WORKSPACE;
   float *psi_v = (float *)ws;
-  if (recompute_grad) {
-    rc = launch_grad_map(images, p->img_dtype, d, p->patch, grad_cache, st);
-    if (rc) return rc;
-  }
-  rc = launch_var_map((const uint16_t *)x, d, p->var_pool, psi_v, st);
+  rc = recompute_grad ? launch_maps(images, p->img_dtype, (const uint16_t *)x, d, p->patch, p->var_pool, grad_cache, psi_v, st)
+                      : launch_var_map((const uint16_t *)x, d, p->var_pool, psi_v, st);
   if (rc) return rc;
   return launch_ga_fuse(grad_cache, psi_v, d, p->alpha, p->beta, score, st);
 }
@@ -334,11 +331,8 @@ int litevggt_layers_run(const litevggt_params *p, int n_layers, const void *imag
     };
     if ((rc = mark(LV_EV_LAYER_BEGIN))) return rc;
     if (refresh && ga) {
-      if (l == 0) {
-        rc = launch_grad_map(images, p->img_dtype, d, p->patch, grad_cache, st);
-        if (rc) return rc;
-      }
-      rc = launch_var_map(xx, d, p->var_pool, (float *)op_ws, st);
+      rc = l == 0 ? launch_maps(images, p->img_dtype, xx, d, p->patch, p->var_pool, grad_cache, (float *)op_ws, st)
+                  : launch_var_map(xx, d, p->var_pool, (float *)op_ws, st);
       if (rc) return rc;
       // fusion and partition are one launch, unless the caller times them
       if (events) {

@@ -28,13 +28,13 @@ __device__ __forceinline__ f32x4 quad_f32(uint32_t v) {
   return f32x4{(float)(v & 255u), (float)((v >> 8) & 255u), (float)((v >> 16) & 255u), (float)(v >> 24)};
 }
 
-template <typename PixT, bool VEC>
-__global__ __launch_bounds__(640) void k_grad_map(const PixT *__restrict__ img, int F, int H, int W,
-                                                  int patch, float *__restrict__ psi_g) {
-  extern __shared__ f32x4 luma4[];           // luma of the pixel rows, from the last multiple of 4 pixels on
-  float *luma = (float *)luma4;
+// PIECES: pieces of every plane whose loads a thread has in flight.
+template <typename PixT, bool VEC, int PIECES>
+__device__ __forceinline__ void grad_rows(const PixT *__restrict__ img, int F, int H, int W, int patch,
+                                          float *__restrict__ psi_g, uint32_t block, f32x4 *luma4) {
+  float *luma = (float *)luma4;              // luma of the pixel rows, from the last multiple of 4 pixels on
   const int Hi = H * patch, Wi = W * patch;
-  const uint32_t nblk = (uint32_t)F * H, lb = xcd_contiguous(blockIdx.x, nblk);
+  const uint32_t nblk = (uint32_t)F * H, lb = xcd_contiguous(block, nblk);
   if (lb >= nblk) return;
   const int f = lb / H, ph = lb % H, tid = threadIdx.x, nt = blockDim.x;
   const size_t plane = (size_t)Hi * Wi;
@@ -47,17 +47,17 @@ __global__ __launch_bounds__(640) void k_grad_map(const PixT *__restrict__ img, 
     typedef typename Quad<PixT>::type Q;
     const Q *r4 = (const Q *)base, *g4 = (const Q *)(base + plane), *b4 = (const Q *)(base + 2 * plane);
     const int q1 = (p1 + 3) >> 2;
-    for (int q = q0 + tid; q < q1; q += 4 * nt) {
-      Q v[4][3];
+    for (int q = q0 + tid; q < q1; q += PIECES * nt) {
+      Q v[PIECES][3];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
+      for (int u = 0; u < PIECES; ++u) {
         const int at = min(q + u * nt, q1 - 1);
         v[u][0] = r4[at];
         v[u][1] = g4[at];
         v[u][2] = b4[at];
       }
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
+      for (int u = 0; u < PIECES; ++u) {
         const f32x4 r = quad_f32(v[u][0]) * unit, g = quad_f32(v[u][1]) * unit, b = quad_f32(v[u][2]) * unit;
         f32x4 l;
 #pragma unroll
@@ -107,6 +107,12 @@ __global__ __launch_bounds__(640) void k_grad_map(const PixT *__restrict__ img, 
     for (int i = 0; i < patch; ++i) acc += colsum[pw * patch + i];
     psi_g[((size_t)f * H + ph) * W + pw] = (float)(acc / pp);
   }
+}
+template <typename PixT, bool VEC>
+__global__ __launch_bounds__(640) void k_grad_map(const PixT *__restrict__ img, int F, int H, int W,
+                                                  int patch, float *__restrict__ psi_g) {
+  extern __shared__ f32x4 luma4[];
+  grad_rows<PixT, VEC, 4>(img, F, H, W, patch, psi_g, blockIdx.x, luma4);
 }
 
 int launch_grad_map(const void *images, int img_dtype, const Dims &d, int patch, float *psi_g,
@@ -265,22 +271,28 @@ __global__ __launch_bounds__(128) void k_var_map(const uint16_t *__restrict__ x,
 constexpr int kSeg = LV_VAR_SEG;
 constexpr int kVarWaves = 2;                   // waves per workgroup: 512 channels each, 8 per lane
 
-template <bool SEG>
-__global__ __launch_bounds__(64 * kVarWaves) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_var_map3(
+// STRIPS (SEG only): strips of the workgroup, `block` STRIPS + 0, 1, ..., two waves each; they walk one number of rows.
+template <bool SEG, int STRIPS>
+__device__ __forceinline__ void var_strip(
     const uint16_t *__restrict__ x, int F, int H, int W, int S, int C, int nseg, int row_segs,
-    float *__restrict__ psi_v) {
+    float *__restrict__ psi_v, uint32_t block) {
   constexpr int NC = kSeg + 2;               // columns a strip reads: its own and one on each side
-  __shared__ float comb[2][kVarWaves][kSeg]; // the waves' partial sums of a grid row, by row parity
+  __shared__ float comb_[STRIPS][2][kVarWaves][kSeg]; // the waves' partial sums of a grid row, by row parity
+  const int strip = STRIPS == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x / (64 * kVarWaves));
+  auto &comb = comb_[strip];
   if constexpr (!SEG) row_segs = 1;
   const uint32_t nblk = (uint32_t)F * row_segs * nseg;
-  const uint32_t lb = xcd_contiguous(blockIdx.x, nblk);   // neighbouring strips share an L2
-  if (lb >= nblk) return;
+  uint32_t lb = STRIPS == 1 ? xcd_contiguous(block, nblk) : block * STRIPS + strip;   // neighbouring strips share an L2
+  const bool spare = lb >= nblk;             // (of several: goes through the motions of the last one)
+  if (STRIPS == 1 && spare) return;
+  if (spare) lb = nblk - 1;
   const int fr = lb / nseg, j0 = (int)(lb % nseg) * kSeg;
   const int f = fr / row_segs, rs = fr % row_segs;
   // output rows [r0, r1), and the grid rows that are read
   const int r0 = SEG ? (int)((int64_t)H * rs / row_segs) : 0, r1 = SEG ? (int)((int64_t)H * (rs + 1) / row_segs) : H;
   const int ib = SEG ? max(r0 - 1, 0) : 0, row_end = SEG ? min(r1 + 1, H) : H;
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int steps = STRIPS == 1 ? r1 + 1 - ib : (H + row_segs - 1) / row_segs + 2;   // at least r1 + 1 - ib
+  const int wave = (threadIdx.x >> 6) % kVarWaves, lane = threadIdx.x & 63;
   const int T = H * W + S;
   const uint16_t *frame = x + ((size_t)f * T + S) * C;
   float *out = psi_v + (size_t)f * H * W;
@@ -363,7 +375,7 @@ __global__ __launch_bounds__(64 * kVarWaves) __attribute__((amdgpu_waves_per_eu(
       const int par = SEG ? decltype(parity)::value : i & 1;
       if (lane < kSeg) comb[par][wave][lane] = r;
       __syncthreads();
-      if (wave == 0 && lane < kSeg && io >= r0 && io < r1 && j0 + lane < W) {
+      if (wave == 0 && lane < kSeg && io >= r0 && io < r1 && j0 + lane < W && !spare) {
         r = 0.f;
 #pragma unroll
         for (int w2 = 0; w2 < kVarWaves; ++w2) r += comb[par][w2][lane];
@@ -374,12 +386,34 @@ __global__ __launch_bounds__(64 * kVarWaves) __attribute__((amdgpu_waves_per_eu(
     };
     // rows ib .. r1; row H is a row of pivots that flushes output row H - 1 (a step beyond r1 sees
     // pivots only and writes nothing)
-    for (int i = ib; i <= r1; i += 2) {
+    for (int i = ib; i < ib + steps; i += 2) {
       step(std::integral_constant<int, 0>{}, i);
       step(std::integral_constant<int, 1>{}, i + 1);
     }
     __syncthreads();                           // comb is reused by the next channel pass
   }
+}
+
+template <bool SEG>
+__global__ __launch_bounds__(64 * kVarWaves) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_var_map3(
+    const uint16_t *__restrict__ x, int F, int H, int W, int S, int C, int nseg, int row_segs,
+    float *__restrict__ psi_v) {
+  var_strip<SEG, 1>(x, F, H, W, S, C, nseg, row_segs, psi_v, blockIdx.x);
+}
+
+// Both maps of a short sequence in one launch, side by side: workgroups of 256 threads, first the strips, two each, then the
+// patch rows.  While all of them are on the chip at once (two per CU) the gradient map costs next to nothing beside the
+// variance map: with the fusion, apart and like this, us, 2 frames of 16 x 16, C = 256 15.0 and 12.1, 8 of them 16.9 and 12.3,
+// 2 of 37 x 37, C = 1024 (444 workgroups) 20.3 and 16.9.  Beyond, the strips' 250 registers leave the patch rows too few waves:
+// 588 workgroups 20.9 and 22.5, 1024 18.7 and 20.1, 100 frames of 37 x 37 143 and 160 at best, in any order of the two.
+constexpr int kBothStrips = 2, kBothThreads = 64 * kVarWaves * kBothStrips;
+template <typename PixT>
+__global__ __launch_bounds__(kBothThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_both_maps(
+    const PixT *__restrict__ img, int patch, float *__restrict__ psi_g, const uint16_t *__restrict__ x, int F, int H, int W, int S,
+    int C, int nseg, int row_segs, float *__restrict__ psi_v, int strip_blocks) {
+  extern __shared__ f32x4 luma4[];
+  if ((int)blockIdx.x < strip_blocks) var_strip<true, kBothStrips>(x, F, H, W, S, C, nseg, row_segs, psi_v, blockIdx.x);
+  else grad_rows<PixT, true, 8>(img, F, H, W, patch, psi_g, blockIdx.x - strip_blocks, luma4);
 }
 
 // Row segments per strip: rounds of 1024 workgroups (256 CUs, 2 waves per SIMD, 2 waves each), a
@@ -395,6 +429,40 @@ static int var_row_segments(int64_t strips, int H) {
     }
   }
   return best;
+}
+
+int launch_maps(const void *images, int img_dtype, const uint16_t *x, const Dims &d, int patch, int pool, float *psi_g, float *psi_v,
+                hipStream_t st) {
+  const int Wi = d.W * patch, nseg = (d.W + kSeg - 1) / kSeg;
+  const size_t pix = img_dtype == LV_IMG_F32 ? 4 : 1, lds = ((size_t)(patch + 2) * Wi + Wi + 8) * sizeof(float);
+  const bool vec = (size_t)d.H * patch * Wi % 4 == 0 && (uintptr_t)images % (4 * pix) == 0;
+  int dev = 0, n_cu = 0;
+  if (hipGetDevice(&dev) != hipSuccess ||
+      hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+    return LV_ERR_HIP;
+  const int64_t strips = (int64_t)d.F * nseg, rows = (int64_t)d.F * d.H;
+  const int row_segs = var_row_segments(strips, d.H);
+  const int64_t strip_blocks = (strips * row_segs + kBothStrips - 1) / kBothStrips, row_blocks = (int64_t)align_up((size_t)rows, kXcd);
+  // (launch_grad_map has the limit of image rows)
+  if (pool != 3 || !vec || lds > 64 * 1024 || strip_blocks + row_blocks > 2 * n_cu) {
+    if (int rc = launch_grad_map(images, img_dtype, d, patch, psi_g, st)) return rc;
+    return launch_var_map(x, d, pool, psi_v, st);
+  }
+  const dim3 grid((unsigned)(strip_blocks + row_blocks));
+  static std::atomic<uint64_t> lds_done[2];
+  int rc;
+#define LV_BOTH(T, I)                                                                                            \
+  if ((rc = allow_dynamic_lds((const void *)k_both_maps<T>, 64 * 1024, lds_done[I]))) return rc;                   \
+  hipLaunchKernelGGL((k_both_maps<T>), grid, dim3(kBothThreads), lds, st, (const T *)images, patch, psi_g, x, d.F, d.H, d.W, \
+                     d.S, d.C, nseg, row_segs, psi_v, (int)strip_blocks)
+  if (img_dtype == LV_IMG_F32) {
+    LV_BOTH(float, 0);
+  } else {
+    LV_BOTH(uint8_t, 1);
+  }
+#undef LV_BOTH
+  LV_HIP_CHECK_LAUNCH();
+  return LV_OK;
 }
 
 int launch_var_map(const uint16_t *x, const Dims &d, int pool, float *psi_v, hipStream_t st) {

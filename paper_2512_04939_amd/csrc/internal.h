@@ -35,6 +35,9 @@ inline int allow_dynamic_lds(const void *kernel, size_t bytes, std::atomic<uint6
 // importance.hip
 int launch_grad_map(const void *images, int img_dtype, const Dims &d, int patch, float *psi_g,
                     hipStream_t st);
+// both maps
+int launch_maps(const void *images, int img_dtype, const uint16_t *x, const Dims &d, int patch, int pool, float *psi_g, float *psi_v,
+                hipStream_t st);
 int launch_naive_score(const Dims &d, int policy, uint32_t seed, float *score, hipStream_t st);
 int launch_var_map(const uint16_t *x, const Dims &d, int pool, float *psi_v, hipStream_t st);
 int launch_ga_fuse(const float *psi_g, const float *psi_v, const Dims &d, float alpha, float beta,
