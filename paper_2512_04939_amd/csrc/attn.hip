@@ -19,6 +19,8 @@
 #include "common.h"
 #include "internal.h"
 
+#include <type_traits>
+
 namespace lv {
 
 constexpr int kKT = 32;              // keys per MFMA tile
@@ -49,7 +51,8 @@ __device__ __forceinline__ u32x4 rms_scale8(const u32x4 w, int log2_lanes) {
 // SYNC: also clears the words that workgroups meet at (pieces of cut blocks, the next blocks' counters); FLAGS: and the flags of the online
 // kernel, n_flags (<= n_kt) per (sequence, head) pair, which took a launch of 2 us (kernels of their own:
 // behind a run-time test it cost every call 2 %, 42.8 -> 43.7 us for 32 frames of 1374 tokens).
-template <bool SYNC, bool FLAGS>
+// V false: K only (k_attn_bf16_stream takes V's rows as they lie).
+template <bool SYNC, bool FLAGS, bool V>
 __global__ __launch_bounds__(256) void k_attn_pack(const uint16_t *__restrict__ k,
                                                    const uint16_t *__restrict__ v, int64_t n,
                                                    int heads, int n_kt, int qk_norm,
@@ -72,11 +75,12 @@ __global__ __launch_bounds__(256) void k_attn_pack(const uint16_t *__restrict__ 
   u32x4 wk = {0u, 0u, 0u, 0u}, wv = {0u, 0u, 0u, 0u};
   if (row < n) {
     wk = *(const u32x4 *)(k + (size_t)row * C + head * 64 + chunk * 8);
-    wv = *(const u32x4 *)(v + (size_t)row * C + head * 64 + chunk * 8);
+    if constexpr (V) wv = *(const u32x4 *)(v + (size_t)row * C + head * 64 + chunk * 8);
   }
   if (qk_norm) wk = rms_scale8(wk, 3);   // the 8 lanes that share a key hold its 64 values
   const size_t tile = ((size_t)blockIdx.y * n_kt + kt) * 4 * kFragU4;
   kp[tile + (chunk >> 1) * kFragU4 + (chunk & 1) * 32 + key] = wk;
+  if constexpr (!V) return;
   *(u32x4 *)&vt[key][chunk * 8] = wv;
   __syncthreads();
   const int u = t >> 7, dt = (t >> 6) & 1, lane = t & 63, h = lane >> 5, dr = lane & 31;
@@ -968,13 +972,33 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 constexpr int kStreamStages = 4;     // key stages of a sequence, at least
 constexpr int kStreamMost = 1024;    // ... and at most (65,536 keys): the seam is nothing beside a longer block (100,000
                                      // tokens level, 143,232 level on one box and 3 % slower on another)
+constexpr int kVRowsStages = 64;     // key stages of a sequence whose V is read as it lies, at most
 constexpr int kStreamWords = 8 * 8;  // counters: one per XCD, 32 bytes apart
 constexpr int kGiveWayStages = 32;   // (2,525 tokens, up to two rounds: 0.98 of one launch per block with, 0.96 without; 1,805
                                      // 0.98 and 1.00, 765 0.99 and 1.06)
 
-template <bool PACKED, bool RES>
+// VROWS: V is not re-laid out, which takes as long as K (100 frames of 37 x 37, 16 heads: 133 us for both, 90 for K).  Its rows
+// go into the ring as they lie, 64 of 128 bytes per stage, and the fragments come out by transposing reads, 16 per stage
+// in place of 8.  The loop pays 1 to 3 % for them, so it is for sequences short enough that the copy weighs more, us:
+// 200 frames of 16 x 16 207.8 -> 183.3, 100 of 37 x 37 941.5 -> 908.7, 20 of 60 x 60 1020 -> 1011, one sequence of 8,200 tokens
+// 302.9 and 300.3, of 9,000 335.6 and 338.4, of 30,000 3102 and 3143.  (K's fragments asked for a phase earlier than V's, to spread the
+// reads: level, and 2 to 4 registers short in the forms without a residual.)
+
+// Eight transposing reads: the four fragments of 32 keys of V from its rows in LDS (k_attn_bf16_stream), two 8-byte
+// halves each, not waited for.  addr: where channels 0-31 of the lane's row lie; channels 32-63 are at addr ^ 64.
+__device__ __forceinline__ void lds_read_vt_async(u32x2 (&dst)[8], uint32_t addr) {
+  asm volatile("ds_read_b64_tr_b16 %0, %8\n\tds_read_b64_tr_b16 %1, %8 offset:1024\n\t"
+               "ds_read_b64_tr_b16 %2, %9\n\tds_read_b64_tr_b16 %3, %9 offset:1024\n\t"
+               "ds_read_b64_tr_b16 %4, %8 offset:2048\n\tds_read_b64_tr_b16 %5, %8 offset:3072\n\t"
+               "ds_read_b64_tr_b16 %6, %9 offset:2048\n\tds_read_b64_tr_b16 %7, %9 offset:3072"
+               : "=&v"(dst[0]), "=&v"(dst[1]), "=&v"(dst[2]), "=&v"(dst[3]), "=&v"(dst[4]), "=&v"(dst[5]), "=&v"(dst[6]), "=&v"(dst[7])
+               : "v"(addr), "v"(addr ^ 64u)
+               : "memory");
+}
+
+template <bool PACKED, bool RES, bool VROWS>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_attn_bf16_stream(
-    const uint16_t *q, const u32x4 *__restrict__ kp, const u32x4 *__restrict__ vp, uint16_t *o,
+    const uint16_t *q, const u32x4 *__restrict__ kp, const u32x4 *__restrict__ vp, const uint16_t *vrows, uint16_t *o,
     const uint16_t *res, int64_t n, int heads, int n_seq, int n_kt, int nqb, float c, int qk_norm, uint32_t *ctr) {
   __shared__ u32x4 ks[kBStages][8 * kFragU4];
   __shared__ u32x4 vs[kBStages][8 * kFragU4];
@@ -989,23 +1013,38 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 
   int sh = 0, qb = 0;
   const u32x4 *kh, *vh;
+  __amdgpu_buffer_rsrc_t vb;         // VROWS: the head's columns of the sequence's rows; what lies beyond reads as zeros
+  // thread tid moves the 16-byte piece c of rows tid / 8 and tid / 8 + 32 to place c ^ 4 (row / 2 % 2) of the row in LDS, so
+  // that the four rows that 32 lanes of a transposing read take 64 bytes each from lie in different banks
+  const int v_off = VROWS ? (tid >> 3) * C * 2 + ((tid & 7) ^ (tid >> 4 & 1) * 4) * 16 : 0;
   auto place = [&](int b) {          // block b of the list: its pair, query block and packed K and V
     sh = list * (pairs / lists) + b / nqb;
     qb = b % nqb;
     kh = kp + (size_t)sh * n_kt * 4 * kFragU4 + tid;
-    vh = vp + (size_t)sh * n_kt * 4 * kFragU4 + tid;
+    if constexpr (VROWS) {
+      const int seq = sh / heads, head = sh - seq * heads;
+      vb = __builtin_amdgcn_make_buffer_rsrc((void *)(vrows + (size_t)seq * n * C + head * 64), 0, (int)((n - 1) * C * 2 + 128),
+                                             0x00020000);
+    } else {
+      vh = vp + (size_t)sh * n_kt * 4 * kFragU4 + tid;
+    }
   };
   int base = 0;                      // ring slot of the block's stage 0
-  int fslot = 0;
+  int fslot = 0, fstage = 0;
   size_t foff = 0;
   auto fetch1 = [&](int part) {      // one of the four fetch instructions of a stage
-    const u32x4 *src = (part < 2 ? kh : vh) + foff + (part & 1) * 256;
     u32x4 *dst = (part < 2 ? &ks[fslot][0] : &vs[fslot][0]) + (part & 1) * 256 + wave * 64;
-    __builtin_amdgcn_global_load_lds(src, dst, 16, 0, 0);
+    if (VROWS && part >= 2) {
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(vb, dst, 16, v_off, (2 * fstage + (part & 1)) * 64 * C, 0, 0);
+    } else {
+      const u32x4 *src = (part < 2 ? kh : vh) + foff + (part & 1) * 256;
+      __builtin_amdgcn_global_load_lds(src, dst, 16, 0, 0);
+    }
   };
   auto at_stage = [&](int src, int ring) {
     fslot = (base + ring) & (kBStages - 1);
     foff = (size_t)src * 8 * kFragU4;
+    fstage = src;
   };
   auto fetch = [&](int stage) {
     at_stage(stage, stage);
@@ -1029,7 +1068,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   bf16x8 qf[2][4];
   f32x16 oacc[2][2], sacc[2];
   float lrow[2][2];
-  u32x4 pb[2][2], fv[2][4], fk[2][4];
+  u32x4 pb[2][2], fk[2][4];
+  using VF = std::conditional_t<VROWS, u32x2[8], u32x4[4]>;   // V fragments of a tile: as halves, or whole
+  VF fv[2];
   const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   auto mma_s = [&](int sub, const u32x4(&kf)[4]) {
     f32x16 acc = zero;
@@ -1038,12 +1079,16 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, kf[s]), qf[sub][s], acc, 0, 0, 0);
     sacc[sub] = acc;
   };
-  auto mma_pv = [&](int sub, const u32x4(&vf)[4]) {
+  auto frag_v = [&](const VF &vf, int f) {
+    if constexpr (VROWS) return u32x4{vf[2 * f].x, vf[2 * f].y, vf[2 * f + 1].x, vf[2 * f + 1].y};
+    else return vf[f];
+  };
+  auto mma_pv = [&](int sub, const VF &vf) {
 #pragma unroll
     for (int u = 0; u < 2; ++u)
 #pragma unroll
       for (int dt = 0; dt < 2; ++dt)
-        oacc[sub][dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, vf[u * 2 + dt]),
+        oacc[sub][dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, frag_v(vf, u * 2 + dt)),
                                                                 __builtin_bit_cast(bf16x8, pb[sub][u]), oacc[sub][dt], 0, 0, 0);
   };
   const int n_last = (int)(n - (int64_t)(nkv - 1) * kKV) - 4 * h;   // keys of the last stage, from this lane half's first row
@@ -1078,13 +1123,32 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       __builtin_amdgcn_sched_group_barrier(0x002, 3, 0);   // pack + 2 adds
     }
   };
-  const uint32_t ks_lane = lds_addr(&ks[0][lane]), vs_lane = lds_addr(&vs[0][lane]);
+  const uint32_t ks_lane = lds_addr(&ks[0][lane]);
+  const uint32_t vs_lane = VROWS ? lds_addr(&vs[0][0]) + (4 * h + (lane >> 2 & 3)) * 128 + (lane >> 3 & 1) * 64 + (lane >> 4 & 1) * 32 +
+                                       (lane & 3) * 8
+                                 : lds_addr(&vs[0][lane]);
+  auto read_v = [&](VF &dst, uint32_t addr) {
+    if constexpr (VROWS) lds_read_vt_async(dst, addr);
+    else lds_read4_async(dst, addr);
+  };
+  // The fragments are there.  VROWS: the operands beside V's halves are kept behind the wait in their place (two halves are
+  // one operand: a copy of each otherwise).
+  auto wait_frags = [&](VF &v, u32x4(&k)[4]) {
+    if constexpr (VROWS) {
+      asm volatile("s_waitcnt lgkmcnt(0)"
+                   : "+v"(k[0]), "+v"(k[1]), "+v"(k[2]), "+v"(k[3]), "+v"(oacc[0][0]), "+v"(oacc[0][1]), "+v"(oacc[1][0]), "+v"(oacc[1][1])
+                   :
+                   : "memory");
+      __builtin_amdgcn_sched_barrier(0);
+    } else {
+      lds_wait(v, k);
+    }
+  };
   auto frag_off = [&](int t) {   // byte offset of tile t's four fragments in a ring array
     return (uint32_t)(((((t >> 1) + base) & (kBStages - 1)) * 8 + (t & 1) * 4) * kFragU4 * 16);
   };
-  auto phase_a = [&](int t, const u32x4(&v_prev)[4], u32x4(&v_cur)[4], const u32x4(&k_cur)[4], u32x4(&k_next)[4],
-                     int fq = -1) {
-    lds_read4_async(v_cur, vs_lane + frag_off(t));
+  auto phase_a = [&](int t, const VF &v_prev, VF &v_cur, const u32x4(&k_cur)[4], u32x4(&k_next)[4], int fq = -1) {
+    read_v(v_cur, vs_lane + frag_off(t));
     lds_read4_async(k_next, ks_lane + frag_off(t + 1));   // past the last tile: a slot that may be arriving, never used
     if (fq >= 0) fetch1(fq);
     __builtin_amdgcn_sched_barrier(0);
@@ -1093,9 +1157,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     mma_pv(1, v_prev);
     recipe();
   };
-  auto phase_b = [&](u32x4(&v_cur)[4], u32x4(&k_next)[4], int fq = -1) {
+  auto phase_b = [&](VF &v_cur, u32x4(&k_next)[4], int fq = -1) {
     __builtin_amdgcn_sched_barrier(0);
-    lds_wait(v_cur, k_next);
+    wait_frags(v_cur, k_next);
     if (fq >= 0) {
       fetch1(fq);
       __builtin_amdgcn_sched_barrier(0);
@@ -1200,8 +1264,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       load_q();
     } else {
       lds_read4_async(fk[0], ks_lane + frag_off(0));
-      lds_read4_async(fv[0], vs_lane + frag_off(0));
-      lds_wait(fk[0], fv[0]);
+      read_v(fv[0], vs_lane + frag_off(0));
+      wait_frags(fv[0], fk[0]);
       lds_read4_async(fk[1], ks_lane + frag_off(1));
       mma_s(0, fk[0]);
       weights(0);
@@ -1231,7 +1295,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       publish(std::integral_constant<int, 0>{});
       phase_a(nkt - 4, fv[1], fv[0], fk[0], fk[1]);
       pin();
-      lds_wait(fv[0], fk[1]);
+      wait_frags(fv[0], fk[1]);
       turn();                                               // from here on the next block's stages 0 and 1 are fetched
       at_stage(0, nkv);
       phase_b(fv[0], fk[1], 0);
@@ -1253,7 +1317,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       fetch1(3);
       pin();
       if (n_last + 4 * h < kKV) mask_tail(1, 1);
-      lds_wait(fv[1], fk[0]);
+      wait_frags(fv[1], fk[0]);
       weights(1);
       pin();
       // this block's residual rows and the next block's q rows, in the registers of the fragments and scores
@@ -2574,19 +2638,27 @@ int launch_attn(const uint16_t *q, const uint16_t *k, const uint16_t *v, uint16_
   u32x4 *kp = (u32x4 *)a.frag, *vp = (u32x4 *)(a.frag + a.per);
   uint32_t *const sync = a.sync, *const ctr = a.head;
   float *const partial = a.partial;
+  // V as it lies: not where a block's output may take the place of rows that another one still reads
+  const size_t bytes = (size_t)n_seq * n * heads * 128;
+  const bool kv_ready = ready && ready->kp;
+  const bool vrows = stream && n_kt / 2 <= kVRowsStages && !kv_ready && !(operand && !operand->inv) && n * heads * 128 < ((int64_t)1 << 31) &&
+                     ((uintptr_t)o >= (uintptr_t)v + bytes || (uintptr_t)v >= (uintptr_t)o + bytes);
   auto pack_kernel = [&](auto has_sync) {
     constexpr bool SYNC = decltype(has_sync)::value;
     uint32_t *const cleared = stream ? ctr : sync;
     const int n_cleared = stream ? kStreamWords : kSyncWords;
     const dim3 grid((unsigned)n_kt, (unsigned)(heads * n_seq));
-    if (bounded)
-      hipLaunchKernelGGL((k_attn_pack<SYNC, false>), grid, dim3(256), 0, st, k, v, n, heads, n_kt, qk_norm, kp, vp, cleared,
+    if (vrows)
+      hipLaunchKernelGGL((k_attn_pack<true, false, false>), grid, dim3(256), 0, st, k, v, n, heads, n_kt, qk_norm, kp, vp, cleared,
+                         n_cleared, redo, 0);
+    else if (bounded)
+      hipLaunchKernelGGL((k_attn_pack<SYNC, false, true>), grid, dim3(256), 0, st, k, v, n, heads, n_kt, qk_norm, kp, vp, cleared,
                          n_cleared, redo, 0);
     else
-      hipLaunchKernelGGL((k_attn_pack<SYNC, true>), grid, dim3(256), 0, st, k, v, n, heads, n_kt, qk_norm, kp, vp, cleared,
+      hipLaunchKernelGGL((k_attn_pack<SYNC, true, true>), grid, dim3(256), 0, st, k, v, n, heads, n_kt, qk_norm, kp, vp, cleared,
                          n_cleared, redo, 2 * nqb);
   };
-  if (ready && ready->kp) {}          // the layer that produced k and v has packed them, and what they clear is cleared
+  if (kv_ready) {}          // the layer that produced k and v has packed them, and what they clear is cleared
   else if (cut.n_cut || stream) pack_kernel(std::true_type{});
   else pack_kernel(std::false_type{});
   if (after_pack && hipEventRecord(after_pack, st) != hipSuccess) return LV_ERR_HIP;
@@ -2598,8 +2670,10 @@ int launch_attn(const uint16_t *q, const uint16_t *k, const uint16_t *v, uint16_
       hipLaunchKernelGGL((k_attn_bf16_short<ON, PK>), dim3((unsigned)(nqs * heads * n_seq)), dim3(256), 0, st, q, kp, vp, out,
                          res, n, heads, n_seq, n_kt, nqs, c, qk_norm, flags, stride);
     else if (!ON && stream)
-      hipLaunchKernelGGL((res ? k_attn_bf16_stream<PK, !PK> : k_attn_bf16_stream<PK, false>), dim3((unsigned)(2 * n_cu)),
-                         dim3(256), 0, st, q, kp, vp, out, res, n, heads, n_seq, n_kt, nqb2, c, qk_norm, ctr);
+      hipLaunchKernelGGL((vrows ? res ? k_attn_bf16_stream<false, true, true> : k_attn_bf16_stream<false, false, true>
+                                : res ? k_attn_bf16_stream<PK, !PK, false> : k_attn_bf16_stream<PK, false, false>),
+                         dim3((unsigned)(2 * n_cu)), dim3(256), 0, st, q, kp, vp, v, out, res, n, heads, n_seq, n_kt, nqb2, c,
+                         qk_norm, ctr);
     else if (cut.n_cut)
       hipLaunchKernelGGL((k_attn_bf16_cut<ON, PK>), dim3((unsigned)(kXcd * 2 * cut.n_cut)), dim3(256), 0, st, q, kp, vp, out,
                          n, heads, n_kt, nqb2, c, qk_norm, flags, stride, cut, sync, partial);
