@@ -983,6 +983,10 @@ constexpr int kGiveWayStages = 32;   // (2,525 tokens, up to two rounds: 0.98 of
 // 200 frames of 16 x 16 207.8 -> 183.3, 100 of 37 x 37 941.5 -> 908.7, 20 of 60 x 60 1020 -> 1011, one sequence of 8,200 tokens
 // 302.9 and 300.3, of 9,000 335.6 and 338.4, of 30,000 3102 and 3143.  (K's fragments asked for a phase earlier than V's, to spread the
 // reads: level, and 2 to 4 registers short in the forms without a residual.)
+// A sequence's last block, with at most half of its queries there, gives every wave 32 of them instead of 64 to one or two
+// waves: the block's waves do half the work, and the SIMDs that had none of it share it, us: 200 frames of 16 x 16 (5 queries
+// of 256) 190 -> 181, 50 of 28 x 37 (17) 299 -> 289, 100 of 37 x 37 (94) 874 -> 856.  The same additions in the same order.
+// (In the forms with packed V, whose sequences are longer, the second loop costs 20 registers in scratch.)
 
 // Eight transposing reads: the four fragments of 32 keys of V from its rows in LDS (k_attn_bf16_stream), two 8-byte
 // halves each, not waited for.  addr: where channels 0-31 of the lane's row lie; channels 32-63 are at addr ^ 64.
@@ -1053,12 +1057,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     fetch1(2);
     fetch1(3);
   };
+  auto narrow = [&]() { return VROWS && n - (int64_t)qb * kBQB <= kBQB / 2; };   // the block's waves take 32 queries each
   u32x4 qraw[2][4];
   auto load_q = [&]() {
-    const int seq = sh / heads, head = sh - seq * heads;
+    const int seq = sh / heads, head = sh - seq * heads, qw = narrow() ? kQW / 2 : kQW;
 #pragma unroll
     for (int sub = 0; sub < 2; ++sub) {
-      const int64_t row = (int64_t)seq * n + min((int64_t)qb * kBQB + wave * kQW + sub * 32 + ql, n - 1);
+      const int64_t row = (int64_t)seq * n + min((int64_t)qb * kBQB + wave * qw + sub * 32 + ql, n - 1);
       const uint16_t *qp = q + (size_t)row * C + head * 64 + 8 * h;
 #pragma unroll
       for (int s = 0; s < 4; ++s) qraw[sub][s] = *(const u32x4 *)(qp + 16 * s);
@@ -1072,33 +1077,36 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   using VF = std::conditional_t<VROWS, u32x2[8], u32x4[4]>;   // V fragments of a tile: as halves, or whole
   VF fv[2];
   const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-  auto mma_s = [&](int sub, const u32x4(&kf)[4]) {
+  // (of_sub: the query block; sub: whose registers hold its scores and weights)
+  auto mma_s_of = [&](int of_sub, int sub, const u32x4(&kf)[4]) {
     f32x16 acc = zero;
 #pragma unroll
     for (int s = 0; s < 4; ++s)
-      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, kf[s]), qf[sub][s], acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, kf[s]), qf[of_sub][s], acc, 0, 0, 0);
     sacc[sub] = acc;
   };
+  auto mma_s = [&](int sub, const u32x4(&kf)[4]) { mma_s_of(sub, sub, kf); };
   auto frag_v = [&](const VF &vf, int f) {
     if constexpr (VROWS) return u32x4{vf[2 * f].x, vf[2 * f].y, vf[2 * f + 1].x, vf[2 * f + 1].y};
     else return vf[f];
   };
-  auto mma_pv = [&](int sub, const VF &vf) {
+  auto mma_pv_of = [&](int of_sub, int sub, const VF &vf) {
 #pragma unroll
     for (int u = 0; u < 2; ++u)
 #pragma unroll
       for (int dt = 0; dt < 2; ++dt)
-        oacc[sub][dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, frag_v(vf, u * 2 + dt)),
-                                                                __builtin_bit_cast(bf16x8, pb[sub][u]), oacc[sub][dt], 0, 0, 0);
+        oacc[of_sub][dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, frag_v(vf, u * 2 + dt)),
+                                                                   __builtin_bit_cast(bf16x8, pb[sub][u]), oacc[of_sub][dt], 0, 0, 0);
   };
+  auto mma_pv = [&](int sub, const VF &vf) { mma_pv_of(sub, sub, vf); };
   const int n_last = (int)(n - (int64_t)(nkv - 1) * kKV) - 4 * h;   // keys of the last stage, from this lane half's first row
   auto mask_tail = [&](int tile, int sub) {                         // tile 0, 1 of the last stage
 #pragma unroll
     for (int r = 0; r < 16; ++r)
       if (tile * kKT + (r >> 2) * 8 + (r & 3) >= n_last) sacc[sub][r] = -INFINITY;
   };
-  auto weights = [&](int sub) {
-    float l0 = lrow[sub][0], l1 = lrow[sub][1];
+  auto weights_of = [&](int of_sub, int sub) {
+    float l0 = lrow[of_sub][0], l1 = lrow[of_sub][1];
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
       uint32_t w[4];
@@ -1112,9 +1120,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       }
       pb[sub][u] = u32x4{w[0], w[1], w[2], w[3]};
     }
-    lrow[sub][0] = l0;
-    lrow[sub][1] = l1;
+    lrow[of_sub][0] = l0;
+    lrow[of_sub][1] = l1;
   };
+  auto weights = [&](int sub) { weights_of(sub, sub); };
   auto recipe = [&]() {
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
@@ -1144,6 +1153,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       lds_wait(v, k);
     }
   };
+  auto wait_k = [&](u32x4(&k)[4]) {
+    asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(k[0]), "+v"(k[1]), "+v"(k[2]), "+v"(k[3]) : : "memory");
+    __builtin_amdgcn_sched_barrier(0);
+  };
   auto frag_off = [&](int t) {   // byte offset of tile t's four fragments in a ring array
     return (uint32_t)(((((t >> 1) + base) & (kBStages - 1)) * 8 + (t & 1) * 4) * kFragU4 * 16);
   };
@@ -1168,6 +1181,22 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     weights(1);
     mma_pv(0, v_cur);
     recipe();
+  };
+  // One query block: tile t's weights beside the scores of tile t + 1 and the output of tile t - 1; the registers
+  // that hold a second query block's scores, weights and fragments hold every other tile's.  The wait is for the reads of the step before.
+  auto step = [&](auto first, auto last, auto odd, int t, int fq0 = -1, int fq1 = -1) {
+    constexpr int P = decltype(odd)::value;               // t % 2
+    __builtin_amdgcn_sched_barrier(0);
+    wait_frags(fv[P ^ 1], fk[P ^ 1]);
+    read_v(fv[P], vs_lane + frag_off(t));
+    if constexpr (!decltype(last)::value) lds_read4_async(fk[P], ks_lane + frag_off(t + 2));
+    if (fq0 >= 0) fetch1(fq0);
+    if (fq1 >= 0) fetch1(fq1);
+    __builtin_amdgcn_sched_barrier(0);
+    if constexpr (!decltype(last)::value) mma_s_of(0, P ^ 1, fk[P ^ 1]);
+    weights_of(0, P);
+    if constexpr (!decltype(first)::value) mma_pv_of(0, P ^ 1, fv[P ^ 1]);
+    if constexpr (!decltype(first)::value && !decltype(last)::value) recipe();
   };
   // outside the loop: the row sums are taken where they stand (else the additions are moved to the
   // end of the block and the weights that wait for them to scratch)
@@ -1220,7 +1249,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   while (true) {
     if (give_way) take_turn();
-    const int64_t q0 = (int64_t)qb * kBQB + wave * kQW;
+    const bool one_sub = narrow();
+    const int64_t q0 = (int64_t)qb * kBQB + wave * (one_sub ? kQW / 2 : kQW);
     const int seq = sh / heads, head = sh - seq * heads;
     uint16_t *const ob = o + (size_t)seq * n * C;
     const uint16_t *const rb = RES ? res + (size_t)seq * n * C : nullptr;
@@ -1242,6 +1272,49 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_sched_barrier(0);
     fetch(2);
+    // lanes l and l + 32 trade halves: lane l then has channels 0-7, lane l + 32 channels 8-15 of 16
+    auto store = [&](int sub, const u32x4(&rs)[4]) {
+      float l = lrow[sub][0] + lrow[sub][1];
+      l += __shfl_xor(l, 32, 64);
+      const int64_t row = q0 + sub * 32 + ql;
+      const bool live = row < n;
+      const float inv = PACKED && !live ? 0.f : 1.0f / l;
+#pragma unroll
+      for (int dt = 0; dt < 2; ++dt)
+#pragma unroll
+        for (int gp = 0; gp < 2; ++gp) {
+          float r[8];
+#pragma unroll
+          for (int i = 0; i < 8; ++i) r[i] = PACKED && !live ? 0.f : oacc[sub][dt][8 * gp + i] * inv;
+          if constexpr (RES) {   // out = res + attention, one rounding: halves traded the other way first
+            const u32x4 x = rs[dt * 2 + gp];
+            const auto a = __builtin_amdgcn_permlane32_swap(x.x, x.z, false, false);
+            const auto b = __builtin_amdgcn_permlane32_swap(x.y, x.w, false, false);
+            r[0] += bf16_lo(a[0]);
+            r[1] += bf16_hi(a[0]);
+            r[2] += bf16_lo(b[0]);
+            r[3] += bf16_hi(b[0]);
+            r[4] += bf16_lo(a[1]);
+            r[5] += bf16_hi(a[1]);
+            r[6] += bf16_lo(b[1]);
+            r[7] += bf16_hi(b[1]);
+          }
+          const auto s0 = __builtin_amdgcn_permlane32_swap(pack_bf16(r[0], r[1]), pack_bf16(r[4], r[5]), false, false);
+          const auto s1 = __builtin_amdgcn_permlane32_swap(pack_bf16(r[2], r[3]), pack_bf16(r[6], r[7]), false, false);
+          const u32x4 w = u32x4{s0[0], s1[0], s0[1], s1[1]};
+          if constexpr (PACKED)
+            ((u32x4 *)o)[((size_t)((q0 + sub * 32) >> 5) * (C >> 4) + head * 4 + dt * 2 + gp) * 64 + lane] = w;
+          else if (live)
+            *(u32x4 *)(ob + (size_t)row * C + head * 64 + 32 * dt + 16 * gp + 8 * h) = w;
+        }
+    };
+    auto load_res = [&](int sub, u32x4(&rs)[4]) {
+      const int64_t row = min(q0 + sub * 32 + ql, n - 1);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) rs[i] = *(const u32x4 *)(rb + (size_t)row * C + head * 64 + 16 * i + 8 * h);
+    };
+    using Yes = std::true_type;
+    using No = std::false_type;
     if (q0 >= n) {
       // no queries: the wave only moves its share of the stages
       for (int i = 0; i < nkv - 3; ++i) {
@@ -1262,6 +1335,52 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         fetch1(3);
       }
       load_q();
+    } else if (one_sub) {
+      lds_read4_async(fk[0], ks_lane + frag_off(0));
+      wait_k(fk[0]);
+      lds_read4_async(fk[1], ks_lane + frag_off(1));
+      mma_s_of(0, 0, fk[0]);
+      step(Yes{}, No{}, No{}, 0);
+      pin();
+      uint32_t taken = 0u;
+#pragma unroll 1
+      for (int i = 0; i < nkv - 3; ++i) {
+        if (i == nkv - kStreamStages && tid == 0)
+          taken = __hip_atomic_fetch_add(ctr + list * 8, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        int st = i + 3;
+        asm volatile("" : "+s"(st));
+        at_stage(st, st);
+        step(No{}, No{}, Yes{}, 2 * i + 1, 0, 1);
+        fetch1(2);
+        wait_frags(fv[1], fk[1]);
+        publish(std::integral_constant<int, 3>{});
+        step(No{}, No{}, No{}, 2 * i + 2, 3);
+      }
+      if (tid == 0) next_block = slots + (int)taken;
+      step(No{}, No{}, Yes{}, nkt - 5);
+      pin();
+      wait_frags(fv[1], fk[1]);
+      publish(std::integral_constant<int, 0>{});
+      turn();                                               // from here on the next block's stages 0 and 1 are fetched
+      at_stage(0, nkv);
+      step(No{}, No{}, No{}, nkt - 4, 0, 1);
+      pin();
+      step(No{}, No{}, Yes{}, nkt - 3, 2, 3);
+      pin();
+      if (n_last + 4 * h < kKV) mask_tail(0, 0);
+      at_stage(1, nkv + 1);
+      step(No{}, No{}, No{}, nkt - 2, 0, 1);
+      pin();
+      if (n_last + 4 * h < kKV) mask_tail(1, 1);
+      step(No{}, Yes{}, Yes{}, nkt - 1, 2, 3);
+      pin();
+      wait_frags(fv[1], fk[1]);
+      u32x4 rw[4];
+      if constexpr (RES) load_res(0, rw);
+      load_q();
+      __builtin_amdgcn_sched_barrier(0);
+      mma_pv_of(0, 1, fv[1]);
+      store(0, rw);
     } else {
       lds_read4_async(fk[0], ks_lane + frag_off(0));
       read_v(fv[0], vs_lane + frag_off(0));
@@ -1324,54 +1443,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       __builtin_amdgcn_sched_barrier(0);
       u32x4 rw[2][4];
       if constexpr (RES) {
-#pragma unroll
-        for (int sub = 0; sub < 2; ++sub) {
-          const int64_t row = min(q0 + sub * 32 + ql, n - 1);
-#pragma unroll
-          for (int i = 0; i < 4; ++i) rw[sub][i] = *(const u32x4 *)(rb + (size_t)row * C + head * 64 + 16 * i + 8 * h);
-        }
+        load_res(0, rw[0]);
+        load_res(1, rw[1]);
       }
       load_q();
       __builtin_amdgcn_sched_barrier(0);
       mma_pv(0, fv[1]);
       mma_pv(1, fv[1]);
-      // lanes l and l + 32 trade halves: lane l then has channels 0-7, lane l + 32 channels 8-15 of 16
-#pragma unroll
-      for (int sub = 0; sub < 2; ++sub) {
-        float l = lrow[sub][0] + lrow[sub][1];
-        l += __shfl_xor(l, 32, 64);
-        const int64_t row = q0 + sub * 32 + ql;
-        const bool live = row < n;
-        const float inv = PACKED && !live ? 0.f : 1.0f / l;
-#pragma unroll
-        for (int dt = 0; dt < 2; ++dt)
-#pragma unroll
-          for (int gp = 0; gp < 2; ++gp) {
-            float r[8];
-#pragma unroll
-            for (int i = 0; i < 8; ++i) r[i] = PACKED && !live ? 0.f : oacc[sub][dt][8 * gp + i] * inv;
-            if constexpr (RES) {   // out = res + attention, one rounding: halves traded the other way first
-              const u32x4 x = rw[sub][dt * 2 + gp];
-              const auto a = __builtin_amdgcn_permlane32_swap(x.x, x.z, false, false);
-              const auto b = __builtin_amdgcn_permlane32_swap(x.y, x.w, false, false);
-              r[0] += bf16_lo(a[0]);
-              r[1] += bf16_hi(a[0]);
-              r[2] += bf16_lo(b[0]);
-              r[3] += bf16_hi(b[0]);
-              r[4] += bf16_lo(a[1]);
-              r[5] += bf16_hi(a[1]);
-              r[6] += bf16_lo(b[1]);
-              r[7] += bf16_hi(b[1]);
-            }
-            const auto s0 = __builtin_amdgcn_permlane32_swap(pack_bf16(r[0], r[1]), pack_bf16(r[4], r[5]), false, false);
-            const auto s1 = __builtin_amdgcn_permlane32_swap(pack_bf16(r[2], r[3]), pack_bf16(r[6], r[7]), false, false);
-            const u32x4 w = u32x4{s0[0], s1[0], s0[1], s1[1]};
-            if constexpr (PACKED)
-              ((u32x4 *)o)[((size_t)((q0 + sub * 32) >> 5) * (C >> 4) + head * 4 + dt * 2 + gp) * 64 + lane] = w;
-            else if (live)
-              *(u32x4 *)(ob + (size_t)row * C + head * 64 + 32 * dt + 16 * gp + 8 * h) = w;
-          }
-      }
+      store(0, rw[0]);
+      store(1, rw[1]);
     }
     base = (base + nkv) & (kBStages - 1);
     if (!more) break;

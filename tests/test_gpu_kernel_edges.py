@@ -786,6 +786,25 @@ def test_attention_blocks_in_a_stream(B, frames, h, w, heads, res):
     assert torch.equal(outs[0], outs[1])
 
 
+# last blocks whose waves take 32 queries each: 127 and 128 queries (and 129, where they take 64), whole waves and one more query
+@pytest.mark.parametrize("frames,h,w,heads", [(33, 18, 21, 8), (33, 1, 379, 8), (33, 19, 20, 8), (33, 15, 21, 8), (33, 4, 79, 8),
+                                              (22, 11, 49, 8), (22, 20, 27, 8), (30, 9, 67, 6), (30, 4, 151, 6)])
+@pytest.mark.parametrize("res", [0, 1])
+def test_attention_stream_narrow_last_blocks(B, frames, h, w, heads, res):
+    import torch
+    n = h * w + 5
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n)
+    x = torch.randn(frames * n, heads * 64, generator=g, device="cuda").to(torch.bfloat16)
+    ph = B.make_params(frames, h, w, heads * 64, heads, qk_norm=1)
+    got = torch.full_like(x, float("nan"))
+    B.litevggt_frame_attn(ph, x, x, x, x if res else None, got, B.alloc_ws(B.litevggt_frame_attn_ws_bytes(ph)))
+    torch.cuda.synchronize()
+    ref = torch.cat([_attn64(f, f, f, True, heads) + (f.double() if res else 0.0) for f in x.reshape(frames, n, -1)])
+    # bf16 weights and outputs: 2^-8 of a value twice, as for the other blocks
+    assert float((got.double() - ref).abs().max() / ref.abs().max()) <= 2e-2
+
+
 # the same rows alone (one launch per block) and as one of many blocks have the same bits
 @pytest.mark.parametrize("n,heads", [(8200, 16), (13500, 16), (11200, 12)])
 def test_attention_stream_equals_single_blocks(B, n, heads):
