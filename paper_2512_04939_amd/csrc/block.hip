@@ -598,7 +598,16 @@ __global__ __launch_bounds__((GemmShape<BM, BN>::kThreads * KG)) __attribute__((
   constexpr bool PACKED = OUT == kOperand, QKV = OUT == kQkvAmax || OUT == kQkvPacked;
   static_assert(OUT != kQkvPacked || BM == BN, "V's tiles swap rows and columns");
   constexpr int kStages = S::kStages, kStageU4 = S::kStageU4, kB = S::kB;
-  constexpr bool kTwoSets = !FP8 || kB <= 2;   // registers for two sets of weight fragments
+  // 256 x 256: two groups of four waves, one wave of each on every SIMD, take turns.  One reads the fragments of its next
+  // stage and fetches while the other's MFMAs run, a barrier ends both.  (All eight waves in step, reads, fetches and
+  // MFMAs mixed as below: every wave of a SIMD waited for the same barrier and address unit at once, 1,450 cycles
+  // per E4M3 stage of 1,024 MFMA cycles on a chip that is mostly idle, 1,250 in turns; on a full one the clock takes a part
+  // back.)  The ring runs on from tile to tile: a tile's last stages fetch the next one's first, nothing is
+  // drained between them.  us for qkv / out / MLP 1 / MLP 2, C = 1024, in step and in turns: E4M3, M = 15,432 62.0 26.8 102.6
+  // 71.8, 58.6 26.5 96.2 67.8, 30,000 113 43.7 196 134, 111 41.1 181 125; bf16, 30,000 176 65.9 268 233, 165 62.1 251 221.
+  constexpr bool kTurns = BM == 256 && BN == 256;
+  constexpr bool kTwoSets = !kTurns && (!FP8 || kB <= 2);   // registers for two sets of weight fragments
+  constexpr int kAhead = kTurns ? kStages - 1 : kStages;   // stages fetched ahead
   extern __shared__ u32x4 rings[];             // one ring per K group
   const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5;
   const int kg = KG == 1 ? 0 : __builtin_amdgcn_readfirstlane(tid >> 6) / S::kWaves;   // this wave's part of K
@@ -634,7 +643,10 @@ __global__ __launch_bounds__((GemmShape<BM, BN>::kThreads * KG)) __attribute__((
   __shared__ uint32_t qkv_amax[OUT == kQkvAmax ? 3 : 1];   // kQkvAmax: of q, k and v
   if (OUT == kQkvAmax && tid < 3) qkv_amax[tid] = 0u;
   __shared__ float half_head[QKV && kB == 1 ? 2 * 2 * 32 : 1];   // two waves share a head: their sums of squares
-  bool primed = false;   // the previous tile's epilogue has issued this tile's first stages
+  bool primed = false;   // this tile's first stages have been issued by the previous tile('s epilogue)
+  bool stored = false;   // kTurns: the previous tile has ended with at least kStores stores behind its last fetch
+  constexpr int kStores = FP8 && PACKED ? 2 * kB : 4 * kB;
+  const float alpha = alpha_p ? *alpha_p : 1.0f, r = FP8 && PACKED ? __uint_as_float(*out_inv) : 1.0f;
   int parity = 0;
   int tm = 0, tn = 0, tm2 = 0, tn2 = 0;
   for (int v = by_xcd ? (int)blockIdx.x >> 3 : (int)blockIdx.x; v < my_tiles; v += stride, parity ^= 1) {
@@ -644,12 +656,16 @@ __global__ __launch_bounds__((GemmShape<BM, BN>::kThreads * KG)) __attribute__((
   // this tile's bias values wait in LDS behind the ring (read in the epilogue, many barriers
   // later); two buffers in turn, so a wave still in the previous tile's epilogue reads its own
   float *bias_lds = (float *)(rings + (size_t)KG * kStages * kStageU4) + parity * BN;
-  if (tid < BN) bias_lds[tid] = bias ? bias[tn * BN + tid] : 0.f;
+  if (tid < BN) {                            // (whole waves; straight to LDS: nobody waits for it, nor for the stores before it)
+    if (bias) __builtin_amdgcn_global_load_lds(bias + tn * BN + tid, bias_lds + (tid & ~63), 4, 0, 0);
+    else bias_lds[tid] = 0.f;
+  }
 
   // fetch: with 8 waves, waves 0-3 move 4 weight fragments of a stage each, waves 4-7 4 activation
   // fragments; with 4 waves each moves kB weight and 2 activation fragments
   const int f_ks = S::kWaves == 2 ? wave : (wave >> 1) & 1, f_half = S::kWaves == 2 ? 0 : wave & 1;
   int pf_g = 0, f_tm = tm, f_tn = tn;
+  if (kTurns && primed) pf_g = kAhead;
   auto slot_of = [](int g) { return kStages == 4 ? g & 3 : g % kStages; };
   // kQkvPacked: the tiles of V take activations and weights the other way round, so that a lane has one channel of four
   // consecutive tokens per register group
@@ -658,7 +674,12 @@ __global__ __launch_bounds__((GemmShape<BM, BN>::kThreads * KG)) __attribute__((
   const u32x4 *f_src[2];   // this wave's next weight and activation fragments (8 waves: [0] is either)
   u32x4 *f_dst[2];
   auto fetch_begin = [&]() {
-    const int s = pf_g < total ? pf_g : total - 1;   // past the end: the last stage again, into a free slot
+    int s = pf_g < total ? pf_g : total - 1;   // past the end: the last stage again, into a free slot ...
+    if (kTurns && pf_g >= total && more) {     // ... or the next tile's first ones
+      s = pf_g - total;
+      f_tm = tm2;
+      f_tn = tn2;
+    }
     const size_t at = (size_t)((kg * total + s) * 2 + f_ks) * 64;   // uniform: the lane is added in the load
     u32x4 *stage = ring + (size_t)slot_of(pf_g) * kStageU4;
     if constexpr (S::kWaves == 8) {
@@ -694,7 +715,7 @@ __global__ __launch_bounds__((GemmShape<BM, BN>::kThreads * KG)) __attribute__((
   // byte offsets of this wave's fragments inside a stage, k-step 0, and from k-step 0 to k-step 1
   const uint32_t b_off = (uint32_t)((wn * kB) * 1024), a_off = (uint32_t)((2 * S::kFragW + wd * 2) * 1024);
   constexpr uint32_t b_ks = S::kFragW * 1024, a_ks = S::kFragA * 1024;
-  u32x4 fb[kTwoSets ? 2 : 1][2][kB], fa[2][2][2];   // [set][k-step (FP8: unit of 32)][fragment]
+  u32x4 fb[kTwoSets ? 2 : 1][2][kB], fa[kTurns ? 1 : 2][2][2];   // [set][k-step (FP8: unit of 32)][fragment]
   auto read_frags = [&](int g, int ks, u32x4(&b)[kB], u32x4(&a)[2]) {
     const uint32_t base = ring_lane + (uint32_t)(slot_of(g) * kStageU4 * 16);
     if constexpr (kB == 4) lds_read4_async(b, base + b_off + ks * b_ks);
@@ -709,17 +730,19 @@ __global__ __launch_bounds__((GemmShape<BM, BN>::kThreads * KG)) __attribute__((
     for (int b = 0; b < kB; ++b)
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[a][b][r] = 0.f;
-  if (primed) {
-    pf_g = kStages;
+  if (kTurns && primed) {
+    // (landed: the last tile's last stage has waited for stage 0)
+  } else if (primed) {
+    pf_g = kAhead;
     // the stages were issued ahead of the previous epilogue's stores: wait for everything
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   } else {
 #pragma unroll
-    for (int i = 0; i < kStages; ++i) fetch();               // the ring's stages
-    asm volatile("s_waitcnt vmcnt(%0)" ::"n"((kStages - 1) * S::kLoads) : "memory");   // stage 0 has landed (this wave's part)
+    for (int i = 0; i < kAhead; ++i) fetch();                // the ring's stages
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"((kAhead - 1) * S::kLoads) : "memory");   // stage 0 has landed (this wave's part)
   }
-  __builtin_amdgcn_s_barrier();
-  // Steady state: all fragments of a stage are in registers while its MFMAs run, and those of the
+  if (!kTurns || !primed) __builtin_amdgcn_s_barrier();
+  // Steady state of the smaller tiles: all fragments of a stage are in registers while its MFMAs run, and those of the
   // next stage are read meanwhile: into a second set, a whole stage ahead of their use (bf16), or,
   // where the registers do not hold two sets of weight fragments beside the 8-register operands
   // (FP8), the activations into a second set and each weight fragment into its own registers once
@@ -832,6 +855,39 @@ __global__ __launch_bounds__((GemmShape<BM, BN>::kThreads * KG)) __attribute__((
     }
   };
 #undef LV_LD
+  if constexpr (kTurns) {
+    const bool late = wave >= 4;             // this group is one barrier behind the other; level again in the epilogue,
+    if (late) __builtin_amdgcn_s_barrier();  // where both at once hide each other's latencies
+    // A stage: [reads of stage g, fetch of stage g + 3 into the slot of g - 1 | barrier | its MFMAs | barrier].  Both groups
+    // have read stage g - 1 by then: the late one in the turn before.
+    auto turn = [&](int g, auto younger) {
+      __builtin_amdgcn_sched_barrier(0);
+      read_frags(g, 0, fb[0][0], fa[0][0]);
+      read_frags(g, 1, fb[0][1], fa[0][1]);
+      fetch();
+      __builtin_amdgcn_sched_barrier(0);
+      asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * S::kLoads + decltype(younger)::value) : "memory");   // stage g+1 has landed
+      wait_set(fb[0], fa[0]);
+      __builtin_amdgcn_s_barrier();
+      __builtin_amdgcn_sched_barrier(0);
+      __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+      for (int u = 0; u < (FP8 ? 1 : 2); ++u)
+#pragma unroll
+        for (int b = 0; b < kB; ++b) pair(fb[0], fa[0], u, b);
+      __builtin_amdgcn_s_setprio(0);
+      __builtin_amdgcn_sched_barrier(0);
+      __builtin_amdgcn_s_barrier();
+    };
+    int g = 0;
+    if (stored) {                            // the last tile's stores may still be on their way
+      turn(0, std::integral_constant<int, kStores>{});
+      turn(1, std::integral_constant<int, kStores>{});
+      g = 2;
+    }
+    for (; g < total; ++g) turn(g, std::integral_constant<int, 0>{});
+    if (!late) __builtin_amdgcn_s_barrier();
+  } else {
   read_frags(0, 0, fb[0][0], fa[0][0]);
   read_frags(0, 1, fb[0][1], fa[0][1]);
   constexpr int kSetB = kTwoSets ? 1 : 0;   // the weight set of odd stages
@@ -842,8 +898,11 @@ __global__ __launch_bounds__((GemmShape<BM, BN>::kThreads * KG)) __attribute__((
   // the reads issued by the last stage are waited for before their registers die
   wait_set(fb[0], fa[0]);
   wait_set(fb[kSetB], fa[1]);
-  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");   // nothing may land in LDS any more
-  __syncthreads();
+  }
+  if constexpr (!kTurns) {
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");   // nothing may land in LDS any more
+    __syncthreads();
+  }
   // Two K groups trade sums through their rings: group kg finishes row block a = kg, group 0's sum first.
   auto mine = [&](int a) { return KG == 1 || a == kg; };
   if constexpr (KG == 2) {
@@ -879,15 +938,17 @@ __global__ __launch_bounds__((GemmShape<BM, BN>::kThreads * KG)) __attribute__((
   // lanes l and l + 32 trade halves (one v_permlane32_swap per register pair: the first operand's
   // lanes 32-63 against the second operand's lanes 0-31), after which lane l has channels 0-7 and
   // lane l + 32 channels 8-15 of a run of 16, 16 bytes per lane.
-  const float alpha = alpha_p ? *alpha_p : 1.0f;
   int anchor = 0;   // opaque zero: keeps the address arithmetic below inside this tile's epilogue
   asm volatile("" : "+v"(anchor));   // (hoisted out of the tile loop it would stay live through the main loop)
-  if (KG == 1 && more) {
+  if (kTurns) {
+    primed = true;
+    stored = (int64_t)(tm + 1) * BM <= M;
+  } else if (KG == 1 && more) {
     f_tn = tn2;
     f_tm = tm2;
     pf_g = 0;
 #pragma unroll
-    for (int i = 0; i < kStages; ++i) fetch();
+    for (int i = 0; i < kAhead; ++i) fetch();
     primed = true;
   } else {
     primed = false;
@@ -903,7 +964,6 @@ __global__ __launch_bounds__((GemmShape<BM, BN>::kThreads * KG)) __attribute__((
       // bf16 as if it had been stored, then scaled by *out_inv; a lane has one dword of four codes
       // per register group g, lanes l and l + 32 trade groups 2, 3 against groups 0, 1.  The
       // largest |value| of the rows below M goes into *out_amax; the tile's rows beyond M are written as zeros.
-      const float r = __uint_as_float(*out_inv);
       const int KSn = nt_n * (BN / 32);
       u32x4 *op = (u32x4 *)out + ((size_t)(tm * S::kFragA + wd * 2) * KSn + tn * (BN / 32) + wn * kB) * 64 + lane + anchor;
       float m = 0.f;
@@ -1104,6 +1164,7 @@ __global__ __launch_bounds__((GemmShape<BM, BN>::kThreads * KG)) __attribute__((
       }
     }
   }   // tiles
+  if constexpr (kTurns) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // nothing may land in LDS once the workgroup has ended
   if constexpr (FP8 && PACKED) {
     __syncthreads();
     if (tid == 0) raise_max(out_amax, __uint_as_float(wg_amax));
@@ -1180,13 +1241,17 @@ struct LinearOpts {
 
 // Which output tile suits M rows and Nout columns: 256 x 256 (one workgroup per CU), 128 x 256 or
 // 128 x 128 (two), by estimated time in units of a 256 x 256 tile's on one CU (24-36 us at K = 1024).
-// Whole rounds of workgroups cost 1, 1.03 and 0.6 (smaller tiles fetch 1.5 and 2 times as much into
+// Whole rounds of workgroups cost 0.97, 1.03 and 0.6 (smaller tiles fetch 1.5 and 2 times as much into
 // LDS per product); what is left over costs less where every CU gets one at most, and less still
 // where it is the only round.  Fitted to (C = 1024, bf16, us for the layers qkv / out / MLP 1 / MLP 2)
 //   M =    394: 25 24 29 75   19 16 21 50   13 12 15 32        M =  9000: 62 29 100  92   65 30  81  97   62 27  85  92
 //   M =   2200: 28 24 33 77   22 18 32 52   20 12 34 36        M = 15432: 99 36 143 116  100 35 139 119  112 38 159 133
 //   M =   5776: 54 27 66 83   43 19 54 59   42 19 58 56        M = 143232: 890 282 1183 1015  952 311 1242 1172
-// with the three tiles in that order.
+// with the three tiles in that order, and the first one's waves in step.  In turns (k_gemm_bt) it takes, M = 3000, 9000, 15432, 30000:
+//   bf16   29 23 33 72   61 28 95 86   94 35 134 116   175 63 254 222     E4M3   21 16 27 42   39 19 70 50   59 25 96 67   110 40 181 124
+// (128 x 256 in E4M3: 23 14 27 36   42 20 57 56   61 23 96 73   112 44 170 139).  E4M3 through GELU, whose epilogue is half as long as the
+// tile's loop: two workgroups per CU run one's beside the other's loop, so there the whole tile keeps its 1.
+// Over 23 sizes (C = 512, 768, 1024, M = 3,000 to 30,000) the choice is 0.6 % (bf16) and 0.8 % (E4M3) above the best of the three.
 // Where even the 128 x 128 tiles leave CUs idle, what counts is how long one workgroup is at a tile: it
 // gets 16 KB per stage at 150 GB/s and pays the barrier of every stage.  64 x 64 tiles in two K groups halve both, as
 // long as all of them are on the chip at once (two per CU); longer rows (K >= 2048 in bf16) gain from two K groups of 128 x 128
@@ -1197,9 +1262,8 @@ struct LinearOpts {
 // Whole blocks with and without the 64 x 64 tiles, bf16 and E4M3 layers (delayed scaling), us: C = 256, where the output layers take them
 // up to 8,192 rows: M = 394 42.6 and 53.4, 55.9 and 65.3; 2048 55.6 and 64.8, 73.7 and 79.7; 4096 69.7 and 74.9, 87.2 and 92.5;
 // 8192 131.2 and 133.6, E4M3 level.  C = 512: 1000 61.9 and 73.1, 72.8 and 80.8; 4096 112.4 and 114.3, 124.7 and 126.7.
-// The costs below are bf16's; E4M3 layers take the same shapes.
 enum TileShape { kTile256x256, kTile128x256, kTile128x128, kTile128x128K2, kTile64x64K2 };
-static TileShape tile_shape(int64_t M, int Nout, int K, bool fp8, int n_cu) {
+static TileShape tile_shape(int64_t M, int Nout, int K, bool fp8, bool gelu, int n_cu) {
   if ((M + 63) / 64 * (Nout / 64) <= 2 * n_cu) return kTile64x64K2;
   if (!fp8 && K >= 2048 && (M + 127) / 128 * (Nout / 128) <= n_cu) return kTile128x128K2;
   int64_t rest = 0;
@@ -1214,7 +1278,8 @@ static TileShape tile_shape(int64_t M, int Nout, int K, bool fp8, int n_cu) {
     return per / s;
   };
   const int64_t r256 = rounds(256, 256, n_cu);
-  const double t256 = (double)r256 + (rest ? 1.0 : 0.0);
+  const double round256 = fp8 && gelu ? 1.0 : 0.97, only256 = fp8 && gelu ? 1.0 : 0.85;
+  const double t256 = round256 * (double)r256 + (rest == 0 ? 0.0 : r256 ? round256 : only256);
   const int64_t r128 = rounds(128, 256, 2 * n_cu);
   const double t128 = 1.03 * (double)r128 + (rest == 0 ? 0.0 : rest > n_cu ? 1.03 : r128 ? 0.55 : 0.72);
   const int64_t r64 = rounds(128, 128, 2 * n_cu);
@@ -1238,7 +1303,7 @@ static int launch_linear(const uint16_t *A, int64_t M, int K, int Nout,
   if (hipGetDevice(&dev) != hipSuccess ||
       hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n_cu < 1)
     return LV_ERR_HIP;
-  const TileShape shape = tile_shape(M, Nout, K, o.fp8, n_cu);
+  const TileShape shape = tile_shape(M, Nout, K, o.fp8, gelu != 0, n_cu);
   QkvOut qkv;
   if (o.kv) qkv = QkvOut{(u32x4 *)o.kv->kp, (u32x4 *)o.kv->vp, o.kv->amax, o.kv->n_kt, o.kv->qk_norm};
   auto gemm = [&](auto fp8, auto kind, auto bm, auto bn, auto kg, const u32x4 *act, int KS, const float *alpha) -> int {

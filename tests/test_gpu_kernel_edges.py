@@ -313,8 +313,8 @@ def test_block_layernorm_cancels_opposite_lanes_first(B, dim):
 
 
 # the first MLP layer on 256 x 256 tiles with its output in operand order, more tiles than CUs (8 x 61, 12 x 35)
-# and a ragged last row tile
-@pytest.mark.parametrize("m,dim", [(15400, 512), (8900, 768)])
+# and a ragged last row tile; tiles of four stages, the ring's fewest, that follow each other (98 x 4)
+@pytest.mark.parametrize("m,dim", [(15400, 512), (8900, 768), (25001, 256)])
 @pytest.mark.parametrize("linear", ["bf16", "fp8-delayed"])
 def test_block_largest_tiles(B, m, dim, linear):
     import torch
