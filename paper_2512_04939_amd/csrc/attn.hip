@@ -1472,10 +1472,16 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 // attn_is_short says where it is used.
 // ---------------------------------------------------------------------------------------
 constexpr int kShortWaves = 4;   // (sum4 below)
-template <bool ONLINE, bool PACKED>
+// ROWS: K and V are not re-laid out before.  A wave normalises the keys of its tiles itself, as k_attn_pack does, and V's rows pass
+// through its own 4 KB of LDS per tile, read transposed; both are asked for two tiles ahead.  That takes a launch away and
+// pays with every block's own normalisation of all keys, so it is for few blocks per sequence, with the re-layout and without, us:
+// 394 tokens of 16 heads 11.8 and 9.7, 700 12.9 and 11.9, 800 of 8 heads 12.1 and 12.3, 1,500 of 16 23.3 and 25.9; 25 frames of 15 x 17, 4
+// heads, 21.1 and 13.0, 6 of 16 x 16, 16 heads, 16.4 and 13.0, 2 of 37 x 37, 8 heads, 22.7 and 25.0.
+constexpr int kRowsBlocks = 12;  // 64-query blocks of a sequence, at most
+template <bool ONLINE, bool PACKED, bool ROWS>
 __global__ __launch_bounds__(64 * kShortWaves) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_attn_bf16_short(
-    const uint16_t *q, const u32x4 *__restrict__ kp, const u32x4 *__restrict__ vp, uint16_t *o,
-    const uint16_t *res, int64_t n, int heads, int n_seq, int n_kt, int nqs, float c, int qk_norm,
+    const uint16_t *q, const u32x4 *__restrict__ kp, const u32x4 *__restrict__ vp, const uint16_t *krows, const uint16_t *vrows,
+    uint16_t *o, const uint16_t *res, int64_t n, int heads, int n_seq, int n_kt, int nqs, float c, int qk_norm,
     uint32_t *__restrict__ redo, int redo_stride) {
   constexpr int WAVES = kShortWaves, R = 64 / WAVES;   // of a lane's 64 output registers (query block, channels 32 dt .., row) a
                                              // wave adds up and stores R
@@ -1512,6 +1518,60 @@ __global__ __launch_bounds__(64 * kShortWaves) __attribute__((amdgpu_waves_per_e
     const u32x4 *p = from + (size_t)min(t, t1 - 1) * 4 * kFragU4;
 #pragma unroll
     for (int f = 0; f < 4; ++f) dst[f] = p[f * kFragU4];
+  };
+  // ROWS: a lane's 64 bytes of its key's row; V's 32 rows into one of three places in what will hold this wave's sums, in
+  // k_attn_bf16_stream's order there (rows beyond the sequence as zeros)
+  const uint16_t *const krow = ROWS ? krows + (size_t)seq * n * C + head * 64 + 8 * h : nullptr;
+  auto load_k = [&](int t, u32x4(&dst)[4]) {
+    if constexpr (ROWS) {
+      const uint16_t *p = krow + (size_t)min((int64_t)min(t, t1 - 1) * kKT + ql, n - 1) * C;
+#pragma unroll
+      for (int f = 0; f < 4; ++f) dst[f] = *(const u32x4 *)(p + 16 * f);
+    } else {
+      load(kh, t, dst);
+    }
+  };
+  __amdgpu_buffer_rsrc_t vb;
+  if constexpr (ROWS)
+    vb = __builtin_amdgcn_make_buffer_rsrc((void *)(vrows + (size_t)seq * n * C + head * 64), 0, (int)((n - 1) * C * 2 + 128), 0x00020000);
+  const int v_off = ROWS ? (lane >> 3) * C * 2 + ((lane & 7) ^ (lane >> 4 & 1) * 4) * 16 : 0;
+  auto fetch_v = [&](int t) {              // (ahead of the same tile of K: once that is there, so is this)
+    if (t < t1)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(vb, (u32x4 *)part[wave] + (t % 3) * 256 + i * 64, 16, v_off, (4 * t + i) * 16 * C, 0, 0);
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("" ::: "memory");
+  };
+  const uint32_t v_lane = ROWS ? lds_addr(&part[wave]) + (4 * h + (lane >> 2 & 3)) * 128 + (lane >> 3 & 1) * 64 + (lane >> 4 & 1) * 32 +
+                                     (lane & 3) * 8
+                               : 0u;
+  u32x2 vt[8];
+  auto read_v = [&](int t) {
+    __builtin_amdgcn_sched_barrier(0);
+    lds_read_vt_async(vt, v_lane + (t % 3) * 4096);
+  };
+  auto wait_v = [&](u32x4(&v)[4]) {
+    asm volatile("s_waitcnt lgkmcnt(0)"
+                 : "+v"(vt[0]), "+v"(vt[1]), "+v"(vt[2]), "+v"(vt[3]), "+v"(vt[4]), "+v"(vt[5]), "+v"(vt[6]), "+v"(vt[7])
+                 :
+                 : "memory");
+#pragma unroll
+    for (int f = 0; f < 4; ++f) v[f] = u32x4{vt[2 * f].x, vt[2 * f].y, vt[2 * f + 1].x, vt[2 * f + 1].y};
+  };
+  auto norm_k = [&](u32x4(&k)[4]) {        // k_attn_pack's values: chunks of 8 channels, added in pairs
+    if constexpr (ROWS) {
+      float pair_sum[4];
+#pragma unroll
+      for (int f = 0; f < 4; ++f) {
+        const float cs = sumsq8(k[f]);
+        const auto x = __builtin_amdgcn_permlane32_swap(__float_as_uint(cs), __float_as_uint(cs), false, false);
+        pair_sum[f] = __uint_as_float(x[0]) + __uint_as_float(x[1]);
+      }
+      const float r = 1.0f / sqrtf(((pair_sum[0] + pair_sum[1]) + (pair_sum[2] + pair_sum[3])) * (1.0f / 64.0f) + kQkEps);
+#pragma unroll
+      for (int f = 0; f < 4; ++f) k[f] = scale8(k[f], r);
+    }
   };
   u32x4 fv[2][4], fk[2][4];            // [tile & 1]
   bf16x8 qf[2][4];
@@ -1600,23 +1660,31 @@ __global__ __launch_bounds__(64 * kShortWaves) __attribute__((amdgpu_waves_per_e
   };
 
   if (t0 < t1) {
-    load(kh, t0, fk[0]);
-    load(vh, t0, fv[0]);
-    load(kh, t0 + 1, fk[1]);
+    if constexpr (ROWS) fetch_v(t0);
+    load_k(t0, fk[0]);
+    if constexpr (ROWS) fetch_v(t0 + 1);
+    else load(vh, t0, fv[0]);
+    load_k(t0 + 1, fk[1]);
+    __builtin_amdgcn_sched_barrier(0);
+    u32x4 qw[2][4];
+#pragma unroll
+    for (int sub = 0; sub < 2; ++sub) {
+      const int64_t row = min(q0 + sub * 32 + ql, n - 1);
+      const uint16_t *qp = q + (size_t)row * C + head * 64 + 8 * h;
+#pragma unroll
+      for (int s = 0; s < 4; ++s) qw[sub][s] = *(const u32x4 *)(qp + 16 * s);
+    }
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int sub = 0; sub < 2; ++sub) {      // q as in the main kernel
-      const int64_t row = min(q0 + sub * 32 + ql, n - 1);
-      const uint16_t *qp = q + (size_t)row * C + head * 64 + 8 * h;
-      u32x4 w[4];
-#pragma unroll
-      for (int s = 0; s < 4; ++s) w[s] = *(const u32x4 *)(qp + 16 * s);
+      const u32x4(&w)[4] = qw[sub];
       float ss = (sumsq8(w[0]) + sumsq8(w[1])) + (sumsq8(w[2]) + sumsq8(w[3]));
       ss += __shfl_xor(ss, 32, 64);
       const float r = qk_norm ? c / sqrtf(ss * (1.0f / 64.0f) + kQkEps) : c;
 #pragma unroll
       for (int s = 0; s < 4; ++s) qf[sub][s] = __builtin_bit_cast(bf16x8, scale8(w[s], r));
     }
+    norm_k(fk[0]);
     mma_s(0, fk[0]);
     mma_s(1, fk[0]);
     mask_tail(t0, 0);
@@ -1641,11 +1709,18 @@ __global__ __launch_bounds__(64 * kShortWaves) __attribute__((amdgpu_waves_per_e
     // tile t + 1 || PV(t) and scores(t + 1) of block 1.  V(t + 1) and K(t + 2) are requested ahead of both.
     auto tile = [&](int t, u32x4(&v)[4], u32x4(&v2)[4], u32x4(&k1)[4], u32x4(&k2)[4]) {
       __builtin_amdgcn_sched_barrier(0);
-      load(vh, t + 1, v2);
-      load(kh, t + 2, k2);
+      if constexpr (ROWS) {
+        read_v(t);                             // (K(t) has been used)
+        fetch_v(t + 2);
+      } else {
+        load(vh, t + 1, v2);
+      }
+      load_k(t + 2, k2);
       __builtin_amdgcn_sched_barrier(0);
       weights(1);
+      if constexpr (ROWS) wait_v(v);
       mma_pv(0, v);
+      norm_k(k1);
       mma_s(0, k1);
       mask_tail(t + 1, 0);
       settle(1);
@@ -1662,10 +1737,13 @@ __global__ __launch_bounds__(64 * kShortWaves) __attribute__((amdgpu_waves_per_e
     }
     if (t + 1 < t1) {
       tile(t, fv[0], fv[1], fk[1], fk[0]);
+      ++t;
 #pragma unroll
       for (int f = 0; f < 4; ++f) fv[0][f] = fv[1][f];
     }
+    if constexpr (ROWS) read_v(t);
     weights(1);                              // the last tile
+    if constexpr (ROWS) wait_v(fv[0]);
     mma_pv(0, fv[0]);
     settle(1);
     mma_pv(1, fv[0]);
@@ -2718,11 +2796,13 @@ int launch_attn(const uint16_t *q, const uint16_t *k, const uint16_t *v, uint16_
   u32x4 *kp = (u32x4 *)a.frag, *vp = (u32x4 *)(a.frag + a.per);
   uint32_t *const sync = a.sync, *const ctr = a.head;
   float *const partial = a.partial;
-  // V as it lies: not where a block's output may take the place of rows that another one still reads
+  // K and V as they lie: not where a block's output may take the place of rows that another one still reads
   const size_t bytes = (size_t)n_seq * n * heads * 128;
   const bool kv_ready = ready && ready->kp;
-  const bool vrows = stream && n_kt / 2 <= kVRowsStages && !kv_ready && !(operand && !operand->inv) && n * heads * 128 < ((int64_t)1 << 31) &&
-                     ((uintptr_t)o >= (uintptr_t)v + bytes || (uintptr_t)v >= (uintptr_t)o + bytes);
+  const auto apart = [&](const void *x) { return (uintptr_t)o >= (uintptr_t)x + bytes || (uintptr_t)x >= (uintptr_t)o + bytes; };
+  const bool as_is = !kv_ready && !(operand && !operand->inv) && n * heads * 128 < ((int64_t)1 << 31) && apart(v);
+  const bool vrows = stream && n_kt / 2 <= kVRowsStages && as_is;
+  const bool rows = is_short && bounded && as_is && apart(k) && nqs <= kRowsBlocks;
   auto pack_kernel = [&](auto has_sync) {
     constexpr bool SYNC = decltype(has_sync)::value;
     uint32_t *const cleared = stream ? ctr : sync;
@@ -2738,7 +2818,7 @@ int launch_attn(const uint16_t *q, const uint16_t *k, const uint16_t *v, uint16_
       hipLaunchKernelGGL((k_attn_pack<SYNC, true, true>), grid, dim3(256), 0, st, k, v, n, heads, n_kt, qk_norm, kp, vp, cleared,
                          n_cleared, redo, 2 * nqb);
   };
-  if (kv_ready) {}          // the layer that produced k and v has packed them, and what they clear is cleared
+  if (kv_ready || rows) {}  // the layer that produced k and v has packed them, and what they clear is cleared
   else if (cut.n_cut || stream) pack_kernel(std::true_type{});
   else pack_kernel(std::false_type{});
   if (after_pack && hipEventRecord(after_pack, st) != hipSuccess) return LV_ERR_HIP;
@@ -2747,8 +2827,9 @@ int launch_attn(const uint16_t *q, const uint16_t *k, const uint16_t *v, uint16_
     uint32_t *const flags = ON ? redo : nullptr;
     const int stride = ON ? 2 * nqb : 0;
     if (is_short)
-      hipLaunchKernelGGL((k_attn_bf16_short<ON, PK>), dim3((unsigned)(nqs * heads * n_seq)), dim3(256), 0, st, q, kp, vp, out,
-                         res, n, heads, n_seq, n_kt, nqs, c, qk_norm, flags, stride);
+      hipLaunchKernelGGL((rows ? k_attn_bf16_short<false, false, true> : k_attn_bf16_short<ON, PK, false>),
+                         dim3((unsigned)(nqs * heads * n_seq)), dim3(256), 0, st, q, kp, vp, k, v, out, res, n, heads, n_seq, n_kt,
+                         nqs, c, qk_norm, flags, stride);
     else if (!ON && stream)
       hipLaunchKernelGGL((vrows ? res ? k_attn_bf16_stream<false, true, true> : k_attn_bf16_stream<false, false, true>
                                 : res ? k_attn_bf16_stream<PK, !PK, false> : k_attn_bf16_stream<PK, false, false>),

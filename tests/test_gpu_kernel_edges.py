@@ -735,6 +735,33 @@ def test_attention_short_blocks_left_to_the_second_pass(B, n, heads):
     assert float((q.double() - ref).abs().max() / ref.abs().max()) <= 2e-2
 
 
+# K and V read from their rows (up to 768 tokens) and from their re-layout (the output takes V's place): the same bits; fewer
+# keys than waves have tiles for, ragged tiles, waves with one to six tiles, the longest sequence and one token more, an
+# infinite value of the last key, whose neighbours beyond the end count as zeros
+@pytest.mark.parametrize("n,heads", [(1, 1), (31, 2), (32, 1), (33, 3), (64, 1), (65, 8), (127, 4), (129, 2), (257, 3), (394, 16),
+                                     (511, 8), (640, 4), (767, 8), (768, 16), (769, 8)])
+def test_attention_short_rows_equal_relaid(B, n, heads):
+    import torch
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n)
+    q, k, v = (torch.randn(n, heads * 64, generator=g, device="cuda").to(torch.bfloat16) for _ in range(3))
+    v[-1, 5] = float("inf")
+    ph = B.make_params(1, 1, 1, heads * 64, heads, n_special=0, qk_norm=1)
+    ws = B.alloc_ws(B.litevggt_attn_ws_bytes(ph, n))
+    o = torch.full_like(q, float("nan"))
+    B.litevggt_global_attn(ph, n, q, k, v, o, ws)
+    relaid = v.clone()
+    B.litevggt_global_attn(ph, n, q, k, relaid, relaid, ws)
+    torch.cuda.synchronize()
+    assert torch.equal(o.view(torch.int16), relaid.view(torch.int16))
+    fine = torch.ones(heads * 64, dtype=torch.bool, device="cuda")
+    fine[5] = False
+    v[-1, 5] = 0.0
+    ref = _attn64(q, k, v, True, heads)
+    assert bool(torch.isinf(o[:, 5]).all())
+    assert float((o.double() - ref)[:, fine].abs().max() / ref.abs().max()) <= 2e-2
+
+
 # frames of a few hundred tokens with the residual added in place, in 64-query blocks and one frame beyond
 @pytest.mark.parametrize("frames,h,w,heads,norm", [(2, 16, 16, 4, 1), (25, 15, 17, 4, 1), (26, 15, 17, 4, 1), (2, 37, 37, 8, 1),
                                                    (2, 5, 5, 1, 0)])
