@@ -185,6 +185,9 @@ __device__ __forceinline__ float ln_packed_tile(const uint16_t *__restrict__ x, 
   return 0.f;
 }
 
+// what 32 rows take in LDS
+static size_t ln_packed_lds(int C, bool fp8) { return fp8 ? (size_t)32 * (C / 8 + 2) * 8 : (size_t)32 * (C / 8 + 1) * 16; }
+
 template <int CPL, bool FP8>
 __global__ __launch_bounds__(64 * kLnWaves) void k_layernorm_packed(const uint16_t *__restrict__ x,
                                                           const uint16_t *__restrict__ add,
@@ -209,7 +212,7 @@ static int launch_layernorm(const uint16_t *x, const uint16_t *add, const float 
   if (C % 32 != 0 || cpl > 4) return LV_ERR_SHAPE;
   if (packed) {
     if (Mp % 32 != 0 || Mp < M || !fp8_inv != !fp8_amax) return LV_ERR_SHAPE;
-    const size_t lds = (size_t)32 * (C / 8 + 1) * 16;   // the FP8 rows (C + 16 bytes) fit as well
+    const size_t lds = ln_packed_lds(C, fp8_inv != nullptr);
     static std::atomic<uint64_t> lds_done[8];
     const unsigned grid = (unsigned)(Mp / 32);
     int rc;
@@ -462,12 +465,12 @@ static int launch_block_head(const uint16_t *z, const float *gamma, const float 
   const int n_pack = bw ? C / 32 * (8 * ((C + per - 1) / per) + (4 * C + per - 1) / per) : 0;
   const unsigned grid = (unsigned)(n_ln + n_pack + 1);
   const ClearWords cw = {{kv.clear[0], kv.clear[1]}, {kv.n_clear[0], kv.n_clear[1]}};
-  const size_t lds = packed ? (size_t)32 * (C / 8 + 1) * 16 : 0;
+  const size_t lds = packed ? ln_packed_lds(C, fp8) : 0;
   static std::atomic<uint64_t> lds_done[8];
   const BlockWeights4 w4 = bw ? *bw : BlockWeights4{};
   int rc;
 #define LV_HEAD(CPL, F8)                                                                                       \
-  if ((rc = allow_dynamic_lds((const void *)k_block_head<CPL, F8>, (size_t)32 * (C / 8 + 1) * 16, lds_done[(CPL - 1) * 2 + F8]))) \
+  if ((rc = allow_dynamic_lds((const void *)k_block_head<CPL, F8>, ln_packed_lds(C, F8), lds_done[(CPL - 1) * 2 + F8]))) \
     return rc;                                                                                                 \
   hipLaunchKernelGGL((k_block_head<CPL, F8>), dim3(grid), dim3(64 * kLnWaves), lds, st, z, gamma, beta, M, C, n_ln, packed, w4, n_pack, hd, cw)
 #define LV_HEADS(F8)                   \
