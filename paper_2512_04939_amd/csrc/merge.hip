@@ -90,10 +90,13 @@ __device__ __forceinline__ void sum_rows(const uint16_t *__restrict__ x,
 // row that a lane holds, 64 CPL pieces in all from x on.  The
 // loads of a batch are issued ahead of the stores of the batch before it: loads and stores of a wave are
 // waited for in the order of their issue, so behind them they would wait for the stores as well.
-// Few rows per batch: the two batches' registers decide how many waves a SIMD holds (with four rows of C = 1024
-// four; 32 frames of 37 x 37
-// patches, C = 1024, R = 8: 57 us, 4: 46, 2: 47; 200 frames 290, 254, 270; without the loads ahead 61 us).
-constexpr int kAddRows = 4, kAddRowsCoop = 16;
+// The two batches' registers decide how many waves a SIMD holds (four with 4 KB in flight each).  A wave has 512 channels of
+// eight rows there rather than whole rows of 1024, four of them: twice the waves, half as long each, where a wave's time
+// is that of its slot's batches one after the other (32 frames of 37 x 37 have 5,776 slots of 1 to 95 members).  C = 1024, whole rows
+// and halves, us: 8 frames 22.4 and 16.5, 32 46.4 and 39.1, 100 132 and 124, 200 254 and 244, 24 of 28 x 37 at ratio 0.5 32.4
+// and 27.9; C = 768, 48 of 37 x 37 at 0.75 55.4 and 48.9.  (256 channels of 8, 12 or 16 rows: 38 to 39 for the 32 frames, 36 to 52
+// at ratio 0.5; four rows of 512 channels 40.6.)  Up to 512 channels four rows: 16 frames of 16 x 16, C = 256, 5.3, with eight 6.1.
+constexpr int kAddRows = 8, kAddRowsFew = 4, kAddRowsCoop = 16;
 template <typename V, int CPL, int R>
 __device__ __forceinline__ void add_sum_rows(uint16_t *x, const V (&y)[CPL], const int32_t *__restrict__ group_mem,
                                              int lo, int hi, int C, int nch, int lane, float (&a)[CPL][sizeof(V) / 2]) {
@@ -168,8 +171,7 @@ __device__ __forceinline__ void store_mean(uint16_t *__restrict__ z, int m, int 
 // the same groups: row i of slot m becomes x[i] + y[m] (the sum that k_unmerge stores, bit for bit) and
 // enters the mean of its slot as it is stored.  Bound by HBM like its two halves, which read x twice and
 // gather y per token; C = 1024, 37 x 37 patches, both halves -> together: 32 frames at ratio 0.9
-// 56 -> 46 us (4.4 TB/s), 200 frames 358 -> 254 (5.0 TB/s), 48 frames at ratio 0.5 100 -> 74; two frames
-// of 16 x 16, C = 256 7.2 -> 3.9.
+// 56 -> 39 us (5.2 TB/s), 200 frames 358 -> 244 (5.2 TB/s); two frames of 16 x 16, C = 256 7.2 -> 3.9.
 // Its large groups are bound by the rows that a workgroup has in flight, a quarter of merge's where a wave holds two
 // batches of four whole rows.  So a workgroup takes a slice of the channels (128 up to 512 channels, else 256) of
 // 16 rows per batch and wave, in the same registers, and there are at least 512 of them, or as many as make sets of 8 slots
@@ -238,7 +240,21 @@ __global__ __launch_bounds__(256) void k_merge(typename MergeX<ADD>::type x, con
     }
     return;
   }
-  const int m = ((int)blockIdx.x - nb0 * slices) * 4 + wave;   // own slot, if small
+  const int own = ((int)blockIdx.x - nb0 * slices) * 4 + wave;   // own slot, if small; ADD: 512 channels of it
+  if constexpr (ADD) {
+    const int m = own / CPL, ch0 = (own - m * CPL) * 512, pieces = (C - ch0) >> 3;
+    if (m < M) {
+      const int b = group_off[m], e = group_off[m + 1];
+      if (e - b <= kCoopSize) {
+        float a[1][8] = {{0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f}};
+        const u32x4 ym[1] = {lane < pieces ? ((const u32x4 *)(y + (size_t)m * C + ch0))[lane] : u32x4{0u, 0u, 0u, 0u}};
+        add_sum_rows<u32x4, 1, CPL == 1 ? kAddRowsFew : kAddRows>(x + ch0, ym, group_mem, b, e, C, pieces, lane, a);
+        store_mean(z + ch0, m, C, pieces, lane, a, 1.0f / (float)(e - b));
+      }
+    }
+    return;
+  }
+  const int m = own;
   if (m < M) {
     const int b = group_off[m], e = group_off[m + 1];
     if (e - b <= kCoopSize) {
@@ -247,15 +263,7 @@ __global__ __launch_bounds__(256) void k_merge(typename MergeX<ADD>::type x, con
       for (int c = 0; c < CPL; ++c)
 #pragma unroll
         for (int i = 0; i < 8; ++i) a[c][i] = 0.f;
-      if constexpr (ADD) {
-        u32x4 ym[CPL];
-#pragma unroll
-        for (int c = 0; c < CPL; ++c)
-          ym[c] = lane + 64 * c < nch ? ((const u32x4 *)(y + (size_t)m * C))[lane + 64 * c] : u32x4{0u, 0u, 0u, 0u};
-        add_sum_rows<u32x4, CPL, kAddRows>(x, ym, group_mem, b, e, C, nch, lane, a);
-      } else {
-        sum_rows<CPL, 8>(x, group_mem, b, e, C, nch, lane, a);
-      }
+      sum_rows<CPL, 8>(x, group_mem, b, e, C, nch, lane, a);
       store_mean(z, m, C, nch, lane, a, 1.0f / (float)(e - b));
     }
   }
@@ -268,7 +276,8 @@ static int merge_rows(typename MergeX<ADD>::type x, const uint16_t *y, const Dim
   int64_t nb0 = (M + kScan - 1) / kScan;
   const int slice = cpl == 1 ? 128 : 256, slices = ADD ? (d.C + slice - 1) / slice : 1;   // kSlice
   if (ADD) nb0 = std::max(nb0, std::min<int64_t>(512 / slices, (M + 7) / 8));
-  const unsigned grid = (unsigned)(nb0 * slices + (M + 3) / 4);
+  const int parts = ADD ? cpl : 1;            // waves of a small slot
+  const unsigned grid = (unsigned)(nb0 * slices + (M * parts + 3) / 4);
 #define LV_MERGE(CPL)                                                                                     \
   hipLaunchKernelGGL((k_merge<CPL, ADD>), dim3(grid), dim3(256), 0, st, x, y, ix.group_off, ix.group_mem, \
                      (int)M, d.C, (int)nb0, z)
