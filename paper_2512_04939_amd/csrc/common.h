@@ -70,6 +70,30 @@ __device__ __forceinline__ float wave_sum_ordered(float v) {
   v += dpp_take<0xB1, 0xF>(v);    // quad_perm [1,0,3,2]
   return v;
 }
+// the same for doubles, whose halves travel side by side
+template <int kCtrl>
+__device__ __forceinline__ double dpp_take(double v) {
+  const uint64_t b = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)b, kCtrl, 0xF, 0xF, false);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(b >> 32), kCtrl, 0xF, 0xF, false);
+  return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
+}
+__device__ __forceinline__ double wave_sum_ordered(double v) {
+  auto join = [](uint32_t lo, uint32_t hi) { return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo); };
+  uint64_t b = __builtin_bit_cast(uint64_t, v);
+  const auto l32 = __builtin_amdgcn_permlane32_swap((uint32_t)b, (uint32_t)b, false, false);
+  const auto h32 = __builtin_amdgcn_permlane32_swap((uint32_t)(b >> 32), (uint32_t)(b >> 32), false, false);
+  v = join(l32[0], h32[0]) + join(l32[1], h32[1]);
+  b = __builtin_bit_cast(uint64_t, v);
+  const auto l16 = __builtin_amdgcn_permlane16_swap((uint32_t)b, (uint32_t)b, false, false);
+  const auto h16 = __builtin_amdgcn_permlane16_swap((uint32_t)(b >> 32), (uint32_t)(b >> 32), false, false);
+  v = join(l16[0], h16[0]) + join(l16[1], h16[1]);
+  v += dpp_take<0x128>(v);   // row_ror:8
+  v += dpp_take<0x124>(v);   // row_ror:4
+  v += dpp_take<0x4E>(v);    // quad_perm [2,3,0,1]
+  v += dpp_take<0xB1>(v);    // quad_perm [1,0,3,2]
+  return v;
+}
 __device__ __forceinline__ float wave_max(float v) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));

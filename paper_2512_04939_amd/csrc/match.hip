@@ -602,6 +602,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
 // 8 rows and no more, because in late refreshes most rows are near-equal and want many waves.
 constexpr int kFinRows = 8;
 
+// A row that goes to 64 bits is a chain of round trips, and a wave with a few of them is what the launch waits for: two candidates
+// and the src row itself are read at once, and their five sums cross the lanes side by side by DPP (one after the other,
+// by LDS shuffles: refreshes of 5 frames of 16 x 16, C = 1024, 38.1 -> 36.0 us, 12 of 37 x 37 154.4 -> 152.0, 32 435.5 ->
+// 433.3; the same bits).
 __global__ __launch_bounds__(256) void k_match_finish(
     const uint16_t *__restrict__ x, const int32_t *__restrict__ src_idx,
     const int32_t *__restrict__ dst_idx, const float *__restrict__ inv_src,
@@ -646,47 +650,53 @@ __global__ __launch_bounds__(256) void k_match_finish(
     if (lane < n_lists) o = part[lane * stride + rp];
     uint64_t c1 = __builtin_amdgcn_ballot_w64(o.i1 >= 0 && (v1 - o.v1) * is32 < kRescoreGap);
     uint64_t c2 = __builtin_amdgcn_ballot_w64(o.i2 >= 0 && (v1 - o.v2) * is32 < kRescoreGap);
-    double ss = 0;
-    for (int ch = lane; ch < nch; ch += 64) {
-      const u32x4 w = ((const u32x4 *)(x + (size_t)rs * C))[ch];
-      const uint32_t us[4] = {w.x, w.y, w.z, w.w};
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const double sl = bf16_lo(us[q]), sh = bf16_hi(us[q]);
-        ss += sl * sl + sh * sh;
-      }
-    }
-    ss = wave_sum(ss);
-    const double is = 1.0 / fmax(sqrt(ss), 1e-12);
     float bs = -INFINITY;
     int bd = 0x7fffffff, bi = 0;
-    while (c1 | c2) {                          // the candidates inside the gap (never none: the best is one)
+    auto take = [&]() {                        // the next candidate inside the gap
       const bool first = c1 != 0;
       const int l = __builtin_ctzll(first ? c1 : c2);
       if (first) c1 &= c1 - 1;
       else c2 &= c2 - 1;
-      const int ci = first ? __builtin_amdgcn_readlane(o.i1, l) : __builtin_amdgcn_readlane(o.i2, l);
-      const int d = dst_idx[ci];
-      double nn = 0, pp = 0;
+      return first ? __builtin_amdgcn_readlane(o.i1, l) : __builtin_amdgcn_readlane(o.i2, l);
+    };
+    while (c1 | c2) {                          // two at a time (never none: the best is one; an odd last one twice)
+      int ci[2];
+      ci[0] = take();
+      ci[1] = c1 | c2 ? take() : ci[0];
+      const int d[2] = {dst_idx[ci[0]], dst_idx[ci[1]]};
+      double ss = 0, nn[2] = {0, 0}, pp[2] = {0, 0};
       for (int ch = lane; ch < nch; ch += 64) {
-        const u32x4 wd = ((const u32x4 *)(x + (size_t)d * C))[ch];
-        const u32x4 w = ((const u32x4 *)(x + (size_t)rs * C))[ch];   // the src row again: a cache hit
-        const uint32_t us[4] = {w.x, w.y, w.z, w.w}, ud[4] = {wd.x, wd.y, wd.z, wd.w};
+        const u32x4 w = ((const u32x4 *)(x + (size_t)rs * C))[ch];
+        const u32x4 wd[2] = {((const u32x4 *)(x + (size_t)d[0] * C))[ch], ((const u32x4 *)(x + (size_t)d[1] * C))[ch]};
+        const uint32_t us[4] = {w.x, w.y, w.z, w.w};
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
           const double sl = bf16_lo(us[q]), sh = bf16_hi(us[q]);
-          const double al = bf16_lo(ud[q]), ah = bf16_hi(ud[q]);
-          nn += al * al + ah * ah;
-          pp += sl * al + sh * ah;
+          ss += sl * sl + sh * sh;
+#pragma unroll
+          for (int k = 0; k < 2; ++k) {
+            const uint32_t ud = q == 0 ? wd[k].x : q == 1 ? wd[k].y : q == 2 ? wd[k].z : wd[k].w;
+            const double al = bf16_lo(ud), ah = bf16_hi(ud);
+            nn[k] += al * al + ah * ah;
+            pp[k] += sl * al + sh * ah;
+          }
         }
       }
-      nn = wave_sum(nn);
-      pp = wave_sum(pp);
-      const float sc = (float)(pp * is * (1.0 / fmax(sqrt(nn), 1e-12)));
-      if (sc > bs || (sc == bs && d < bd)) {
-        bs = sc;
-        bd = d;
-        bi = ci;
+      ss = wave_sum_ordered(ss);
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        nn[k] = wave_sum_ordered(nn[k]);
+        pp[k] = wave_sum_ordered(pp[k]);
+      }
+      const double is = 1.0 / fmax(sqrt(ss), 1e-12);
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        const float sc = (float)(pp[k] * is * (1.0 / fmax(sqrt(nn[k]), 1e-12)));
+        if (sc > bs || (sc == bs && d[k] < bd)) {
+          bs = sc;
+          bd = d[k];
+          bi = ci[k];
+        }
       }
     }
     if (lane == r && bd != 0x7fffffff) {       // (NaN similarities leave the fp32 choice)
