@@ -883,8 +883,10 @@ __global__ __launch_bounds__(256) void k_radix_scatter(const uint32_t *__restric
 // the places where its elements come to lie, and the second one finds the groups' starts as the lowest
 // place of each slot; both by integer atomics, whose order leaves no trace.
 // One refresh call, seven launches -> three: 12 frames of 37 x 37 patches 94.7 -> 90.5 us, 64 of 16 x 16
-// 79.5 -> 73.7, 100 of 28 x 37 (13,056 counters) 1226.0 -> 1221.3; with 32,768 counters 1419 -> 1424.
-constexpr int kMoveCounters = 16384;   // chunks x digits, at most
+// 79.5 -> 73.7, 100 of 28 x 37 (13,056 counters) 1226.0 -> 1221.3; above 16,384 counters, 100 of 28 x 37 under the fixed rule
+// 3308 -> 3290, C = 256 at ratio 0.5 952 -> 937, 52 of 37 x 37, C = 256 369 -> 361, 200 of 28 x 37, C = 512 (52,480) 2853 -> 2813, 200 of
+// 37 x 37 (68,864) level: what every workgroup reads grows with the tokens' square.
+constexpr int kMoveCounters = 65536;   // chunks x digits, at most
 
 // Counts the first pass' digits, clears the second pass' counters, and sets group_off to no place yet.
 __global__ __launch_bounds__(256) void k_radix_first(const uint32_t *__restrict__ keys, int N, int M, int bits,
