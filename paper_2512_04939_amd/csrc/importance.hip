@@ -272,8 +272,8 @@ constexpr int kSeg = LV_VAR_SEG;
 constexpr int kVarWaves = 2;                   // waves per workgroup: 512 channels each, 8 per lane
 
 // STRIPS (SEG only): strips of the workgroup, `block` STRIPS + 0, 1, ..., two waves each; they walk one number of rows.
-// wave_sum_uniform of four values, the same additions: sums inside the rows of 16 lanes, then rows change places so that one
-// addition serves two values, and four.  Value q ends up in all lanes of row q.  (One after the other each value's six steps
+// Sums of four values over the 64 lanes, with DPP moves and permlane swaps only: butterflies inside the rows of 16 lanes, then rows
+// change places so that one addition serves two values, and four.  Value q ends up in all lanes of row q.  (One after the other each value's six steps
 // waited for one another, 42 idle slots in two grid rows, and a move or a lane read each: importance of 32 frames of
 // 37 x 37, C = 1024, 57.1 -> 54.1 us, 60 of 16 x 16, C = 512, 28.4 -> 26.8; 100 of 37 x 37, bound by its reads beside this, level.
 // The pivot kept out of the fetches that do not need it, 12 % fewer instructions, loses 4 % there to the branches.)
