@@ -1017,7 +1017,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 
   int sh = 0, qb = 0;
   const u32x4 *kh, *vh;
-  __amdgpu_buffer_rsrc_t vb;         // VROWS: the head's columns of the sequence's rows; what lies beyond reads as zeros
+  // VROWS: the head's columns of the sequence's rows; what lies beyond reads as zeros.  (Whole offsets are the lanes': the
+  // scalar offset of a buffer load is left out of its check against the range.)
+  __amdgpu_buffer_rsrc_t vb;
   // thread tid moves the 16-byte piece c of rows tid / 8 and tid / 8 + 32 to place c ^ 4 (row / 2 % 2) of the row in LDS, so
   // that the four rows that 32 lanes of a transposing read take 64 bytes each from lie in different banks
   const int v_off = VROWS ? (tid >> 3) * C * 2 + ((tid & 7) ^ (tid >> 4 & 1) * 4) * 16 : 0;
@@ -1039,7 +1041,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   auto fetch1 = [&](int part) {      // one of the four fetch instructions of a stage
     u32x4 *dst = (part < 2 ? &ks[fslot][0] : &vs[fslot][0]) + (part & 1) * 256 + wave * 64;
     if (VROWS && part >= 2) {
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(vb, dst, 16, v_off, (2 * fstage + (part & 1)) * 64 * C, 0, 0);
+      int rows = (2 * fstage + (part & 1)) * 64 * C;
+      asm volatile("" : "+s"(rows));   // (added here: the sums of the first stages would stay in registers all along)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(vb, dst, 16, v_off + rows, 0, 0, 0);
     } else {
       const u32x4 *src = (part < 2 ? kh : vh) + foff + (part & 1) * 256;
       __builtin_amdgcn_global_load_lds(src, dst, 16, 0, 0);
@@ -1539,7 +1543,7 @@ __global__ __launch_bounds__(64 * kShortWaves) __attribute__((amdgpu_waves_per_e
     if (t < t1)
 #pragma unroll
       for (int i = 0; i < 4; ++i)
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(vb, (u32x4 *)part[wave] + (t % 3) * 256 + i * 64, 16, v_off, (4 * t + i) * 16 * C, 0, 0);
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(vb, (u32x4 *)part[wave] + (t % 3) * 256 + i * 64, 16, v_off + (4 * t + i) * 16 * C, 0, 0, 0);
     __builtin_amdgcn_sched_barrier(0);
     asm volatile("" ::: "memory");
   };

@@ -762,6 +762,35 @@ def test_attention_short_rows_equal_relaid(B, n, heads):
     assert float((o.double() - ref)[:, fine].abs().max() / ref.abs().max()) <= 2e-2
 
 
+# V read from its rows: what lies beyond a sequence's end counts as zeros, whatever it is.  Frames between frames of NaN
+# and of infinity and before rows of NaN give what the re-layout (the output takes V's place) gives among zeros: in 64-query
+# blocks and in a stream, last tiles and stages of 1, 2, 9, 10, 30 and 33 keys, so that rows, and whole parts of a stage, lie beyond
+@pytest.mark.parametrize("frames,h,w,heads", [(3, 4, 7, 4), (3, 6, 6, 4), (3, 4, 23, 4), (3, 13, 25, 4), (2, 12, 61, 16),
+                                              (33, 4, 79, 8), (33, 13, 25, 8), (33, 12, 29, 8), (33, 5, 89, 8), (20, 37, 37, 8)])
+@pytest.mark.parametrize("res", [0, 1])
+def test_attention_values_end_with_their_sequence(B, frames, h, w, heads, res):
+    import torch
+    n, c = h * w + 5, heads * 64
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n)
+    q, k, x = (torch.randn(frames * n, c, generator=g, device="cuda").to(torch.bfloat16) for _ in range(3))
+    room = torch.full((frames * n + 64, c), float("nan"), dtype=torch.bfloat16, device="cuda")
+    v = room[:frames * n]
+    v.copy_(torch.randn(frames * n, c, generator=g, device="cuda"))
+    relaid = v.clone()
+    relaid.view(frames, n, c)[1::2] = 0.0
+    v.view(frames, n, c)[1::4] = float("nan")
+    v.view(frames, n, c)[3::4] = float("inf")
+    ph = B.make_params(frames, h, w, c, heads, qk_norm=1)
+    ws = B.alloc_ws(B.litevggt_frame_attn_ws_bytes(ph))
+    got = torch.full_like(q, float("nan"))
+    B.litevggt_frame_attn(ph, q, k, v, x if res else None, got, ws)
+    B.litevggt_frame_attn(ph, q, k, relaid, x if res else None, relaid, ws)
+    torch.cuda.synchronize()
+    got, relaid = (t.view(torch.int16).view(frames, n, c)[::2] for t in (got, relaid))
+    assert torch.equal(got, relaid)
+
+
 # frames of a few hundred tokens with the residual added in place, in 64-query blocks and one frame beyond
 @pytest.mark.parametrize("frames,h,w,heads,norm", [(2, 16, 16, 4, 1), (25, 15, 17, 4, 1), (26, 15, 17, 4, 1), (2, 37, 37, 8, 1),
                                                    (2, 5, 5, 1, 0)])
