@@ -989,7 +989,9 @@ constexpr int kGiveWayStages = 32;   // (2,525 tokens, up to two rounds: 0.98 of
 // (In the forms with packed V, whose sequences are longer, the second loop costs 20 registers in scratch.)
 
 // Eight transposing reads: the four fragments of 32 keys of V from its rows in LDS (k_attn_bf16_stream), two 8-byte
-// halves each, not waited for.  addr: where channels 0-31 of the lane's row lie; channels 32-63 are at addr ^ 64.
+// halves each, not waited for.  addr: where channels 0-31 of the lane's row lie; channels 32-63 are at addr ^ 64 (rows of
+// 128 bytes, at multiples of kVRowBytes).
+constexpr size_t kVRowBytes = 128;
 __device__ __forceinline__ void lds_read_vt_async(u32x2 (&dst)[8], uint32_t addr) {
   asm volatile("ds_read_b64_tr_b16 %0, %8\n\tds_read_b64_tr_b16 %1, %8 offset:1024\n\t"
                "ds_read_b64_tr_b16 %2, %9\n\tds_read_b64_tr_b16 %3, %9 offset:1024\n\t"
@@ -1005,8 +1007,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     const uint16_t *q, const u32x4 *__restrict__ kp, const u32x4 *__restrict__ vp, const uint16_t *vrows, uint16_t *o,
     const uint16_t *res, int64_t n, int heads, int n_seq, int n_kt, int nqb, float c, int qk_norm, uint32_t *ctr) {
   __shared__ u32x4 ks[kBStages][8 * kFragU4];
-  __shared__ u32x4 vs[kBStages][8 * kFragU4];
+  __shared__ __attribute__((aligned(kVRowBytes))) u32x4 vs[kBStages][8 * kFragU4];
   __shared__ int next_block;
+  static_assert(__alignof__(vs) % kVRowBytes == 0, "lds_read_vt_async");
   const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5, ql = lane & 31;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int C = heads * 64, nkv = n_kt >> 1, nkt = n_kt;
@@ -1489,7 +1492,9 @@ __global__ __launch_bounds__(64 * kShortWaves) __attribute__((amdgpu_waves_per_e
     uint32_t *__restrict__ redo, int redo_stride) {
   constexpr int WAVES = kShortWaves, R = 64 / WAVES;   // of a lane's 64 output registers (query block, channels 32 dt .., row) a
                                              // wave adds up and stores R
-  __shared__ f32x4 part[WAVES][WAVES - 1][R / 4 * 64];   // [wave][whose registers, its own left out][group of 4][lane]
+  // [wave][whose registers, its own left out][group of 4][lane]; ROWS: V's rows before
+  __shared__ __attribute__((aligned(kVRowBytes))) f32x4 part[WAVES][WAVES - 1][R / 4 * 64];
+  static_assert(__alignof__(part) % kVRowBytes == 0 && sizeof(part[0]) % kVRowBytes == 0, "lds_read_vt_async");
   __shared__ f32x2 psum[WAVES][64];          // row sums of the two query blocks
   __shared__ float pref[WAVES];              // ONLINE: the waves' references
   __shared__ int any_low;
