@@ -186,7 +186,7 @@ __device__ __forceinline__ float ln_packed_tile(const uint16_t *__restrict__ x, 
 }
 
 // what 32 rows take in LDS
-static size_t ln_packed_lds(int C, bool fp8) { return fp8 ? (size_t)32 * (C / 8 + 2) * 8 : (size_t)32 * (C / 8 + 1) * 16; }
+static constexpr size_t ln_packed_lds(int C, bool fp8) { return fp8 ? (size_t)32 * (C / 8 + 2) * 8 : (size_t)32 * (C / 8 + 1) * 16; }
 
 template <int CPL, bool FP8>
 __global__ __launch_bounds__(64 * kLnWaves) void k_layernorm_packed(const uint16_t *__restrict__ x,
@@ -217,7 +217,7 @@ static int launch_layernorm(const uint16_t *x, const uint16_t *add, const float 
     const unsigned grid = (unsigned)(Mp / 32);
     int rc;
 #define LV_LNP(CPL, F8)                                                                                       \
-  if ((rc = allow_dynamic_lds((const void *)k_layernorm_packed<CPL, F8>, lds, lds_done[(CPL - 1) * 2 + F8])))   \
+  if ((rc = allow_dynamic_lds<ln_packed_lds(512 * CPL, F8)>((const void *)k_layernorm_packed<CPL, F8>, lds_done[(CPL - 1) * 2 + F8]))) \
     return rc;                                                                                                \
   hipLaunchKernelGGL((k_layernorm_packed<CPL, F8>), dim3(grid), dim3(64 * kLnWaves), lds, st, x, add, gamma, beta, M, C,  \
                      packed, fp8_inv, fp8_amax)
@@ -470,7 +470,7 @@ static int launch_block_head(const uint16_t *z, const float *gamma, const float 
   const BlockWeights4 w4 = bw ? *bw : BlockWeights4{};
   int rc;
 #define LV_HEAD(CPL, F8)                                                                                       \
-  if ((rc = allow_dynamic_lds((const void *)k_block_head<CPL, F8>, ln_packed_lds(C, F8), lds_done[(CPL - 1) * 2 + F8]))) \
+  if ((rc = allow_dynamic_lds<ln_packed_lds(512 * CPL, F8)>((const void *)k_block_head<CPL, F8>, lds_done[(CPL - 1) * 2 + F8]))) \
     return rc;                                                                                                 \
   hipLaunchKernelGGL((k_block_head<CPL, F8>), dim3(grid), dim3(64 * kLnWaves), lds, st, z, gamma, beta, M, C, n_ln, packed, w4, n_pack, hd, cw)
 #define LV_HEADS(F8)                   \
@@ -1316,7 +1316,7 @@ static int launch_linear(const uint16_t *A, int64_t M, int K, int Nout,
     using S = GemmShape<BM, BN>;
     constexpr size_t kLds = S::kLds + (KG - 1) * (size_t)S::kStages * S::kStageU4 * 16;
     static std::atomic<uint64_t> lds_done{0};
-    if (int rc2 = allow_dynamic_lds((const void *)k_gemm_bt<F8, PK, BM, BN, KG>, kLds, lds_done)) return rc2;
+    if (int rc2 = allow_dynamic_lds<kLds>((const void *)k_gemm_bt<F8, PK, BM, BN, KG>, lds_done)) return rc2;
     const int nt_m = (int)((M + BM - 1) / BM), nt_n = Nout / BN, n_tiles = nt_m * nt_n;
     const int slots = n_cu * (KG == 1 ? 256 / BM : BM == 64 ? 2 : 1);   // KG = 2: tile_shape() leaves one tile per workgroup
     // One round only: row tiles still go to one XCD each (M = 5776, K = 4096: 69 us dealt out in

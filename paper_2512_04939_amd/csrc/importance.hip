@@ -130,7 +130,7 @@ int launch_grad_map(const void *images, int img_dtype, const Dims &d, int patch,
   int rc;
 #define LV_GRAD(T, V, I)                                                                          \
   do {                                                                                            \
-    if ((rc = allow_dynamic_lds((const void *)k_grad_map<T, V>, 96 * 1024, lds_done[I]))) return rc; \
+    if ((rc = allow_dynamic_lds<96 * 1024>((const void *)k_grad_map<T, V>, lds_done[I]))) return rc; \
     hipLaunchKernelGGL((k_grad_map<T, V>), grid, dim3(threads), lds, st, (const T *)images, d.F, d.H, d.W, patch, psi_g); \
   } while (0)
   if (img_dtype == LV_IMG_F32) {
@@ -472,7 +472,7 @@ int launch_maps(const void *images, int img_dtype, const uint16_t *x, const Dims
   static std::atomic<uint64_t> lds_done[2];
   int rc;
 #define LV_BOTH(T, I)                                                                                            \
-  if ((rc = allow_dynamic_lds((const void *)k_both_maps<T>, 64 * 1024, lds_done[I]))) return rc;                   \
+  if ((rc = allow_dynamic_lds<64 * 1024>((const void *)k_both_maps<T>, lds_done[I]))) return rc;                   \
   hipLaunchKernelGGL((k_both_maps<T>), grid, dim3(kBothThreads), lds, st, (const T *)images, patch, psi_g, x, d.F, d.H, d.W, \
                      d.S, d.C, nseg, row_segs, psi_v, (int)strip_blocks)
   if (img_dtype == LV_IMG_F32) {

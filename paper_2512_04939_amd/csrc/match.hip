@@ -1166,9 +1166,9 @@ int launch_match(const uint16_t *x, const Dims &d, const litevggt_plan_t &pl,
     if (d.C % 64 != 0 || n_dst <= 0) return LV_ERR_SHAPE;   // (64: k_match_small)
     // 128 KB ring (reused for the final merge) + per wave kInvBufs buffers of 64 inverse norms
     // and two buffers of 8 x 4 x 32 second-best bounds the waves of a column exchange
-    const size_t lds = (size_t)kGStages * kGStageU4 * 16 + 8 * kInvBufs * 64 * sizeof(float) + 2 * 1024 * sizeof(float);
+    constexpr size_t lds = (size_t)kGStages * kGStageU4 * 16 + 8 * kInvBufs * 64 * sizeof(float) + 2 * 1024 * sizeof(float);
     static std::atomic<uint64_t> lds_done{0};
-    if (int rc = allow_dynamic_lds((const void *)k_match_sim, lds, lds_done)) return rc;
+    if (int rc = allow_dynamic_lds<lds>((const void *)k_match_sim, lds_done)) return rc;
     const int pack_dst = w.n_dst_pad / 32, pack_src = w.n_src_pad / 32;
     hipLaunchKernelGGL(k_match_pack, dim3((unsigned)(pack_dst + pack_src)), dim3(256), 0, st, x, ix.dst_idx, n_dst,
                        pack_dst, ix.src_idx, n_src, d.C, w.dstp, w.srcp, w.invd, w.invs, w.team_ctr);
@@ -1204,9 +1204,9 @@ int launch_match(const uint16_t *x, const Dims &d, const litevggt_plan_t &pl,
   if (d.N <= kCsrSmall) {   // M <= N: slots fit 14 bits
     const size_t lds = align_up((size_t)d.N * sizeof(uint32_t), 16);
     static std::atomic<uint64_t> lds_done{0};
-    if (int rc = allow_dynamic_lds((const void *)k_csr_small<false>, kCsrSmall * sizeof(uint32_t), lds_done)) return rc;
+    if (int rc = allow_dynamic_lds<kCsrSmall * sizeof(uint32_t)>((const void *)k_csr_small<false>, lds_done)) return rc;
     static std::atomic<uint64_t> lds_done2{0};
-    if (int rc = allow_dynamic_lds((const void *)k_csr_small<true>, kCsrSmall * sizeof(uint32_t), lds_done2)) return rc;
+    if (int rc = allow_dynamic_lds<kCsrSmall * sizeof(uint32_t)>((const void *)k_csr_small<true>, lds_done2)) return rc;
     hipLaunchKernelGGL((with_csr ? k_csr_small<true> : k_csr_small<false>), dim3(1), dim3(1024), lds, st,
                        (const int32_t *)ix.slot_of, (int)d.N, (int)pl.M, ix.group_off, ix.group_mem, finish);
     LV_HIP_CHECK_LAUNCH();

@@ -285,6 +285,15 @@ def test_block_tile_shapes(B, m, dim, linear):
     assert err <= (2e-2 if linear == "bf16" else 1e-1)
 
 
+# the LayerNorms' rows in LDS, 40 to 132 KB of 32: the fewer channels of one kernel before the most of the same one, whose
+# limit of dynamic LDS is raised once per device
+@pytest.mark.parametrize("fewer,most", [(1280, 1536), (1792, 2048)])
+@pytest.mark.parametrize("linear", ["bf16", "fp8-delayed"])
+def test_block_of_more_channels_after_fewer(B, fewer, most, linear):
+    for dim in (fewer, most):
+        test_block_tile_shapes(B, 100, dim, linear)
+
+
 @pytest.mark.parametrize("dim", [512, 768, 1024])
 def test_block_layernorm_cancels_opposite_lanes_first(B, dim):
     """Two channels 32 lanes apart hold +-2^30: added to each other first they vanish and the mean of the
