@@ -1982,10 +1982,13 @@ __device__ __forceinline__ i32x8 cat_fp8(u32x2 a, u32x2 b, u32x2 c, u32x2 d) {
 // Where the output of the E4M3 kernels goes: rows, or a linear layer's activation operand (rows beyond the sequence end
 // up to whole blocks of 256 zero): in bf16, or as E4M3 codes of the values rounded to bf16 (scale *inv), whose largest
 // magnitude is raised in *amax.  The layer's own pass over the rows took 10.6 us at 15,432 tokens of 16 heads.
+// (The bounded kernel leaves each wave's magnitude, four per flag, in wave_max: the second pass knows which blocks
+// keep their rows and raises theirs.)
 enum AttnOut { kOutRows, kOutBf16, kOutE4M3 };
 struct AttnOutArgs {
   const uint32_t *inv;
   uint32_t *amax;
+  float *wave_max;
 };
 // 32 queries from row0 on (query lane % 32) x the head's 64 channels, as a lane's accumulators hold them, times the lane's inv;
 // returns the largest |value| of a live row
@@ -2070,8 +2073,14 @@ __global__ __launch_bounds__(512) void k_attn_fp8(
   }
   // second pass behind the bounded kernel: only the query blocks it has flagged (one flag per
   // 256 queries; the whole workgroup takes the same branch, before any barrier)
-  if (SECOND && redo[(size_t)head * (2 * nqb) + 2 * qb] == 0u && redo[(size_t)head * (2 * nqb) + 2 * qb + 1] == 0u)
+  if (SECOND && redo[(size_t)head * (2 * nqb) + 2 * qb] == 0u && redo[(size_t)head * (2 * nqb) + 2 * qb + 1] == 0u) {
+    if (OUT == kOutE4M3 && wave == 0) {
+      const bool there = lane < kQB / kQW && (int64_t)qb * kQB + lane * kQW < n;   // (the last flag may have no block)
+      const float m = wave_max(there ? oa.wave_max[((size_t)head * (2 * nqb) + 2 * qb) * (kBQB / kQW) + lane] : 0.f);
+      if (lane == 0) raise_max(oa.amax, m);
+    }
     return;
+  }
   const int64_t q0 = (int64_t)qb * kQB + wave * kQW;
   const float inv_sq = fp8_scale_inv(amax[0]);
   // scores come out in units of scale_q*scale_k; fold both into the exponent scale
@@ -2601,11 +2610,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     low |= q0 + sub * 32 + ql < n && !(l >= 1.0f);
     m = fmaxf(m, store_head<OUT>(oacc[sub], out_scale / l, q0 + sub * 32, n, C, head, o, code_inv, lane));
   }
-  const bool flag = __builtin_amdgcn_ballot_w64(low) != 0;
-  if (flag && lane == 0) atomicOr(&redo[(size_t)head * redo_stride + qb], 1u);
-  if constexpr (OUT == kOutE4M3) {     // (a flagged wave's rows are not what the block ends up with)
+  const size_t at = (size_t)head * redo_stride + qb;
+  if (__builtin_amdgcn_ballot_w64(low) != 0 && lane == 0) atomicOr(&redo[at], 1u);
+  if constexpr (OUT == kOutE4M3) {
     m = wave_max(m);
-    if (!flag && lane == 0) raise_max(oa.amax, m);
+    if (lane == 0) oa.wave_max[at * (kBQB / kQW) + wave] = m;
   }
 }
 
@@ -2663,8 +2672,9 @@ size_t attn_ws_bytes(int heads, int64_t n_tokens, int attn_dtype, int n_seq, boo
   const size_t elem = attn_dtype == LV_ATTN_FP8_E4M3 ? sizeof(u32x2) : sizeof(u32x4);
   const size_t per = (size_t)heads * n_seq * n_key_tiles(n_tokens) * 4 * kFragU4 * elem;
   // [amax block][K fragments][V fragments]; FP8: the first pair is the running-maximum kernel's (with qk_norm the
-  // workgroups' maxima lie there until K is written), the second the bounded kernel's and its second pass', then
-  // the flags.  No call uses both pairs; they stay apart because callers have sized their scratch by this.
+  // workgroups' maxima lie there until K is written, or a block's, of its attention's output), the second the bounded
+  // kernel's and its second pass', then the flags.  No call uses K and V of both pairs; they stay apart because callers
+  // have sized their scratch by this.
   size_t total = 256 + 2 * align_up(per, 256);
   if (attn_dtype == LV_ATTN_FP8_E4M3) total += 2 * align_up(per, 256) + align_up(fp8_flag_words(heads, n_tokens) * 4, 256);
   // bf16: the flags of the online-softmax pass (one word per 256-query block)
@@ -2782,7 +2792,8 @@ int launch_attn(const uint16_t *q, const uint16_t *k, const uint16_t *v, uint16_
     if (after_pack && hipEventRecord(after_pack, st) != hipSuccess) return LV_ERR_HIP;
     auto kernels = [&](auto kind, uint16_t *out) {
       constexpr AttnOut OUT = decltype(kind)::value;
-      const AttnOutArgs oa = {operand ? operand->inv : nullptr, operand ? operand->amax : nullptr};
+      // (the running-maximum kernel's K, which the bounded one does without, has room for its waves' maxima)
+      const AttnOutArgs oa = {operand ? operand->inv : nullptr, operand ? operand->amax : nullptr, (float *)kp};
       if (bounded) {
         // the branch-free kernel against the fixed reference first, then the running-maximum kernel on the query
         // blocks the first one flagged (normally none: its workgroups return at once)

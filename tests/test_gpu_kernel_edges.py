@@ -350,6 +350,64 @@ def test_block_largest_tiles(B, m, dim, linear):
         assert all(abs(a / s - 1) <= 0.1 for a, s in zip(amax[1:], seen[1:])), (amax, seen)
 
 
+def _exact_qkv_block(B, n, seed, far):
+    """A block's tokens and weights whose q, k and v are exact in every type, and those three.  Rows of +-1, so LN(z) = z; q and
+    k are selections of it, the same for all heads, v sums of eight entries.  Keys share 48 of 64 channels: queries agree with
+    them in half of these, and the rows `far` in none, 8.6 binades below."""
+    import torch
+    g = torch.Generator(device="cuda")
+    g.manual_seed(seed)
+    dim, heads = 256, 4
+    z = torch.randint(0, 2, (n, dim), generator=g, device="cuda") * 2.0 - 1.0
+    z[:, 64:112] = z[0, 64:112]                                    # keys: channels 64 .. 127; queries: 0 .. 63
+    z[:, 0:48] = z[0, 64:112]
+    z[:, 0:48] *= 1.0 - 2.0 * (torch.rand(n, 48, generator=g, device="cuda").argsort(1) < 24)
+    z[far, 0:48] = -z[0, 64:112]
+    for row in range(n):                                           # mean 0
+        free = 128 + torch.randperm(128, generator=g, device="cuda")
+        flip = free[(z[row, free] > 0) == (z[row].sum() > 0)][:int(z[row].sum().abs()) // 2]
+        z[row, flip] *= -1.0
+    assert bool((z.sum(1) == 0).all())
+    t = {k: torch.zeros(v.shape, device="cuda") for k, v in synth.block_weights(dim, seed=0).items()}
+    t["ln1_g"] += 1.0
+    t["ln2_g"] += 1.0
+    for h in range(heads):
+        for part in range(2):
+            t["w_qkv"][part * dim + h * 64:part * dim + h * 64 + 64, part * 64:part * 64 + 64] = torch.eye(64, device="cuda")
+    for c in range(dim):
+        at = torch.randperm(dim, generator=g, device="cuda")[:8]
+        t["w_qkv"][2 * dim + c, at] = 2.0 ** -torch.randint(0, 3, (8,), generator=g, device="cuda").float()
+    t["w_o"][:] = torch.eye(dim, device="cuda")
+    t["w_1"][:dim], t["w_2"][:, :dim] = torch.eye(dim, device="cuda"), torch.eye(dim, device="cuda")
+    t = {k: v.to(torch.bfloat16) if k.startswith("w_") else v for k, v in t.items()}
+    qkv = (z.double() @ t["w_qkv"].double().t().contiguous()).to(torch.bfloat16)
+    return z.to(torch.bfloat16), t, [qkv[:, i * dim:i * dim + dim].contiguous() for i in range(3)]
+
+
+# E4M3 attention whose blocks' first pass is not enough for some query: the amax that goes into the history is that of the rows
+# that the second pass leaves, and of other blocks' first pass.  One block of 512 queries, flagged in its first half, in its ragged
+# second one, and none of it; a flagged one among others
+@pytest.mark.parametrize("n,far", [(200, [10]), (512, [511]), (230, []), (1300, [600, 700])])
+def test_block_attention_amax_of_the_rows_it_leaves(B, n, far):
+    import torch
+    ph = B.make_params(1, 1, 1, 256, 4, n_special=0, attn_dtype=B.ATTN_FP8_E4M3, qk_norm=1)
+    ws = B.alloc_ws(B.litevggt_global_block_ws_bytes(ph, n))
+    for seed in range(8):
+        z, t, (q, k, v) = _exact_qkv_block(B, n, seed, far)
+        o, delta, aws = torch.full_like(q, float("nan")), torch.full_like(q, float("nan")), B.alloc_ws(B.litevggt_attn_ws_bytes(ph, n))
+        B.litevggt_global_attn(ph, n, q, k, v, o, aws)
+        state = torch.zeros(B.FP8_STATE_BYTES, dtype=torch.uint8, device="cuda")
+        B.litevggt_global_block(ph, n, z, B.block_weights(t, B.LINEAR_FP8_E4M3, B.FP8_DELAYED, state), delta, ws)
+        torch.cuda.synchronize()
+        amax = state.view(torch.float32).reshape(4, -1)[:, 0].tolist()
+        assert amax[0] == 1.0 and amax[1] == float(o.abs().max()), (seed, amax, float(o.abs().max()))
+        assert bool(torch.isfinite(delta).all())
+        words, nqb = 4 * 2 * ((n + 511) // 512), (n + 255) // 256         # one flag per head and 256 queries, behind K and V twice
+        base = (aws.data_ptr() + 255) // 256 * 256 - aws.data_ptr() + 256 + 4 * (4 * 2 * ((n + 63) // 64) * 4 * 64 * 8)
+        flags = aws[base:base + words * 4].view(torch.int32).reshape(4, -1)[:, :nqb]
+        assert flags.ne(0).nonzero().tolist() == [[h, b] for h in range(4) for b in sorted({f // 256 for f in far})]
+
+
 # ------------------------------------------------------------------------------- importance
 # pixel rows that are no multiple of 4 pixels, planes that are none (one pixel at a time), images
 # behind an unaligned address, a single patch row and column, pixel rows wider than a workgroup,
