@@ -325,7 +325,8 @@ def test_block_layernorm_cancels_opposite_lanes_first(B, dim):
 # and a ragged last row tile; tiles of four stages, the ring's fewest, that follow each other (98 x 4)
 @pytest.mark.parametrize("m,dim", [(15400, 512), (8900, 768), (25001, 256)])
 @pytest.mark.parametrize("linear", ["bf16", "fp8-delayed"])
-def test_block_largest_tiles(B, m, dim, linear):
+@pytest.mark.parametrize("attn", ["bf16", "fp8"])
+def test_block_largest_tiles(B, m, dim, linear, attn):
     import torch
     t = {k: torch.from_numpy(v).cuda() for k, v in synth.block_weights(dim, seed=m).items()}
     t = {k: v.to(torch.bfloat16) if k.startswith("w_") else v for k, v in t.items()}
@@ -334,7 +335,7 @@ def test_block_largest_tiles(B, m, dim, linear):
     z = torch.randn(m, dim, generator=g, device="cuda").to(torch.bfloat16)
     state = torch.zeros(B.FP8_STATE_BYTES, dtype=torch.uint8, device="cuda")
     bw = B.block_weights(t) if linear == "bf16" else B.block_weights(t, B.LINEAR_FP8_E4M3, B.FP8_DELAYED, state)
-    ph = B.make_params(1, 1, 1, dim, dim // 64, n_special=0, qk_norm=1)
+    ph = B.make_params(1, 1, 1, dim, dim // 64, n_special=0, qk_norm=1, attn_dtype=B.ATTN_FP8_E4M3 if attn == "fp8" else B.ATTN_BF16)
     delta = torch.full_like(z, float("nan"))
     ws = B.alloc_ws(B.litevggt_global_block_ws_bytes(ph, m))
     for _ in range(1 if linear == "bf16" else 2):            # the second call scales by the first one's amaxes
@@ -343,65 +344,116 @@ def test_block_largest_tiles(B, m, dim, linear):
     seen = []
     ref = _block64(z, t, dim // 64, seen)
     err = float((delta.double() - ref).abs().max() / ref.abs().max())
-    assert err <= (2e-2 if linear == "bf16" else 1e-1)       # as in test_block_tile_shapes
+    assert err <= (2e-2 if linear == attn == "bf16" else 1e-1)   # as in test_block_tile_shapes; E4M3 attention as E4M3 layers
     if linear != "bf16":    # recorded amaxes of the four layers' inputs: LayerNorm of z to a bf16 step, the others behind E4M3 layers
         amax = state.view(torch.float32).reshape(4, -1)[:, 1].tolist()
         assert abs(amax[0] / seen[0] - 1) <= 2.0 ** -8
         assert all(abs(a / s - 1) <= 0.1 for a, s in zip(amax[1:], seen[1:])), (amax, seen)
 
 
-def _exact_qkv_block(B, n, seed, far):
-    """A block's tokens and weights whose q, k and v are exact in every type, and those three.  Rows of +-1, so LN(z) = z; q and
-    k are selections of it, the same for all heads, v sums of eight entries.  Keys share 48 of 64 channels: queries agree with
-    them in half of these, and the rows `far` in none, 8.6 binades below."""
+def _exact_qkv_block(n, dim, seed, far=None):
+    """A block's tokens and weights whose q, k and v are exact in every type, and those three; its output is its attention's, as
+    the output projection takes it.  Rows of +-1, so LN(z) = z; q and k are selections of it in powers of two that differ from
+    head to head, v sums of eight entries.  Keys share 48 of 64 channels.  With `far`, all heads are alike; queries agree with
+    the keys in half of these 48, and the rows `far` in none, 8.6 binades below."""
     import torch
     g = torch.Generator(device="cuda")
     g.manual_seed(seed)
-    dim, heads = 256, 4
+    heads = dim // 64
     z = torch.randint(0, 2, (n, dim), generator=g, device="cuda") * 2.0 - 1.0
-    z[:, 64:112] = z[0, 64:112]                                    # keys: channels 64 .. 127; queries: 0 .. 63
-    z[:, 0:48] = z[0, 64:112]
-    z[:, 0:48] *= 1.0 - 2.0 * (torch.rand(n, 48, generator=g, device="cuda").argsort(1) < 24)
-    z[far, 0:48] = -z[0, 64:112]
-    for row in range(n):                                           # mean 0
-        free = 128 + torch.randperm(128, generator=g, device="cuda")
-        flip = free[(z[row, free] > 0) == (z[row].sum() > 0)][:int(z[row].sum().abs()) // 2]
-        z[row, flip] *= -1.0
+    z[:, 64:112] = z[0, 64:112].clone()                            # keys: channels 64 .. 127; queries: 0 .. 63
+    if far is not None:
+        z[:, 0:48] = z[0, 64:112] * (1.0 - 2.0 * (torch.rand(n, 48, generator=g, device="cuda").argsort(1).argsort(1) < 24))
+        z[far, 0:48] = -z[0, 64:112]
+    ones = (dim - 128 - z[:, :128].sum(1)) / 2                     # mean 0
+    rank = torch.rand(n, dim - 128, generator=g, device="cuda").argsort(1).argsort(1)
+    z[:, 128:] = (rank < ones[:, None]) * 2.0 - 1.0
     assert bool((z.sum(1) == 0).all())
     t = {k: torch.zeros(v.shape, device="cuda") for k, v in synth.block_weights(dim, seed=0).items()}
     t["ln1_g"] += 1.0
     t["ln2_g"] += 1.0
+    i = torch.arange(64, device="cuda")
     for h in range(heads):
-        for part in range(2):
-            t["w_qkv"][part * dim + h * 64:part * dim + h * 64 + 64, part * 64:part * 64 + 64] = torch.eye(64, device="cuda")
-    for c in range(dim):
-        at = torch.randperm(dim, generator=g, device="cuda")[:8]
-        t["w_qkv"][2 * dim + c, at] = 2.0 ** -torch.randint(0, 3, (8,), generator=g, device="cuda").float()
+        gain_q, gain_k = (torch.ones(64, device="cuda"),) * 2 if far is not None else (
+            2.0 ** -(i % 3 + (heads - 1 - h) % 4).float(), 2.0 ** -((i + h) % 3 + h % 4).float())
+        t["w_qkv"][h * 64 + i, i] = gain_q
+        t["w_qkv"][dim + h * 64 + i, 64 + i] = gain_k
+    at = torch.rand(dim, dim, generator=g, device="cuda").argsort(1)[:, :8]
+    t["w_qkv"][2 * dim:].scatter_(1, at, 2.0 ** -torch.randint(0, 3, (dim, 8), generator=g, device="cuda").float())
     t["w_o"][:] = torch.eye(dim, device="cuda")
-    t["w_1"][:dim], t["w_2"][:, :dim] = torch.eye(dim, device="cuda"), torch.eye(dim, device="cuda")
     t = {k: v.to(torch.bfloat16) if k.startswith("w_") else v for k, v in t.items()}
     qkv = (z.double() @ t["w_qkv"].double().t().contiguous()).to(torch.bfloat16)
     return z.to(torch.bfloat16), t, [qkv[:, i * dim:i * dim + dim].contiguous() for i in range(3)]
 
 
-# E4M3 attention whose blocks' first pass is not enough for some query: the amax that goes into the history is that of the rows
-# that the second pass leaves, and of other blocks' first pass.  One block of 512 queries, flagged in its first half, in its ragged
-# second one, and none of it; a flagged one among others
+def _through_e4m3(o, inv):
+    """Rows through an identity layer with E4M3 operands (weight: code 448), their scale inv."""
+    import torch
+    f = lambda x: torch.tensor(x, dtype=torch.float32, device="cuda")  # noqa: E731
+    codes = (o.float() * f(inv)).clamp(-448.0, 448.0).to(torch.float8_e4m3fn).float()
+    return (codes * 448.0 * ((f(1.0) / f(inv)) * (f(1.0) / f(448.0)))).to(torch.bfloat16)
+
+
+def _f32(x):
+    return float(np.float32(x))
+
+
+# blocks around E4M3 attention, and bf16 attention: q, k and v from every tile shape of their layer (64 x 64 in two K groups: one
+# row, one row more than a tile; 128 x 128 in two K groups with bf16 layers; 128 x 128; 128 x 256; 256 x 256), ragged ends,
+# among them ones whose last 512 queries reach beyond the next layer's operand; normalised and as given, the attention's
+# output as rows, as bf16 and as E4M3 operand: the attention entry point's bits, rounded as the output layer rounds its input
+@pytest.mark.parametrize("n,dim", [(1, 256), (65, 256), (300, 512), (700, 256), (400, 2048), (2200, 1024), (5200, 512),
+                                   (5601, 512), (12001, 256)])
+@pytest.mark.parametrize("linear", ["bf16", "fp8", "fp8-delayed"])
+@pytest.mark.parametrize("attn", ["fp8", "bf16"])
+@pytest.mark.parametrize("norm", [1, 0])
+def test_block_is_its_attention_between_identity_layers(B, n, dim, linear, attn, norm):
+    import torch
+    z, t, (q, k, v) = _exact_qkv_block(n, dim, n)
+    ph = B.make_params(1, 1, 1, dim, dim // 64, n_special=0, attn_dtype=B.ATTN_FP8_E4M3 if attn == "fp8" else B.ATTN_BF16, qk_norm=norm)
+    o = torch.full_like(q, float("nan"))
+    B.litevggt_global_attn(ph, n, q, k, v, o, B.alloc_ws(B.litevggt_attn_ws_bytes(ph, n)))
+    top = float(o.abs().max())
+    state = torch.zeros(B.FP8_STATE_BYTES, dtype=torch.uint8, device="cuda")
+    bw = B.block_weights(t) if linear == "bf16" else B.block_weights(
+        t, B.LINEAR_FP8_E4M3, B.FP8_CURRENT if linear == "fp8" else B.FP8_DELAYED, state)
+    ws = B.alloc_ws(B.litevggt_global_block_ws_bytes(ph, n))
+    ws.fill_(0x7f)
+    for call in range(2):                                          # (delayed: scale 1, then by the first call's amax)
+        delta = torch.full_like(z, float("nan"))
+        B.litevggt_global_block(ph, n, z, bw, delta, ws)
+        torch.cuda.synchronize()
+        scale = 1.0 if linear == "fp8-delayed" and call == 0 else _f32(np.float32(448.0) / np.float32(top))
+        assert torch.equal(delta, o if linear == "bf16" else _through_e4m3(o, scale)), call
+    if linear == "fp8-delayed":
+        amax = state.view(torch.float32).reshape(4, -1)[:, :2].tolist()
+        assert amax[0] == [1.0, 1.0] and amax[1] == [top, top]
+
+
+# E4M3 attention whose blocks' first pass is not enough for some query: the second pass rewrites the output layer's operand, and
+# the amax that goes into the history is that of the rows that it leaves, and of other blocks' first pass.  One block of 512 queries,
+# flagged in its first half, in its ragged second one, and none of it; a flagged one among others
 @pytest.mark.parametrize("n,far", [(200, [10]), (512, [511]), (230, []), (1300, [600, 700])])
-def test_block_attention_amax_of_the_rows_it_leaves(B, n, far):
+@pytest.mark.parametrize("linear", ["bf16", "fp8", "fp8-delayed"])
+def test_block_attention_left_to_the_second_pass(B, n, far, linear):
     import torch
     ph = B.make_params(1, 1, 1, 256, 4, n_special=0, attn_dtype=B.ATTN_FP8_E4M3, qk_norm=1)
     ws = B.alloc_ws(B.litevggt_global_block_ws_bytes(ph, n))
     for seed in range(8):
-        z, t, (q, k, v) = _exact_qkv_block(B, n, seed, far)
+        z, t, (q, k, v) = _exact_qkv_block(n, 256, seed, far)
         o, delta, aws = torch.full_like(q, float("nan")), torch.full_like(q, float("nan")), B.alloc_ws(B.litevggt_attn_ws_bytes(ph, n))
         B.litevggt_global_attn(ph, n, q, k, v, o, aws)
         state = torch.zeros(B.FP8_STATE_BYTES, dtype=torch.uint8, device="cuda")
-        B.litevggt_global_block(ph, n, z, B.block_weights(t, B.LINEAR_FP8_E4M3, B.FP8_DELAYED, state), delta, ws)
+        bw = B.block_weights(t) if linear == "bf16" else B.block_weights(
+            t, B.LINEAR_FP8_E4M3, B.FP8_CURRENT if linear == "fp8" else B.FP8_DELAYED, state)
+        B.litevggt_global_block(ph, n, z, bw, delta, ws)
         torch.cuda.synchronize()
-        amax = state.view(torch.float32).reshape(4, -1)[:, 0].tolist()
-        assert amax[0] == 1.0 and amax[1] == float(o.abs().max()), (seed, amax, float(o.abs().max()))
-        assert bool(torch.isfinite(delta).all())
+        top = float(o.abs().max())
+        if linear == "fp8-delayed":
+            amax = state.view(torch.float32).reshape(4, -1)[:, 0].tolist()
+            assert amax[0] == 1.0 and amax[1] == top, (seed, amax, top)
+        scale = 1.0 if linear == "fp8-delayed" else _f32(np.float32(448.0) / np.float32(top))
+        assert torch.equal(delta, o if linear == "bf16" else _through_e4m3(o, scale)), seed
         words, nqb = 4 * 2 * ((n + 511) // 512), (n + 255) // 256         # one flag per head and 256 queries, behind K and V twice
         base = (aws.data_ptr() + 255) // 256 * 256 - aws.data_ptr() + 256 + 4 * (4 * 2 * ((n + 63) // 64) * 4 * 64 * 8)
         flags = aws[base:base + words * 4].view(torch.int32).reshape(4, -1)[:, :nqb]
@@ -699,18 +751,21 @@ def test_large_groups_in_one_pass_equal_the_single_steps(B, frames, h, w, specia
     assert largest > (pl.n_src if blank else 64)
 
 
-# With a block y is the block's delta, z feeds its LayerNorms and the packed weights are kept across the layers
+# With a block y is the block's delta, z feeds its LayerNorms and the packed weights are kept across the layers; in bf16, and as it
+# is served in FP8 (E4M3 attention, E4M3 layers, delayed scaling: a history each)
 @pytest.mark.parametrize("frames,h,w,dim,still", [(2, 16, 16, 256, False), (80, 5, 6, 256, True), (3, 12, 13, 768, False)])
-def test_layers_with_a_block_in_one_pass_equal_the_single_steps(B, frames, h, w, dim, still):
+@pytest.mark.parametrize("fp8", [False, True])
+def test_layers_with_a_block_in_one_pass_equal_the_single_steps(B, frames, h, w, dim, still, fp8):
     import torch
     g = torch.Generator(device="cuda")
     g.manual_seed(frames + dim)
     t = {k: torch.from_numpy(v).cuda() for k, v in synth.block_weights(dim, seed=frames).items()}
     t = {k: v.to(torch.bfloat16) if k.startswith("w_") else v for k, v in t.items()}
-    bw = B.block_weights(t)
+    states = torch.zeros(2, B.FP8_STATE_BYTES, dtype=torch.uint8, device="cuda")
+    bws = [B.block_weights(t, B.LINEAR_FP8_E4M3, B.FP8_DELAYED, s) if fp8 else B.block_weights(t) for s in states]
     wl = synth.Workload("t", frames=frames, grid_h=h, grid_w=w, dim=dim, heads=dim // 64, n_special=5, merge_ratio=0.9,
                         refresh_interval=3)
-    ph = hip_params(wl, block=bw)
+    ph = hip_params(wl, block=bws[0], attn_dtype=B.ATTN_FP8_E4M3 if fp8 else B.ATTN_BF16)
     pl = B.litevggt_plan(ph)
     x = torch.randn(frames, h * w + 5, dim, generator=g, device="cuda")
     if still:
@@ -729,10 +784,11 @@ def test_layers_with_a_block_in_one_pass_equal_the_single_steps(B, frames, h, w,
             B.litevggt_select_anchors(ph, maps[3], ix)
             B.litevggt_match(ph, want, ix, None, ws)
         B.litevggt_merge(ph, want, ix, z)
-        B.litevggt_global_block(ph, pl.M, z, bw, y, B.alloc_ws(B.litevggt_global_block_ws_bytes(ph, pl.M)))
+        B.litevggt_global_block(ph, pl.M, z, bws[1], y, B.alloc_ws(B.litevggt_global_block_ws_bytes(ph, pl.M)))
         B.litevggt_unmerge(ph, y, ix, want, want)
     torch.cuda.synchronize()
     assert torch.equal(got.view(torch.int16), want.view(torch.int16))
+    assert torch.equal(states[0], states[1]) and bool(states.any()) == fp8
     assert not still or int(ix.group_off[1:].sub(ix.group_off[:-1]).max()) > 64
 
 
