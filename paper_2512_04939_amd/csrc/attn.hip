@@ -1148,7 +1148,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     else lds_read4_async(dst, addr);
   };
   // The fragments are there.  VROWS: the operands beside V's halves are kept behind the wait in their place (two halves are
-  // one operand: a copy of each otherwise).
+  // one operand: a copy of each otherwise).  Nothing then tells the compiler not to move or copy a half between its read and
+  // the wait; tests/test_isa_lds_waits.py looks for that in the built code.
   auto wait_frags = [&](VF &v, u32x4(&k)[4]) {
     if constexpr (VROWS) {
       asm volatile("s_waitcnt lgkmcnt(0)"
@@ -2482,7 +2483,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     }
   };
   // Fragment reads but the newest `newer` are there.  `with`: the other operands of the MFMAs that need them, which keep
-  // those behind this wait (the fragments themselves in their place would cost a copy of each: two form one operand).
+  // those behind this wait (the fragments themselves in their place would cost a copy of each: two form one operand).  A
+  // fragment that the compiler moved or copied ahead of it would be lost: tests/test_isa_lds_waits.py reads the built code for that.
   auto wait_frags = [&](i32x8(&with)[2], auto newer) {
     asm volatile("s_waitcnt lgkmcnt(%2)" : "+v"(with[0]), "+v"(with[1]) : "n"(decltype(newer)::value) : "memory");
     __builtin_amdgcn_sched_barrier(0);
