@@ -1484,13 +1484,14 @@ constexpr int kShortWaves = 4;   // (sum4 below)
 // through its own 4 KB of LDS per tile, read transposed; both are asked for two tiles ahead.  That takes a launch away and
 // pays with every block's own normalisation of all keys, so it is for few blocks per sequence, with the re-layout and without, us:
 // 394 tokens of 16 heads 11.8 and 9.7, 700 12.9 and 11.9, 800 of 8 heads 12.1 and 12.3, 1,500 of 16 23.3 and 25.9; 25 frames of 15 x 17, 4
-// heads, 21.1 and 13.0, 6 of 16 x 16, 16 heads, 16.4 and 13.0, 2 of 37 x 37, 8 heads, 22.7 and 25.0.
+// heads, 21.1 and 13.0, 6 of 16 x 16, 16 heads, 16.4 and 13.0, 2 of 37 x 37, 8 heads, 22.7 and 25.0.  (Its two
+// arguments stand last: in front they push others out of the first 64 bytes, and every form waits 0.2 us longer.)
 constexpr int kRowsBlocks = 12;  // 64-query blocks of a sequence, at most
 template <bool ONLINE, bool PACKED, bool ROWS>
 __global__ __launch_bounds__(64 * kShortWaves) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_attn_bf16_short(
-    const uint16_t *q, const u32x4 *__restrict__ kp, const u32x4 *__restrict__ vp, const uint16_t *krows, const uint16_t *vrows,
-    uint16_t *o, const uint16_t *res, int64_t n, int heads, int n_seq, int n_kt, int nqs, float c, int qk_norm,
-    uint32_t *__restrict__ redo, int redo_stride) {
+    const uint16_t *q, const u32x4 *__restrict__ kp, const u32x4 *__restrict__ vp, uint16_t *o,
+    const uint16_t *res, int64_t n, int heads, int n_seq, int n_kt, int nqs, float c, int qk_norm,
+    uint32_t *__restrict__ redo, int redo_stride, const uint16_t *krows, const uint16_t *vrows) {
   constexpr int WAVES = kShortWaves, R = 64 / WAVES;   // of a lane's 64 output registers (query block, channels 32 dt .., row) a
                                              // wave adds up and stores R
   // [wave][whose registers, its own left out][group of 4][lane]; ROWS: V's rows before
@@ -1676,17 +1677,24 @@ __global__ __launch_bounds__(64 * kShortWaves) __attribute__((amdgpu_waves_per_e
     else load(vh, t0, fv[0]);
     load_k(t0 + 1, fk[1]);
     __builtin_amdgcn_sched_barrier(0);
+    // both blocks' q rows at once, but for the plain form behind a re-layout, which takes them one after the other sooner
+    // (1,130 tokens of 8 heads 13.1 us at once, 12.9)
+    constexpr bool kQAtOnce = ROWS || ONLINE || PACKED;
     u32x4 qw[2][4];
-#pragma unroll
-    for (int sub = 0; sub < 2; ++sub) {
+    auto load_q = [&](int sub) {
       const int64_t row = min(q0 + sub * 32 + ql, n - 1);
       const uint16_t *qp = q + (size_t)row * C + head * 64 + 8 * h;
 #pragma unroll
       for (int s = 0; s < 4; ++s) qw[sub][s] = *(const u32x4 *)(qp + 16 * s);
+    };
+    if constexpr (kQAtOnce) {
+      load_q(0);
+      load_q(1);
+      __builtin_amdgcn_sched_barrier(0);
     }
-    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int sub = 0; sub < 2; ++sub) {      // q as in the main kernel
+      if constexpr (!kQAtOnce) load_q(sub);
       const u32x4(&w)[4] = qw[sub];
       float ss = (sumsq8(w[0]) + sumsq8(w[1])) + (sumsq8(w[2]) + sumsq8(w[3]));
       ss += __shfl_xor(ss, 32, 64);
@@ -2850,8 +2858,8 @@ int launch_attn(const uint16_t *q, const uint16_t *k, const uint16_t *v, uint16_
     const int stride = ON ? 2 * nqb : 0;
     if (is_short)
       hipLaunchKernelGGL((rows ? k_attn_bf16_short<false, false, true> : k_attn_bf16_short<ON, PK, false>),
-                         dim3((unsigned)(nqs * heads * n_seq)), dim3(256), 0, st, q, kp, vp, k, v, out, res, n, heads, n_seq, n_kt,
-                         nqs, c, qk_norm, flags, stride);
+                         dim3((unsigned)(nqs * heads * n_seq)), dim3(256), 0, st, q, kp, vp, out, res, n, heads, n_seq, n_kt,
+                         nqs, c, qk_norm, flags, stride, k, v);
     else if (!ON && stream)
       hipLaunchKernelGGL((vrows ? res ? k_attn_bf16_stream<false, true, true> : k_attn_bf16_stream<false, false, true>
                                 : res ? k_attn_bf16_stream<PK, !PK, false> : k_attn_bf16_stream<PK, false, false>),
