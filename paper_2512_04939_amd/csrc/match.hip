@@ -599,30 +599,23 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
 // Bound by the latency of its index chain: a wave takes kFinRows consecutive rows at once, 8 lanes
 // per row reading the row's lists, and only the rows with near-equal candidates one after the
 // other with all 64 lanes (a wave per row: 32 us for 38,192 rows none of which is near-equal).
-// 8 rows and no more, because in late refreshes most rows are near-equal and want many waves.
+// 8 rows and no more, because in late refreshes most rows are near-equal and want many waves.  (Up to 256 rows by the one
+// workgroup that sorts the groups behind them, a launch less: us, matching of 2 frames of 16 x 16, C = 256, tokens that differ 19.6
+// and 18.5 at ratio 0.5, 18.4 and 20.7 at 0.9; all alike 62 and 134, 63 and 244.)
 constexpr int kFinRows = 8;
 
 // A row that goes to 64 bits is a chain of round trips, and a wave with a few of them is what the launch waits for: two candidates
 // and the src row itself are read at once, and their five sums cross the lanes side by side by DPP (one after the other,
 // by LDS shuffles: refreshes of 5 frames of 16 x 16, C = 1024, 38.1 -> 36.0 us, 12 of 37 x 37 154.4 -> 152.0, 32 435.5 ->
 // 433.3; the same bits).
-struct FinishArgs {
-  const uint16_t *x;
-  const int32_t *src_idx, *dst_idx;
-  const float *inv_src;
-  const Top2 *top2p;
-  MatchSched sched;
-  int n_src, C;
-  int32_t *anchor_of, *slot_of;
-  float *best_sim;
-};
-// rows p0 .. p0 + kFinRows - 1 by one wave (p0 < n_src)
-__device__ __forceinline__ void finish_rows(
+__global__ __launch_bounds__(256) void k_match_finish(
     const uint16_t *__restrict__ x, const int32_t *__restrict__ src_idx,
     const int32_t *__restrict__ dst_idx, const float *__restrict__ inv_src,
-    const Top2 *__restrict__ top2p, const MatchSched &sched, int n_src, int C,
-    int32_t *__restrict__ anchor_of, int32_t *slot_of, float *__restrict__ best_sim, int64_t p0) {
+    const Top2 *__restrict__ top2p, MatchSched sched, int n_src, int C,
+    int32_t *__restrict__ anchor_of, int32_t *slot_of, float *__restrict__ best_sim) {
   const int lane = threadIdx.x & 63, nch = C >> 3, sub = lane & 7;
+  const int64_t p0 = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * kFinRows;
+  if (p0 >= n_src) return;
   const int p = (int)min(p0 + (lane >> 3), (int64_t)n_src - 1);
   // the sweeps of the rows of this wave (a tile of 256 rows holds whole waves' rows)
   const int tile = (int)(p0 / kGTile);
@@ -719,11 +712,6 @@ __device__ __forceinline__ void finish_rows(
     slot_of[s] = slot_of[a];
     if (best_sim) best_sim[p] = sim;
   }
-}
-__global__ __launch_bounds__(256) void k_match_finish(FinishArgs f) {
-  const int64_t p0 = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * kFinRows;
-  if (p0 < f.n_src)
-    finish_rows(f.x, f.src_idx, f.dst_idx, f.inv_src, f.top2p, f.sched, f.n_src, f.C, f.anchor_of, f.slot_of, f.best_sim, p0);
 }
 
 // ---------------------------------------------------------------------------------
@@ -1027,15 +1015,11 @@ __global__ __launch_bounds__(256) void k_csr_finish(const uint32_t *__restrict__
 // 61.3, 6,870 63.7 and 61.5, 10,992 84.3 and 75.1, 15,114 95.6 and 78.5.  With at most 256 slots the general way is one digit
 // pass in four launches: 2,448 tokens 35.0 and 37.8, 4,320 38.3 and 38.0, 6,400 39.8 and 33.1.
 constexpr int kCsrSmall = 5120;
-// FINISH: the src rows' decisions (k_match_finish) first, in the same launch, while its 16 waves have two batches of rows each at
-// most.  Refresh of 2 frames of 16 x 16, C = 256, at ratio 0.5 (128 src rows) 31.1 -> 27.9 us, at 0.9, C = 1024 (230) 32.2 -> 31.8; 3 frames
-// (460) 31.9 and 32.5, 5 at 0.75 (768) 34.7 and 43.4.
-constexpr int kFinWithCsr = 256;
 constexpr int kCsrSteps = kCsrSmall / 1024;   // 64-element steps per wave, at most
 
-template <bool FINISH>
-__global__ __launch_bounds__(1024) void k_csr_small(const int32_t *slot_of, int N, int M, int32_t *__restrict__ group_off,
-                                                    int32_t *__restrict__ group_mem, FinishArgs f) {
+__global__ __launch_bounds__(1024) void k_csr_small(const int32_t *__restrict__ slot_of, int N, int M,
+                                                    int32_t *__restrict__ group_off,
+                                                    int32_t *__restrict__ group_mem) {
   extern __shared__ uint32_t elem[];            // [N]
   __shared__ uint32_t cnt[128 * 16];            // [digit][wave]
   __shared__ uint32_t wtot[16];
@@ -1044,11 +1028,6 @@ __global__ __launch_bounds__(1024) void k_csr_small(const int32_t *slot_of, int 
   const uint64_t below = lane == 0 ? 0ull : (~0ull >> (64 - lane));
   const int steps = (N + 1023) / 1024, b = wave * steps * 64 + lane;
   uint32_t e[kCsrSteps], rk[kCsrSteps];
-  if constexpr (FINISH) {
-    for (int64_t p0 = wave * kFinRows; p0 < f.n_src; p0 += 16 * kFinRows)
-      finish_rows(f.x, f.src_idx, f.dst_idx, f.inv_src, f.top2p, f.sched, f.n_src, f.C, f.anchor_of, f.slot_of, f.best_sim, p0);
-    __syncthreads();                            // the slots that the other waves have written are read below
-  }
 #pragma unroll
   for (int i = 0; i < kCsrSteps; ++i) {
     const int g = b + i * 64;
@@ -1160,8 +1139,6 @@ int launch_match(const uint16_t *x, const Dims &d, const litevggt_plan_t &pl,
                  const litevggt_index &ix, float *best_sim, void *ws, size_t ws_bytes, hipStream_t st) {
   MatchWs w = carve(d, pl, ws_bytes < match_ws_bytes(d, pl), (char *)ws);
   const int n_src = (int)pl.n_src, n_dst = (int)pl.n_dst;
-  FinishArgs finish{};
-  bool with_csr = false;     // the decisions are taken by the launch that sorts the groups
   if (n_src > 0) {
     if (d.C % 64 != 0 || n_dst <= 0) return LV_ERR_SHAPE;   // (64: k_match_small)
     // 128 KB ring (reused for the final merge) + per wave kInvBufs buffers of 64 inverse norms
@@ -1192,23 +1169,18 @@ int launch_match(const uint16_t *x, const Dims &d, const litevggt_plan_t &pl,
       hipLaunchKernelGGL(k_match_sim, dim3((unsigned)(per_team * kXcd)), dim3(512), lds, st, w.srcp, w.dstp, w.invd, dst_tiles,
                          sched, d.C / 16, kTeamSpin, w.team_ctr, w.top2p);
     }
-    finish = FinishArgs{x, ix.src_idx, ix.dst_idx, w.invs, w.top2p, sched, n_src, d.C, ix.anchor_of, ix.slot_of, best_sim};
-    with_csr = d.N <= kCsrSmall && n_src <= kFinWithCsr;
-    if (!with_csr) {
-      const unsigned fin = (unsigned)((n_src + 4 * kFinRows - 1) / (4 * kFinRows));
-      hipLaunchKernelGGL(k_match_finish, dim3(fin), dim3(256), 0, st, finish);
-      LV_HIP_CHECK_LAUNCH();
-    }
+    const unsigned fin = (unsigned)((n_src + 4 * kFinRows - 1) / (4 * kFinRows));
+    hipLaunchKernelGGL(k_match_finish, dim3(fin), dim3(256), 0, st, x, ix.src_idx, ix.dst_idx,
+                       w.invs, w.top2p, sched, n_src, d.C, ix.anchor_of, ix.slot_of, best_sim);
+    LV_HIP_CHECK_LAUNCH();
   }
   // CSR groups by stable radix sort of slot_of
   if (d.N <= kCsrSmall) {   // M <= N: slots fit 14 bits
     const size_t lds = align_up((size_t)d.N * sizeof(uint32_t), 16);
     static std::atomic<uint64_t> lds_done{0};
-    if (int rc = allow_dynamic_lds<kCsrSmall * sizeof(uint32_t)>((const void *)k_csr_small<false>, lds_done)) return rc;
-    static std::atomic<uint64_t> lds_done2{0};
-    if (int rc = allow_dynamic_lds<kCsrSmall * sizeof(uint32_t)>((const void *)k_csr_small<true>, lds_done2)) return rc;
-    hipLaunchKernelGGL((with_csr ? k_csr_small<true> : k_csr_small<false>), dim3(1), dim3(1024), lds, st,
-                       (const int32_t *)ix.slot_of, (int)d.N, (int)pl.M, ix.group_off, ix.group_mem, finish);
+    if (int rc = allow_dynamic_lds<kCsrSmall * sizeof(uint32_t)>((const void *)k_csr_small, lds_done)) return rc;
+    hipLaunchKernelGGL(k_csr_small, dim3(1), dim3(1024), lds, st, (const int32_t *)ix.slot_of, (int)d.N, (int)pl.M,
+                       ix.group_off, ix.group_mem);
     LV_HIP_CHECK_LAUNCH();
     return LV_OK;
   }

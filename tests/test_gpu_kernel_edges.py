@@ -1026,8 +1026,8 @@ def test_attention_stream_replays_from_a_graph(B):
 
 # ------------------------------------------------------------------------------- matching of few tokens
 # 64 x 64 row tiles: one src row, whole tiles of both, one row more; one, three and five channel batches per
-# half, sixteen; the most dst tiles that are lists (4096 dst rows) and one more, and near the most workgroups; decisions in the
-# launch that sorts the groups: 128 src rows, 256 (the most) and 258
+# half, sixteen; the most dst tiles that are lists (4096 dst rows) and one more, and near the most workgroups; 128,
+# 256 and 258 src rows
 @pytest.mark.parametrize("frames,h,w,special,ratio,dim", [(2, 1, 2, 0, 0.5, 64), (2, 8, 16, 0, 0.5, 192), (3, 8, 8, 0, 0.5, 320),
                                                           (2, 64, 63, 0, 0.016, 64), (2, 64, 64, 0, 0.016, 64), (4, 37, 37, 5, 0.9, 128),
                                                           (2, 37, 37, 5, 0.9, 1024), (30, 16, 16, 5, 0.9, 64),
