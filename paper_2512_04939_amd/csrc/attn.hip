@@ -2711,10 +2711,6 @@ static int attn_plan(AttnPlan &a, int64_t n, int heads, float scale, int attn_dt
   if (n_seq < 1 || (int64_t)heads * n_seq > 65535) return LV_ERR_SHAPE;
   if ((n_seq > 1 || res) && attn_dtype != LV_ATTN_BF16) return LV_ERR_DTYPE;
   if (attn_dtype != LV_ATTN_BF16 && attn_dtype != LV_ATTN_FP8_E4M3) return LV_ERR_DTYPE;
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess ||
-      hipDeviceGetAttribute(&a.n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
-    return LV_ERR_HIP;
   const float c = scale * 1.4426950408889634f;
   const bool f8 = attn_dtype == LV_ATTN_FP8_E4M3;
   a.n_kt = n_key_tiles(n);
@@ -2734,6 +2730,10 @@ static int attn_plan(AttnPlan &a, int64_t n, int heads, float scale, int attn_dt
   // blocks the first pass flagged (normally none: its workgroups return at once)
   a.bounded = qk_norm && (f8 ? kF8Bound : 64.25f) * c <= 64.0f;
   if (f8) return LV_OK;
+  int dev = 0;   // (not for E4M3: calls of few tokens are bound by the host, and its answer takes 0.2 us of their 20)
+  if (hipGetDevice(&dev) != hipSuccess ||
+      hipDeviceGetAttribute(&a.n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+    return LV_ERR_HIP;
   a.is_short = attn_is_short((int64_t)a.nqs * heads * n_seq, a.bounded, n_seq == 1 && heads % kXcd == 0, res || o == q, a.n_cu);
   if (!a.is_short && n_seq == 1 && !res && 2 * a.n_cu == kXcd * kSlots && ws_bytes >= attn_ws_bytes(heads, n, attn_dtype))
     a.cut = attn_cut(heads, n, a.bounded);
