@@ -315,7 +315,8 @@ __device__ __forceinline__ void var_strip(
   // output rows [r0, r1), and the grid rows that are read
   const int r0 = SEG ? (int)((int64_t)H * rs / row_segs) : 0, r1 = SEG ? (int)((int64_t)H * (rs + 1) / row_segs) : H;
   const int ib = SEG ? max(r0 - 1, 0) : 0, row_end = SEG ? min(r1 + 1, H) : H;
-  const int steps = STRIPS == 1 ? r1 + 1 - ib : (H + row_segs - 1) / row_segs + 2;   // at least r1 + 1 - ib
+  // of several strips one number, at least r1 + 1 - ib of each (a whole strip has no row ahead of it)
+  const int steps = STRIPS == 1 ? r1 + 1 - ib : (H + row_segs - 1) / row_segs + (row_segs > 1 ? 2 : 1);
   const int wave = (threadIdx.x >> 6) % kVarWaves, lane = threadIdx.x & 63;
   const int T = H * W + S;
   const uint16_t *frame = x + ((size_t)f * T + S) * C;

@@ -489,8 +489,9 @@ def test_importance_edges(B, frames, h, w, patch, dim, kind):
 
 
 # more than 1024 channels: a second pass over the channels adds to the map, with the rows of a strip in
-# segments (few frames) and whole
-@pytest.mark.parametrize("frames,h,w,dim", [(2, 9, 5, 1536), (1, 37, 6, 1088), (260, 4, 5, 1536)])
+# segments (few frames) and whole; both maps in one launch with whole strips, an odd number of them, of one and three rows
+@pytest.mark.parametrize("frames,h,w,dim", [(2, 9, 5, 1536), (1, 37, 6, 1088), (260, 4, 5, 1536), (1, 3, 36, 1088), (3, 1, 60, 1536),
+                                            (1, 2, 20, 256)])
 def test_importance_two_channel_passes(B, frames, h, w, dim):
     test_importance_edges(B, frames, h, w, 2, dim, "f32")
 
