@@ -655,7 +655,13 @@ __global__ __launch_bounds__((GemmShape<BM, BN>::kThreads * KG)) __attribute__((
   bool primed = false;   // this tile's first stages have been issued by the previous tile('s epilogue)
   bool stored = false;   // kTurns: the previous tile has ended with at least kStores stores behind its last fetch
   constexpr int kStores = FP8 && PACKED ? 2 * kB : 4 * kB;
-  const float alpha = alpha_p ? *alpha_p : 1.0f, r = FP8 && PACKED ? __uint_as_float(*out_inv) : 1.0f;
+  // (kTurns: the scalars once for all tiles, nothing waits in an epilogue; else there, a short tile's first loads come first)
+  float alpha = 1.0f, r = 1.0f;
+  auto load_scalars = [&]() {
+    if (alpha_p) alpha = *alpha_p;
+    if constexpr (FP8 && PACKED) r = __uint_as_float(*out_inv);
+  };
+  if constexpr (kTurns) load_scalars();
   int parity = 0;
   int tm = 0, tn = 0, tm2 = 0, tn2 = 0;
   for (int v = by_xcd ? (int)blockIdx.x >> 3 : (int)blockIdx.x; v < my_tiles; v += stride, parity ^= 1) {
@@ -947,6 +953,7 @@ __global__ __launch_bounds__((GemmShape<BM, BN>::kThreads * KG)) __attribute__((
   // lanes l and l + 32 trade halves (one v_permlane32_swap per register pair: the first operand's
   // lanes 32-63 against the second operand's lanes 0-31), after which lane l has channels 0-7 and
   // lane l + 32 channels 8-15 of a run of 16, 16 bytes per lane.
+  if constexpr (!kTurns) load_scalars();
   int anchor = 0;   // opaque zero: keeps the address arithmetic below inside this tile's epilogue
   asm volatile("" : "+v"(anchor));   // (hoisted out of the tile loop it would stay live through the main loop)
   if (kTurns) {
