@@ -457,15 +457,15 @@ int launch_maps(const void *images, int img_dtype, const uint16_t *x, const Dims
   const int Wi = d.W * patch, nseg = (d.W + kSeg - 1) / kSeg;
   const size_t pix = img_dtype == LV_IMG_F32 ? 4 : 1, lds = ((size_t)(patch + 2) * Wi + Wi + 8) * sizeof(float);
   const bool vec = (size_t)d.H * patch * Wi % 4 == 0 && (uintptr_t)images % (4 * pix) == 0;
-  int dev = 0, n_cu = 0;
-  if (hipGetDevice(&dev) != hipSuccess ||
-      hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
-    return LV_ERR_HIP;
   const int64_t strips = (int64_t)d.F * nseg, rows = (int64_t)d.F * d.H;
   const int row_segs = var_row_segments(strips, d.H);
   const int64_t strip_blocks = (strips * row_segs + kBothStrips - 1) / kBothStrips, row_blocks = (int64_t)align_up((size_t)rows, kXcd);
-  // (launch_grad_map has the limit of image rows)
-  if (pool != 3 || !vec || lds > 64 * 1024 || strip_blocks + row_blocks > 2 * n_cu) {
+  int dev = 0, n_cu = 0;   // (launch_grad_map has the limit of image rows)
+  const bool can = pool == 3 && vec && lds <= 64 * 1024;
+  if (can && (hipGetDevice(&dev) != hipSuccess ||
+              hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess))
+    return LV_ERR_HIP;
+  if (!can || strip_blocks + row_blocks > 2 * n_cu) {
     if (int rc = launch_grad_map(images, img_dtype, d, patch, psi_g, st)) return rc;
     return launch_var_map(x, d, pool, psi_v, st);
   }
