@@ -986,6 +986,8 @@ constexpr int kGiveWayStages = 32;   // (2,525 tokens, up to two rounds: 0.98 of
 // A sequence's last block, with at most half of its queries there, gives every wave 32 of them instead of 64 to one or two
 // waves: the block's waves do half the work, and the SIMDs that had none of it share it, us: 200 frames of 16 x 16 (5 queries
 // of 256) 190 -> 181, 50 of 28 x 37 (17) 299 -> 289, 100 of 37 x 37 (94) 874 -> 856.  The same additions in the same order.
+// Both go for calls whose output lies apart from V: in place, as the layer driver has its frame attention, a block's output
+// would take rows that another one still reads, and V is re-laid out.
 // (In the forms with packed V, whose sequences are longer, the second loop costs 20 registers in scratch.)
 
 // Eight transposing reads: the four fragments of 32 keys of V from its rows in LDS (k_attn_bf16_stream), two 8-byte

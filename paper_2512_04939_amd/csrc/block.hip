@@ -549,7 +549,7 @@ struct GemmShape {
 // half in its constants; the negative side uses erfc itself, so nothing cancels there.  The epilogue of the
 // first MLP layer evaluates it 65536 times per tile, where it is as long as an E4M3 main loop: 12 VALU instructions and
 // two transcendental ones (as v / 2 * (2 - erfc) with a select 17 and two; C = 1024, E4M3, the layer at M = 5,776 46.6 -> 39.7 us, 15,432 107 -> 99).  Against 64 bits on
-// [-12, 12] never further off than that form.  (|v| beyond 64, where the product is 0, is held there: infinity stays.)
+// [-12, 12] at most 3.3e-7 off and 7.6e-8 rms, that form 4.2e-7 and 8.1e-8 (9 % of the points are further off, 26 % closer).  (|v| beyond 64, where the product is 0, is held there: infinity stays.)
 __device__ __forceinline__ float gelu_erf(float v) {
   const float a = fminf(fabsf(v), 64.0f);
   const float t = __builtin_amdgcn_rcpf(__builtin_fmaf(0.23164189f, a, 1.0f));

@@ -110,7 +110,8 @@ __device__ __forceinline__ float ga_score(float g, float v, float glo, float gr,
 
 // Only a value that would raise the word sends an atomic (a stale read only sends one too many), and
 // one thread per workgroup does: a few thousand waves that start together all find the word at 0,
-// and their atomics on one address take longer than reading the tensor (5-10 ns each).
+// and their atomics on one address take longer than reading the tensor (5-10 ns each).  (Per wave in the E4M3 kernel with a
+// running maximum, whose waves end far apart.)
 __device__ __forceinline__ void raise_max(uint32_t *word, float m) {
   if (__float_as_uint(m) > __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
     atomicMax(word, __float_as_uint(m));

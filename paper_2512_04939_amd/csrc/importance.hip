@@ -265,17 +265,13 @@ __global__ __launch_bounds__(128) void k_var_map(const uint16_t *__restrict__ x,
 // 25 -> 9 for 2 of 16 x 16).  Whole strips are a kernel of their own (SEG false): with the bounds of a
 // segment in registers 1000 frames took 800 us, without them 760.
 // ---------------------------------------------------------------------------------
-#ifndef LV_VAR_SEG
-#define LV_VAR_SEG 4
-#endif
-constexpr int kSeg = LV_VAR_SEG;
+constexpr int kSeg = 4;                        // (wave_sum4)
 constexpr int kVarWaves = 2;                   // waves per workgroup: 512 channels each, 8 per lane
 
-// STRIPS (SEG only): strips of the workgroup, `block` STRIPS + 0, 1, ..., two waves each; they walk one number of rows.
 // Sums of four values over the 64 lanes, with DPP moves and permlane swaps only: butterflies inside the rows of 16 lanes, then rows
 // change places so that one addition serves two values, and four.  Value q ends up in all lanes of row q.  (One after the other each value's six steps
 // waited for one another, 42 idle slots in two grid rows, and a move or a lane read each: importance of 32 frames of
-// 37 x 37, C = 1024, 57.1 -> 54.1 us, 60 of 16 x 16, C = 512, 28.4 -> 26.8; 100 of 37 x 37, bound by its reads beside this, level.
+// 37 x 37, C = 1024, 54.7 -> 51.7 us, 60 of 16 x 16, C = 512, 26.9 -> 25.3, 100 of 37 x 37 138.6 -> 133.8, 1000 1213 -> 1172.
 // The pivot kept out of the fetches that do not need it, 12 % fewer instructions, loses 4 % there to the branches.)
 __device__ __forceinline__ float wave_sum4(float (&v)[4]) {
 #pragma unroll
@@ -296,6 +292,7 @@ __device__ __forceinline__ float wave_sum4(float (&v)[4]) {
   return __uint_as_float(y[0]) + __uint_as_float(y[1]);
 }
 
+// STRIPS (SEG only): strips of the workgroup, `block` STRIPS + 0, 1, ..., two waves each; they walk one number of rows.
 template <bool SEG, int STRIPS>
 __device__ __forceinline__ void var_strip(
     const uint16_t *__restrict__ x, int F, int H, int W, int S, int C, int nseg, int row_segs,

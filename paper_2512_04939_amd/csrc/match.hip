@@ -606,8 +606,8 @@ constexpr int kFinRows = 8;
 
 // A row that goes to 64 bits is a chain of round trips, and a wave with a few of them is what the launch waits for: two candidates
 // and the src row itself are read at once, and their five sums cross the lanes side by side by DPP (one after the other,
-// by LDS shuffles: refreshes of 5 frames of 16 x 16, C = 1024, 38.1 -> 36.0 us, 12 of 37 x 37 154.4 -> 152.0, 32 435.5 ->
-// 433.3; the same bits).
+// by LDS shuffles: refreshes of 5 frames of 16 x 16, C = 1024, 38.1 -> 36.0 us, 12 of 37 x 37 154.4 -> 152.0; matching of 2 frames of
+// 16 x 16 with tokens all alike, C = 256, 79 -> 62, 1024 108 -> 81, of 37 x 37 484 -> 356; the same bits).
 __global__ __launch_bounds__(256) void k_match_finish(
     const uint16_t *__restrict__ x, const int32_t *__restrict__ src_idx,
     const int32_t *__restrict__ dst_idx, const float *__restrict__ inv_src,
@@ -885,8 +885,8 @@ __global__ __launch_bounds__(256) void k_radix_scatter(const uint32_t *__restric
 // the places where its elements come to lie, and the second one finds the groups' starts as the lowest
 // place of each slot; both by integer atomics, whose order leaves no trace.
 // One refresh call, seven launches -> three: 12 frames of 37 x 37 patches 94.7 -> 90.5 us, 64 of 16 x 16
-// 79.5 -> 73.7, 100 of 28 x 37 (13,056 counters) 1226.0 -> 1221.3; above 16,384 counters, 100 of 28 x 37 under the fixed rule
-// 3308 -> 3290, C = 256 at ratio 0.5 952 -> 937, 52 of 37 x 37, C = 256 369 -> 361, 200 of 28 x 37, C = 512 (52,480) 2853 -> 2813, 200 of
+// 79.5 -> 73.7, 100 of 28 x 37 (13,056 counters) 1226.0 -> 1221.3; above 16,384 counters, 100 of 28 x 37,
+// C = 256, at ratio 0.5 952 -> 937, 52 of 37 x 37, C = 256 369 -> 361, 200 of 28 x 37, C = 512 (52,480) 2853 -> 2813, 200 of
 // 37 x 37 (68,864) level: what every workgroup reads grows with the tokens' square.
 constexpr int kMoveCounters = 65536;   // chunks x digits, at most
 

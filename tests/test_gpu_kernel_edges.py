@@ -203,13 +203,14 @@ def test_match_lists_keep_their_own_candidates(B, frames, h, w, ratio):
 
 # groups: the largest sequence one workgroup sorts, the smallest beyond it, one digit pass, a chunk of the general
 # sort that ends on a wave's last element, and one slot count above 16 bits (three digit passes); two
-# passes in three launches: whole chunks of kept tokens only, large groups of few slots, the most counters
-# that are summed in the move and one chunk more
+# passes in three launches: whole chunks of kept tokens only, large groups of few slots, 16,384 counters and a chunk
+# more, the most counters that are summed in the move (65,536) and one chunk more
 @pytest.mark.parametrize("frames,h,w,special,ratio", [(20, 15, 17, 1, 0.9), (3, 42, 40, 27, 0.5), (50, 8, 16, 0, 0.99),
                                                       (64, 15, 17, 1, 0.9), (5, 52, 63, 1, 0.5), (2, 1, 1, 0, 0.0),
                                                       (17, 32, 32, 0, 0.75), (70, 32, 32, 2, 0.0),
                                                       (17, 32, 32, 0, 0.0), (40, 20, 21, 0, 0.98), (64, 32, 32, 0, 0.5),
-                                                      (65, 32, 32, 0, 0.5), (32, 37, 37, 5, 0.9)])
+                                                      (65, 32, 32, 0, 0.5), (32, 37, 37, 5, 0.9), (256, 32, 32, 0, 0.8),
+                                                      (257, 32, 32, 0, 0.8)])
 def test_groups_edges(B, frames, h, w, special, ratio):
     import torch
     ph = B.make_params(frames, h, w, 64, 1, n_special=special, merge_ratio=ratio)
@@ -966,7 +967,8 @@ def test_attention_blocks_in_a_stream(B, frames, h, w, heads, res):
     assert torch.equal(outs[0], outs[1])
 
 
-# last blocks whose waves take 32 queries each: 127 and 128 queries (and 129, where they take 64), whole waves and one more query
+# last blocks whose waves take 32 queries each: 127 and 128 queries (and 129, where they take 64), whole waves and one more query;
+# the bits of the re-laid form (the output takes V's place), whose waves take 64
 @pytest.mark.parametrize("frames,h,w,heads", [(33, 18, 21, 8), (33, 1, 379, 8), (33, 19, 20, 8), (33, 15, 21, 8), (33, 4, 79, 8),
                                               (22, 11, 49, 8), (22, 20, 27, 8), (30, 9, 67, 6), (30, 4, 151, 6)])
 @pytest.mark.parametrize("res", [0, 1])
@@ -980,6 +982,10 @@ def test_attention_stream_narrow_last_blocks(B, frames, h, w, heads, res):
     got = torch.full_like(x, float("nan"))
     B.litevggt_frame_attn(ph, x, x, x, x if res else None, got, B.alloc_ws(B.litevggt_frame_attn_ws_bytes(ph)))
     torch.cuda.synchronize()
+    relaid = x.clone()
+    B.litevggt_frame_attn(ph, x, x, relaid, x if res else None, relaid, B.alloc_ws(B.litevggt_frame_attn_ws_bytes(ph)))
+    torch.cuda.synchronize()
+    assert torch.equal(got.view(torch.int16), relaid.view(torch.int16))
     ref = torch.cat([_attn64(f, f, f, True, heads) + (f.double() if res else 0.0) for f in x.reshape(frames, n, -1)])
     # bf16 weights and outputs: 2^-8 of a value twice, as for the other blocks
     assert float((got.double() - ref).abs().max() / ref.abs().max()) <= 2e-2
