@@ -2343,13 +2343,15 @@ __global__ __launch_bounds__(256) void k_attn_pack_fp8b(const uint16_t *__restri
                                                         int heads, int n_kt,
                                                         const uint32_t *__restrict__ amax,
                                                         u32x2 *__restrict__ kp, u32x2 *__restrict__ vp,
-                                                        uint32_t *__restrict__ flags, int n_flags) {
+                                                        uint32_t *__restrict__ flags) {
   __shared__ __attribute__((aligned(8))) uint8_t vt[kKT][72];
   const int kt = blockIdx.x, head = blockIdx.y, t = threadIdx.x;
   const int C = heads * 64;
   const int key = t >> 3, chunk = t & 7;
   const int64_t row = (int64_t)kt * kKT + key;
-  if (t == 0 && kt < n_flags) flags[(size_t)head * n_flags + kt] = 0u;   // (n_flags <= n_kt per head)
+  // two flags per 512 tokens, fewer than key tiles.  (From n: one argument more would take the others past 64 bytes, 0.2 us.)
+  const int n_flags = 2 * (int)((n + kQB - 1) / kQB);
+  if (t == 0 && kt < n_flags) flags[(size_t)head * n_flags + kt] = 0u;
   u32x4 wk = {0u, 0u, 0u, 0u}, wv = {0u, 0u, 0u, 0u};
   if (row < n) {
     wk = *(const u32x4 *)(k + (size_t)row * C + head * 64 + chunk * 8);
@@ -2797,7 +2799,7 @@ int launch_attn(const uint16_t *q, const uint16_t *k, const uint16_t *v, uint16_
     u32x2 *kpb = (u32x2 *)(a.frag + 2 * a.per), *vpb = (u32x2 *)(a.frag + 3 * a.per);
     if (bounded)
       hipLaunchKernelGGL(k_attn_pack_fp8b, dim3((unsigned)n_kt, (unsigned)heads), dim3(256), 0, st, k, v, n,
-                         heads, n_kt, amax, kpb, vpb, redo, 2 * nqb);
+                         heads, n_kt, amax, kpb, vpb, redo);
     else
       hipLaunchKernelGGL(k_attn_pack_fp8, dim3((unsigned)n_kt, (unsigned)heads), dim3(256), 0, st, k,
                          v, n, heads, n_kt, qk_norm, amax, kp, vp);
