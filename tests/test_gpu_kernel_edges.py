@@ -461,6 +461,39 @@ def test_block_attention_left_to_the_second_pass(B, n, far, linear):
         assert flags.ne(0).nonzero().tolist() == [[h, b] for h in range(4) for b in sorted({f // 256 for f in far})]
 
 
+# a captured block as it is served in FP8: every replay clears its words, takes its scales from the history and records into it,
+# also after eager calls in the same scratch
+@pytest.mark.parametrize("attn", ["fp8", "bf16"])
+def test_block_replays_from_a_graph(B, attn):
+    import torch
+    n, dim = 700, 256
+    t = {k: torch.from_numpy(v).cuda() for k, v in synth.block_weights(dim, seed=5).items()}
+    t = {k: v.to(torch.bfloat16) if k.startswith("w_") else v for k, v in t.items()}
+    states = torch.zeros(3, B.FP8_STATE_BYTES, dtype=torch.uint8, device="cuda")
+    bws = [B.block_weights(t, B.LINEAR_FP8_E4M3, B.FP8_DELAYED, s) for s in states]
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n)
+    z = torch.randn(n, dim, generator=g, device="cuda").to(torch.bfloat16)
+    ph = B.make_params(1, 1, 1, dim, 4, n_special=0, qk_norm=1, attn_dtype=B.ATTN_FP8_E4M3 if attn == "fp8" else B.ATTN_BF16)
+    ws, got, other = B.alloc_ws(B.litevggt_global_block_ws_bytes(ph, n)), torch.empty_like(z), torch.empty_like(z)
+    B.litevggt_global_block(ph, n, z, bws[2], other, ws)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        B.litevggt_global_block(ph, n, z, bws[0], got, ws)
+    for _ in range(4):
+        want = torch.full_like(z, float("nan"))
+        B.litevggt_global_block(ph, n, z, bws[1], want, ws)
+        got.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(got, want) and torch.equal(states[0], states[1])
+        z.mul_(1.5)
+        B.litevggt_global_block(ph, n, z, bws[2], other, ws)
+        ws.fill_(0x7f)
+        torch.cuda.synchronize()
+
+
 # ------------------------------------------------------------------------------- importance
 # pixel rows that are no multiple of 4 pixels, planes that are none (one pixel at a time), images
 # behind an unaligned address, a single patch row and column, pixel rows wider than a workgroup,
