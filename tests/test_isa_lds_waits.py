@@ -128,11 +128,11 @@ READ2 = ("ds_read_b128 v[0:3], v8", "ds_read_b128 v[4:7], v8 offset:1024")
     (READ2 + ("ds_write_b32 v9, v10", "s_waitcnt lgkmcnt(1)", "v_mov_b32_e32 v9, v4", "s_endpgm"), []),
     (("ds_bpermute_b32 v1, v2, v3", "v_mov_b32_e32 v9, v1", "s_endpgm"), [1]),
 ])
-def test_checker_on_straight_code(lines, bad):
+def test_early_uses_on_straight_code(lines, bad):
     assert early_uses(_code(*lines)) == bad
 
 
-def test_checker_follows_branches():
+def test_early_uses_follows_branches():
     code = _code("v_mov_b32_e32 v9, v0", "ds_read_b128 v[0:3], v8", "s_cbranch_scc1 x", "s_waitcnt lgkmcnt(0)", "s_endpgm")
     code[2] = (*code[2][:3], 0)                                   # back to the start without a wait
     assert early_uses(code) == [0, 1]
